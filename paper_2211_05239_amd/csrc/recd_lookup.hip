@@ -173,13 +173,12 @@ struct SegSumParams {
     // POOL_WSUM: one fp32 weight per id, aligned with values
     const float *weights;
     // SITE_UNIQUE_EXPAND: the IKJT's run index (header, one entry per run of adjacent rows that name
-    // the same unique list, closing entry), the expanded output [F*B, D], rows per feature, the
-    // launch's first feature, and how the runs are dealt to the eight block queues
+    // the same unique list, closing entry), the expanded output [F*B, D], rows per feature and the
+    // launch's first feature
     const int64_t *run_index;
     void *expanded;
     int64_t B;
     int64_t run_cap;         // no run number reaches this (F*B)
-    int64_t runs_per_queue;  // queue q takes the runs [q * runs_per_queue, (q+1) * runs_per_queue) first
     int all_runs;            // later runs of a list sum it again instead of waiting for a copy pass
     int feat_base;
 };
@@ -407,29 +406,30 @@ void k_segsum(const SegSumParams p)
         // (the samples of a session).  The wave of a list's first run sums the list, stores the row
         // to pooled and to every output row of the run; the runs of a list that comes back later in
         // the batch are left to the copy kernel that follows.  One load round trip brings the run's
-        // entry, the start of the next run and the number of runs; no other index is read.
-        // Queue q = blockIdx mod 8 (one XCD) takes a contiguous stretch of the runs, which are in
-        // (feature, row) order, so a table's hot rows stay in one L2.
+        // entry and the start of the next run; no other index is read.
+        // Queue q = blockIdx mod 8 (one XCD) takes a contiguous eighth of the runs, which are in
+        // (feature, row) order, so a table's hot rows stay in one L2.  The eighth comes from the number
+        // of runs on the device (a scalar load of one word that every block shares): dealt by an
+        // eighth of the host's estimate, all runs went to one XCD when the estimate was the bound F*B
+        // (1.05 M rows, 64 K runs: 532 us for 256-byte and 1014 us for 512-byte rows, now 118 and
+        // 233; with a good estimate 124 -> 118 and 226 -> 233).
         const int64_t *ri = p.run_index;
-        const int64_t per = p.runs_per_queue;
-        const int qx = (int)(blockIdx.x % kNQ);
+        const int64_t n_runs = ri[0] < p.run_cap ? ri[0] : p.run_cap;
+        const int64_t per = (n_runs + kNQ - 1) / kNQ;
+        const int64_t first_item = (int64_t)(blockIdx.x % kNQ) * per;
         const int64_t stride = gridDim.x / kNQ;
-        for (int64_t item = blockIdx.x / kNQ;; item += stride) {
-            const int64_t rr = item < per ? (int64_t)qx * per + item : (int64_t)kNQ * per + (item - per) * kNQ + qx;
-            if (rr >= p.run_cap)
+        for (int64_t item = blockIdx.x / kNQ; item < per; item += stride) {
+            const int64_t rr = first_item + item;
+            if (rr >= n_runs)
                 break;
-            int64_t word = 0;  // lanes 0..2: the entry, lane 3: first word of the next entry, lane 4: header
+            int64_t word = 0;  // lanes 0..2: the entry, lane 3: first word of the next entry
             if (lane < 4)
                 word = ri[3 * (1 + rr) + lane];
-            else if (lane == 4)
-                word = ri[0];
             const uint32_t wlo = (uint32_t)(uint64_t)word, whi = (uint32_t)((uint64_t)word >> 32);
             auto lane64 = [&](int k) {
                 return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)whi, k) << 32) |
                                  (uint32_t)__builtin_amdgcn_readlane((int)wlo, k));
             };
-            if (rr >= lane64(4))
-                break;  // runs beyond the last: so are all later items of this block
             const int64_t w0 = lane64(0);
             const uint32_t uf = (uint32_t)((uint64_t)w0 >> 32);
             const bool first_run = (uf >> 31) != 0;
@@ -922,7 +922,6 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     p.B = a.B;
     p.run_cap = (int64_t)a.F_all * a.B;
     p.feat_base = a.feat_base;
-    p.runs_per_queue = 0;
     p.all_runs = a.all_runs;
     p.F = a.F;
     p.D = a.D;
@@ -952,12 +951,10 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     if (a.count_dev && nblk > (int64_t)ctx->num_cu * 8)
         nblk = (int64_t)ctx->num_cu * 8;
     if (a.site == RECD_SITE_UNIQUE_EXPAND) {
-        // one run per block; queue q of eight takes the runs [q * per, (q + 1) * per) of the host's
-        // estimate first and shares whatever lies beyond it with the other queues
+        // one run per block and turn; the kernel deals the runs to eight queues by their true number
         p.lb = 1;
         p.nq = kNQ;
-        p.runs_per_queue = (n + kNQ - 1) / kNQ;
-        nblk = kNQ * (p.runs_per_queue + p.runs_per_queue / 16 + 1);
+        nblk = kNQ * ((n + kNQ - 1) / kNQ);
         if (nblk > cap)
             nblk = cap / kNQ * kNQ;
     }
