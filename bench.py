@@ -69,9 +69,8 @@ def parse_args():
                     help="also time the partial IKJT path on the workload with this probability of a "
                          "sample's lists shifting by one id within a session (0 = skip)")
     ap.add_argument("--plan-from-runs", dest="run_plan", action="store_true",
-                    help="the backward's plan sorts the batch's runs (recd_build_ikjt_runs + "
-                         "recd_backward_plan_runs) instead of all F*B rows by unique list (recd_build_ikjt + "
-                         "recd_backward_plan); measured a few microseconds slower per step at cfg5")
+                    help="plan the backward through recd_build_ikjt_runs + recd_backward_plan_runs (the same plan) "
+                         "instead of recd_build_ikjt + recd_backward_plan")
     ap.add_argument("--one-call-backward", dest="planned", action="store_false",
                     help="run the backward as one call after the expand instead of plan (next to the forward "
                          "calls) + apply")

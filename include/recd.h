@@ -19,7 +19,7 @@
  *   16-19. per-id weights: builder, unique and KJT lookups, backward
  *   20. backward of the max-pooled lookup   21, 22. the backward in two halves (plan / apply)
  *   23, 24. run index of a batch (adjacent rows holding one list)   25. lookup and expand in one pass
- *   26. the backward's plan from the run index
+ *   26. the backward's plan of a batch with a run index
  *
  * General rules
  *   - Every array argument marked "device" is a pointer into GPU memory owned by the caller and
@@ -434,10 +434,10 @@ recd_status recd_last_ikjt_run_count(recd_ctx *ctx, int64_t *host_runs);
 
 /* 21, 22. Call 5 in two halves.  What the backward does before it touches a gradient (keys, the two
  *    stable sorts, the numbering of the segments, touched_rows and feat_roff) depends on the IKJT
- *    alone.  recd_backward_plan enqueues that half on the context's two side streams and returns; if
- *    inverse and u_values are the outputs of the context's most recent call 1 / 16, the side streams
- *    start where that build ended, so the plan runs next to calls 2 and 3 enqueued meanwhile on the
- *    context's stream; otherwise they start at the stream's current position.
+ *    alone.  recd_backward_plan enqueues that half on the context's side stream and returns; if
+ *    inverse and u_values are the outputs of the context's most recent call 1 / 16, the side stream
+ *    starts where that build ended, so the plan runs next to calls 2 and 3 enqueued meanwhile on the
+ *    context's stream; otherwise it starts at the stream's current position.
  *    recd_backward_apply makes the stream wait for the plan and runs the two segment sums (and the
  *    optimizer) exactly as call 5 / call 15 would: same kernels, same results bit for bit.
  *    Between the two calls the context's workspace holds the plan: no other call that uses the
@@ -450,10 +450,9 @@ recd_status recd_backward_plan(recd_ctx *ctx, int F, int64_t B, int D, const int
                                const int64_t *feat_uoff, const int64_t *u_values,
                                const int64_t *u_offsets, const int64_t *rows, int64_t U_cap,
                                int64_t M_cap, int64_t *touched_rows, int64_t *feat_roff);
-/* 26. Call 21 for a batch with a run index (call 23 / 24): the first grouping (rows by unique list)
- *    sorts the runs, of which a session-clustered batch has about as many as unique lists, instead
- *    of all F*B rows, and writes the sorted runs out as the row list the full sort would have given:
- *    the plan is the same plan, recd_backward_apply and its results are unchanged bit for bit.
+/* 26. Call 21 for a batch with a run index (call 23 / 24): the same plan and the same results bit for
+ *    bit.  (The grouping reads `inverse`; grouping the runs instead of the rows takes fewer keys but
+ *    more launches and was not faster.)
  *    run_index: device, must describe `inverse`.  runs_cap: host upper bound of the number of runs
  *    (recd_last_ikjt_run_count gives the exact value; F*B always bounds it; 0 = F*B); if it is too
  *    small, recd_backward_apply with host_R reports RECD_ECAPACITY.  All else as in call 21. */

@@ -3,537 +3,15 @@
 //   step A  g_u[u,:] = sum_{b : inverse[f,b] = u} grad_out[f,b,:]            (b ascending)
 //   step B  G_f[r,:] = sum_{j : u_values[j] = r} g_u[list of j,:]            (j ascending)
 // Each step is "group the contributions by destination, then sum every group in a fixed order":
-// a stable least-significant-digit radix sort of (destination key, source row) pairs puts equal
-// destinations next to each other with their sources still ascending, head flags + a scan number
-// the groups, and the segmented gather-sum kernel of the forward pass adds each group's rows.
-// There are no floating-point atomics, so two runs give bit-identical gradients.
-//
-// Radix sort pass (digits of up to 9 bits): per-tile digit histograms -> one block per digit scans its
-// row of tile counts -> scatter (which first scans the digit totals itself).  Inside a tile every
-// wave owns a contiguous run of keys and walks it 64 keys at a time: ballots tell each lane which
-// lanes hold its digit (its rank among them), a per-wave running digit count in LDS gives the rank
-// among the wave's earlier keys, and a prefix over the four waves completes the stable rank.
+// recd_group.hip puts equal destinations next to each other with their sources still ascending and
+// numbers the groups, and a segmented gather-sum adds each group's rows.  There are no
+// floating-point atomics, so two runs give bit-identical gradients.
 #include "recd_internal.h"
 
 #include <algorithm>
 #include <type_traits>
 
 namespace {
-
-constexpr int kSortThreads = 256;
-constexpr int kIPT = 8;                       // keys per thread in a tile
-constexpr int kTile = kSortThreads * kIPT;    // keys per tile
-constexpr int kRadixMax = 512;                // digits of up to 9 bits
-constexpr int kScanItems = 4;                 // items per thread in the generic scan
-constexpr int kScanTile = 256 * kScanItems;
-
-// ---------------------------------------------------------------- block-wide exclusive scan (uint32)
-__device__ __forceinline__ uint32_t block_excl_scan_u32(uint32_t v, uint32_t &total)
-{
-    __shared__ uint32_t s_w[16];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t x = __shfl_up(inc, d);
-        if (lane >= d)
-            inc += x;
-    }
-    __syncthreads();
-    if (lane == 63)
-        s_w[w] = inc;
-    __syncthreads();
-    uint32_t off = 0;
-    total = 0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); i++) {
-        if (i < w)
-            off += s_w[i];
-        total += s_w[i];
-    }
-    return off + inc - v;
-}
-
-// n may live on the device (n_dev != nullptr) or be given directly
-__device__ __forceinline__ int64_t count_of(const int64_t *n_dev, int64_t n_host)
-{
-    return n_dev ? *n_dev : n_host;
-}
-
-__global__ __launch_bounds__(1024) void k_scan_small(uint32_t *a, int64_t n)
-{
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < n; base += 1024) {
-        const int64_t i = base + threadIdx.x;
-        const uint32_t v = i < n ? a[i] : 0;
-        uint32_t total;
-        const uint32_t e = block_excl_scan_u32(v, total);
-        if (i < n)
-            a[i] = carry + e;
-        carry += total;
-    }
-}
-
-// ---------------------------------------------------------------- stable LSD radix sort of pairs
-template <typename KeyT>
-__global__ __launch_bounds__(kSortThreads) void k_sort_hist(const KeyT *__restrict__ keys,
-                                                            const int64_t *n_dev, int64_t n_host,
-                                                            int shift, int dbits,
-                                                            uint32_t *__restrict__ hist, int ntiles)
-{
-    __shared__ uint32_t s_h[kRadixMax];
-    // every XCD takes a contiguous eighth of the tiles (see k_sort_scatter): the counters that
-    // neighbouring tiles write lie next to each other in a digit's row
-    const int tiles_per_xcd = (ntiles + 7) / 8;
-    const int tile = (int)(blockIdx.x % 8) * tiles_per_xcd + (int)(blockIdx.x / 8);
-    if (tile >= ntiles)
-        return;
-    const uint32_t radix = 1u << dbits;
-    for (uint32_t d = threadIdx.x; d < radix; d += kSortThreads)
-        s_h[d] = 0;
-    __syncthreads();
-    const int64_t n = count_of(n_dev, n_host);
-    const int64_t base = (int64_t)tile * kTile;
-#pragma unroll
-    for (int k = 0; k < kIPT; k++) {
-        const int64_t i = base + k * kSortThreads + threadIdx.x;
-        if (i < n)
-            atomicAdd(&s_h[(uint32_t)(keys[i] >> shift) & (radix - 1)], 1u);
-    }
-    __syncthreads();
-    for (uint32_t d = threadIdx.x; d < radix; d += kSortThreads)
-        hist[(int64_t)d * ntiles + tile] = s_h[d];
-}
-
-// one block per digit: in-place exclusive scan of the digit's row of tile counts; row total out
-__global__ __launch_bounds__(256) void k_sort_rowscan(uint32_t *__restrict__ hist, int ntiles,
-                                                      uint32_t *__restrict__ digit_total)
-{
-    uint32_t *row = hist + (int64_t)blockIdx.x * ntiles;
-    uint32_t carry = 0;
-    for (int base = 0; base < ntiles; base += 256) {
-        const int i = base + threadIdx.x;
-        const uint32_t v = i < ntiles ? row[i] : 0;
-        uint32_t total;
-        const uint32_t e = block_excl_scan_u32(v, total);
-        if (i < ntiles)
-            row[i] = carry + e;
-        carry += total;
-    }
-    if (threadIdx.x == 0)
-        digit_total[blockIdx.x] = carry;
-}
-
-template <typename KeyT>
-__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
-    const KeyT *__restrict__ kin, const uint32_t *__restrict__ pin, KeyT *__restrict__ kout,
-    uint32_t *__restrict__ pout, const int64_t *n_dev, int64_t n_host, int shift, int dbits,
-    const uint32_t *__restrict__ hist_scanned, const uint32_t *__restrict__ digit_total, int ntiles)
-{
-    constexpr int W = kSortThreads / 64;
-    constexpr int kPerWave = 64 * kIPT;  // contiguous keys of one wave
-    __shared__ uint32_t s_run[W][kRadixMax];  // per wave: keys seen so far per digit
-    __shared__ uint32_t s_base[kRadixMax];    // where this tile's keys of a digit start in the output
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const uint32_t radix = 1u << dbits;
-    const int64_t n = count_of(n_dev, n_host);
-    // Blocks go to the XCDs in turn; every XCD takes a contiguous eighth of the tiles, so that the
-    // short runs that neighbouring tiles append to one digit's output meet in one L2 and leave it
-    // as whole lines.
-    const int tiles_per_xcd = (ntiles + 7) / 8;
-    const int tile = (int)(blockIdx.x % 8) * tiles_per_xcd + (int)(blockIdx.x / 8);
-    const int64_t base = (int64_t)tile * kTile;
-    if (tile >= ntiles || base >= n)
-        return;  // whole block: nothing in this tile
-    // digit bases = exclusive scan of the digit totals (two digits per thread), plus this tile's
-    // offset inside the digit
-    {
-        const uint32_t d0 = 2 * tid, d1 = 2 * tid + 1;
-        const uint32_t t0 = d0 < radix ? digit_total[d0] : 0, t1 = d1 < radix ? digit_total[d1] : 0;
-        uint32_t total;
-        const uint32_t e = block_excl_scan_u32(t0 + t1, total);
-        if (d0 < radix)
-            s_base[d0] = e + hist_scanned[(int64_t)d0 * ntiles + tile];
-        if (d1 < radix)
-            s_base[d1] = e + t0 + hist_scanned[(int64_t)d1 * ntiles + tile];
-    }
-    for (int i = tid; i < W * kRadixMax; i += kSortThreads)
-        (&s_run[0][0])[i] = 0;
-    __syncthreads();
-
-    KeyT key[kIPT];
-    uint32_t rank[kIPT];
-    const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    const int64_t wbase = base + (int64_t)w * kPerWave;
-#pragma unroll
-    for (int k = 0; k < kIPT; k++) {
-        const int64_t i = wbase + k * 64 + lane;
-        const bool valid = i < n;
-        key[k] = valid ? kin[i] : (KeyT)0;
-        const uint32_t d = (uint32_t)(key[k] >> shift) & (radix - 1);
-        uint64_t mask = __ballot(valid);
-#pragma unroll
-        for (int bit = 0; bit < 9; bit++) {
-            if (bit < dbits) {  // uniform
-                const bool one = (d >> bit) & 1u;
-                const uint64_t bal = __ballot(one);
-                mask &= one ? bal : ~bal;
-            }
-        }
-        const uint32_t in_round = (uint32_t)__popcll(mask & lt_mask);
-        // keys of this digit in the wave's earlier rounds; the first lane of each digit then adds
-        // this round's count (same wave: the read above is complete before the write is issued)
-        const uint32_t before = valid ? s_run[w][d] : 0;
-        __builtin_amdgcn_wave_barrier();
-        if (valid && in_round == 0)
-            s_run[w][d] = before + (uint32_t)__popcll(mask);
-        __builtin_amdgcn_wave_barrier();
-        rank[k] = before + in_round;
-    }
-    __syncthreads();
-    // s_run[w][d] now holds wave w's count of digit d: exclusive prefix over the waves
-    for (uint32_t d = tid; d < radix; d += kSortThreads) {
-        uint32_t run = 0;
-#pragma unroll
-        for (int ww = 0; ww < W; ww++) {
-            const uint32_t c = s_run[ww][d];
-            s_run[ww][d] = run;
-            run += c;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kIPT; k++) {
-        const int64_t i = wbase + k * 64 + lane;
-        if (i < n) {
-            const uint32_t d = (uint32_t)(key[k] >> shift) & (radix - 1);
-            const int64_t dst = (int64_t)s_base[d] + s_run[w][d] + rank[k];
-            kout[dst] = key[k];
-            pout[dst] = pin[i];
-        }
-    }
-}
-
-// Sorts (keys, pay) by the low `bits` bits of the key; returns through *kres/*pres which of the two
-// buffer pairs holds the result.
-template <typename KeyT>
-recd_status radix_sort_pairs(recd_ctx *ctx, hipStream_t st, KeyT *k0, uint32_t *p0, KeyT *k1,
-                             uint32_t *p1, const int64_t *n_dev, int64_t n_cap, int bits,
-                             uint32_t *hist, uint32_t *bsum, KeyT **kres, uint32_t **pres)
-{
-    const int ntiles = (int)((n_cap + kTile - 1) / kTile);
-    KeyT *ka = k0, *kb = k1;
-    uint32_t *pa = p0, *pb = p1;
-    // fewest passes with digits of at most 9 bits, digits as even as possible
-    const int passes = (bits + 8) / 9;
-    const int dbits = passes > 0 ? (bits + passes - 1) / passes : 0;
-    for (int shift = 0; shift < bits && ntiles > 0; shift += dbits) {
-        hipLaunchKernelGGL((k_sort_hist<KeyT>), dim3(8 * ((ntiles + 7) / 8)), dim3(kSortThreads), 0, st, ka, n_dev,
-                           n_cap, shift, dbits, hist, ntiles);
-        hipLaunchKernelGGL(k_sort_rowscan, dim3(1u << dbits), dim3(256), 0, st, hist, ntiles, bsum);
-        hipLaunchKernelGGL((k_sort_scatter<KeyT>), dim3(8 * ((ntiles + 7) / 8)), dim3(kSortThreads), 0, st, ka, pa, kb,
-                           pb, n_dev, n_cap, shift, dbits, hist, bsum, ntiles);
-        KeyT *tk = ka; ka = kb; kb = tk;
-        uint32_t *tp = pa; pa = pb; pb = tp;
-    }
-    RECD_HIP(ctx, hipGetLastError());
-    *kres = ka;
-    *pres = pa;
-    return RECD_OK;
-}
-
-// ---------------------------------------------------------------- keys
-// step A: destination = global unique-list index, source = row (f,b) of grad_out
-__global__ void k_keys_rows(const int32_t *__restrict__ inverse, const int64_t *__restrict__ feat_uoff,
-                            int64_t B, int64_t n_lists, uint32_t *__restrict__ keys,
-                            uint32_t *__restrict__ pay, int64_t *n_out)
-{
-    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (l == 0) {
-        n_out[0] = n_lists;
-        n_out[1] = 0;
-    }
-    if (l < n_lists) {
-        keys[l] = (uint32_t)(feat_uoff[l / B] + inverse[l]);
-        pay[l] = (uint32_t)l;
-    }
-}
-
-// step B: destination = (feature, table row), source = unique list holding position j
-template <typename KeyT, int SG>
-__global__ __launch_bounds__(256) void k_keys_ids(const int64_t *__restrict__ u_values,
-                                                  const int64_t *__restrict__ u_offsets,
-                                                  const int64_t *__restrict__ feat_uoff, int F,
-                                                  int row_bits, int64_t lists_cap, int64_t M_cap,
-                                                  KeyT *__restrict__ keys, uint32_t *__restrict__ pay,
-                                                  int64_t *n_out, int pay_positions,
-                                                  uint32_t *__restrict__ pos_list = nullptr)
-{
-    const int s = threadIdx.x % SG;
-    const int per_block = blockDim.x / SG;
-    int64_t U = feat_uoff[F];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        // never write past the caller's capacity; n_out[1] tells the host that M_cap was too small
-        const int64_t M = u_offsets[U];
-        n_out[0] = M < M_cap ? M : M_cap;
-        n_out[1] = M > M_cap ? 1 : 0;
-    }
-    if (U > lists_cap)
-        U = lists_cap;
-    // the grid is sized by the caller's bound on U and strides, so any bound gives the same keys
-    for (int64_t u = (int64_t)blockIdx.x * per_block + threadIdx.x / SG; u < U; u += (int64_t)gridDim.x * per_block) {
-        int lo = 0, hi = F;  // feature of u: feat_uoff[f] <= u < feat_uoff[f+1]
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (feat_uoff[mid] <= u)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        const KeyT fkey = (KeyT)lo << row_bits;
-        const int64_t j0 = u_offsets[u];
-        const int64_t j1 = u_offsets[u + 1] < M_cap ? u_offsets[u + 1] : M_cap;
-        for (int64_t j = j0 + s; j < j1; j += SG) {
-            keys[j] = fkey | (KeyT)u_values[j];
-            pay[j] = pay_positions ? (uint32_t)j : (uint32_t)u;  // source row of the later sum: g_emb[j] or g_u[u]
-            if (pos_list)
-                pos_list[j] = (uint32_t)u;
-        }
-    }
-}
-
-// Blocks of k_keys_ids for a caller's bound on U (at least one; never more than the lists there are).
-static unsigned keys_ids_blocks(int64_t U_cap, int64_t n_lists, int SG, int block)
-{
-    int64_t lists = U_cap < n_lists ? U_cap : n_lists;
-    if (lists < 1)
-        lists = 1;
-    const int per_block = block / SG;
-    return (unsigned)((lists + per_block - 1) / per_block);
-}
-
-// Weighted lookup: the sort carried the position j of every entry.  Replace it by the entry's
-// source row (the unique list of j) and fetch the entry's weight, both in sorted order, so that the
-// segment sums read them as streams.
-__global__ __launch_bounds__(256) void k_weight_payload(uint32_t *__restrict__ pay,
-                                                        const uint32_t *__restrict__ pos_list,
-                                                        const float *__restrict__ u_weights,
-                                                        const int64_t *__restrict__ n_dev,
-                                                        float *__restrict__ pay_w)
-{
-    const int64_t n = *n_dev;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t j = pay[i];
-        pay_w[i] = u_weights[j];
-        pay[i] = pos_list[j];
-    }
-}
-
-// ---------------------------------------------------------------- step A from the batch's runs
-// With session-clustered batches the rows that name one unique list come in runs of adjacent rows
-// (the run index of the builder).  Grouping the rows by unique list then only needs the runs: keys =
-// unique list of every run, payload = run number, the same stable sort (runs of a list stay in row
-// order), and an expansion of the sorted runs into the row list that the sort of all F*B rows would
-// have produced - the same rows in the same order, so the segment sums that follow are unchanged.
-__global__ __launch_bounds__(256) void k_run_keys(const int64_t *__restrict__ run_index, int64_t runs_cap,
-                                                  uint32_t *__restrict__ keys, uint32_t *__restrict__ pay,
-                                                  int64_t *n_out)
-{
-    const int64_t all = run_index[0];
-    const int64_t n = all < runs_cap ? all : runs_cap;
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r == 0) {
-        n_out[0] = n;
-        n_out[1] = all > runs_cap ? 1 : 0;  // the caller's bound on the runs was too small
-    }
-    if (r < n) {
-        keys[r] = (uint32_t)((uint64_t)run_index[3 * (1 + r)] >> 32) & 0x7fffffffu;
-        pay[r] = (uint32_t)r;
-    }
-}
-
-// Sorted runs (ks = unique list, ps = run number).  EMIT = false: per tile, the number of lists that
-// start in it and the rows of its runs.  EMIT = true, with both tile arrays scanned: seg_start of
-// every list (in rows), list_off = {0, lists}, and the rows of every run written out in order.
-template <bool EMIT>
-__global__ __launch_bounds__(256) void k_run_rows(const uint32_t *__restrict__ ks, const uint32_t *__restrict__ ps,
-                                                  const int64_t *__restrict__ run_index,
-                                                  const int64_t *__restrict__ n_dev,
-                                                  uint32_t *__restrict__ tile_heads,
-                                                  uint32_t *__restrict__ tile_rows,
-                                                  int64_t *__restrict__ seg_start,
-                                                  int64_t *__restrict__ list_off, uint32_t *__restrict__ rows_out,
-                                                  int64_t *long_count)
-{
-    const int64_t n = *n_dev;
-    if (EMIT && blockIdx.x == 0 && threadIdx.x == 0) {
-        long_count[0] = 0;
-        long_count[1] = 0;
-        if (n == 0) {
-            seg_start[0] = 0;
-            list_off[0] = 0;
-            list_off[1] = 0;
-        }
-    }
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    uint32_t prev = (base > 0 && base <= n) ? ks[base - 1] : 0u;
-    uint32_t head[kScanItems], row0[kScanItems], len[kScanItems];
-    uint32_t hs = 0, rs = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-        const int64_t i = base + k;
-        head[k] = 0;
-        row0[k] = 0;
-        len[k] = 0;
-        if (i < n) {
-            const uint32_t key = ks[i];
-            const int64_t r = ps[i];
-            head[k] = (i == 0 || key != prev) ? 1u : 0u;
-            row0[k] = (uint32_t)(uint64_t)run_index[3 * (1 + r)];
-            len[k] = (uint32_t)(uint64_t)run_index[3 * (2 + r)] - row0[k];
-            prev = key;
-        }
-        hs += head[k];
-        rs += len[k];
-    }
-    uint32_t th, tr;
-    const uint32_t eh = block_excl_scan_u32(hs, th);
-    const uint32_t er = block_excl_scan_u32(rs, tr);
-    if (!EMIT) {
-        if (threadIdx.x == 0) {
-            tile_heads[blockIdx.x] = th;
-            tile_rows[blockIdx.x] = tr;
-        }
-        return;
-    }
-    int64_t h = (int64_t)tile_heads[blockIdx.x] + eh;  // lists that start before this thread's runs
-    int64_t at = (int64_t)tile_rows[blockIdx.x] + er;  // rows before them
-#pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-        const int64_t i = base + k;
-        if (i < n) {
-            if (head[k])
-                seg_start[h] = at;
-            for (uint32_t t = 0; t < len[k]; t++)
-                rows_out[at + t] = row0[k] + t;
-            h += head[k];
-            at += len[k];
-            if (i == n - 1) {
-                seg_start[h] = at;
-                list_off[0] = 0;
-                list_off[1] = h;
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------- segments of equal keys
-// A head is an element whose key differs from its predecessor's (or the first element).  Numbering
-// the heads is an exclusive scan of the head flags; the flags are recomputed from the keys where
-// they are needed instead of being stored: k_head_count (heads per tile) -> k_scan_small (tile
-// offsets) -> k_segments (segment number of every head, and what hangs on it).
-template <typename KeyT>
-__global__ __launch_bounds__(256) void k_head_count(const KeyT *__restrict__ keys, const int64_t *n_dev,
-                                                    uint32_t *__restrict__ bsum, int64_t *long_count)
-{
-    const int64_t n = *n_dev;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        long_count[0] = 0;
-        long_count[1] = 0;
-    }
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    KeyT prev = (base > 0 && base <= n) ? keys[base - 1] : (KeyT)0;
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-        const int64_t i = base + k;
-        if (i < n) {
-            const KeyT key = keys[i];
-            s += (i == 0 || key != prev) ? 1u : 0u;
-            prev = key;
-        }
-    }
-    uint32_t total;
-    block_excl_scan_u32(s, total);
-    if (threadIdx.x == 0)
-        bsum[blockIdx.x] = total;
-}
-
-// bsum holds the exclusive scan of the per-tile head counts.  Heads record where their segment
-// starts; the last element closes the list (seg_start[R] = n, list_off = {0, R}).  With
-// row_bits >= 0 the key is (feature, row): also emit the row ids, the feature of every segment and
-// the per-feature prefix of distinct-row counts.
-template <typename KeyT>
-__global__ __launch_bounds__(256) void k_segments(const KeyT *__restrict__ keys, const int64_t *n_dev,
-                                                  const uint32_t *__restrict__ bsum,
-                                                  int64_t *__restrict__ seg_start,
-                                                  int64_t *__restrict__ list_off, int row_bits, int F,
-                                                  int64_t *__restrict__ touched_rows,
-                                                  int64_t *__restrict__ feat_roff,
-                                                  int32_t *__restrict__ seg_feat)
-{
-    const int64_t n = *n_dev;
-    if (n == 0) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            seg_start[0] = 0;
-            list_off[0] = 0;
-            list_off[1] = 0;
-            if (row_bits >= 0)
-                for (int f = 0; f <= F; f++)
-                    feat_roff[f] = 0;
-        }
-        return;
-    }
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    const KeyT before = (base > 0 && base <= n) ? keys[base - 1] : (KeyT)0;
-    KeyT key[kScanItems];
-    uint32_t s = 0;
-    {
-        KeyT prev = before;
-#pragma unroll
-        for (int k = 0; k < kScanItems; k++) {
-            const int64_t i = base + k;
-            key[k] = i < n ? keys[i] : (KeyT)0;
-            if (i < n)
-                s += (i == 0 || key[k] != prev) ? 1u : 0u;
-            prev = key[k];
-        }
-    }
-    uint32_t total;
-    int64_t sidx = (int64_t)bsum[blockIdx.x] + block_excl_scan_u32(s, total);  // heads before `base`
-    KeyT prev = before;
-#pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-        const int64_t i = base + k;
-        if (i < n) {
-            const bool head = i == 0 || key[k] != prev;
-            if (head) {
-                seg_start[sidx] = i;
-                if (row_bits >= 0) {
-                    touched_rows[sidx] = (int64_t)(key[k] & (((KeyT)1 << row_bits) - 1));
-                    const int f = (int)(key[k] >> row_bits);
-                    seg_feat[sidx] = f;
-                    const int fprev = i == 0 ? -1 : (int)(prev >> row_bits);
-                    for (int ff = fprev + 1; ff <= f; ff++)
-                        feat_roff[ff] = sidx;
-                }
-            }
-            if (i == n - 1) {
-                const int64_t R = sidx + (head ? 1 : 0);
-                seg_start[R] = n;
-                list_off[0] = 0;
-                list_off[1] = R;
-                if (row_bits >= 0) {
-                    const int f = (int)(key[k] >> row_bits);
-                    for (int ff = f + 1; ff <= F; ff++)
-                        feat_roff[ff] = R;
-                }
-            }
-            sidx += head ? 1 : 0;
-            prev = key[k];
-        }
-    }
-}
 
 // ---------------------------------------------------------------- row-wise Adagrad
 // One 32-lane group per touched row k (rows of features [f0, f0+nf) only):
@@ -674,35 +152,6 @@ __device__ __forceinline__ void finish_segment(const RowSumParams &p, const OptA
     }
 }
 
-// Segments longer than p.long_seg entries are cut into chunks of 256 entries, or larger ones if that would
-// give more than 64 chunks.  The cut depends on the segment's length only; the order in which
-// segments and chunks are listed does not matter for the sums.
-__global__ __launch_bounds__(256) void k_find_long(const RowSumParams p)
-{
-    const int64_t R = *p.n_seg;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < R;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t start = p.seg_start[k], end = p.seg_start[k + 1];
-        const int64_t len = end - start;
-        if (len <= p.long_seg)
-            continue;
-        int64_t ch = 256;
-        if ((len + ch - 1) / ch > 64)
-            ch = (len + 63) / 64;
-        const int nch = (int)((len + ch - 1) / ch);
-        const int64_t first = (int64_t)atomicAdd(reinterpret_cast<unsigned long long *>(p.long_count + 1),
-                                                 (unsigned long long)nch);
-        const int64_t slot = (int64_t)atomicAdd(reinterpret_cast<unsigned long long *>(p.long_count), 1ull);
-        p.lseg_t[slot] = (int32_t)k;
-        p.lseg_first[slot] = (int32_t)first;
-        p.lseg_n[slot] = nch;
-        for (int c = 0; c < nch; c++) {
-            p.item_start[first + c] = start + c * ch;
-            p.item_end[first + c] = start + (c + 1) * ch < end ? start + (c + 1) * ch : end;
-        }
-    }
-}
-
 // FINALIZE = false: segments of at most p.long_seg entries are summed here (longer ones are skipped).
 // FINALIZE = true: the "segments" are the cut ones; their entries are the chunk partial sums, in
 // chunk order.
@@ -755,7 +204,7 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
                     row_seg = opt.touched_rows[k];
                 }
                 const int64_t len = end - start;
-                n = len <= p.long_seg ? (int)len : 0;  // longer segments were cut into chunks by k_find_long
+                n = len <= p.long_seg ? (int)len : 0;  // longer segments were cut into chunks
             }
         }
         const bool mine = n > 0;  // uniform inside the lane group
@@ -954,15 +403,6 @@ __global__ void k_no_rows(int F, int64_t *feat_roff, int64_t *list_off)
     }
 }
 
-int bits_for(uint64_t max_value)
-{
-    int b = 1;
-    while (b < 64 && (max_value >> b) != 0)
-        b++;
-    return b;
-}
-
-// Buffers of one sort (the two sorts of a backward call run on two streams at the same time).
 // ---------------------------------------------------------------- sequence path, step A
 // g_emb[u_offsets[u] + t, :] = sum over the rows l (ascending) of unique list u of
 // grad_out[offsets[l] + t, :].  The rows of u are ps[seg_start[u] .. seg_start[u+1]) (rows sorted by
@@ -1083,22 +523,15 @@ __global__ __launch_bounds__(256) void k_jagged_reduce(const float4 *__restrict_
     }
 }
 
-struct SortSet {
-    int64_t *n_dev;  // [0] number of pairs, [1] capacity-overflow flag
-    void *k0, *k1;
-    uint32_t *p0, *p1, *hist, *bsum;
-};
-
 struct BwdWs {
-    SortSet a, b;
-    // Segment numbering of step A (list_off, seg_start, long_count_a) and of step B (the _b arrays,
-    // seg_feat, long_count and what follows): separate, the two are numbered on different streams.
-    int64_t *list_off, *seg_start, *long_count_a;
+    RecdGroupWs group;
+    // segments of step A (list_off, seg_start) and of step B (the _b arrays and what follows)
+    int64_t *list_off, *seg_start;
     int64_t *list_off_b, *seg_start_b;
     int32_t *seg_feat, *lseg_t, *lseg_first, *lseg_n;
     int64_t *long_count, *item_start, *item_end;
     float *g_u, *partials;
-    uint32_t *pos_list;  // weighted lookup: unique list of every position of u_values
+    uint32_t *pos_list;  // unique list of every position of u_values
     float *pay_w;        // weighted lookup: weight of every sorted entry of step B
     float *emb;          // max pooling: one masked gradient row per position of u_values [M, D]
     int long_seg;        // step B: segments with more entries are cut into chunks
@@ -1113,38 +546,16 @@ struct BwdWs {
 // 4.55 with 32.
 constexpr int kDefaultLongSeg = 32;
 
-SortSet carve_sort(WsCarver &c, int64_t n, bool wide_keys)
-{
-    SortSet s;
-    const int64_t ntiles = (n + kTile - 1) / kTile;
-    const int64_t hist_n = (int64_t)kRadixMax * ntiles;
-    s.n_dev = c.take<int64_t>(2);
-    if (wide_keys) {
-        s.k0 = c.take<uint64_t>(n);
-        s.k1 = c.take<uint64_t>(n);
-    } else {
-        s.k0 = c.take<uint32_t>(n);
-        s.k1 = c.take<uint32_t>(n);
-    }
-    s.p0 = c.take<uint32_t>(n);
-    s.p1 = c.take<uint32_t>(n);
-    s.hist = c.take<uint32_t>(hist_n);
-    // block sums of the head-flag scan, and the digit totals of a sort pass
-    s.bsum = c.take<uint32_t>((n + kScanTile - 1) / kScanTile + 1 + kRadixMax);
-    return s;
-}
-
-BwdWs carve_bwd(char *base, int64_t n_lists, int64_t M_cap, int F, int D, int long_seg, bool with_emb = false)
+BwdWs carve_bwd(char *base, int F, int64_t B, int64_t M_cap, int D, int long_seg, bool with_emb = false)
 {
     WsCarver c(base);
     BwdWs w;
     (void)c.take<char>(1024);  // the head of the workspace stays with the validation passes' flags
+    const int64_t n_lists = (int64_t)F * B;
     const int64_t n_max = n_lists > M_cap ? n_lists : M_cap;
     int64_t u_cap = M_cap + F < n_lists ? M_cap + F : n_lists;
-    w.a = carve_sort(c, n_lists, false);
-    w.b = carve_sort(c, M_cap, true);
+    w.group = recd_group_carve(c, F, B, M_cap);
     w.list_off = c.take<int64_t>(2);
-    w.long_count_a = c.take<int64_t>(2);
     w.seg_start = c.take<int64_t>(n_lists + 1);
     w.list_off_b = c.take<int64_t>(2);
     w.seg_start_b = c.take<int64_t>(M_cap + 1);
@@ -1166,34 +577,6 @@ BwdWs carve_bwd(char *base, int64_t n_lists, int64_t M_cap, int F, int D, int lo
     w.emb = with_emb ? c.take<float>((size_t)M_cap * D) : nullptr;
     w.bytes = c.off;
     return w;
-}
-
-// Segments of equal keys in the sorted keys ks: seg_start, list_off = {0, R} and, for (feature, row)
-// keys, the row ids, the feature of every segment and feat_roff.
-// (row_bits < 0: step A's arrays; row_bits >= 0: step B's.)
-struct SegBufs {
-    int64_t *seg_start, *list_off, *long_count;
-};
-
-SegBufs seg_bufs(const BwdWs &w, int row_bits)
-{
-    return row_bits < 0 ? SegBufs{w.seg_start, w.list_off, w.long_count_a}
-                        : SegBufs{w.seg_start_b, w.list_off_b, w.long_count};
-}
-
-template <typename KeyT>
-recd_status number_segments(recd_ctx *ctx, hipStream_t st, const BwdWs &w, const SortSet &set, const KeyT *ks,
-                            int64_t n_cap, int row_bits, int F, int64_t *touched_rows, int64_t *feat_roff)
-{
-    const SegBufs sb = seg_bufs(w, row_bits);
-    const unsigned tiles = (unsigned)((n_cap + kScanTile - 1) / kScanTile > 0 ? (n_cap + kScanTile - 1) / kScanTile : 1);
-    hipLaunchKernelGGL((k_head_count<KeyT>), dim3(tiles), dim3(256), 0, st, ks, set.n_dev, set.bsum,
-                       sb.long_count);
-    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, st, set.bsum, (int64_t)tiles);
-    hipLaunchKernelGGL((k_segments<KeyT>), dim3(tiles), dim3(256), 0, st, ks, set.n_dev, set.bsum,
-                       sb.seg_start, sb.list_off, row_bits, F, touched_rows, feat_roff, w.seg_feat);
-    RECD_HIP(ctx, hipGetLastError());
-    return RECD_OK;
 }
 
 // What the row-gradient kernels of step B need to know about its segments.
@@ -1219,53 +602,62 @@ RowSumParams row_params(const BwdWs &w, const uint32_t *ps, const float *pay_w, 
     return rp;
 }
 
-// Step B's segments need the sorted keys only, not the result of step A: numbered, and the long
-// ones cut into chunks, on the stream the sort ran on.
-template <typename KeyT>
-recd_status prepare_rows(recd_ctx *ctx, hipStream_t st, const BwdWs &w, const SortSet &set, const KeyT *ks,
-                         int64_t n_cap, int64_t seg_bound, int row_bits, int F, int64_t *touched_rows,
-                         int64_t *feat_roff, hipEvent_t numbered = nullptr)
+// Step A: the sum of every unique list's grad_out rows (ps, grouped) into out.
+recd_status sum_lists(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t U_cap, const float *grad_out, int D,
+                      const int64_t *div_off)
 {
-    RECD_TRY(number_segments<KeyT>(ctx, st, w, set, ks, n_cap, row_bits, F, touched_rows, feat_roff));
-    // the sum of the short segments needs nothing of what follows: whoever waits for `numbered`
-    // instead of the end of this stream's work starts it one kernel earlier
-    if (numbered)
-        RECD_HIP(ctx, hipEventRecord(numbered, st));
-    const RowSumParams rp = row_params(w, nullptr, nullptr, nullptr, 4, nullptr);
-    int64_t fblk = (seg_bound + 255) / 256;
-    if (fblk > (int64_t)ctx->num_cu * 8)
-        fblk = (int64_t)ctx->num_cu * 8;
-    hipLaunchKernelGGL(k_find_long, dim3((unsigned)(fblk < 1 ? 1 : fblk)), dim3(256), 0, st, rp);
-    RECD_HIP(ctx, hipGetLastError());
-    return RECD_OK;
-}
-
-// Step A: segments of equal keys in the sorted pairs (ks, ps) of `set`, then the sum of every
-// segment's rows (the block-cooperative gather-sum kernel handles any segment length).
-recd_status segment_and_sum_lists(recd_ctx *ctx, const BwdWs &w, const SortSet &set, const uint32_t *ks,
-                                  const uint32_t *ps, int64_t n_cap, int64_t seg_bound, int F,
-                                  const void *table, int D, void *out, const int64_t *div_off)
-{
-    RECD_TRY(number_segments<uint32_t>(ctx, ctx->stream, w, set, ks, n_cap, -1, F, nullptr, nullptr));
     SegSumArgs a{};
     a.site = RECD_SITE_GRAD_STREAM;  // every grad_out row is read exactly once
     a.F = 1;
     a.D = D;
     a.table_dt = RECD_F32;
     a.out_dt = RECD_F32;
-    a.tables.p[0] = table;
+    a.tables.p[0] = grad_out;
     a.values = ps;
     a.values_are_i32 = 1;
     a.offsets = w.seg_start;
     a.list_off = w.list_off;
-    a.lists_bound = seg_bound;
+    a.lists_bound = U_cap;
     a.flat = 1;
-    a.out = out;
+    a.out = w.g_u;
     a.div_off = div_off;
     return recd_launch_segsum(ctx, a);
 }
 
-// Step B after prepare_rows: short segments (at most long_seg entries) by one lane group each, the cut
+// What the grouping writes for a backward pass in the workspace w.
+RecdGroupArgs group_args(const BwdWs &w, int F, int64_t B, int64_t U_cap, int64_t M_cap, int64_t max_rows,
+                         const int32_t *inverse, const int64_t *feat_uoff, const int64_t *u_values,
+                         const int64_t *u_offsets, int64_t *touched_rows, int64_t *feat_roff)
+{
+    RecdGroupArgs a{};
+    a.F = F;
+    a.B = B;
+    a.U_cap = U_cap;
+    a.M_cap = M_cap;
+    a.max_rows = max_rows;
+    a.inverse = inverse;
+    a.feat_uoff = feat_uoff;
+    a.u_values = u_values;
+    a.u_offsets = u_offsets;
+    a.pos_list = w.pos_list;
+    a.seg_start_a = w.seg_start;
+    a.list_off_a = w.list_off;
+    a.seg_start_b = w.seg_start_b;
+    a.list_off_b = w.list_off_b;
+    a.touched_rows = touched_rows;
+    a.feat_roff = feat_roff;
+    a.seg_feat = w.seg_feat;
+    a.long_count = w.long_count;
+    a.item_start = w.item_start;
+    a.item_end = w.item_end;
+    a.lseg_t = w.lseg_t;
+    a.lseg_first = w.lseg_first;
+    a.lseg_n = w.lseg_n;
+    a.long_seg = w.long_seg;
+    return a;
+}
+
+// Step B after the grouping: short segments (at most long_seg entries) by one lane group each, the cut
 // ones by the block-cooperative kernel on the side stream next to them; optimizer fused.
 recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t n_cap, int64_t seg_bound,
                      const void *table, int D, void *out, int64_t *touched_rows, const OptAdagrad *opt,
@@ -1348,7 +740,7 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
 
 size_t recd_backward_workspace(int F, int64_t B, int64_t M_cap, int D)
 {
-    return carve_bwd(nullptr, (int64_t)F * B, M_cap, F, D, kDefaultLongSeg).bytes;
+    return carve_bwd(nullptr, F, B, M_cap, D, kDefaultLongSeg).bytes;
 }
 
 // The fused update reads and writes a table row (and its accumulator) once per (feature, row)
@@ -1428,8 +820,8 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         RECD_TRY(recd_validate_inverse(ctx, F, B, feat_uoff, inverse));
     const bool maxmode = max_tables != nullptr;
     ctx->plan.valid = false;  // this call reuses the workspace a plan would live in
-    RECD_TRY(recd_reserve(ctx, carve_bwd(nullptr, n_lists, M_cap, F, D, ctx->long_seg_cut, maxmode).bytes));
-    const BwdWs w = carve_bwd(ctx->ws, n_lists, M_cap, F, D, ctx->long_seg_cut, maxmode);
+    RECD_TRY(recd_reserve(ctx, carve_bwd(nullptr, F, B, M_cap, D, ctx->long_seg_cut, maxmode).bytes));
+    const BwdWs w = carve_bwd(ctx->ws, F, B, M_cap, D, ctx->long_seg_cut, maxmode);
     hipStream_t st = ctx->stream;
 
     if (n_lists == 0 || M_cap == 0) {
@@ -1457,28 +849,21 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         oa.lr = lr;
         oa.eps = eps;
     }
-    const int row_bits = bits_for((uint64_t)(max_rows - 1));
-    const int bits_b = row_bits + bits_for((uint64_t)(F > 1 ? F - 1 : 1));
-    const int bits_a = bits_for((uint64_t)(U_cap > 1 ? U_cap - 1 : 1));
-    const bool wide = bits_b > 32;
-
-    // The sort of step B needs nothing from step A: it runs on the side stream meanwhile, forked from
-    // the point before step A.  Step A's launches are issued first: its chain is the longer one, and
-    // while the host issues the side stream's fifteen short launches the main stream would idle.
-    hipStream_t side = ctx->side_stream;
-    RECD_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
-    // ---- step A: group rows (f,b) by unique list, sum grad_out rows into g_u --------------------
+    // ---- both groupings ----------------------------------------------------------------------------
+    RecdGroupArgs ga = group_args(w, F, B, U_cap, M_cap, max_rows, inverse, feat_uoff, u_values, u_offsets,
+                                  touched_rows, feat_roff);
+    ga.pay_positions = seq || u_weights || maxmode ? 1 : 0;  // the later sum's source row: position or list
+    if (seq || maxmode)
+        ga.pos_list = nullptr;
+    ga.u_weights = u_weights;
+    ga.pay_w = w.pay_w;
+    RECD_TRY(recd_group(ctx, st, w.group, ga));
+    const uint32_t *ps_a = recd_group_rows(w.group, B, U_cap), *ps_b = recd_group_positions(w.group, max_rows);
+    // ---- step A: sum grad_out rows into g_u (or, for sequences, into grad_emb) ---------------------------
     {
-        uint32_t *k0 = static_cast<uint32_t *>(w.a.k0), *k1 = static_cast<uint32_t *>(w.a.k1), *ks, *ps;
-        hipLaunchKernelGGL(k_keys_rows, dim3((unsigned)((n_lists + 255) / 256)), dim3(256), 0, st,
-                           inverse, feat_uoff, B, n_lists, k0, w.a.p0, w.a.n_dev);
-        RECD_TRY(radix_sort_pairs<uint32_t>(ctx, st, k0, w.a.p0, k1, w.a.p1, w.a.n_dev, n_lists, bits_a,
-                                            w.a.hist, w.a.bsum, &ks, &ps));
         if (!seq) {
-            RECD_TRY(segment_and_sum_lists(ctx, w, w.a, ks, ps, n_lists, U_cap, F, grad_out, D, w.g_u,
-                                           mean ? u_offsets : nullptr));
+            RECD_TRY(sum_lists(ctx, w, ps_a, U_cap, grad_out, D, mean ? u_offsets : nullptr));
         } else {
-            RECD_TRY(number_segments<uint32_t>(ctx, st, w, w.a, ks, n_lists, -1, F, nullptr, nullptr));
             // lists per block: about 128 positions
             const double avg = (double)M_cap / (double)(U_cap > 0 ? U_cap : 1);
             int lists = 1;
@@ -1491,7 +876,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
                 blocks = 1;
 #define RECD_JR(L)                                                                                    \
     hipLaunchKernelGGL((k_jagged_reduce<L>), dim3((unsigned)blocks), dim3(256), 0, st,                 \
-                       reinterpret_cast<const float4 *>(grad_out), kjt_offsets, ps, w.seg_start,       \
+                       reinterpret_cast<const float4 *>(grad_out), kjt_offsets, ps_a, w.seg_start,     \
                        w.list_off + 1, u_offsets, reinterpret_cast<float4 *>(grad_emb), D / 4, N, M_cap)
             switch (lists) {
             case 1: RECD_JR(1); break;
@@ -1535,50 +920,8 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         }
         RECD_HIP(ctx, hipGetLastError());
     }
-    // ---- step B's keys, sort and segment numbering on the side stream ------------------------------
-    RECD_HIP(ctx, hipStreamWaitEvent(side, ctx->ev_fork, 0));
-    void *ks_b = nullptr;
-    uint32_t *ps_b = nullptr;
-    {
-        constexpr int SG = 16;
-        const unsigned kb = keys_ids_blocks(U_cap, n_lists, SG, 256);
-        if (!wide) {
-            uint32_t *k0 = static_cast<uint32_t *>(w.b.k0), *k1 = static_cast<uint32_t *>(w.b.k1), *ks;
-            hipLaunchKernelGGL((k_keys_ids<uint32_t, SG>), dim3(kb), dim3(256), 0, side, u_values,
-                               u_offsets, feat_uoff, F, row_bits, n_lists, M_cap, k0, w.b.p0, w.b.n_dev,
-                               (seq || u_weights || maxmode) ? 1 : 0, u_weights ? w.pos_list : nullptr);
-            RECD_TRY(radix_sort_pairs<uint32_t>(ctx, side, k0, w.b.p0, k1, w.b.p1, w.b.n_dev, M_cap, bits_b,
-                                                w.b.hist, w.b.bsum, &ks, &ps_b));
-            ks_b = ks;
-        } else {
-            uint64_t *k0 = static_cast<uint64_t *>(w.b.k0), *k1 = static_cast<uint64_t *>(w.b.k1), *ks;
-            hipLaunchKernelGGL((k_keys_ids<uint64_t, SG>), dim3(kb), dim3(256), 0, side, u_values,
-                               u_offsets, feat_uoff, F, row_bits, n_lists, M_cap, k0, w.b.p0, w.b.n_dev,
-                               (seq || u_weights || maxmode) ? 1 : 0, u_weights ? w.pos_list : nullptr);
-            RECD_TRY(radix_sort_pairs<uint64_t>(ctx, side, k0, w.b.p0, k1, w.b.p1, w.b.n_dev, M_cap, bits_b,
-                                                w.b.hist, w.b.bsum, &ks, &ps_b));
-            ks_b = ks;
-        }
-        if (u_weights) {
-            int64_t wb = (M_cap + 255) / 256;
-            if (wb > (int64_t)ctx->num_cu * 16)
-                wb = (int64_t)ctx->num_cu * 16;
-            hipLaunchKernelGGL(k_weight_payload, dim3((unsigned)(wb < 1 ? 1 : wb)), dim3(256), 0, side, ps_b,
-                               w.pos_list, u_weights, w.b.n_dev, w.pay_w);
-        }
-        RECD_HIP(ctx, hipGetLastError());
-        // the segments of step B (row ids, per-feature counts, chunks of the long ones) as well
-        if (!wide)
-            RECD_TRY(prepare_rows<uint32_t>(ctx, side, w, w.b, static_cast<const uint32_t *>(ks_b), M_cap, M_cap,
-                                            row_bits, F, touched_rows, feat_roff));
-        else
-            RECD_TRY(prepare_rows<uint64_t>(ctx, side, w, w.b, static_cast<const uint64_t *>(ks_b), M_cap, M_cap,
-                                            row_bits, F, touched_rows, feat_roff));
-        RECD_HIP(ctx, hipEventRecord(ctx->ev_join, side));
-    }
     const float *b_table = seq ? grad_emb : (maxmode ? w.emb : w.g_u);
-    // ---- step B: group unique-id positions by (feature, row), sum g_u rows into grad_rows --------
-    RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_join, 0));
+    // ---- step B: sum the source rows of every (feature, row) into grad_rows -------------------------
     RECD_TRY(sum_rows(ctx, w, ps_b, M_cap, M_cap, b_table, D, grad_rows, touched_rows, fused ? &oa : nullptr,
                       u_weights ? w.pay_w : nullptr));
     // ---- optimizer -------------------------------------------------------------------------------
@@ -1598,7 +941,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
     if (host_R) {
         RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned, w.list_off_b + 1, sizeof(int64_t),
                                      hipMemcpyDeviceToHost, st));
-        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 1, w.b.n_dev + 1, sizeof(int64_t),
+        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 1, w.group.b.n_dev + 1, sizeof(int64_t),
                                      hipMemcpyDeviceToHost, st));
         RECD_HIP(ctx, hipStreamSynchronize(st));
         host_R[0] = ctx->host_pinned[0];
@@ -1609,14 +952,14 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
 }
 
 // ---------------------------------------------------------------- planned backward
-// The backward's grouping work (keys, sorts, segment numbering of both steps) depends on the IKJT
-// only, not on the gradient.  recd_backward_plan runs it on the two side streams, starting where the
-// IKJT's build ended, so that it overlaps the forward calls (which are bandwidth-bound, while the
-// plan is a chain of short latency-bound kernels); recd_backward_apply then waits for the plan on the
-// main stream and runs the two segment sums with the fused update.  Same kernels, same inputs, same
-// results as the one-call form.
-// run_index: null, or the batch's run index (then step A's grouping sorts the runs, at most
-// runs_cap of them, instead of all F*B rows)
+// The backward's grouping work depends on the IKJT only, not on the gradient.  recd_backward_plan runs it
+// on the side stream, starting where the IKJT's build ended, so that it overlaps the forward calls
+// (which are bandwidth-bound, while the plan is a chain of short latency-bound kernels);
+// recd_backward_apply then waits for the plan on the main stream and runs the two segment sums with
+// the fused update.  Same kernels, same inputs, same results as the one-call form.
+// run_index: null, or the batch's run index, whose number of runs is checked against runs_cap (the
+// grouping itself reads `inverse`: sorting the runs instead of the rows took fewer keys and more
+// launches).
 static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int32_t *inverse,
                                const int64_t *feat_uoff, const int64_t *u_values, const int64_t *u_offsets,
                                const int64_t *rows, int64_t U_cap, int64_t M_cap, const int64_t *run_index,
@@ -1651,11 +994,11 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
     RECD_HIP(ctx, hipSetDevice(ctx->device));
     if (ctx->validate && n_lists > 0)
         RECD_TRY(recd_validate_inverse(ctx, F, B, feat_uoff, inverse));
-    // the side streams may start at the end of the build only if nothing on the stream has used the
+    // the side stream may start at the end of the build only if nothing on the stream has used the
     // workspace since (this call's own reservation does not count)
     const bool ws_idle_since_build = !ctx->ws_used_since_build;
-    RECD_TRY(recd_reserve(ctx, carve_bwd(nullptr, n_lists, M_cap, F, D, ctx->long_seg_cut).bytes));
-    const BwdWs w = carve_bwd(ctx->ws, n_lists, M_cap, F, D, ctx->long_seg_cut);
+    RECD_TRY(recd_reserve(ctx, carve_bwd(nullptr, F, B, M_cap, D, ctx->long_seg_cut).bytes));
+    const BwdWs w = carve_bwd(ctx->ws, F, B, M_cap, D, ctx->long_seg_cut);
     recd_ctx::BackwardPlan &pl = ctx->plan;
     pl.F = F;
     pl.B = B;
@@ -1667,8 +1010,8 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
     pl.feat_roff = feat_roff;
     pl.ws = ctx->ws;
     pl.empty = n_lists == 0 || M_cap == 0;
-    hipStream_t st = ctx->stream, sa = ctx->side_stream2, sb = ctx->side_stream;
-    // Where the side streams may start: at the end of the build that produced this IKJT if it is the
+    hipStream_t st = ctx->stream, side = ctx->side_stream;
+    // Where the side stream may start: at the end of the build that produced this IKJT if it is the
     // context's most recent one, else at the main stream's current position.
     hipEvent_t from = ctx->ev_fork;
     if (ctx->build_valid && ws_idle_since_build && ctx->built_inverse == inverse &&
@@ -1676,90 +1019,17 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
         from = ctx->ev_built;
     else
         RECD_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
-    RECD_HIP(ctx, hipStreamWaitEvent(sa, from, 0));
-    RECD_HIP(ctx, hipStreamWaitEvent(sb, from, 0));
+    RECD_HIP(ctx, hipStreamWaitEvent(side, from, 0));
     if (!pl.empty) {
-        const int row_bits = bits_for((uint64_t)(max_rows - 1));
-        const int bits_b = row_bits + bits_for((uint64_t)(F > 1 ? F - 1 : 1));
-        const int bits_a = bits_for((uint64_t)(U_cap > 1 ? U_cap - 1 : 1));
-        pl.row_bits = row_bits;
-        pl.wide = bits_b > 32;
-        auto chain_a = [&]() -> recd_status {
-        // step A's grouping on the second side stream
-        if (run_index) {
-            // the runs sorted by unique list, then written out as the rows they stand for
-            if (runs_cap > n_lists || runs_cap == 0)
-                runs_cap = n_lists;
-            uint32_t *k0 = static_cast<uint32_t *>(w.a.k0), *k1 = static_cast<uint32_t *>(w.a.k1), *ks, *ps;
-            hipLaunchKernelGGL(k_run_keys, dim3((unsigned)((runs_cap + 255) / 256)), dim3(256), 0, sa, run_index,
-                               runs_cap, k0, w.a.p0, w.a.n_dev);
-            RECD_TRY(radix_sort_pairs<uint32_t>(ctx, sa, k0, w.a.p0, k1, w.a.p1, w.a.n_dev, runs_cap, bits_a,
-                                                w.a.hist, w.a.bsum, &ks, &ps));
-            const unsigned tiles = (unsigned)((runs_cap + kScanTile - 1) / kScanTile);
-            uint32_t *rows_out = ps == w.a.p0 ? w.a.p1 : w.a.p0;
-            hipLaunchKernelGGL((k_run_rows<false>), dim3(tiles), dim3(256), 0, sa, ks, ps, run_index, w.a.n_dev,
-                               w.a.bsum, w.a.hist, w.seg_start, w.list_off, rows_out, w.long_count_a);
-            hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, sa, w.a.bsum, (int64_t)tiles);
-            hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, sa, w.a.hist, (int64_t)tiles);
-            hipLaunchKernelGGL((k_run_rows<true>), dim3(tiles), dim3(256), 0, sa, ks, ps, run_index, w.a.n_dev,
-                               w.a.bsum, w.a.hist, w.seg_start, w.list_off, rows_out, w.long_count_a);
-            RECD_HIP(ctx, hipGetLastError());
-            pl.ks_a = ks;
-            pl.ps_a = rows_out;
-        } else {
-            uint32_t *k0 = static_cast<uint32_t *>(w.a.k0), *k1 = static_cast<uint32_t *>(w.a.k1), *ks, *ps;
-            hipLaunchKernelGGL(k_keys_rows, dim3((unsigned)((n_lists + 255) / 256)),
-                               dim3(256), 0, sa, inverse,
-                               feat_uoff, B, n_lists, k0, w.a.p0, w.a.n_dev);
-            RECD_TRY(radix_sort_pairs<uint32_t>(ctx, sa, k0, w.a.p0, k1, w.a.p1, w.a.n_dev, n_lists, bits_a,
-                                                w.a.hist, w.a.bsum, &ks, &ps));
-            RECD_TRY(number_segments<uint32_t>(ctx, sa, w, w.a, ks, n_lists, -1, F, nullptr, nullptr));
-            pl.ks_a = ks;
-            pl.ps_a = ps;
-        }
-        return RECD_OK;
-        };
-        auto chain_b = [&]() -> recd_status {
-        // step B's grouping on the first
-        {
-            constexpr int SG = 16;
-            const unsigned kb = keys_ids_blocks(U_cap, n_lists, SG, 256);
-            if (!pl.wide) {
-                uint32_t *k0 = static_cast<uint32_t *>(w.b.k0), *k1 = static_cast<uint32_t *>(w.b.k1), *ks, *ps;
-                hipLaunchKernelGGL((k_keys_ids<uint32_t, SG>), dim3(kb), dim3(256), 0, sb, u_values, u_offsets,
-                                   feat_uoff, F, row_bits, n_lists, M_cap, k0, w.b.p0, w.b.n_dev, 0, nullptr);
-                RECD_TRY(radix_sort_pairs<uint32_t>(ctx, sb, k0, w.b.p0, k1, w.b.p1, w.b.n_dev, M_cap, bits_b,
-                                                    w.b.hist, w.b.bsum, &ks, &ps));
-                RECD_TRY(prepare_rows<uint32_t>(ctx, sb, w, w.b, ks, M_cap, M_cap, row_bits, F, touched_rows,
-                                                feat_roff, ctx->ev_plan_rows));
-                pl.ps_b = ps;
-            } else {
-                uint64_t *k0 = static_cast<uint64_t *>(w.b.k0), *k1 = static_cast<uint64_t *>(w.b.k1), *ks;
-                uint32_t *ps;
-                hipLaunchKernelGGL((k_keys_ids<uint64_t, SG>), dim3(kb), dim3(256), 0, sb, u_values, u_offsets,
-                                   feat_uoff, F, row_bits, n_lists, M_cap, k0, w.b.p0, w.b.n_dev, 0, nullptr);
-                RECD_TRY(radix_sort_pairs<uint64_t>(ctx, sb, k0, w.b.p0, k1, w.b.p1, w.b.n_dev, M_cap, bits_b,
-                                                    w.b.hist, w.b.bsum, &ks, &ps));
-                RECD_TRY(prepare_rows<uint64_t>(ctx, sb, w, w.b, ks, M_cap, M_cap, row_bits, F, touched_rows,
-                                                feat_roff, ctx->ev_plan_rows));
-                pl.ps_b = ps;
-            }
-        }
-        return RECD_OK;
-        };
-        // The host issues one chain after the other: the longer one first.  Sorting all F*B rows makes
-        // step A's chain the longer one; from the run index it is a fraction of step B's.
-        if (run_index) {
-            RECD_TRY(chain_b());
-            RECD_TRY(chain_a());
-        } else {
-            RECD_TRY(chain_a());
-            RECD_TRY(chain_b());
-        }
-        RECD_HIP(ctx, hipGetLastError());
+        RecdGroupArgs ga = group_args(w, F, B, U_cap, M_cap, max_rows, inverse, feat_uoff, u_values, u_offsets,
+                                      touched_rows, feat_roff);
+        ga.run_index = run_index;
+        ga.runs_cap = runs_cap > n_lists || runs_cap == 0 ? n_lists : runs_cap;
+        RECD_TRY(recd_group(ctx, side, w.group, ga));
+        pl.ps_a = recd_group_rows(w.group, B, U_cap);
+        pl.ps_b = recd_group_positions(w.group, max_rows);
     }
-    RECD_HIP(ctx, hipEventRecord(ctx->ev_plan_a, sa));
-    RECD_HIP(ctx, hipEventRecord(ctx->ev_plan_b, sb));
+    RECD_HIP(ctx, hipEventRecord(ctx->ev_plan, side));
     pl.pending = true;
     pl.valid = true;
     return RECD_OK;
@@ -1816,11 +1086,10 @@ extern "C" recd_status recd_backward_apply(recd_ctx *ctx, recd_pooling mode, con
     RECD_TRY(check_distinct_tables(ctx, F, tables, adagrad_state));
     RECD_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
-    const BwdWs w = carve_bwd(ctx->ws, n_lists, M_cap, F, D, ctx->long_seg_cut);
-    RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_plan_a, 0));
+    const BwdWs w = carve_bwd(ctx->ws, F, B, M_cap, D, ctx->long_seg_cut);
+    RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_plan, 0));
+    pl.pending = false;  // the stream now waits for everything the plan enqueued
     if (pl.empty) {
-        RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_plan_b, 0));
-        pl.pending = false;
         hipLaunchKernelGGL(k_no_rows, dim3(1), dim3(64), 0, st, F, pl.feat_roff, w.list_off_b);
         RECD_HIP(ctx, hipGetLastError());
         if (host_R) {
@@ -1841,32 +1110,9 @@ extern "C" recd_status recd_backward_apply(recd_ctx *ctx, recd_pooling mode, con
         oa.lr = lr;
         oa.eps = eps;
     }
-    // step A's sum over the planned segments
-    {
-        SegSumArgs a{};
-        a.site = RECD_SITE_GRAD_STREAM;
-        a.F = 1;
-        a.D = D;
-        a.table_dt = RECD_F32;
-        a.out_dt = RECD_F32;
-        a.tables.p[0] = grad_out;
-        a.values = pl.ps_a;
-        a.values_are_i32 = 1;
-        a.offsets = w.seg_start;
-        a.list_off = w.list_off;
-        a.lists_bound = pl.U_cap;
-        a.flat = 1;
-        a.out = w.g_u;
-        a.div_off = mode == RECD_POOL_MEAN ? pl.u_offsets : nullptr;
-        RECD_TRY(recd_launch_segsum(ctx, a));
-    }
-    // Step B's grouping may still be running next to the sum above.  The cut of the long segments,
-    // the last kernel of that chain, is needed only by the chunk passes, which sum_rows enqueues on
-    // the same side stream behind it; the stream joins that side stream at the end of sum_rows.
-    RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_plan_rows, 0));
+    RECD_TRY(sum_lists(ctx, w, pl.ps_a, pl.U_cap, grad_out, D, mode == RECD_POOL_MEAN ? pl.u_offsets : nullptr));
     RECD_TRY(sum_rows(ctx, w, pl.ps_b, M_cap, M_cap, w.g_u, D, grad_rows, pl.touched_rows, fused ? &oa : nullptr,
                       nullptr));
-    pl.pending = false;  // the stream now waits for everything the plan enqueued
     if (tables && !fused) {
         for (int f0 = 0; f0 < F; f0 += RECD_F_PER_LAUNCH) {
             OptPtrs ptrs;
@@ -1882,9 +1128,9 @@ extern "C" recd_status recd_backward_apply(recd_ctx *ctx, recd_pooling mode, con
     }
     if (host_R) {
         RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned, w.list_off_b + 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 1, w.b.n_dev + 1, sizeof(int64_t), hipMemcpyDeviceToHost,
+        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 1, w.group.b.n_dev + 1, sizeof(int64_t), hipMemcpyDeviceToHost,
                                      st));
-        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 2, w.a.n_dev + 1, sizeof(int64_t), hipMemcpyDeviceToHost,
+        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 2, w.group.a.n_dev + 1, sizeof(int64_t), hipMemcpyDeviceToHost,
                                      st));
         RECD_HIP(ctx, hipStreamSynchronize(st));
         host_R[0] = ctx->host_pinned[0];

@@ -33,12 +33,11 @@ recd_status recd_check_rows(recd_ctx *ctx, int F, const int64_t *rows)
 recd_status recd_reserve(recd_ctx *ctx, size_t bytes)
 {
     // Every call that is about to use the workspace comes through here first.  A plan that was never
-    // applied may still be running on the side streams, in the same memory: the caller's kernels go
+    // applied may still be running on the side stream, in the same memory: the caller's kernels go
     // behind it.
     ctx->ws_used_since_build = true;
     if (ctx->plan.pending) {
-        RECD_HIP(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_plan_a, 0));
-        RECD_HIP(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_plan_b, 0));
+        RECD_HIP(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_plan, 0));
         ctx->plan.pending = false;
     }
     if (bytes <= ctx->ws_bytes)
@@ -47,8 +46,6 @@ recd_status recd_reserve(recd_ctx *ctx, size_t bytes)
     RECD_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (ctx->side_stream)
         RECD_HIP(ctx, hipStreamSynchronize(ctx->side_stream));
-    if (ctx->side_stream2)
-        RECD_HIP(ctx, hipStreamSynchronize(ctx->side_stream2));
     ctx->plan.valid = false;
     if (ctx->ws) {
         RECD_HIP(ctx, hipFree(ctx->ws));
@@ -253,11 +250,8 @@ recd_status recd_create(recd_ctx **out, int device, void *hip_stream, size_t wor
     if (ok && hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
         ctx->num_cu = prop.multiProcessorCount;
     ok = ok && hipStreamCreateWithFlags(&ctx->side_stream, hipStreamNonBlocking) == hipSuccess;
-    ok = ok && hipStreamCreateWithFlags(&ctx->side_stream2, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->ev_built, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&ctx->ev_plan_a, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&ctx->ev_plan_b, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&ctx->ev_plan_rows, hipEventDisableTiming) == hipSuccess;
+    ok = ok && hipEventCreateWithFlags(&ctx->ev_plan, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming) == hipSuccess;
     void *p = nullptr;
@@ -284,6 +278,11 @@ recd_status recd_create(recd_ctx **out, int device, void *hip_stream, size_t wor
     const size_t sa_bytes = (2 * RECD_SMALL_MAX_FEATURES + 2) * sizeof(uint64_t);
     ok = ok && hipMalloc(&sa, sa_bytes) == hipSuccess;
     ok = ok && hipMemset(sa, 0, sa_bytes) == hipSuccess;
+    void *ga = nullptr;
+    const size_t ga_bytes = 2 * RECD_MAX_FEATURES * sizeof(uint32_t);
+    ok = ok && hipMalloc(&ga, ga_bytes) == hipSuccess;
+    ctx->group_arrive = static_cast<uint32_t *>(ga);
+    ok = ok && hipMemset(ga, 0, ga_bytes) == hipSuccess;
     ok = ok && hipStreamSynchronize(nullptr) == hipSuccess;  // cleared before any stream of the context reads it
     ctx->small_agg = static_cast<uint64_t *>(sa);
     ok = ok && recd_static_scratch(ctx, device) == RECD_OK;
@@ -308,10 +307,6 @@ recd_status recd_destroy(recd_ctx *ctx)
         (void)hipStreamSynchronize(ctx->side_stream);
         (void)hipStreamDestroy(ctx->side_stream);
     }
-    if (ctx->side_stream2) {
-        (void)hipStreamSynchronize(ctx->side_stream2);
-        (void)hipStreamDestroy(ctx->side_stream2);
-    }
     for (KernelTimer &t : ctx->timers)
         for (size_t i = 0; i < t.a.size(); i++) {
             (void)hipEventDestroy(t.a[i]);
@@ -319,12 +314,8 @@ recd_status recd_destroy(recd_ctx *ctx)
         }
     if (ctx->ev_built)
         (void)hipEventDestroy(ctx->ev_built);
-    if (ctx->ev_plan_a)
-        (void)hipEventDestroy(ctx->ev_plan_a);
-    if (ctx->ev_plan_b)
-        (void)hipEventDestroy(ctx->ev_plan_b);
-    if (ctx->ev_plan_rows)
-        (void)hipEventDestroy(ctx->ev_plan_rows);
+    if (ctx->ev_plan)
+        (void)hipEventDestroy(ctx->ev_plan);
     if (ctx->ev_fork)
         (void)hipEventDestroy(ctx->ev_fork);
     if (ctx->ev_join)
@@ -337,6 +328,8 @@ recd_status recd_destroy(recd_ctx *ctx)
         (void)hipFree(ctx->build_counts_dev);
     if (ctx->small_agg)
         (void)hipFree(ctx->small_agg);
+    if (ctx->group_arrive)
+        (void)hipFree(ctx->group_arrive);
     if (ctx->build_table)
         (void)hipFree(ctx->build_table);
     if (ctx->host_pinned)

@@ -1,0 +1,992 @@
+// Grouping for the backward pass: which entries go to which destination, in a fixed order.
+//
+//   side A   the rows (f,b) of every unique list, ascending              key = inverse[f*B+b]
+//   side B   the positions j of every (feature, table row), ascending    key = u_values[j]
+// Both are stable sorts of the entries *inside* a feature (the entries of a feature are one contiguous
+// stretch on either side), so a key is a slot number or a row id and the feature needs no key bits:
+// 20 bits for a million rows, two digits of 10.  The two sides go through the same launches:
+//
+//   k_group_count    digit counts of every feature and digit position -> where a digit starts
+//   k_group_sweep    one launch per digit: a tile ranks its entries, learns from the tiles of its feature
+//                    before it how many entries of each digit they hold (decoupled look-back), and
+//                    writes its entries in order, regrouped in LDS so that neighbours go out together
+//   k_group_segments side A: where every unique list's rows start (the slot number is the segment
+//                    number); side B: the numbering of the distinct rows, the row ids, and the chunks
+//                    of the rows with many entries
+//
+// Four launches for tables of up to 2^20 rows, where separate histogram, scan and scatter kernels per
+// digit and side took 24 in two chains; with a dozen microseconds between dependent launches of two
+// busy streams the chains, not their kernels, bounded every backward pass but the very largest.
+//
+// Look-back only ever waits for tiles of the same feature with a smaller number.  Tiles are handed out by
+// tickets in that order (eight queues, feature f in queue f mod 8, which the blocks of one XCD serve
+// first), so whoever is waited for has started and itself waits only further back: every wait ends.
+#include "recd_internal.h"
+
+namespace {
+
+constexpr int kCountThreads = 256;
+constexpr int kFPT = RECD_MAX_FEATURES / kCountThreads;  // features per thread of k_group_count
+constexpr int kTileThreads = 512;
+constexpr int kItems = 8;
+constexpr int kTile = kTileThreads * kItems;  // entries of a tile
+constexpr int kWaves = kTileThreads / 64;
+constexpr int kMaxBits = 10;
+constexpr int kMaxRadix = 1 << kMaxBits;
+constexpr int kMaxPasses = 4;
+constexpr int kQueues = 8;
+
+__device__ __forceinline__ uint32_t ld_agent(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ uint64_t ld_agent(const uint64_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_agent(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_agent(uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Waits until the memory system has acknowledged this wave's stores.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// A look-back word: the count below, two bits on top (0: nothing yet, 1: the tile's own count, 2: the
+// count of the tile and all tiles of the feature before it).  32-bit words hold 2^30 entries; the
+// 64-bit form serves larger sides.
+template <typename S> struct Word {
+    static constexpr int shift = sizeof(S) * 8 - 2;
+    static __device__ __forceinline__ S own(uint32_t c) { return ((S)1 << shift) | c; }
+    static __device__ __forceinline__ S all(uint32_t c) { return ((S)2 << shift) | c; }
+    static __device__ __forceinline__ int kind(S w) { return (int)(w >> shift); }
+    static __device__ __forceinline__ uint32_t count(S w) { return (uint32_t)(w & (((S)1 << shift) - 1)); }
+};
+
+// Inclusive sums over a wave.
+template <typename T> __device__ __forceinline__ T wave_incl(T v, int lane)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const T x = __shfl_up(v, d);
+        if (lane >= d)
+            v += x;
+    }
+    return v;
+}
+
+// Exclusive sum over the block's NW waves; every thread gets the total.
+template <typename T, int NW> __device__ __forceinline__ T block_excl(T v, T &total)
+{
+    __shared__ T s_w[NW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const T inc = wave_incl(v, lane);
+    __syncthreads();
+    if (lane == 63)
+        s_w[w] = inc;
+    __syncthreads();
+    T off = 0, all = 0;
+#pragma unroll
+    for (int i = 0; i < NW; i++) {
+        off += i < w ? s_w[i] : 0;
+        all += s_w[i];
+    }
+    total = all;
+    return off + inc - v;
+}
+
+struct SideParams {
+    uint32_t *key[2], *pay[2];  // ping-pong buffers; pass p writes the pair p & 1
+    int passes, dbits;
+    uint32_t *base;             // [F][passes][radix]: where a digit starts inside the feature
+    uint32_t *chunk_hist;       // [chunks][passes][radix] (features of several chunks only)
+    void *status;               // [passes][tiles][radix] look-back words
+    uint32_t *ticket;           // [kMaxPasses + 1][kQueues]
+    uint32_t *arrive;           // [F] chunks of a feature that have been counted; zero between launches
+    int64_t chunk;              // entries per block of k_group_count
+    int64_t tiles_cap;          // bound of the number of tiles
+};
+
+struct GroupParams {
+    int F;
+    int64_t B, M_cap, n_lists;
+    const int32_t *inverse;
+    const int64_t *feat_uoff, *u_values, *u_offsets;
+    SideParams a, b;
+    int tpf, cpf;               // side A: tiles and chunks of a feature
+    unsigned a_blocks;          // blocks of the running launch that work on side A
+    // side B
+    uint32_t *pb;               // [F+1] first position of every feature
+    uint32_t *queue_start;      // [kQueues+1] first tile of every queue
+    uint2 *desc_queue;          // tile (in queue order) -> {feature, tile inside the feature}
+    uint2 *desc_feat;           // tile (in feature order) -> the same
+    uint32_t *tile_total;       // [1]
+    uint32_t *pos_list;         // list of every position, or null (then the payload is the position)
+    int pay_positions;          // 1: the payload is the position also where pos_list is written
+    const float *u_weights;     // weights of the positions, or null; sorted ones go to pay_w and the
+    float *pay_w;               // payload of the last pass is pos_list of the position
+    const int64_t *run_index;   // not null: only its count is compared with runs_cap
+    int64_t runs_cap;
+    int64_t *n_dev_a, *n_dev_b; // [0] entries, [1] the caller's bound was too small
+    // segments
+    uint64_t *seg_status;       // [tiles] look-back words of the numbering
+    int64_t *seg_start_a, *list_off_a, *seg_start_b, *list_off_b;
+    int64_t *touched_rows, *feat_roff;
+    int32_t *seg_feat;
+    int64_t *long_count;        // [0] segments that are cut, [1] their chunks
+    int32_t *lseg_t, *lseg_first, *lseg_n;
+    int64_t *item_start, *item_end;
+    int long_seg;
+};
+
+// Digit starts of feature f from the block's counts in LDS.
+__device__ __forceinline__ void write_bases(const SideParams &s, int f, const uint32_t *hist)
+{
+    const int radix = 1 << s.dbits;
+    constexpr int kPer = kMaxRadix / kCountThreads;  // neighbouring digits of a thread
+    for (int p = 0; p < s.passes; p++) {
+        uint32_t v[kPer], sum = 0, total;
+#pragma unroll
+        for (int i = 0; i < kPer; i++) {
+            const int d = threadIdx.x * kPer + i;
+            v[i] = d < radix ? hist[p * radix + d] : 0;
+            sum += v[i];
+        }
+        uint32_t e = block_excl<uint32_t, kCountThreads / 64>(sum, total);
+        uint32_t *base = s.base + ((size_t)f * s.passes + p) * radix;
+#pragma unroll
+        for (int i = 0; i < kPer; i++) {
+            const int d = threadIdx.x * kPer + i;
+            if (d < radix)
+                base[d] = e;
+            e += v[i];
+        }
+    }
+}
+
+// ---- digit counts -----------------------------------------------------------------------------------
+// A block takes a chunk of one feature's entries (a tile, or as many as keep the chunks below some 500),
+// counts the digits of all passes in LDS and, where the feature is a single chunk, turns the counts into
+// digit starts at once; else the block that arrives last adds up the feature's chunks.  The block also
+// clears the look-back words of its tiles, and on side B writes the list of every position.  What is
+// read is small (8 bytes an entry): the kernel is a few dependent round trips and the LDS atomics of a
+// chunk. 
+template <typename S>
+__global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams g)
+{
+    extern __shared__ uint32_t s_dyn[];          // the counts [passes * radix], side B also pb [F+1]: as little
+    uint32_t *s_hist = s_dyn;                    // LDS as there is, so that blocks find room beside the lookup's
+    __shared__ uint32_t s_off[kCountThreads + 1];
+    __shared__ uint32_t s_pick[6];
+    const int tid = threadIdx.x;
+    const bool side_a = blockIdx.x < g.a_blocks;
+    const SideParams &s = side_a ? g.a : g.b;
+    const unsigned blk = side_a ? blockIdx.x : blockIdx.x - g.a_blocks;
+    int f, c, n_chunks;
+    uint32_t begin, end;           // entries of the chunk
+    size_t first_tile, chunk_row;  // in queue order; row of chunk_hist
+    uint32_t tiles_f;
+    if (blockIdx.x == 0 && tid < (kMaxPasses + 1) * kQueues) {
+        g.a.ticket[tid] = 0;
+        g.b.ticket[tid] = 0;
+    }
+    if (side_a) {
+        f = (int)(blk / g.cpf);
+        c = (int)(blk % g.cpf);
+        n_chunks = g.cpf;
+        begin = (uint32_t)(f * g.B + c * s.chunk);
+        end = (uint32_t)(c * s.chunk + s.chunk < g.B ? begin + s.chunk : (f + 1) * g.B);
+        const int q = f % kQueues, per_q = g.F / kQueues, more = g.F % kQueues;
+        first_tile = (size_t)(q * per_q + (q < more ? q : more) + f / kQueues) * g.tpf + (size_t)c * (s.chunk / kTile);
+        chunk_row = blk;
+        tiles_f = g.tpf;
+        if (blk == 0 && tid == 0) {
+            g.n_dev_a[0] = g.n_lists;
+            g.n_dev_a[1] = g.run_index && g.run_index[0] > g.runs_cap ? 1 : 0;
+        }
+    } else {
+        uint32_t *s_pb = s_dyn + (s.passes << s.dbits);
+        // where every feature's positions lie; tiles and chunks of the features before each one
+        for (int i = tid; i <= g.F; i += kCountThreads) {
+            const int64_t at = g.u_offsets[g.feat_uoff[i]];
+            s_pb[i] = (uint32_t)(at < g.M_cap ? at : g.M_cap);  // never past the caller's capacity
+        }
+        if (tid == 0)
+            s_pick[0] = ~0u;
+        __syncthreads();
+        // a thread stands for kFPT neighbouring features, and for kFPT neighbouring places of the queue
+        // order (features 0, 8, 16, ..., then 1, 9, ...)
+        const int per_q = g.F / kQueues, more = g.F % kQueues;
+        const int wide = more * (per_q + 1);  // places in the queues that hold one feature more
+        auto tiles_of = [&](int x) { return (s_pb[x + 1] - s_pb[x] + kTile - 1) / kTile; };
+        auto chunks_of = [&](int x) { return (uint32_t)((s_pb[x + 1] - s_pb[x] + s.chunk - 1) / s.chunk); };
+        auto queue_of = [&](int i) { return i < wide ? i / (per_q + 1) : more + (i - wide) / per_q; };
+        auto in_queue = [&](int i) { return i < wide ? i % (per_q + 1) : (i - wide) % per_q; };
+        uint64_t sum = 0, all;
+        uint32_t sum_q = 0, all_q;
+#pragma unroll
+        for (int i = 0; i < kFPT; i++) {
+            const int x = tid * kFPT + i;
+            if (x < g.F) {
+                sum += ((uint64_t)tiles_of(x) << 32) | chunks_of(x);
+                sum_q += tiles_of(in_queue(x) * kQueues + queue_of(x));
+            }
+        }
+        uint64_t ex = block_excl<uint64_t, kCountThreads / 64>(sum, all);
+        uint32_t t_q = block_excl<uint32_t, kCountThreads / 64>(sum_q, all_q);
+#pragma unroll
+        for (int i = 0; i < kFPT; i++) {
+            const int x = tid * kFPT + i;
+            if (x < g.F) {
+                const uint32_t c_f = chunks_of(x), c0 = (uint32_t)ex;
+                if (blk >= c0 && blk < c0 + c_f) {
+                    s_pick[0] = x;
+                    s_pick[1] = blk - c0;
+                    s_pick[2] = c_f;
+                    s_pick[3] = (uint32_t)(ex >> 32);
+                    s_pick[4] = tiles_of(x);
+                }
+                ex += ((uint64_t)tiles_of(x) << 32) | c_f;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kFPT; i++) {
+            const int x = tid * kFPT + i;
+            if (x < g.F) {
+                const int fq = in_queue(x) * kQueues + queue_of(x);
+                if ((uint32_t)fq == s_pick[0])
+                    s_pick[5] = t_q;
+                if (blk == 0 && in_queue(x) == 0)
+                    g.queue_start[queue_of(x)] = t_q;
+                t_q += tiles_of(fq);
+            }
+        }
+        if (blk == 0) {
+            for (int i = tid; i <= g.F; i += kCountThreads)
+                g.pb[i] = s_pb[i];
+            if (tid >= (g.F < kQueues ? g.F : kQueues) && tid <= kQueues)
+                g.queue_start[tid] = all_q;  // queues without a feature, and the end
+            if (tid == 0) {
+                g.tile_total[0] = all_q;
+                const int64_t M = g.u_offsets[g.feat_uoff[g.F]];
+                g.n_dev_b[0] = M < g.M_cap ? M : g.M_cap;
+                g.n_dev_b[1] = M > g.M_cap ? 1 : 0;
+                g.long_count[0] = g.long_count[1] = 0;
+            }
+        }
+        __syncthreads();
+        if (s_pick[0] == ~0u)
+            return;  // whole block: fewer chunks than the bound
+        f = (int)s_pick[0];
+        c = (int)s_pick[1];
+        n_chunks = (int)s_pick[2];
+        tiles_f = s_pick[4];
+        begin = s_pb[f] + (uint32_t)(c * s.chunk);
+        end = (uint32_t)((int64_t)begin + s.chunk < (int64_t)s_pb[f + 1] ? begin + s.chunk : s_pb[f + 1]);
+        first_tile = s_pick[5] + (size_t)c * (s.chunk / kTile);
+        chunk_row = blk;
+        const uint32_t my_tiles = (end - begin + kTile - 1) / kTile, k0 = (uint32_t)(c * (s.chunk / kTile));
+        for (uint32_t k = tid; k < my_tiles; k += kCountThreads) {
+            g.desc_queue[first_tile + k] = make_uint2(f, k0 + k);
+            g.desc_feat[s_pick[3] + k0 + k] = make_uint2(f, k0 + k);
+            g.seg_status[s_pick[3] + k0 + k] = 0;
+        }
+    }
+    const uint32_t n = end - begin;
+    const int radix = 1 << s.dbits;
+    const uint32_t mask = radix - 1;
+    for (int i = tid; i < s.passes * radix; i += kCountThreads)
+        s_hist[i] = 0;
+    __syncthreads();
+    for (uint32_t i0 = tid; i0 < n; i0 += 16 * kCountThreads) {
+        uint32_t key[16];
+#pragma unroll
+        for (int u = 0; u < 16; u++) {
+            const uint32_t i = i0 + u * kCountThreads;
+            key[u] = i < n ? (side_a ? (uint32_t)g.inverse[begin + i] : (uint32_t)g.u_values[begin + i]) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; u++)
+            if (i0 + u * kCountThreads < n)
+                for (int p = 0; p < s.passes; p++)
+                    atomicAdd(&s_hist[p * radix + ((key[u] >> (p * s.dbits)) & mask)], 1u);
+    }
+    if (tiles_f > 1) {  // a feature of one tile looks back nowhere
+        const size_t words = (size_t)((n + kTile - 1) / kTile) * radix;
+        for (int p = 0; p < s.passes; p++) {
+            S *st = static_cast<S *>(s.status) + ((size_t)p * s.tiles_cap + first_tile) * radix;
+            for (size_t i = tid; i < words; i += kCountThreads)
+                st[i] = 0;
+        }
+    }
+    if (!side_a && g.pos_list) {
+        // the last list of the feature that starts at or before the chunk's first position: 256 places
+        // of the remaining stretch are tried at once (two rounds for 65 K lists)
+        int64_t lo = g.feat_uoff[f], hi = g.feat_uoff[f + 1];
+        const int64_t u_end = hi;
+        while (c > 0 && hi - lo > 1) {
+            const int64_t step = (hi - lo + kCountThreads - 1) / kCountThreads;
+            const int64_t at = lo + tid * step;
+            const bool le = at < hi && g.u_offsets[at] <= (int64_t)begin;
+            __syncthreads();
+            if (tid == 0)
+                s_pick[0] = 0;
+            __syncthreads();
+            const uint64_t m = __ballot(le);
+            if ((tid & 63) == 0)
+                atomicAdd(&s_pick[0], (uint32_t)__popcll(m));
+            __syncthreads();
+            // the list at lo starts at or before begin, so at least one place passed
+            lo += ((int64_t)s_pick[0] - 1) * step;
+            hi = lo + step < hi ? lo + step : hi;
+        }
+        // it and the lists behind it, 256 at a time; 16 lanes write a list's positions
+        for (int64_t u0 = lo; u0 < u_end; u0 += kCountThreads) {
+            const int nl = (int)(u_end - u0 < kCountThreads ? u_end - u0 : kCountThreads);
+            __syncthreads();
+            for (int i = tid; i <= nl; i += kCountThreads) {
+                const int64_t at = g.u_offsets[u0 + i];
+                s_off[i] = (uint32_t)(at < (int64_t)begin ? 0 : (at < (int64_t)end ? at - begin : n));
+            }
+            __syncthreads();
+            for (int i = tid / 16; i < nl; i += kCountThreads / 16)
+                for (uint32_t j = s_off[i] + tid % 16; j < s_off[i + 1]; j += 16)
+                    g.pos_list[begin + j] = (uint32_t)(u0 + i);
+            if (s_off[nl] >= n)
+                break;  // the same value in every thread
+        }
+    }
+    __syncthreads();
+    if (n_chunks == 1) {
+        write_bases(s, f, s_hist);
+        return;
+    }
+    const int words = s.passes * radix;
+    uint32_t *row = s.chunk_hist + chunk_row * words;
+    for (int i = tid; i < words; i += kCountThreads)
+        st_agent(row + i, s_hist[i]);
+    // The counts are written through to where every XCD reads them; once the stores are acknowledged the
+    // arrival may be counted.  A release here would write back the whole L2 of the XCD, once per block
+    // (measured beside the forward kernels: 375 us for this kernel, and those slowed by half).
+    stores_done();
+    __syncthreads();
+    if (tid == 0)
+        s_pick[0] = __hip_atomic_fetch_add(s.arrive + f, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_pick[0] != (uint32_t)(n_chunks - 1))
+        return;
+    const uint32_t *rows = s.chunk_hist + (chunk_row - c) * words;
+    constexpr int kPer = 3 * kMaxRadix / kCountThreads;  // counts of a thread, all of a chunk's in flight together
+    uint32_t sum[kPer] = {};
+    for (int k = 0; k < n_chunks; k++) {
+        uint32_t x[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; i++)
+            x[i] = i * kCountThreads + tid < words ? ld_agent(rows + (size_t)k * words + i * kCountThreads + tid) : 0;
+#pragma unroll
+        for (int i = 0; i < kPer; i++)
+            sum[i] += x[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; i++)
+        if (i * kCountThreads + tid < words)
+            s_hist[i * kCountThreads + tid] = sum[i];
+    __syncthreads();
+    write_bases(s, f, s_hist);
+    if (tid == 0)
+        st_agent(s.arrive + f, 0u);
+}
+
+// ---- one digit ----------------------------------------------------------------------------------------
+// A tile is 4096 entries (512 threads, 8 each; a wave owns 512 consecutive entries and walks them 64 at a
+// time).  Ballots give a lane the lanes that hold its digit, a per-wave digit count in LDS the wave's
+// earlier ones; a prefix over the waves completes the rank.  The entries are then laid out in LDS in
+// digit order, so that a digit's entries (four on average with 10-bit digits) leave as one short run
+// instead of as scattered words.  Bound by the latency of its chain (ticket, keys, ranks, look-back,
+// stores); 40 KB of LDS keep four tiles on a CU.
+template <typename S>
+__global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams g, int pass)
+{
+    __shared__ union {
+        uint16_t run[kWaves][kMaxRadix];       // per wave: entries seen so far per digit
+        struct { uint32_t key[kTile], pay[kTile]; } out;
+    } sh;
+    __shared__ uint32_t s_from[kMaxRadix];     // where the tile's entries of a digit go, less their place in LDS
+    __shared__ uint16_t s_loc[kMaxRadix];      // where they start in LDS
+    __shared__ uint32_t s_tile;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const bool side_a = blockIdx.x < g.a_blocks;
+    const SideParams &s = side_a ? g.a : g.b;
+    // ---- a tile: from the block's own queue while it has any, then from the others ------------------
+    if (tid == 0) {
+        uint32_t tile = ~0u;
+        const int per_q = g.F / kQueues, more = g.F % kQueues;
+        for (int i = 0; i < kQueues && tile == ~0u; i++) {
+            const int q = (int)((blockIdx.x + i) % kQueues);
+            uint32_t q0, q1;
+            if (side_a) {
+                q0 = (uint32_t)((q * per_q + (q < more ? q : more)) * g.tpf);
+                q1 = q0 + (uint32_t)((per_q + (q < more ? 1 : 0)) * g.tpf);
+            } else {
+                q0 = g.queue_start[q];
+                q1 = g.queue_start[q + 1];
+            }
+            if (q1 > q0) {
+                const uint32_t t = __hip_atomic_fetch_add(s.ticket + pass * kQueues + q, 1u, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT);
+                if (t < q1 - q0)
+                    tile = q0 + t;
+            }
+        }
+        s_tile = tile;
+    }
+    const int radix = 1 << s.dbits;
+    for (int i = tid; i < kWaves * kMaxRadix / 2; i += kTileThreads)
+        reinterpret_cast<uint32_t *>(&sh.run[0][0])[i] = 0;
+    __syncthreads();
+    const uint32_t tile = s_tile;
+    if (tile == ~0u)
+        return;  // whole block: no tile left
+    uint32_t f, k, begin, n, tiles_f, f_begin;
+    if (side_a) {
+        const int per_q = g.F / kQueues, more = g.F % kQueues;
+        const uint32_t i = tile / g.tpf;  // the i-th feature in queue order
+        const uint32_t wide = more * (per_q + 1);
+        f = i < wide ? (i % (per_q + 1)) * kQueues + i / (per_q + 1)
+                     : ((i - wide) % per_q) * kQueues + more + (i - wide) / per_q;
+        k = tile % g.tpf;
+        f_begin = (uint32_t)(f * g.B);
+        begin = f_begin + k * kTile;
+        n = (uint32_t)(g.B - (int64_t)k * kTile < kTile ? g.B - (int64_t)k * kTile : kTile);
+        tiles_f = g.tpf;
+    } else {
+        const uint2 d = g.desc_queue[tile];
+        f = d.x;
+        k = d.y;
+        f_begin = g.pb[f];
+        const uint32_t f_end = g.pb[f + 1];
+        begin = f_begin + k * kTile;
+        n = f_end - begin < (uint32_t)kTile ? f_end - begin : (uint32_t)kTile;
+        tiles_f = (f_end - f_begin + kTile - 1) / kTile;
+    }
+    const uint32_t *kin = s.key[(pass + 1) & 1], *pin = s.pay[(pass + 1) & 1];
+    uint32_t *kout = s.key[pass & 1], *pout = s.pay[pass & 1];
+    const int shift = pass * s.dbits;
+    const uint32_t mask = radix - 1;
+
+    // ---- ranks ------------------------------------------------------------------------------------------
+    uint32_t key[kItems], pay[kItems], rank[kItems];
+    const uint32_t wbase = w * (64 * kItems) + lane;
+#pragma unroll
+    for (int u = 0; u < kItems; u++) {
+        const uint32_t i = wbase + u * 64;
+        key[u] = pay[u] = 0;
+        if (i < n) {
+            if (pass > 0) {
+                key[u] = kin[begin + i];
+                pay[u] = pin[begin + i];
+            } else if (side_a) {
+                key[u] = (uint32_t)g.inverse[begin + i];
+                pay[u] = begin + i;
+            } else {
+                key[u] = (uint32_t)g.u_values[begin + i];
+                pay[u] = g.pay_positions ? begin + i : g.pos_list[begin + i];
+            }
+        }
+    }
+    const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int u = 0; u < kItems; u++) {
+        const bool valid = wbase + u * 64 < n;
+        const uint32_t d = (key[u] >> shift) & mask;
+        uint64_t same = __ballot(valid);
+#pragma unroll
+        for (int bit = 0; bit < kMaxBits; bit++) {
+            if (bit < s.dbits) {  // uniform
+                const bool one = (d >> bit) & 1u;
+                const uint64_t bal = __ballot(one);
+                same &= one ? bal : ~bal;
+            }
+        }
+        const uint32_t in_round = (uint32_t)__popcll(same & lt_mask);
+        // entries of this digit in the wave's earlier rounds; the first lane of each digit then adds this
+        // round's (same wave: the read is complete before the write is issued)
+        const uint32_t before = valid ? sh.run[w][d] : 0;
+        __builtin_amdgcn_wave_barrier();
+        if (valid && in_round == 0)
+            sh.run[w][d] = (uint16_t)(before + (uint32_t)__popcll(same));
+        __builtin_amdgcn_wave_barrier();
+        rank[u] = before + in_round;
+    }
+    __syncthreads();
+    // ---- digits d = 2 * tid, 2 * tid + 1: prefix over the waves, count of the tile --------------------------
+    uint32_t cnt[2] = {0, 0};
+    const int d0 = 2 * tid;
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        if (d0 + e < radix) {
+            uint32_t run = 0;
+#pragma unroll
+            for (int ww = 0; ww < kWaves; ww++) {
+                const uint32_t x = sh.run[ww][d0 + e];
+                sh.run[ww][d0 + e] = (uint16_t)run;
+                run += x;
+            }
+            cnt[e] = run;
+        }
+    }
+    S *st = static_cast<S *>(s.status) + ((size_t)pass * s.tiles_cap + (tile - k)) * radix;  // the feature's tiles
+    if (tiles_f > 1) {
+#pragma unroll
+        for (int e = 0; e < 2; e++)
+            if (d0 + e < radix)
+                st_agent(st + (size_t)k * radix + d0 + e, k == 0 ? Word<S>::all(cnt[e]) : Word<S>::own(cnt[e]));
+    }
+    uint32_t total;
+    const uint32_t loc = block_excl<uint32_t, kWaves>(cnt[0] + cnt[1], total);
+    // ---- look-back ------------------------------------------------------------------------------------------
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        const int d = d0 + e;
+        if (d >= radix)
+            continue;
+        uint32_t excl = 0;
+        int64_t j = (int64_t)k - 1;
+        bool done = j < 0;
+        while (!done) {
+            constexpr int W = 8;  // words in flight
+            S x[W];
+#pragma unroll
+            for (int u = 0; u < W; u++)
+                x[u] = j - u >= 0 ? ld_agent(st + (size_t)(j - u) * radix + d) : (S)0;
+            bool stop = false;
+#pragma unroll
+            for (int u = 0; u < W; u++) {
+                const int kind = Word<S>::kind(x[u]);
+                stop = stop || kind == 0;
+                if (!stop && !done) {
+                    excl += Word<S>::count(x[u]);
+                    done = kind == 2;
+                    j--;
+                }
+            }
+            if (!done && stop)
+                __builtin_amdgcn_s_sleep(1);
+        }
+        if (k > 0 && k + 1 < tiles_f)
+            st_agent(st + (size_t)k * radix + d, Word<S>::all(excl + cnt[e]));
+        const uint32_t at = loc + (e ? cnt[0] : 0);
+        s_loc[d] = (uint16_t)at;
+        s_from[d] = f_begin + s.base[((size_t)f * s.passes + pass) * radix + d] + excl - at;
+    }
+    __syncthreads();
+    // ---- into LDS in digit order, then out ---------------------------------------------------------------
+#pragma unroll
+    for (int u = 0; u < kItems; u++)
+        if (wbase + u * 64 < n) {
+            const uint32_t d = (key[u] >> shift) & mask;
+            rank[u] += (uint32_t)s_loc[d] + sh.run[w][d];
+        }
+    __syncthreads();  // the counts have been read: their memory takes the entries
+#pragma unroll
+    for (int u = 0; u < kItems; u++)
+        if (wbase + u * 64 < n) {
+            sh.out.key[rank[u]] = key[u];
+            sh.out.pay[rank[u]] = pay[u];
+        }
+    __syncthreads();
+    const bool weigh = !side_a && g.u_weights && pass == s.passes - 1;
+#pragma unroll
+    for (int u = 0; u < kItems; u++) {
+        const uint32_t i = tid + u * kTileThreads;
+        if (i < n) {
+            const uint32_t kk = sh.out.key[i], pp = sh.out.pay[i];
+            const uint32_t dst = s_from[(kk >> shift) & mask] + i;
+            kout[dst] = kk;
+            if (weigh) {  // the entry's source row and weight, both in sorted order
+                pout[dst] = g.pos_list[pp];
+                g.pay_w[dst] = g.u_weights[pp];
+            } else {
+                pout[dst] = pp;
+            }
+        }
+    }
+}
+
+// ---- segments of equal keys ---------------------------------------------------------------------------
+// Side A: the segment number of a slot is feat_uoff[f] + slot, so starts are written without numbering
+// (a slot that no row names gets an empty segment).  Side B: a head is an entry whose key differs from
+// its predecessor's in the feature; heads are numbered across all tiles in feature order by look-back
+// words that carry the number of heads and the position of the last one, so the block that finds the
+// next head also knows the length of the segment it closes: segments of more than long_seg entries are
+// cut into chunks of 256 entries (larger ones if that would give more than 64).  The cut depends on the
+// length only; the order in which segments and chunks are listed does not matter for the sums.
+__global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupParams g)
+{
+    __shared__ uint32_t s_tile;
+    __shared__ uint64_t s_wave[kWaves];  // heads of a wave (high half), position of its last head + 1
+    __shared__ uint64_t s_before, s_long[2];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (blockIdx.x < g.a_blocks) {
+        const uint32_t *ks = g.a.key[(g.a.passes - 1) & 1];
+        const uint32_t n = (uint32_t)g.n_lists, B = (uint32_t)g.B;
+#pragma unroll
+        for (int u = 0; u < kItems; u++) {
+            const uint32_t i = blockIdx.x * kTile + u * kTileThreads + tid;
+            if (i >= n)
+                break;
+            const uint32_t f = i / B;
+            const int64_t key = ks[i], prev = i == f * B ? -1 : (int64_t)ks[i - 1];
+            const int64_t u0 = g.feat_uoff[f];
+            for (int64_t x = prev + 1; x <= key; x++)  // at most one turn where every slot is named
+                g.seg_start_a[u0 + x] = i;
+            if (i == f * B + (B - 1)) {
+                const int64_t u1 = g.feat_uoff[f + 1];
+                for (int64_t x = u0 + key + 1; x < u1; x++)
+                    g.seg_start_a[x] = (int64_t)i + 1;
+                if ((int)f == g.F - 1) {
+                    g.seg_start_a[u1] = n;
+                    g.list_off_a[0] = 0;
+                    g.list_off_a[1] = u1;
+                }
+            }
+        }
+        return;
+    }
+    const uint32_t total = g.tile_total[0];
+    if (tid == 0)
+        s_tile = __hip_atomic_fetch_add(g.b.ticket + kMaxPasses * kQueues, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const uint32_t tile = s_tile;
+    if (tile >= total) {
+        if (total == 0 && tile == 0) {  // no id anywhere
+            for (int f = tid; f <= g.F; f += kTileThreads)
+                g.feat_roff[f] = 0;
+            if (tid == 0)
+                g.seg_start_b[0] = g.list_off_b[0] = g.list_off_b[1] = 0;
+        }
+        return;
+    }
+    const uint2 dsc = g.desc_feat[tile];
+    const uint32_t f = dsc.x, k = dsc.y;
+    const uint32_t f_end = g.pb[f + 1], begin = g.pb[f] + k * kTile;
+    const uint32_t n = f_end - begin < (uint32_t)kTile ? f_end - begin : (uint32_t)kTile;
+    const uint32_t *ks = g.b.key[(g.b.passes - 1) & 1] + begin;
+    // a wave owns 512 consecutive entries, 64 a round: heads are ballots, their numbers popcounts and the
+    // nearest head before a lane a leading-zero count
+    const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const uint32_t wbase = w * (64 * kItems);
+    uint32_t key[kItems], num[kItems], open[kItems];  // open: position + 1 of the nearest head before, 0: none in the wave
+    uint32_t prev_last = wbase > 0 && wbase < n ? ks[wbase - 1] : (k > 0 && wbase == 0 ? ks[-1] : 0);
+    uint64_t hm[kItems];
+#pragma unroll
+    for (int u = 0; u < kItems; u++) {
+        const uint32_t i = wbase + u * 64 + lane;
+        key[u] = i < n ? ks[i] : 0;
+    }
+    uint32_t heads = 0, last = 0;  // of the wave so far
+#pragma unroll
+    for (int u = 0; u < kItems; u++) {
+        const uint32_t i = wbase + u * 64 + lane;
+        uint32_t prev = __shfl_up(key[u], 1);
+        if (lane == 0)
+            prev = prev_last;
+        prev_last = __shfl(key[u], 63);
+        hm[u] = __ballot(i < n && ((k == 0 && i == 0) || key[u] != prev));
+        const uint64_t below = hm[u] & lt_mask;
+        num[u] = heads + (uint32_t)__popcll(below);
+        open[u] = below ? begin + wbase + u * 64 + (63 - __builtin_clzll(below)) + 1 : last;
+        heads += (uint32_t)__popcll(hm[u]);
+        if (hm[u])
+            last = begin + wbase + u * 64 + (63 - __builtin_clzll(hm[u])) + 1;
+    }
+    if (lane == 0)
+        s_wave[w] = ((uint64_t)heads << 32) | last;
+    __syncthreads();
+    uint32_t wh = 0, wl = 0, all_h = 0, all_l = 0;  // the tile's waves before this one; the tile
+#pragma unroll
+    for (int i = 0; i < kWaves; i++) {
+        const uint32_t h = (uint32_t)(s_wave[i] >> 32), l = (uint32_t)s_wave[i];
+        if (i < w) {
+            wh += h;
+            wl = l > wl ? l : wl;
+        }
+        all_h += h;
+        all_l = l > all_l ? l : all_l;
+    }
+    // look-back word: two bits, heads (31), position of the last head + 1 (31; positions stay below 2^31)
+    constexpr uint64_t m31 = (1ull << 31) - 1;
+    if (w == 0) {
+        uint64_t bh = 0, bl = 0;
+        if (lane == 0)
+            st_agent(g.seg_status + tile, ((uint64_t)(tile == 0 ? 2 : 1) << 62) | ((uint64_t)all_h << 31) | all_l);
+        int64_t j = (int64_t)tile - 1;
+        while (j >= 0) {  // 64 tiles at a time
+            const uint64_t x = j - lane >= 0 ? ld_agent(g.seg_status + (j - lane)) : 0;
+            const uint64_t none = __ballot((x >> 62) == 0), full = __ballot((x >> 62) == 2);
+            const int stop = none ? __builtin_ctzll(none) : 64;      // words from here on are not there yet
+            const int fin = full ? __builtin_ctzll(full) : 64;
+            const int take = fin < stop ? fin + 1 : stop;
+            uint64_t h = lane < take ? (x >> 31) & m31 : 0, l = lane < take ? x & m31 : 0;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                h += __shfl_xor(h, d);
+                const uint64_t y = __shfl_xor(l, d);
+                l = y > l ? y : l;
+            }
+            bh += h;
+            bl = l > bl ? l : bl;
+            if (fin < stop)
+                break;
+            j -= take;
+            if (take == 0)
+                __builtin_amdgcn_s_sleep(1);
+        }
+        if (lane == 0) {
+            if (tile > 0)
+                st_agent(g.seg_status + tile, (2ull << 62) | ((bh + all_h) << 31) | (all_l > bl ? all_l : bl));
+            s_before = (bh << 32) | bl;
+        }
+    }
+    __syncthreads();
+    const uint32_t bh = (uint32_t)(s_before >> 32), bl = (uint32_t)s_before;
+    const uint32_t seg0 = bh + wh, open0 = wl > bl ? wl : bl;
+    // chunks of a segment that is cut
+    auto chunk_of = [&](uint32_t len) { return len > 64 * 256 ? (len + 63) / 64 : 256u; };
+    auto chunks_of = [&](uint32_t len) { return len > (uint32_t)g.long_seg ? (len + chunk_of(len) - 1) / chunk_of(len) : 0u; };
+    uint64_t mine = 0;  // cut segments that this thread's entries close (high half) and their chunks
+#pragma unroll
+    for (int u = 0; u < kItems; u++) {
+        const uint32_t i = wbase + u * 64 + lane, at = begin + i;
+        if ((hm[u] >> lane) & 1) {
+            const uint32_t seg = seg0 + num[u];
+            if (open[u] == 0)
+                open[u] = open0;
+            const uint32_t nch = open[u] ? chunks_of(at + 1 - open[u]) : 0;
+            mine += nch ? (1ull << 32) | nch : 0;
+            g.seg_start_b[seg] = at;
+            g.touched_rows[seg] = key[u];
+            g.seg_feat[seg] = (int32_t)f;
+            if (k == 0 && i == 0) {
+                const int first = tile == 0 ? 0 : (int)g.desc_feat[tile - 1].x + 1;
+                for (int ff = first; ff <= (int)f; ff++)  // features without ids before this one
+                    g.feat_roff[ff] = seg;
+            }
+        }
+    }
+    // the last entry of all closes the list
+    uint32_t tail_seg = 0, tail_open = 0, tail_end = 0;
+    if (tile == total - 1 && tid == 0) {
+        tail_seg = bh + all_h - 1;
+        tail_open = (all_l > bl ? all_l : bl) - 1;
+        tail_end = begin + n;
+        const uint32_t nch = chunks_of(tail_end - tail_open);
+        mine += nch ? (1ull << 32) | nch : 0;
+        g.seg_start_b[tail_seg + 1] = tail_end;
+        g.list_off_b[0] = 0;
+        g.list_off_b[1] = (int64_t)tail_seg + 1;
+        for (int ff = (int)f + 1; ff <= g.F; ff++)
+            g.feat_roff[ff] = (int64_t)tail_seg + 1;
+    }
+    // room for the tile's cut segments: one pair of atomics a tile
+    uint64_t all;
+    const uint64_t ex = block_excl<uint64_t, kWaves>(mine, all);
+    if (all == 0)
+        return;
+    if (tid == 0) {
+        s_long[0] = atomicAdd(reinterpret_cast<unsigned long long *>(g.long_count), (unsigned long long)(all >> 32));
+        s_long[1] = atomicAdd(reinterpret_cast<unsigned long long *>(g.long_count + 1), (unsigned long long)(uint32_t)all);
+    }
+    __syncthreads();
+    uint64_t slot = s_long[0] + (ex >> 32), item = s_long[1] + (uint32_t)ex;
+    auto put = [&](uint32_t seg, uint32_t start, uint32_t end) {
+        const uint32_t nch = chunks_of(end - start), ch = chunk_of(end - start);
+        if (nch == 0)
+            return;
+        g.lseg_t[slot] = (int32_t)seg;
+        g.lseg_first[slot] = (int32_t)item;
+        g.lseg_n[slot] = (int32_t)nch;
+        for (uint32_t c = 0; c < nch; c++) {
+            g.item_start[item + c] = (int64_t)start + c * ch;
+            g.item_end[item + c] = c + 1 < nch ? (int64_t)start + (c + 1) * ch : end;
+        }
+        slot++;
+        item += nch;
+    };
+#pragma unroll
+    for (int u = 0; u < kItems; u++)
+        if (((hm[u] >> lane) & 1) && open[u])
+            put(seg0 + num[u] - 1, open[u] - 1, begin + wbase + u * 64 + lane);
+    if (tail_end)
+        put(tail_seg, tail_open, tail_end);
+}
+
+int bits_for(uint64_t max_value)
+{
+    int b = 1;
+    while (b < 64 && (max_value >> b) != 0)
+        b++;
+    return b;
+}
+
+// Bits of a slot number: a feature has at most B slots, all features U_cap.
+int slot_bits(int64_t B, int64_t U_cap)
+{
+    const int64_t slots = U_cap < B ? U_cap : B;
+    return bits_for((uint64_t)(slots > 1 ? slots - 1 : 1));
+}
+
+// The fewest digits of at most 10 bits, as even as possible.
+void digits_for(int bits, int *passes, int *dbits)
+{
+    *passes = (bits + kMaxBits - 1) / kMaxBits;
+    *dbits = (bits + *passes - 1) / *passes;
+}
+
+int64_t chunk_for(int64_t n)
+{
+    int64_t chunk = kTile;
+    while (n / chunk > 512)
+        chunk *= 2;
+    return chunk;
+}
+
+// Both sides use one width of look-back words.
+bool wide_words(int64_t n_lists, int64_t M_cap) { return (n_lists > M_cap ? n_lists : M_cap) >= (int64_t)1 << 30; }
+
+// Words (digit counts of all passes) of a tile whose keys have at most `bits` bits.  Fewer bits can
+// need more words: 10 bits are one digit of 1024, 14 bits two of 128.
+size_t words_for(int bits)
+{
+    size_t most = 0;
+    for (int b = 1; b <= bits; b++) {
+        int passes, dbits;
+        digits_for(b, &passes, &dbits);
+        const size_t n = (size_t)passes << dbits;
+        most = n > most ? n : most;
+    }
+    return most;
+}
+
+}  // namespace
+
+RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap)
+{
+    RecdGroupWs w{};
+    const int64_t n_lists = (int64_t)F * B;
+    auto side = [&](RecdGroupWs::Side &s, int64_t n, int64_t tiles, int64_t chunks, size_t words_per_tile) {
+        for (int i = 0; i < 2; i++) {
+            s.key[i] = c.take<uint32_t>(n);
+            s.pay[i] = c.take<uint32_t>(n);
+        }
+        s.n_dev = c.take<int64_t>(2);
+        s.tiles_cap = tiles;
+        s.base = c.take<uint32_t>((size_t)F * words_per_tile);
+        s.chunk_hist = c.take<uint32_t>((size_t)chunks * words_per_tile);
+        s.status = wide_words(n_lists, M_cap) ? static_cast<void *>(c.take<uint64_t>((size_t)tiles * words_per_tile))
+                                              : static_cast<void *>(c.take<uint32_t>((size_t)tiles * words_per_tile));
+        s.ticket = c.take<uint32_t>((kMaxPasses + 1) * kQueues);
+    };
+    const int64_t tpf = (B + kTile - 1) / kTile, ch_a = chunk_for(n_lists);
+    side(w.a, n_lists, (int64_t)F * tpf, (int64_t)F * ((B + ch_a - 1) / ch_a), words_for(bits_for((uint64_t)(B > 1 ? B - 1 : 1))));
+    const int64_t tiles_b = M_cap / kTile + F + 1, ch_b = chunk_for(M_cap);
+    // the number of rows of the tables is not known here: ids have at most 31 bits
+    side(w.b, M_cap, tiles_b, M_cap / ch_b + F + 1, words_for(31));
+    w.pb = c.take<uint32_t>(F + 1);
+    w.queue_start = c.take<uint32_t>(kQueues + 1);
+    w.desc_queue = c.take<uint2>(tiles_b);
+    w.desc_feat = c.take<uint2>(tiles_b);
+    w.seg_status = c.take<uint64_t>(tiles_b);
+    w.tile_total = c.take<uint32_t>(1);
+    return w;
+}
+
+const uint32_t *recd_group_rows(const RecdGroupWs &w, int64_t B, int64_t U_cap)
+{
+    int passes, dbits;
+    digits_for(slot_bits(B, U_cap), &passes, &dbits);
+    return w.a.pay[(passes - 1) & 1];
+}
+
+const uint32_t *recd_group_positions(const RecdGroupWs &w, int64_t max_rows)
+{
+    int passes, dbits;
+    digits_for(bits_for((uint64_t)(max_rows > 1 ? max_rows - 1 : 1)), &passes, &dbits);
+    return w.b.pay[(passes - 1) & 1];
+}
+
+recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, const RecdGroupArgs &a)
+{
+    GroupParams g{};
+    g.F = a.F;
+    g.B = a.B;
+    g.M_cap = a.M_cap;
+    g.n_lists = (int64_t)a.F * a.B;
+    g.inverse = a.inverse;
+    g.feat_uoff = a.feat_uoff;
+    g.u_values = a.u_values;
+    g.u_offsets = a.u_offsets;
+    auto side = [&](SideParams &s, const RecdGroupWs::Side &v, int bits, int64_t n, uint32_t *arrive) {
+        for (int i = 0; i < 2; i++) {
+            s.key[i] = v.key[i];
+            s.pay[i] = v.pay[i];
+        }
+        digits_for(bits, &s.passes, &s.dbits);
+        s.base = v.base;
+        s.chunk_hist = v.chunk_hist;
+        s.status = v.status;
+        s.ticket = v.ticket;
+        s.arrive = arrive;
+        s.chunk = chunk_for(n);
+        s.tiles_cap = v.tiles_cap;
+    };
+    side(g.a, w.a, slot_bits(a.B, a.U_cap), g.n_lists, ctx->group_arrive);
+    side(g.b, w.b, bits_for((uint64_t)(a.max_rows > 1 ? a.max_rows - 1 : 1)), a.M_cap, ctx->group_arrive + RECD_MAX_FEATURES);
+    g.tpf = (int)((a.B + kTile - 1) / kTile);
+    g.cpf = (int)((a.B + g.a.chunk - 1) / g.a.chunk);
+    g.pb = w.pb;
+    g.queue_start = w.queue_start;
+    g.desc_queue = w.desc_queue;
+    g.desc_feat = w.desc_feat;
+    g.tile_total = w.tile_total;
+    g.pos_list = a.pos_list;
+    g.pay_positions = a.pay_positions;
+    g.u_weights = a.u_weights;
+    g.pay_w = a.pay_w;
+    g.run_index = a.run_index;
+    g.runs_cap = a.runs_cap;
+    g.n_dev_a = w.a.n_dev;
+    g.n_dev_b = w.b.n_dev;
+    g.seg_status = w.seg_status;
+    g.seg_start_a = a.seg_start_a;
+    g.list_off_a = a.list_off_a;
+    g.seg_start_b = a.seg_start_b;
+    g.list_off_b = a.list_off_b;
+    g.touched_rows = a.touched_rows;
+    g.feat_roff = a.feat_roff;
+    g.seg_feat = a.seg_feat;
+    g.long_count = a.long_count;
+    g.lseg_t = a.lseg_t;
+    g.lseg_first = a.lseg_first;
+    g.lseg_n = a.lseg_n;
+    g.item_start = a.item_start;
+    g.item_end = a.item_end;
+    g.long_seg = a.long_seg;
+    const bool wide = wide_words(g.n_lists, a.M_cap);
+    const unsigned a_tiles = (unsigned)((g.a.tiles_cap + kQueues - 1) / kQueues * kQueues);
+    const unsigned b_tiles = (unsigned)(a.M_cap / kTile + a.F + 1);
+    g.a_blocks = (unsigned)((int64_t)a.F * g.cpf);
+    const unsigned cb = g.a_blocks + (unsigned)(a.M_cap / g.b.chunk + a.F + 1);
+    const size_t lds_a = (size_t)g.a.passes << g.a.dbits, lds_b = ((size_t)g.b.passes << g.b.dbits) + a.F + 1;
+    const size_t lds = (lds_a > lds_b ? lds_a : lds_b) * sizeof(uint32_t);
+    if (wide)
+        hipLaunchKernelGGL(k_group_count<uint64_t>, dim3(cb), dim3(kCountThreads), lds, st, g);
+    else
+        hipLaunchKernelGGL(k_group_count<uint32_t>, dim3(cb), dim3(kCountThreads), lds, st, g);
+    const int passes = g.a.passes > g.b.passes ? g.a.passes : g.b.passes;
+    for (int p = 0; p < passes; p++) {
+        g.a_blocks = p < g.a.passes ? a_tiles : 0;
+        const unsigned nb = g.a_blocks + (p < g.b.passes ? b_tiles : 0);
+        if (wide)
+            hipLaunchKernelGGL(k_group_sweep<uint64_t>, dim3(nb), dim3(kTileThreads), 0, st, g, p);
+        else
+            hipLaunchKernelGGL(k_group_sweep<uint32_t>, dim3(nb), dim3(kTileThreads), 0, st, g, p);
+    }
+    g.a_blocks = (unsigned)((g.n_lists + kTile - 1) / kTile);
+    hipLaunchKernelGGL(k_group_segments, dim3(g.a_blocks + b_tiles), dim3(kTileThreads), 0, st, g);
+    RECD_HIP(ctx, hipGetLastError());
+    return RECD_OK;
+}

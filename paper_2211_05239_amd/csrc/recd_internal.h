@@ -34,28 +34,25 @@ struct recd_ctx {
     hipStream_t stream = nullptr;
     hipStream_t side_stream = nullptr;   // independent work of one call (default priority, non-blocking)
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    // Planned backward: the gradient-independent half (sorts, segment numbering) of a backward pass
-    // runs on two side streams from the end of the last build on, next to the forward calls.
-    hipStream_t side_stream2 = nullptr;
-    hipEvent_t ev_built = nullptr;                    // end of the most recent plain / weighted build
-    hipEvent_t ev_plan_a = nullptr, ev_plan_b = nullptr;   // end of each of the plan's two chains
-    hipEvent_t ev_plan_rows = nullptr;  // step B's segments numbered (before the cut of the long ones)
+    // Planned backward: the gradient-independent half (the grouping) of a backward pass runs on the
+    // side stream from the end of the last build on, next to the forward calls.
+    hipEvent_t ev_built = nullptr;  // end of the most recent plain / weighted build
+    hipEvent_t ev_plan = nullptr;   // end of the plan
     const void *built_inverse = nullptr, *built_u_values = nullptr;  // outputs of that build
     // A call that uses the workspace has been enqueued on the context's stream since that build (set
     // by recd_reserve, cleared by the builder): a plan must then start at the stream's current
-    // position, not at ev_built, or its side streams would write the workspace under that call.
+    // position, not at ev_built, or its side stream would write the workspace under that call.
     bool ws_used_since_build = true;
     // Step B of the backward: table rows with more entries than this are cut into chunks that whole
     // blocks sum (RECD_OPT_LONG_SEGMENT_CUT).
     int long_seg_cut = 32;
     struct BackwardPlan {
-        bool valid = false, empty = false, wide = false;
-        // the side streams may still be working in the workspace: set by recd_backward_plan, cleared
-        // once the context's stream has been made to wait for both of the plan's events
+        bool valid = false, empty = false;
+        // the side stream may still be working in the workspace: set by recd_backward_plan, cleared
+        // once the context's stream has been made to wait for the plan's event
         bool pending = false;
-        int F = 0, D = 0, row_bits = 0;
+        int F = 0, D = 0;
         int64_t B = 0, U_cap = 0, M_cap = 0;
-        const void *ks_a = nullptr;
         const uint32_t *ps_a = nullptr, *ps_b = nullptr;
         const int64_t *u_offsets = nullptr;
         int64_t *touched_rows = nullptr, *feat_roff = nullptr;
@@ -93,6 +90,9 @@ struct recd_ctx {
     // blocks exchange their counts through, all zero between launches.  small_path: 0 = never, 1 =
     // whenever the batch qualifies, 2 = as 1 with every wait between the blocks made to expire.
     uint64_t *small_agg = nullptr;
+    // chunks of a feature that the grouping's counting kernel has seen, [2][RECD_MAX_FEATURES], all
+    // zero between launches
+    uint32_t *group_arrive = nullptr;
     int small_path = 1;
     int timing = 0;  // RECD_OPT_INTERNAL_TIMING
     KernelTimer timers[RECD_T_COUNT];
@@ -221,6 +221,45 @@ struct SegSumArgs {
     hipStream_t stream;       // nullptr: the context's stream
 };
 recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a);
+
+// Grouping of the backward pass (recd_group.hip): the rows of every unique list (side A) and the
+// positions of every (feature, table row) (side B), both by stable sorts inside the features.
+struct RecdGroupWs {
+    struct Side {
+        uint32_t *key[2], *pay[2];
+        int64_t *n_dev;          // [0] entries, [1] the caller's bound was too small
+        int64_t tiles_cap;
+        uint32_t *base, *chunk_hist, *ticket;
+        void *status;
+    } a, b;
+    uint32_t *pb, *queue_start, *tile_total;
+    uint2 *desc_queue, *desc_feat;
+    uint64_t *seg_status;
+};
+struct RecdGroupArgs {
+    int F;
+    int64_t B, U_cap, M_cap, max_rows;
+    const int32_t *inverse;
+    const int64_t *feat_uoff, *u_values, *u_offsets;
+    const int64_t *run_index;    // or null: its count is checked against runs_cap
+    int64_t runs_cap;
+    uint32_t *pos_list;          // [M_cap] out: the list of every position, or null
+    int pay_positions;           // 1: side B's payload is the position j, 0: its list
+    const float *u_weights;      // weighted lookup: the payload of the result is the list, and
+    float *pay_w;                // pay_w the weights in sorted order (pay_positions = 1, pos_list given)
+    int64_t *seg_start_a, *list_off_a;   // rows of list u: payload a[seg_start_a[u] .. seg_start_a[u+1])
+    int64_t *seg_start_b, *list_off_b;   // positions of the t-th distinct row; list_off_b[1] = their number
+    int64_t *touched_rows, *feat_roff;
+    int32_t *seg_feat;
+    int64_t *long_count, *item_start, *item_end;  // segments of side B with more than long_seg entries
+    int32_t *lseg_t, *lseg_first, *lseg_n;
+    int long_seg;
+};
+RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap);
+recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, const RecdGroupArgs &a);
+// The payload buffers that hold the result for these sizes.
+const uint32_t *recd_group_rows(const RecdGroupWs &w, int64_t B, int64_t U_cap);
+const uint32_t *recd_group_positions(const RecdGroupWs &w, int64_t max_rows);
 recd_status recd_validate_inverse(recd_ctx *ctx, int F, int64_t B, const int64_t *feat_uoff,
                                   const int32_t *inverse);
 recd_status recd_validate_kjt_offsets(recd_ctx *ctx, int F, int64_t B, int64_t N, const int64_t *offsets);
