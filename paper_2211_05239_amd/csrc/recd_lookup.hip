@@ -17,11 +17,11 @@
 //     length and content only, never on where the list sits in a batch: the deduplicated and the
 //     non-deduplicated lookup (same W) agree bit for bit.
 //   * blocks are dealt to lists statically (no atomics; the hardware's block dispatch balances the
-//     load).  With F a multiple of 8 the mapping is XCD-aware: block b serves the features
-//     f with f mod 8 = b mod 8, and since consecutive blocks go to consecutive XCDs, the hot rows of
-//     a table stay in one XCD's L2.  The number of lists may live on the device only (unique
-//     lists): the grid is sized from a host-side bound and every block strides until its queue is
-//     exhausted, so any grid size is correct.
+//     load).  The lookups' mapping is XCD-aware: block b serves the (b mod 8)-th contiguous eighth of
+//     the lists, and since consecutive blocks go to consecutive XCDs, the hot rows of a table stay
+//     in one XCD's L2.  The number of lists may live on the device only (unique lists): the grid is
+//     sized from a host-side bound and every block strides until its queue is exhausted, so any grid
+//     size is correct.
 #include "recd_internal.h"
 
 #include <hip/hip_fp16.h>
@@ -159,8 +159,8 @@ struct SegSumParams {
     int F;
     int D;
     int vecs_per_row;  // D / elements per 16-byte vector
-    int nq;            // 8: XCD-aware queues (feature f -> queue f mod 8); 1: one flat queue
-    int lb;            // lists per block item, <= kMaxLB
+    int nq;            // 8: XCD-aware queues (forward sites only); 1: one flat queue
+    int lb;            // lists per block item, <= kMaxLB; 0 (forward sites): chosen by the number of lists
     // optional (flat queue only): list l ends at ends[l] instead of offsets[l+1], and the number of
     // lists is *count_dev
     const int64_t *ends;
@@ -253,7 +253,9 @@ __device__ __forceinline__ void add_chunks(float (*acc)[Elem<TT>::per_vec * VPL]
 }
 
 // Occupancy target: 7 waves per SIMD (72 VGPRs) measured best for one-vector-per-lane fp32 rows; more
-// loads in flight per wave at lower occupancy, or fewer at 8 waves, were both slower.  The
+// loads in flight per wave at lower occupancy, or fewer at 8 waves, were both slower.  The KJT lookup,
+// whose waves share rows through L1, is held to it (16.8 M ids: 8 waves of 61 registers 551 us, 7
+// waves 538); the unique lookup takes the eighth where it fits.  The
 // instantiations that need more registers than that (16-bit tables decode into twice the
 // accumulators, rows of at most 128 bytes put 8 rows into every load, the weighted sum carries
 // the weights: 6 waves for the KJT lookup, 5 for the unique lists) get a lower target instead of
@@ -277,7 +279,8 @@ template <int LPR, int VPL, int TT, int OT, int SITE, int MODE> constexpr int se
 
 template <int LPR, int VPL, int TT, int OT, typename IdxT, int SITE, int MODE = POOL_SUM>
 __global__ __launch_bounds__(SegBlock<SITE>::threads)
-__attribute__((amdgpu_waves_per_eu(segsum_waves<LPR, VPL, TT, OT, SITE, MODE>())))
+__attribute__((amdgpu_waves_per_eu(segsum_waves<LPR, VPL, TT, OT, SITE, MODE>(),
+                                   SITE == SITE_KJT ? segsum_waves<LPR, VPL, TT, OT, SITE, MODE>() : 8)))
 void k_segsum(const SegSumParams p)
 {
     constexpr int kSegBlock = SegBlock<SITE>::threads;
@@ -307,7 +310,7 @@ void k_segsum(const SegSumParams p)
     const int64_t item_stride = nq == 1 ? gridDim.x : gridDim.x / kNQ;
     const int nslots = (p.F - q + nq - 1) / nq;  // features in my queue: q, q+nq, ...
 
-    if constexpr (!EXPAND) {
+    if constexpr (kWaves > 1) {
     for (int f = tid; f <= p.F; f += kSegBlock)
         s_loff[f] = p.list_off ? p.list_off[f] : (int64_t)f * p.lists_per_feature;
     __syncthreads();
@@ -335,7 +338,7 @@ void k_segsum(const SegSumParams p)
     }
     __syncthreads();
     }
-    const int64_t total = EXPAND ? 0 : (p.count_dev ? *p.count_dev : s_qpref[nslots]);
+    const int64_t total = kWaves == 1 ? 0 : (p.count_dev ? *p.count_dev : s_qpref[nslots]);
 
     const int g = lane / LPR;   // lane group = which of the G rows of a load
     const int r = lane % LPR;   // 16-byte piece of the row
@@ -356,16 +359,15 @@ void k_segsum(const SegSumParams p)
                 acc[i] = pool2<MODE>(acc[i], __shfl_xor(acc[i], s));
     };
 
-    // A finished row: lanes of group 0 hold its NACC-element pieces in vals.
-    auto finish_row = [&](int j, float *vals) {
+    // A finished row (list l of len ids): lanes of group 0 hold its NACC-element pieces in vals.
+    auto finish_row = [&](int64_t l, int64_t len, float *vals) {
         if (MODE == POOL_MEAN || MODE == POOL_MAX) {
-            const int64_t len = s_end[j] - s_start[j];
 #pragma unroll
             for (int i = 0; i < NACC; i++)
                 vals[i] = len == 0 ? 0.f : (MODE == POOL_MEAN ? vals[i] / (float)len : vals[i]);
         }
         if ((SITE == SITE_GRAD_LISTS || SITE == SITE_GRAD_STREAM) && p.div_off) {
-            const int64_t n = p.div_off[s_list[j] + 1] - p.div_off[s_list[j]];
+            const int64_t n = p.div_off[l + 1] - p.div_off[l];
             if (n > 0) {
 #pragma unroll
                 for (int i = 0; i < NACC; i++)
@@ -373,7 +375,7 @@ void k_segsum(const SegSumParams p)
             }
         }
         if (g == 0 && piece_ok) {
-            char *dst = static_cast<char *>(p.out) + s_list[j] * out_row_bytes;
+            char *dst = static_cast<char *>(p.out) + l * out_row_bytes;
 #pragma unroll
             for (int w = 0; w < VPL; w++)
                 store_row_piece<OT, EPV, NT>(dst + ((int64_t)w * LPR + r) * OB, vals + w * EPV);
@@ -475,6 +477,69 @@ void k_segsum(const SegSumParams p)
         return;
     }
 
+    if constexpr (kWaves == 1) {
+        // One wave: a lane looks at the first lists of two features, the feature of a list is a count of
+        // ballots, and one load brings the bounds of the block's lists; they wait in 320 bytes of LDS
+        // while rows are gathered (in registers they cost the seventh wave).  (Prefix sums over the
+        // features and 4.6 KB of LDS a wave before; 28 waves of that on a CU also kept blocks of other
+        // streams out.)  Queue q = blockIdx mod 8 (one XCD) takes a contiguous eighth of the lists,
+        // which are feature by feature, so a table's hot rows stay in one L2 whatever the number of
+        // features.
+        const int64_t first = p.list_off ? uniform64(p.list_off[0]) : p.list_base;
+        const int64_t end_all = p.list_off ? uniform64(p.list_off[p.F]) : p.list_base + p.F * p.lists_per_feature;
+        const int64_t all = end_all - first;
+        // lists per block: as many as keep the number of blocks in bounds (measured at 61 K unique lists
+        // and at 1.05 M KJT lists: 1 and 4), by the true number of lists
+        const int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
+        const int64_t per = nq == 1 ? all : ((all + kNQ - 1) / kNQ + lpb - 1) / lpb * lpb;
+        const int64_t q0 = first + q * per, q1 = q0 + per < end_all ? q0 + per : end_all;
+        for (int64_t l0 = q0 + item0 * lpb; l0 < q1; l0 += item_stride * lpb) {
+            const int cnt = (int)(q1 - l0 < lpb ? q1 - l0 : lpb);
+            {
+                int ln = lane;
+                asm volatile("" : "+v"(ln));  // its addresses are made here, not kept over the gathers
+                int64_t fo0 = INT64_MAX, fo1 = INT64_MAX;
+                if (ln < p.F)
+                    fo0 = p.list_off ? p.list_off[ln] : p.list_base + ln * p.lists_per_feature;
+                if (64 + ln < p.F)
+                    fo1 = p.list_off ? p.list_off[64 + ln] : p.list_base + (64 + ln) * p.lists_per_feature;
+                if (ln < cnt) {
+                    const int64_t start = p.offsets[l0 + ln];
+                    s_start[ln] = start;
+                    s_end[ln] = p.lens ? start + p.lens[l0 + ln] : p.offsets[l0 + ln + 1];
+                }
+                for (int j = 0; j < cnt; j++) {
+                    const int f = (int)(__popcll(__ballot(fo0 <= l0 + j)) + __popcll(__ballot(fo1 <= l0 + j))) - 1;
+                    if (lane == 0)
+                        s_feat[j] = f;
+                }
+                __syncthreads();  // a block of one wave: orders the LDS accesses, nobody waits
+            }
+            for (int j = 0; j < cnt; j++) {
+                const int64_t l = l0 + j;
+                const int64_t start = uniform64(s_start[j]);
+                const int64_t len = uniform64(s_end[j]) - start;
+                const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
+                const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
+                float acc[1][NACC];
+#pragma unroll
+                for (int i = 0; i < NACC; i++)
+                    acc[0][i] = pool_identity<MODE>();
+                if (len > kChunk) {
+                    walk_long_list(acc, table, start, start + len);
+                } else {
+                    const int n = (int)len;
+                    add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes,
+                                                                        lane, g, p.weights);
+                }
+                fold_groups(acc[0]);
+                finish_row(l, len, acc[0]);
+            }
+            __syncthreads();
+        }
+        return;
+    }
+
     for (int64_t item = item0; item * lb < total; item += item_stride) {
         const int64_t t0 = item * lb;
         const int cnt = (int)(total - t0 < lb ? total - t0 : lb);
@@ -512,28 +577,20 @@ void k_segsum(const SegSumParams p)
 #pragma unroll
                 for (int i = 0; i < NACC; i++)
                     acc[0][i] = pool_identity<MODE>();
-                if constexpr (kWaves == 1) {
-                    walk_long_list(acc, table, start, end);
-                } else {
-                    for (int64_t base = start + (int64_t)wv * kChunk; base < end; base += kWaves * kChunk) {
-                        const int n = (int)(end - base < kChunk ? end - base : kChunk);
-                        add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, SITE == SITE_GRAD_STREAM>(
-                            acc, &table, values, &base, &n, row_bytes, lane, g, p.weights);
-                    }
+                for (int64_t base = start + (int64_t)wv * kChunk; base < end; base += kWaves * kChunk) {
+                    const int n = (int)(end - base < kChunk ? end - base : kChunk);
+                    add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, SITE == SITE_GRAD_STREAM>(
+                        acc, &table, values, &base, &n, row_bytes, lane, g, p.weights);
                 }
                 fold_groups(acc[0]);
-                if constexpr (kWaves == 1) {
-                    finish_row(j, acc[0]);  // no other wave's partial to add
-                } else {
-                    if (g == 0) {
+                if (g == 0) {
 #pragma unroll
-                        for (int w = 0; w < VPL; w++)
+                    for (int w = 0; w < VPL; w++)
 #pragma unroll
-                            for (int i = 0; i < EPV; i++)
-                                s_part[nb][wv][(w * LPR + r) * EPV + i] = acc[0][w * EPV + i];
-                    }
-                    batch[nb++] = j;
+                        for (int i = 0; i < EPV; i++)
+                            s_part[nb][wv][(w * LPR + r) * EPV + i] = acc[0][w * EPV + i];
                 }
+                batch[nb++] = j;
             }
             if (nb == LL || (j == cnt && nb > 0)) {
                 __syncthreads();
@@ -550,7 +607,7 @@ void k_segsum(const SegSumParams p)
                                 t_ = pool2<MODE>(t_, s_part[e][w2][x]);  // wave order
                             tot[w * EPV + i] = t_;
                         }
-                    finish_row(batch[e], tot);
+                    finish_row(s_list[batch[e]], s_end[batch[e]] - s_start[batch[e]], tot);
                 }
                 __syncthreads();
                 nb = 0;
@@ -572,7 +629,7 @@ void k_segsum(const SegSumParams p)
             add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, SITE == SITE_GRAD_STREAM>(acc, &table, values, &start, &n,
                                                                                    row_bytes, lane, g, p.weights);
             fold_groups(acc[0]);
-            finish_row(j, acc[0]);
+            finish_row(s_list[j], len, acc[0]);
         }
     }
 }
@@ -930,18 +987,18 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     // Launch shape.  Any grid is correct (blocks stride over their queue); these choices only
     // decide how well the chip is filled.
     const int64_t n = a.lists_bound > 0 ? a.lists_bound : 1;
-    p.nq = (a.F >= kNQ && a.F % kNQ == 0 && !a.flat && !ctx->tune_flat && !a.count_dev) ? kNQ : 1;
-    // lists per block: four-wave blocks (backward) take 4 to 16, single-wave blocks (forward) 1 to 4
-    // (measured at 61 K unique lists and at 1.05 M KJT lists: 1 and 4)
-    if (a.site == RECD_SITE_UNIQUE || a.site == RECD_SITE_KJT || a.site == RECD_SITE_UNIQUE_EXPAND)
-        p.lb = n >= (512 << 10) ? 4 : (n >= (128 << 10) ? 2 : 1);
-    else
-        p.lb = n >= (512 << 10) ? 16 : (n >= (128 << 10) ? 8 : 4);
+    const bool one_wave = a.site == RECD_SITE_UNIQUE || a.site == RECD_SITE_KJT || a.site == RECD_SITE_UNIQUE_EXPAND;
+    p.nq = one_wave && !a.flat && !ctx->tune_flat ? kNQ : 1;
+    // lists per block: four-wave blocks (backward) take 4 to 16, single-wave blocks (forward) 1 to 4, by
+    // the number of lists that the kernel finds (0); the grid is sized as if it were the host's bound
+    int lb = one_wave ? (n >= (512 << 10) ? 4 : (n >= (128 << 10) ? 2 : 1))
+                      : (n >= (512 << 10) ? 16 : (n >= (128 << 10) ? 8 : 4));
+    p.lb = one_wave ? 0 : lb;
     if (ctx->tune_lb > 0)
-        p.lb = ctx->tune_lb;
+        p.lb = lb = ctx->tune_lb;
     if (a.count_dev)
-        p.lb = 1;  // chunks of long segments: every list is long, one block per list
-    const int64_t items = (n + p.lb - 1) / p.lb;
+        p.lb = lb = 1;  // chunks of long segments: every list is long, one block per list
+    const int64_t items = (n + lb - 1) / lb;
     int64_t nblk = p.nq == 1 ? items : kNQ * ((items + kNQ - 1) / kNQ + (items / kNQ) / 8 + 1);
     const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : 64);
     if (nblk > cap)
