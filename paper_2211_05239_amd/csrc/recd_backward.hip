@@ -78,8 +78,13 @@ __global__ __launch_bounds__(256) void k_adagrad(const float *__restrict__ grad_
 // few hot rows by thousands).  Here a group of LPR lanes owns a whole segment: G = 64/LPR segments
 // advance side by side in one wave, each lane carries up to four 16-byte pieces of the row, no
 // cross-lane fold is needed, and the Adagrad update of the destination row follows in the same
-// lanes.  Segments longer than the cut (32 or 64 entries, see long_seg_cut) are only recorded; the block-cooperative gather-sum
-// kernel sums them afterwards.  Order of additions inside a segment: ascending position.
+// lanes.  Order of additions inside such a segment: ascending position.
+// A wave lasts as long as its longest segment, so segments longer than the cut (32 entries by default, see
+// long_seg_cut) are cut into chunks, which whole blocks sum: the first blocks of the same launch.  A
+// chunk's entries go to the block's lane groups in turn, the groups' sums are folded by a fixed
+// butterfly and the four waves' in order.  A segment of one chunk is finished on the spot; else the
+// block that arrives last adds the chunks' partial sums in chunk order: what is added in which order
+// depends on the segment's length alone.
 struct RowSumParams {
     const float *table;        // g_u [U, D]
     const uint32_t *pay;       // sorted payload: unique-list index of every position
@@ -89,12 +94,12 @@ struct RowSumParams {
     float *out;                // grad_rows [R, D] or nullptr
     int D;
     int pieces;                // D / 4
-    // segments longer than long_seg entries are cut into chunks (work items) whose partial sums another
-    // kernel computes; lseg_* describe the cut segments, item_* the chunks
-    int64_t *long_count;       // [0] cut segments, [1] chunks
-    int32_t *lseg_t, *lseg_first, *lseg_n;
-    int64_t *item_start, *item_end;
-    const float *partials;     // [chunks, D] (k_long_finalize)
+    // segments longer than long_seg entries are cut into chunks
+    const int64_t *chunk_count;
+    const RecdChunk *chunks;
+    uint32_t *chunk_arrive;    // at a segment's first chunk: its chunks that are summed; zero before the launch
+    float *partials;           // [chunks, D]: sums of the chunks of segments of several
+    unsigned chunk_blocks;     // blocks of the launch that take chunks (a multiple of 8)
     int long_seg;              // segments with more entries than this are the cut ones
 };
 
@@ -152,68 +157,199 @@ __device__ __forceinline__ void finish_segment(const RowSumParams &p, const OptA
     }
 }
 
-// FINALIZE = false: segments of at most p.long_seg entries are summed here (longer ones are skipped).
-// FINALIZE = true: the "segments" are the cut ones; their entries are the chunk partial sums, in
-// chunk order.
-// WT (with FINALIZE = false): entry j contributes pay_w[j] times its source row.
-template <int LPR, bool FINALIZE, bool WT = false>
+// Waits until the memory system has acknowledged this wave's stores.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Destination row of a segment for the update: pointers, and its operands fetched ahead of the sums.
+template <int LPR>
+__device__ __forceinline__ void fetch_row(const OptAdagrad &opt, int D, int f, int64_t row, const bool *piece, int r,
+                                          float4 *wreg, float &mreg, float *&wrow, float *&mp)
+{
+    typedef float f32x4l __attribute__((ext_vector_type(4)));
+    mp = opt.m[f] + row;
+    wrow = opt.w[f] + row * D;
+    mreg = *mp;
+#pragma unroll
+    for (int w = 0; w < 4; w++)
+        if (piece[w]) {
+            const f32x4l t = __builtin_nontemporal_load(reinterpret_cast<const f32x4l *>(wrow) + w * LPR + r);
+            wreg[w] = make_float4(t.x, t.y, t.z, t.w);
+        }
+}
+
+template <bool WT> __device__ __forceinline__ void add4(float4 &acc, const float4 &v, float wt)
+{
+    acc.x = WT ? __fmaf_rn(wt, v.x, acc.x) : acc.x + v.x;
+    acc.y = WT ? __fmaf_rn(wt, v.y, acc.y) : acc.y + v.y;
+    acc.z = WT ? __fmaf_rn(wt, v.z, acc.z) : acc.z + v.z;
+    acc.w = WT ? __fmaf_rn(wt, v.w, acc.w) : acc.w + v.w;
+}
+
+// One chunk of a cut segment, summed by the block.
+template <int LPR, bool WT>
+__device__ __forceinline__ void sum_chunk(const RowSumParams &p, const OptAdagrad &opt, int64_t item, const bool *piece)
+{
+    constexpr int G = 64 / LPR, VPL = 4, W = 256 / 64;
+    __shared__ float4 s_part[W][VPL][LPR];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int g = lane / LPR, r = lane % LPR;
+    const float4 *table = reinterpret_cast<const float4 *>(p.table);
+    const RecdChunk c = p.chunks[item];
+    float4 acc[VPL];
+#pragma unroll
+    for (int w = 0; w < VPL; w++)
+        acc[w] = make_float4(0.f, 0.f, 0.f, 0.f);
+    // entries wv * G + g, + 4 G, ...: two of a group's in flight
+    for (uint32_t i = c.start + wv * G + g; i < c.end; i += 2 * W * G) {
+        const uint32_t i1 = i + W * G;
+        const bool two = i1 < c.end;
+        const uint32_t id0 = p.pay[i], id1 = two ? p.pay[i1] : id0;
+        const float wt0 = WT ? p.pay_w[i] : 1.f, wt1 = WT && two ? p.pay_w[i1] : 1.f;
+        float4 v0[VPL], v1[VPL];
+#pragma unroll
+        for (int w = 0; w < VPL; w++)
+            if (piece[w]) {
+                v0[w] = table[(int64_t)id0 * p.pieces + w * LPR + r];
+                v1[w] = table[(int64_t)id1 * p.pieces + w * LPR + r];
+            }
+#pragma unroll
+        for (int w = 0; w < VPL; w++)
+            if (piece[w]) {
+                add4<WT>(acc[w], v0[w], wt0);
+                if (two)
+                    add4<WT>(acc[w], v1[w], wt1);
+            }
+    }
+#pragma unroll
+    for (int s = LPR; s < 64; s <<= 1)
+#pragma unroll
+        for (int w = 0; w < VPL; w++) {
+            acc[w].x += __shfl_xor(acc[w].x, s);
+            acc[w].y += __shfl_xor(acc[w].y, s);
+            acc[w].z += __shfl_xor(acc[w].z, s);
+            acc[w].w += __shfl_xor(acc[w].w, s);
+        }
+    __syncthreads();  // the previous chunk is done with the shared arrays
+    if (g == 0) {
+#pragma unroll
+        for (int w = 0; w < VPL; w++)
+            s_part[wv][w][r] = acc[w];
+    }
+    __syncthreads();
+    if (wv != 0)
+        return;
+    const bool update = opt.n_feat > 0;
+    float4 wreg[VPL];
+    float mreg = 0.f, *wrow = nullptr, *mp = nullptr;
+#pragma unroll
+    for (int w = 0; w < VPL; w++) {
+        acc[w] = s_part[0][w][r];
+#pragma unroll
+        for (int k = 1; k < W; k++)
+            add4<false>(acc[w], s_part[k][w][r], 1.f);
+    }
+    if (c.n > 1) {
+        // the partial sum goes where every XCD reads it, then the arrival is counted (see the grouping's
+        // counting kernel: no release, which would write back the whole L2)
+        if (g == 0) {
+            uint32_t *dst = reinterpret_cast<uint32_t *>(p.partials + item * p.D);
+#pragma unroll
+            for (int w = 0; w < VPL; w++)
+                if (piece[w]) {
+                    const uint32_t v[4] = {__float_as_uint(acc[w].x), __float_as_uint(acc[w].y), __float_as_uint(acc[w].z),
+                                           __float_as_uint(acc[w].w)};
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        __hip_atomic_store(dst + 4 * (w * LPR + r) + e, v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+        }
+        stores_done();
+        uint32_t before = 0;
+        if (lane == 0)
+            before = __hip_atomic_fetch_add(p.chunk_arrive + c.first, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) != c.n - 1)
+            return;
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int w = 0; w < VPL; w++)
+            acc[w] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (uint32_t k = 0; k < c.n; k++) {
+            const uint32_t *src = reinterpret_cast<const uint32_t *>(p.partials + (int64_t)(c.first + k) * p.D);
+#pragma unroll
+            for (int w = 0; w < VPL; w++)
+                if (piece[w]) {
+                    uint32_t v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        v[e] = __hip_atomic_load(src + 4 * (w * LPR + r) + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    acc[w].x += __uint_as_float(v[0]);
+                    acc[w].y += __uint_as_float(v[1]);
+                    acc[w].z += __uint_as_float(v[2]);
+                    acc[w].w += __uint_as_float(v[3]);
+                }
+        }
+    }
+    if (g != 0)
+        return;
+    if (update)
+        fetch_row<LPR>(opt, p.D, opt.seg_feat[c.seg], opt.touched_rows[c.seg], piece, r, wreg, mreg, wrow, mp);
+    finish_segment<LPR>(p, opt, c.seg, acc, wreg, mreg, wrow, mp, piece, r, update);
+}
+
+// WT: entry j contributes pay_w[j] times its source row.
+template <int LPR, bool WT>
 __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const OptAdagrad opt)
 {
     constexpr int G = 64 / LPR, VPL = 4;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int g = lane / LPR, r = lane % LPR;
-    const int64_t R = FINALIZE ? p.long_count[0] : *p.n_seg;
-    const int per_block = (256 / 64) * G;
-    const float4 *table = reinterpret_cast<const float4 *>(FINALIZE ? p.partials : p.table);
     bool piece[VPL];
 #pragma unroll
     for (int w = 0; w < VPL; w++)
         piece[w] = w * LPR + r < p.pieces;
-
+    if (blockIdx.x < p.chunk_blocks) {
+        const int64_t n = *p.chunk_count;
+        for (int64_t item = blockIdx.x; item < n; item += p.chunk_blocks)
+            sum_chunk<LPR, WT>(p, opt, item, piece);
+        return;
+    }
+    const int64_t R = *p.n_seg;
+    const int per_block = (256 / 64) * G;
+    const float4 *table = reinterpret_cast<const float4 *>(p.table);
     // The segments are ordered by (feature, row) and their entries name rows of the source array that
     // belong to the same feature.  Blocks go to the XCDs in turn; every XCD takes a contiguous eighth
     // of the segments and its blocks stride through it side by side, so that the source rows an XCD
     // gathers at one time are a few features' worth and stay in its L2.
-    // The few cut segments of the FINALIZE pass, and any grid that is not a multiple of 8 blocks, are
-    // dealt to the blocks in turn instead.
-    const bool by_xcd = !FINALIZE && gridDim.x % 8 == 0;
+    const unsigned blk = blockIdx.x - p.chunk_blocks;  // this part of the grid is a multiple of 8 blocks
     const int64_t groups = (R + per_block - 1) / per_block;
     const int64_t per_xcd = (groups + 7) / 8;
-    const int64_t g_first = by_xcd ? (int64_t)(blockIdx.x % 8) * per_xcd : 0;
-    const int64_t g_count = by_xcd ? (per_xcd < groups - g_first ? per_xcd : groups - g_first) : groups;
-    const int64_t g_step = by_xcd ? gridDim.x / 8 : gridDim.x;
-    for (int64_t gi = by_xcd ? blockIdx.x / 8 : blockIdx.x; gi < g_count; gi += g_step) {
-        const int64_t t0 = (g_first + gi) * per_block;
-        const int64_t k = t0 + wv * G + g;
-        int64_t t = k;       // destination segment
+    const int64_t g_first = (int64_t)(blk % 8) * per_xcd;
+    const int64_t g_count = per_xcd < groups - g_first ? per_xcd : groups - g_first;
+    const int64_t g_step = (gridDim.x - p.chunk_blocks) / 8;
+    for (int64_t gi = blk / 8; gi < g_count; gi += g_step) {
+        const int64_t k = (g_first + gi) * per_block + wv * G + g;
         int64_t start = 0;
         int n = 0;
         int f_seg = 0;
         int64_t row_seg = 0;
         if (k < R) {
-            if (FINALIZE) {
-                t = p.lseg_t[k];
-                start = p.lseg_first[k];
-                n = p.lseg_n[k];
-            } else {
-                // one round trip: where the segment lies, and (for the update) which row it is
-                start = p.seg_start[k];
-                const int64_t end = p.seg_start[k + 1];
-                if (opt.n_feat > 0) {
-                    f_seg = opt.seg_feat[k];
-                    row_seg = opt.touched_rows[k];
-                }
-                const int64_t len = end - start;
-                n = len <= p.long_seg ? (int)len : 0;  // longer segments were cut into chunks
+            // one round trip: where the segment lies, and (for the update) which row it is
+            start = p.seg_start[k];
+            const int64_t end = p.seg_start[k + 1];
+            if (opt.n_feat > 0) {
+                f_seg = opt.seg_feat[k];
+                row_seg = opt.touched_rows[k];
             }
+            const int64_t len = end - start;
+            n = len <= p.long_seg ? (int)len : 0;  // longer segments were cut into chunks
         }
         const bool mine = n > 0;  // uniform inside the lane group
         const bool update = mine && opt.n_feat > 0;
         // second round trip: the segment's entries (the first kPre * LPR of them, one load per lane
         // and LPR entries) together with the destination row and its accumulator
-        constexpr int kPre = FINALIZE ? 0 : 4;
-        uint32_t pre[kPre > 0 ? kPre : 1];
-        float prew[kPre > 0 ? kPre : 1];
+        constexpr int kPre = 4;
+        uint32_t pre[kPre];
+        float prew[kPre];
 #pragma unroll
         for (int u = 0; u < kPre; u++) {
             const int idx = u * LPR + r;
@@ -223,23 +359,8 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
         float4 wreg[VPL];
         float mreg = 0.f;
         float *wrow = nullptr, *mp = nullptr;
-        if (update) {
-            if (FINALIZE) {
-                f_seg = opt.seg_feat[t];
-                row_seg = opt.touched_rows[t];
-            }
-            mp = opt.m[f_seg] + row_seg;
-            wrow = opt.w[f_seg] + row_seg * p.D;
-            mreg = *mp;
-#pragma unroll
-            for (int w = 0; w < VPL; w++)
-                if (piece[w])
-                {
-                    typedef float f32x4l __attribute__((ext_vector_type(4)));
-                    const f32x4l t = __builtin_nontemporal_load(reinterpret_cast<const f32x4l *>(wrow) + w * LPR + r);
-                    wreg[w] = make_float4(t.x, t.y, t.z, t.w);
-                }
-        }
+        if (update)
+            fetch_row<LPR>(opt, p.D, f_seg, row_seg, piece, r, wreg, mreg, wrow, mp);
         float4 acc[VPL];
 #pragma unroll
         for (int w = 0; w < VPL; w++)
@@ -253,19 +374,8 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
                     v[w] = table[id * p.pieces + w * LPR + r];
 #pragma unroll
             for (int w = 0; w < VPL; w++)
-                if (piece[w]) {
-                    if (WT) {
-                        acc[w].x = __fmaf_rn(wt, v[w].x, acc[w].x);
-                        acc[w].y = __fmaf_rn(wt, v[w].y, acc[w].y);
-                        acc[w].z = __fmaf_rn(wt, v[w].z, acc[w].z);
-                        acc[w].w = __fmaf_rn(wt, v[w].w, acc[w].w);
-                    } else {
-                        acc[w].x += v[w].x;
-                        acc[w].y += v[w].y;
-                        acc[w].z += v[w].z;
-                        acc[w].w += v[w].w;
-                    }
-                }
+                if (piece[w])
+                    add4<WT>(acc[w], v[w], wt);
         };
         // entries in ascending order: the fetched ones come out of the lane group's registers, any
         // further ones (cuts above kPre * LPR entries) are read one by one
@@ -279,12 +389,10 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
                 add_entry((int64_t)id, wt);
             }
         }
-        for (int i = kPre * LPR; i < n; i++) {
-            const int64_t j = start + i;
-            add_entry(FINALIZE ? j : (int64_t)p.pay[j], WT ? p.pay_w[j] : 1.f);
-        }
+        for (int i = kPre * LPR; i < n; i++)
+            add_entry((int64_t)p.pay[start + i], WT ? p.pay_w[start + i] : 1.f);
         if (mine)
-            finish_segment<LPR>(p, opt, t, acc, wreg, mreg, wrow, mp, piece, r, update);
+            finish_segment<LPR>(p, opt, k, acc, wreg, mreg, wrow, mp, piece, r, update);
     }
 }
 
@@ -528,8 +636,10 @@ struct BwdWs {
     // segments of step A (list_off, seg_start) and of step B (the _b arrays and what follows)
     int64_t *list_off, *seg_start;
     int64_t *list_off_b, *seg_start_b;
-    int32_t *seg_feat, *lseg_t, *lseg_first, *lseg_n;
-    int64_t *long_count, *item_start, *item_end;
+    int32_t *seg_feat;
+    int64_t *chunk_count;
+    RecdChunk *chunks;
+    uint32_t *chunk_arrive;
     float *g_u, *partials;
     uint32_t *pos_list;  // unique list of every position of u_values
     float *pay_w;        // weighted lookup: weight of every sorted entry of step B
@@ -552,7 +662,6 @@ BwdWs carve_bwd(char *base, int F, int64_t B, int64_t M_cap, int D, int long_seg
     BwdWs w;
     (void)c.take<char>(1024);  // the head of the workspace stays with the validation passes' flags
     const int64_t n_lists = (int64_t)F * B;
-    const int64_t n_max = n_lists > M_cap ? n_lists : M_cap;
     int64_t u_cap = M_cap + F < n_lists ? M_cap + F : n_lists;
     w.group = recd_group_carve(c, F, B, M_cap);
     w.list_off = c.take<int64_t>(2);
@@ -560,16 +669,12 @@ BwdWs carve_bwd(char *base, int F, int64_t B, int64_t M_cap, int D, int long_seg
     w.list_off_b = c.take<int64_t>(2);
     w.seg_start_b = c.take<int64_t>(M_cap + 1);
     w.seg_feat = c.take<int32_t>(M_cap);
-    // cut segments (more than long_seg entries): at most n/(long_seg+1) of them, in at most
-    // n/256 + n/(long_seg+1) chunks
+    // at most n/(long_seg+1) segments of more than long_seg entries, in at most n/256 + n/(long_seg+1) chunks
     w.long_seg = long_seg;
-    const int64_t lseg_cap = n_max / (w.long_seg + 1) + 16, item_cap = n_max / 256 + n_max / (w.long_seg + 1) + 16;
-    w.lseg_t = c.take<int32_t>(lseg_cap);
-    w.lseg_first = c.take<int32_t>(lseg_cap);
-    w.lseg_n = c.take<int32_t>(lseg_cap);
-    w.long_count = c.take<int64_t>(2);
-    w.item_start = c.take<int64_t>(item_cap);
-    w.item_end = c.take<int64_t>(item_cap);
+    const int64_t item_cap = M_cap / 256 + M_cap / (w.long_seg + 1) + 16;
+    w.chunk_count = c.take<int64_t>(1);
+    w.chunks = c.take<RecdChunk>(item_cap);
+    w.chunk_arrive = c.take<uint32_t>(item_cap);
     w.partials = c.take<float>((size_t)item_cap * D);
     w.g_u = c.take<float>((size_t)u_cap * D);
     w.pos_list = c.take<uint32_t>(M_cap);
@@ -591,12 +696,9 @@ RowSumParams row_params(const BwdWs &w, const uint32_t *ps, const float *pay_w, 
     rp.out = static_cast<float *>(out);
     rp.D = D;
     rp.pieces = D / 4;
-    rp.long_count = w.long_count;
-    rp.lseg_t = w.lseg_t;
-    rp.lseg_first = w.lseg_first;
-    rp.lseg_n = w.lseg_n;
-    rp.item_start = w.item_start;
-    rp.item_end = w.item_end;
+    rp.chunk_count = w.chunk_count;
+    rp.chunks = w.chunks;
+    rp.chunk_arrive = w.chunk_arrive;
     rp.partials = w.partials;
     rp.long_seg = w.long_seg;
     return rp;
@@ -647,24 +749,20 @@ RecdGroupArgs group_args(const BwdWs &w, int F, int64_t B, int64_t U_cap, int64_
     a.touched_rows = touched_rows;
     a.feat_roff = feat_roff;
     a.seg_feat = w.seg_feat;
-    a.long_count = w.long_count;
-    a.item_start = w.item_start;
-    a.item_end = w.item_end;
-    a.lseg_t = w.lseg_t;
-    a.lseg_first = w.lseg_first;
-    a.lseg_n = w.lseg_n;
+    a.chunk_count = w.chunk_count;
+    a.chunks = w.chunks;
+    a.chunk_arrive = w.chunk_arrive;
     a.long_seg = w.long_seg;
     return a;
 }
 
-// Step B after the grouping: short segments (at most long_seg entries) by one lane group each, the cut
-// ones by the block-cooperative kernel on the side stream next to them; optimizer fused.
+// Step B after the grouping: all segments in one launch, optimizer fused.
 recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t n_cap, int64_t seg_bound,
                      const void *table, int D, void *out, int64_t *touched_rows, const OptAdagrad *opt,
                      const float *pay_w)
 {
     hipStream_t st = ctx->stream;
-    const RowSumParams rp = row_params(w, ps, pay_w, table, D, out);
+    RowSumParams rp = row_params(w, ps, pay_w, table, D, out);
     OptAdagrad o;
     if (opt)
         o = *opt;
@@ -682,57 +780,30 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
     nblk = (nblk + 7) / 8 * 8;  // the kernel deals its blocks to 8 XCDs
     if (nblk < 8)
         nblk = 8;
-    const dim3 block(256);
-    auto launch_rows = [&](auto fin, auto wt, unsigned nb, hipStream_t stream) {
-        constexpr bool FIN = decltype(fin)::value, WT = decltype(wt)::value;
-        const dim3 grid(nb);
+    // blocks for the chunks: their number is on the device, usually far below the bound: at most what the
+    // chip holds at once, striding
+    int64_t cblk = n_cap / 256 + n_cap / (w.long_seg + 1);
+    if (cblk > (int64_t)ctx->num_cu * 8)
+        cblk = (int64_t)ctx->num_cu * 8;
+    rp.chunk_blocks = (unsigned)((cblk + 7) / 8 * 8);
+    const dim3 grid((unsigned)(nblk + rp.chunk_blocks)), block(256);
+    recd_time_begin(ctx, RECD_T_GRAD_ROWS, st);
+    auto launch = [&](auto wt) {
+        constexpr bool WT = decltype(wt)::value;
         switch (lpr) {
-        case 4: hipLaunchKernelGGL((k_segsum_rows<4, FIN, WT>), grid, block, 0, stream, rp, o); break;
-        case 8: hipLaunchKernelGGL((k_segsum_rows<8, FIN, WT>), grid, block, 0, stream, rp, o); break;
-        case 16: hipLaunchKernelGGL((k_segsum_rows<16, FIN, WT>), grid, block, 0, stream, rp, o); break;
-        case 32: hipLaunchKernelGGL((k_segsum_rows<32, FIN, WT>), grid, block, 0, stream, rp, o); break;
-        default: hipLaunchKernelGGL((k_segsum_rows<64, FIN, WT>), grid, block, 0, stream, rp, o); break;
+        case 4: hipLaunchKernelGGL((k_segsum_rows<4, WT>), grid, block, 0, st, rp, o); break;
+        case 8: hipLaunchKernelGGL((k_segsum_rows<8, WT>), grid, block, 0, st, rp, o); break;
+        case 16: hipLaunchKernelGGL((k_segsum_rows<16, WT>), grid, block, 0, st, rp, o); break;
+        case 32: hipLaunchKernelGGL((k_segsum_rows<32, WT>), grid, block, 0, st, rp, o); break;
+        default: hipLaunchKernelGGL((k_segsum_rows<64, WT>), grid, block, 0, st, rp, o); break;
         }
     };
-    // 1. on the side stream: partial sum of every chunk of the cut segments (block-cooperative
-    //    gather-sum, one block per chunk), then the chunk partials added in chunk order and the same
-    //    update / store as for short segments.  Long and short segments name different rows.
-    hipStream_t side = ctx->side_stream;
-    RECD_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
-    RECD_HIP(ctx, hipStreamWaitEvent(side, ctx->ev_fork, 0));
-    SegSumArgs c{};
-    c.site = RECD_SITE_GRAD_LISTS;
-    c.F = 1;
-    c.D = D;
-    c.table_dt = RECD_F32;
-    c.out_dt = RECD_F32;
-    c.tables.p[0] = table;
-    c.values = ps;
-    c.values_are_i32 = 1;
-    c.flat = 1;
-    c.offsets = w.item_start;
-    c.ends = w.item_end;
-    c.count_dev = w.long_count + 1;
-    c.lists_bound = n_cap / 256 + n_cap / (w.long_seg + 1) + 1;
-    c.out = w.partials;
-    c.stream = side;
-    if (pay_w) {  // the chunk partials carry the weights; adding the partials does not
-        c.mode = 3;
-        c.weights = pay_w;
-    }
-    RECD_TRY(recd_launch_segsum(ctx, c));
-    launch_rows(std::true_type(), std::false_type(), (unsigned)((ctx->num_cu + 7) / 8 * 8), side);
-    RECD_HIP(ctx, hipGetLastError());
-    RECD_HIP(ctx, hipEventRecord(ctx->ev_join, side));
-    // 2. short segments summed and updated
-    recd_time_begin(ctx, RECD_T_GRAD_ROWS, st);
     if (pay_w)
-        launch_rows(std::false_type(), std::true_type(), (unsigned)nblk, st);
+        launch(std::true_type());
     else
-        launch_rows(std::false_type(), std::false_type(), (unsigned)nblk, st);
+        launch(std::false_type());
     recd_time_end(ctx, RECD_T_GRAD_ROWS, st);
     RECD_HIP(ctx, hipGetLastError());
-    RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_join, 0));
     return RECD_OK;
 }
 

@@ -253,7 +253,6 @@ recd_status recd_create(recd_ctx **out, int device, void *hip_stream, size_t wor
     ok = ok && hipEventCreateWithFlags(&ctx->ev_built, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->ev_plan, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming) == hipSuccess;
     void *p = nullptr;
     ok = ok && hipHostMalloc(&p, 8 * sizeof(int64_t), hipHostMallocDefault) == hipSuccess;
     ctx->host_pinned = static_cast<int64_t *>(p);
@@ -318,8 +317,6 @@ recd_status recd_destroy(recd_ctx *ctx)
         (void)hipEventDestroy(ctx->ev_plan);
     if (ctx->ev_fork)
         (void)hipEventDestroy(ctx->ev_fork);
-    if (ctx->ev_join)
-        (void)hipEventDestroy(ctx->ev_join);
     if (ctx->ws)
         (void)hipFree(ctx->ws);
     if (ctx->group_map_dev)

@@ -125,9 +125,9 @@ struct GroupParams {
     int64_t *seg_start_a, *list_off_a, *seg_start_b, *list_off_b;
     int64_t *touched_rows, *feat_roff;
     int32_t *seg_feat;
-    int64_t *long_count;        // [0] segments that are cut, [1] their chunks
-    int32_t *lseg_t, *lseg_first, *lseg_n;
-    int64_t *item_start, *item_end;
+    int64_t *chunk_count;       // chunks of the segments that are cut
+    RecdChunk *chunks;
+    uint32_t *chunk_arrive;
     int long_seg;
 };
 
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
                 const int64_t M = g.u_offsets[g.feat_uoff[g.F]];
                 g.n_dev_b[0] = M < g.M_cap ? M : g.M_cap;
                 g.n_dev_b[1] = M > g.M_cap ? 1 : 0;
-                g.long_count[0] = g.long_count[1] = 0;
+                g.chunk_count[0] = 0;
             }
         }
         __syncthreads();
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
 {
     __shared__ uint32_t s_tile;
     __shared__ uint64_t s_wave[kWaves];  // heads of a wave (high half), position of its last head + 1
-    __shared__ uint64_t s_before, s_long[2];
+    __shared__ uint64_t s_before, s_chunk0;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (blockIdx.x < g.a_blocks) {
         const uint32_t *ks = g.a.key[(g.a.passes - 1) & 1];
@@ -747,7 +747,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
     // chunks of a segment that is cut
     auto chunk_of = [&](uint32_t len) { return len > 64 * 256 ? (len + 63) / 64 : 256u; };
     auto chunks_of = [&](uint32_t len) { return len > (uint32_t)g.long_seg ? (len + chunk_of(len) - 1) / chunk_of(len) : 0u; };
-    uint64_t mine = 0;  // cut segments that this thread's entries close (high half) and their chunks
+    uint32_t mine = 0;  // chunks of the segments that this thread's entries close
 #pragma unroll
     for (int u = 0; u < kItems; u++) {
         const uint32_t i = wbase + u * 64 + lane, at = begin + i;
@@ -755,8 +755,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
             const uint32_t seg = seg0 + num[u];
             if (open[u] == 0)
                 open[u] = open0;
-            const uint32_t nch = open[u] ? chunks_of(at + 1 - open[u]) : 0;
-            mine += nch ? (1ull << 32) | nch : 0;
+            mine += open[u] ? chunks_of(at + 1 - open[u]) : 0;
             g.seg_start_b[seg] = at;
             g.touched_rows[seg] = key[u];
             g.seg_feat[seg] = (int32_t)f;
@@ -773,38 +772,29 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
         tail_seg = bh + all_h - 1;
         tail_open = (all_l > bl ? all_l : bl) - 1;
         tail_end = begin + n;
-        const uint32_t nch = chunks_of(tail_end - tail_open);
-        mine += nch ? (1ull << 32) | nch : 0;
+        mine += chunks_of(tail_end - tail_open);
         g.seg_start_b[tail_seg + 1] = tail_end;
         g.list_off_b[0] = 0;
         g.list_off_b[1] = (int64_t)tail_seg + 1;
         for (int ff = (int)f + 1; ff <= g.F; ff++)
             g.feat_roff[ff] = (int64_t)tail_seg + 1;
     }
-    // room for the tile's cut segments: one pair of atomics a tile
-    uint64_t all;
-    const uint64_t ex = block_excl<uint64_t, kWaves>(mine, all);
+    // room for the tile's chunks: one atomic a tile
+    uint32_t all;
+    const uint32_t ex = block_excl<uint32_t, kWaves>(mine, all);
     if (all == 0)
         return;
-    if (tid == 0) {
-        s_long[0] = atomicAdd(reinterpret_cast<unsigned long long *>(g.long_count), (unsigned long long)(all >> 32));
-        s_long[1] = atomicAdd(reinterpret_cast<unsigned long long *>(g.long_count + 1), (unsigned long long)(uint32_t)all);
-    }
+    if (tid == 0)
+        s_chunk0 = atomicAdd(reinterpret_cast<unsigned long long *>(g.chunk_count), (unsigned long long)all);
     __syncthreads();
-    uint64_t slot = s_long[0] + (ex >> 32), item = s_long[1] + (uint32_t)ex;
+    uint32_t item = (uint32_t)s_chunk0 + ex;
     auto put = [&](uint32_t seg, uint32_t start, uint32_t end) {
-        const uint32_t nch = chunks_of(end - start), ch = chunk_of(end - start);
+        const uint32_t nch = chunks_of(end - start), ch = chunk_of(end - start), first = item;
         if (nch == 0)
             return;
-        g.lseg_t[slot] = (int32_t)seg;
-        g.lseg_first[slot] = (int32_t)item;
-        g.lseg_n[slot] = (int32_t)nch;
-        for (uint32_t c = 0; c < nch; c++) {
-            g.item_start[item + c] = (int64_t)start + c * ch;
-            g.item_end[item + c] = c + 1 < nch ? (int64_t)start + (c + 1) * ch : end;
-        }
-        slot++;
-        item += nch;
+        g.chunk_arrive[first] = 0;
+        for (uint32_t c = 0; c < nch; c++)
+            g.chunks[item++] = RecdChunk{start + c * ch, c + 1 < nch ? start + (c + 1) * ch : end, seg, first, nch};
     };
 #pragma unroll
     for (int u = 0; u < kItems; u++)
@@ -958,12 +948,9 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     g.touched_rows = a.touched_rows;
     g.feat_roff = a.feat_roff;
     g.seg_feat = a.seg_feat;
-    g.long_count = a.long_count;
-    g.lseg_t = a.lseg_t;
-    g.lseg_first = a.lseg_first;
-    g.lseg_n = a.lseg_n;
-    g.item_start = a.item_start;
-    g.item_end = a.item_end;
+    g.chunk_count = a.chunk_count;
+    g.chunks = a.chunks;
+    g.chunk_arrive = a.chunk_arrive;
     g.long_seg = a.long_seg;
     const bool wide = wide_words(g.n_lists, a.M_cap);
     const unsigned a_tiles = (unsigned)((g.a.tiles_cap + kQueues - 1) / kQueues * kQueues);

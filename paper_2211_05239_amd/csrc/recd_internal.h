@@ -33,7 +33,7 @@ struct recd_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     hipStream_t side_stream = nullptr;   // independent work of one call (default priority, non-blocking)
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    hipEvent_t ev_fork = nullptr;
     // Planned backward: the gradient-independent half (the grouping) of a backward pass runs on the
     // side stream from the end of the last build on, next to the forward calls.
     hipEvent_t ev_built = nullptr;  // end of the most recent plain / weighted build
@@ -183,11 +183,10 @@ struct OptAdagrad {
 
 // ---- cross-file entry points (host side launchers) -------------------------------------------
 // Exclusive scan of n int64 pairs is private to each file; the segmented gather-sum is shared.
-// GRAD_STREAM: as GRAD_LISTS, for source rows that are read once (step A reads every grad_out row
-// exactly once): their loads bypass the caches' retention.
+// GRAD_STREAM: step A of the backward reads every grad_out row exactly once: the loads bypass the
+// caches' retention.
 // UNIQUE_EXPAND: the unique lookup that also writes the output rows of every list's first run.
-enum { RECD_SITE_UNIQUE = 0, RECD_SITE_KJT = 1, RECD_SITE_GRAD_LISTS = 2, RECD_SITE_GRAD_STREAM = 3,
-       RECD_SITE_UNIQUE_EXPAND = 4 };
+enum { RECD_SITE_UNIQUE = 0, RECD_SITE_KJT = 1, RECD_SITE_GRAD_STREAM = 3, RECD_SITE_UNIQUE_EXPAND = 4 };
 struct SegSumArgs {
     int F;                    // features in this launch (<= RECD_F_PER_LAUNCH)
     int D;
@@ -201,8 +200,6 @@ struct SegSumArgs {
     int64_t list_base;        // added to every list index (feature chunking of the KJT path)
     int64_t lists_bound;      // host upper bound of the number of lists in this launch (sizes the grid)
     int flat;                 // 1: no XCD-aware feature->block mapping
-    const int64_t *ends;            // optional (single table, flat): list l ends at ends[l] ...
-    const int64_t *count_dev;       // ... and the number of lists lives on the device
     const int64_t *lens;            // optional: list l spans offsets[l] .. offsets[l] + lens[l]
     const float *weights;           // mode 3 (weighted sum): one fp32 weight per id, beside values
     const int64_t *div_off;         // optional (backward sums only): the finished row of list l is
@@ -236,6 +233,11 @@ struct RecdGroupWs {
     uint2 *desc_queue, *desc_feat;
     uint64_t *seg_status;
 };
+// A chunk of a segment with many entries: entries [start, end) of segment seg, whose n chunks are listed
+// from chunk `first` on.
+struct RecdChunk {
+    uint32_t start, end, seg, first, n;
+};
 struct RecdGroupArgs {
     int F;
     int64_t B, U_cap, M_cap, max_rows;
@@ -251,8 +253,9 @@ struct RecdGroupArgs {
     int64_t *seg_start_b, *list_off_b;   // positions of the t-th distinct row; list_off_b[1] = their number
     int64_t *touched_rows, *feat_roff;
     int32_t *seg_feat;
-    int64_t *long_count, *item_start, *item_end;  // segments of side B with more than long_seg entries
-    int32_t *lseg_t, *lseg_first, *lseg_n;
+    int64_t *chunk_count;        // chunks of the segments of side B with more than long_seg entries, and
+    RecdChunk *chunks;           // a zero for each segment, at its first chunk
+    uint32_t *chunk_arrive;
     int long_seg;
 };
 RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap);

@@ -1,7 +1,7 @@
 // Segmented row gather-sum (the pooled embedding lookup), the inverse expand, and input validation.
 //
 // One kernel body serves the deduplicated lookup on an IKJT's unique lists, the non-deduplicated
-// KJT lookup and both segment reductions of the backward pass: "for every list l, sum the table
+// KJT lookup and the backward's sum over the rows of every unique list: "for every list l, sum the table
 // rows named by values[offsets[l] .. offsets[l+1]) and store the sum as row l of the output".
 //
 // Mapping to the machine (gfx950: 64-lane waves, 8 XCDs each with a private L2):
@@ -34,7 +34,7 @@ constexpr int kBlock = 256;
 // waves of a block finish their lists at different times, and a block's registers are only free
 // again when its last wave is done, so with lists of 1 to 256 ids a four-wave block keeps idle
 // waves resident (unique lookup 0.124 ms against 0.133, KJT lookup 0.99 against 1.16).  The
-// backward's sums keep four waves: their long segments and 256-entry chunks want the whole block.
+// backward's sum keeps four waves: its long segments want the whole block.
 template <int SITE> struct SegBlock {
     static constexpr int threads = (SITE == 0 || SITE == 1 || SITE == 4) ? 64 : 256;
 };
@@ -142,11 +142,11 @@ template <int OT, int N, bool NT> __device__ __forceinline__ void store_row_piec
 }
 
 // Call sites of the gather-sum kernel.  Each gets its own instantiation (and symbol): the unique
-// lookup, the KJT comparison lookup, and the backward's sums over grad_out rows / chunk partials.
+// lookup, the KJT comparison lookup, and the backward's sums over grad_out rows.
 // SITE_UNIQUE_EXPAND: the unique lookup whose waves also store a finished row to the output rows of
 // the run of adjacent samples that starts at the list's first row (Sec. 5: lookup on the unique
 // lists, then the index select back to the batch - here for the samples a session put side by side).
-enum { SITE_UNIQUE = 0, SITE_KJT = 1, SITE_GRAD_LISTS = 2, SITE_GRAD_STREAM = 3, SITE_UNIQUE_EXPAND = 4 };
+enum { SITE_UNIQUE = 0, SITE_KJT = 1, SITE_GRAD_STREAM = 3, SITE_UNIQUE_EXPAND = 4 };
 
 struct SegSumParams {
     TablePtrs tables;
@@ -161,13 +161,9 @@ struct SegSumParams {
     int vecs_per_row;  // D / elements per 16-byte vector
     int nq;            // 8: XCD-aware queues (forward sites only); 1: one flat queue
     int lb;            // lists per block item, <= kMaxLB; 0 (forward sites): chosen by the number of lists
-    // optional (flat queue only): list l ends at ends[l] instead of offsets[l+1], and the number of
-    // lists is *count_dev
-    const int64_t *ends;
-    const int64_t *count_dev;
     // optional: list l spans offsets[l] .. offsets[l] + lens[l] (windows of a partial IKJT)
     const int64_t *lens;
-    // optional (SITE_GRAD_LISTS only): the finished row of list l is divided by
+    // optional (SITE_GRAD_STREAM only): the finished row of list l is divided by
     // div_off[l+1] - div_off[l] when that is positive (backward of average pooling)
     const int64_t *div_off;
     // POOL_WSUM: one fp32 weight per id, aligned with values
@@ -338,7 +334,7 @@ void k_segsum(const SegSumParams p)
     }
     __syncthreads();
     }
-    const int64_t total = kWaves == 1 ? 0 : (p.count_dev ? *p.count_dev : s_qpref[nslots]);
+    const int64_t total = kWaves == 1 ? 0 : s_qpref[nslots];
 
     const int g = lane / LPR;   // lane group = which of the G rows of a load
     const int r = lane % LPR;   // 16-byte piece of the row
@@ -366,7 +362,7 @@ void k_segsum(const SegSumParams p)
             for (int i = 0; i < NACC; i++)
                 vals[i] = len == 0 ? 0.f : (MODE == POOL_MEAN ? vals[i] / (float)len : vals[i]);
         }
-        if ((SITE == SITE_GRAD_LISTS || SITE == SITE_GRAD_STREAM) && p.div_off) {
+        if (SITE == SITE_GRAD_STREAM && p.div_off) {
             const int64_t n = p.div_off[l + 1] - p.div_off[l];
             if (n > 0) {
 #pragma unroll
@@ -555,12 +551,12 @@ void k_segsum(const SegSumParams p)
                     hi = mid;
             }
             const int f = q + lo * nq;
-            const int64_t l = p.count_dev ? t : p.list_base + s_loff[f] + (t - s_qpref[lo]);
+            const int64_t l = p.list_base + s_loff[f] + (t - s_qpref[lo]);
             s_feat[tid] = f;
             s_list[tid] = l;
             const int64_t start = p.offsets[l];
             s_start[tid] = start;
-            s_end[tid] = p.ends ? p.ends[l] : (p.lens ? start + p.lens[l] : p.offsets[l + 1]);
+            s_end[tid] = p.lens ? start + p.lens[l] : p.offsets[l + 1];
         }
         __syncthreads();
 
@@ -969,8 +965,6 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     p.lists_per_feature = a.lists_per_feature;
     p.list_base = a.list_base;
     p.out = a.out;
-    p.ends = a.ends;
-    p.count_dev = a.count_dev;
     p.lens = a.lens;
     p.div_off = a.div_off;
     p.weights = a.weights;
@@ -996,17 +990,11 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     p.lb = one_wave ? 0 : lb;
     if (ctx->tune_lb > 0)
         p.lb = lb = ctx->tune_lb;
-    if (a.count_dev)
-        p.lb = lb = 1;  // chunks of long segments: every list is long, one block per list
     const int64_t items = (n + lb - 1) / lb;
     int64_t nblk = p.nq == 1 ? items : kNQ * ((items + kNQ - 1) / kNQ + (items / kNQ) / 8 + 1);
     const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : 64);
     if (nblk > cap)
         nblk = cap / kNQ * kNQ;
-    // a pass whose true list count lives on the device is usually far below the host bound: a
-    // resident-sized grid that strides wastes no blocks
-    if (a.count_dev && nblk > (int64_t)ctx->num_cu * 8)
-        nblk = (int64_t)ctx->num_cu * 8;
     if (a.site == RECD_SITE_UNIQUE_EXPAND) {
         // one run per block and turn; the kernel deals the runs to eight queues by their true number
         p.lb = 1;
@@ -1045,15 +1033,9 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
         ok = launch_forward<SITE_UNIQUE, POOL_WSUM>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_WSUM && a.weights)
         ok = launch_forward<SITE_KJT, POOL_WSUM>(st, blocks, v, a, p);
-    else if (a.site == RECD_SITE_GRAD_LISTS && a.values_are_i32 && a.table_dt == RECD_F32 &&
-             a.out_dt == RECD_F32 && a.mode == POOL_SUM)
-        ok = launch_shape<RECD_F32, RECD_F32, int32_t, SITE_GRAD_LISTS>(st, blocks, v, p);
     else if (a.site == RECD_SITE_GRAD_STREAM && a.values_are_i32 && a.table_dt == RECD_F32 &&
              a.out_dt == RECD_F32 && a.mode == POOL_SUM)
         ok = launch_shape<RECD_F32, RECD_F32, int32_t, SITE_GRAD_STREAM>(st, blocks, v, p);
-    else if (a.site == RECD_SITE_GRAD_LISTS && a.values_are_i32 && a.table_dt == RECD_F32 &&
-             a.out_dt == RECD_F32 && a.mode == POOL_WSUM && a.weights)
-        ok = launch_shape<RECD_F32, RECD_F32, int32_t, SITE_GRAD_LISTS, POOL_WSUM>(st, blocks, v, p);
     if (slot >= 0)
         recd_time_end(ctx, slot, st);
     if (!ok)
