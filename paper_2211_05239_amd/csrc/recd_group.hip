@@ -44,17 +44,6 @@ __device__ __forceinline__ void st_agent(uint64_t *p, uint64_t v) { __hip_atomic
 // Waits until the memory system has acknowledged this wave's stores.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// A look-back word: the count below, two bits on top (0: nothing yet, 1: the tile's own count, 2: the
-// count of the tile and all tiles of the feature before it).  32-bit words hold 2^30 entries; the
-// 64-bit form serves larger sides.
-template <typename S> struct Word {
-    static constexpr int shift = sizeof(S) * 8 - 2;
-    static __device__ __forceinline__ S own(uint32_t c) { return ((S)1 << shift) | c; }
-    static __device__ __forceinline__ S all(uint32_t c) { return ((S)2 << shift) | c; }
-    static __device__ __forceinline__ int kind(S w) { return (int)(w >> shift); }
-    static __device__ __forceinline__ uint32_t count(S w) { return (uint32_t)(w & (((S)1 << shift) - 1)); }
-};
-
 // Inclusive sums over a wave.
 template <typename T> __device__ __forceinline__ T wave_incl(T v, int lane)
 {
@@ -92,7 +81,8 @@ struct SideParams {
     int passes, dbits;
     uint32_t *base;             // [F][passes][radix]: where a digit starts inside the feature
     uint32_t *chunk_hist;       // [chunks][passes][radix] (features of several chunks only)
-    void *status;               // [passes][tiles][radix] look-back words
+    uint32_t *own, *upto;       // [tiles][radix] look-back: a tile's counts, and those of it and all before it
+    uint32_t *flag;             // [passes][tiles] 0: nothing yet, 1: own is there, 2: upto is
     uint32_t *ticket;           // [kMaxPasses + 1][kQueues]
     uint32_t *arrive;           // [F] chunks of a feature that have been counted; zero between launches
     int64_t chunk;              // entries per block of k_group_count
@@ -160,10 +150,9 @@ __device__ __forceinline__ void write_bases(const SideParams &s, int f, const ui
 // A block takes a chunk of one feature's entries (a tile, or as many as keep the chunks below some 500),
 // counts the digits of all passes in LDS and, where the feature is a single chunk, turns the counts into
 // digit starts at once; else the block that arrives last adds up the feature's chunks.  The block also
-// clears the look-back words of its tiles, and on side B writes the list of every position.  What is
+// clears the look-back flags of its tiles, and on side B writes the list of every position.  What is
 // read is small (8 bytes an entry): the kernel is a few dependent round trips and the LDS atomics of a
 // chunk. 
-template <typename S>
 __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams g)
 {
     extern __shared__ uint32_t s_dyn[];          // the counts [passes * radix], side B also pb [F+1]: as little
@@ -299,18 +288,37 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
             key[u] = i < n ? (side_a ? (uint32_t)g.inverse[begin + i] : (uint32_t)g.u_values[begin + i]) : 0u;
         }
 #pragma unroll
-        for (int u = 0; u < 16; u++)
-            if (i0 + u * kCountThreads < n)
+        for (int u = 0; u < 16; u++) {
+            // Side A comes in runs of one slot (the samples of a session): the first lane of a run counts for
+            // all of it, where every lane's own atomic would queue at one address.
+            const bool on = i0 + u * kCountThreads < n;
+            uint32_t many = 1;
+            bool count = on;
+            if (side_a) {
+                const uint32_t left = __shfl_up(key[u], 1);
+                const int ln = tid & 63;
+                count = on && (ln == 0 || left != key[u]);
+                const uint64_t heads = __ballot(count), live = __ballot(on);
+                const uint64_t above = ln == 63 ? 0 : heads >> (ln + 1);
+                many = above ? (uint32_t)__builtin_ctzll(above) + 1 : (uint32_t)__popcll(live) - ln;
+            }
+            if (count)
                 for (int p = 0; p < s.passes; p++)
-                    atomicAdd(&s_hist[p * radix + ((key[u] >> (p * s.dbits)) & mask)], 1u);
-    }
-    if (tiles_f > 1) {  // a feature of one tile looks back nowhere
-        const size_t words = (size_t)((n + kTile - 1) / kTile) * radix;
-        for (int p = 0; p < s.passes; p++) {
-            S *st = static_cast<S *>(s.status) + ((size_t)p * s.tiles_cap + first_tile) * radix;
-            for (size_t i = tid; i < words; i += kCountThreads)
-                st[i] = 0;
+                    atomicAdd(&s_hist[p * radix + ((key[u] >> (p * s.dbits)) & mask)], many);
         }
+    }
+    // look-back flags of the chunk's tiles
+    for (int i = tid; i < (int)((n + kTile - 1) / kTile) * s.passes; i += kCountThreads)
+        s.flag[(size_t)(i % s.passes) * s.tiles_cap + first_tile + i / s.passes] = 0;
+    // a feature's counts leave before the lists are written: acknowledged by the time the arrival is counted
+    const int words = s.passes * radix;
+    __syncthreads();
+    if (n_chunks == 1) {
+        write_bases(s, f, s_hist);
+    } else {
+        uint32_t *row = s.chunk_hist + chunk_row * words;
+        for (int i = tid; i < words; i += kCountThreads)
+            st_agent(row + i, s_hist[i]);
     }
     if (!side_a && g.pos_list) {
         // the last list of the feature that starts at or before the chunk's first position: 256 places
@@ -349,15 +357,8 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
                 break;  // the same value in every thread
         }
     }
-    __syncthreads();
-    if (n_chunks == 1) {
-        write_bases(s, f, s_hist);
+    if (n_chunks == 1)
         return;
-    }
-    const int words = s.passes * radix;
-    uint32_t *row = s.chunk_hist + chunk_row * words;
-    for (int i = tid; i < words; i += kCountThreads)
-        st_agent(row + i, s_hist[i]);
     // The counts are written through to where every XCD reads them; once the stores are acknowledged the
     // arrival may be counted.  A release here would write back the whole L2 of the XCD, once per block
     // (measured beside the forward kernels: 375 us for this kernel, and those slowed by half).
@@ -369,21 +370,29 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
     if (s_pick[0] != (uint32_t)(n_chunks - 1))
         return;
     const uint32_t *rows = s.chunk_hist + (chunk_row - c) * words;
-    constexpr int kPer = 3 * kMaxRadix / kCountThreads;  // counts of a thread, all of a chunk's in flight together
-    uint32_t sum[kPer] = {};
-    for (int k = 0; k < n_chunks; k++) {
-        uint32_t x[kPer];
+    constexpr int kPer = 8, kFly = 4;  // counts of a thread, and chunks, in flight together
+    for (int i0 = tid; i0 < words; i0 += kPer * kCountThreads) {
+        uint32_t sum[kPer] = {};
+        for (int k = 0; k < n_chunks; k += kFly) {
+            uint32_t x[kFly][kPer];
+#pragma unroll
+            for (int j = 0; j < kFly; j++)
+#pragma unroll
+                for (int i = 0; i < kPer; i++) {
+                    const int at = i0 + i * kCountThreads;
+                    x[j][i] = k + j < n_chunks && at < words ? ld_agent(rows + (size_t)(k + j) * words + at) : 0;
+                }
+#pragma unroll
+            for (int j = 0; j < kFly; j++)
+#pragma unroll
+                for (int i = 0; i < kPer; i++)
+                    sum[i] += x[j][i];
+        }
 #pragma unroll
         for (int i = 0; i < kPer; i++)
-            x[i] = i * kCountThreads + tid < words ? ld_agent(rows + (size_t)k * words + i * kCountThreads + tid) : 0;
-#pragma unroll
-        for (int i = 0; i < kPer; i++)
-            sum[i] += x[i];
+            if (i0 + i * kCountThreads < words)
+                s_hist[i0 + i * kCountThreads] = sum[i];
     }
-#pragma unroll
-    for (int i = 0; i < kPer; i++)
-        if (i * kCountThreads + tid < words)
-            s_hist[i * kCountThreads + tid] = sum[i];
     __syncthreads();
     write_bases(s, f, s_hist);
     if (tid == 0)
@@ -397,7 +406,6 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
 // digit order, so that a digit's entries (four on average with 10-bit digits) leave as one short run
 // instead of as scattered words.  Bound by the latency of its chain (ticket, keys, ranks, look-back,
 // stores); 40 KB of LDS keep four tiles on a CU.
-template <typename S>
 __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams g, int pass)
 {
     __shared__ union {
@@ -406,7 +414,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
     } sh;
     __shared__ uint32_t s_from[kMaxRadix];     // where the tile's entries of a digit go, less their place in LDS
     __shared__ uint16_t s_loc[kMaxRadix];      // where they start in LDS
-    __shared__ uint32_t s_tile;
+    __shared__ uint32_t s_tile, s_window;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const bool side_a = blockIdx.x < g.a_blocks;
     const SideParams &s = side_a ? g.a : g.b;
@@ -487,27 +495,29 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
             }
         }
     }
-    const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
     for (int u = 0; u < kItems; u++) {
         const bool valid = wbase + u * 64 < n;
         const uint32_t d = (key[u] >> shift) & mask;
-        uint64_t same = __ballot(valid);
+        const uint64_t all = __ballot(valid);
+        uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);  // lanes with my digit
 #pragma unroll
         for (int bit = 0; bit < kMaxBits; bit++) {
             if (bit < s.dbits) {  // uniform
-                const bool one = (d >> bit) & 1u;
-                const uint64_t bal = __ballot(one);
-                same &= one ? bal : ~bal;
+                const int one = (int)(d << (31 - bit)) >> 31;  // all ones where the bit is set
+                const uint64_t bal = __ballot(one != 0);
+                lo &= ~((uint32_t)bal ^ (uint32_t)one);
+                hi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)one);
             }
         }
-        const uint32_t in_round = (uint32_t)__popcll(same & lt_mask);
+        const uint32_t in_round = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+        const uint32_t of_digit = (uint32_t)(__popc(lo) + __popc(hi));
         // entries of this digit in the wave's earlier rounds; the first lane of each digit then adds this
         // round's (same wave: the read is complete before the write is issued)
         const uint32_t before = valid ? sh.run[w][d] : 0;
         __builtin_amdgcn_wave_barrier();
         if (valid && in_round == 0)
-            sh.run[w][d] = (uint16_t)(before + (uint32_t)__popcll(same));
+            sh.run[w][d] = (uint16_t)(before + of_digit);
         __builtin_amdgcn_wave_barrier();
         rank[u] = before + in_round;
     }
@@ -528,49 +538,82 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
             cnt[e] = run;
         }
     }
-    S *st = static_cast<S *>(s.status) + ((size_t)pass * s.tiles_cap + (tile - k)) * radix;  // the feature's tiles
+    // Look-back: the counts go out first, a flag per tile behind them, so that whoever waits polls one word
+    // a tile (polling the 1024 counts themselves kept the fabric busy: 37 us a sweep at 2.2 M entries).
+    uint32_t *const own = s.own + (size_t)(tile - k) * radix, *const upto = s.upto + (size_t)(tile - k) * radix;
+    uint32_t *const flag = s.flag + (size_t)pass * s.tiles_cap + (tile - k);  // of the feature's tiles
     if (tiles_f > 1) {
+        uint32_t *dst = (k == 0 ? upto : own) + (size_t)k * radix;
 #pragma unroll
         for (int e = 0; e < 2; e++)
             if (d0 + e < radix)
-                st_agent(st + (size_t)k * radix + d0 + e, k == 0 ? Word<S>::all(cnt[e]) : Word<S>::own(cnt[e]));
+                st_agent(dst + d0 + e, cnt[e]);
     }
     uint32_t total;
     const uint32_t loc = block_excl<uint32_t, kWaves>(cnt[0] + cnt[1], total);
-    // ---- look-back ------------------------------------------------------------------------------------------
+    if (tiles_f > 1) {
+        stores_done();
+        __syncthreads();
+        if (tid == 0)
+            st_agent(flag + k, k == 0 ? 2u : 1u);
+    }
+    uint32_t excl[2] = {0, 0};
+    for (int64_t j = (int64_t)k - 1; j >= 0;) {
+        if (w == 0) {
+            // 64 tiles at a time, the nearest first: up to one that has the counts of all before it, or all
+            const int window = j + 1 < 64 ? (int)j + 1 : 64;
+            int take;
+            bool last;
+            for (;;) {
+                const uint32_t x = lane < window ? ld_agent(flag + (j - lane)) : 0;
+                const uint64_t none = __ballot(lane < window && x == 0), full = __ballot(x == 2);
+                const int stop = none ? __builtin_ctzll(none) : window;
+                const int fin = full ? __builtin_ctzll(full) : 64;
+                last = fin < stop;
+                take = last ? fin + 1 : window;
+                if (last || stop == window)
+                    break;
+                __builtin_amdgcn_s_sleep(2);
+            }
+            if (lane == 0)
+                s_window = (uint32_t)take | (last ? 256u : 0u);
+        }
+        __syncthreads();
+        const uint32_t win = s_window;
+        const int take = (int)(win & 255u);
+        const bool last = (win & 256u) != 0;
+        __syncthreads();
+        constexpr int kFly = 8;
+        for (int i = 0; i < take; i += kFly) {
+            uint32_t x[2][kFly];
+#pragma unroll
+            for (int u = 0; u < kFly; u++) {
+                const uint32_t *src = (last && i + u == take - 1 ? upto : own) + (size_t)(j - i - u) * radix + d0;
+#pragma unroll
+                for (int e = 0; e < 2; e++)
+                    x[e][u] = i + u < take && d0 + e < radix ? ld_agent(src + e) : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kFly; u++) {
+                excl[0] += x[0][u];
+                excl[1] += x[1][u];
+            }
+        }
+        if (last)
+            break;
+        j -= take;
+    }
+    const bool pass_on = k > 0 && k + 1 < tiles_f;
 #pragma unroll
     for (int e = 0; e < 2; e++) {
         const int d = d0 + e;
         if (d >= radix)
             continue;
-        uint32_t excl = 0;
-        int64_t j = (int64_t)k - 1;
-        bool done = j < 0;
-        while (!done) {
-            constexpr int W = 8;  // words in flight
-            S x[W];
-#pragma unroll
-            for (int u = 0; u < W; u++)
-                x[u] = j - u >= 0 ? ld_agent(st + (size_t)(j - u) * radix + d) : (S)0;
-            bool stop = false;
-#pragma unroll
-            for (int u = 0; u < W; u++) {
-                const int kind = Word<S>::kind(x[u]);
-                stop = stop || kind == 0;
-                if (!stop && !done) {
-                    excl += Word<S>::count(x[u]);
-                    done = kind == 2;
-                    j--;
-                }
-            }
-            if (!done && stop)
-                __builtin_amdgcn_s_sleep(1);
-        }
-        if (k > 0 && k + 1 < tiles_f)
-            st_agent(st + (size_t)k * radix + d, Word<S>::all(excl + cnt[e]));
+        if (pass_on)
+            st_agent(upto + (size_t)k * radix + d, excl[e] + cnt[e]);
         const uint32_t at = loc + (e ? cnt[0] : 0);
         s_loc[d] = (uint16_t)at;
-        s_from[d] = f_begin + s.base[((size_t)f * s.passes + pass) * radix + d] + excl - at;
+        s_from[d] = f_begin + s.base[((size_t)f * s.passes + pass) * radix + d] + excl[e] - at;
     }
     __syncthreads();
     // ---- into LDS in digit order, then out ---------------------------------------------------------------
@@ -580,7 +623,11 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
             const uint32_t d = (key[u] >> shift) & mask;
             rank[u] += (uint32_t)s_loc[d] + sh.run[w][d];
         }
+    if (pass_on)
+        stores_done();
     __syncthreads();  // the counts have been read: their memory takes the entries
+    if (pass_on && tid == 0)
+        st_agent(flag + k, 2u);
 #pragma unroll
     for (int u = 0; u < kItems; u++)
         if (wbase + u * 64 < n) {
@@ -834,10 +881,7 @@ int64_t chunk_for(int64_t n)
     return chunk;
 }
 
-// Both sides use one width of look-back words.
-bool wide_words(int64_t n_lists, int64_t M_cap) { return (n_lists > M_cap ? n_lists : M_cap) >= (int64_t)1 << 30; }
-
-// Words (digit counts of all passes) of a tile whose keys have at most `bits` bits.  Fewer bits can
+// Words (digit counts of all passes) of a feature or chunk whose keys have at most `bits` bits.  Fewer bits can
 // need more words: 10 bits are one digit of 1024, 14 bits two of 128.
 size_t words_for(int bits)
 {
@@ -866,8 +910,9 @@ RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap)
         s.tiles_cap = tiles;
         s.base = c.take<uint32_t>((size_t)F * words_per_tile);
         s.chunk_hist = c.take<uint32_t>((size_t)chunks * words_per_tile);
-        s.status = wide_words(n_lists, M_cap) ? static_cast<void *>(c.take<uint64_t>((size_t)tiles * words_per_tile))
-                                              : static_cast<void *>(c.take<uint32_t>((size_t)tiles * words_per_tile));
+        s.own = c.take<uint32_t>((size_t)tiles * kMaxRadix);
+        s.upto = c.take<uint32_t>((size_t)tiles * kMaxRadix);
+        s.flag = c.take<uint32_t>((size_t)tiles * kMaxPasses);
         s.ticket = c.take<uint32_t>((kMaxPasses + 1) * kQueues);
     };
     const int64_t tpf = (B + kTile - 1) / kTile, ch_a = chunk_for(n_lists);
@@ -917,7 +962,9 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
         digits_for(bits, &s.passes, &s.dbits);
         s.base = v.base;
         s.chunk_hist = v.chunk_hist;
-        s.status = v.status;
+        s.own = v.own;
+        s.upto = v.upto;
+        s.flag = v.flag;
         s.ticket = v.ticket;
         s.arrive = arrive;
         s.chunk = chunk_for(n);
@@ -952,25 +999,18 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     g.chunks = a.chunks;
     g.chunk_arrive = a.chunk_arrive;
     g.long_seg = a.long_seg;
-    const bool wide = wide_words(g.n_lists, a.M_cap);
     const unsigned a_tiles = (unsigned)((g.a.tiles_cap + kQueues - 1) / kQueues * kQueues);
     const unsigned b_tiles = (unsigned)(a.M_cap / kTile + a.F + 1);
     g.a_blocks = (unsigned)((int64_t)a.F * g.cpf);
     const unsigned cb = g.a_blocks + (unsigned)(a.M_cap / g.b.chunk + a.F + 1);
     const size_t lds_a = (size_t)g.a.passes << g.a.dbits, lds_b = ((size_t)g.b.passes << g.b.dbits) + a.F + 1;
     const size_t lds = (lds_a > lds_b ? lds_a : lds_b) * sizeof(uint32_t);
-    if (wide)
-        hipLaunchKernelGGL(k_group_count<uint64_t>, dim3(cb), dim3(kCountThreads), lds, st, g);
-    else
-        hipLaunchKernelGGL(k_group_count<uint32_t>, dim3(cb), dim3(kCountThreads), lds, st, g);
+    hipLaunchKernelGGL(k_group_count, dim3(cb), dim3(kCountThreads), lds, st, g);
     const int passes = g.a.passes > g.b.passes ? g.a.passes : g.b.passes;
     for (int p = 0; p < passes; p++) {
         g.a_blocks = p < g.a.passes ? a_tiles : 0;
         const unsigned nb = g.a_blocks + (p < g.b.passes ? b_tiles : 0);
-        if (wide)
-            hipLaunchKernelGGL(k_group_sweep<uint64_t>, dim3(nb), dim3(kTileThreads), 0, st, g, p);
-        else
-            hipLaunchKernelGGL(k_group_sweep<uint32_t>, dim3(nb), dim3(kTileThreads), 0, st, g, p);
+        hipLaunchKernelGGL(k_group_sweep, dim3(nb), dim3(kTileThreads), 0, st, g, p);
     }
     g.a_blocks = (unsigned)((g.n_lists + kTile - 1) / kTile);
     hipLaunchKernelGGL(k_group_segments, dim3(g.a_blocks + b_tiles), dim3(kTileThreads), 0, st, g);

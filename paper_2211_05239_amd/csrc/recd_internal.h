@@ -226,8 +226,7 @@ struct RecdGroupWs {
         uint32_t *key[2], *pay[2];
         int64_t *n_dev;          // [0] entries, [1] the caller's bound was too small
         int64_t tiles_cap;
-        uint32_t *base, *chunk_hist, *ticket;
-        void *status;
+        uint32_t *base, *chunk_hist, *ticket, *own, *upto, *flag;
     } a, b;
     uint32_t *pb, *queue_start, *tile_total;
     uint2 *desc_queue, *desc_feat;
