@@ -929,7 +929,8 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
     ga.u_weights = u_weights;
     ga.pay_w = w.pay_w;
     RECD_TRY(recd_group(ctx, st, w.group, ga));
-    const uint32_t *ps_a = recd_group_rows(w.group, B, U_cap), *ps_b = recd_group_positions(w.group, max_rows);
+    const uint32_t *ps_a = recd_group_rows(w.group, F, B, U_cap, M_cap, max_rows);
+    const uint32_t *ps_b = recd_group_positions(w.group, F, B, M_cap, max_rows);
     // ---- step A: sum grad_out rows into g_u (or, for sequences, into grad_emb) ---------------------------
     {
         if (!seq) {
@@ -1024,8 +1025,9 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
 
 // ---------------------------------------------------------------- planned backward
 // The backward's grouping work depends on the IKJT only, not on the gradient.  recd_backward_plan runs it
-// on the side stream, starting where the IKJT's build ended, so that it overlaps the forward calls
-// (which are bandwidth-bound, while the plan is a chain of short latency-bound kernels);
+// on the side stream (a small batch's on the stream itself), starting where the IKJT's build ended, so
+// that it overlaps the forward calls (which are bandwidth-bound, while the plan is a chain of short
+// latency-bound kernels);
 // recd_backward_apply then waits for the plan on the main stream and runs the two segment sums with
 // the fused update.  Same kernels, same inputs, same results as the one-call form.
 // run_index: null, or the batch's run index, whose number of runs is checked against runs_cap (the
@@ -1081,27 +1083,36 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
     pl.feat_roff = feat_roff;
     pl.ws = ctx->ws;
     pl.empty = n_lists == 0 || M_cap == 0;
-    hipStream_t st = ctx->stream, side = ctx->side_stream;
+    // A small batch's grouping is one short kernel: on the stream itself it costs less than the two events
+    // that would take it to the side stream and back.
+    hipStream_t st = ctx->stream;
+    const bool own_stream = pl.empty || recd_group_is_small(F, B, M_cap, max_rows);
+    hipStream_t side = own_stream ? st : ctx->side_stream;
     // Where the side stream may start: at the end of the build that produced this IKJT if it is the
     // context's most recent one, else at the main stream's current position.
     hipEvent_t from = ctx->ev_fork;
-    if (ctx->build_valid && ws_idle_since_build && ctx->built_inverse == inverse &&
+    if (own_stream)
+        from = nullptr;
+    else if (ctx->build_valid && ws_idle_since_build && ctx->built_inverse == inverse &&
         ctx->built_u_values == u_values && n_lists > 0)
         from = ctx->ev_built;
     else
         RECD_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
-    RECD_HIP(ctx, hipStreamWaitEvent(side, from, 0));
+    if (from)
+        RECD_HIP(ctx, hipStreamWaitEvent(side, from, 0));
     if (!pl.empty) {
         RecdGroupArgs ga = group_args(w, F, B, U_cap, M_cap, max_rows, inverse, feat_uoff, u_values, u_offsets,
                                       touched_rows, feat_roff);
         ga.run_index = run_index;
         ga.runs_cap = runs_cap > n_lists || runs_cap == 0 ? n_lists : runs_cap;
         RECD_TRY(recd_group(ctx, side, w.group, ga));
-        pl.ps_a = recd_group_rows(w.group, B, U_cap);
-        pl.ps_b = recd_group_positions(w.group, max_rows);
+        pl.ps_a = recd_group_rows(w.group, F, B, U_cap, M_cap, max_rows);
+        pl.ps_b = recd_group_positions(w.group, F, B, M_cap, max_rows);
     }
-    RECD_HIP(ctx, hipEventRecord(ctx->ev_plan, side));
-    pl.pending = true;
+    if (!own_stream) {
+        RECD_HIP(ctx, hipEventRecord(ctx->ev_plan, side));
+        pl.pending = true;
+    }
     pl.valid = true;
     return RECD_OK;
 }
@@ -1158,7 +1169,8 @@ extern "C" recd_status recd_backward_apply(recd_ctx *ctx, recd_pooling mode, con
     RECD_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
     const BwdWs w = carve_bwd(ctx->ws, F, B, M_cap, D, ctx->long_seg_cut);
-    RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_plan, 0));
+    if (pl.pending)
+        RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_plan, 0));
     pl.pending = false;  // the stream now waits for everything the plan enqueued
     if (pl.empty) {
         hipLaunchKernelGGL(k_no_rows, dim3(1), dim3(64), 0, st, F, pl.feat_roff, w.list_off_b);

@@ -851,6 +851,255 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
         put(tail_seg, tail_open, tail_end);
 }
 
+// ---- small batches: both sides in one launch -------------------------------------------------------
+// Up to 8192 ids and 8192 rows per feature: block 0 groups all of side B (key = feature and row), block
+// 1 + f the rows of feature f, each by a radix sort in LDS, and writes the segments straight from there.
+// No block looks at another.  The four launches above cost such a batch their launches and a chain
+// of dependent round trips each (2048 rows, 5 K ids: 38 us of kernels); here it is one chain.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / 64;
+constexpr int kSmallRounds = 8;
+constexpr int kSmallCap = kSmallThreads * kSmallRounds;
+
+__global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams g, int row_bits, int passes_b, int dbits_b)
+{
+    __shared__ uint32_t s_key[kSmallCap], s_pay[kSmallCap];
+    __shared__ uint16_t s_run[kSmallWaves][kMaxRadix];
+    __shared__ uint16_t s_loc[kMaxRadix];
+    __shared__ uint64_t s_wave[kSmallWaves];
+    __shared__ uint32_t s_fu[RECD_MAX_FEATURES + 1], s_chunks;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const bool side_a = blockIdx.x > 0;
+    const uint32_t f_a = blockIdx.x - 1;
+    uint32_t n;
+    if (side_a) {
+        n = (uint32_t)g.B;
+    } else {
+        for (int i = tid; i <= g.F; i += kSmallThreads)
+            s_fu[i] = (uint32_t)g.feat_uoff[i];
+        const int64_t M = g.u_offsets[g.feat_uoff[g.F]];
+        n = (uint32_t)(M < g.M_cap ? M : g.M_cap);
+        if (tid == 0) {
+            g.n_dev_b[0] = n;
+            g.n_dev_b[1] = M > g.M_cap ? 1 : 0;
+            s_chunks = 0;
+        }
+        __syncthreads();
+        // every list fills in its number and its feature at its positions (an empty list has none)
+        const uint32_t U = s_fu[g.F];
+        for (uint32_t u = tid; u < U; u += kSmallThreads) {
+            const int64_t a = g.u_offsets[u], e = g.u_offsets[u + 1];
+            int f = 0;  // the last feature with s_fu[f] <= u
+#pragma unroll
+            for (int st = RECD_MAX_FEATURES / 2; st >= 1; st >>= 1)
+                if (f + st < g.F && s_fu[f + st] <= u)
+                    f += st;
+            const uint32_t end = e < (int64_t)n ? (uint32_t)e : n;
+            for (uint32_t j = a < (int64_t)n ? (uint32_t)a : n; j < end; j++) {
+                s_pay[j] = u;
+                s_key[j] = (uint32_t)f << row_bits;
+            }
+        }
+        __syncthreads();
+    }
+    // a wave owns `rounds` * 64 consecutive entries
+    const int rounds = (int)((n + kSmallThreads - 1) / kSmallThreads);
+    const uint32_t wbase = w * (rounds * 64) + lane;
+    uint32_t key[kSmallRounds], pay[kSmallRounds], rank[kSmallRounds];
+#pragma unroll
+    for (int u = 0; u < kSmallRounds; u++) {
+        const uint32_t i = wbase + u * 64;
+        key[u] = pay[u] = 0;
+        if (u < rounds && i < n) {
+            if (side_a) {
+                key[u] = (uint32_t)g.inverse[f_a * g.B + i];
+                pay[u] = (uint32_t)(f_a * g.B + i);
+            } else {
+                key[u] = s_key[i] | (uint32_t)g.u_values[i];
+                pay[u] = g.pay_positions ? i : s_pay[i];
+                if (g.u_weights)
+                    g.pos_list[i] = s_pay[i];
+            }
+        }
+    }
+    const int passes = side_a ? g.a.passes : passes_b, dbits = side_a ? g.a.dbits : dbits_b;
+    const int radix = 1 << dbits;
+    const uint32_t mask = radix - 1;
+    for (int p = 0; p < passes; p++) {
+        const int shift = p * dbits;
+        __syncthreads();  // the previous pass is done with the shared arrays
+        for (int i = tid; i < kSmallWaves * kMaxRadix / 2; i += kSmallThreads)
+            reinterpret_cast<uint32_t *>(&s_run[0][0])[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kSmallRounds; u++) {
+            if (u >= rounds)  // the same in every thread
+                break;
+            const bool valid = wbase + u * 64 < n;
+            const uint32_t d = (key[u] >> shift) & mask;
+            const uint64_t all = __ballot(valid);
+            uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);  // lanes with my digit
+#pragma unroll
+            for (int bit = 0; bit < kMaxBits; bit++) {
+                if (bit < dbits) {
+                    const int one = (int)(d << (31 - bit)) >> 31;
+                    const uint64_t bal = __ballot(one != 0);
+                    lo &= ~((uint32_t)bal ^ (uint32_t)one);
+                    hi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)one);
+                }
+            }
+            const uint32_t in_round = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+            const uint32_t before = valid ? s_run[w][d] : 0;
+            __builtin_amdgcn_wave_barrier();
+            if (valid && in_round == 0)
+                s_run[w][d] = (uint16_t)(before + __popc(lo) + __popc(hi));
+            __builtin_amdgcn_wave_barrier();
+            rank[u] = before + in_round;
+        }
+        __syncthreads();
+        uint32_t cnt = 0, total;
+        if (tid < radix) {
+#pragma unroll
+            for (int ww = 0; ww < kSmallWaves; ww++) {
+                const uint32_t x = s_run[ww][tid];
+                s_run[ww][tid] = (uint16_t)cnt;
+                cnt += x;
+            }
+        }
+        const uint32_t at = block_excl<uint32_t, kSmallWaves>(cnt, total);
+        if (tid < radix)
+            s_loc[tid] = (uint16_t)at;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kSmallRounds; u++)
+            if (u < rounds && wbase + u * 64 < n) {
+                const uint32_t d = (key[u] >> shift) & mask;
+                const uint32_t to = (uint32_t)s_loc[d] + s_run[w][d] + rank[u];
+                s_key[to] = key[u];
+                s_pay[to] = pay[u];
+            }
+        __syncthreads();
+        if (p + 1 < passes) {
+#pragma unroll
+            for (int u = 0; u < kSmallRounds; u++)
+                if (u < rounds && wbase + u * 64 < n) {
+                    key[u] = s_key[wbase + u * 64];
+                    pay[u] = s_pay[wbase + u * 64];
+                }
+        }
+    }
+    // ---- out, in the same order of threads ---------------------------------------------------------------
+    if (side_a) {
+        const int64_t u0 = g.feat_uoff[f_a], u1 = g.feat_uoff[f_a + 1];
+        const uint32_t l0 = (uint32_t)(f_a * g.B);
+        for (uint32_t i = tid; i < n; i += kSmallThreads) {
+            g.a.pay[0][l0 + i] = s_pay[i];
+            const int64_t k = s_key[i], prev = i == 0 ? -1 : (int64_t)s_key[i - 1];
+            for (int64_t x = prev + 1; x <= k; x++)
+                g.seg_start_a[u0 + x] = (int64_t)l0 + i;
+            if (i == n - 1) {
+                for (int64_t x = u0 + k + 1; x < u1; x++)
+                    g.seg_start_a[x] = (int64_t)l0 + n;
+                if ((int)f_a == g.F - 1) {
+                    g.seg_start_a[u1] = g.n_lists;
+                    g.list_off_a[0] = 0;
+                    g.list_off_a[1] = u1;
+                    g.n_dev_a[0] = g.n_lists;
+                    g.n_dev_a[1] = g.run_index && g.run_index[0] > g.runs_cap ? 1 : 0;
+                }
+            }
+        }
+        return;
+    }
+    if (n == 0) {  // no id anywhere
+        for (int f = tid; f <= g.F; f += kSmallThreads)
+            g.feat_roff[f] = 0;
+        if (tid == 0)
+            g.seg_start_b[0] = g.list_off_b[0] = g.list_off_b[1] = g.chunk_count[0] = 0;
+        return;
+    }
+    const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    uint32_t heads = 0, last = 0;  // of the wave so far; last: position of its last head + 1
+    uint32_t num[kSmallRounds], open[kSmallRounds];
+    uint64_t hm[kSmallRounds];
+#pragma unroll
+    for (int u = 0; u < kSmallRounds; u++) {
+        const uint32_t i = wbase + u * 64;
+        const bool in = u < rounds && i < n;
+        hm[u] = __ballot(in && (i == 0 || s_key[i] != s_key[i - 1]));
+        const uint64_t below = hm[u] & lt_mask;
+        const uint32_t at0 = i - lane;
+        num[u] = heads + (uint32_t)__popcll(below);
+        open[u] = below ? at0 + (63 - __builtin_clzll(below)) + 1 : last;
+        heads += (uint32_t)__popcll(hm[u]);
+        if (hm[u])
+            last = at0 + (63 - __builtin_clzll(hm[u])) + 1;
+    }
+    if (lane == 0)
+        s_wave[w] = ((uint64_t)heads << 32) | last;
+    __syncthreads();
+    uint32_t wh = 0, wl = 0, R = 0, end_open = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallWaves; i++) {
+        const uint32_t h = (uint32_t)(s_wave[i] >> 32), l = (uint32_t)s_wave[i];
+        if (i < w) {
+            wh += h;
+            wl = l > wl ? l : wl;
+        }
+        R += h;
+        end_open = l > end_open ? l : end_open;
+    }
+    const uint32_t row_mask = row_bits < 32 ? (1u << row_bits) - 1 : ~0u;
+    auto list_chunks = [&](uint32_t seg, uint32_t start, uint32_t end) {
+        const uint32_t len = end - start;
+        if (len <= (uint32_t)g.long_seg)
+            return;
+        const uint32_t ch = len > 64 * 256 ? (len + 63) / 64 : 256u, nch = (len + ch - 1) / ch;
+        const uint32_t first = atomicAdd(&s_chunks, nch);
+        g.chunk_arrive[first] = 0;
+        for (uint32_t c = 0; c < nch; c++)
+            g.chunks[first + c] = RecdChunk{start + c * ch, c + 1 < nch ? start + (c + 1) * ch : end, seg, first, nch};
+    };
+#pragma unroll
+    for (int u = 0; u < kSmallRounds; u++) {
+        const uint32_t i = wbase + u * 64;
+        if (u >= rounds || i >= n)
+            continue;
+        const uint32_t pp = s_pay[i];
+        if (g.u_weights) {  // the entry's source row and weight, both in sorted order
+            g.b.pay[0][i] = g.pos_list[pp];
+            g.pay_w[i] = g.u_weights[pp];
+        } else {
+            g.b.pay[0][i] = pp;
+        }
+        const uint32_t seg = wh + num[u];
+        if ((hm[u] >> lane) & 1) {
+            const uint32_t kk = s_key[i], f = kk >> row_bits;
+            const int fprev = i == 0 ? -1 : (int)(s_key[i - 1] >> row_bits);
+            if (open[u] == 0)
+                open[u] = wl;
+            g.seg_start_b[seg] = i;
+            g.touched_rows[seg] = kk & row_mask;
+            g.seg_feat[seg] = (int32_t)f;
+            for (int ff = fprev + 1; ff <= (int)f; ff++)
+                g.feat_roff[ff] = seg;
+            if (i > 0)
+                list_chunks(seg - 1, open[u] - 1, i);
+        }
+        if (i == n - 1) {
+            list_chunks(R - 1, end_open - 1, n);
+            g.seg_start_b[R] = n;
+            g.list_off_b[0] = 0;
+            g.list_off_b[1] = R;
+            for (int ff = (int)(s_key[i] >> row_bits) + 1; ff <= g.F; ff++)
+                g.feat_roff[ff] = R;
+        }
+    }
+    __syncthreads();
+    if (tid == 0)
+        g.chunk_count[0] = s_chunks;
+}
+
 int bits_for(uint64_t max_value)
 {
     int b = 1;
@@ -929,16 +1178,26 @@ RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap)
     return w;
 }
 
-const uint32_t *recd_group_rows(const RecdGroupWs &w, int64_t B, int64_t U_cap)
+bool recd_group_is_small(int F, int64_t B, int64_t M_cap, int64_t max_rows)
+{
+    return B <= kSmallCap && M_cap <= kSmallCap && bits_for((uint64_t)(max_rows > 1 ? max_rows - 1 : 1)) +
+                                                           bits_for((uint64_t)(F > 1 ? F - 1 : 1)) <= 32;
+}
+
+const uint32_t *recd_group_rows(const RecdGroupWs &w, int F, int64_t B, int64_t U_cap, int64_t M_cap, int64_t max_rows)
 {
     int passes, dbits;
+    if (recd_group_is_small(F, B, M_cap, max_rows))
+        return w.a.pay[0];
     digits_for(slot_bits(B, U_cap), &passes, &dbits);
     return w.a.pay[(passes - 1) & 1];
 }
 
-const uint32_t *recd_group_positions(const RecdGroupWs &w, int64_t max_rows)
+const uint32_t *recd_group_positions(const RecdGroupWs &w, int F, int64_t B, int64_t M_cap, int64_t max_rows)
 {
     int passes, dbits;
+    if (recd_group_is_small(F, B, M_cap, max_rows))
+        return w.b.pay[0];
     digits_for(bits_for((uint64_t)(max_rows > 1 ? max_rows - 1 : 1)), &passes, &dbits);
     return w.b.pay[(passes - 1) & 1];
 }
@@ -999,6 +1258,14 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     g.chunks = a.chunks;
     g.chunk_arrive = a.chunk_arrive;
     g.long_seg = a.long_seg;
+    if (recd_group_is_small(a.F, a.B, a.M_cap, a.max_rows)) {
+        const int row_bits = bits_for((uint64_t)(a.max_rows > 1 ? a.max_rows - 1 : 1));
+        int passes, dbits;
+        digits_for(row_bits + (a.F > 1 ? bits_for((uint64_t)(a.F - 1)) : 0), &passes, &dbits);
+        hipLaunchKernelGGL(k_group_small, dim3(1 + a.F), dim3(kSmallThreads), 0, st, g, row_bits, passes, dbits);
+        RECD_HIP(ctx, hipGetLastError());
+        return RECD_OK;
+    }
     const unsigned a_tiles = (unsigned)((g.a.tiles_cap + kQueues - 1) / kQueues * kQueues);
     const unsigned b_tiles = (unsigned)(a.M_cap / kTile + a.F + 1);
     g.a_blocks = (unsigned)((int64_t)a.F * g.cpf);

@@ -259,9 +259,11 @@ struct RecdGroupArgs {
 };
 RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap);
 recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, const RecdGroupArgs &a);
+// Whether both sides are grouped by one launch.
+bool recd_group_is_small(int F, int64_t B, int64_t M_cap, int64_t max_rows);
 // The payload buffers that hold the result for these sizes.
-const uint32_t *recd_group_rows(const RecdGroupWs &w, int64_t B, int64_t U_cap);
-const uint32_t *recd_group_positions(const RecdGroupWs &w, int64_t max_rows);
+const uint32_t *recd_group_rows(const RecdGroupWs &w, int F, int64_t B, int64_t U_cap, int64_t M_cap, int64_t max_rows);
+const uint32_t *recd_group_positions(const RecdGroupWs &w, int F, int64_t B, int64_t M_cap, int64_t max_rows);
 recd_status recd_validate_inverse(recd_ctx *ctx, int F, int64_t B, const int64_t *feat_uoff,
                                   const int32_t *inverse);
 recd_status recd_validate_kjt_offsets(recd_ctx *ctx, int F, int64_t B, int64_t N, const int64_t *offsets);

@@ -45,6 +45,13 @@ CASES = [
     ([TILE * 3 + 77, 1, TILE * 2], TILE + 1, 1025, 1 << 20, True),
     ([40000], 2 * TILE + 3, 4000, (1 << 20) + 1, True),
     ([300, 0, 9000, 5000, 1, 0, 0, 4097, 12000, 64, 8192], 700, 600, 50000, True),
+    # at most 8192 ids and rows per feature: one launch
+    ([8000 - 3, 0, 192], 8192, 8000, 1 << 17, True),   # with the bound M_cap = 8192 exactly
+    ([0, 1024, 0, 1025, 3], 1025, 1024, 70000, True),
+    ([8190], 8193, 90, 4000, True),                    # one row too many
+    ([8190], 70, 60, 4000, True),                      # one id too many (M_cap = 8193)
+    ([700, 0, 600], 2000, 7, (1 << 31) - 1, False),    # 31 + 2 bits of key: too many for one launch
+    ([1400], 2000, 7, (1 << 31) - 1, False),           # 31 + 1 bits
     ([50] * 130, 40, 33, 5000, False),       # more features than one launch of the optimizer takes
     ([9] * 1024, 3, 3, 100, False),          # the most features
 ]
