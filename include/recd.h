@@ -474,8 +474,8 @@ recd_status recd_backward_apply(recd_ctx *ctx, recd_pooling mode, const float *g
  *                  of g_u[u, d]
  *    lookup_tables: HOST array of F device pointers to the fp32 tables [rows_f, D] the forward pass
  *    looked up (fp32 only); they are read before any update, so they may be the same as `tables`.
- *    The call materialises one masked gradient row per position of u_values in the workspace
- *    (M_cap * D * 4 bytes more than recd_workspace_bytes reports; the workspace grows on demand, which
+ *    The call keeps one byte per position of u_values and four elements in the workspace
+ *    (up to M_cap * max(16, D / 2) bytes more than recd_workspace_bytes reports; the workspace grows on demand, which
  *    synchronises and allocates).  All other arguments, and the guarantees, as in call 5. */
 recd_status recd_backward_dedup_max(recd_ctx *ctx, int F, int64_t B, int D, const float *grad_out,
                                     const int32_t *inverse, const int64_t *feat_uoff,

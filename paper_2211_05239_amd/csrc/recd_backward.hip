@@ -89,6 +89,8 @@ struct RowSumParams {
     const float *table;        // g_u [U, D]
     const uint32_t *pay;       // sorted payload: unique-list index of every position
     const float *pay_w;        // weighted lookup: the weight of every sorted entry, else nullptr
+    const uint32_t *pay_pos;   // max pooling: the position of every sorted entry, else nullptr
+    const uint32_t *won;       // max pooling [M, LPR]: byte w of word r: which elements of piece w * LPR + r the position won
     const int64_t *seg_start;  // [R+1]
     const int64_t *n_seg;      // device: R
     float *out;                // grad_rows [R, D] or nullptr
@@ -177,8 +179,39 @@ __device__ __forceinline__ void fetch_row(const OptAdagrad &opt, int D, int f, i
         }
 }
 
-template <bool WT> __device__ __forceinline__ void add4(float4 &acc, const float4 &v, float wt)
+// How a segment's entry counts: its source row, the row times the entry's weight, or (max pooling) the
+// elements of the row that the entry's position won.
+enum { ROWS_PLAIN = 0, ROWS_WEIGHTED = 1, ROWS_MAX = 2 };
+
+// Piece w * LPR + r of an entry's source row; won: the entry's word r (max pooling).
+template <int LPR, int MODE>
+__device__ __forceinline__ float4 entry_piece(const RowSumParams &p, uint32_t id, int w, int r, uint32_t won)
 {
+    float4 v = reinterpret_cast<const float4 *>(p.table)[(int64_t)id * p.pieces + w * LPR + r];
+    if constexpr (MODE == ROWS_MAX) {
+        won >>= 8 * w;
+        v.x = won & 1u ? v.x : 0.f;
+        v.y = won & 2u ? v.y : 0.f;
+        v.z = won & 4u ? v.z : 0.f;
+        v.w = won & 8u ? v.w : 0.f;
+    }
+    return v;
+}
+
+template <int LPR, int MODE> __device__ __forceinline__ uint32_t entry_won(const RowSumParams &p, uint32_t x, int r)
+{
+    return MODE == ROWS_MAX ? p.won[(int64_t)x * LPR + r] : 0u;
+}
+
+template <int MODE> __device__ __forceinline__ uint32_t entry_extra(const RowSumParams &p, int64_t i)
+{
+    return MODE == ROWS_WEIGHTED ? __float_as_uint(p.pay_w[i]) : (MODE == ROWS_MAX ? p.pay_pos[i] : 0u);
+}
+
+template <int MODE> __device__ __forceinline__ void add4(float4 &acc, const float4 &v, uint32_t x)
+{
+    constexpr bool WT = MODE == ROWS_WEIGHTED;
+    const float wt = __uint_as_float(x);
     acc.x = WT ? __fmaf_rn(wt, v.x, acc.x) : acc.x + v.x;
     acc.y = WT ? __fmaf_rn(wt, v.y, acc.y) : acc.y + v.y;
     acc.z = WT ? __fmaf_rn(wt, v.z, acc.z) : acc.z + v.z;
@@ -186,39 +219,54 @@ template <bool WT> __device__ __forceinline__ void add4(float4 &acc, const float
 }
 
 // One chunk of a cut segment, summed by the block.
-template <int LPR, bool WT>
+template <int LPR, int MODE>
 __device__ __forceinline__ void sum_chunk(const RowSumParams &p, const OptAdagrad &opt, int64_t item, const bool *piece)
 {
     constexpr int G = 64 / LPR, VPL = 4, W = 256 / 64;
     __shared__ float4 s_part[W][VPL][LPR];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = lane / LPR, r = lane % LPR;
-    const float4 *table = reinterpret_cast<const float4 *>(p.table);
     const RecdChunk c = p.chunks[item];
     float4 acc[VPL];
 #pragma unroll
     for (int w = 0; w < VPL; w++)
         acc[w] = make_float4(0.f, 0.f, 0.f, 0.f);
-    // entries wv * G + g, + 4 G, ...: two of a group's in flight
-    for (uint32_t i = c.start + wv * G + g; i < c.end; i += 2 * W * G) {
-        const uint32_t i1 = i + W * G;
-        const bool two = i1 < c.end;
-        const uint32_t id0 = p.pay[i], id1 = two ? p.pay[i1] : id0;
-        const float wt0 = WT ? p.pay_w[i] : 1.f, wt1 = WT && two ? p.pay_w[i1] : 1.f;
-        float4 v0[VPL], v1[VPL];
+    // A group takes the entries wv * G + g, + W * G, ...: LPR of them (256 of the block) are fetched by one
+    // load, one per lane, and handed round by shuffles; two source rows in flight.
+    const int gbase = lane - r;
+    for (uint32_t base = c.start + wv * G + g; base < c.end; base += W * G * LPR) {
+        const uint32_t idx = base + r * (W * G);
+        const uint32_t pre = idx < c.end ? p.pay[idx] : 0u, prex = idx < c.end ? entry_extra<MODE>(p, idx) : 0u;
+        const int left = (int)((c.end - base + W * G - 1) / (W * G)), cnt = left < LPR ? left : LPR;
+        for (int i0 = 0; i0 < cnt; i0 += 4) {
+            uint32_t won[4];
 #pragma unroll
-        for (int w = 0; w < VPL; w++)
-            if (piece[w]) {
-                v0[w] = table[(int64_t)id0 * p.pieces + w * LPR + r];
-                v1[w] = table[(int64_t)id1 * p.pieces + w * LPR + r];
-            }
+            for (int i = 0; i < 4; i++)
+                won[i] = entry_won<LPR, MODE>(p, __shfl(prex, gbase + (i0 + i < cnt ? i0 + i : cnt - 1)), r);
 #pragma unroll
-        for (int w = 0; w < VPL; w++)
-            if (piece[w]) {
-                add4<WT>(acc[w], v0[w], wt0);
-                if (two)
-                    add4<WT>(acc[w], v1[w], wt1);
+            for (int i = 0; i < 4; i += 2) {
+                const bool one = i0 + i < cnt, two = i0 + i + 1 < cnt;
+                if (!one)
+                    break;
+                const int k1 = i0 + i + (two ? 1 : 0);
+                const uint32_t id0 = __shfl(pre, gbase + i0 + i), id1 = __shfl(pre, gbase + k1);
+                const uint32_t x0 = __shfl(prex, gbase + i0 + i), x1 = __shfl(prex, gbase + k1);
+                float4 v0[VPL], v1[VPL];
+#pragma unroll
+                for (int w = 0; w < VPL; w++)
+                    if (piece[w]) {
+                        v0[w] = entry_piece<LPR, MODE>(p, id0, w, r, won[i]);
+                        v1[w] = entry_piece<LPR, MODE>(p, id1, w, r, won[i + 1]);
+                    }
+#pragma unroll
+                for (int w = 0; w < VPL; w++)
+                    if (piece[w]) {
+                        add4<MODE>(acc[w], v0[w], x0);
+                        if (two)
+                            add4<MODE>(acc[w], v1[w], x1);
+                    }
             }
+        }
     }
 #pragma unroll
     for (int s = LPR; s < 64; s <<= 1)
@@ -246,7 +294,7 @@ __device__ __forceinline__ void sum_chunk(const RowSumParams &p, const OptAdagra
         acc[w] = s_part[0][w][r];
 #pragma unroll
         for (int k = 1; k < W; k++)
-            add4<false>(acc[w], s_part[k][w][r], 1.f);
+            add4<ROWS_PLAIN>(acc[w], s_part[k][w][r], 0);
     }
     if (c.n > 1) {
         // the partial sum goes where every XCD reads it, then the arrival is counted (see the grouping's
@@ -296,8 +344,7 @@ __device__ __forceinline__ void sum_chunk(const RowSumParams &p, const OptAdagra
     finish_segment<LPR>(p, opt, c.seg, acc, wreg, mreg, wrow, mp, piece, r, update);
 }
 
-// WT: entry j contributes pay_w[j] times its source row.
-template <int LPR, bool WT>
+template <int LPR, int MODE>
 __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const OptAdagrad opt)
 {
     constexpr int G = 64 / LPR, VPL = 4;
@@ -310,12 +357,11 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
     if (blockIdx.x < p.chunk_blocks) {
         const int64_t n = *p.chunk_count;
         for (int64_t item = blockIdx.x; item < n; item += p.chunk_blocks)
-            sum_chunk<LPR, WT>(p, opt, item, piece);
+            sum_chunk<LPR, MODE>(p, opt, item, piece);
         return;
     }
     const int64_t R = *p.n_seg;
     const int per_block = (256 / 64) * G;
-    const float4 *table = reinterpret_cast<const float4 *>(p.table);
     // The segments are ordered by (feature, row) and their entries name rows of the source array that
     // belong to the same feature.  Blocks go to the XCDs in turn; every XCD takes a contiguous eighth
     // of the segments and its blocks stride through it side by side, so that the source rows an XCD
@@ -348,13 +394,12 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
         // second round trip: the segment's entries (the first kPre * LPR of them, one load per lane
         // and LPR entries) together with the destination row and its accumulator
         constexpr int kPre = 4;
-        uint32_t pre[kPre];
-        float prew[kPre];
+        uint32_t pre[kPre], prex[kPre];
 #pragma unroll
         for (int u = 0; u < kPre; u++) {
             const int idx = u * LPR + r;
             pre[u] = idx < n ? p.pay[start + idx] : 0u;
-            prew[u] = (WT && idx < n) ? p.pay_w[start + idx] : 1.f;
+            prex[u] = idx < n ? entry_extra<MODE>(p, start + idx) : 0u;
         }
         float4 wreg[VPL];
         float mreg = 0.f;
@@ -365,17 +410,16 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
 #pragma unroll
         for (int w = 0; w < VPL; w++)
             acc[w] = make_float4(0.f, 0.f, 0.f, 0.f);
-        // one entry: the source row `id` (times wt) added to the segment's sum
-        auto add_entry = [&](int64_t id, float wt) {
+        auto add_entry = [&](uint32_t id, uint32_t x, uint32_t won) {
             float4 v[VPL];
 #pragma unroll
             for (int w = 0; w < VPL; w++)
                 if (piece[w])
-                    v[w] = table[id * p.pieces + w * LPR + r];
+                    v[w] = entry_piece<LPR, MODE>(p, id, w, r, won);
 #pragma unroll
             for (int w = 0; w < VPL; w++)
                 if (piece[w])
-                    add4<WT>(acc[w], v[w], wt);
+                    add4<MODE>(acc[w], v[w], x);
         };
         // entries in ascending order: the fetched ones come out of the lane group's registers, any
         // further ones (cuts above kPre * LPR entries) are read one by one
@@ -383,38 +427,54 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
 #pragma unroll
         for (int u = 0; u < kPre; u++) {
             const int cnt = n - u * LPR < LPR ? n - u * LPR : LPR;
-            for (int ii = 0; ii < cnt; ii++) {
-                const uint32_t id = __shfl(pre[u], gbase + ii);
-                const float wt = WT ? __shfl(prew[u], gbase + ii) : 1.f;
-                add_entry((int64_t)id, wt);
+            if constexpr (MODE == ROWS_MAX) {
+                // the words come from memory (another XCD wrote them) while the rows of g_u are in L2: those of
+                // eight entries are fetched ahead of the walk
+                for (int i0 = 0; i0 < cnt; i0 += 8) {
+                    uint32_t won[8];
+#pragma unroll
+                    for (int i = 0; i < 8; i++)
+                        won[i] = entry_won<LPR, MODE>(p, __shfl(prex[u], gbase + (i0 + i < cnt ? i0 + i : cnt - 1)), r);
+#pragma unroll
+                    for (int i = 0; i < 8; i++)
+                        if (i0 + i < cnt)
+                            add_entry(__shfl(pre[u], gbase + i0 + i), 0u, won[i]);
+                }
+            } else {
+                for (int ii = 0; ii < cnt; ii++) {
+                    const uint32_t id = __shfl(pre[u], gbase + ii);
+                    add_entry(id, MODE != ROWS_PLAIN ? __shfl(prex[u], gbase + ii) : 0u, 0u);
+                }
             }
         }
-        for (int i = kPre * LPR; i < n; i++)
-            add_entry((int64_t)p.pay[start + i], WT ? p.pay_w[start + i] : 1.f);
+        for (int i = kPre * LPR; i < n; i++) {
+            const uint32_t x = entry_extra<MODE>(p, start + i);
+            add_entry(p.pay[start + i], x, entry_won<LPR, MODE>(p, x, r));
+        }
         if (mine)
             finish_segment<LPR>(p, opt, k, acc, wreg, mreg, wrow, mp, piece, r, update);
     }
 }
 
-// ---------------------------------------------------------------- max pooling: route g_u to the winners
+// ---------------------------------------------------------------- max pooling: who won
 // Backward of the max-pooled lookup: element d of g_u[u] belongs to the position of list u that holds
 // the largest table element d (the first such position).  A group of LPR lanes owns a unique list
-// (lane r: pieces r, r + LPR, ... of the row, 16 bytes each; one piece per lane up to 1 KiB rows):
-// pass 1 walks the list's table rows, eight loads in flight per lane, and keeps the running
-// maximum and its position per element, pass 2 writes one row per position,
-// g_u[u] masked to the elements that position won, into emb[M, D].  The row-gradient segment sum
-// then adds those rows per table row exactly as it does for the sequence path.
+// (lane r: pieces r, r + LPR, ... of the row, 16 bytes each; one piece per lane up to 1 KiB rows), walks
+// its table rows, eight loads in flight per lane, and writes for every position and piece which elements
+// it won: one byte.  The row-gradient sum then takes of g_u[u] what the entry's position won; the rows
+// of g_u stay in L2.  (One masked row per position went to memory and back before: 300 K positions of
+// 512 bytes took 55 us here and 58 + 20 in the sums; now 44 and 72, the latter bound by reading and
+// writing 118 K scattered table rows.)
 struct MaxTables {
     const float *w[RECD_F_PER_LAUNCH];
 };
 
 template <int LPR, int VPL>
-__global__ __launch_bounds__(256) void k_max_route(const int64_t *__restrict__ u_values,
+__global__ __launch_bounds__(256) void k_max_winner(const int64_t *__restrict__ u_values,
                                                    const int64_t *__restrict__ u_offsets,
                                                    const int64_t *__restrict__ feat_uoff, int f0, int nf,
-                                                   MaxTables tabs, const float4 *__restrict__ g_u,
-                                                   float4 *__restrict__ emb, int pieces, int64_t lists_cap,
-                                                   int64_t m_cap)
+                                                   MaxTables tabs, uint8_t *__restrict__ won, int won_lpr, int pieces,
+                                                   int64_t lists_cap, int64_t m_cap)
 {
     constexpr int G = 64 / LPR, US = 8 / VPL;  // US positions of a list in flight per lane
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -424,9 +484,12 @@ __global__ __launch_bounds__(256) void k_max_route(const int64_t *__restrict__ u
     int64_t u_hi = feat_uoff[f0 + nf];
     u_hi = u_hi < lists_cap ? u_hi : lists_cap;
     bool piece[VPL];
+    int place[VPL];  // byte of a piece among a position's words: word = piece mod won_lpr, byte = piece / won_lpr
 #pragma unroll
-    for (int w = 0; w < VPL; w++)
+    for (int w = 0; w < VPL; w++) {
         piece[w] = w * LPR + r < pieces;
+        place[w] = (w * LPR + r) % won_lpr * 4 + (w * LPR + r) / won_lpr;
+    }
     for (int64_t u = u_lo + (int64_t)blockIdx.x * per_block + wv * G + g; u < u_hi;
          u += (int64_t)gridDim.x * per_block) {
         int lo = 0, hi = nf;  // feature of u inside [f0, f0 + nf)
@@ -448,7 +511,7 @@ __global__ __launch_bounds__(256) void k_max_route(const int64_t *__restrict__ u
             best[w] = make_float4(0.f, 0.f, 0.f, 0.f);
             arg[w] = make_int4(0, 0, 0, 0);
         }
-        // pass 1: positions in ascending order, US rows in flight
+        // positions in ascending order, US rows in flight
         for (int64_t jb = j0; jb < j1; jb += US) {
             float4 v[US][VPL];
 #pragma unroll
@@ -475,28 +538,13 @@ __global__ __launch_bounds__(256) void k_max_route(const int64_t *__restrict__ u
                         }
                 }
         }
-        // pass 2: one masked row per position
-        float4 gu[VPL];
-#pragma unroll
-        for (int w = 0; w < VPL; w++)
-            if (piece[w])
-                gu[w] = g_u[u * pieces + w * LPR + r];
         for (int64_t j = j0; j < j1; j++) {
             const int t = (int)(j - j0);
 #pragma unroll
             for (int w = 0; w < VPL; w++)
-                if (piece[w]) {
-                    float4 o;
-                    o.x = arg[w].x == t ? gu[w].x : 0.f;
-                    o.y = arg[w].y == t ? gu[w].y : 0.f;
-                    o.z = arg[w].z == t ? gu[w].z : 0.f;
-                    o.w = arg[w].w == t ? gu[w].w : 0.f;
-                    {   // written once, read back once by the row-gradient sum: a streaming store
-                        typedef float f32x4m __attribute__((ext_vector_type(4)));
-                        const f32x4m ov = {o.x, o.y, o.z, o.w};
-                        __builtin_nontemporal_store(ov, reinterpret_cast<f32x4m *>(emb) + j * pieces + w * LPR + r);
-                    }
-                }
+                if (piece[w])
+                    won[j * 4 * won_lpr + place[w]] = (uint8_t)((arg[w].x == t ? 1 : 0) | (arg[w].y == t ? 2 : 0) |
+                                                              (arg[w].z == t ? 4 : 0) | (arg[w].w == t ? 8 : 0));
         }
     }
 }
@@ -643,7 +691,7 @@ struct BwdWs {
     float *g_u, *partials;
     uint32_t *pos_list;  // unique list of every position of u_values
     float *pay_w;        // weighted lookup: weight of every sorted entry of step B
-    float *emb;          // max pooling: one masked gradient row per position of u_values [M, D]
+    uint32_t *won;       // max pooling [M, row_lanes(D)]: which elements of every piece the position won
     int long_seg;        // step B: segments with more entries are cut into chunks
     size_t bytes;
 };
@@ -656,7 +704,14 @@ struct BwdWs {
 // 4.55 with 32.
 constexpr int kDefaultLongSeg = 32;
 
-BwdWs carve_bwd(char *base, int F, int64_t B, int64_t M_cap, int D, int long_seg, bool with_emb = false)
+// Lanes that carry a row in the row-gradient sum (up to four 16-byte pieces each).
+int row_lanes(int D)
+{
+    const int P = D / 4;
+    return P <= 16 ? 4 : (P <= 32 ? 8 : (P <= 64 ? 16 : (P <= 128 ? 32 : 64)));
+}
+
+BwdWs carve_bwd(char *base, int F, int64_t B, int64_t M_cap, int D, int long_seg, bool with_won = false)
 {
     WsCarver c(base);
     BwdWs w;
@@ -679,7 +734,7 @@ BwdWs carve_bwd(char *base, int F, int64_t B, int64_t M_cap, int D, int long_seg
     w.g_u = c.take<float>((size_t)u_cap * D);
     w.pos_list = c.take<uint32_t>(M_cap);
     w.pay_w = c.take<float>(M_cap);
-    w.emb = with_emb ? c.take<float>((size_t)M_cap * D) : nullptr;
+    w.won = with_won ? c.take<uint32_t>((size_t)M_cap * row_lanes(D)) : nullptr;
     w.bytes = c.off;
     return w;
 }
@@ -759,10 +814,12 @@ RecdGroupArgs group_args(const BwdWs &w, int F, int64_t B, int64_t U_cap, int64_
 // Step B after the grouping: all segments in one launch, optimizer fused.
 recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t n_cap, int64_t seg_bound,
                      const void *table, int D, void *out, int64_t *touched_rows, const OptAdagrad *opt,
-                     const float *pay_w)
+                     const float *pay_w, const uint32_t *won = nullptr)
 {
     hipStream_t st = ctx->stream;
     RowSumParams rp = row_params(w, ps, pay_w, table, D, out);
+    rp.pay_pos = reinterpret_cast<const uint32_t *>(pay_w);  // what lies beside the entries: weights or positions
+    rp.won = won;
     OptAdagrad o;
     if (opt)
         o = *opt;
@@ -770,8 +827,7 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
         o.n_feat = 0;
     o.touched_rows = touched_rows;
     o.seg_feat = w.seg_feat;
-    const int P = rp.pieces;
-    const int lpr = P <= 16 ? 4 : (P <= 32 ? 8 : (P <= 64 ? 16 : (P <= 128 ? 32 : 64)));
+    const int lpr = row_lanes(D);
     const int per_block = 4 * (64 / lpr);
     int64_t nblk = (seg_bound + per_block - 1) / per_block;
     const int64_t cap = (int64_t)ctx->num_cu * 64;
@@ -788,20 +844,22 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
     rp.chunk_blocks = (unsigned)((cblk + 7) / 8 * 8);
     const dim3 grid((unsigned)(nblk + rp.chunk_blocks)), block(256);
     recd_time_begin(ctx, RECD_T_GRAD_ROWS, st);
-    auto launch = [&](auto wt) {
-        constexpr bool WT = decltype(wt)::value;
+    auto launch = [&](auto mode) {
+        constexpr int MODE = decltype(mode)::value;
         switch (lpr) {
-        case 4: hipLaunchKernelGGL((k_segsum_rows<4, WT>), grid, block, 0, st, rp, o); break;
-        case 8: hipLaunchKernelGGL((k_segsum_rows<8, WT>), grid, block, 0, st, rp, o); break;
-        case 16: hipLaunchKernelGGL((k_segsum_rows<16, WT>), grid, block, 0, st, rp, o); break;
-        case 32: hipLaunchKernelGGL((k_segsum_rows<32, WT>), grid, block, 0, st, rp, o); break;
-        default: hipLaunchKernelGGL((k_segsum_rows<64, WT>), grid, block, 0, st, rp, o); break;
+        case 4: hipLaunchKernelGGL((k_segsum_rows<4, MODE>), grid, block, 0, st, rp, o); break;
+        case 8: hipLaunchKernelGGL((k_segsum_rows<8, MODE>), grid, block, 0, st, rp, o); break;
+        case 16: hipLaunchKernelGGL((k_segsum_rows<16, MODE>), grid, block, 0, st, rp, o); break;
+        case 32: hipLaunchKernelGGL((k_segsum_rows<32, MODE>), grid, block, 0, st, rp, o); break;
+        default: hipLaunchKernelGGL((k_segsum_rows<64, MODE>), grid, block, 0, st, rp, o); break;
         }
     };
-    if (pay_w)
-        launch(std::true_type());
+    if (won)
+        launch(std::integral_constant<int, ROWS_MAX>());
+    else if (pay_w)
+        launch(std::integral_constant<int, ROWS_WEIGHTED>());
     else
-        launch(std::false_type());
+        launch(std::integral_constant<int, ROWS_PLAIN>());
     recd_time_end(ctx, RECD_T_GRAD_ROWS, st);
     RECD_HIP(ctx, hipGetLastError());
     return RECD_OK;
@@ -838,7 +896,7 @@ static recd_status check_distinct_tables(recd_ctx *ctx, int F, void *const *tabl
 // segment of step A is one unique list, in order: each has at least one row).
 // u_weights: the pooled path's lookup was the weighted sum: position j hands u_weights[j] * g_u on.
 // max_tables: the pooled path's lookup was the maximum over these fp32 tables: element d of g_u
-// goes to the position that won it (k_max_route), then step B adds per-position rows.
+// goes to the position that won it (k_max_winner); step B takes of g_u what each position won.
 static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, int64_t B, int64_t N, int D,
                                    const float *grad_out, const int64_t *kjt_offsets,
                                    const int32_t *inverse, const int64_t *feat_uoff,
@@ -924,8 +982,10 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
     RecdGroupArgs ga = group_args(w, F, B, U_cap, M_cap, max_rows, inverse, feat_uoff, u_values, u_offsets,
                                   touched_rows, feat_roff);
     ga.pay_positions = seq || u_weights || maxmode ? 1 : 0;  // the later sum's source row: position or list
-    if (seq || maxmode)
+    if (seq)
         ga.pos_list = nullptr;
+    if (maxmode)
+        ga.pay_pos = reinterpret_cast<uint32_t *>(w.pay_w);  // the sorted positions take the place of weights
     ga.u_weights = u_weights;
     ga.pay_w = w.pay_w;
     RECD_TRY(recd_group(ctx, st, w.group, ga));
@@ -978,8 +1038,8 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
                 nblk = (int64_t)ctx->num_cu * 64;
             const dim3 grid((unsigned)(nblk < 1 ? 1 : nblk)), block(256);
 #define RECD_MR(L, V)                                                                                    \
-    hipLaunchKernelGGL((k_max_route<L, V>), grid, block, 0, st, u_values, u_offsets, feat_uoff, f0, nf, mt,  \
-                       reinterpret_cast<const float4 *>(w.g_u), reinterpret_cast<float4 *>(w.emb), P, U_cap, \
+    hipLaunchKernelGGL((k_max_winner<L, V>), grid, block, 0, st, u_values, u_offsets, feat_uoff, f0, nf, mt,  \
+                       reinterpret_cast<uint8_t *>(w.won), row_lanes(D), P, U_cap,                            \
                        M_cap)
             if (vpl == 4) RECD_MR(64, 4);
             else if (vpl == 2) RECD_MR(64, 2);
@@ -992,10 +1052,10 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         }
         RECD_HIP(ctx, hipGetLastError());
     }
-    const float *b_table = seq ? grad_emb : (maxmode ? w.emb : w.g_u);
+    const float *b_table = seq ? grad_emb : w.g_u;
     // ---- step B: sum the source rows of every (feature, row) into grad_rows -------------------------
     RECD_TRY(sum_rows(ctx, w, ps_b, M_cap, M_cap, b_table, D, grad_rows, touched_rows, fused ? &oa : nullptr,
-                      u_weights ? w.pay_w : nullptr));
+                      u_weights || maxmode ? w.pay_w : nullptr, maxmode ? w.won : nullptr));
     // ---- optimizer -------------------------------------------------------------------------------
     if (tables && !fused) {
         for (int f0 = 0; f0 < F; f0 += RECD_F_PER_LAUNCH) {

@@ -107,6 +107,7 @@ struct GroupParams {
     int pay_positions;          // 1: the payload is the position also where pos_list is written
     const float *u_weights;     // weights of the positions, or null; sorted ones go to pay_w and the
     float *pay_w;               // payload of the last pass is pos_list of the position
+    uint32_t *pay_pos;          // as pay_w, with the positions themselves; or null
     const int64_t *run_index;   // not null: only its count is compared with runs_cap
     int64_t runs_cap;
     int64_t *n_dev_a, *n_dev_b; // [0] entries, [1] the caller's bound was too small
@@ -635,7 +636,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
             sh.out.pay[rank[u]] = pay[u];
         }
     __syncthreads();
-    const bool weigh = !side_a && g.u_weights && pass == s.passes - 1;
+    const bool resolve = !side_a && (g.u_weights || g.pay_pos) && pass == s.passes - 1;
 #pragma unroll
     for (int u = 0; u < kItems; u++) {
         const uint32_t i = tid + u * kTileThreads;
@@ -643,9 +644,12 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
             const uint32_t kk = sh.out.key[i], pp = sh.out.pay[i];
             const uint32_t dst = s_from[(kk >> shift) & mask] + i;
             kout[dst] = kk;
-            if (weigh) {  // the entry's source row and weight, both in sorted order
+            if (resolve) {  // the entry's source row and its weight or position, both in sorted order
                 pout[dst] = g.pos_list[pp];
-                g.pay_w[dst] = g.u_weights[pp];
+                if (g.u_weights)
+                    g.pay_w[dst] = g.u_weights[pp];
+                else
+                    g.pay_pos[dst] = pp;
             } else {
                 pout[dst] = pp;
             }
@@ -917,7 +921,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
             } else {
                 key[u] = s_key[i] | (uint32_t)g.u_values[i];
                 pay[u] = g.pay_positions ? i : s_pay[i];
-                if (g.u_weights)
+                if (g.u_weights || g.pay_pos)
                     g.pos_list[i] = s_pay[i];
             }
         }
@@ -1066,9 +1070,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
         if (u >= rounds || i >= n)
             continue;
         const uint32_t pp = s_pay[i];
-        if (g.u_weights) {  // the entry's source row and weight, both in sorted order
+        if (g.u_weights || g.pay_pos) {  // the entry's source row and its weight or position, both in sorted order
             g.b.pay[0][i] = g.pos_list[pp];
-            g.pay_w[i] = g.u_weights[pp];
+            if (g.u_weights)
+                g.pay_w[i] = g.u_weights[pp];
+            else
+                g.pay_pos[i] = pp;
         } else {
             g.b.pay[0][i] = pp;
         }
@@ -1242,6 +1249,7 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     g.pay_positions = a.pay_positions;
     g.u_weights = a.u_weights;
     g.pay_w = a.pay_w;
+    g.pay_pos = a.pay_pos;
     g.run_index = a.run_index;
     g.runs_cap = a.runs_cap;
     g.n_dev_a = w.a.n_dev;

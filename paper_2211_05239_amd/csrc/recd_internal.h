@@ -248,6 +248,7 @@ struct RecdGroupArgs {
     int pay_positions;           // 1: side B's payload is the position j, 0: its list
     const float *u_weights;      // weighted lookup: the payload of the result is the list, and
     float *pay_w;                // pay_w the weights in sorted order (pay_positions = 1, pos_list given)
+    uint32_t *pay_pos;           // max pooling: the same with the positions in the place of weights
     int64_t *seg_start_a, *list_off_a;   // rows of list u: payload a[seg_start_a[u] .. seg_start_a[u+1])
     int64_t *seg_start_b, *list_off_b;   // positions of the t-th distinct row; list_off_b[1] = their number
     int64_t *touched_rows, *feat_roff;
