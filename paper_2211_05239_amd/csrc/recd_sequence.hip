@@ -418,12 +418,14 @@ recd_status recd_jagged_expand_inverse(recd_ctx *ctx, int F, int64_t B, int64_t 
             return recd_fail(ctx, RECD_EBOUNDS, "a row's unique slot holds a list of another length");
     }
     const int vecs = (int)((size_t)D * elem_size(dt) / 16);
-    // Lists per block: about 128 rows to read and write per block.  Small blocks keep the region
-    // that the resident blocks write at any one time compact, which measures faster than large
-    // blocks although runs of duplicates are cut at block borders.
-    const double avg = (double)N / (double)L;
+    // Lists per block: 10 to 20 KB of output.  Small blocks keep the region that the resident blocks write at
+    // any one time compact, which measures faster than large blocks although runs of duplicates are cut at
+    // block borders: 0.9 M rows, 7 / 14 / 28 / 56 KB a block, us: 512-byte rows (from 14 on) 83 / 88 / 92,
+    // 256-byte rows 62 / 41 / 46 / 50, 64-byte rows 24 / 14 / 14 / 15 (3.5 KB: 43); a fill of the same
+    // size takes 65, 32 and 8.  (About 128 rows a block whatever their size before.)
+    const double avg = (double)N / (double)L * (double)(vecs * 16);
     int lists = 2;
-    while (lists < 64 && 2.0 * lists * avg <= 192.0)
+    while (lists < 64 && 2.0 * lists * avg <= 20480.0)
         lists *= 2;
 #define JAG(LISTS)                                                                                \
     hipLaunchKernelGGL((k_jagged_expand<LISTS, kRPT>),                                             \
