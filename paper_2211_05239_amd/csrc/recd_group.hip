@@ -97,6 +97,7 @@ struct GroupParams {
     SideParams a, b;
     int tpf, cpf;               // side A: tiles and chunks of a feature
     unsigned a_blocks;          // blocks of the running launch that work on side A
+    unsigned list_block0;       // k_group_count: the first block that writes pos_list
     // side B
     uint32_t *pb;               // [F+1] first position of every feature
     uint32_t *queue_start;      // [kQueues+1] first tile of every queue
@@ -151,16 +152,25 @@ __device__ __forceinline__ void write_bases(const SideParams &s, int f, const ui
 // A block takes a chunk of one feature's entries (a tile, or as many as keep the chunks below some 500),
 // counts the digits of all passes in LDS and, where the feature is a single chunk, turns the counts into
 // digit starts at once; else the block that arrives last adds up the feature's chunks.  The block also
-// clears the look-back flags of its tiles, and on side B writes the list of every position.  What is
+// clears the look-back flags of its tiles; further blocks write the list of every position.  What is
 // read is small (8 bytes an entry): the kernel is a few dependent round trips and the LDS atomics of a
 // chunk. 
 __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams g)
 {
     extern __shared__ uint32_t s_dyn[];          // the counts [passes * radix], side B also pb [F+1]: as little
     uint32_t *s_hist = s_dyn;                    // LDS as there is, so that blocks find room beside the lookup's
-    __shared__ uint32_t s_off[kCountThreads + 1];
     __shared__ uint32_t s_pick[6];
     const int tid = threadIdx.x;
+    if (blockIdx.x >= g.list_block0) {
+        // the list of every position, 16 lanes to a list: blocks of their own, beside the chain of the others
+        const int64_t U = g.feat_uoff[g.F], step = (int64_t)(gridDim.x - g.list_block0) * (kCountThreads / 16);
+        for (int64_t u = (int64_t)(blockIdx.x - g.list_block0) * (kCountThreads / 16) + tid / 16; u < U; u += step) {
+            const int64_t at = g.u_offsets[u], end = g.u_offsets[u + 1] < g.M_cap ? g.u_offsets[u + 1] : g.M_cap;
+            for (int64_t j = at + tid % 16; j < end; j += 16)
+                g.pos_list[j] = (uint32_t)u;
+        }
+        return;
+    }
     const bool side_a = blockIdx.x < g.a_blocks;
     const SideParams &s = side_a ? g.a : g.b;
     const unsigned blk = side_a ? blockIdx.x : blockIdx.x - g.a_blocks;
@@ -311,7 +321,6 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
     // look-back flags of the chunk's tiles
     for (int i = tid; i < (int)((n + kTile - 1) / kTile) * s.passes; i += kCountThreads)
         s.flag[(size_t)(i % s.passes) * s.tiles_cap + first_tile + i / s.passes] = 0;
-    // a feature's counts leave before the lists are written: acknowledged by the time the arrival is counted
     const int words = s.passes * radix;
     __syncthreads();
     if (n_chunks == 1) {
@@ -320,43 +329,6 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         uint32_t *row = s.chunk_hist + chunk_row * words;
         for (int i = tid; i < words; i += kCountThreads)
             st_agent(row + i, s_hist[i]);
-    }
-    if (!side_a && g.pos_list) {
-        // the last list of the feature that starts at or before the chunk's first position: 256 places
-        // of the remaining stretch are tried at once (two rounds for 65 K lists)
-        int64_t lo = g.feat_uoff[f], hi = g.feat_uoff[f + 1];
-        const int64_t u_end = hi;
-        while (c > 0 && hi - lo > 1) {
-            const int64_t step = (hi - lo + kCountThreads - 1) / kCountThreads;
-            const int64_t at = lo + tid * step;
-            const bool le = at < hi && g.u_offsets[at] <= (int64_t)begin;
-            __syncthreads();
-            if (tid == 0)
-                s_pick[0] = 0;
-            __syncthreads();
-            const uint64_t m = __ballot(le);
-            if ((tid & 63) == 0)
-                atomicAdd(&s_pick[0], (uint32_t)__popcll(m));
-            __syncthreads();
-            // the list at lo starts at or before begin, so at least one place passed
-            lo += ((int64_t)s_pick[0] - 1) * step;
-            hi = lo + step < hi ? lo + step : hi;
-        }
-        // it and the lists behind it, 256 at a time; 16 lanes write a list's positions
-        for (int64_t u0 = lo; u0 < u_end; u0 += kCountThreads) {
-            const int nl = (int)(u_end - u0 < kCountThreads ? u_end - u0 : kCountThreads);
-            __syncthreads();
-            for (int i = tid; i <= nl; i += kCountThreads) {
-                const int64_t at = g.u_offsets[u0 + i];
-                s_off[i] = (uint32_t)(at < (int64_t)begin ? 0 : (at < (int64_t)end ? at - begin : n));
-            }
-            __syncthreads();
-            for (int i = tid / 16; i < nl; i += kCountThreads / 16)
-                for (uint32_t j = s_off[i] + tid % 16; j < s_off[i + 1]; j += 16)
-                    g.pos_list[begin + j] = (uint32_t)(u0 + i);
-            if (s_off[nl] >= n)
-                break;  // the same value in every thread
-        }
     }
     if (n_chunks == 1)
         return;
@@ -1277,7 +1249,11 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     const unsigned a_tiles = (unsigned)((g.a.tiles_cap + kQueues - 1) / kQueues * kQueues);
     const unsigned b_tiles = (unsigned)(a.M_cap / kTile + a.F + 1);
     g.a_blocks = (unsigned)((int64_t)a.F * g.cpf);
-    const unsigned cb = g.a_blocks + (unsigned)(a.M_cap / g.b.chunk + a.F + 1);
+    g.list_block0 = g.a_blocks + (unsigned)(a.M_cap / g.b.chunk + a.F + 1);
+    int64_t list_blocks = ((a.U_cap < g.n_lists ? a.U_cap : g.n_lists) + kCountThreads / 16 - 1) / (kCountThreads / 16);
+    if (list_blocks > (int64_t)ctx->num_cu * 8)
+        list_blocks = (int64_t)ctx->num_cu * 8;
+    const unsigned cb = g.list_block0 + (a.pos_list ? (unsigned)(list_blocks < 1 ? 1 : list_blocks) : 0u);
     const size_t lds_a = (size_t)g.a.passes << g.a.dbits, lds_b = ((size_t)g.b.passes << g.b.dbits) + a.F + 1;
     const size_t lds = (lds_a > lds_b ? lds_a : lds_b) * sizeof(uint32_t);
     hipLaunchKernelGGL(k_group_count, dim3(cb), dim3(kCountThreads), lds, st, g);
