@@ -689,6 +689,7 @@ struct BwdWs {
     RecdChunk *chunks;
     uint32_t *chunk_arrive;
     float *g_u, *partials;
+    int64_t lists_cap;   // rows of g_u
     uint32_t *pos_list;  // unique list of every position of u_values
     float *pay_w;        // weighted lookup: weight of every sorted entry of step B
     uint32_t *won;       // max pooling [M, row_lanes(D)]: which elements of every piece the position won
@@ -711,13 +712,13 @@ int row_lanes(int D)
     return P <= 16 ? 4 : (P <= 32 ? 8 : (P <= 64 ? 16 : (P <= 128 ? 32 : 64)));
 }
 
-BwdWs carve_bwd(char *base, int F, int64_t B, int64_t M_cap, int D, int long_seg, bool with_won = false)
+BwdWs carve_bwd(char *base, int F, int64_t B, int64_t U_cap, int64_t M_cap, int D, int long_seg, bool with_won = false)
 {
     WsCarver c(base);
     BwdWs w;
     (void)c.take<char>(1024);  // the head of the workspace stays with the validation passes' flags
     const int64_t n_lists = (int64_t)F * B;
-    int64_t u_cap = M_cap + F < n_lists ? M_cap + F : n_lists;
+    w.lists_cap = recd_lists_held(F, B, U_cap, M_cap);
     w.group = recd_group_carve(c, F, B, M_cap);
     w.list_off = c.take<int64_t>(2);
     w.seg_start = c.take<int64_t>(n_lists + 1);
@@ -731,7 +732,7 @@ BwdWs carve_bwd(char *base, int F, int64_t B, int64_t M_cap, int D, int long_seg
     w.chunks = c.take<RecdChunk>(item_cap);
     w.chunk_arrive = c.take<uint32_t>(item_cap);
     w.partials = c.take<float>((size_t)item_cap * D);
-    w.g_u = c.take<float>((size_t)u_cap * D);
+    w.g_u = c.take<float>((size_t)w.lists_cap * D);
     w.pos_list = c.take<uint32_t>(M_cap);
     w.pay_w = c.take<float>(M_cap);
     w.won = with_won ? c.take<uint32_t>((size_t)M_cap * row_lanes(D)) : nullptr;
@@ -808,6 +809,7 @@ RecdGroupArgs group_args(const BwdWs &w, int F, int64_t B, int64_t U_cap, int64_
     a.chunks = w.chunks;
     a.chunk_arrive = w.chunk_arrive;
     a.long_seg = w.long_seg;
+    a.lists_cap = w.lists_cap;
     return a;
 }
 
@@ -869,7 +871,7 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
 
 size_t recd_backward_workspace(int F, int64_t B, int64_t M_cap, int D)
 {
-    return carve_bwd(nullptr, F, B, M_cap, D, kDefaultLongSeg).bytes;
+    return carve_bwd(nullptr, F, B, (int64_t)F * B, M_cap, D, kDefaultLongSeg).bytes;
 }
 
 // The fused update reads and writes a table row (and its accumulator) once per (feature, row)
@@ -887,6 +889,18 @@ static recd_status check_distinct_tables(recd_ctx *ctx, int F, void *const *tabl
             return recd_fail(ctx, RECD_EINVAL,
                              "tables[] and adagrad_state[] must each hold pairwise distinct pointers "
                              "(one table per feature)");
+    return RECD_OK;
+}
+
+// What the grouping found about the caller's bounds (host_pinned[1]: side B's word, [2]: side A's).
+static recd_status check_bounds(recd_ctx *ctx, int64_t U_cap, int64_t M_cap)
+{
+    if (ctx->host_pinned[1])
+        return recd_fail(ctx, RECD_ECAPACITY, "M_cap=%lld is smaller than M", (long long)M_cap);
+    if (ctx->host_pinned[2] & RECD_GROUP_LISTS)
+        return recd_fail(ctx, RECD_ECAPACITY, "U_cap=%lld is smaller than U", (long long)U_cap);
+    if (ctx->host_pinned[2] & RECD_GROUP_RUNS)
+        return recd_fail(ctx, RECD_ECAPACITY, "runs_cap is smaller than the number of runs");
     return RECD_OK;
 }
 
@@ -949,8 +963,8 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         RECD_TRY(recd_validate_inverse(ctx, F, B, feat_uoff, inverse));
     const bool maxmode = max_tables != nullptr;
     ctx->plan.valid = false;  // this call reuses the workspace a plan would live in
-    RECD_TRY(recd_reserve(ctx, carve_bwd(nullptr, F, B, M_cap, D, ctx->long_seg_cut, maxmode).bytes));
-    const BwdWs w = carve_bwd(ctx->ws, F, B, M_cap, D, ctx->long_seg_cut, maxmode);
+    RECD_TRY(recd_reserve(ctx, carve_bwd(nullptr, F, B, U_cap, M_cap, D, ctx->long_seg_cut, maxmode).bytes));
+    const BwdWs w = carve_bwd(ctx->ws, F, B, U_cap, M_cap, D, ctx->long_seg_cut, maxmode);
     hipStream_t st = ctx->stream;
 
     if (n_lists == 0 || M_cap == 0) {
@@ -1075,12 +1089,13 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
     if (host_R) {
         RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned, w.list_off_b + 1, sizeof(int64_t),
                                      hipMemcpyDeviceToHost, st));
-        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 1, w.group.b.n_dev + 1, sizeof(int64_t),
+        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 1, w.group.b.too_small, sizeof(int64_t),
+                                     hipMemcpyDeviceToHost, st));
+        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 2, w.group.a.too_small, sizeof(int64_t),
                                      hipMemcpyDeviceToHost, st));
         RECD_HIP(ctx, hipStreamSynchronize(st));
         host_R[0] = ctx->host_pinned[0];
-        if (ctx->host_pinned[1])
-            return recd_fail(ctx, RECD_ECAPACITY, "M_cap=%lld is smaller than M", (long long)M_cap);
+        RECD_TRY(check_bounds(ctx, U_cap, M_cap));
     }
     return RECD_OK;
 }
@@ -1132,8 +1147,8 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
     // the side stream may start at the end of the build only if nothing on the stream has used the
     // workspace since (this call's own reservation does not count)
     const bool ws_idle_since_build = !ctx->ws_used_since_build;
-    RECD_TRY(recd_reserve(ctx, carve_bwd(nullptr, F, B, M_cap, D, ctx->long_seg_cut).bytes));
-    const BwdWs w = carve_bwd(ctx->ws, F, B, M_cap, D, ctx->long_seg_cut);
+    RECD_TRY(recd_reserve(ctx, carve_bwd(nullptr, F, B, U_cap, M_cap, D, ctx->long_seg_cut).bytes));
+    const BwdWs w = carve_bwd(ctx->ws, F, B, U_cap, M_cap, D, ctx->long_seg_cut);
     recd_ctx::BackwardPlan &pl = ctx->plan;
     pl.F = F;
     pl.B = B;
@@ -1230,7 +1245,7 @@ extern "C" recd_status recd_backward_apply(recd_ctx *ctx, recd_pooling mode, con
     RECD_TRY(check_distinct_tables(ctx, F, tables, adagrad_state));
     RECD_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
-    const BwdWs w = carve_bwd(ctx->ws, F, B, M_cap, D, ctx->long_seg_cut);
+    const BwdWs w = carve_bwd(ctx->ws, F, B, pl.U_cap, M_cap, D, ctx->long_seg_cut);
     if (pl.pending)
         RECD_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_plan, 0));
     pl.pending = false;  // the stream now waits for everything the plan enqueued
@@ -1273,16 +1288,13 @@ extern "C" recd_status recd_backward_apply(recd_ctx *ctx, recd_pooling mode, con
     }
     if (host_R) {
         RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned, w.list_off_b + 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 1, w.group.b.n_dev + 1, sizeof(int64_t), hipMemcpyDeviceToHost,
+        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 1, w.group.b.too_small, sizeof(int64_t), hipMemcpyDeviceToHost,
                                      st));
-        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 2, w.group.a.n_dev + 1, sizeof(int64_t), hipMemcpyDeviceToHost,
+        RECD_HIP(ctx, hipMemcpyAsync(ctx->host_pinned + 2, w.group.a.too_small, sizeof(int64_t), hipMemcpyDeviceToHost,
                                      st));
         RECD_HIP(ctx, hipStreamSynchronize(st));
         host_R[0] = ctx->host_pinned[0];
-        if (ctx->host_pinned[1])
-            return recd_fail(ctx, RECD_ECAPACITY, "M_cap=%lld is smaller than M", (long long)M_cap);
-        if (ctx->host_pinned[2])
-            return recd_fail(ctx, RECD_ECAPACITY, "runs_cap is smaller than the number of runs");
+        RECD_TRY(check_bounds(ctx, pl.U_cap, M_cap));
     }
     return RECD_OK;
 }

@@ -111,7 +111,8 @@ struct GroupParams {
     uint32_t *pay_pos;          // as pay_w, with the positions themselves; or null
     const int64_t *run_index;   // not null: only its count is compared with runs_cap
     int64_t runs_cap;
-    int64_t *n_dev_a, *n_dev_b; // [0] entries, [1] the caller's bound was too small
+    int64_t *too_small_a, *too_small_b;  // whether the caller's bounds were too small
+    int64_t lists_cap;          // no list at or beyond this is summed: a position of such a list names the last
     // segments
     uint64_t *seg_status;       // [tiles] look-back words of the numbering
     int64_t *seg_start_a, *list_off_a, *seg_start_b, *list_off_b;
@@ -122,6 +123,13 @@ struct GroupParams {
     uint32_t *chunk_arrive;
     int long_seg;
 };
+
+// Side A's word about the caller's bounds, for U unique lists.
+__device__ __forceinline__ void report_side_a(const GroupParams &g, int64_t U)
+{
+    g.too_small_a[0] = (g.run_index && g.run_index[0] > g.runs_cap ? RECD_GROUP_RUNS : 0) |
+                       (U > g.lists_cap ? RECD_GROUP_LISTS : 0);
+}
 
 // Digit starts of feature f from the block's counts in LDS.
 __device__ __forceinline__ void write_bases(const SideParams &s, int f, const uint32_t *hist)
@@ -166,8 +174,9 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         const int64_t U = g.feat_uoff[g.F], step = (int64_t)(gridDim.x - g.list_block0) * (kCountThreads / 16);
         for (int64_t u = (int64_t)(blockIdx.x - g.list_block0) * (kCountThreads / 16) + tid / 16; u < U; u += step) {
             const int64_t at = g.u_offsets[u], end = g.u_offsets[u + 1] < g.M_cap ? g.u_offsets[u + 1] : g.M_cap;
+            const uint32_t name = (uint32_t)(u < g.lists_cap ? u : g.lists_cap - 1);
             for (int64_t j = at + tid % 16; j < end; j += 16)
-                g.pos_list[j] = (uint32_t)u;
+                g.pos_list[j] = name;
         }
         return;
     }
@@ -192,10 +201,8 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         first_tile = (size_t)(q * per_q + (q < more ? q : more) + f / kQueues) * g.tpf + (size_t)c * (s.chunk / kTile);
         chunk_row = blk;
         tiles_f = g.tpf;
-        if (blk == 0 && tid == 0) {
-            g.n_dev_a[0] = g.n_lists;
-            g.n_dev_a[1] = g.run_index && g.run_index[0] > g.runs_cap ? 1 : 0;
-        }
+        if (blk == 0 && tid == 0)
+            report_side_a(g, g.feat_uoff[g.F]);
     } else {
         uint32_t *s_pb = s_dyn + (s.passes << s.dbits);
         // where every feature's positions lie; tiles and chunks of the features before each one
@@ -262,8 +269,7 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
             if (tid == 0) {
                 g.tile_total[0] = all_q;
                 const int64_t M = g.u_offsets[g.feat_uoff[g.F]];
-                g.n_dev_b[0] = M < g.M_cap ? M : g.M_cap;
-                g.n_dev_b[1] = M > g.M_cap ? 1 : 0;
+                g.too_small_b[0] = M > g.M_cap ? 1 : 0;
                 g.chunk_count[0] = 0;
             }
         }
@@ -663,7 +669,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
                 if ((int)f == g.F - 1) {
                     g.seg_start_a[u1] = n;
                     g.list_off_a[0] = 0;
-                    g.list_off_a[1] = u1;
+                    g.list_off_a[1] = u1 < g.lists_cap ? u1 : g.lists_cap;
                 }
             }
         }
@@ -856,8 +862,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
         const int64_t M = g.u_offsets[g.feat_uoff[g.F]];
         n = (uint32_t)(M < g.M_cap ? M : g.M_cap);
         if (tid == 0) {
-            g.n_dev_b[0] = n;
-            g.n_dev_b[1] = M > g.M_cap ? 1 : 0;
+            g.too_small_b[0] = M > g.M_cap ? 1 : 0;
             s_chunks = 0;
         }
         __syncthreads();
@@ -871,8 +876,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
                 if (f + st < g.F && s_fu[f + st] <= u)
                     f += st;
             const uint32_t end = e < (int64_t)n ? (uint32_t)e : n;
+            const uint32_t name = (int64_t)u < g.lists_cap ? u : (uint32_t)(g.lists_cap - 1);
             for (uint32_t j = a < (int64_t)n ? (uint32_t)a : n; j < end; j++) {
-                s_pay[j] = u;
+                s_pay[j] = name;
                 s_key[j] = (uint32_t)f << row_bits;
             }
         }
@@ -979,9 +985,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
                 if ((int)f_a == g.F - 1) {
                     g.seg_start_a[u1] = g.n_lists;
                     g.list_off_a[0] = 0;
-                    g.list_off_a[1] = u1;
-                    g.n_dev_a[0] = g.n_lists;
-                    g.n_dev_a[1] = g.run_index && g.run_index[0] > g.runs_cap ? 1 : 0;
+                    g.list_off_a[1] = u1 < g.lists_cap ? u1 : g.lists_cap;
+                    report_side_a(g, u1);
                 }
             }
         }
@@ -1134,7 +1139,7 @@ RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap)
             s.key[i] = c.take<uint32_t>(n);
             s.pay[i] = c.take<uint32_t>(n);
         }
-        s.n_dev = c.take<int64_t>(2);
+        s.too_small = c.take<int64_t>(1);
         s.tiles_cap = tiles;
         s.base = c.take<uint32_t>((size_t)F * words_per_tile);
         s.chunk_hist = c.take<uint32_t>((size_t)chunks * words_per_tile);
@@ -1224,8 +1229,8 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     g.pay_pos = a.pay_pos;
     g.run_index = a.run_index;
     g.runs_cap = a.runs_cap;
-    g.n_dev_a = w.a.n_dev;
-    g.n_dev_b = w.b.n_dev;
+    g.too_small_a = w.a.too_small;
+    g.too_small_b = w.b.too_small;
     g.seg_status = w.seg_status;
     g.seg_start_a = a.seg_start_a;
     g.list_off_a = a.list_off_a;
@@ -1238,6 +1243,7 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     g.chunks = a.chunks;
     g.chunk_arrive = a.chunk_arrive;
     g.long_seg = a.long_seg;
+    g.lists_cap = a.lists_cap;
     if (recd_group_is_small(a.F, a.B, a.M_cap, a.max_rows)) {
         const int row_bits = bits_for((uint64_t)(a.max_rows > 1 ? a.max_rows - 1 : 1));
         int passes, dbits;

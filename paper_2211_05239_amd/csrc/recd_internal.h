@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "recd.h"
+#include "recd_rules.h"
 
 // Optional HIP-event brackets around single kernel launches (benchmark instrumentation, off by
 // default): `slot` names the kernel, every bracket is one pair of events on the stream the kernel is
@@ -224,7 +225,7 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a);
 struct RecdGroupWs {
     struct Side {
         uint32_t *key[2], *pay[2];
-        int64_t *n_dev;          // [0] entries, [1] the caller's bound was too small
+        int64_t *too_small;      // whether the caller's bound was too small (side A: RECD_GROUP_*)
         int64_t tiles_cap;
         uint32_t *base, *chunk_hist, *ticket, *own, *upto, *flag;
     } a, b;
@@ -257,7 +258,10 @@ struct RecdGroupArgs {
     RecdChunk *chunks;           // a zero for each segment, at its first chunk
     uint32_t *chunk_arrive;
     int long_seg;
+    int64_t lists_cap;           // lists that there is room for: what lies beyond is left out and reported
 };
+// Side A's too_small word: which of the caller's bounds were too small.
+enum { RECD_GROUP_RUNS = 1, RECD_GROUP_LISTS = 2 };
 RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap);
 recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, const RecdGroupArgs &a);
 // Whether both sides are grouped by one launch.

@@ -64,3 +64,19 @@ def test_product_has_no_oracle_import():
                 text = open(os.path.join(dirpath, fn)).read()
                 assert "import oracle" not in text and "from oracle" not in text, fn
                 assert "librecd_oracle" not in text, fn
+
+
+def _workspace(F, B, N, D):
+    lib = C.CDLL(LIB)
+    lib.recd_workspace_bytes.argtypes = [C.c_int, C.c_int64, C.c_int64, C.c_int, C.POINTER(C.c_size_t)]
+    out = C.c_size_t(0)
+    assert lib.recd_workspace_bytes(F, B, N, D, C.byref(out)) == 0
+    return out.value
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="librecd.so not built")
+@pytest.mark.parametrize("F,B,N", [(3, 8192, 8195), (6, 1000, 40), (64, 16384, 1000), (2, 7, 0)])
+def test_workspace_holds_a_row_of_every_unique_list(F, B, N):
+    """The backward sums one fp32 row per unique list, and a grouped IKJT may hold F * B lists with hardly an id
+    among them."""
+    assert _workspace(F, B, N, 128) - _workspace(F, B, N, 64) >= F * B * 64 * 4

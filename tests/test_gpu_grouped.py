@@ -184,3 +184,54 @@ def test_grouped_forward_backward(ctx, name, F, B, groups):
     assert R == len(tr) and np.array_equal(touched[:R].cpu().numpy(), tr)
     assert np.array_equal(feat_roff.cpu().numpy(), fr)
     gu.assert_close_f32(gu.out_to_f64(grad_rows[:R]), gr, "row gradients on a grouped IKJT")
+
+
+@pytest.mark.parametrize("B", [600, 9000])   # grouped by one launch and by four
+@pytest.mark.parametrize("planned", [False, True])
+def test_backward_with_more_empty_lists_than_ids(recd, B, planned):
+    """A group stores one list per slot for each of its features, empty ones too: far more unique lists than ids.
+    The context gets exactly the workspace that it asks for."""
+    rng = np.random.default_rng(31)
+    F, D, rows = 5, 64, 400
+    lists = [[[int(rng.integers(rows))] if f == 0 or b == 3 else [] for b in range(B)] for f in range(F)]
+    for b in range(B):
+        lists[0][b] = [b % rows, b // rows]      # every row a slot of its own
+    batch = synth.batch_from_lists(lists)
+    c = recd.Context(0, workspace_hint_bytes=recd.workspace_bytes(F, B, batch.N, D))
+    _, _, ik = gpu_build_grouped(c, batch, [0, F])
+    assert ik.U == F * B and ik.M < ik.U // 2
+    grad_out = rng.standard_normal((F, B, D)).astype(np.float32)
+    touched = torch.zeros(ik.M, dtype=torch.int64, device="cuda")
+    feat_roff = torch.zeros(F + 1, dtype=torch.int64, device="cuda")
+    grad_rows = torch.zeros(ik.M, D, device="cuda")
+    if planned:
+        c.backward_plan(F, B, D, ik.inverse_f, ik.feat_uoff, ik.u_values, ik.u_offsets, [rows] * F, ik.U, ik.M,
+                        touched, feat_roff)
+        R = c.backward_apply(gu.to_dev(grad_out), grad_rows, want_count=True)
+    else:
+        R = c.backward_dedup(F, B, gu.to_dev(grad_out), ik.inverse_f, ik.feat_uoff, ik.u_values, ik.u_offsets,
+                             [rows] * F, ik.U, ik.M, touched, feat_roff, grad_rows, want_count=True)
+    tr, fr, gr = orc.backward_kjt(F, B, grad_out, batch.values, batch.offsets)
+    assert R == len(tr) and np.array_equal(touched[:R].cpu().numpy(), tr)
+    assert np.array_equal(feat_roff.cpu().numpy(), fr)
+    gu.assert_close_f32(gu.out_to_f64(grad_rows[:R]), gr, "row gradients with empty lists")
+    c.close()
+
+
+def test_backward_with_too_small_a_bound_of_the_ids_stays_in_its_workspace(recd):
+    """M_cap below M is reported, and whatever was summed before that stayed inside the buffers."""
+    rng = np.random.default_rng(32)
+    F, B, D, rows = 2, 300, 32, 5000
+    batch = synth.batch_from_lists([[[int(b), int(rng.integers(rows))] for b in range(B)] for _ in range(F)])
+    c = recd.Context(0, workspace_hint_bytes=recd.workspace_bytes(F, B, batch.N, D))
+    _, _, ik = gu.gpu_build(c, batch)
+    touched = torch.full((40,), -1, dtype=torch.int64, device="cuda")
+    feat_roff = torch.zeros(F + 1, dtype=torch.int64, device="cuda")
+    grad_rows = torch.full((40, D), 7.0, device="cuda")
+    grad_out = torch.ones(F, B, D, device="cuda")
+    with pytest.raises(recd.RecdError) as e:
+        c.backward_dedup(F, B, grad_out, ik.inverse, ik.feat_uoff, ik.u_values, ik.u_offsets, [rows] * F, ik.U, 10,
+                         touched, feat_roff, grad_rows, want_count=True)
+    assert e.value.status == recd.RECD_ECAPACITY
+    assert (touched[10:] == -1).all() and (grad_rows[10:] == 7.0).all()
+    c.close()
