@@ -131,6 +131,9 @@ __device__ __forceinline__ void report_side_a(const GroupParams &g, int64_t U)
                        (U > g.lists_cap ? RECD_GROUP_LISTS : 0);
 }
 
+// The bits of a key that a side's digits cover.
+__device__ __forceinline__ uint32_t sorted_bits(const SideParams &s) { return (uint32_t)((1ull << (s.passes * s.dbits)) - 1); }
+
 // Digit starts of feature f from the block's counts in LDS.
 __device__ __forceinline__ void write_bases(const SideParams &s, int f, const uint32_t *hist)
 {
@@ -469,7 +472,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
                 key[u] = (uint32_t)g.inverse[begin + i];
                 pay[u] = begin + i;
             } else {
-                key[u] = (uint32_t)g.u_values[begin + i];
+                key[u] = (uint32_t)g.u_values[begin + i] & sorted_bits(s);  // an id beyond the tables stays a key
                 pay[u] = g.pay_positions ? begin + i : g.pos_list[begin + i];
             }
         }
@@ -637,9 +640,9 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
 
 // ---- segments of equal keys ---------------------------------------------------------------------------
 // Side A: the segment number of a slot is feat_uoff[f] + slot, so starts are written without numbering
-// (a slot that no row names gets an empty segment).  Side B: a head is an entry whose key differs from
-// its predecessor's in the feature; heads are numbered across all tiles in feature order by look-back
-// words that carry the number of heads and the position of the last one, so the block that finds the
+// (recd_slot_starts: a slot that no row names gets an empty segment).  Side B: a head is an entry whose key
+// differs from its predecessor's in the feature; heads are numbered across all tiles in feature order by
+// look-back words that carry the number of heads and the position of the last one, so the block that finds the
 // next head also knows the length of the segment it closes: segments of more than long_seg entries are
 // cut into chunks of 256 entries (larger ones if that would give more than 64).  The cut depends on the
 // length only; the order in which segments and chunks are listed does not matter for the sums.
@@ -658,19 +661,14 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
             if (i >= n)
                 break;
             const uint32_t f = i / B;
-            const int64_t key = ks[i], prev = i == f * B ? -1 : (int64_t)ks[i - 1];
-            const int64_t u0 = g.feat_uoff[f];
-            for (int64_t x = prev + 1; x <= key; x++)  // at most one turn where every slot is named
-                g.seg_start_a[u0 + x] = i;
-            if (i == f * B + (B - 1)) {
-                const int64_t u1 = g.feat_uoff[f + 1];
-                for (int64_t x = u0 + key + 1; x < u1; x++)
-                    g.seg_start_a[x] = (int64_t)i + 1;
-                if ((int)f == g.F - 1) {
-                    g.seg_start_a[u1] = n;
-                    g.list_off_a[0] = 0;
-                    g.list_off_a[1] = u1 < g.lists_cap ? u1 : g.lists_cap;
-                }
+            const bool last = i == f * B + (B - 1);
+            const int64_t u0 = g.feat_uoff[f], u1 = g.feat_uoff[f + 1];
+            recd_slot_starts(ks[i], i == f * B ? 0u : ks[i - 1], i == f * B, last, sorted_bits(g.a), u1 - u0,
+                             [&](int64_t x, bool closed) { g.seg_start_a[u0 + x] = (int64_t)i + closed; });
+            if (last && (int)f == g.F - 1) {
+                g.seg_start_a[u1] = n;
+                g.list_off_a[0] = 0;
+                g.list_off_a[1] = u1 < g.lists_cap ? u1 : g.lists_cap;
             }
         }
         return;
@@ -853,6 +851,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const bool side_a = blockIdx.x > 0;
     const uint32_t f_a = blockIdx.x - 1;
+    const uint32_t row_mask = (1u << row_bits) - 1;  // with the feature's bits, at least one, it fits 32
     uint32_t n;
     if (side_a) {
         n = (uint32_t)g.B;
@@ -897,7 +896,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
                 key[u] = (uint32_t)g.inverse[f_a * g.B + i];
                 pay[u] = (uint32_t)(f_a * g.B + i);
             } else {
-                key[u] = s_key[i] | (uint32_t)g.u_values[i];
+                key[u] = s_key[i] | ((uint32_t)g.u_values[i] & row_mask);  // an id beyond the tables stays in its feature
                 pay[u] = g.pay_positions ? i : s_pay[i];
                 if (g.u_weights || g.pay_pos)
                     g.pos_list[i] = s_pay[i];
@@ -976,18 +975,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
         const uint32_t l0 = (uint32_t)(f_a * g.B);
         for (uint32_t i = tid; i < n; i += kSmallThreads) {
             g.a.pay[0][l0 + i] = s_pay[i];
-            const int64_t k = s_key[i], prev = i == 0 ? -1 : (int64_t)s_key[i - 1];
-            for (int64_t x = prev + 1; x <= k; x++)
-                g.seg_start_a[u0 + x] = (int64_t)l0 + i;
-            if (i == n - 1) {
-                for (int64_t x = u0 + k + 1; x < u1; x++)
-                    g.seg_start_a[x] = (int64_t)l0 + n;
-                if ((int)f_a == g.F - 1) {
-                    g.seg_start_a[u1] = g.n_lists;
-                    g.list_off_a[0] = 0;
-                    g.list_off_a[1] = u1 < g.lists_cap ? u1 : g.lists_cap;
-                    report_side_a(g, u1);
-                }
+            recd_slot_starts(s_key[i], i == 0 ? 0u : s_key[i - 1], i == 0, i == n - 1, sorted_bits(g.a), u1 - u0,
+                             [&](int64_t x, bool closed) { g.seg_start_a[u0 + x] = (int64_t)l0 + i + closed; });
+            if (i == n - 1 && (int)f_a == g.F - 1) {
+                g.seg_start_a[u1] = g.n_lists;
+                g.list_off_a[0] = 0;
+                g.list_off_a[1] = u1 < g.lists_cap ? u1 : g.lists_cap;
+                report_side_a(g, u1);
             }
         }
         return;
@@ -1030,7 +1024,6 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
         R += h;
         end_open = l > end_open ? l : end_open;
     }
-    const uint32_t row_mask = row_bits < 32 ? (1u << row_bits) - 1 : ~0u;
     auto list_chunks = [&](uint32_t seg, uint32_t start, uint32_t end) {
         const uint32_t len = end - start;
         if (len <= (uint32_t)g.long_seg)

@@ -18,3 +18,18 @@ RECD_RULE int64_t recd_lists_held(int64_t F, int64_t B, int64_t U_cap, int64_t M
     const int64_t most = U_cap > M_cap + F ? U_cap : M_cap + F;
     return most < F * B ? most : F * B;
 }
+
+// Where the rows of a feature's unique lists start, from its rows sorted by slot: the row whose slot is `key`
+// and its predecessor's `prev` (first: none) opens the slots after prev's up to its own, the last row also
+// closes those that no row names.  put(slot, closed) is called once for every slot of the feature, whatever
+// the keys hold: of an inverse entry that is no slot only the sorted bits count, and it counts as the last slot.
+template <typename Put>
+RECD_RULE void recd_slot_starts(uint32_t key, uint32_t prev, bool first, bool last, uint32_t sorted_bits, int64_t slots, Put put)
+{
+    const int64_t key_in = key & sorted_bits, prev_in = prev & sorted_bits;
+    const int64_t k = key_in < slots ? key_in : slots - 1, p = first ? -1 : (prev_in < slots ? prev_in : slots - 1);
+    for (int64_t x = p + 1; x <= k; x++)  // at most one turn where every slot is named
+        put(x, false);
+    for (int64_t x = k + 1; last && x < slots; x++)
+        put(x, true);
+}

@@ -1,0 +1,86 @@
+"""Sizes and bounds that host code and kernels share (csrc/recd_rules.h), built for the CPU and checked there."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2211_05239_amd", "csrc")
+
+HARNESS = r"""
+#include "recd_rules.h"
+extern "C" {
+int64_t lists_held(int64_t F, int64_t B, int64_t U_cap, int64_t M_cap) { return recd_lists_held(F, B, U_cap, M_cap); }
+
+// starts[slot] and how often each was written, of n >= 1 sorted keys; returns the writes outside [0, slots)
+int64_t slot_starts(const uint32_t *keys, int64_t n, uint32_t bits, int64_t slots, int64_t *starts, int32_t *writes)
+{
+    int64_t outside = 0;
+    for (int64_t i = 0; i < n; i++)
+        recd_slot_starts(keys[i], i ? keys[i - 1] : 0u, i == 0, i == n - 1, bits, slots, [&](int64_t x, bool closed) {
+            if (x < 0 || x >= slots) {
+                outside++;
+                return;
+            }
+            starts[x] = i + closed;
+            writes[x]++;
+        });
+    return outside;
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, lib = d / "rules.cpp", d / "rules.so"
+    src.write_text(HARNESS)
+    subprocess.check_call(["g++", "-std=c++20", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(src),
+                           "-o", str(lib)])
+    return C.CDLL(str(lib))
+
+
+def _ptr(a):
+    return a.ctypes.data_as(C.c_void_p)
+
+
+def test_room_for_every_unique_list(rules):
+    rules.lists_held.restype = C.c_int64
+    rules.lists_held.argtypes = [C.c_int64] * 4
+    assert rules.lists_held(5, 600, 3000, 40) == 3000      # a group's empty lists
+    assert rules.lists_held(5, 600, 3000, 10 ** 9) == 3000
+    assert rules.lists_held(5, 600, 7, 40) == 45           # no fewer than a plain IKJT of M_cap ids can have
+    assert rules.lists_held(5, 600, 10 ** 9, 40) == 3000
+
+
+@pytest.mark.parametrize("seed", range(6))
+@pytest.mark.parametrize("bad", [False, True])
+def test_slot_starts_stay_inside_the_feature(rules, seed, bad):
+    """Every slot's start is written exactly once and nowhere else, also where inverse entries are no slots
+    (negative, or beyond the feature's last): sorted as the grouping sorts, by the low bits."""
+    rng = np.random.default_rng(seed)
+    slots, n = int(rng.integers(1, 40)), int(rng.integers(1, 120))
+    bits = 0x3f
+    keys = rng.integers(0, slots, n).astype(np.int64)
+    if bad:
+        at = rng.random(n) < 0.3
+        keys[at] = rng.choice([-1, -2 ** 31, 2 ** 31 - 1, slots, slots + 1, 63], at.sum())
+    keys = keys.astype(np.int64).astype(np.uint32)
+    keys = keys[np.argsort(keys & bits, kind="stable")]
+    starts, writes = np.full(slots, -1, dtype=np.int64), np.zeros(slots, dtype=np.int32)
+    rules.slot_starts.restype = C.c_int64
+    rules.slot_starts.argtypes = [C.c_void_p, C.c_int64, C.c_uint32, C.c_int64, C.c_void_p, C.c_void_p]
+    assert rules.slot_starts(_ptr(keys), n, bits, slots, _ptr(starts), _ptr(writes)) == 0
+    assert (writes == 1).all() and (np.diff(starts) >= 0).all() and starts[0] == 0
+    if not bad:
+        assert np.array_equal(starts, np.searchsorted(keys, np.arange(slots)))
+
+
+def test_slot_starts_of_a_feature_without_slots(rules):
+    keys = np.array([0, 5, 0xffffffff], dtype=np.uint32)
+    none = np.zeros(1, dtype=np.int64)
+    rules.slot_starts.restype = C.c_int64
+    rules.slot_starts.argtypes = [C.c_void_p, C.c_int64, C.c_uint32, C.c_int64, C.c_void_p, C.c_void_p]
+    assert rules.slot_starts(_ptr(keys), 3, 0x3ff, 0, _ptr(none), _ptr(none.astype(np.int32))) == 0
