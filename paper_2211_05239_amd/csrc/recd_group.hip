@@ -35,6 +35,7 @@ constexpr int kMaxBits = 10;
 constexpr int kMaxRadix = 1 << kMaxBits;
 constexpr int kMaxPasses = 4;
 constexpr int kQueues = 8;
+constexpr int kMostChunks = 512;
 
 __device__ __forceinline__ uint32_t ld_agent(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ uint64_t ld_agent(const uint64_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -1102,10 +1103,14 @@ void digits_for(int bits, int *passes, int *dbits)
 int64_t chunk_for(int64_t n)
 {
     int64_t chunk = kTile;
-    while (n / chunk > 512)
+    while (n / chunk > kMostChunks)
         chunk *= 2;
     return chunk;
 }
+
+// No fewer than n / chunk_for(n), for n itself and everything below it: a bound that grows with n, so that the
+// workspace for a batch's ids also holds every smaller M_cap.
+int64_t chunks_bound(int64_t n) { return n / kTile < kMostChunks ? n / kTile : kMostChunks; }
 
 // Words (digit counts of all passes) of a feature or chunk whose keys have at most `bits` bits.  Fewer bits can
 // need more words: 10 bits are one digit of 1024, 14 bits two of 128.
@@ -1143,9 +1148,9 @@ RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap)
     };
     const int64_t tpf = (B + kTile - 1) / kTile, ch_a = chunk_for(n_lists);
     side(w.a, n_lists, (int64_t)F * tpf, (int64_t)F * ((B + ch_a - 1) / ch_a), words_for(bits_for((uint64_t)(B > 1 ? B - 1 : 1))));
-    const int64_t tiles_b = M_cap / kTile + F + 1, ch_b = chunk_for(M_cap);
+    const int64_t tiles_b = M_cap / kTile + F + 1;
     // the number of rows of the tables is not known here: ids have at most 31 bits
-    side(w.b, M_cap, tiles_b, M_cap / ch_b + F + 1, words_for(31));
+    side(w.b, M_cap, tiles_b, chunks_bound(M_cap) + F + 1, words_for(31));
     w.pb = c.take<uint32_t>(F + 1);
     w.queue_start = c.take<uint32_t>(kQueues + 1);
     w.desc_queue = c.take<uint2>(tiles_b);

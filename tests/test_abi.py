@@ -80,3 +80,13 @@ def test_workspace_holds_a_row_of_every_unique_list(F, B, N):
     """The backward sums one fp32 row per unique list, and a grouped IKJT may hold F * B lists with hardly an id
     among them."""
     assert _workspace(F, B, N, 128) - _workspace(F, B, N, 64) >= F * B * 64 * 4
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="librecd.so not built")
+@pytest.mark.parametrize("F,B,D", [(1, 20, 4), (4, 4096, 16), (64, 16384, 128)])
+def test_workspace_grows_with_the_ids(F, B, D):
+    """What recd_workspace_bytes gives for the ids of a batch also holds the backward of fewer unique ids (M_cap):
+    it must not shrink anywhere, or such a call would have to grow the workspace."""
+    sizes = [1, 8192, 8193] + [k * 4096 * s + d for s in (1, 2, 4, 64) for k in (1, 512, 513, 514) for d in (-1, 0, 1)]
+    got = [_workspace(F, B, n, D) for n in sorted(sizes)]
+    assert got == sorted(got)
