@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
                 key[u] = (uint32_t)g.inverse[begin + i];
                 pay[u] = begin + i;
             } else {
-                key[u] = (uint32_t)g.u_values[begin + i] & sorted_bits(s);  // an id beyond the tables stays a key
+                key[u] = (uint32_t)g.u_values[begin + i];
                 pay[u] = g.pay_positions ? begin + i : g.pos_list[begin + i];
             }
         }
@@ -785,7 +785,7 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
                 open[u] = open0;
             mine += open[u] ? chunks_of(at + 1 - open[u]) : 0;
             g.seg_start_b[seg] = at;
-            g.touched_rows[seg] = key[u];
+            g.touched_rows[seg] = key[u] & sorted_bits(g.b);  // of an id beyond the tables only these count
             g.seg_feat[seg] = (int32_t)f;
             if (k == 0 && i == 0) {
                 const int first = tile == 0 ? 0 : (int)g.desc_feat[tile - 1].x + 1;
