@@ -17,9 +17,9 @@
 //     length and content only, never on where the list sits in a batch: the deduplicated and the
 //     non-deduplicated lookup (same W) agree bit for bit.
 //   * blocks are dealt to lists statically (no atomics; the hardware's block dispatch balances the
-//     load).  The lookups' mapping is XCD-aware: block b serves the (b mod 8)-th contiguous eighth of
-//     the lists, and since consecutive blocks go to consecutive XCDs, the hot rows of a table stay
-//     in one XCD's L2.  The number of lists may live on the device only (unique lists): the grid is
+//     load).  The lookups' mapping is XCD-aware: consecutive blocks go to consecutive XCDs, and block b
+//     serves every eighth 64 neighbouring lists from the (b mod 8)-th on, so that lists that share
+//     rows meet in one XCD's L2 and features of unequal mean length load the XCDs alike.  The number of lists may live on the device only (unique lists): the grid is
 //     sized from a host-side bound and every block strides until its queue is exhausted, so any grid
 //     size is correct.
 #include "recd_internal.h"
@@ -478,19 +478,25 @@ void k_segsum(const SegSumParams p)
         // ballots, and one load brings the bounds of the block's lists; they wait in 320 bytes of LDS
         // while rows are gathered (in registers they cost the seventh wave).  (Prefix sums over the
         // features and 4.6 KB of LDS a wave before; 28 waves of that on a CU also kept blocks of other
-        // streams out.)  Queue q = blockIdx mod 8 (one XCD) takes a contiguous eighth of the lists,
-        // which are feature by feature, so a table's hot rows stay in one L2 whatever the number of
-        // features.
+        // streams out.)  Queue q = blockIdx mod 8 (one XCD) takes every eighth 64 neighbouring lists:
+        // balanced whatever the features' mean lengths.  (A contiguous eighth each, as few XCDs for a feature as
+        // there can be, is at best a tenth faster and up to 2.6 times slower: fp32 rows of 512 bytes, unique / KJT
+        // lookup, us, contiguous -> dealt: 32 even features 67 / 307 -> 68 / 306, 5 even ones 22 / 53 -> 24 / 51;
+        // four of 32 of mean 64 and the rest of 2: 114 / 792 -> 51 / 246; the first of 6 of mean 100, the rest of
+        // 2: 71 / 190 -> 31 / 72; one of 65 of mean 150, the rest of 4: 131 / 414 -> 87 / 241.  32 to 256 lists
+        // at a time are alike; from 512 on a feature's heavy lists stay on too few XCDs again.)
         const int64_t first = p.list_off ? uniform64(p.list_off[0]) : p.list_base;
         const int64_t end_all = p.list_off ? uniform64(p.list_off[p.F]) : p.list_base + p.F * p.lists_per_feature;
         const int64_t all = end_all - first;
         // lists per block: as many as keep the number of blocks in bounds (measured at 61 K unique lists
         // and at 1.05 M KJT lists: 1 and 4), by the true number of lists
         const int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
-        const int64_t per = nq == 1 ? all : ((all + kNQ - 1) / kNQ + lpb - 1) / lpb * lpb;
-        const int64_t q0 = first + q * per, q1 = q0 + per < end_all ? q0 + per : end_all;
-        for (int64_t l0 = q0 + item0 * lpb; l0 < q1; l0 += item_stride * lpb) {
-            const int cnt = (int)(q1 - l0 < lpb ? q1 - l0 : lpb);
+        // (64 is a multiple of every number of lists per block)
+        for (int64_t t = item0 * lpb;; t += item_stride * lpb) {
+            const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ));
+            if (l0 >= end_all)
+                break;  // so are all later items of this block
+            const int cnt = (int)(end_all - l0 < lpb ? end_all - l0 : lpb);
             {
                 int ln = lane;
                 asm volatile("" : "+v"(ln));  // its addresses are made here, not kept over the gathers

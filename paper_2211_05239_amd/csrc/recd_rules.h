@@ -33,3 +33,12 @@ RECD_RULE void recd_slot_starts(uint32_t key, uint32_t prev, bool first, bool la
     for (int64_t x = k + 1; last && x < slots; x++)
         put(x, true);
 }
+
+// The lookups deal their lists to the XCDs' block queues in turn, 64 neighbours at a time: the t-th list of
+// queue q of `queues`.  Neighbours (a session's lists, a feature's) stay together, and features of unequal
+// mean length load the queues alike.
+constexpr int kDealtLists = 64;
+RECD_RULE int64_t recd_dealt(int64_t t, int q, int queues)
+{
+    return ((t / kDealtLists) * queues + q) * kDealtLists + t % kDealtLists;
+}

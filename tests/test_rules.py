@@ -28,6 +28,22 @@ int64_t slot_starts(const uint32_t *keys, int64_t n, uint32_t bits, int64_t slot
         });
     return outside;
 }
+
+// work[q] of the lists that the blocks of queue q take, lists per block item lpb, `stride` blocks a queue
+void deal(int64_t n, int queues, int lpb, int64_t stride, const int64_t *len, int64_t *work, int32_t *taken)
+{
+    for (int q = 0; q < queues; q++)
+        for (int64_t b = 0; b < stride; b++)
+            for (int64_t t = b * lpb;; t += stride * lpb) {
+                const int64_t l0 = recd_dealt(t, q, queues);
+                if (l0 >= n)
+                    break;
+                for (int64_t l = l0; l < n && l < l0 + lpb; l++) {
+                    taken[l]++;
+                    work[q] += len[l];
+                }
+            }
+}
 }
 """
 
@@ -84,3 +100,28 @@ def test_slot_starts_of_a_feature_without_slots(rules):
     rules.slot_starts.restype = C.c_int64
     rules.slot_starts.argtypes = [C.c_void_p, C.c_int64, C.c_uint32, C.c_int64, C.c_void_p, C.c_void_p]
     assert rules.slot_starts(_ptr(keys), 3, 0x3ff, 0, _ptr(none), _ptr(none.astype(np.int32))) == 0
+
+
+@pytest.mark.parametrize("means", [[16] * 32, [64] * 4 + [2] * 28, [100] + [2] * 5, [2] * 40 + [128] + [2] * 23,
+                                   [4] * 50 + [150] + [4] * 14])
+def test_lookup_lists_are_dealt_evenly(rules, means):
+    """Every list goes to one block of one queue, and features of unequal mean length load the queues (the XCDs)
+    alike: none has more than a quarter above its share of the ids."""
+    rules.deal.restype = None
+    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
+    lens = np.concatenate([np.full(1800, m, dtype=np.int64) for m in means])
+    for lpb, stride in ((1, 3000), (2, 7), (4, 500), (16, 100)):
+        work, taken = np.zeros(8, dtype=np.int64), np.zeros(len(lens), dtype=np.int32)
+        rules.deal(len(lens), 8, lpb, stride, _ptr(lens), _ptr(work), _ptr(taken))
+        assert (taken == 1).all()
+        assert work.max() <= 1.25 * work.mean(), work
+
+
+@pytest.mark.parametrize("n", [0, 1, 63, 64, 65, 511, 512, 513, 5000])
+def test_lookup_lists_of_any_number_are_all_dealt(rules, n):
+    rules.deal.restype = None
+    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
+    lens = np.ones(max(n, 1), dtype=np.int64)
+    work, taken = np.zeros(8, dtype=np.int64), np.zeros(max(n, 1), dtype=np.int32)
+    rules.deal(n, 8, 4, 3, _ptr(lens), _ptr(work), _ptr(taken))
+    assert (taken[:n] == 1).all() and work.sum() == n
