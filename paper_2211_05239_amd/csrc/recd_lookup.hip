@@ -250,8 +250,8 @@ __device__ __forceinline__ void add_chunks(float (*acc)[Elem<TT>::per_vec * VPL]
 
 // Occupancy target: 7 waves per SIMD (72 VGPRs) measured best for one-vector-per-lane fp32 rows; more
 // loads in flight per wave at lower occupancy, or fewer at 8 waves, were both slower.  The KJT lookup,
-// whose waves share rows through L1, is held to it (16.8 M ids: 8 waves of 61 registers 551 us, 7
-// waves 538); the unique lookup takes the eighth where it fits.  The
+// whose waves share rows through L1, is held to seven where that is its target (16.8 M ids of 512-byte rows:
+// 8 waves of 61 registers 551 us, 7 waves 538); the unique lookup takes the eighth where it fits.  The
 // instantiations that need more registers than that (16-bit tables decode into twice the
 // accumulators, rows of at most 128 bytes put 8 rows into every load, the weighted sum carries
 // the weights: 6 waves for the KJT lookup, 5 for the unique lists) get a lower target instead of
@@ -272,11 +272,19 @@ template <int LPR, int VPL, int TT, int OT, int SITE, int MODE> constexpr int se
         w -= 1;
     return w < 3 ? 3 : w;
 }
+// The lower targets are no limits: held to them, KJT lookups took up to three times as long (0.5 M ids of
+// 2 KiB rows 57 -> 174 us, 0.13 M of 4 KiB rows 36 -> 63, 4.2 M of 128 bytes 99 -> 120).
+template <int LPR, int VPL, int TT, int OT, int SITE, int MODE> constexpr int segsum_most_waves()
+{
+    return SITE == SITE_KJT && segsum_waves<LPR, VPL, TT, OT, SITE, MODE>() == 7 ? 7 : 8;
+}
+static_assert(segsum_most_waves<64, 2, RECD_F32, RECD_F32, SITE_KJT, POOL_SUM>() == 8, "rows above 1 KiB: no limit");
+static_assert(segsum_most_waves<8, 1, RECD_F32, RECD_F32, SITE_KJT, POOL_WSUM>() == 8, "short rows, weights: no limit");
 
 template <int LPR, int VPL, int TT, int OT, typename IdxT, int SITE, int MODE = POOL_SUM>
 __global__ __launch_bounds__(SegBlock<SITE>::threads)
 __attribute__((amdgpu_waves_per_eu(segsum_waves<LPR, VPL, TT, OT, SITE, MODE>(),
-                                   SITE == SITE_KJT ? segsum_waves<LPR, VPL, TT, OT, SITE, MODE>() : 8)))
+                                   segsum_most_waves<LPR, VPL, TT, OT, SITE, MODE>())))
 void k_segsum(const SegSumParams p)
 {
     constexpr int kSegBlock = SegBlock<SITE>::threads;
