@@ -866,20 +866,37 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
             s_chunks = 0;
         }
         __syncthreads();
-        // every list fills in its number and its feature at its positions (an empty list has none)
+        // every list fills in its number and its feature at its positions (an empty list has none): a lane up to
+        // 64 of them, the whole wave what lies beyond, list by list (a list of 7000 ids by one lane: backward 230 us,
+        // now 44; with 16 instead of 64 the lists of 20 ids in a batch of 5 K took 1 us more)
         const uint32_t U = s_fu[g.F];
-        for (uint32_t u = tid; u < U; u += kSmallThreads) {
-            const int64_t a = g.u_offsets[u], e = g.u_offsets[u + 1];
-            int f = 0;  // the last feature with s_fu[f] <= u
+        for (uint32_t u0 = 0; u0 < U; u0 += kSmallThreads) {
+            const uint32_t u = u0 + tid;
+            uint32_t at = 0, end = 0, name = 0, fkey = 0;
+            if (u < U) {
+                const int64_t a = g.u_offsets[u], e = g.u_offsets[u + 1];
+                int f = 0;  // the last feature with s_fu[f] <= u
 #pragma unroll
-            for (int st = RECD_MAX_FEATURES / 2; st >= 1; st >>= 1)
-                if (f + st < g.F && s_fu[f + st] <= u)
-                    f += st;
-            const uint32_t end = e < (int64_t)n ? (uint32_t)e : n;
-            const uint32_t name = (int64_t)u < g.lists_cap ? u : (uint32_t)(g.lists_cap - 1);
-            for (uint32_t j = a < (int64_t)n ? (uint32_t)a : n; j < end; j++) {
+                for (int st = RECD_MAX_FEATURES / 2; st >= 1; st >>= 1)
+                    if (f + st < g.F && s_fu[f + st] <= u)
+                        f += st;
+                at = a < (int64_t)n ? (uint32_t)a : n;
+                end = e < (int64_t)n ? (uint32_t)e : n;
+                name = (int64_t)u < g.lists_cap ? u : (uint32_t)(g.lists_cap - 1);
+                fkey = (uint32_t)f << row_bits;
+            }
+            const uint32_t own = end > at + 64 ? at + 64 : end;
+            for (uint32_t j = at; j < own; j++) {
                 s_pay[j] = name;
-                s_key[j] = (uint32_t)f << row_bits;
+                s_key[j] = fkey;
+            }
+            for (uint64_t longer = __ballot(own < end); longer; longer &= longer - 1) {
+                const int l = __builtin_ctzll(longer);
+                const uint32_t to = __shfl(end, l), list = __shfl(name, l), key_f = __shfl(fkey, l);
+                for (uint32_t j = __shfl(own, l) + lane; j < to; j += 64) {
+                    s_pay[j] = list;
+                    s_key[j] = key_f;
+                }
             }
         }
         __syncthreads();

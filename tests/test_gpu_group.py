@@ -1,6 +1,8 @@
 """The grouping of the backward pass (recd_group.hip) at the sizes where it can go wrong: features of no
 id, one id, a tile less one, a whole tile, one more and several tiles; row ids of one, two and three
-digits; slots of one and two digits; queues with more features than others."""
+digits; slots of one and two digits; queues with more features than others; segments of one chunk, of several
+and of chunks larger than 256 entries; a long list in a small batch.  Gradients and weights are small multiples of
+a power of two, so that every sum is exact in fp32 and is compared for equality."""
 import numpy as np
 import pytest
 import torch
@@ -16,9 +18,9 @@ def recd():
     return m
 
 
-def _case(seed, ids_per_feature, B, slots, rows, hot):
+def _case(seed, ids_per_feature, B, slots, rows, hot, named=False):
     """A batch's IKJT made directly: `slots` lists per feature that hold ids_per_feature[f] ids, every row of
-    the batch naming one of them (some lists are named by no row)."""
+    the batch naming one of them (some lists are named by no row, unless `named`)."""
     rng = np.random.default_rng(seed)
     F = len(ids_per_feature)
     lens, ids, inverse = [], [], []
@@ -30,7 +32,10 @@ def _case(seed, ids_per_feature, B, slots, rows, hot):
             few = rng.integers(0, min(rows, 3), size=n)
             x = np.where(rng.random(n) < 1 / 3, few, x)
         ids.append(x)
-        inverse.append(rng.integers(0, slots, size=B))
+        slot = rng.integers(0, slots, size=B)
+        if named:
+            slot[rng.permutation(B)[:slots]] = np.arange(slots)
+        inverse.append(slot)
     lens = np.concatenate(lens)
     return (np.concatenate(ids).astype(np.int64), np.concatenate([[0], np.cumsum(lens)]).astype(np.int64),
             np.concatenate(inverse).astype(np.int32), np.arange(F + 1, dtype=np.int64) * slots)
@@ -54,47 +59,126 @@ CASES = [
     ([1400], 2000, 7, (1 << 31) - 1, False),           # 31 + 1 bits
     ([50] * 130, 40, 33, 5000, False),       # more features than one launch of the optimizer takes
     ([9] * 1024, 3, 3, 100, False),          # the most features
+    ([8000, 150], 300, 2, 5000, True),       # one launch, a list of thousands of ids
+    ([40000, 0, 20000], 5000, 1000, 1, False),   # one row: segments of 157 chunks cut down to 64, and of 79
 ]
+
+
+class Batch:
+    """A case on the device, and its gradients in 64 bits."""
+
+    def __init__(self, k, **kw):
+        ids_per_feature, self.B, self.slots, self.rows, hot = CASES[k]
+        self.F, self.D, self.n = len(ids_per_feature), 8, sum(ids_per_feature)
+        self.uv, self.uo, self.inv, self.fu = _case(100 + k, ids_per_feature, self.B, self.slots, self.rows, hot, **kw)
+        self.U, self.M_cap = self.F * self.slots, self.n + 3       # a bound, not the exact number
+        self.rng = np.random.default_rng(7 + k)
+        self.d_uv = self.dev(np.concatenate([self.uv, [0, 0, 0]]))
+        self.d_uo, self.d_inv, self.d_fu = self.dev(self.uo), self.dev(self.inv), self.dev(self.fu)
+        self.touched = torch.full((self.M_cap,), -1, dtype=torch.int64, device="cuda")
+        self.froff = torch.full((self.F + 1,), -1, dtype=torch.int64, device="cuda")
+        self.grad_rows = torch.full((self.M_cap, self.D), 99.0, device="cuda")
+        self.list_of = np.repeat(np.arange(self.U), np.diff(self.uo))             # of every position
+        self.list_of_row = self.fu[np.arange(self.F * self.B) // self.B] + self.inv
+        self.ikjt = (self.d_inv, self.d_fu, self.d_uv, self.d_uo)
+        self.bounds = ([self.rows] * self.F, self.U, self.M_cap)
+
+    @staticmethod
+    def dev(a):
+        return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+    def integers(self, *shape):
+        return self.rng.integers(-8, 9, size=shape).astype(np.float32)
+
+    def list_sums(self, g):
+        gu, most = np.zeros((self.U, self.D)), np.zeros((self.U, self.D))
+        np.add.at(gu, self.list_of_row, g.astype(np.float64))
+        np.add.at(most, self.list_of_row, np.abs(g).astype(np.float64))
+        return gu, most
+
+    def check(self, R, entry, most):
+        """entry: what every position adds to its row; most: a bound of its magnitude."""
+        key = (self.list_of // self.slots) * (1 << 32) + self.uv
+        want, back = np.unique(key, return_inverse=True)
+        ref, size = np.zeros((len(want), self.D)), np.zeros((len(want), self.D))
+        np.add.at(ref, back, entry)
+        np.add.at(size, back, most)
+        assert len(want) == 0 or size.max() < 2 ** 22   # in quarters: below 2^24 units, every partial sum is exact
+        assert R == len(want)
+        assert np.array_equal(self.touched[:R].cpu().numpy(), want & 0xffffffff)
+        assert np.array_equal(self.froff.cpu().numpy(), np.searchsorted(want >> 32, np.arange(self.F + 1)))
+        assert np.array_equal(self.grad_rows[:R].double().cpu().numpy(), ref)
+        assert (self.grad_rows[R:] == 99.0).all()
 
 
 @pytest.mark.parametrize("k", range(len(CASES)))
 @pytest.mark.parametrize("planned", [False, True])
 def test_grouping_against_sums_in_64_bits(recd, k, planned):
-    ids_per_feature, B, slots, rows, hot = CASES[k]
-    F, D, n = len(ids_per_feature), 8, sum(ids_per_feature)
-    uv, uo, inv, fu = _case(100 + k, ids_per_feature, B, slots, rows, hot)
     print(f"grouping case {k} planned={planned}", flush=True)
-    g = np.random.default_rng(7 + k).standard_normal((F * B, D), dtype=np.float32) * np.float32(0.01)
+    c = Batch(k)
     ctx = recd.Context(0)
-    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
-    U = F * slots
-    M_cap = n + 3                            # a bound, not the exact number
-    touched = torch.full((M_cap,), -1, dtype=torch.int64, device="cuda")
-    froff = torch.full((F + 1,), -1, dtype=torch.int64, device="cuda")
-    grad_rows = torch.full((M_cap, D), 99.0, device="cuda")
-    gout, d_uv, d_uo, d_inv, d_fu = dev(g), dev(np.concatenate([uv, [0, 0, 0]])), dev(uo), dev(inv), dev(fu)
-    args = (F, B, D, d_inv, d_fu, d_uv, d_uo, [rows] * F, U, M_cap, touched, froff)
+    g = c.integers(c.F * c.B, c.D)
+    gout = c.dev(g).view(c.F, c.B, c.D)
     if planned:
-        ctx.backward_plan(*args)
-        R = ctx.backward_apply(gout.view(F, B, D), grad_rows, want_count=True)
+        ctx.backward_plan(c.F, c.B, c.D, *c.ikjt, *c.bounds, c.touched, c.froff)
+        R = ctx.backward_apply(gout, c.grad_rows, want_count=True)
     else:
-        R = ctx.backward_dedup(F, B, gout.view(F, B, D), d_inv, d_fu, d_uv, d_uo, [rows] * F, U, M_cap, touched,
-                               froff, grad_rows, want_count=True)
-    gu = np.zeros((U, D))
-    np.add.at(gu, fu[np.arange(F * B) // B] + inv, g.astype(np.float64))
-    lst = np.repeat(np.arange(U), np.diff(uo))
-    key = (lst // slots) * (1 << 32) + uv
-    want, back = np.unique(key, return_inverse=True)
-    ref, size = np.zeros((len(want), D)), np.zeros((len(want), D))
-    np.add.at(ref, back, gu[lst])
-    gabs = np.zeros((U, D))
-    np.add.at(gabs, fu[np.arange(F * B) // B] + inv, np.abs(g).astype(np.float64))
-    np.add.at(size, back, gabs[lst])
-    assert R == len(want)
-    assert np.array_equal(touched[:R].cpu().numpy(), want & 0xffffffff)
-    assert np.array_equal(froff.cpu().numpy(), np.searchsorted(want >> 32, np.arange(F + 1)))
-    # fp32 sums through trees in which no term passes more than 2^12 additions (a list's rows in steps of 64
-    # and a row's entries in chunks): 2^12 * 2^-24 of the sum of magnitudes, and the project's own bar
-    bound = np.maximum(1e-5 * (1 + np.abs(ref)), 2.0 ** -12 * size)
-    assert np.all(np.abs(grad_rows[:R].double().cpu().numpy() - ref) <= bound)
+        R = ctx.backward_dedup(c.F, c.B, gout, *c.ikjt, *c.bounds, c.touched, c.froff, c.grad_rows, want_count=True)
+    gu, most = c.list_sums(g)
+    c.check(R, gu[c.list_of], most[c.list_of])
+    ctx.close()
+
+
+@pytest.mark.parametrize("k", range(len(CASES)))
+def test_grouping_with_weights(recd, k):
+    print(f"weighted grouping case {k}", flush=True)
+    c = Batch(k)
+    ctx = recd.Context(0)
+    g, w = c.integers(c.F * c.B, c.D), c.rng.integers(1, 5, size=c.n).astype(np.float32) / 4
+    R = ctx.backward_dedup_weighted(c.F, c.B, c.dev(g).view(c.F, c.B, c.D), c.d_inv, c.d_fu, c.d_uv,
+                                    c.dev(np.concatenate([w, [0, 0, 0]]).astype(np.float32)), c.d_uo, *c.bounds,
+                                    c.touched, c.froff, c.grad_rows, want_count=True)
+    gu, most = c.list_sums(g)
+    c.check(R, gu[c.list_of] * w[:, None], most[c.list_of])
+    ctx.close()
+
+
+@pytest.mark.parametrize("k", [k for k in range(len(CASES)) if CASES[k][3] <= (1 << 20) + 1])
+def test_grouping_with_max_pooling(recd, k):
+    print(f"max-pooled grouping case {k}", flush=True)
+    c = Batch(k)
+    ctx = recd.Context(0)
+    g = c.integers(c.F * c.B, c.D)
+    tables = [c.rng.integers(0, 50, size=(c.rows, c.D)).astype(np.float32) for _ in range(c.F)]   # with ties
+    d_tables = [c.dev(t) for t in tables]
+    R = ctx.backward_dedup_max(c.F, c.B, c.dev(g).view(c.F, c.B, c.D), *c.ikjt, *c.bounds, d_tables, c.touched, c.froff,
+                               c.grad_rows, want_count=True)
+    gu, most = c.list_sums(g)
+    won = np.zeros((c.n, c.D))
+    for u in np.unique(c.list_of):
+        a, e = c.uo[u], c.uo[u + 1]
+        won[a + tables[u // c.slots][c.uv[a:e]].argmax(axis=0), np.arange(c.D)] = 1   # the first among equals
+    c.check(R, gu[c.list_of] * won, most[c.list_of])
+    ctx.close()
+
+
+@pytest.mark.parametrize("k", range(len(CASES)))
+def test_grouping_of_sequences(recd, k):
+    print(f"sequence grouping case {k}", flush=True)
+    c = Batch(k, named=True)   # the sequence path knows lists that a row names only
+    ctx = recd.Context(0)
+    lens = np.diff(c.uo)[c.list_of_row]
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    N = int(offsets[-1])
+    g = c.integers(N, c.D)
+    emb = torch.full((c.M_cap, c.D), 99.0, device="cuda")
+    d_g = c.dev(g) if N else torch.zeros(1, c.D, device="cuda")[:0]
+    R = ctx.backward_sequence_dedup(c.F, c.B, d_g, c.dev(offsets), *c.ikjt, *c.bounds, emb, c.touched, c.froff,
+                                    c.grad_rows, want_count=True)
+    at = np.repeat(c.uo[c.list_of_row] - offsets[:-1], lens) + np.arange(N)       # position of every KJT id
+    ge, most = np.zeros((c.n, c.D)), np.zeros((c.n, c.D))
+    np.add.at(ge, at, g.astype(np.float64))
+    np.add.at(most, at, np.abs(g).astype(np.float64))
+    assert np.array_equal(emb[:c.n].double().cpu().numpy(), ge)
+    c.check(R, ge, most)
     ctx.close()
