@@ -278,7 +278,7 @@ recd_status recd_create(recd_ctx **out, int device, void *hip_stream, size_t wor
     ok = ok && hipMalloc(&sa, sa_bytes) == hipSuccess;
     ok = ok && hipMemset(sa, 0, sa_bytes) == hipSuccess;
     void *ga = nullptr;
-    const size_t ga_bytes = 2 * RECD_MAX_FEATURES * sizeof(uint32_t);
+    const size_t ga_bytes = 2 * RECD_GROUP_ARRIVE * sizeof(uint32_t);
     ok = ok && hipMalloc(&ga, ga_bytes) == hipSuccess;
     ctx->group_arrive = static_cast<uint32_t *>(ga);
     ok = ok && hipMemset(ga, 0, ga_bytes) == hipSuccess;

@@ -30,6 +30,8 @@ struct KernelTimer {
     int n = 0;
 };
 
+constexpr int RECD_GROUP_ARRIVE = 4096;  // counters of a side of the grouping
+
 struct recd_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -91,8 +93,7 @@ struct recd_ctx {
     // blocks exchange their counts through, all zero between launches.  small_path: 0 = never, 1 =
     // whenever the batch qualifies, 2 = as 1 with every wait between the blocks made to expire.
     uint64_t *small_agg = nullptr;
-    // chunks of a feature that the grouping's counting kernel has seen, [2][RECD_MAX_FEATURES], all
-    // zero between launches
+    // chunks that the grouping's counting kernel has seen, [2][RECD_GROUP_ARRIVE], all zero between launches
     uint32_t *group_arrive = nullptr;
     int small_path = 1;
     int timing = 0;  // RECD_OPT_INTERNAL_TIMING

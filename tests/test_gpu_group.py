@@ -60,6 +60,7 @@ CASES = [
     ([50] * 130, 40, 33, 5000, False),       # more features than one launch of the optimizer takes
     ([9] * 1024, 3, 3, 100, False),          # the most features
     ([8000, 150], 300, 2, 5000, True),       # one launch, a list of thousands of ids
+    ([23 * TILE + 5], 18 * TILE + 7, 3000, 5000, True),   # counted in chunks of which more than sixteen are added up
     ([40000, 0, 20000], 5000, 1000, 1, False),   # one row: segments of 157 chunks cut down to 64, and of 79
 ]
 
