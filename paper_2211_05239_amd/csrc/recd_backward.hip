@@ -1010,13 +1010,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         if (!seq) {
             RECD_TRY(sum_lists(ctx, w, ps_a, U_cap, grad_out, D, mean ? u_offsets : nullptr));
         } else {
-            // lists per block: 24 to 48 positions (whole call at 0.96 M rows of 256 bytes, 30 K lists' rows, by
-            // the bound 24 / 48 / 96 / 192 / 384 / 768: 156 / 155 / 160 / 167 / 172 / 197 us; of 512 bytes 226 /
-            // 225 / 232 / 242 / 253 / 296; skewed lengths 156 / 156 / 163 / 168 / 183 / 226)
-            const double avg = (double)M_cap / (double)(U_cap > 0 ? U_cap : 1);
-            int lists = 1;
-            while (lists < 64 && 2.0 * lists * avg <= 48.0)
-                lists *= 2;
+            const int lists = recd_jagged_lists(N, U_cap, M_cap);
             int64_t blocks = (U_cap + lists - 1) / lists;
             if (blocks > (int64_t)ctx->num_cu * 64)
                 blocks = (int64_t)ctx->num_cu * 64;

@@ -42,3 +42,17 @@ RECD_RULE int64_t recd_dealt(int64_t t, int q, int queues)
 {
     return ((t / kDealtLists) * queues + q) * kDealtLists + t % kDealtLists;
 }
+
+// Unique lists per block of the sequence backward's sum over their rows: 24 to 48 positions where a list is
+// known to have many rows, else twice as many (the bounds are all that the host knows).  Whole call, us, by the
+// bound 48 / 96 / 192 / 384: eight rows a list, 0.26 M positions: of 256 bytes 186 / 192 / 208 / 242, of 64 bytes
+// 101 / 100 / 104 / 114; one row a list, 2.1 M positions: of 256 bytes 720 / 681 / 684, of 64 bytes 346 / 306 / 286
+// / 282, of 16 bytes 304 / 242 / 214 / 207 (0.26 M positions of 128 bytes in lists of 2: 177 / 209 / 282).
+RECD_RULE int recd_jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap)
+{
+    const double positions = (double)M_cap / (double)(U_cap > 0 ? U_cap : 1), most = N > 4 * M_cap ? 48.0 : 96.0;
+    int lists = 1;
+    while (lists < 64 && 2.0 * lists * positions <= most)
+        lists *= 2;
+    return lists;
+}

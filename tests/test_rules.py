@@ -11,6 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 HARNESS = r"""
 #include "recd_rules.h"
 extern "C" {
+int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap) { return recd_jagged_lists(N, U_cap, M_cap); }
 int64_t lists_held(int64_t F, int64_t B, int64_t U_cap, int64_t M_cap) { return recd_lists_held(F, B, U_cap, M_cap); }
 
 // starts[slot] and how often each was written, of n >= 1 sorted keys; returns the writes outside [0, slots)
@@ -125,3 +126,15 @@ def test_lookup_lists_of_any_number_are_all_dealt(rules, n):
     work, taken = np.zeros(8, dtype=np.int64), np.zeros(max(n, 1), dtype=np.int32)
     rules.deal(n, 8, 4, 3, _ptr(lens), _ptr(work), _ptr(taken))
     assert (taken[:n] == 1).all() and work.sum() == n
+
+
+def test_lists_per_block_of_the_sequence_backward(rules):
+    """A power of two up to 64; lists that are not known to have many rows come twice as many positions a block,
+    whose threads short rows would leave idle."""
+    rules.jagged_lists.argtypes = [C.c_int64] * 3
+    for U, M in ((1, 0), (0, 0), (10 ** 6, 16 * 10 ** 6), (10 ** 6, 10 ** 5), (7, 10 ** 9), (300, 300 * 30)):
+        few, many = rules.jagged_lists(M, U, M), rules.jagged_lists(9 * M + 9, U, M)
+        assert few in (1, 2, 4, 8, 16, 32, 64) and many in (few, few // 2)
+        assert few == 1 or few * M <= 96 * U
+        assert few == 64 or 2 * few * M > 96 * max(U, 1)
+        assert many == 64 or 2 * many * M > 48 * max(U, 1)
