@@ -1010,7 +1010,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         if (!seq) {
             RECD_TRY(sum_lists(ctx, w, ps_a, U_cap, grad_out, D, mean ? u_offsets : nullptr));
         } else {
-            const int lists = recd_jagged_lists(N, U_cap, M_cap);
+            const int lists = recd_jagged_lists(N, U_cap, M_cap, D / 4, ctx->num_cu);
             int64_t blocks = (U_cap + lists - 1) / lists;
             if (blocks > (int64_t)ctx->num_cu * 64)
                 blocks = (int64_t)ctx->num_cu * 64;

@@ -486,7 +486,8 @@ void k_segsum(const SegSumParams p)
         // ballots, and one load brings the bounds of the block's lists; they wait in 320 bytes of LDS
         // while rows are gathered (in registers they cost the seventh wave).  (Prefix sums over the
         // features and 4.6 KB of LDS a wave before; 28 waves of that on a CU also kept blocks of other
-        // streams out.)  Queue q = blockIdx mod 8 (one XCD) takes every eighth 64 neighbouring lists:
+        // streams out.)  Queue q = blockIdx mod 8 (one XCD) takes every eighth 64 neighbouring lists (of fewer
+        // than 8 K lists fewer, recd_deal_log: dealt 64 at a time, a few hundred would leave XCDs idle):
         // balanced whatever the features' mean lengths.  (A contiguous eighth each, as few XCDs for a feature as
         // there can be, is at best a tenth faster and up to 2.6 times slower: fp32 rows of 512 bytes, unique / KJT
         // lookup, us, contiguous -> dealt: 32 even features 67 / 307 -> 68 / 306, 5 even ones 22 / 53 -> 24 / 51;
@@ -499,9 +500,9 @@ void k_segsum(const SegSumParams p)
         // lists per block: as many as keep the number of blocks in bounds (measured at 61 K unique lists
         // and at 1.05 M KJT lists: 1 and 4), by the true number of lists
         const int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
-        // (64 is a multiple of every number of lists per block)
+        const int deal_log = recd_deal_log(all, kNQ, 31 - __builtin_clz(lpb));
         for (int64_t t = item0 * lpb;; t += item_stride * lpb) {
-            const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ));
+            const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ, deal_log));
             if (l0 >= end_all)
                 break;  // so are all later items of this block
             const int cnt = (int)(end_all - l0 < lpb ? end_all - l0 : lpb);

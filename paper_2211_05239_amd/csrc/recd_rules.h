@@ -34,25 +34,37 @@ RECD_RULE void recd_slot_starts(uint32_t key, uint32_t prev, bool first, bool la
         put(x, true);
 }
 
-// The lookups deal their lists to the XCDs' block queues in turn, 64 neighbours at a time: the t-th list of
-// queue q of `queues`.  Neighbours (a session's lists, a feature's) stay together, and features of unequal
-// mean length load the queues alike.
-constexpr int kDealtLists = 64;
-RECD_RULE int64_t recd_dealt(int64_t t, int q, int queues)
+// The lookups deal their n lists to the XCDs' block queues in turn, up to 64 neighbours (2^6) at a time and at least
+// 16 times round, but no fewer than the 2^lb_log lists of a block.  Neighbours (a session's lists, a feature's)
+// stay together, features of unequal mean length load the queues alike, and a few lists spread over all of them.
+RECD_RULE int recd_deal_log(int64_t n, int queues, int lb_log)
 {
-    return ((t / kDealtLists) * queues + q) * kDealtLists + t % kDealtLists;
+    int log = 0;
+    while (log < 6 && ((int64_t)queues * 32 << log) <= n)
+        log++;
+    return log > lb_log ? log : lb_log;
 }
 
-// Unique lists per block of the sequence backward's sum over their rows: 24 to 48 positions where a list is
-// known to have many rows, else twice as many (the bounds are all that the host knows).  Whole call, us, by the
-// bound 48 / 96 / 192 / 384: eight rows a list, 0.26 M positions: of 256 bytes 186 / 192 / 208 / 242, of 64 bytes
-// 101 / 100 / 104 / 114; one row a list, 2.1 M positions: of 256 bytes 720 / 681 / 684, of 64 bytes 346 / 306 / 286
-// / 282, of 16 bytes 304 / 242 / 214 / 207 (0.26 M positions of 128 bytes in lists of 2: 177 / 209 / 282).
-RECD_RULE int recd_jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap)
+// The t-th list of queue q.
+RECD_RULE int64_t recd_dealt(int64_t t, int q, int queues, int deal_log)
 {
-    const double positions = (double)M_cap / (double)(U_cap > 0 ? U_cap : 1), most = N > 4 * M_cap ? 48.0 : 96.0;
+    return ((((t >> deal_log) * queues) + q) << deal_log) + (t & (((int64_t)1 << deal_log) - 1));
+}
+
+// Unique lists per block of the sequence backward's sum over their rows, of 16 * vecs bytes each: 24 to 48
+// positions, and twice as many where rows are short, lists are neither short nor known to have many rows, and
+// there are more blocks than the chip holds several times over (2.1 M positions, one row a list, whole call, us, by the
+// bound 48 / 96: rows of 16 bytes 304 / 242, of 64 bytes 346 / 306, of 128 bytes 478 / 434).  Elsewhere the smaller
+// block is the better or the safer one: eight rows a list, 0.26 M positions of 256 bytes 186 / 192; lists of 2
+// positions 177 / 209; 0.3 M positions in lists of 1 to 400, 256 bytes, 205 / 250.
+RECD_RULE int recd_jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vecs, int num_cu)
+{
+    const double positions = (double)M_cap / (double)(U_cap > 0 ? U_cap : 1);
     int lists = 1;
-    while (lists < 64 && 2.0 * lists * positions <= most)
+    while (lists < 64 && 2.0 * lists * positions <= 48.0)
+        lists *= 2;
+    if (vecs <= 8 && positions >= 8.0 && N <= 4 * M_cap && 2.0 * lists * positions <= 96.0 &&
+        U_cap / (2 * lists) >= (int64_t)num_cu * 32)
         lists *= 2;
     return lists;
 }

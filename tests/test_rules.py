@@ -11,7 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 HARNESS = r"""
 #include "recd_rules.h"
 extern "C" {
-int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap) { return recd_jagged_lists(N, U_cap, M_cap); }
+int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vecs) { return recd_jagged_lists(N, U_cap, M_cap, vecs, 256); }
 int64_t lists_held(int64_t F, int64_t B, int64_t U_cap, int64_t M_cap) { return recd_lists_held(F, B, U_cap, M_cap); }
 
 // starts[slot] and how often each was written, of n >= 1 sorted keys; returns the writes outside [0, slots)
@@ -33,10 +33,11 @@ int64_t slot_starts(const uint32_t *keys, int64_t n, uint32_t bits, int64_t slot
 // work[q] of the lists that the blocks of queue q take, lists per block item lpb, `stride` blocks a queue
 void deal(int64_t n, int queues, int lpb, int64_t stride, const int64_t *len, int64_t *work, int32_t *taken)
 {
+    const int log = recd_deal_log(n, queues, 31 - __builtin_clz(lpb));
     for (int q = 0; q < queues; q++)
         for (int64_t b = 0; b < stride; b++)
             for (int64_t t = b * lpb;; t += stride * lpb) {
-                const int64_t l0 = recd_dealt(t, q, queues);
+                const int64_t l0 = recd_dealt(t, q, queues, log);
                 if (l0 >= n)
                     break;
                 for (int64_t l = l0; l < n && l < l0 + lpb; l++) {
@@ -128,13 +129,24 @@ def test_lookup_lists_of_any_number_are_all_dealt(rules, n):
     assert (taken[:n] == 1).all() and work.sum() == n
 
 
+@pytest.mark.parametrize("n", [8, 50, 100, 300, 530, 1000, 4000, 8191, 8192, 20000])
+def test_few_lookup_lists_spread_over_all_queues(rules, n):
+    rules.deal.restype = None
+    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
+    work, taken = np.zeros(8, dtype=np.int64), np.zeros(n, dtype=np.int32)
+    rules.deal(n, 8, 1, n, _ptr(np.ones(n, dtype=np.int64)), _ptr(work), _ptr(taken))
+    assert work.max() <= n / 8 * 1.0625 + 1
+
+
 def test_lists_per_block_of_the_sequence_backward(rules):
-    """A power of two up to 64; lists that are not known to have many rows come twice as many positions a block,
-    whose threads short rows would leave idle."""
-    rules.jagged_lists.argtypes = [C.c_int64] * 3
+    """A power of two up to 64 and at most 48 positions; twice that for short rows of many lists that are not
+    known to have many rows: a block's threads would be idle for the most part."""
+    rules.jagged_lists.argtypes = [C.c_int64] * 3 + [C.c_int]
     for U, M in ((1, 0), (0, 0), (10 ** 6, 16 * 10 ** 6), (10 ** 6, 10 ** 5), (7, 10 ** 9), (300, 300 * 30)):
-        few, many = rules.jagged_lists(M, U, M), rules.jagged_lists(9 * M + 9, U, M)
-        assert few in (1, 2, 4, 8, 16, 32, 64) and many in (few, few // 2)
-        assert few == 1 or few * M <= 96 * U
-        assert few == 64 or 2 * few * M > 96 * max(U, 1)
-        assert many == 64 or 2 * many * M > 48 * max(U, 1)
+        base = rules.jagged_lists(M, U, M, 16)
+        assert base in (1, 2, 4, 8, 16, 32, 64) and (base == 1 or base * M <= 48 * max(U, 1))
+        assert base == 64 or 2 * base * M > 48 * max(U, 1)
+        assert rules.jagged_lists(9 * M + 9, U, M, 1) == base
+    assert rules.jagged_lists(16 * 10 ** 6, 10 ** 6, 16 * 10 ** 6, 4) == 4
+    assert rules.jagged_lists(16 * 10 ** 6, 10 ** 6, 16 * 10 ** 6, 16) == 2     # long rows
+    assert rules.jagged_lists(16 * 10 ** 3, 10 ** 3, 16 * 10 ** 3, 4) == 2      # few lists
