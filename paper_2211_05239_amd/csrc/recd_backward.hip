@@ -697,12 +697,12 @@ struct BwdWs {
     size_t bytes;
 };
 
-// Step B's lane groups walk a segment entry by entry, eight segments to a wave, so a wave lasts as
+// Step B's lane groups walk a segment entry by entry, several segments to a wave, so a wave lasts as
 // long as its longest segment; segments with more entries than the context's cut
-// (RECD_OPT_LONG_SEGMENT_CUT, default 32) go to the block-cooperative chunk passes on the side
-// stream.  Measured at 2.2 M entries: 0.847 ms per step with 64, 0.838 with 32, 0.836 with 24 or 16;
-// at 35 M entries (no deduplication), where the chunk passes are the larger part: 4.28 ms with 64,
-// 4.55 with 32.
+// (RECD_OPT_LONG_SEGMENT_CUT, default 32) are cut into chunks, which the first blocks of the launch sum.
+// Whole backward, us, with a cut of 16 / 32 / 64 / 128: 2.2 M entries of 512 bytes 482 / 474 / 501 / 538, 0.19 M
+// 127 / 132 / 148 / 184, 0.3 M 139 / 142 / 159 / 192; 35 M of 256 bytes (no deduplication, where the chunks are
+// the larger part) 3410 / 3220 / 3125 / 3185; uniform ids alike.
 constexpr int kDefaultLongSeg = 32;
 
 // Lanes that carry a row in the row-gradient sum (up to four 16-byte pieces each).
@@ -814,9 +814,9 @@ RecdGroupArgs group_args(const BwdWs &w, int F, int64_t B, int64_t U_cap, int64_
 }
 
 // Step B after the grouping: all segments in one launch, optimizer fused.
-recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t n_cap, int64_t seg_bound,
-                     const void *table, int D, void *out, int64_t *touched_rows, const OptAdagrad *opt,
-                     const float *pay_w, const uint32_t *won = nullptr)
+recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t M_cap, const void *table,
+                     int D, void *out, int64_t *touched_rows, const OptAdagrad *opt, const float *pay_w,
+                     const uint32_t *won = nullptr)
 {
     hipStream_t st = ctx->stream;
     RowSumParams rp = row_params(w, ps, pay_w, table, D, out);
@@ -831,7 +831,7 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
     o.seg_feat = w.seg_feat;
     const int lpr = row_lanes(D);
     const int per_block = 4 * (64 / lpr);
-    int64_t nblk = (seg_bound + per_block - 1) / per_block;
+    int64_t nblk = (M_cap + per_block - 1) / per_block;
     const int64_t cap = (int64_t)ctx->num_cu * 64;
     if (nblk > cap)
         nblk = cap;
@@ -840,7 +840,7 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
         nblk = 8;
     // blocks for the chunks: their number is on the device, usually far below the bound: at most what the
     // chip holds at once, striding
-    int64_t cblk = n_cap / 256 + n_cap / (w.long_seg + 1);
+    int64_t cblk = M_cap / 256 + M_cap / (w.long_seg + 1);
     if (cblk > (int64_t)ctx->num_cu * 8)
         cblk = (int64_t)ctx->num_cu * 8;
     rp.chunk_blocks = (unsigned)((cblk + 7) / 8 * 8);
@@ -875,8 +875,8 @@ size_t recd_backward_workspace(int F, int64_t B, int64_t M_cap, int D)
 }
 
 // The fused update reads and writes a table row (and its accumulator) once per (feature, row)
-// segment, from different lane groups and two streams at the same time: two features must not name
-// the same table or the same accumulator array.
+// segment, from different lane groups at the same time: two features must not name the same table or
+// the same accumulator array.
 static recd_status check_distinct_tables(recd_ctx *ctx, int F, void *const *tables, float *const *state)
 {
     if (!tables)
@@ -1064,7 +1064,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
     }
     const float *b_table = seq ? grad_emb : w.g_u;
     // ---- step B: sum the source rows of every (feature, row) into grad_rows -------------------------
-    RECD_TRY(sum_rows(ctx, w, ps_b, M_cap, M_cap, b_table, D, grad_rows, touched_rows, fused ? &oa : nullptr,
+    RECD_TRY(sum_rows(ctx, w, ps_b, M_cap, b_table, D, grad_rows, touched_rows, fused ? &oa : nullptr,
                       u_weights || maxmode ? w.pay_w : nullptr, maxmode ? w.won : nullptr));
     // ---- optimizer -------------------------------------------------------------------------------
     if (tables && !fused) {
@@ -1265,7 +1265,7 @@ extern "C" recd_status recd_backward_apply(recd_ctx *ctx, recd_pooling mode, con
         oa.eps = eps;
     }
     RECD_TRY(sum_lists(ctx, w, pl.ps_a, pl.U_cap, grad_out, D, mode == RECD_POOL_MEAN ? pl.u_offsets : nullptr));
-    RECD_TRY(sum_rows(ctx, w, pl.ps_b, M_cap, M_cap, w.g_u, D, grad_rows, pl.touched_rows, fused ? &oa : nullptr,
+    RECD_TRY(sum_rows(ctx, w, pl.ps_b, M_cap, w.g_u, D, grad_rows, pl.touched_rows, fused ? &oa : nullptr,
                       nullptr));
     if (tables && !fused) {
         for (int f0 = 0; f0 < F; f0 += RECD_F_PER_LAUNCH) {

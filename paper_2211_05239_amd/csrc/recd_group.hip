@@ -170,12 +170,12 @@ __device__ __forceinline__ void write_bases(const SideParams &s, int f, const ui
 // last of every sixteen adds up these first).  The block also
 // clears the look-back flags of its tiles; further blocks write the list of every position.  What is
 // read is small (8 bytes an entry): the kernel is a few dependent round trips and the LDS atomics of a
-// chunk. 
+// chunk.
 __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams g)
 {
     extern __shared__ uint32_t s_dyn[];          // the counts [passes * radix], side B also pb [F+1]: as little
     uint32_t *s_hist = s_dyn;                    // LDS as there is, so that blocks find room beside the lookup's
-    __shared__ uint32_t s_pick[6];
+    __shared__ uint32_t s_pick[5];
     const int tid = threadIdx.x;
     if (blockIdx.x >= g.list_block0) {
         // the list of every position, 16 lanes to a list: blocks of their own, beside the chain of the others
@@ -194,7 +194,6 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
     int f, c, n_chunks;
     uint32_t begin, end;           // entries of the chunk
     size_t first_tile, chunk_row;  // in queue order; row of chunk_hist
-    uint32_t tiles_f;
     if (blockIdx.x == 0 && tid < (kMaxPasses + 1) * kQueues) {
         g.a.ticket[tid] = 0;
         g.b.ticket[tid] = 0;
@@ -208,7 +207,6 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         const int q = f % kQueues, per_q = g.F / kQueues, more = g.F % kQueues;
         first_tile = (size_t)(q * per_q + (q < more ? q : more) + f / kQueues) * g.tpf + (size_t)c * (s.chunk / kTile);
         chunk_row = blk;
-        tiles_f = g.tpf;
         if (blk == 0 && tid == 0)
             report_side_a(g, g.feat_uoff[g.F]);
     } else {
@@ -251,7 +249,6 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
                     s_pick[1] = blk - c0;
                     s_pick[2] = c_f;
                     s_pick[3] = (uint32_t)(ex >> 32);
-                    s_pick[4] = tiles_of(x);
                 }
                 ex += ((uint64_t)tiles_of(x) << 32) | c_f;
             }
@@ -263,7 +260,7 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
             if (x < g.F) {
                 const int fq = in_queue(x) * kQueues + queue_of(x);
                 if ((uint32_t)fq == s_pick[0])
-                    s_pick[5] = t_q;
+                    s_pick[4] = t_q;
                 if (blk == 0 && in_queue(x) == 0)
                     g.queue_start[queue_of(x)] = t_q;
                 t_q += tiles_of(fq);
@@ -287,10 +284,9 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         f = (int)s_pick[0];
         c = (int)s_pick[1];
         n_chunks = (int)s_pick[2];
-        tiles_f = s_pick[4];
         begin = s_pb[f] + (uint32_t)(c * s.chunk);
         end = (uint32_t)((int64_t)begin + s.chunk < (int64_t)s_pb[f + 1] ? begin + s.chunk : s_pb[f + 1]);
-        first_tile = s_pick[5] + (size_t)c * (s.chunk / kTile);
+        first_tile = s_pick[4] + (size_t)c * (s.chunk / kTile);
         chunk_row = blk;
         const uint32_t my_tiles = (end - begin + kTile - 1) / kTile, k0 = (uint32_t)(c * (s.chunk / kTile));
         for (uint32_t k = tid; k < my_tiles; k += kCountThreads) {

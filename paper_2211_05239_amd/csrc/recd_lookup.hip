@@ -297,9 +297,7 @@ void k_segsum(const SegSumParams p)
     constexpr int UNR = (VPL == 1) ? 8 : (VPL == 2 ? 4 : 2);
     constexpr int LL = ROWF <= 256 ? 4 : (ROWF <= 512 ? 2 : 1);  // long lists folded per barrier pair
 
-    __shared__ int64_t s_loff[RECD_F_PER_LAUNCH + 1];
-    __shared__ int64_t s_qpref[RECD_F_PER_LAUNCH + 1];
-    __shared__ int64_t s_start[kMaxLB], s_end[kMaxLB], s_list[kMaxLB];
+    __shared__ int64_t s_start[kMaxLB], s_end[kMaxLB];
     __shared__ int s_feat[kMaxLB];
     __shared__ float s_part[LL][kWaves][ROWF];
     constexpr bool EXPAND = SITE == SITE_UNIQUE_EXPAND;
@@ -312,37 +310,6 @@ void k_segsum(const SegSumParams p)
     const int q = nq == 1 ? 0 : (int)(blockIdx.x % kNQ);
     const int64_t item0 = nq == 1 ? blockIdx.x : blockIdx.x / kNQ;
     const int64_t item_stride = nq == 1 ? gridDim.x : gridDim.x / kNQ;
-    const int nslots = (p.F - q + nq - 1) / nq;  // features in my queue: q, q+nq, ...
-
-    if constexpr (kWaves > 1) {
-    for (int f = tid; f <= p.F; f += kSegBlock)
-        s_loff[f] = p.list_off ? p.list_off[f] : (int64_t)f * p.lists_per_feature;
-    __syncthreads();
-    if (wv == 0) {
-        // exclusive prefix of my queue's per-feature list counts: two slots per lane
-        const int k0 = 2 * lane, k1 = 2 * lane + 1;
-        const int f0 = q + k0 * nq, f1 = q + k1 * nq;
-        const int64_t c0 = k0 < nslots ? s_loff[f0 + 1] - s_loff[f0] : 0;
-        const int64_t c1 = k1 < nslots ? s_loff[f1 + 1] - s_loff[f1] : 0;
-        int64_t inc = c0 + c1;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int64_t x = __shfl_up(inc, d);
-            if (lane >= d)
-                inc += x;
-        }
-        const int64_t ex = inc - c0 - c1;
-        if (k0 < nslots)
-            s_qpref[k0] = ex;
-        if (k1 < nslots)
-            s_qpref[k1] = ex + c0;
-        const int64_t all = __shfl(inc, 63);
-        if (lane == 0)
-            s_qpref[nslots] = all;
-    }
-    __syncthreads();
-    }
-    const int64_t total = kWaves == 1 ? 0 : s_qpref[nslots];
 
     const int g = lane / LPR;   // lane group = which of the G rows of a load
     const int r = lane % LPR;   // 16-byte piece of the row
@@ -551,27 +518,16 @@ void k_segsum(const SegSumParams p)
         return;
     }
 
+    // Four waves: the lists of one table, one flat queue.
+    const int64_t total = uniform64(p.list_off[1]);
+    const char *table = static_cast<const char *>(p.tables.p[0]) + lane_off;
     for (int64_t item = item0; item * lb < total; item += item_stride) {
         const int64_t t0 = item * lb;
         const int cnt = (int)(total - t0 < lb ? total - t0 : lb);
         __syncthreads();  // the previous item no longer reads the shared arrays
         if (tid < cnt) {
-            const int64_t t = t0 + tid;
-            int lo = 0, hi = nslots;  // slot with s_qpref[slot] <= t < s_qpref[slot+1]
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (s_qpref[mid] <= t)
-                    lo = mid;
-                else
-                    hi = mid;
-            }
-            const int f = q + lo * nq;
-            const int64_t l = p.list_base + s_loff[f] + (t - s_qpref[lo]);
-            s_feat[tid] = f;
-            s_list[tid] = l;
-            const int64_t start = p.offsets[l];
-            s_start[tid] = start;
-            s_end[tid] = p.lens ? start + p.lens[l] : p.offsets[l + 1];
+            s_start[tid] = p.offsets[t0 + tid];
+            s_end[tid] = p.offsets[t0 + tid + 1];
         }
         __syncthreads();
 
@@ -583,7 +539,6 @@ void k_segsum(const SegSumParams p)
             const bool is_long = j < cnt && s_end[j] - s_start[j] > kChunk;  // block-uniform
             if (is_long) {
                 const int64_t start = uniform64(s_start[j]), end = uniform64(s_end[j]);
-                const char *table = static_cast<const char *>(p.tables.p[s_feat[j]]) + lane_off;
                 float acc[1][NACC];
 #pragma unroll
                 for (int i = 0; i < NACC; i++)
@@ -618,7 +573,7 @@ void k_segsum(const SegSumParams p)
                                 t_ = pool2<MODE>(t_, s_part[e][w2][x]);  // wave order
                             tot[w * EPV + i] = t_;
                         }
-                    finish_row(s_list[batch[e]], s_end[batch[e]] - s_start[batch[e]], tot);
+                    finish_row(t0 + batch[e], s_end[batch[e]] - s_start[batch[e]], tot);
                 }
                 __syncthreads();
                 nb = 0;
@@ -631,7 +586,6 @@ void k_segsum(const SegSumParams p)
             const int64_t len = uniform64(s_end[j]) - start;
             if (len > kChunk)
                 continue;
-            const char *table = static_cast<const char *>(p.tables.p[s_feat[j]]) + lane_off;
             const int n = (int)len;
             float acc[1][NACC];
 #pragma unroll
@@ -640,7 +594,7 @@ void k_segsum(const SegSumParams p)
             add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, SITE == SITE_GRAD_STREAM>(acc, &table, values, &start, &n,
                                                                                    row_bytes, lane, g, p.weights);
             fold_groups(acc[0]);
-            finish_row(s_list[j], len, acc[0]);
+            finish_row(t0 + j, len, acc[0]);
         }
     }
 }
