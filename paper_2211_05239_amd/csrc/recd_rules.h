@@ -39,9 +39,8 @@ RECD_RULE void recd_slot_starts(uint32_t key, uint32_t prev, bool first, bool la
 // stay together, features of unequal mean length load the queues alike, and a few lists spread over all of them.
 RECD_RULE int recd_deal_log(int64_t n, int queues, int lb_log)
 {
-    int log = 0;
-    while (log < 6 && ((int64_t)queues * 32 << log) <= n)
-        log++;
+    const int64_t rounds = n / (queues * 32);
+    const int bits = rounds > 0 ? 64 - __builtin_clzll((uint64_t)rounds) : 0, log = bits < 6 ? bits : 6;
     return log > lb_log ? log : lb_log;
 }
 
