@@ -18,7 +18,7 @@
 //     non-deduplicated lookup (same W) agree bit for bit.
 //   * blocks are dealt to lists statically (no atomics; the hardware's block dispatch balances the
 //     load).  The lookups' mapping is XCD-aware: consecutive blocks go to consecutive XCDs, and block b
-//     serves every eighth 64 neighbouring lists from the (b mod 8)-th on, so that lists that share
+//     serves every eighth stretch of neighbouring lists from the (b mod 8)-th on, so that lists that share
 //     rows meet in one XCD's L2 and features of unequal mean length load the XCDs alike.  The number of lists may live on the device only (unique lists): the grid is
 //     sized from a host-side bound and every block strides until its queue is exhausted, so any grid
 //     size is correct.
@@ -453,14 +453,13 @@ void k_segsum(const SegSumParams p)
         // ballots, and one load brings the bounds of the block's lists; they wait in 320 bytes of LDS
         // while rows are gathered (in registers they cost the seventh wave).  (Prefix sums over the
         // features and 4.6 KB of LDS a wave before; 28 waves of that on a CU also kept blocks of other
-        // streams out.)  Queue q = blockIdx mod 8 (one XCD) takes every eighth 64 neighbouring lists (of fewer
-        // than 8 K lists fewer, recd_deal_log: dealt 64 at a time, a few hundred would leave XCDs idle):
-        // balanced whatever the features' mean lengths.  (A contiguous eighth each, as few XCDs for a feature as
-        // there can be, is at best a tenth faster and up to 2.6 times slower: fp32 rows of 512 bytes, unique / KJT
-        // lookup, us, contiguous -> dealt: 32 even features 67 / 307 -> 68 / 306, 5 even ones 22 / 53 -> 24 / 51;
-        // four of 32 of mean 64 and the rest of 2: 114 / 792 -> 51 / 246; the first of 6 of mean 100, the rest of
-        // 2: 71 / 190 -> 31 / 72; one of 65 of mean 150, the rest of 4: 131 / 414 -> 87 / 241.  32 to 256 lists
-        // at a time are alike; from 512 on a feature's heavy lists stay on too few XCDs again.)
+        // streams out.)  Queue q = blockIdx mod 8 (one XCD) takes every eighth stretch of neighbouring lists
+        // (recd_deal_log): balanced whatever the features' mean lengths.  (A contiguous eighth each, as few XCDs for a
+        // feature as there can be, is up to a tenth faster and up to 2.6 times slower: fp32 rows of 512 bytes, unique /
+        // KJT lookup, us, contiguous -> dealt: 32 even features 67 / 307 -> 69 / 305, 5 even ones 22 / 53 -> 24 / 51,
+        // 64 of skewed ids 122 / 990 -> 125 / 1005; four of 32 of mean 64 and the rest of 2: 114 / 792 -> 53 / 250;
+        // the first of 6 of mean 100, the rest of 2: 71 / 190 -> 30 / 72; one of 65 of mean 150, the rest of 4:
+        // 131 / 414 -> 91 / 242.  Four times fewer and longer stretches: one feature of 64 KJT 297 -> 355.)
         const int64_t first = p.list_off ? uniform64(p.list_off[0]) : p.list_base;
         const int64_t end_all = p.list_off ? uniform64(p.list_off[p.F]) : p.list_base + p.F * p.lists_per_feature;
         const int64_t all = end_all - first;

@@ -34,13 +34,14 @@ RECD_RULE void recd_slot_starts(uint32_t key, uint32_t prev, bool first, bool la
         put(x, true);
 }
 
-// The lookups deal their n lists to the XCDs' block queues in turn, up to 64 neighbours (2^6) at a time and at least
-// 16 times round, but no fewer than the 2^lb_log lists of a block.  Neighbours (a session's lists, a feature's)
-// stay together, features of unequal mean length load the queues alike, and a few lists spread over all of them.
+// The lookups deal their n lists to the XCDs' block queues in turn, up to 1024 neighbours (2^10) at a time and at
+// least 32 times round, but no fewer than the 2^lb_log lists of a block.  Neighbours (a session's lists, a
+// feature's) stay together, features of unequal mean length load the queues alike, and a few lists spread over all
+// of them.  (64 at a time at most is alike but for the largest: 1.05 M KJT lists of fp32 rows 1022 us, now 1005.)
 RECD_RULE int recd_deal_log(int64_t n, int queues, int lb_log)
 {
-    const int64_t rounds = n / (queues * 32);
-    const int bits = rounds > 0 ? 64 - __builtin_clzll((uint64_t)rounds) : 0, log = bits < 6 ? bits : 6;
+    const int64_t rounds = n / (queues * 64);
+    const int bits = rounds > 0 ? 64 - __builtin_clzll((uint64_t)rounds) : 0, log = bits < 10 ? bits : 10;
     return log > lb_log ? log : lb_log;
 }
 
