@@ -161,6 +161,7 @@ struct SegSumParams {
     int vecs_per_row;  // D / elements per 16-byte vector
     int nq;            // 8: XCD-aware queues (forward sites only); 1: one flat queue
     int lb;            // lists per block item, <= kMaxLB; 0 (forward sites): chosen by the number of lists
+    int deal_log;      // SITE_KJT: how many lists are dealt to a queue at a time (recd_deal_log_kjt)
     // optional: list l spans offsets[l] .. offsets[l] + lens[l] (windows of a partial IKJT)
     const int64_t *lens;
     // optional (SITE_GRAD_STREAM only): the finished row of list l is divided by
@@ -457,16 +458,16 @@ void k_segsum(const SegSumParams p)
         // (recd_deal_log): balanced whatever the features' mean lengths.  (A contiguous eighth each, as few XCDs for a
         // feature as there can be, is up to a tenth faster and up to 2.6 times slower: fp32 rows of 512 bytes, unique /
         // KJT lookup, us, contiguous -> dealt: 32 even features 67 / 307 -> 69 / 305, 5 even ones 22 / 53 -> 24 / 51,
-        // 64 of skewed ids 122 / 990 -> 125 / 1005; four of 32 of mean 64 and the rest of 2: 114 / 792 -> 53 / 250;
+        // 64 of skewed ids 122 / 987 -> 124 / 995; four of 32 of mean 64 and the rest of 2: 114 / 792 -> 53 / 250;
         // the first of 6 of mean 100, the rest of 2: 71 / 190 -> 30 / 72; one of 65 of mean 150, the rest of 4:
-        // 131 / 414 -> 91 / 242.  Four times fewer and longer stretches: one feature of 64 KJT 297 -> 355.)
+        // 131 / 414 -> 91 / 242.)
         const int64_t first = p.list_off ? uniform64(p.list_off[0]) : p.list_base;
         const int64_t end_all = p.list_off ? uniform64(p.list_off[p.F]) : p.list_base + p.F * p.lists_per_feature;
         const int64_t all = end_all - first;
         // lists per block: as many as keep the number of blocks in bounds (measured at 61 K unique lists
         // and at 1.05 M KJT lists: 1 and 4), by the true number of lists
         const int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
-        const int deal_log = recd_deal_log(all, kNQ, 31 - __builtin_clz(lpb));
+        const int deal_log = SITE == SITE_KJT ? p.deal_log : recd_deal_log(all, kNQ, 31 - __builtin_clz(lpb));
         for (int64_t t = item0 * lpb;; t += item_stride * lpb) {
             const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ, deal_log));
             if (l0 >= end_all)
@@ -958,6 +959,7 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     p.lb = one_wave ? 0 : lb;
     if (ctx->tune_lb > 0)
         p.lb = lb = ctx->tune_lb;
+    p.deal_log = recd_deal_log_kjt(n, a.F, kNQ, 31 - __builtin_clz(lb));
     const int64_t items = (n + lb - 1) / lb;
     int64_t nblk = p.nq == 1 ? items : kNQ * ((items + kNQ - 1) / kNQ + (items / kNQ) / 8 + 1);
     const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : 64);

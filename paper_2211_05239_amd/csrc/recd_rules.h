@@ -45,6 +45,21 @@ RECD_RULE int recd_deal_log(int64_t n, int queues, int lb_log)
     return log > lb_log ? log : lb_log;
 }
 
+// The same for the KJT's n lists, which the host knows.  Half a million and more of features that the queues can share
+// evenly: up to 8192 at a time, 16 times round, so that a feature's hot rows are in fewer L2s (1.05 M lists of 64
+// features, skewed ids 1038 -> 993 us; one feature of the 64 with half of the ids 297 -> 434, which a queue per
+// feature took 636 for; 65 features, one with a third of the ids, would go from 242 to 324 where lists dealt one
+// by one took 253).
+RECD_RULE int recd_deal_log_kjt(int64_t n, int F, int queues, int lb_log)
+{
+    if (F % queues != 0 || n < (int64_t)1 << 19)
+        return recd_deal_log(n, queues, lb_log);
+    int log = 10;
+    while (log < 13 && ((int64_t)queues * 16 << (log + 1)) <= n)
+        log++;
+    return log > lb_log ? log : lb_log;
+}
+
 // The t-th list of queue q.
 RECD_RULE int64_t recd_dealt(int64_t t, int q, int queues, int deal_log)
 {

@@ -31,9 +31,9 @@ int64_t slot_starts(const uint32_t *keys, int64_t n, uint32_t bits, int64_t slot
 }
 
 // work[q] of the lists that the blocks of queue q take, lists per block item lpb, `stride` blocks a queue
-void deal(int64_t n, int queues, int lpb, int64_t stride, const int64_t *len, int64_t *work, int32_t *taken)
+void deal(int64_t n, int F, int queues, int lpb, int64_t stride, const int64_t *len, int64_t *work, int32_t *taken)
 {
-    const int log = recd_deal_log(n, queues, 31 - __builtin_clz(lpb));
+    const int log = recd_deal_log_kjt(n, F, queues, 31 - __builtin_clz(lpb));
     for (int q = 0; q < queues; q++)
         for (int64_t b = 0; b < stride; b++)
             for (int64_t t = b * lpb;; t += stride * lpb) {
@@ -110,11 +110,11 @@ def test_lookup_lists_are_dealt_evenly(rules, means):
     """Every list goes to one block of one queue, and features of unequal mean length load the queues (the XCDs)
     alike: none has more than a quarter above its share of the ids."""
     rules.deal.restype = None
-    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
+    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
     lens = np.concatenate([np.full(1800, m, dtype=np.int64) for m in means])
     for lpb, stride in ((1, 3000), (2, 7), (4, 500), (16, 100)):
         work, taken = np.zeros(8, dtype=np.int64), np.zeros(len(lens), dtype=np.int32)
-        rules.deal(len(lens), 8, lpb, stride, _ptr(lens), _ptr(work), _ptr(taken))
+        rules.deal(len(lens), len(means), 8, lpb, stride, _ptr(lens), _ptr(work), _ptr(taken))
         assert (taken == 1).all()
         assert work.max() <= 1.25 * work.mean(), work
 
@@ -122,19 +122,19 @@ def test_lookup_lists_are_dealt_evenly(rules, means):
 @pytest.mark.parametrize("n", [0, 1, 63, 64, 65, 511, 512, 513, 5000])
 def test_lookup_lists_of_any_number_are_all_dealt(rules, n):
     rules.deal.restype = None
-    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
+    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
     lens = np.ones(max(n, 1), dtype=np.int64)
     work, taken = np.zeros(8, dtype=np.int64), np.zeros(max(n, 1), dtype=np.int32)
-    rules.deal(n, 8, 4, 3, _ptr(lens), _ptr(work), _ptr(taken))
+    rules.deal(n, 8, 8, 4, 3, _ptr(lens), _ptr(work), _ptr(taken))
     assert (taken[:n] == 1).all() and work.sum() == n
 
 
-@pytest.mark.parametrize("n", [8, 50, 100, 300, 530, 1000, 4000, 8191, 8192, 20000])
+@pytest.mark.parametrize("n", [8, 50, 100, 300, 530, 1000, 4000, 8191, 8192, 20000, 1 << 19, (1 << 20) + 5])
 def test_few_lookup_lists_spread_over_all_queues(rules, n):
     rules.deal.restype = None
-    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
+    rules.deal.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
     work, taken = np.zeros(8, dtype=np.int64), np.zeros(n, dtype=np.int32)
-    rules.deal(n, 8, 1, n, _ptr(np.ones(n, dtype=np.int64)), _ptr(work), _ptr(taken))
+    rules.deal(n, 8, 8, 1, n, _ptr(np.ones(n, dtype=np.int64)), _ptr(work), _ptr(taken))
     assert work.max() <= n / 8 * 1.0625 + 1
 
 
