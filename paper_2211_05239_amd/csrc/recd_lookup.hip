@@ -386,7 +386,7 @@ void k_segsum(const SegSumParams p)
         // of runs on the device (a scalar load of one word that every block shares): dealt by an
         // eighth of the host's estimate, all runs went to one XCD when the estimate was the bound F*B
         // (1.05 M rows, 64 K runs: 532 us for 256-byte and 1014 us for 512-byte rows, now 118 and
-        // 233; with a good estimate 124 -> 118 and 226 -> 233).
+        // 233; with a good estimate 95 -> 91 and 180 -> 180).
         const int64_t *ri = p.run_index;
         const int64_t n_runs = ri[0] < p.run_cap ? ri[0] : p.run_cap;
         const int64_t per = (n_runs + kNQ - 1) / kNQ;
