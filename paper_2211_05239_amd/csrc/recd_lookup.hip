@@ -39,6 +39,7 @@ template <int SITE> struct SegBlock {
     static constexpr int threads = (SITE == 0 || SITE == 1 || SITE == 4) ? 64 : 256;
 };
 constexpr int kMaxLB = 16;     // lists per block item (upper bound)
+constexpr int64_t kSampledLists = 32768;  // KJT lists from which on a sample decides how many a wave takes
 constexpr int kChunk = 64;     // ids per chunk: a wave loads a chunk's ids with one instruction
 
 __device__ __forceinline__ int64_t uniform64(int64_t v)
@@ -331,8 +332,8 @@ void k_segsum(const SegSumParams p)
                 acc[i] = pool2<MODE>(acc[i], __shfl_xor(acc[i], s));
     };
 
-    // A finished row (list l of len ids): lanes of group 0 hold its NACC-element pieces in vals.
-    auto finish_row = [&](int64_t l, int64_t len, float *vals) {
+    // A list's sum (list l of len ids) into its finished row, in place.
+    auto scale_row = [&](int64_t l, int64_t len, float *vals) {
         if (MODE == POOL_MEAN || MODE == POOL_MAX) {
 #pragma unroll
             for (int i = 0; i < NACC; i++)
@@ -346,20 +347,28 @@ void k_segsum(const SegSumParams p)
                     vals[i] = vals[i] / (float)n;
             }
         }
-        if (g == 0 && piece_ok) {
+    };
+    // A finished row, whose NACC-element pieces the lanes of a lane group hold in vals.
+    auto store_row = [&](int64_t l, const float *vals) {
+        if (piece_ok) {
             char *dst = static_cast<char *>(p.out) + l * out_row_bytes;
 #pragma unroll
             for (int w = 0; w < VPL; w++)
                 store_row_piece<OT, EPV, NT>(dst + ((int64_t)w * LPR + r) * OB, vals + w * EPV);
         }
     };
+    auto finish_row = [&](int64_t l, int64_t len, float *vals) {
+        scale_row(l, len, vals);
+        if (g == 0)
+            store_row(l, vals);
+    };
 
     // One wave walks a whole list of more than 64 ids: the ids of the next chunk are fetched before
     // the rows of this one, so their latency hides behind the row loads.
-    auto walk_long_list = [&](float (*acc)[NACC], const char *table, int64_t start, int64_t end) {
+    // cur: this lane's id of the first chunk.
+    auto walk_long_list = [&](float (*acc)[NACC], const char *table, int64_t start, int64_t end, uint32_t cur) {
         int64_t base = start;
-        int n = (int)(end - base < kChunk ? end - base : kChunk);
-        uint32_t cur = lane < n ? (uint32_t)values[base + lane] : 0u;
+        int n = kChunk;
         for (;;) {
             const int64_t nbase = base + kChunk;
             const bool more = nbase < end;
@@ -423,7 +432,7 @@ void k_segsum(const SegSumParams p)
             for (int i = 0; i < NACC; i++)
                 acc[0][i] = pool_identity<MODE>();
             if (len_ids > kChunk) {
-                walk_long_list(acc, table, start, start + len_ids);
+                walk_long_list(acc, table, start, start + len_ids, (uint32_t)values[start + lane]);
             } else {
                 const int n = (int)len_ids;
                 add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes, lane,
@@ -466,7 +475,17 @@ void k_segsum(const SegSumParams p)
         const int64_t all = end_all - first;
         // lists per block: as many as keep the number of blocks in bounds (measured at 61 K unique lists
         // and at 1.05 M KJT lists: 1 and 4), by the true number of lists
-        const int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
+        int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
+        if (SITE == SITE_KJT && lb == 0 && all >= kSampledLists) {
+            // Where most neighbouring lists are as long as each other (60 pairs in four places: every wave sees the
+            // same ones) they are probably equal, and a wave that has more of them sums fewer.  Elsewhere more lists a
+            // wave only spread the waves over more tables: 8192 x 32 lists of 64 ids, by 1 / 2 / 4 / 8 lists, us:
+            // sessions of 8 556 / 407 / 340 / 341, of 2 920 / 882 / 928 / 962, no sessions 1441 / 1422 / 1488 / 1563.
+            const int64_t at = first + (all >> 2) * (lane >> 4) + (all >> 3) + (lane & 15);
+            const int64_t len = p.offsets[at + 1] - p.offsets[at], left = __shfl_up(len, 1);
+            if (__popcll(__ballot(len == left && (lane & 15) != 0)) >= 40)
+                lpb = all >= (96 << 10) ? 8 : 4;
+        }
         const int deal_log = SITE == SITE_KJT ? p.deal_log : recd_deal_log(all, kNQ, 31 - __builtin_clz(lpb));
         for (int64_t t = item0 * lpb;; t += item_stride * lpb) {
             const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ, deal_log));
@@ -493,25 +512,78 @@ void k_segsum(const SegSumParams p)
                 }
                 __syncthreads();  // a block of one wave: orders the LDS accesses, nobody waits
             }
-            for (int j = 0; j < cnt; j++) {
-                const int64_t l = l0 + j;
-                const int64_t start = uniform64(s_start[j]);
-                const int64_t len = uniform64(s_end[j]) - start;
-                const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
-                const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
-                float acc[1][NACC];
+            if constexpr (SITE == SITE_KJT) {
+                // Neighbouring lists of a session-ordered batch are mostly the same list.  The wave compares each of
+                // its lists with the one before it, all at once with 64 / lpb lanes to a list, sums the first of every
+                // run of equal ones and stores its row for the whole run: the same ids in the same order give the same
+                // bits.  What bounds the lookup is the gathered rows, and those of a run are gathered once (262 K lists
+                // of 64 ids, 512-byte rows, sessions of 8: 549 -> 328 us; 1.05 M of 34 ids, sessions of 16: 1010 -> 420).
+                // (Runs that go on into other waves' lists, with those left out there: 485; the waves that find
+                // nothing to do cost more than the sums saved.  One list after the other with the ids still in registers:
+                // 342.)
+                const int per = 6 - (31 - __builtin_clz(lpb)), at = lane & ((1 << per) - 1), mine = lane >> per;
+                bool same = false;
+                if (mine > 0 && mine < cnt && s_feat[mine] == s_feat[mine - 1]) {
+                    const int64_t start = s_start[mine], len = s_end[mine] - start, back = start - s_start[mine - 1];
+                    same = back == len;
+                    for (int64_t t = at; same && t < len; t += 4ll << per) {
 #pragma unroll
-                for (int i = 0; i < NACC; i++)
-                    acc[0][i] = pool_identity<MODE>();
-                if (len > kChunk) {
-                    walk_long_list(acc, table, start, start + len);
-                } else {
-                    const int n = (int)len;
-                    add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes,
-                                                                        lane, g, p.weights);
+                        for (int u = 0; u < 4; u++) {
+                            const int64_t k = t + ((int64_t)u << per);
+                            if (k < len) {
+                                same &= (uint32_t)values[start + k] == (uint32_t)values[start + k - back];
+                                if (MODE == POOL_WSUM)  // bit patterns: the sum depends on no more
+                                    same &= __float_as_uint(p.weights[start + k]) ==
+                                            __float_as_uint(p.weights[start + k - back]);
+                            }
+                        }
+                    }
                 }
-                fold_groups(acc[0]);
-                finish_row(l, len, acc[0]);
+                const uint64_t differ = __ballot(!same), group = per == 6 ? ~0ull : (1ull << (1 << per)) - 1;
+                for (int j = 0, end; j < cnt; j = end) {
+                    for (end = j + 1; end < cnt && ((differ >> (end << per)) & group) == 0; end++) {
+                    }
+                    const int64_t start = uniform64(s_start[j]);
+                    const int64_t len = uniform64(s_end[j]) - start;
+                    const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
+                    const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
+                    float acc[1][NACC];
+#pragma unroll
+                    for (int i = 0; i < NACC; i++)
+                        acc[0][i] = pool_identity<MODE>();
+                    if (len > kChunk) {
+                        walk_long_list(acc, table, start, start + len, (uint32_t)values[start + lane]);
+                    } else {
+                        const int n = (int)len;
+                        add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes,
+                                                                            lane, g, p.weights);
+                    }
+                    fold_groups(acc[0]);  // the butterfly leaves the row in every lane group
+                    scale_row(l0 + j, len, acc[0]);
+                    for (int k = j + g; k < end; k += 64 / LPR)
+                        store_row(l0 + k, acc[0]);
+                }
+            } else {
+                for (int j = 0; j < cnt; j++) {
+                    const int64_t l = l0 + j;
+                    const int64_t start = uniform64(s_start[j]);
+                    const int64_t len = uniform64(s_end[j]) - start;
+                    const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
+                    const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
+                    float acc[1][NACC];
+#pragma unroll
+                    for (int i = 0; i < NACC; i++)
+                        acc[0][i] = pool_identity<MODE>();
+                    if (len > kChunk) {
+                        walk_long_list(acc, table, start, start + len, (uint32_t)values[start + lane]);
+                    } else {
+                        const int n = (int)len;
+                        add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes,
+                                                                            lane, g, p.weights);
+                    }
+                    fold_groups(acc[0]);
+                    finish_row(l, len, acc[0]);
+                }
             }
             __syncthreads();
         }
@@ -959,7 +1031,9 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     p.lb = one_wave ? 0 : lb;
     if (ctx->tune_lb > 0)
         p.lb = lb = ctx->tune_lb;
-    p.deal_log = recd_deal_log_kjt(n, a.F, kNQ, 31 - __builtin_clz(lb));
+    // (the KJT lookup may take up to 8 lists a block where it samples them)
+    const bool sampled = a.site == RECD_SITE_KJT && ctx->tune_lb == 0 && n >= kSampledLists;
+    p.deal_log = recd_deal_log_kjt(n, a.F, kNQ, sampled ? 3 : 31 - __builtin_clz(lb));
     const int64_t items = (n + lb - 1) / lb;
     int64_t nblk = p.nq == 1 ? items : kNQ * ((items + kNQ - 1) / kNQ + (items / kNQ) / 8 + 1);
     const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : 64);

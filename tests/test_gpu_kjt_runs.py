@@ -1,0 +1,71 @@
+"""KJT lookup of batches whose neighbouring lists are equal or nearly so: a run of equal lists is summed once, and its
+rows have the bits that every list gives on its own (one list a block)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(seed, n_lists, rows, run):
+    """Runs of equal lists of 0 to 130 ids; one list in ten has an id or a weight changed (at its ends and around its
+    64th id), its ids rotated, or its last id left out."""
+    rng = np.random.default_rng(seed)
+    lists, weights = [], []
+    while len(lists) < n_lists:
+        n = int(rng.choice([0, 1, 2, 5, 17, 40, 63, 64, 65, 130], p=[.1, .15, .15, .2, .2, .1, .025, .025, .025, .025]))
+        ids, wts = rng.integers(0, rows, n), rng.choice([0.25, 0.5, 1.0, 2.0], n).astype(np.float32)
+        for _ in range(int(rng.geometric(1.0 / run))):
+            x, w = ids.copy(), wts.copy()
+            if n and rng.random() < 0.1:
+                at = int(rng.choice([0, n - 1, min(n - 1, 63), min(n - 1, 64)]))
+                kind = rng.integers(4)
+                if kind == 0:
+                    x[at] = (x[at] + 1) % rows
+                elif kind == 1:
+                    x = np.roll(x, 1)
+                elif kind == 2:
+                    w[at] = -w[at]
+                else:
+                    x, w = x[:-1], w[:-1]
+            lists.append(x)
+            weights.append(w)
+    lists, weights = lists[:n_lists], weights[:n_lists]
+    offsets = np.concatenate([[0], np.cumsum([len(x) for x in lists])])
+    return np.concatenate(lists), np.concatenate(weights), offsets
+
+
+# below and above the number of lists that are sampled, odd numbers of lists a feature; long and short runs
+@pytest.mark.parametrize("F,B,run,D,dtype", [(3, 341, 6, 64, "f32"), (5, 6601, 8, 20, "f32"), (9, 11003, 8, 64, "bf16"),
+                                             (5, 6601, 1, 32, "f16"), (2, 16411, 40, 512, "f32")])
+def test_runs_of_equal_lists(F, B, run, D, dtype):
+    from paper_2211_05239_amd import recd
+    dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    rows = 3000
+    v, w, off = _batch(F * B + run, F * B, rows, run)
+    values, weights, offsets = (torch.from_numpy(a).cuda() for a in (v.astype(np.int64), w, off.astype(np.int64)))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    tables = [torch.empty(rows, D, dtype=dt, device="cuda").normal_(0.0, 0.5, generator=gen) for _ in range(F)]
+    ctx = recd.Context(0)
+    calls = [lambda o, m=m: ctx.kjt_pooled_lookup(tables, B, values, offsets, o, mode=m) for m in (None, "mean", "max")]
+    calls.append(lambda o: ctx.kjt_pooled_lookup_weighted(tables, B, values, weights, offsets, o))
+    for call in calls:
+        got = {}
+        for lists_a_block in (1, 0, 2, 4, 8, 16):
+            ctx.set_option(recd._OPT_INTERNAL_TUNE_SEGSUM, lists_a_block)
+            got[lists_a_block] = torch.full((F, B, D), float("nan"), dtype=dt, device="cuda")
+            call(got[lists_a_block])
+        for lists_a_block, out in got.items():
+            assert torch.equal(out, got[1]), lists_a_block
+    # the last call's sums, in 64 bits: fp32 additions of at most 130 terms and one rounding to the output's type
+    lens = offsets[1:] - offsets[:-1]
+    to = torch.repeat_interleave(torch.arange(F * B, device="cuda"), lens)
+    for f in range(F):
+        a, b = int(offsets[f * B]), int(offsets[(f + 1) * B])
+        terms = tables[f][values[a:b]].double() * weights[a:b, None].double()
+        ref = torch.zeros(B, D, dtype=torch.float64, device="cuda").index_add_(0, to[a:b] - f * B, terms)
+        size = torch.zeros(B, D, dtype=torch.float64, device="cuda").index_add_(0, to[a:b] - f * B, terms.abs())
+        bound = 130 * 2.0 ** -24 * size + {"f32": 0.0, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype] * ref.abs() + 1e-7
+        assert bool(((got[0][f].double() - ref).abs() <= bound).all())
+    ctx.close()
