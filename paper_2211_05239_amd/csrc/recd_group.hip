@@ -14,6 +14,8 @@
 //                    number); side B: the numbering of the distinct rows, the row ids, and the chunks
 //                    of the rows with many entries
 //
+// A side of few entries goes by smaller tiles that need no look-back (sweep_small_tiles).
+//
 // Four launches for tables of up to 2^20 rows, where separate histogram, scan and scatter kernels per
 // digit and side took 24 in two chains; with a dozen microseconds between dependent launches of two
 // busy streams the chains, not their kernels, bounded every backward pass but the very largest.
@@ -37,6 +39,13 @@ constexpr int kMaxPasses = 4;
 constexpr int kQueues = 8;
 constexpr int kMostChunks = 512;
 constexpr int kSumChunks = 16;
+// Small tiles (sweep_small_tiles): a side of at most kSmallTilesMost entries whose features have at most
+// kSmallTilesPer of them each.
+constexpr int kSmallItems = 2;
+constexpr int kSmallTile = kTileThreads * kSmallItems;
+constexpr int kSmallTilesPer = 32;
+constexpr int64_t kSmallTilesMost = 1 << 19;
+static_assert(kTile % kSmallTile == 0 && kSmallTilesPer * kSmallTile < 1 << 16, "counts of other tiles are 16 bits");
 static_assert(kMostChunks + 2 * RECD_MAX_FEATURES + 1 <= RECD_GROUP_ARRIVE, "a counter for every feature and every chunk");
 
 __device__ __forceinline__ uint32_t ld_agent(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -83,6 +92,7 @@ struct SideParams {
     uint32_t *key[2], *pay[2];  // ping-pong buffers; pass p writes the pair p & 1
     int passes, dbits;
     uint32_t *base;             // [F][passes][radix]: where a digit starts inside the feature
+    uint32_t *small_hist;       // [small tiles][radix] counts of the first digit
     uint32_t *chunk_hist;       // [chunks][passes][radix] (features of several chunks only)
     uint32_t *own, *upto;       // [tiles][radix] look-back: a tile's counts, and those of it and all before it
     uint32_t *flag;             // [passes][tiles] 0: nothing yet, 1: own is there, 2: upto is
@@ -101,13 +111,17 @@ struct GroupParams {
     SideParams a, b;
     int tpf, cpf;               // side A: tiles and chunks of a feature
     unsigned a_blocks;          // blocks of the running launch that work on side A
+    unsigned b_tiles;           // bound of side B's tiles
     unsigned list_block0;       // k_group_count: the first block that writes pos_list
     // side B
     uint32_t *pb;               // [F+1] first position of every feature
     uint32_t *queue_start;      // [kQueues+1] first tile of every queue
     uint2 *desc_queue;          // tile (in queue order) -> {feature, tile inside the feature}
-    uint2 *desc_feat;           // tile (in feature order) -> the same
-    uint32_t *tile_total;       // [1]
+    uint4 *desc_feat;           // tile (in feature order) -> {feature, tile inside the feature, the feature's first
+                                // position, its positions}
+    uint4 *desc_small;          // the same of the small tiles
+    uint32_t *tile_total;       // [2] tiles; small tiles, 0: side B goes by tiles
+    int small_a, small_b;       // whether side A goes by small tiles; whether side B may
     uint32_t *pos_list;         // list of every position, or null (then the payload is the position)
     int pay_positions;          // 1: the payload is the position also where pos_list is written
     const float *u_weights;     // weights of the positions, or null; sorted ones go to pay_w and the
@@ -168,7 +182,8 @@ __device__ __forceinline__ void write_bases(const SideParams &s, int f, const ui
 // counts the digits of all passes in LDS and, where the feature is a single chunk, turns the counts into
 // digit starts at once; else the block that arrives last adds up the feature's chunks (of more than 16 the
 // last of every sixteen adds up these first).  The block also
-// clears the look-back flags of its tiles; further blocks write the list of every position.  What is
+// clears the look-back flags of its tiles; further blocks write the list of every position.  Of a side that goes by
+// small tiles a block counts the first digit of one small tile, and the sweep adds up.  What is
 // read is small (8 bytes an entry): the kernel is a few dependent round trips and the LDS atomics of a
 // chunk.
 __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams g)
@@ -193,7 +208,8 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
     const unsigned blk = side_a ? blockIdx.x : blockIdx.x - g.a_blocks;
     int f, c, n_chunks;
     uint32_t begin, end;           // entries of the chunk
-    size_t first_tile, chunk_row;  // in queue order; row of chunk_hist
+    size_t first_tile, chunk_row;  // in queue order; row of chunk_hist or small_hist
+    bool small = g.small_a != 0;   // the chunk is a small tile, and only its first digit is counted
     if (blockIdx.x == 0 && tid < (kMaxPasses + 1) * kQueues) {
         g.a.ticket[tid] = 0;
         g.b.ticket[tid] = 0;
@@ -202,8 +218,9 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         f = (int)(blk / g.cpf);
         c = (int)(blk % g.cpf);
         n_chunks = g.cpf;
-        begin = (uint32_t)(f * g.B + c * s.chunk);
-        end = (uint32_t)(c * s.chunk + s.chunk < g.B ? begin + s.chunk : (f + 1) * g.B);
+        const int64_t chunk = small ? kSmallTile : s.chunk;
+        begin = (uint32_t)(f * g.B + c * chunk);
+        end = (uint32_t)(c * chunk + chunk < g.B ? begin + chunk : (f + 1) * g.B);
         const int q = f % kQueues, per_q = g.F / kQueues, more = g.F % kQueues;
         first_tile = (size_t)(q * per_q + (q < more ? q : more) + f / kQueues) * g.tpf + (size_t)c * (s.chunk / kTile);
         chunk_row = blk;
@@ -216,6 +233,7 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
             const int64_t at = g.u_offsets[g.feat_uoff[i]];
             s_pb[i] = (uint32_t)(at < g.M_cap ? at : g.M_cap);  // never past the caller's capacity
         }
+        small = g.small_b != 0;
         if (tid == 0)
             s_pick[0] = ~0u;
         __syncthreads();
@@ -223,8 +241,15 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         // order (features 0, 8, 16, ..., then 1, 9, ...)
         const int per_q = g.F / kQueues, more = g.F % kQueues;
         const int wide = more * (per_q + 1);  // places in the queues that hold one feature more
+        if (small) {
+            bool beyond = false;
+            for (int x = tid; x < g.F; x += kCountThreads)
+                beyond |= s_pb[x + 1] - s_pb[x] > (uint32_t)(kSmallTilesPer * kSmallTile);
+            small = !__syncthreads_or(beyond);
+        }
+        const int64_t chunk = small ? kSmallTile : s.chunk;
         auto tiles_of = [&](int x) { return (s_pb[x + 1] - s_pb[x] + kTile - 1) / kTile; };
-        auto chunks_of = [&](int x) { return (uint32_t)((s_pb[x + 1] - s_pb[x] + s.chunk - 1) / s.chunk); };
+        auto chunks_of = [&](int x) { return (uint32_t)((s_pb[x + 1] - s_pb[x] + chunk - 1) / chunk); };
         auto queue_of = [&](int i) { return i < wide ? i / (per_q + 1) : more + (i - wide) / per_q; };
         auto in_queue = [&](int i) { return i < wide ? i % (per_q + 1) : (i - wide) % per_q; };
         uint64_t sum = 0, all;
@@ -273,6 +298,7 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
                 g.queue_start[tid] = all_q;  // queues without a feature, and the end
             if (tid == 0) {
                 g.tile_total[0] = all_q;
+                g.tile_total[1] = small ? (uint32_t)all : 0;
                 const int64_t M = g.u_offsets[g.feat_uoff[g.F]];
                 g.too_small_b[0] = M > g.M_cap ? 1 : 0;
                 g.chunk_count[0] = 0;
@@ -284,21 +310,26 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         f = (int)s_pick[0];
         c = (int)s_pick[1];
         n_chunks = (int)s_pick[2];
-        begin = s_pb[f] + (uint32_t)(c * s.chunk);
-        end = (uint32_t)((int64_t)begin + s.chunk < (int64_t)s_pb[f + 1] ? begin + s.chunk : s_pb[f + 1]);
-        first_tile = s_pick[4] + (size_t)c * (s.chunk / kTile);
+        begin = s_pb[f] + (uint32_t)(c * chunk);
+        end = (uint32_t)((int64_t)begin + chunk < (int64_t)s_pb[f + 1] ? begin + chunk : s_pb[f + 1]);
+        const uint32_t k0 = (uint32_t)(c * chunk / kTile);
+        first_tile = s_pick[4] + k0;
         chunk_row = blk;
-        const uint32_t my_tiles = (end - begin + kTile - 1) / kTile, k0 = (uint32_t)(c * (s.chunk / kTile));
+        // tiles that start in the chunk
+        const uint32_t my_tiles = small ? (c * chunk % kTile == 0 ? 1 : 0) : (end - begin + kTile - 1) / kTile;
+        if (small && tid == 0)
+            g.desc_small[blk] = make_uint4(f, c, s_pb[f], s_pb[f + 1] - s_pb[f]);
         for (uint32_t k = tid; k < my_tiles; k += kCountThreads) {
             g.desc_queue[first_tile + k] = make_uint2(f, k0 + k);
-            g.desc_feat[s_pick[3] + k0 + k] = make_uint2(f, k0 + k);
+            g.desc_feat[s_pick[3] + k0 + k] = make_uint4(f, k0 + k, s_pb[f], s_pb[f + 1] - s_pb[f]);
             g.seg_status[s_pick[3] + k0 + k] = 0;
         }
     }
     const uint32_t n = end - begin;
     const int radix = 1 << s.dbits;
     const uint32_t mask = radix - 1;
-    for (int i = tid; i < s.passes * radix; i += kCountThreads)
+    const int passes = small ? 1 : s.passes;  // that are counted
+    for (int i = tid; i < passes * radix; i += kCountThreads)
         s_hist[i] = 0;
     __syncthreads();
     for (uint32_t i0 = tid; i0 < n; i0 += 16 * kCountThreads) {
@@ -324,9 +355,15 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
                 many = above ? (uint32_t)__builtin_ctzll(above) + 1 : (uint32_t)__popcll(live) - ln;
             }
             if (count)
-                for (int p = 0; p < s.passes; p++)
+                for (int p = 0; p < passes; p++)
                     atomicAdd(&s_hist[p * radix + ((key[u] >> (p * s.dbits)) & mask)], many);
         }
+    }
+    if (small) {  // the sweep adds up the counts of the feature's small tiles itself
+        __syncthreads();
+        for (int i = tid; i < radix; i += kCountThreads)
+            s.small_hist[chunk_row * radix + i] = s_hist[i];
+        return;
     }
     // look-back flags of the chunk's tiles
     for (int i = tid; i < (int)((n + kTile - 1) / kTile) * s.passes; i += kCountThreads)
@@ -410,18 +447,211 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
 // digit order, so that a digit's entries (four on average with 10-bit digits) leave as one short run
 // instead of as scattered words.  Bound by the latency of its chain (ticket, keys, ranks, look-back,
 // stores); 40 KB of LDS keep four tiles on a CU.
+union SweepShared {
+    uint16_t run[kWaves][kMaxRadix];       // per wave: entries seen so far per digit
+    struct { uint32_t key[kTile], pay[kTile]; } out;
+    struct {
+        uint16_t run[kWaves][kMaxRadix];
+        uint32_t others[kMaxRadix];        // entries of a digit in the feature's tiles before this one (low half) and
+        uint32_t key[kSmallTile], pay[kSmallTile];  // after it
+    } small;
+};
+
+// The rank of an entry of digit d among its wave's entries of that digit so far, this round's included up to the lane;
+// run: the wave's counts.
+__device__ __forceinline__ uint32_t wave_rank(uint16_t *run, uint32_t d, bool valid, int dbits)
+{
+    const uint64_t all = __ballot(valid);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);  // lanes with my digit
+#pragma unroll
+    for (int bit = 0; bit < kMaxBits; bit++) {
+        if (bit < dbits) {  // uniform
+            const int one = (int)(d << (31 - bit)) >> 31;  // all ones where the bit is set
+            const uint64_t bal = __ballot(one != 0);
+            lo &= ~((uint32_t)bal ^ (uint32_t)one);
+            hi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)one);
+        }
+    }
+    const uint32_t in_round = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+    const uint32_t of_digit = (uint32_t)(__popc(lo) + __popc(hi));
+    // entries of this digit in the wave's earlier rounds; the first lane of each digit then adds this
+    // round's (same wave: the read is complete before the write is issued)
+    const uint32_t before = valid ? run[d] : 0;
+    __builtin_amdgcn_wave_barrier();
+    if (valid && in_round == 0)
+        run[d] = (uint16_t)(before + of_digit);
+    __builtin_amdgcn_wave_barrier();
+    return before + in_round;
+}
+
+// One digit of a side of few entries.  Tiles of 4096 would leave most of the chip idle, and their ranks (a ballot per
+// bit and 64 entries) and their look-back are then what a sweep takes; a tile of 1024 finds out for itself what the
+// others of its feature hold, of the first digit from their counts, of a later one by counting their keys again, so
+// that no tile waits for another.  The feature's digits start where the sum of all its tiles puts them.  0.19 M ids in
+// 16 features: count 17.1 -> 11.6 us (its blocks no longer meet), a sweep 13.2 -> 9.8, weighted step 150 -> 137; tiles of
+// 4096 without look-back: sweep 12.8.  With more tiles (and more entries a feature to count again) the chip is full either
+// way: side A of 1.05 M rows in tiles of 4096 without look-back took the step from 797 to 818 us.
+__device__ __forceinline__ void sweep_small_tiles(const GroupParams &g, const SideParams &s, bool side_a, uint32_t tile,
+                                                  int pass, SweepShared &sh, uint32_t *s_from, uint16_t *s_loc)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    uint4 dsc;
+    if (side_a) {
+        const uint32_t per = (uint32_t)((g.B + kSmallTile - 1) / kSmallTile);
+        dsc = make_uint4(tile / per, tile % per, (uint32_t)(tile / per * g.B), (uint32_t)g.B);
+    } else {
+        dsc = g.desc_small[tile];
+    }
+    const uint32_t k = dsc.y, f_begin = dsc.z, f_len = dsc.w, at0 = k * kSmallTile;
+    const uint32_t n = f_len - at0 < (uint32_t)kSmallTile ? f_len - at0 : (uint32_t)kSmallTile;
+    const uint32_t tiles_f = (f_len + kSmallTile - 1) / kSmallTile;
+    const uint32_t *kin = s.key[(pass + 1) & 1] + f_begin, *pin = s.pay[(pass + 1) & 1] + f_begin;
+    uint32_t *kout = s.key[pass & 1], *pout = s.pay[pass & 1];
+    const int radix = 1 << s.dbits, shift = pass * s.dbits, d0 = 2 * tid;  // d0, d0 + 1: the thread's digits
+    const uint32_t mask = radix - 1, i0 = w * (64 * kSmallItems) + lane;
+    uint32_t key[kSmallItems], pay[kSmallItems], rank[kSmallItems];
+#pragma unroll
+    for (int u = 0; u < kSmallItems; u++) {
+        const uint32_t i = at0 + i0 + u * 64;
+        key[u] = pay[u] = 0;
+        if (i0 + u * 64 < n) {
+            if (pass > 0) {
+                key[u] = kin[i];
+                pay[u] = pin[i];
+            } else if (side_a) {
+                key[u] = (uint32_t)g.inverse[f_begin + i];
+                pay[u] = f_begin + i;
+            } else {
+                key[u] = (uint32_t)g.u_values[f_begin + i];
+                pay[u] = g.pay_positions ? f_begin + i : g.pos_list[f_begin + i];
+            }
+        }
+    }
+    uint32_t before[2] = {0, 0}, after[2] = {0, 0};
+    constexpr int kFly = 8;
+    if (pass == 0 && d0 < radix) {
+        const uint32_t *rows = s.small_hist + (size_t)(tile - k) * radix + d0;
+        for (uint32_t j0 = 0; j0 < tiles_f; j0 += kFly) {
+            uint2 x[kFly];
+#pragma unroll
+            for (int u = 0; u < kFly; u++) {
+                const uint32_t j = j0 + u;
+                x[u] = j < tiles_f && j != k ? *reinterpret_cast<const uint2 *>(rows + (size_t)j * radix) : make_uint2(0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < kFly; u++) {
+                before[0] += j0 + u < k ? x[u].x : 0;
+                before[1] += j0 + u < k ? x[u].y : 0;
+                after[0] += j0 + u < k ? 0 : x[u].x;
+                after[1] += j0 + u < k ? 0 : x[u].y;
+            }
+        }
+    }
+    for (int i = tid; i < (int)(offsetof(SweepShared, small.key) / sizeof(uint32_t)); i += kTileThreads)
+        reinterpret_cast<uint32_t *>(&sh)[i] = 0;
+    __syncthreads();
+    if (pass > 0) {
+        for (uint32_t j0 = 0; j0 < f_len; j0 += kFly * kTileThreads) {
+            uint32_t x[kFly];
+#pragma unroll
+            for (int u = 0; u < kFly; u++) {
+                const uint32_t i = j0 + u * kTileThreads + tid;
+                x[u] = i < f_len ? kin[i] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kFly; u++) {
+                // The lanes that hold the first lane's digit are counted by one atomic: skewed ids and the rows of a
+                // session share their high digits, and a wave's atomics on one address queue.
+                const uint32_t i = j0 + u * kTileThreads + tid;
+                const bool on = i < f_len && i - at0 >= n;
+                const uint32_t d = on ? (x[u] >> shift) & mask : ~0u, one = i < at0 ? 1u : 1u << 16;
+                const uint64_t same = __ballot(d == (uint32_t)__builtin_amdgcn_readfirstlane(d));
+                if (on && !((same >> lane) & 1))
+                    atomicAdd(&sh.small.others[d], one);
+                else if (on && lane == 0)
+                    atomicAdd(&sh.small.others[d], one * (uint32_t)__popcll(same));
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kSmallItems; u++)
+        rank[u] = wave_rank(sh.small.run[w], (key[u] >> shift) & mask, i0 + u * 64 < n, s.dbits);
+    __syncthreads();
+    uint32_t cnt[2] = {0, 0}, of_digit[2];
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        if (d0 < radix) {
+#pragma unroll
+            for (int ww = 0; ww < kWaves; ww++) {
+                const uint32_t x = sh.small.run[ww][d0 + e];
+                sh.small.run[ww][d0 + e] = (uint16_t)cnt[e];
+                cnt[e] += x;
+            }
+            if (pass > 0) {
+                before[e] = sh.small.others[d0 + e] & 0xffff;
+                after[e] = sh.small.others[d0 + e] >> 16;
+            }
+        }
+        of_digit[e] = before[e] + cnt[e] + after[e];
+    }
+    uint64_t total;  // low half: where a digit starts in the tile, high half: in the feature
+    const uint64_t starts = block_excl<uint64_t, kWaves>(((uint64_t)(of_digit[0] + of_digit[1]) << 32) | (cnt[0] + cnt[1]),
+                                                         total);
+#pragma unroll
+    for (int e = 0; e < 2; e++)
+        if (d0 < radix) {
+            const uint32_t at = (uint32_t)starts + (e ? cnt[0] : 0);
+            s_loc[d0 + e] = (uint16_t)at;
+            s_from[d0 + e] = f_begin + (uint32_t)(starts >> 32) + (e ? of_digit[0] : 0) + before[e] - at;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kSmallItems; u++)
+        if (i0 + u * 64 < n) {
+            const uint32_t d = (key[u] >> shift) & mask, to = rank[u] + s_loc[d] + sh.small.run[w][d];
+            sh.small.key[to] = key[u];
+            sh.small.pay[to] = pay[u];
+        }
+    __syncthreads();
+    const bool resolve = !side_a && (g.u_weights || g.pay_pos) && pass == s.passes - 1;
+#pragma unroll
+    for (int u = 0; u < kSmallItems; u++) {
+        const uint32_t i = tid + u * kTileThreads;
+        if (i < n) {
+            const uint32_t kk = sh.small.key[i], pp = sh.small.pay[i];
+            const uint32_t dst = s_from[(kk >> shift) & mask] + i;
+            kout[dst] = kk;
+            if (resolve) {  // the entry's source row and its weight or position, both in sorted order
+                pout[dst] = g.pos_list[pp];
+                if (g.u_weights)
+                    g.pay_w[dst] = g.u_weights[pp];
+                else
+                    g.pay_pos[dst] = pp;
+            } else {
+                pout[dst] = pp;
+            }
+        }
+    }
+}
+
 __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams g, int pass)
 {
-    __shared__ union {
-        uint16_t run[kWaves][kMaxRadix];       // per wave: entries seen so far per digit
-        struct { uint32_t key[kTile], pay[kTile]; } out;
-    } sh;
+    __shared__ SweepShared sh;
     __shared__ uint32_t s_from[kMaxRadix];     // where the tile's entries of a digit go, less their place in LDS
     __shared__ uint16_t s_loc[kMaxRadix];      // where they start in LDS
     __shared__ uint32_t s_tile, s_window;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const bool side_a = blockIdx.x < g.a_blocks;
     const SideParams &s = side_a ? g.a : g.b;
+    const unsigned blk = side_a ? blockIdx.x : blockIdx.x - g.a_blocks;
+    const uint32_t small_tiles = side_a ? (g.small_a ? g.a_blocks : 0) : g.tile_total[1];
+    if (small_tiles) {
+        if (blk < small_tiles)
+            sweep_small_tiles(g, s, side_a, blk, pass, sh, s_from, s_loc);
+        return;
+    }
+    if (!side_a && blk >= g.b_tiles)
+        return;  // whole block: there for small tiles
     // ---- a tile: from the block's own queue while it has any, then from the others ------------------
     if (tid == 0) {
         uint32_t tile = ~0u;
@@ -500,31 +730,8 @@ __global__ __launch_bounds__(kTileThreads) void k_group_sweep(const GroupParams 
         }
     }
 #pragma unroll
-    for (int u = 0; u < kItems; u++) {
-        const bool valid = wbase + u * 64 < n;
-        const uint32_t d = (key[u] >> shift) & mask;
-        const uint64_t all = __ballot(valid);
-        uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);  // lanes with my digit
-#pragma unroll
-        for (int bit = 0; bit < kMaxBits; bit++) {
-            if (bit < s.dbits) {  // uniform
-                const int one = (int)(d << (31 - bit)) >> 31;  // all ones where the bit is set
-                const uint64_t bal = __ballot(one != 0);
-                lo &= ~((uint32_t)bal ^ (uint32_t)one);
-                hi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)one);
-            }
-        }
-        const uint32_t in_round = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
-        const uint32_t of_digit = (uint32_t)(__popc(lo) + __popc(hi));
-        // entries of this digit in the wave's earlier rounds; the first lane of each digit then adds this
-        // round's (same wave: the read is complete before the write is issued)
-        const uint32_t before = valid ? sh.run[w][d] : 0;
-        __builtin_amdgcn_wave_barrier();
-        if (valid && in_round == 0)
-            sh.run[w][d] = (uint16_t)(before + of_digit);
-        __builtin_amdgcn_wave_barrier();
-        rank[u] = before + in_round;
-    }
+    for (int u = 0; u < kItems; u++)
+        rank[u] = wave_rank(sh.run[w], (key[u] >> shift) & mask, wbase + u * 64 < n, s.dbits);
     __syncthreads();
     // ---- digits d = 2 * tid, 2 * tid + 1: prefix over the waves, count of the tile --------------------------
     uint32_t cnt[2] = {0, 0};
@@ -707,9 +914,9 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
         }
         return;
     }
-    const uint2 dsc = g.desc_feat[tile];
+    const uint4 dsc = g.desc_feat[tile];
     const uint32_t f = dsc.x, k = dsc.y;
-    const uint32_t f_end = g.pb[f + 1], begin = g.pb[f] + k * kTile;
+    const uint32_t f_end = dsc.z + dsc.w, begin = dsc.z + k * kTile;
     const uint32_t n = f_end - begin < (uint32_t)kTile ? f_end - begin : (uint32_t)kTile;
     const uint32_t *ks = g.b.key[(g.b.passes - 1) & 1] + begin;
     // a wave owns 512 consecutive entries, 64 a round: heads are ballots, their numbers popcounts and the
@@ -1190,9 +1397,15 @@ RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap)
     w.pb = c.take<uint32_t>(F + 1);
     w.queue_start = c.take<uint32_t>(kQueues + 1);
     w.desc_queue = c.take<uint2>(tiles_b);
-    w.desc_feat = c.take<uint2>(tiles_b);
+    w.desc_feat = c.take<uint4>(tiles_b);
+    // room for the small tiles of every batch that has them and is no larger than this one
+    const int64_t most_a = n_lists < kSmallTilesMost ? n_lists : kSmallTilesMost;
+    const int64_t most_b = M_cap < kSmallTilesMost ? M_cap : kSmallTilesMost;
+    w.a.small_hist = c.take<uint32_t>((size_t)(most_a / kSmallTile + F + 1) * kMaxRadix);
+    w.b.small_hist = c.take<uint32_t>((size_t)(most_b / kSmallTile + F + 1) * kMaxRadix);
+    w.desc_small = c.take<uint4>(most_b / kSmallTile + F + 1);
     w.seg_status = c.take<uint64_t>(tiles_b);
-    w.tile_total = c.take<uint32_t>(1);
+    w.tile_total = c.take<uint32_t>(2);
     return w;
 }
 
@@ -1239,6 +1452,7 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
         digits_for(bits, &s.passes, &s.dbits);
         s.base = v.base;
         s.chunk_hist = v.chunk_hist;
+        s.small_hist = v.small_hist;
         s.own = v.own;
         s.upto = v.upto;
         s.flag = v.flag;
@@ -1250,11 +1464,15 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     side(g.a, w.a, slot_bits(a.B, a.U_cap), g.n_lists, ctx->group_arrive);
     side(g.b, w.b, bits_for((uint64_t)(a.max_rows > 1 ? a.max_rows - 1 : 1)), a.M_cap, ctx->group_arrive + RECD_GROUP_ARRIVE);
     g.tpf = (int)((a.B + kTile - 1) / kTile);
-    g.cpf = (int)((a.B + g.a.chunk - 1) / g.a.chunk);
+    g.small_a = g.n_lists <= kSmallTilesMost && a.B <= kSmallTilesPer * kSmallTile;
+    g.small_b = a.M_cap <= kSmallTilesMost;
+    const int64_t chunk_a = g.small_a ? kSmallTile : g.a.chunk, chunk_b = g.small_b ? kSmallTile : g.b.chunk;
+    g.cpf = (int)((a.B + chunk_a - 1) / chunk_a);
     g.pb = w.pb;
     g.queue_start = w.queue_start;
     g.desc_queue = w.desc_queue;
     g.desc_feat = w.desc_feat;
+    g.desc_small = w.desc_small;
     g.tile_total = w.tile_total;
     g.pos_list = a.pos_list;
     g.pay_positions = a.pay_positions;
@@ -1286,10 +1504,12 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
         RECD_HIP(ctx, hipGetLastError());
         return RECD_OK;
     }
-    const unsigned a_tiles = (unsigned)((g.a.tiles_cap + kQueues - 1) / kQueues * kQueues);
-    const unsigned b_tiles = (unsigned)(a.M_cap / kTile + a.F + 1);
+    const unsigned a_tiles = g.small_a ? (unsigned)(a.F * g.cpf)
+                                       : (unsigned)((g.a.tiles_cap + kQueues - 1) / kQueues * kQueues);
+    g.b_tiles = (unsigned)(a.M_cap / kTile + a.F + 1);
+    const unsigned b_blocks = g.small_b ? (unsigned)(a.M_cap / kSmallTile + a.F + 1) : g.b_tiles;
     g.a_blocks = (unsigned)((int64_t)a.F * g.cpf);
-    g.list_block0 = g.a_blocks + (unsigned)(a.M_cap / g.b.chunk + a.F + 1);
+    g.list_block0 = g.a_blocks + (unsigned)(a.M_cap / chunk_b + a.F + 1);
     int64_t list_blocks = ((a.U_cap < g.n_lists ? a.U_cap : g.n_lists) + kCountThreads / 16 - 1) / (kCountThreads / 16);
     if (list_blocks > (int64_t)ctx->num_cu * 8)
         list_blocks = (int64_t)ctx->num_cu * 8;
@@ -1300,11 +1520,11 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     const int passes = g.a.passes > g.b.passes ? g.a.passes : g.b.passes;
     for (int p = 0; p < passes; p++) {
         g.a_blocks = p < g.a.passes ? a_tiles : 0;
-        const unsigned nb = g.a_blocks + (p < g.b.passes ? b_tiles : 0);
+        const unsigned nb = g.a_blocks + (p < g.b.passes ? b_blocks : 0);
         hipLaunchKernelGGL(k_group_sweep, dim3(nb), dim3(kTileThreads), 0, st, g, p);
     }
     g.a_blocks = (unsigned)((g.n_lists + kTile - 1) / kTile);
-    hipLaunchKernelGGL(k_group_segments, dim3(g.a_blocks + b_tiles), dim3(kTileThreads), 0, st, g);
+    hipLaunchKernelGGL(k_group_segments, dim3(g.a_blocks + g.b_tiles), dim3(kTileThreads), 0, st, g);
     RECD_HIP(ctx, hipGetLastError());
     return RECD_OK;
 }

@@ -228,10 +228,11 @@ struct RecdGroupWs {
         uint32_t *key[2], *pay[2];
         int64_t *too_small;      // whether the caller's bound was too small (side A: RECD_GROUP_*)
         int64_t tiles_cap;
-        uint32_t *base, *chunk_hist, *ticket, *own, *upto, *flag;
+        uint32_t *base, *chunk_hist, *small_hist, *ticket, *own, *upto, *flag;
     } a, b;
     uint32_t *pb, *queue_start, *tile_total;
-    uint2 *desc_queue, *desc_feat;
+    uint2 *desc_queue;
+    uint4 *desc_feat, *desc_small;
     uint64_t *seg_status;
 };
 // A chunk of a segment with many entries: entries [start, end) of segment seg, whose n chunks are listed

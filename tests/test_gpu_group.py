@@ -62,6 +62,13 @@ CASES = [
     ([8000, 150], 300, 2, 5000, True),       # one launch, a list of thousands of ids
     ([23 * TILE + 5], 18 * TILE + 7, 3000, 5000, True),   # counted in chunks of which more than sixteen are added up
     ([40000, 0, 20000], 5000, 1000, 1, False),   # one row: segments of 157 chunks cut down to 64, and of 79
+    # small tiles (1024 entries, up to 32 a feature): their edges on both sides, the most of them, one entry more
+    ([1023, 1024, 1025, 0, 2047, 2049, 5000, 1], 1025, 1025, 1 << 20, True),
+    ([32768, 1, 1024, 0, 3073], 32768, 2000, (1 << 20) + 1, True),
+    ([32769, 2000], 32769, 2000, 1 << 20, True),
+    ([30000, 0, 900], 1024, 300, 200, True),
+    ([20164] * 26, 700, 650, 3000, True),    # just below the most ids that a side in small tiles may have
+    ([20165] * 26, 700, 650, 3000, True),    # and just beyond
 ]
 
 
