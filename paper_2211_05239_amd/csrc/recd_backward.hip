@@ -1002,7 +1002,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         ga.pay_pos = reinterpret_cast<uint32_t *>(w.pay_w);  // the sorted positions take the place of weights
     ga.u_weights = u_weights;
     ga.pay_w = w.pay_w;
-    RECD_TRY(recd_group(ctx, st, w.group, ga));
+    RECD_TRY(recd_group(ctx, st, false, w.group, ga));
     const uint32_t *ps_a = recd_group_rows(w.group, F, B, U_cap, M_cap, max_rows);
     const uint32_t *ps_b = recd_group_positions(w.group, F, B, M_cap, max_rows);
     // ---- step A: sum grad_out rows into g_u (or, for sequences, into grad_emb) ---------------------------
@@ -1154,10 +1154,9 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
     pl.feat_roff = feat_roff;
     pl.ws = ctx->ws;
     pl.empty = n_lists == 0 || M_cap == 0;
-    // A small batch's grouping is one short kernel: on the stream itself it costs less than the two events
-    // that would take it to the side stream and back.
+    // A short grouping costs less on the stream itself than the events that would take it to the side stream and back.
     hipStream_t st = ctx->stream;
-    const bool own_stream = pl.empty || recd_group_is_small(F, B, M_cap, max_rows);
+    const bool own_stream = pl.empty || recd_group_is_small(F, B, M_cap, max_rows) || recd_group_is_short(F, B, M_cap);
     hipStream_t side = own_stream ? st : ctx->side_stream;
     // Where the side stream may start: at the end of the build that produced this IKJT if it is the
     // context's most recent one, else at the main stream's current position.
@@ -1165,9 +1164,12 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
     if (own_stream)
         from = nullptr;
     else if (ctx->build_valid && ws_idle_since_build && ctx->built_inverse == inverse &&
-        ctx->built_u_values == u_values && n_lists > 0)
-        from = ctx->ev_built;
-    else
+        ctx->built_u_values == u_values && n_lists > 0) {
+        ctx->ev_built_wanted = ctx->ev_built_used = true;
+        if (ctx->ev_built_recorded)
+            from = ctx->ev_built;
+    }
+    if (from == ctx->ev_fork)
         RECD_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
     if (from)
         RECD_HIP(ctx, hipStreamWaitEvent(side, from, 0));
@@ -1176,7 +1178,7 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
                                       touched_rows, feat_roff);
         ga.run_index = run_index;
         ga.runs_cap = runs_cap > n_lists || runs_cap == 0 ? n_lists : runs_cap;
-        RECD_TRY(recd_group(ctx, side, w.group, ga));
+        RECD_TRY(recd_group(ctx, side, !own_stream, w.group, ga));
         pl.ps_a = recd_group_rows(w.group, F, B, U_cap, M_cap, max_rows);
         pl.ps_b = recd_group_positions(w.group, F, B, M_cap, max_rows);
     }

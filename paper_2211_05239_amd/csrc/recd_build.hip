@@ -1554,9 +1554,7 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
         ctx->ws_used_since_build = false;
         ctx->build_valid = true;
         ctx->plan.valid = false;
-        RECD_HIP(ctx, hipEventRecord(ctx->ev_built, st));
-        ctx->built_inverse = inverse;
-        ctx->built_u_values = u_values;
+        RECD_TRY(recd_mark_build(ctx, F, B, N, inverse, u_values));
         if (host_U_M) {
             ctx->build_published = false;
             RECD_TRY(recd_fetch_scalars(ctx, ctx->build_counts_dev, 2, host_U_M));
@@ -1635,9 +1633,7 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
     RECD_HIP(ctx, hipGetLastError());
     ctx->build_valid = true;
     ctx->plan.valid = false;  // the builder reused the workspace a plan would live in
-    RECD_HIP(ctx, hipEventRecord(ctx->ev_built, st));
-    ctx->built_inverse = inverse;
-    ctx->built_u_values = u_values;
+    RECD_TRY(recd_mark_build(ctx, F, B, N, inverse, u_values));
     if (host_U_M) {
         ctx->build_published = false;  // fetched here; recd_last_ikjt_counts reads the device array
         RECD_TRY(recd_fetch_scalars(ctx, counts, 2, host_U_M));

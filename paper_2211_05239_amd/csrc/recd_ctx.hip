@@ -30,6 +30,21 @@ recd_status recd_check_rows(recd_ctx *ctx, int F, const int64_t *rows)
     return RECD_OK;
 }
 
+recd_status recd_mark_build(recd_ctx *ctx, int F, int64_t B, int64_t N, const int32_t *inverse, const int64_t *u_values)
+{
+    if (ctx->ev_built_recorded && !ctx->ev_built_used)
+        ctx->ev_built_wanted = false;  // until a plan asks for one again
+    ctx->ev_built_recorded = false;
+    ctx->ev_built_used = false;
+    ctx->built_inverse = inverse;
+    ctx->built_u_values = u_values;
+    if (ctx->ev_built_wanted && !recd_group_is_short(F, B, N)) {
+        RECD_HIP(ctx, hipEventRecord(ctx->ev_built, ctx->stream));
+        ctx->ev_built_recorded = true;
+    }
+    return RECD_OK;
+}
+
 recd_status recd_reserve(recd_ctx *ctx, size_t bytes)
 {
     // Every call that is about to use the workspace comes through here first.  A plan that was never

@@ -41,6 +41,9 @@ struct recd_ctx {
     // side stream from the end of the last build on, next to the forward calls.
     hipEvent_t ev_built = nullptr;  // end of the most recent plain / weighted build
     hipEvent_t ev_plan = nullptr;   // end of the plan
+    // ev_built is recorded only where a plan may start at it, since a record costs the kernel behind it 3 to 6 us: not for
+    // batches whose plan goes in line, nor once a build's event was not used (recd_mark_build).
+    bool ev_built_recorded = false, ev_built_used = false, ev_built_wanted = true;
     const void *built_inverse = nullptr, *built_u_values = nullptr;  // outputs of that build
     // A call that uses the workspace has been enqueued on the context's stream since that build (set
     // by recd_reserve, cleared by the builder): a plan must then start at the stream's current
@@ -133,6 +136,8 @@ recd_status recd_check_rows(recd_ctx *ctx, int F, const int64_t *rows);
 // After a builder wrote {U, M} into ctx->build_counts_dev: publish them to the host asynchronously.
 recd_status recd_publish_build_counts(recd_ctx *ctx);
 recd_status recd_reserve(recd_ctx *ctx, size_t bytes);
+// Behind the last kernel of a plain or weighted build of N ids: where a plan for these outputs may start.
+recd_status recd_mark_build(recd_ctx *ctx, int F, int64_t B, int64_t N, const int32_t *inverse, const int64_t *u_values);
 // Looks up the current device's copy of the static scratch array (with `device` current).
 recd_status recd_static_scratch(recd_ctx *ctx, int device);
 
@@ -265,7 +270,12 @@ struct RecdGroupArgs {
 // Side A's too_small word: which of the caller's bounds were too small.
 enum { RECD_GROUP_RUNS = 1, RECD_GROUP_LISTS = 2 };
 RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap);
-recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, const RecdGroupArgs &a);
+// beside: the caller's kernels run next to it on another stream.
+recd_status recd_group(recd_ctx *ctx, hipStream_t st, bool beside, const RecdGroupWs &w, const RecdGroupArgs &a);
+// Whether a plan is so short that it goes in line: the events that take it to the side stream and back cost the host some
+// 45 us and the device what the forward calls would hide of it (step of 65 K lists and 0.19 M ids: 150 us either way,
+// of which the host waits 42 us with the plan beside, 95 in line).
+bool recd_group_is_short(int F, int64_t B, int64_t M_cap);
 // Whether both sides are grouped by one launch.
 bool recd_group_is_small(int F, int64_t B, int64_t M_cap, int64_t max_rows);
 // The payload buffers that hold the result for these sizes.
