@@ -36,10 +36,10 @@ constexpr int kBlock = 256;
 // waves resident (unique lookup 0.124 ms against 0.133, KJT lookup 0.99 against 1.16).  The
 // backward's sum keeps four waves: its long segments want the whole block.
 template <int SITE> struct SegBlock {
-    static constexpr int threads = (SITE == 0 || SITE == 1 || SITE == 4) ? 64 : 256;
+    static constexpr int threads = (SITE == 0 || SITE == 1 || SITE == 2 || SITE == 4) ? 64 : 256;
 };
 constexpr int kMaxLB = 16;     // lists per block item (upper bound)
-constexpr int64_t kSampledLists = 32768;  // KJT lists from which on a sample decides how many a wave takes
+constexpr int64_t kSampledLists = 32768;  // KJT lists from which on equal neighbours may share their sum
 constexpr int kChunk = 64;     // ids per chunk: a wave loads a chunk's ids with one instruction
 
 __device__ __forceinline__ int64_t uniform64(int64_t v)
@@ -147,7 +147,10 @@ template <int OT, int N, bool NT> __device__ __forceinline__ void store_row_piec
 // SITE_UNIQUE_EXPAND: the unique lookup whose waves also store a finished row to the output rows of
 // the run of adjacent samples that starts at the list's first row (Sec. 5: lookup on the unique
 // lists, then the index select back to the batch - here for the samples a session put side by side).
-enum { SITE_UNIQUE = 0, SITE_KJT = 1, SITE_GRAD_STREAM = 3, SITE_UNIQUE_EXPAND = 4 };
+// SITE_KJT_RUNS: the KJT lookup whose waves share the sum of equal neighbours.  In small batches the comparison is only in
+// the way (14.8 K lists of short rows: 14.8 us without it, 16.6 with it).
+enum { SITE_UNIQUE = 0, SITE_KJT = 1, SITE_KJT_RUNS = 2, SITE_GRAD_STREAM = 3, SITE_UNIQUE_EXPAND = 4 };
+constexpr bool is_kjt(int site) { return site == SITE_KJT || site == SITE_KJT_RUNS; }
 
 struct SegSumParams {
     TablePtrs tables;
@@ -162,7 +165,7 @@ struct SegSumParams {
     int vecs_per_row;  // D / elements per 16-byte vector
     int nq;            // 8: XCD-aware queues (forward sites only); 1: one flat queue
     int lb;            // lists per block item, <= kMaxLB; 0 (forward sites): chosen by the number of lists
-    int deal_log;      // SITE_KJT: how many lists are dealt to a queue at a time (recd_deal_log_kjt)
+    int deal_log;      // the KJT lookup: how many lists are dealt to a queue at a time (recd_deal_log_kjt)
     // optional: list l spans offsets[l] .. offsets[l] + lens[l] (windows of a partial IKJT)
     const int64_t *lens;
     // optional (SITE_GRAD_STREAM only): the finished row of list l is divided by
@@ -265,7 +268,7 @@ template <int LPR, int VPL, int TT, int OT, int SITE, int MODE> constexpr int se
 #ifndef RECD_BASE_WAVES
 #define RECD_BASE_WAVES 7
 #endif
-    int w = MODE == POOL_WSUM ? (SITE == SITE_KJT ? 6 : 5) : RECD_BASE_WAVES;
+    int w = MODE == POOL_WSUM ? (is_kjt(SITE) ? 6 : 5) : RECD_BASE_WAVES;
     if (LPR == 8)
         w -= 2;
     else if (TT != RECD_F32 && SITE == SITE_UNIQUE_EXPAND)
@@ -278,7 +281,7 @@ template <int LPR, int VPL, int TT, int OT, int SITE, int MODE> constexpr int se
 // 2 KiB rows 57 -> 174 us, 0.13 M of 4 KiB rows 36 -> 63, 4.2 M of 128 bytes 99 -> 120).
 template <int LPR, int VPL, int TT, int OT, int SITE, int MODE> constexpr int segsum_most_waves()
 {
-    return SITE == SITE_KJT && segsum_waves<LPR, VPL, TT, OT, SITE, MODE>() == 7 ? 7 : 8;
+    return is_kjt(SITE) && segsum_waves<LPR, VPL, TT, OT, SITE, MODE>() == 7 ? 7 : 8;
 }
 static_assert(segsum_most_waves<64, 2, RECD_F32, RECD_F32, SITE_KJT, POOL_SUM>() == 8, "rows above 1 KiB: no limit");
 static_assert(segsum_most_waves<8, 1, RECD_F32, RECD_F32, SITE_KJT, POOL_WSUM>() == 8, "short rows, weights: no limit");
@@ -291,7 +294,7 @@ void k_segsum(const SegSumParams p)
 {
     constexpr int kSegBlock = SegBlock<SITE>::threads;
     constexpr int kWaves = kSegBlock / 64;
-    constexpr bool NT = SITE == SITE_KJT;  // streaming output
+    constexpr bool NT = is_kjt(SITE);  // streaming output
     constexpr int EPV = Elem<TT>::per_vec;
     constexpr int NACC = EPV * VPL;
     constexpr int ROWF = LPR * NACC;                      // floats of one (padded) row
@@ -475,18 +478,8 @@ void k_segsum(const SegSumParams p)
         const int64_t all = end_all - first;
         // lists per block: as many as keep the number of blocks in bounds (measured at 61 K unique lists
         // and at 1.05 M KJT lists: 1 and 4), by the true number of lists
-        int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
-        if (SITE == SITE_KJT && lb == 0 && all >= kSampledLists) {
-            // Where most neighbouring lists are as long as each other (60 pairs in four places: every wave sees the
-            // same ones) they are probably equal, and a wave that has more of them sums fewer.  Elsewhere more lists a
-            // wave only spread the waves over more tables: 8192 x 32 lists of 64 ids, by 1 / 2 / 4 / 8 lists, us:
-            // sessions of 8 556 / 407 / 340 / 341, of 2 920 / 882 / 928 / 962, no sessions 1441 / 1422 / 1488 / 1563.
-            const int64_t at = first + (all >> 2) * (lane >> 4) + (all >> 3) + (lane & 15);
-            const int64_t len = p.offsets[at + 1] - p.offsets[at], left = __shfl_up(len, 1);
-            if (__popcll(__ballot(len == left && (lane & 15) != 0)) >= 40)
-                lpb = all >= (96 << 10) ? 8 : 4;
-        }
-        const int deal_log = SITE == SITE_KJT ? p.deal_log : recd_deal_log(all, kNQ, 31 - __builtin_clz(lpb));
+        const int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
+        const int deal_log = is_kjt(SITE) ? p.deal_log : recd_deal_log(all, kNQ, 31 - __builtin_clz(lpb));
         for (int64_t t = item0 * lpb;; t += item_stride * lpb) {
             const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ, deal_log));
             if (l0 >= end_all)
@@ -512,7 +505,7 @@ void k_segsum(const SegSumParams p)
                 }
                 __syncthreads();  // a block of one wave: orders the LDS accesses, nobody waits
             }
-            if constexpr (SITE == SITE_KJT) {
+            if constexpr (SITE == SITE_KJT_RUNS) {
                 // Neighbouring lists of a session-ordered batch are mostly the same list.  The wave compares each of
                 // its lists with the one before it, all at once with 64 / lpb lanes to a list, sums the first of every
                 // run of equal ones and stores its row for the whole run: the same ids in the same order give the same
@@ -669,6 +662,18 @@ void k_segsum(const SegSumParams p)
             finish_row(t0 + j, len, acc[0]);
         }
     }
+}
+
+// Whether most neighbouring lists of offsets[0 .. n] are as long as each other (60 pairs in four places; n >= 64), and so
+// probably equal: 1 or 0 to a word that the host reads without waiting.
+__global__ __launch_bounds__(64) void k_sample_sessions(const int64_t *offsets, int64_t n, int64_t *sessions)
+{
+    const int lane = threadIdx.x;
+    const int64_t at = (n >> 2) * (lane >> 4) + (n >> 3) + (lane & 15);
+    const int64_t len = offsets[at + 1] - offsets[at], left = __shfl_up(len, 1);
+    const int equal = (int)__popcll(__ballot(len == left && (lane & 15) != 0));
+    if (lane == 0)
+        __hip_atomic_store(sessions, (int64_t)(equal >= 40), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 template <int TT, int OT, typename IdxT, int SITE, int MODE = POOL_SUM>
@@ -1031,9 +1036,20 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     p.lb = one_wave ? 0 : lb;
     if (ctx->tune_lb > 0)
         p.lb = lb = ctx->tune_lb;
-    // (the KJT lookup may take up to 8 lists a block where it samples them)
-    const bool sampled = a.site == RECD_SITE_KJT && ctx->tune_lb == 0 && n >= kSampledLists;
-    p.deal_log = recd_deal_log_kjt(n, a.F, kNQ, sampled ? 3 : 31 - __builtin_clz(lb));
+    // KJT lists of a session-ordered batch are mostly their neighbours': where the context's last sample (one call
+    // in sixteen takes one, on the device) looked like that, a wave takes 8 of them and sums a run of equal ones once.  Any batch gets the same bits either way;
+    // which way is only a matter of speed, and a batch unlike the last ones pays what every list's own sum costs, or up to
+    // a quarter more.  Waves that looked for themselves cost batches without sessions a sixth (131 K lists of 5 ids 50 ->
+    // 58 us), one wave of every launch a tenth where rows are short.
+    // With the sample apart, 131 K / 262 K lists of 5 ids and 512-byte rows: no sessions 50.5 -> 51 / 95 -> 96 us, sessions
+    // of 12 46 -> 25 / 86 -> 41.
+    // 8192 x 32 lists of 64 ids, by 1 / 2 / 4 / 8 lists a wave, us: sessions of 8 556 / 407 / 340 / 341, of 2 920 / 882 /
+    // 928 / 962, no sessions 1441 / 1422 / 1488 / 1563.
+    const bool sample = a.site == RECD_SITE_KJT && ctx->tune_lb == 0 && n >= kSampledLists && ctx->mailbox;
+    const bool runs = sample ? ctx->mailbox[RECD_MAILBOX_SESSIONS] != 0 : a.site == RECD_SITE_KJT && ctx->tune_lb > 1;
+    if (sample && runs)
+        p.lb = lb = n >= (96 << 10) ? 8 : 4;
+    p.deal_log = recd_deal_log_kjt(n, a.F, kNQ, 31 - __builtin_clz(lb));
     const int64_t items = (n + lb - 1) / lb;
     int64_t nblk = p.nq == 1 ? items : kNQ * ((items + kNQ - 1) / kNQ + (items / kNQ) / 8 + 1);
     const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : 64);
@@ -1057,26 +1073,33 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
                      : a.site == RECD_SITE_KJT         ? RECD_T_KJT
                      : a.site == RECD_SITE_GRAD_STREAM ? RECD_T_GRAD_LISTS
                                                        : -1;
+    if (sample && ctx->kjt_calls++ % 16 == 0)
+        hipLaunchKernelGGL(k_sample_sessions, dim3(1), dim3(64), 0, st, a.offsets + a.list_base, n,
+                           ctx->mailbox_dev + RECD_MAILBOX_SESSIONS);
     if (slot >= 0)
         recd_time_begin(ctx, slot, st);
     if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_SUM)
         ok = launch_forward<SITE_UNIQUE>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_SUM)
-        ok = launch_forward<SITE_KJT>(st, blocks, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS>(st, blocks, v, a, p)
+                  : launch_forward<SITE_KJT>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE_EXPAND && fwd && a.mode == POOL_SUM && a.run_index)
         ok = launch_forward<SITE_UNIQUE_EXPAND>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_MEAN)
         ok = launch_forward<SITE_UNIQUE, POOL_MEAN>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_MEAN)
-        ok = launch_forward<SITE_KJT, POOL_MEAN>(st, blocks, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MEAN>(st, blocks, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_MEAN>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_MAX)
         ok = launch_forward<SITE_UNIQUE, POOL_MAX>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_MAX)
-        ok = launch_forward<SITE_KJT, POOL_MAX>(st, blocks, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MAX>(st, blocks, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_MAX>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_WSUM && a.weights)
         ok = launch_forward<SITE_UNIQUE, POOL_WSUM>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_WSUM && a.weights)
-        ok = launch_forward<SITE_KJT, POOL_WSUM>(st, blocks, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_WSUM>(st, blocks, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_WSUM>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_GRAD_STREAM && a.values_are_i32 && a.table_dt == RECD_F32 &&
              a.out_dt == RECD_F32 && a.mode == POOL_SUM)
         ok = launch_shape<RECD_F32, RECD_F32, int32_t, SITE_GRAD_STREAM>(st, blocks, v, p);

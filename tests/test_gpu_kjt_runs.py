@@ -58,6 +58,11 @@ def test_runs_of_equal_lists(F, B, run, D, dtype):
             call(got[lists_a_block])
         for lists_a_block, out in got.items():
             assert torch.equal(out, got[1]), lists_a_block
+        ctx.set_option(recd._OPT_INTERNAL_TUNE_SEGSUM, 0)
+        torch.cuda.synchronize()   # what the first such call found out about the batch is on the host now
+        again = torch.full((F, B, D), float("nan"), dtype=dt, device="cuda")
+        call(again)
+        assert torch.equal(again, got[1])
     # the last call's sums, in 64 bits: fp32 additions of at most 130 terms and one rounding to the output's type
     lens = offsets[1:] - offsets[:-1]
     to = torch.repeat_interleave(torch.arange(F * B, device="cuda"), lens)
