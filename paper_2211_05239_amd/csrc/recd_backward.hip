@@ -1002,7 +1002,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         ga.pay_pos = reinterpret_cast<uint32_t *>(w.pay_w);  // the sorted positions take the place of weights
     ga.u_weights = u_weights;
     ga.pay_w = w.pay_w;
-    RECD_TRY(recd_group(ctx, st, false, w.group, ga));
+    RECD_TRY(recd_group(ctx, st, w.group, ga));
     const uint32_t *ps_a = recd_group_rows(w.group, F, B, U_cap, M_cap, max_rows);
     const uint32_t *ps_b = recd_group_positions(w.group, F, B, M_cap, max_rows);
     // ---- step A: sum grad_out rows into g_u (or, for sequences, into grad_emb) ---------------------------
@@ -1096,7 +1096,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
 
 // ---------------------------------------------------------------- planned backward
 // The backward's grouping work depends on the IKJT only, not on the gradient.  recd_backward_plan runs it
-// on the side stream (a small batch's on the stream itself), starting where the IKJT's build ended, so
+// on the side stream (a short one on the stream itself), starting where the IKJT's build ended, so
 // that it overlaps the forward calls (which are bandwidth-bound, while the plan is a chain of short
 // latency-bound kernels);
 // recd_backward_apply then waits for the plan on the main stream and runs the two segment sums with
@@ -1178,7 +1178,7 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
                                       touched_rows, feat_roff);
         ga.run_index = run_index;
         ga.runs_cap = runs_cap > n_lists || runs_cap == 0 ? n_lists : runs_cap;
-        RECD_TRY(recd_group(ctx, side, !own_stream, w.group, ga));
+        RECD_TRY(recd_group(ctx, side, w.group, ga));
         pl.ps_a = recd_group_rows(w.group, F, B, U_cap, M_cap, max_rows);
         pl.ps_b = recd_group_positions(w.group, F, B, M_cap, max_rows);
     }

@@ -27,11 +27,8 @@
 
 namespace {
 
-// Threads of a counting block.  Beside the lookup, whose blocks are single waves and fill every wave slot as it gets
-// free, a block finds room the sooner the fewer waves it has (step of 1.05 M lists and 2.2 M ids, plan beside, 64 / 128 /
-// 256 threads: 778 / 772 / 787 us); on a stream of its own the larger block counts faster (0.19 M ids, step with the plan
-// in line: 165 / 155 / 150).
-constexpr int kCountThreads = 256, kCountThreadsBeside = 128;
+constexpr int kCountThreads = 256;
+constexpr int kFPT = RECD_MAX_FEATURES / kCountThreads;  // features per thread of k_group_count
 constexpr int kTileThreads = 512;
 constexpr int kItems = 8;
 constexpr int kTile = kTileThreads * kItems;  // entries of a tile
@@ -156,11 +153,10 @@ __device__ __forceinline__ void report_side_a(const GroupParams &g, int64_t U)
 __device__ __forceinline__ uint32_t sorted_bits(const SideParams &s) { return (uint32_t)((1ull << (s.passes * s.dbits)) - 1); }
 
 // Digit starts of feature f from the block's counts in LDS.
-template <int T>
 __device__ __forceinline__ void write_bases(const SideParams &s, int f, const uint32_t *hist)
 {
     const int radix = 1 << s.dbits;
-    constexpr int kPer = kMaxRadix / T;  // neighbouring digits of a thread
+    constexpr int kPer = kMaxRadix / kCountThreads;  // neighbouring digits of a thread
     for (int p = 0; p < s.passes; p++) {
         uint32_t v[kPer], sum = 0, total;
 #pragma unroll
@@ -169,7 +165,7 @@ __device__ __forceinline__ void write_bases(const SideParams &s, int f, const ui
             v[i] = d < radix ? hist[p * radix + d] : 0;
             sum += v[i];
         }
-        uint32_t e = block_excl<uint32_t, T / 64>(sum, total);
+        uint32_t e = block_excl<uint32_t, kCountThreads / 64>(sum, total);
         uint32_t *base = s.base + ((size_t)f * s.passes + p) * radix;
 #pragma unroll
         for (int i = 0; i < kPer; i++) {
@@ -190,18 +186,16 @@ __device__ __forceinline__ void write_bases(const SideParams &s, int f, const ui
 // small tiles a block counts the first digit of one small tile, and the sweep adds up.  What is
 // read is small (8 bytes an entry): the kernel is a few dependent round trips and the LDS atomics of a
 // chunk.
-template <int T>
-__global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
+__global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams g)
 {
-    constexpr int kFPT = RECD_MAX_FEATURES / T;  // features of a thread
     extern __shared__ uint32_t s_dyn[];          // the counts [passes * radix], side B also pb [F+1]: as little
     uint32_t *s_hist = s_dyn;                    // LDS as there is, so that blocks find room beside the lookup's
     __shared__ uint32_t s_pick[5];
     const int tid = threadIdx.x;
     if (blockIdx.x >= g.list_block0) {
         // the list of every position, 16 lanes to a list: blocks of their own, beside the chain of the others
-        const int64_t U = g.feat_uoff[g.F], step = (int64_t)(gridDim.x - g.list_block0) * (T / 16);
-        for (int64_t u = (int64_t)(blockIdx.x - g.list_block0) * (T / 16) + tid / 16; u < U; u += step) {
+        const int64_t U = g.feat_uoff[g.F], step = (int64_t)(gridDim.x - g.list_block0) * (kCountThreads / 16);
+        for (int64_t u = (int64_t)(blockIdx.x - g.list_block0) * (kCountThreads / 16) + tid / 16; u < U; u += step) {
             const int64_t at = g.u_offsets[u], end = g.u_offsets[u + 1] < g.M_cap ? g.u_offsets[u + 1] : g.M_cap;
             const uint32_t name = (uint32_t)(u < g.lists_cap ? u : g.lists_cap - 1);
             for (int64_t j = at + tid % 16; j < end; j += 16)
@@ -235,7 +229,7 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
     } else {
         uint32_t *s_pb = s_dyn + (s.passes << s.dbits);
         // where every feature's positions lie; tiles and chunks of the features before each one
-        for (int i = tid; i <= g.F; i += T) {
+        for (int i = tid; i <= g.F; i += kCountThreads) {
             const int64_t at = g.u_offsets[g.feat_uoff[i]];
             s_pb[i] = (uint32_t)(at < g.M_cap ? at : g.M_cap);  // never past the caller's capacity
         }
@@ -249,7 +243,7 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
         const int wide = more * (per_q + 1);  // places in the queues that hold one feature more
         if (small) {
             bool beyond = false;
-            for (int x = tid; x < g.F; x += T)
+            for (int x = tid; x < g.F; x += kCountThreads)
                 beyond |= s_pb[x + 1] - s_pb[x] > (uint32_t)(kSmallTilesPer * kSmallTile);
             small = !__syncthreads_or(beyond);
         }
@@ -268,8 +262,8 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
                 sum_q += tiles_of(in_queue(x) * kQueues + queue_of(x));
             }
         }
-        uint64_t ex = block_excl<uint64_t, T / 64>(sum, all);
-        uint32_t t_q = block_excl<uint32_t, T / 64>(sum_q, all_q);
+        uint64_t ex = block_excl<uint64_t, kCountThreads / 64>(sum, all);
+        uint32_t t_q = block_excl<uint32_t, kCountThreads / 64>(sum_q, all_q);
 #pragma unroll
         for (int i = 0; i < kFPT; i++) {
             const int x = tid * kFPT + i;
@@ -298,7 +292,7 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
             }
         }
         if (blk == 0) {
-            for (int i = tid; i <= g.F; i += T)
+            for (int i = tid; i <= g.F; i += kCountThreads)
                 g.pb[i] = s_pb[i];
             if (tid >= (g.F < kQueues ? g.F : kQueues) && tid <= kQueues)
                 g.queue_start[tid] = all_q;  // queues without a feature, and the end
@@ -325,7 +319,7 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
         const uint32_t my_tiles = small ? (c * chunk % kTile == 0 ? 1 : 0) : (end - begin + kTile - 1) / kTile;
         if (small && tid == 0)
             g.desc_small[blk] = make_uint4(f, c, s_pb[f], s_pb[f + 1] - s_pb[f]);
-        for (uint32_t k = tid; k < my_tiles; k += T) {
+        for (uint32_t k = tid; k < my_tiles; k += kCountThreads) {
             g.desc_queue[first_tile + k] = make_uint2(f, k0 + k);
             g.desc_feat[s_pick[3] + k0 + k] = make_uint4(f, k0 + k, s_pb[f], s_pb[f + 1] - s_pb[f]);
             g.seg_status[s_pick[3] + k0 + k] = 0;
@@ -335,21 +329,21 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
     const int radix = 1 << s.dbits;
     const uint32_t mask = radix - 1;
     const int passes = small ? 1 : s.passes;  // that are counted
-    for (int i = tid; i < passes * radix; i += T)
+    for (int i = tid; i < passes * radix; i += kCountThreads)
         s_hist[i] = 0;
     __syncthreads();
-    for (uint32_t i0 = tid; i0 < n; i0 += 16 * T) {
+    for (uint32_t i0 = tid; i0 < n; i0 += 16 * kCountThreads) {
         uint32_t key[16];
 #pragma unroll
         for (int u = 0; u < 16; u++) {
-            const uint32_t i = i0 + u * T;
+            const uint32_t i = i0 + u * kCountThreads;
             key[u] = i < n ? (side_a ? (uint32_t)g.inverse[begin + i] : (uint32_t)g.u_values[begin + i]) : 0u;
         }
 #pragma unroll
         for (int u = 0; u < 16; u++) {
             // Side A comes in runs of one slot (the samples of a session): the first lane of a run counts for
             // all of it, where every lane's own atomic would queue at one address.
-            const bool on = i0 + u * T < n;
+            const bool on = i0 + u * kCountThreads < n;
             uint32_t many = 1;
             bool count = on;
             if (side_a) {
@@ -367,20 +361,20 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
     }
     if (small) {  // the sweep adds up the counts of the feature's small tiles itself
         __syncthreads();
-        for (int i = tid; i < radix; i += T)
+        for (int i = tid; i < radix; i += kCountThreads)
             s.small_hist[chunk_row * radix + i] = s_hist[i];
         return;
     }
     // look-back flags of the chunk's tiles
-    for (int i = tid; i < (int)((n + kTile - 1) / kTile) * s.passes; i += T)
+    for (int i = tid; i < (int)((n + kTile - 1) / kTile) * s.passes; i += kCountThreads)
         s.flag[(size_t)(i % s.passes) * s.tiles_cap + first_tile + i / s.passes] = 0;
     const int words = s.passes * radix;
     __syncthreads();
     if (n_chunks == 1) {
-        write_bases<T>(s, f, s_hist);
+        write_bases(s, f, s_hist);
     } else {
         uint32_t *row = s.chunk_hist + chunk_row * words;
-        for (int i = tid; i < words; i += T)
+        for (int i = tid; i < words; i += kCountThreads)
             st_agent(row + i, s_hist[i]);
     }
     if (n_chunks == 1)
@@ -403,7 +397,7 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
     // the sum of `many` rows of counts, `stride` rows apart
     auto add_up = [&](const uint32_t *rows, int many, int stride) {
         constexpr int kPer = 8, kFly = 4;  // counts of a thread, and rows, in flight together
-        for (int i0 = tid; i0 < words; i0 += kPer * T) {
+        for (int i0 = tid; i0 < words; i0 += kPer * kCountThreads) {
             uint32_t sum[kPer] = {};
             for (int k = 0; k < many; k += kFly) {
                 uint32_t x[kFly][kPer];
@@ -411,7 +405,7 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
                 for (int j = 0; j < kFly; j++)
 #pragma unroll
                     for (int i = 0; i < kPer; i++) {
-                        const int at = i0 + i * T;
+                        const int at = i0 + i * kCountThreads;
                         x[j][i] = k + j < many && at < words ? ld_agent(rows + (size_t)(k + j) * stride * words + at) : 0;
                     }
 #pragma unroll
@@ -422,8 +416,8 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
             }
 #pragma unroll
             for (int i = 0; i < kPer; i++)
-                if (i0 + i * T < words)
-                    s_hist[i0 + i * T] = sum[i];
+                if (i0 + i * kCountThreads < words)
+                    s_hist[i0 + i * kCountThreads] = sum[i];
         }
         __syncthreads();
     };
@@ -434,7 +428,7 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
         if (!last_of(s.arrive + RECD_MAX_FEATURES + (chunk_row - c) + first, in))
             return;
         add_up(rows + (size_t)first * words, in, 1);
-        for (int i = tid; i < words; i += T)
+        for (int i = tid; i < words; i += kCountThreads)
             st_agent(rows + (size_t)first * words + i, s_hist[i]);
         stores_done();
         many = (n_chunks + kSumChunks - 1) / kSumChunks;
@@ -443,7 +437,7 @@ __global__ __launch_bounds__(T) void k_group_count(const GroupParams g)
     if (!last_of(s.arrive + f, many))
         return;
     add_up(rows, many, stride);
-    write_bases<T>(s, f, s_hist);
+    write_bases(s, f, s_hist);
 }
 
 // ---- one digit ----------------------------------------------------------------------------------------
@@ -1444,7 +1438,7 @@ const uint32_t *recd_group_positions(const RecdGroupWs &w, int F, int64_t B, int
     return w.b.pay[(passes - 1) & 1];
 }
 
-recd_status recd_group(recd_ctx *ctx, hipStream_t st, bool beside, const RecdGroupWs &w, const RecdGroupArgs &a)
+recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, const RecdGroupArgs &a)
 {
     GroupParams g{};
     g.F = a.F;
@@ -1521,17 +1515,13 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, bool beside, const RecdGro
     const unsigned b_blocks = g.small_b ? (unsigned)(a.M_cap / kSmallTile + a.F + 1) : g.b_tiles;
     g.a_blocks = (unsigned)((int64_t)a.F * g.cpf);
     g.list_block0 = g.a_blocks + (unsigned)(a.M_cap / chunk_b + a.F + 1);
-    const int threads = beside ? kCountThreadsBeside : kCountThreads;
-    int64_t list_blocks = ((a.U_cap < g.n_lists ? a.U_cap : g.n_lists) + threads / 16 - 1) / (threads / 16);
+    int64_t list_blocks = ((a.U_cap < g.n_lists ? a.U_cap : g.n_lists) + kCountThreads / 16 - 1) / (kCountThreads / 16);
     if (list_blocks > (int64_t)ctx->num_cu * 8)
         list_blocks = (int64_t)ctx->num_cu * 8;
     const unsigned cb = g.list_block0 + (a.pos_list ? (unsigned)(list_blocks < 1 ? 1 : list_blocks) : 0u);
     const size_t lds_a = (size_t)g.a.passes << g.a.dbits, lds_b = ((size_t)g.b.passes << g.b.dbits) + a.F + 1;
     const size_t lds = (lds_a > lds_b ? lds_a : lds_b) * sizeof(uint32_t);
-    if (beside)
-        hipLaunchKernelGGL(k_group_count<kCountThreadsBeside>, dim3(cb), dim3(kCountThreadsBeside), lds, st, g);
-    else
-        hipLaunchKernelGGL(k_group_count<kCountThreads>, dim3(cb), dim3(kCountThreads), lds, st, g);
+    hipLaunchKernelGGL(k_group_count, dim3(cb), dim3(kCountThreads), lds, st, g);
     const int passes = g.a.passes > g.b.passes ? g.a.passes : g.b.passes;
     for (int p = 0; p < passes; p++) {
         g.a_blocks = p < g.a.passes ? a_tiles : 0;

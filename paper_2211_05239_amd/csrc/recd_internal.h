@@ -275,8 +275,7 @@ struct RecdGroupArgs {
 // Side A's too_small word: which of the caller's bounds were too small.
 enum { RECD_GROUP_RUNS = 1, RECD_GROUP_LISTS = 2 };
 RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap);
-// beside: the caller's kernels run next to it on another stream.
-recd_status recd_group(recd_ctx *ctx, hipStream_t st, bool beside, const RecdGroupWs &w, const RecdGroupArgs &a);
+recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, const RecdGroupArgs &a);
 // Whether a plan is so short that it goes in line: the events that take it to the side stream and back cost the host some
 // 45 us and the device what the forward calls would hide of it (step of 65 K lists and 0.19 M ids: 150 us either way,
 // of which the host waits 42 us with the plan beside, 95 in line).
