@@ -1073,9 +1073,15 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
                      : a.site == RECD_SITE_KJT         ? RECD_T_KJT
                      : a.site == RECD_SITE_GRAD_STREAM ? RECD_T_GRAD_LISTS
                                                        : -1;
-    if (sample && ctx->kjt_calls++ % 16 == 0)
-        hipLaunchKernelGGL(k_sample_sessions, dim3(1), dim3(64), 0, st, a.offsets + a.list_base, n,
-                           ctx->mailbox_dev + RECD_MAILBOX_SESSIONS);
+    if (sample && ctx->kjt_calls++ % 16 == 0) {
+        // not into a graph, which may be replayed when the context and its mailbox are gone
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &capturing) != hipSuccess)
+            (void)hipGetLastError();
+        else if (capturing == hipStreamCaptureStatusNone)
+            hipLaunchKernelGGL(k_sample_sessions, dim3(1), dim3(64), 0, st, a.offsets + a.list_base, n,
+                               ctx->mailbox_dev + RECD_MAILBOX_SESSIONS);
+    }
     if (slot >= 0)
         recd_time_begin(ctx, slot, st);
     if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_SUM)

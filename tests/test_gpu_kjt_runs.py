@@ -74,3 +74,37 @@ def test_runs_of_equal_lists(F, B, run, D, dtype):
         bound = 130 * 2.0 ** -24 * size + {"f32": 0.0, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype] * ref.abs() + 1e-7
         assert bool(((got[0][f].double() - ref).abs() <= bound).all())
     ctx.close()
+
+
+def test_captured_lookup_outlives_its_context():
+    """A captured lookup holds the caller's tensors only: it is replayed after the context is gone, plain (captured
+    first) and by runs (captured once the sessions are known), each replay with eager work before it."""
+    from paper_2211_05239_amd import recd
+    F, B, D, rows = 5, 6601, 32, 3000
+    v, _, off = _batch(11, F * B, rows, 8)
+    values, offsets = torch.from_numpy(v.astype(np.int64)).cuda(), torch.from_numpy(off.astype(np.int64)).cuda()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    tables = [torch.empty(rows, D, device="cuda").normal_(0.0, 0.5, generator=gen) for _ in range(F)]
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ctx = recd.Context(0)
+        want, graphs = torch.empty(F, B, D, device="cuda"), []
+        for warm in (0, 2):
+            for _ in range(warm):
+                ctx.kjt_pooled_lookup(tables, B, values, offsets, want)
+                side.synchronize()
+            out, graph = torch.zeros(F, B, D, device="cuda"), torch.cuda.CUDAGraph()
+            side.synchronize()
+            with torch.cuda.graph(graph, stream=side):
+                ctx.kjt_pooled_lookup(tables, B, values, offsets, out)
+            graphs.append((graph, out))
+        side.synchronize()
+        ctx.close()
+        for _ in range(3):
+            for graph, out in graphs:
+                out.zero_()
+                side.synchronize()
+                graph.replay()
+                side.synchronize()
+                assert torch.equal(out, want)
