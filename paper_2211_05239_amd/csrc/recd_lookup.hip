@@ -1073,14 +1073,18 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
                      : a.site == RECD_SITE_KJT         ? RECD_T_KJT
                      : a.site == RECD_SITE_GRAD_STREAM ? RECD_T_GRAD_LISTS
                                                        : -1;
-    if (sample && ctx->kjt_calls++ % 16 == 0) {
-        // not into a graph, which may be replayed when the context and its mailbox are gone
+    if (sample && ctx->kjt_calls % 16 != 0) {
+        ctx->kjt_calls++;
+    } else if (sample) {
+        // not into a graph, which may be replayed when the context and its mailbox are gone: the next call samples
         hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &capturing) != hipSuccess)
+        if (hipStreamIsCapturing(st, &capturing) != hipSuccess) {
             (void)hipGetLastError();
-        else if (capturing == hipStreamCaptureStatusNone)
+        } else if (capturing == hipStreamCaptureStatusNone) {
             hipLaunchKernelGGL(k_sample_sessions, dim3(1), dim3(64), 0, st, a.offsets + a.list_base, n,
                                ctx->mailbox_dev + RECD_MAILBOX_SESSIONS);
+            ctx->kjt_calls++;
+        }
     }
     if (slot >= 0)
         recd_time_begin(ctx, slot, st);
