@@ -485,10 +485,7 @@ __device__ __forceinline__ void look_back(uint64_t *look, int64_t blk, int64_t a
 }
 
 // A run head is a first occurrence iff its slot's final row is its own.  LOOK: the blocks learn what those before them hold
-// by look-back, which up to kLookRows rows takes less than a launch of its own for their sums (k_flags; 65 K rows: 4.9 +
-// 6.2 us, with look-back 9.1; 1.05 M rows: 28, with look-back 38).  offsets: null where the rows have no ids.
-constexpr int64_t kLookRows = 256 * kScanBlock;
-
+// by look-back, else from sums that k_flags leaves (recd_looks_back).  offsets: null where the rows have no ids.
 template <bool LOOK>
 __global__ __launch_bounds__(kScanBlock) void k_number(const int64_t *__restrict__ offsets, int64_t B,
                                                        int64_t n_lists, int F,
@@ -1171,8 +1168,8 @@ __global__ __launch_bounds__(256) void k_group_hash_insert(const int64_t *__rest
 }
 
 // Feature-level compaction of a grouped IKJT: list (f,b) is stored iff row b is the representative
-// of its slot in f's group.  COMPACT_LOOK: in one launch, the blocks learn what those before them store by look-back (up
-// to kLookRows lists; 262 K lists: 5.1 + 6.2 + 4.5 us in three launches, now 10.9).  Else per-block sums of
+// of its slot in f's group.  COMPACT_LOOK: in one launch, the blocks learn what those before them store by look-back
+// (recd_looks_back; 262 K lists: 5.1 + 6.2 + 4.5 us in three launches, now 10.9).  Else per-block sums of
 // (stored, stored * length), and after the scan of the block sums the positions of the stored lists.
 enum { COMPACT_SUMS = 0, COMPACT_NUMBER = 1, COMPACT_LOOK = 2 };
 template <int STEP>
@@ -1515,16 +1512,17 @@ struct SlotWs {
     int64_t *bs_cnt, *bs_len, *bs_head;
 };
 
-SlotWs carve_slots(WsCarver &c, int tables, int64_t B, int64_t items, int64_t scan_items)
+// shared: calls of other streams may use the memory at the same time; no look-back then, and no words for it.
+SlotWs carve_slots(WsCarver &c, int tables, int64_t B, int64_t items, int64_t scan_items, bool shared = false)
 {
     SlotWs w;
     const int64_t nblk = (scan_items + kScanBlock - 1) / kScanBlock;
     w.cap = table_cap(B);
     w.counts = c.take<int64_t>(4);
     // the look-back words of the two numberings follow the tables
-    w.table = c.take<uint64_t>((size_t)tables * w.cap + look_words(items) + look_words(scan_items));
-    w.look = w.table + (size_t)tables * w.cap;
-    w.look_lists = w.look + look_words(items);
+    w.table = c.take<uint64_t>((size_t)tables * w.cap + (shared ? 0 : look_words(items) + look_words(scan_items)));
+    w.look = shared ? nullptr : w.table + (size_t)tables * w.cap;
+    w.look_lists = shared ? nullptr : w.look + look_words(items);
     w.slot_of = c.take<int32_t>(items);
     w.rep = c.take<int32_t>(items);
     w.number = c.take<int32_t>(items);
@@ -1539,7 +1537,7 @@ SlotWs carve_slots(WsCarver &c, int tables, int64_t B, int64_t items, int64_t sc
 // Empties the tables and the look-back words behind them (more: words of the second numbering).
 void clear_table(hipStream_t st, const SlotWs &w, int tables, int64_t B, size_t more = 0)
 {
-    const int64_t tab_n = (int64_t)tables * (int64_t)w.cap + (int64_t)(look_words(tables * B) + more);
+    const int64_t tab_n = (int64_t)tables * (int64_t)w.cap + (w.look ? (int64_t)(look_words(tables * B) + more) : 0);
     const int fill_blocks = (int)((tab_n + 1023) / 1024 < 4096 ? (tab_n + 1023) / 1024 : 4096);
     hipLaunchKernelGGL(k_fill_u64, dim3(fill_blocks), dim3(256), 0, st, w.table, tab_n, kEmpty);
 }
@@ -1575,7 +1573,7 @@ void number_slots(hipStream_t st, const SlotWs &w, int tables, int64_t B, const 
     const int64_t n = (int64_t)tables * B;
     const unsigned nblk = (unsigned)((n + kScanBlock - 1) / kScanBlock);
     const uint32_t mask = (uint32_t)(w.cap - 1);
-    if (n <= kLookRows) {
+    if (recd_looks_back(n, !w.look)) {
         hipLaunchKernelGGL(k_number<true>, dim3(nblk), dim3(kScanBlock), 0, st, offsets, B, n, tables, w.table, mask,
                            w.slot_of, w.look, nullptr, nullptr, nullptr, w.rep, w.number, w.src_of, u_off, uoff,
                            w.counts, mailbox, seq, run_index ? w.hrank : nullptr, run_index);
@@ -1758,8 +1756,7 @@ extern "C" recd_status recd_build_ikjt(recd_ctx *ctx, int F, int64_t B, int64_t 
 // row, block sums and counts for at most RECD_NOALLOC_MAX_LISTS lists.  One copy per GPU the library
 // runs on, held until the process ends; every call on a GPU uses it (overlapping calls race).
 namespace {
-// F * cap(B) <= max(64 F, 4 F B), and the look-back words
-constexpr size_t kStaticTableSlots = 4 * (size_t)RECD_NOALLOC_MAX_LISTS + 2 * look_words(RECD_NOALLOC_MAX_LISTS);
+constexpr size_t kStaticTableSlots = 4 * (size_t)RECD_NOALLOC_MAX_LISTS;  // F * cap(B) <= max(64 F, 4 F B)
 constexpr size_t kStaticScratchBytes =
     kStaticTableSlots * sizeof(uint64_t) + 5 * ((size_t)RECD_NOALLOC_MAX_LISTS * sizeof(int32_t) + 256) +
     3 * ((RECD_NOALLOC_MAX_LISTS / kScanBlock + 2) * sizeof(int64_t) + 256) + 2 * 256;
@@ -1806,8 +1803,8 @@ extern "C" recd_status recd_build_ikjt_noalloc(recd_ctx *ctx, int F, int64_t B, 
         return recd_fail(ctx, RECD_EHIP, "the static scratch array was not found when the context was created");
     RECD_HIP(ctx, hipSetDevice(ctx->device));
     WsCarver c(ctx->static_scratch);
-    const SlotWs w = carve_slots(c, F, B, n_lists, n_lists);
-    if ((size_t)F * w.cap + 2 * look_words(n_lists) > kStaticTableSlots || c.off > kStaticScratchBytes)
+    const SlotWs w = carve_slots(c, F, B, n_lists, n_lists, true);
+    if ((size_t)F * w.cap > kStaticTableSlots || c.off > kStaticScratchBytes)
         return recd_fail(ctx, RECD_ECAPACITY, "sizes exceed the static scratch array");
     hipStream_t st = ctx->stream;
     if (n_lists == 0) {
@@ -1954,7 +1951,7 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
                                dev_feat_group, w.rep, w.number, w.look_lists, w.bs_cnt, w.bs_len, w.bs_head, src_of,
                                u_offsets, feat_uoff, inverse_per_feature, counts);
         };
-        if (n_lists <= kLookRows) {
+        if (recd_looks_back(n_lists, false)) {
             compact(k_group_compact<COMPACT_LOOK>);
         } else {
             compact(k_group_compact<COMPACT_SUMS>);

@@ -83,3 +83,10 @@ RECD_RULE int recd_jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vec
         lists *= 2;
     return lists;
 }
+
+// Whether the builders number their rows in one launch whose blocks wait for what those before them hold (look-back):
+// up to 256 blocks of 1024 rows, beyond that a launch for the blocks' sums and one for the numbers (65 K rows: 4.9 + 6.2
+// us, with look-back 9.1; 1.05 M rows: 28, with look-back 38).  Never on scratch that calls of other streams share: one
+// that overlaps may give wrong numbers there, but as it clears the words that the blocks of the other wait for, neither
+// might return.
+RECD_RULE bool recd_looks_back(int64_t rows, bool shared_scratch) { return !shared_scratch && rows <= 256 * 1024; }

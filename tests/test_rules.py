@@ -12,6 +12,7 @@ HARNESS = r"""
 #include "recd_rules.h"
 extern "C" {
 int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vecs) { return recd_jagged_lists(N, U_cap, M_cap, vecs, 256); }
+bool looks_back(int64_t rows, bool shared) { return recd_looks_back(rows, shared); }
 int64_t lists_held(int64_t F, int64_t B, int64_t U_cap, int64_t M_cap) { return recd_lists_held(F, B, U_cap, M_cap); }
 
 // starts[slot] and how often each was written, of n >= 1 sorted keys; returns the writes outside [0, slots)
@@ -71,6 +72,18 @@ def test_room_for_every_unique_list(rules):
     assert rules.lists_held(5, 600, 3000, 10 ** 9) == 3000
     assert rules.lists_held(5, 600, 7, 40) == 45           # no fewer than a plain IKJT of M_cap ids can have
     assert rules.lists_held(5, 600, 10 ** 9, 40) == 3000
+
+
+def test_no_wait_between_blocks_on_shared_scratch(rules):
+    """Overlapping recd_build_ikjt_noalloc calls may give wrong numbers; none may wait for words the other clears."""
+    rules.looks_back.restype = C.c_bool
+    rules.looks_back.argtypes = [C.c_int64, C.c_bool]
+    for rows in (1, 1024, 1025, 65536, 1 << 18):
+        assert rules.looks_back(rows, False) and not rules.looks_back(rows, True)
+    assert not rules.looks_back((1 << 18) + 1, False)
+    source = open(os.path.join(CSRC, "recd_build.hip")).read()
+    call = source[source.index("recd_status recd_build_ikjt_noalloc("):]
+    assert "carve_slots(c, F, B, n_lists, n_lists, true)" in call[:call.index("\n}\n")]
 
 
 @pytest.mark.parametrize("seed", range(6))
