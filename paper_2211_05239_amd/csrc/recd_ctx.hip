@@ -272,11 +272,11 @@ recd_status recd_create(recd_ctx **out, int device, void *hip_stream, size_t wor
     ok = ok && hipHostMalloc(&p, 8 * sizeof(int64_t), hipHostMallocDefault) == hipSuccess;
     ctx->host_pinned = static_cast<int64_t *>(p);
     void *mb = nullptr, *mb_dev = nullptr;
-    if (ok && hipHostMalloc(&mb, RECD_MAILBOX_WORDS * sizeof(int64_t), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
+    if (ok && hipHostMalloc(&mb, 16 * sizeof(int64_t), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
         if (hipHostGetDevicePointer(&mb_dev, mb, 0) == hipSuccess) {
             ctx->mailbox = static_cast<volatile int64_t *>(mb);
             ctx->mailbox_dev = static_cast<int64_t *>(mb_dev);
-            for (int i = 0; i < RECD_MAILBOX_WORDS; i++)
+            for (int i = 0; i < 16; i++)
                 ctx->mailbox[i] = 0;
         } else {
             (void)hipGetLastError();

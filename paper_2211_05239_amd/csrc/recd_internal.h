@@ -78,7 +78,6 @@ struct recd_ctx {
     // one-thread kernel writes (values, then a sequence number); nullptr if it could not be set up.
     volatile int64_t *mailbox = nullptr;
     int64_t *mailbox_dev = nullptr;
-    uint32_t kjt_calls = 0;      // of KJT lookups that choose by RECD_MAILBOX_SESSIONS
     int64_t mailbox_seq = 0;
     // Counts {U, M} of the most recent plain or weighted IKJT build: a device array that outlives the
     // workspace's reuse, and the second half of the mailbox (entries 8..15, sequence number in 15),
@@ -128,10 +127,6 @@ struct recd_ctx {
 // the build's sequence number, bits 0..39 = the value (all ones: the build failed).  A word of the
 // other builders (a plain count below 2^40) never carries a tag.
 #define RECD_MAILBOX_TAG_BIT (1u << 23)
-// Words of the mailbox: 0..7 scalars that are fetched, 8..15 a build's counts, 16 whether a large KJT lookup's batch last
-// looked like sessions (read without waiting: it only chooses between two ways to the same bits).
-#define RECD_MAILBOX_SESSIONS 16
-#define RECD_MAILBOX_WORDS 24
 void recd_time_begin(recd_ctx *ctx, int slot, hipStream_t st);
 void recd_time_end(recd_ctx *ctx, int slot, hipStream_t st);
 

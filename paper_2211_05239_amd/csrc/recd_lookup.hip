@@ -39,7 +39,9 @@ template <int SITE> struct SegBlock {
     static constexpr int threads = (SITE == 0 || SITE == 1 || SITE == 2 || SITE == 4) ? 64 : 256;
 };
 constexpr int kMaxLB = 16;     // lists per block item (upper bound)
-constexpr int64_t kSampledLists = 32768;  // KJT lists from which on equal neighbours may share their sum
+constexpr int64_t kRunsLists = 32768;  // KJT lists from which on a wave takes several and shares equal neighbours' sums
+constexpr int kStage = 1024;   // ids of such a wave's lists that wait in LDS
+constexpr int kStageLoads = 4; // of them in flight at a time, 64 each
 constexpr int kChunk = 64;     // ids per chunk: a wave loads a chunk's ids with one instruction
 
 __device__ __forceinline__ int64_t uniform64(int64_t v)
@@ -147,8 +149,7 @@ template <int OT, int N, bool NT> __device__ __forceinline__ void store_row_piec
 // SITE_UNIQUE_EXPAND: the unique lookup whose waves also store a finished row to the output rows of
 // the run of adjacent samples that starts at the list's first row (Sec. 5: lookup on the unique
 // lists, then the index select back to the batch - here for the samples a session put side by side).
-// SITE_KJT_RUNS: the KJT lookup whose waves share the sum of equal neighbours.  In small batches the comparison is only in
-// the way (14.8 K lists of short rows: 14.8 us without it, 16.6 with it).
+// SITE_KJT_RUNS: the KJT lookup of many lists, whose waves share the sum of equal neighbours.
 enum { SITE_UNIQUE = 0, SITE_KJT = 1, SITE_KJT_RUNS = 2, SITE_GRAD_STREAM = 3, SITE_UNIQUE_EXPAND = 4 };
 constexpr bool is_kjt(int site) { return site == SITE_KJT || site == SITE_KJT_RUNS; }
 
@@ -165,6 +166,7 @@ struct SegSumParams {
     int vecs_per_row;  // D / elements per 16-byte vector
     int nq;            // 8: XCD-aware queues (forward sites only); 1: one flat queue
     int lb;            // lists per block item, <= kMaxLB; 0 (forward sites): chosen by the number of lists
+    int64_t whole;     // SITE_KJT_RUNS: a queue's items of lb lists, the later ones have fewer (recd_item_start)
     int deal_log;      // the KJT lookup: how many lists are dealt to a queue at a time (recd_deal_log_kjt)
     // optional: list l spans offsets[l] .. offsets[l] + lens[l] (windows of a partial IKJT)
     const int64_t *lens;
@@ -304,6 +306,7 @@ void k_segsum(const SegSumParams p)
 
     __shared__ int64_t s_start[kMaxLB], s_end[kMaxLB];
     __shared__ int s_feat[kMaxLB];
+    __shared__ uint32_t s_ids[kStage];                    // SITE_KJT_RUNS
     __shared__ float s_part[LL][kWaves][ROWF];
     constexpr bool EXPAND = SITE == SITE_UNIQUE_EXPAND;
     static_assert(!EXPAND || kWaves == 1, "a finished row is in the registers of one wave");
@@ -352,9 +355,10 @@ void k_segsum(const SegSumParams p)
         }
     };
     // A finished row, whose NACC-element pieces the lanes of a lane group hold in vals.
-    auto store_row = [&](int64_t l, const float *vals) {
+    // below: bytes beyond row l where it goes.
+    auto store_row = [&](int64_t l, const float *vals, uint32_t below = 0) {
         if (piece_ok) {
-            char *dst = static_cast<char *>(p.out) + l * out_row_bytes;
+            char *dst = static_cast<char *>(p.out) + l * out_row_bytes + below;
 #pragma unroll
             for (int w = 0; w < VPL; w++)
                 store_row_piece<OT, EPV, NT>(dst + ((int64_t)w * LPR + r) * OB, vals + w * EPV);
@@ -369,9 +373,8 @@ void k_segsum(const SegSumParams p)
     // One wave walks a whole list of more than 64 ids: the ids of the next chunk are fetched before
     // the rows of this one, so their latency hides behind the row loads.
     // cur: this lane's id of the first chunk.
-    auto walk_long_list = [&](float (*acc)[NACC], const char *table, int64_t start, int64_t end, uint32_t cur) {
+    auto walk_list = [&](float (*acc)[NACC], const char *table, int64_t start, int64_t end, int n, uint32_t cur) {
         int64_t base = start;
-        int n = kChunk;
         for (;;) {
             const int64_t nbase = base + kChunk;
             const bool more = nbase < end;
@@ -385,6 +388,9 @@ void k_segsum(const SegSumParams p)
             n = nn;
             cur = nxt;
         }
+    };
+    auto walk_long_list = [&](float (*acc)[NACC], const char *table, int64_t start, int64_t end, uint32_t cur) {
+        walk_list(acc, table, start, end, kChunk, cur);
     };
 
     if constexpr (EXPAND) {
@@ -478,9 +484,11 @@ void k_segsum(const SegSumParams p)
         const int64_t all = end_all - first;
         // lists per block: as many as keep the number of blocks in bounds (measured at 61 K unique lists
         // and at 1.05 M KJT lists: 1 and 4), by the true number of lists
-        const int lpb = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
-        const int deal_log = is_kjt(SITE) ? p.deal_log : recd_deal_log(all, kNQ, 31 - __builtin_clz(lpb));
-        for (int64_t t = item0 * lpb;; t += item_stride * lpb) {
+        const int most = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
+        const int deal_log = is_kjt(SITE) ? p.deal_log : recd_deal_log(all, kNQ, 31 - __builtin_clz(most));
+        for (int64_t i = item0;; i += item_stride) {
+            const int lpb = SITE == SITE_KJT_RUNS ? recd_item_lists(i, p.whole, most) : most;
+            const int64_t t = SITE == SITE_KJT_RUNS ? recd_item_start(i, p.whole, most) : i * most;
             const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ, deal_log));
             if (l0 >= end_all)
                 break;  // so are all later items of this block
@@ -506,31 +514,49 @@ void k_segsum(const SegSumParams p)
                 __syncthreads();  // a block of one wave: orders the LDS accesses, nobody waits
             }
             if constexpr (SITE == SITE_KJT_RUNS) {
-                // Neighbouring lists of a session-ordered batch are mostly the same list.  The wave compares each of
-                // its lists with the one before it, all at once with 64 / lpb lanes to a list, sums the first of every
-                // run of equal ones and stores its row for the whole run: the same ids in the same order give the same
-                // bits.  What bounds the lookup is the gathered rows, and those of a run are gathered once (262 K lists
-                // of 64 ids, 512-byte rows, sessions of 8: 549 -> 328 us; 1.05 M of 34 ids, sessions of 16: 1010 -> 420).
-                // (Runs that go on into other waves' lists, with those left out there: 485; the waves that find
-                // nothing to do cost more than the sums saved.  One list after the other with the ids still in registers:
-                // 342.)
-                const int per = 6 - (31 - __builtin_clz(lpb)), at = lane & ((1 << per) - 1), mine = lane >> per;
+                // Neighbouring lists of a session-ordered batch are mostly the same list.  The wave brings the ids of all of
+                // its lists, which lie one behind the other, into LDS, compares each list with the one before it, 64 / lpb
+                // lanes to a list, sums the first of every run of equal ones and stores its row for the whole run: the same
+                // ids in the same order give the same bits.  What bounds the lookup is the gathered rows, and those of a run
+                // are gathered once; with the ids at hand the other lists cost a wave a round trip less than one by one, which
+                // pays for the comparison where it finds nothing.  us, by the plain kernel / by this one, 262 K lists:
+                // sessions of 8, 64 ids, rows of 512 bytes 522 / 303, of 64 bytes 172 / 81; 5 ids 87 / 46, 101 / 49;
+                // no sessions, 5 ids 140 / 137, 107 / 103; 64 ids 1154 / 1190, 240 / 286 (the last is the worst: tables
+                // about as large as an L2, of which 7 K waves of 8 lists use more at a time than those of 2).
+                // (Each wave's lists compared in memory, ids read again by the sums: no sessions, 64 ids of 64-byte
+                // rows 290, sessions 107.  Runs that go on into other waves' lists, with those left out there: 485 for
+                // 303.  Four waves a block: its slots are free only when the last is done; sessions of 5 ids 62 for 46.
+                // A kernel before this one to look whether the batch has sessions: 3 us of 14 to 60.)
+                const int64_t base = uniform64(s_start[0]), held = uniform64(s_end[cnt - 1]) - base;
+                const int staged = (int)(held < kStage ? held : kStage);
+                int ln = lane;
+                asm volatile("" : "+v"(ln));  // as above: nothing of this is kept over the gathers
+                for (int u0 = 0; u0 < staged; u0 += kStageLoads * 64) {
+                    uint32_t id[kStageLoads];
+#pragma unroll
+                    for (int u = 0; u < kStageLoads; u++)
+                        id[u] = u0 + u * 64 + ln < staged ? (uint32_t)values[base + u0 + u * 64 + ln] : 0u;
+#pragma unroll
+                    for (int u = 0; u < kStageLoads; u++)
+                        s_ids[u0 + u * 64 + ln] = id[u];
+                }
+                __syncthreads();
+                const int per = 6 - (31 - __builtin_clz(lpb)), at = ln & ((1 << per) - 1), mine = ln >> per;
                 bool same = false;
                 if (mine > 0 && mine < cnt && s_feat[mine] == s_feat[mine - 1]) {
                     const int64_t start = s_start[mine], len = s_end[mine] - start, back = start - s_start[mine - 1];
                     same = back == len;
-                    for (int64_t t = at; same && t < len; t += 4ll << per) {
-#pragma unroll
-                        for (int u = 0; u < 4; u++) {
-                            const int64_t k = t + ((int64_t)u << per);
-                            if (k < len) {
-                                same &= (uint32_t)values[start + k] == (uint32_t)values[start + k - back];
-                                if (MODE == POOL_WSUM)  // bit patterns: the sum depends on no more
-                                    same &= __float_as_uint(p.weights[start + k]) ==
-                                            __float_as_uint(p.weights[start + k - back]);
-                            }
-                        }
+                    const int64_t rel = start - base;
+                    if (rel - back >= 0 && rel + len <= staged) {
+                        for (int t = at; same && t < (int)len; t += 1 << per)
+                            same = s_ids[(int)rel + t] == s_ids[(int)(rel - back) + t];
+                    } else {
+                        for (int64_t t = at; same && t < len; t += 1 << per)
+                            same = (uint32_t)values[start + t] == (uint32_t)values[start + t - back];
                     }
+                    if (MODE == POOL_WSUM)  // bit patterns: the sum depends on no more
+                        for (int64_t t = at; same && t < len; t += 1 << per)
+                            same = __float_as_uint(p.weights[start + t]) == __float_as_uint(p.weights[start + t - back]);
                 }
                 const uint64_t differ = __ballot(!same), group = per == 6 ? ~0ull : (1ull << (1 << per)) - 1;
                 for (int j = 0, end; j < cnt; j = end) {
@@ -540,21 +566,26 @@ void k_segsum(const SegSumParams p)
                     const int64_t len = uniform64(s_end[j]) - start;
                     const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
                     const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
+                    const int n = (int)(len < kChunk ? len : kChunk);
+                    const int64_t rel = start - base;
+                    uint32_t cur = 0;
+                    if (rel >= 0 && rel + n <= staged) {
+                        if (lane < n)
+                            cur = s_ids[(int)rel + lane];
+                    } else if (lane < n) {
+                        cur = (uint32_t)values[start + lane];
+                    }
                     float acc[1][NACC];
 #pragma unroll
                     for (int i = 0; i < NACC; i++)
                         acc[0][i] = pool_identity<MODE>();
-                    if (len > kChunk) {
-                        walk_long_list(acc, table, start, start + len, (uint32_t)values[start + lane]);
-                    } else {
-                        const int n = (int)len;
-                        add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes,
-                                                                            lane, g, p.weights);
-                    }
+                    walk_list(acc, table, start, start + len, n, cur);
                     fold_groups(acc[0]);  // the butterfly leaves the row in every lane group
                     scale_row(l0 + j, len, acc[0]);
-                    for (int k = j + g; k < end; k += 64 / LPR)
-                        store_row(l0 + k, acc[0]);
+                    int gg = g;
+                    asm volatile("" : "+v"(gg));  // its offset is not kept over the gathers either
+                    for (int k = gg; k < end - j; k += 64 / LPR)
+                        store_row(l0 + j, acc[0], (uint32_t)k * (uint32_t)out_row_bytes);
                 }
             } else {
                 for (int j = 0; j < cnt; j++) {
@@ -662,18 +693,6 @@ void k_segsum(const SegSumParams p)
             finish_row(t0 + j, len, acc[0]);
         }
     }
-}
-
-// Whether most neighbouring lists of offsets[0 .. n] are as long as each other (60 pairs in four places; n >= 64), and so
-// probably equal: 1 or 0 to a word that the host reads without waiting.
-__global__ __launch_bounds__(64) void k_sample_sessions(const int64_t *offsets, int64_t n, int64_t *sessions)
-{
-    const int lane = threadIdx.x;
-    const int64_t at = (n >> 2) * (lane >> 4) + (n >> 3) + (lane & 15);
-    const int64_t len = offsets[at + 1] - offsets[at], left = __shfl_up(len, 1);
-    const int equal = (int)__popcll(__ballot(len == left && (lane & 15) != 0));
-    if (lane == 0)
-        __hip_atomic_store(sessions, (int64_t)(equal >= 40), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 template <int TT, int OT, typename IdxT, int SITE, int MODE = POOL_SUM>
@@ -1036,22 +1055,23 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     p.lb = one_wave ? 0 : lb;
     if (ctx->tune_lb > 0)
         p.lb = lb = ctx->tune_lb;
-    // KJT lists of a session-ordered batch are mostly their neighbours': where the context's last sample (one call
-    // in sixteen takes one, on the device) looked like that, a wave takes 8 of them and sums a run of equal ones once.  Any batch gets the same bits either way;
-    // which way is only a matter of speed, and a batch unlike the last ones pays what every list's own sum costs, or up to
-    // a quarter more.  Waves that looked for themselves cost batches without sessions a sixth (131 K lists of 5 ids 50 ->
-    // 58 us), one wave of every launch a tenth where rows are short.
-    // With the sample apart, 131 K / 262 K lists of 5 ids and 512-byte rows: no sessions 50.5 -> 51 / 95 -> 96 us, sessions
-    // of 12 46 -> 25 / 86 -> 41.
-    // 8192 x 32 lists of 64 ids, by 1 / 2 / 4 / 8 lists a wave, us: sessions of 8 556 / 407 / 340 / 341, of 2 920 / 882 /
-    // 928 / 962, no sessions 1441 / 1422 / 1488 / 1563.
-    const bool sample = a.site == RECD_SITE_KJT && ctx->tune_lb == 0 && n >= kSampledLists && ctx->mailbox;
-    const bool runs = sample ? ctx->mailbox[RECD_MAILBOX_SESSIONS] != 0 : a.site == RECD_SITE_KJT && ctx->tune_lb > 1;
-    if (sample && runs)
-        p.lb = lb = n >= (96 << 10) ? 8 : 4;
+    // KJT lists: from kRunsLists on a wave takes 8 or, where that would leave too few waves, 4.  Which way a lookup goes
+    // depends on the numbers of lists and features alone.
+    // Plain / 4 / 8 lists a wave, us, rows of 512 bytes, sessions of 8 and none: 32 K lists of 5 ids 17 / 15 / 14 and
+    // 21 / 22 / 21, of 24 27 / 22 / 25 and 68 / 70 / 73; 64 K of 5 30 / 22 / 19 and 38 / 35 / 35, of 24 47 / 35 / 36 and
+    // 134 / 143 / 151.  16 K, sessions of 8, plain / 4: of 5 10.9 / 10.3, of 64 33 / 39.
+    const bool runs = a.site == RECD_SITE_KJT && (ctx->tune_lb == 0 ? n >= kRunsLists : ctx->tune_lb > 1);
+    if (runs && ctx->tune_lb == 0)
+        p.lb = lb = n >= 2 * kRunsLists ? 8 : 4;
     p.deal_log = recd_deal_log_kjt(n, a.F, kNQ, 31 - __builtin_clz(lb));
     const int64_t items = (n + lb - 1) / lb;
+    p.whole = INT64_MAX;
     int64_t nblk = p.nq == 1 ? items : kNQ * ((items + kNQ - 1) / kNQ + (items / kNQ) / 8 + 1);
+    if (runs) {  // the host knows the lists: no block more than they need
+        const int64_t most = p.nq == 1 ? n : recd_deal_most(n, kNQ, p.deal_log);
+        p.whole = recd_whole_items(most, p.nq, lb);
+        nblk = (int64_t)p.nq * recd_items(most, p.whole, lb);
+    }
     const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : 64);
     if (nblk > cap)
         nblk = cap / kNQ * kNQ;
@@ -1073,19 +1093,6 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
                      : a.site == RECD_SITE_KJT         ? RECD_T_KJT
                      : a.site == RECD_SITE_GRAD_STREAM ? RECD_T_GRAD_LISTS
                                                        : -1;
-    if (sample && ctx->kjt_calls % 16 != 0) {
-        ctx->kjt_calls++;
-    } else if (sample) {
-        // not into a graph, which may be replayed when the context and its mailbox are gone: the next call samples
-        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &capturing) != hipSuccess) {
-            (void)hipGetLastError();
-        } else if (capturing == hipStreamCaptureStatusNone) {
-            hipLaunchKernelGGL(k_sample_sessions, dim3(1), dim3(64), 0, st, a.offsets + a.list_base, n,
-                               ctx->mailbox_dev + RECD_MAILBOX_SESSIONS);
-            ctx->kjt_calls++;
-        }
-    }
     if (slot >= 0)
         recd_time_begin(ctx, slot, st);
     if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_SUM)

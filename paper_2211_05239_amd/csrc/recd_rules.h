@@ -66,6 +66,29 @@ RECD_RULE int64_t recd_dealt(int64_t t, int q, int queues, int deal_log)
     return ((((t >> deal_log) * queues) + q) << deal_log) + (t & (((int64_t)1 << deal_log) - 1));
 }
 
+// Lists of the queue that is dealt the most of n.
+RECD_RULE int64_t recd_deal_most(int64_t n, int queues, int deal_log)
+{
+    const int64_t stretch = (int64_t)1 << deal_log, rest = n % (stretch * queues);
+    return n / (stretch * queues) * stretch + (rest < stretch ? rest : stretch);
+}
+
+// Items of a queue of a KJT lookup whose waves share sums: `whole` items of lb lists, then items of two, so that the chip's
+// last waves are short ones.  16384 lists, at most half of them, go two by two (65 K lists of 5 / 24 / 64 ids without
+// sessions 40 -> 35, 156 -> 151, 362 -> 353 us; with sessions and of 262 K lists the same within 2 %).
+enum { RECD_LAST_LISTS = 2 };
+RECD_RULE int64_t recd_whole_items(int64_t lists, int queues, int lb)
+{
+    const int64_t tail = lists / 2 < 16384 / queues ? lists / 2 : 16384 / queues;
+    return lb <= RECD_LAST_LISTS ? INT64_MAX : (lists - tail) / lb;
+}
+RECD_RULE int64_t recd_item_start(int64_t i, int64_t whole, int lb) { return i < whole ? i * lb : whole * lb + (i - whole) * RECD_LAST_LISTS; }
+RECD_RULE int recd_item_lists(int64_t i, int64_t whole, int lb) { return i < whole ? lb : RECD_LAST_LISTS; }
+RECD_RULE int64_t recd_items(int64_t lists, int64_t whole, int lb)
+{
+    return whole == INT64_MAX ? (lists + lb - 1) / lb : whole + (lists - whole * lb + RECD_LAST_LISTS - 1) / RECD_LAST_LISTS;
+}
+
 // Unique lists per block of the sequence backward's sum over their rows, of 16 * vecs bytes each: 24 to 48
 // positions, and twice as many where rows are short, lists are neither short nor known to have many rows, and
 // there are more blocks than the chip holds several times over (2.1 M positions, one row a list, whole call, us, by the

@@ -59,7 +59,7 @@ def test_runs_of_equal_lists(F, B, run, D, dtype):
         for lists_a_block, out in got.items():
             assert torch.equal(out, got[1]), lists_a_block
         ctx.set_option(recd._OPT_INTERNAL_TUNE_SEGSUM, 0)
-        torch.cuda.synchronize()   # what the first such call found out about the batch is on the host now
+        torch.cuda.synchronize()
         again = torch.full((F, B, D), float("nan"), dtype=dt, device="cuda")
         call(again)
         assert torch.equal(again, got[1])
@@ -78,7 +78,7 @@ def test_runs_of_equal_lists(F, B, run, D, dtype):
 
 def test_captured_lookup_outlives_its_context():
     """A captured lookup holds the caller's tensors only: it is replayed after the context is gone, plain (captured
-    first) and by runs (captured once the sessions are known), each replay with eager work before it."""
+    first) and after eager calls, each replay with eager work before it."""
     from paper_2211_05239_amd import recd
     F, B, D, rows = 5, 6601, 32, 3000
     v, _, off = _batch(11, F * B, rows, 8)
@@ -108,3 +108,39 @@ def test_captured_lookup_outlives_its_context():
                 graph.replay()
                 side.synchronize()
                 assert torch.equal(out, want)
+
+
+def _lists(F, B, fixed, run, rows):
+    """Lists of `fixed` ids in runs of `run` equal ones."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(F * B + fixed)
+    ids = torch.randint(0, rows, (F, (B + run - 1) // run, fixed), device="cuda", generator=gen)
+    values = ids.repeat_interleave(run, dim=1)[:, :B].reshape(-1).contiguous()
+    return values, torch.arange(F * B + 1, device="cuda") * fixed
+
+
+def test_way_depends_on_the_sizes_alone():
+    """Every call of a size is the same single kernel: a context's first one, one after batches of another kind, and
+    one captured; lists of one length that hold different ids are summed as such."""
+    from torch.profiler import ProfilerActivity, profile
+    from paper_2211_05239_amd import recd
+    F, B, D, rows = 5, 6601, 32, 3000
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    tables = [torch.empty(rows, D, device="cuda").normal_(0.0, 0.5, generator=gen) for _ in range(F)]
+    batches = [_lists(F, B, 5, 8, rows), _lists(F, B, 5, 1, rows), _lists(F, B, 70, 1, rows), _lists(F, B, 1, 1, rows)]
+    out = torch.empty(F, B, D, device="cuda")
+    with profile(activities=[ProfilerActivity.CUDA]):
+        torch.cuda.synchronize()   # the profiler's own start is not measured
+    ctx, seen = recd.Context(0), []
+    for values, offsets in batches + batches[::-1]:
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            ctx.kjt_pooled_lookup(tables, B, values, offsets, out)
+            torch.cuda.synchronize()
+        seen.append([e.name for e in prof.events() if "k_" in e.name])
+        n = values.numel() // (F * B)
+        ref = torch.stack([tables[f][values.view(F, B, n)[f]].double().sum(1) for f in range(F)])
+        size = torch.stack([tables[f][values.view(F, B, n)[f]].double().abs().sum(1) for f in range(F)])
+        assert bool(((out.double() - ref).abs() <= n * 2.0 ** -24 * size).all())   # n fp32 additions
+    assert len(seen[0]) == 1 and all(x == seen[0] for x in seen), seen
+    ctx.close()

@@ -47,6 +47,25 @@ void deal(int64_t n, int F, int queues, int lpb, int64_t stride, const int64_t *
                 }
             }
 }
+
+// the same for a KJT lookup whose waves share sums; returns the items of the queue that has the most
+int64_t deal_items(int64_t n, int F, int queues, int lpb, int64_t stride, const int64_t *len, int64_t *work, int32_t *taken)
+{
+    const int log = recd_deal_log_kjt(n, F, queues, 31 - __builtin_clz(lpb));
+    const int64_t most = recd_deal_most(n, queues, log), whole = recd_whole_items(most, queues, lpb);
+    for (int q = 0; q < queues; q++)
+        for (int64_t b = 0; b < stride; b++)
+            for (int64_t i = b;; i += stride) {
+                const int64_t l0 = recd_dealt(recd_item_start(i, whole, lpb), q, queues, log);
+                if (l0 >= n)
+                    break;
+                for (int64_t l = l0; l < n && l < l0 + recd_item_lists(i, whole, lpb); l++) {
+                    taken[l]++;
+                    work[q] += len[l];
+                }
+            }
+    return recd_items(most, whole, lpb);
+}
 }
 """
 
@@ -140,6 +159,27 @@ def test_lookup_lists_of_any_number_are_all_dealt(rules, n):
     work, taken = np.zeros(8, dtype=np.int64), np.zeros(max(n, 1), dtype=np.int32)
     rules.deal(n, 8, 8, 4, 3, _ptr(lens), _ptr(work), _ptr(taken))
     assert (taken[:n] == 1).all() and work.sum() == n
+
+
+@pytest.mark.parametrize("n,F", [(32768, 16), (32769, 3), (65535, 5), (65536, 8), (100003, 7), (1 << 19, 64),
+                                 ((1 << 20) + 5, 8), (1030, 1), (9, 3)])
+@pytest.mark.parametrize("lpb", [2, 4, 8, 16])
+def test_items_of_several_and_of_two_lists_cover_every_list_once(rules, n, F, lpb):
+    """Whole items and the short ones behind them take every list once, also by fewer blocks than items, and as many
+    blocks a queue as the host launches are enough for one item each."""
+    rules.deal_items.restype = C.c_int64
+    rules.deal_items.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
+    lens = np.ones(n, dtype=np.int64)
+    for queues in (8, 1):
+        items = None
+        for stride in (3 * n, 1013):
+            work, taken = np.zeros(8, dtype=np.int64), np.zeros(n, dtype=np.int32)
+            items = rules.deal_items(n, F, queues, lpb, min(stride, items or stride), _ptr(lens), _ptr(work), _ptr(taken))
+            assert (taken == 1).all() and work.sum() == n
+        work, taken = np.zeros(8, dtype=np.int64), np.zeros(n, dtype=np.int32)
+        rules.deal_items(n, F, queues, lpb, items, _ptr(lens), _ptr(work), _ptr(taken))
+        assert (taken == 1).all() and items * 2 >= n // queues // lpb
+        assert items <= n // queues // lpb + 8192 // min(queues, 8) + 1024 // lpb + 2
 
 
 @pytest.mark.parametrize("n", [8, 50, 100, 300, 530, 1000, 4000, 8191, 8192, 20000, 1 << 19, (1 << 20) + 5])
