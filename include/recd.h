@@ -441,8 +441,8 @@ recd_status recd_last_ikjt_run_count(recd_ctx *ctx, int64_t *host_runs);
  *    fit 32: on the context's stream) and returns; if
  *    inverse and u_values are the outputs of the context's most recent call 1 / 16, the side stream
  *    starts where that build ended, so the plan runs next to calls 2 and 3 enqueued meanwhile on the
- *    context's stream; otherwise, and for the first plan after builds that no plan followed, it starts at the
- *    stream's current position.
+ *    context's stream; otherwise, and for the first plan after 16 such builds in a row that no plan followed, it
+ *    starts at the stream's current position.
  *    recd_backward_apply makes the stream wait for the plan and runs the two segment sums (and the
  *    optimizer) exactly as call 5 / call 15 would: same kernels, same results bit for bit.
  *    Between the two calls the context's workspace holds the plan: no other call that uses the

@@ -1165,8 +1165,7 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
         from = nullptr;
     else if (ctx->build_valid && ws_idle_since_build && ctx->built_inverse == inverse &&
         ctx->built_u_values == u_values && n_lists > 0) {
-        ctx->ev_built_wanted = ctx->ev_built_used = true;
-        if (ctx->ev_built_recorded)
+        if (ctx->build_event.at_plan())
             from = ctx->ev_built;
     }
     if (from == ctx->ev_fork)

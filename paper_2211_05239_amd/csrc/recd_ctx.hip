@@ -32,15 +32,12 @@ recd_status recd_check_rows(recd_ctx *ctx, int F, const int64_t *rows)
 
 recd_status recd_mark_build(recd_ctx *ctx, int F, int64_t B, int64_t N, const int32_t *inverse, const int64_t *u_values)
 {
-    if (ctx->ev_built_recorded && !ctx->ev_built_used)
-        ctx->ev_built_wanted = false;  // until a plan asks for one again
-    ctx->ev_built_recorded = false;
-    ctx->ev_built_used = false;
     ctx->built_inverse = inverse;
     ctx->built_u_values = u_values;
-    if (ctx->ev_built_wanted && !recd_group_is_short(F, B, N)) {
+    if (ctx->build_event.at_build(!recd_group_is_short(F, B, N))) {
+        ctx->build_event.recorded = false;
         RECD_HIP(ctx, hipEventRecord(ctx->ev_built, ctx->stream));
-        ctx->ev_built_recorded = true;
+        ctx->build_event.recorded = true;
     }
     return RECD_OK;
 }

@@ -41,9 +41,7 @@ struct recd_ctx {
     // side stream from the end of the last build on, next to the forward calls.
     hipEvent_t ev_built = nullptr;  // end of the most recent plain / weighted build
     hipEvent_t ev_plan = nullptr;   // end of the plan
-    // ev_built is recorded only where a plan may start at it, since a record costs the kernel behind it 3 to 6 us: not for
-    // batches whose plan goes in line, nor once a build's event was not used (recd_mark_build).
-    bool ev_built_recorded = false, ev_built_used = false, ev_built_wanted = true;
+    RecdBuildEvent build_event;     // whether there is one
     const void *built_inverse = nullptr, *built_u_values = nullptr;  // outputs of that build
     // A call that uses the workspace has been enqueued on the context's stream since that build (set
     // by recd_reserve, cleared by the builder): a plan must then start at the stream's current

@@ -113,3 +113,27 @@ RECD_RULE int recd_jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vec
 // that overlaps may give wrong numbers there, but as it clears the words that the blocks of the other wait for, neither
 // might return.
 RECD_RULE bool recd_looks_back(int64_t rows, bool shared_scratch) { return !shared_scratch && rows <= 256 * 1024; }
+
+// Whether a build records the event that a plan beside the forward calls starts at.  The record costs the kernel behind it
+// 3 to 6 us, a plan without one up to some 90 us that the forward calls would hide: as many unused events as make up for one
+// such plan are recorded before a context stops, until a plan asks for one again.  So plans that come after one build or
+// after a few (two batches a step, an evaluation between) find theirs, and a context that only evaluates pays for 16.
+struct RecdBuildEvent {
+    int unused = 0;          // events in a row that no plan waited for
+    bool recorded = false;   // of the last build
+    bool used = false;
+    bool at_build(bool plans_beside)  // whether this build records one
+    {
+        if (recorded && !used && unused < 16)
+            unused++;
+        recorded = plans_beside && unused < 16;
+        used = false;
+        return recorded;
+    }
+    bool at_plan()  // of the last build, beside the forward calls: whether there is one
+    {
+        used = true;
+        unused = 0;
+        return recorded;
+    }
+};

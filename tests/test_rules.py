@@ -13,6 +13,20 @@ HARNESS = r"""
 extern "C" {
 int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vecs) { return recd_jagged_lists(N, U_cap, M_cap, vecs, 256); }
 bool looks_back(int64_t rows, bool shared) { return recd_looks_back(rows, shared); }
+
+// a build per character of `steps`: p: a plan follows it, -: none, s: a short one; says of each p whether it had an event
+// (counted) and of every build whether it recorded one
+int events(const char *steps, int *records)
+{
+    RecdBuildEvent e;
+    int had = 0;
+    for (; *steps; steps++) {
+        *records += e.at_build(*steps != 's');
+        if (*steps == 'p')
+            had += e.at_plan();
+    }
+    return had;
+}
 int64_t lists_held(int64_t F, int64_t B, int64_t U_cap, int64_t M_cap) { return recd_lists_held(F, B, U_cap, M_cap); }
 
 // starts[slot] and how often each was written, of n >= 1 sorted keys; returns the writes outside [0, slots)
@@ -91,6 +105,19 @@ def test_room_for_every_unique_list(rules):
     assert rules.lists_held(5, 600, 3000, 10 ** 9) == 3000
     assert rules.lists_held(5, 600, 7, 40) == 45           # no fewer than a plain IKJT of M_cap ids can have
     assert rules.lists_held(5, 600, 10 ** 9, 40) == 3000
+
+
+@pytest.mark.parametrize("steps", ["p" * 9, "-p" * 9, "p-" * 9, "--p" * 9, "s-p" * 9, "p" + "-" * 15 + "p" + "-" * 15 + "p",
+                                   "-" * 100 + "ppp", "s" * 100 + "p", "-" * 100])
+def test_plans_find_the_event_of_their_build(rules, steps):
+    """Every plan starts where its build ended, whatever builds without a plan lie between, unless these are 16 and
+    more in a row; builds that no plan ever follows record 16 events and no more."""
+    records = C.c_int(0)
+    rules.events.argtypes = [C.c_char_p, C.c_void_p]
+    had = rules.events(steps.encode(), C.byref(records))
+    many = "-" * 16 in steps
+    assert had == steps.count("p") - many * ("p" in steps)
+    assert records.value == (16 + max(steps.count("p") - 1, 0) if many else len(steps) - steps.count("s"))
 
 
 def test_no_wait_between_blocks_on_shared_scratch(rules):
