@@ -436,8 +436,8 @@ recd_status recd_last_ikjt_run_count(recd_ctx *ctx, int64_t *host_runs);
 
 /* 21, 22. Call 5 in two halves.  What the backward does before it touches a gradient (keys, the two
  *    stable sorts, the numbering of the segments, touched_rows and feat_roff) depends on the IKJT
- *    alone.  recd_backward_plan enqueues that half on the context's side stream (with F*B and M_cap of at
- *    most 2^19, or M_cap and B of at most 8192 and bits of the largest row number and of the feature number that
+ *    alone.  recd_backward_plan enqueues that half on the context's side stream (with F*B + M_cap of at
+ *    most 480 K, or M_cap and B of at most 8192 and bits of the largest row number and of the feature number that
  *    fit 32: on the context's stream) and returns; if
  *    inverse and u_values are the outputs of the context's most recent call 1 / 16, the side stream
  *    starts where that build ended, so the plan runs next to calls 2 and 3 enqueued meanwhile on the

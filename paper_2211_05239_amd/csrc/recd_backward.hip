@@ -1156,7 +1156,7 @@ static recd_status plan_common(recd_ctx *ctx, int F, int64_t B, int D, const int
     pl.empty = n_lists == 0 || M_cap == 0;
     // A short grouping costs less on the stream itself than the events that would take it to the side stream and back.
     hipStream_t st = ctx->stream;
-    const bool own_stream = pl.empty || recd_group_is_small(F, B, M_cap, max_rows) || recd_group_is_short(F, B, M_cap);
+    const bool own_stream = pl.empty || recd_group_is_small(F, B, M_cap, max_rows) || recd_grouping_is_short((int64_t)F * B, M_cap);
     hipStream_t side = own_stream ? st : ctx->side_stream;
     // Where the side stream may start: at the end of the build that produced this IKJT if it is the
     // context's most recent one, else at the main stream's current position.

@@ -34,7 +34,7 @@ recd_status recd_mark_build(recd_ctx *ctx, int F, int64_t B, int64_t N, const in
 {
     ctx->built_inverse = inverse;
     ctx->built_u_values = u_values;
-    if (ctx->build_event.at_build(!recd_group_is_short(F, B, N))) {
+    if (ctx->build_event.at_build(!recd_grouping_is_short((int64_t)F * B, N))) {
         ctx->build_event.recorded = false;
         RECD_HIP(ctx, hipEventRecord(ctx->ev_built, ctx->stream));
         ctx->build_event.recorded = true;

@@ -39,12 +39,12 @@ constexpr int kMaxPasses = 4;
 constexpr int kQueues = 8;
 constexpr int kMostChunks = 512;
 constexpr int kSumChunks = 16;
-// Small tiles (sweep_small_tiles): a side of at most kSmallTilesMost entries whose features have at most
-// kSmallTilesPer of them each.
+// Small tiles (sweep_small_tiles): both sides of a short grouping (recd_grouping_is_short), where the features have at most
+// kSmallTilesPer tiles each.
 constexpr int kSmallItems = 2;
 constexpr int kSmallTile = kTileThreads * kSmallItems;
 constexpr int kSmallTilesPer = 32;
-constexpr int64_t kSmallTilesMost = 1 << 19;
+constexpr int64_t kSmallTilesMost = 480 << 10;  // entries of a side
 static_assert(kTile % kSmallTile == 0 && kSmallTilesPer * kSmallTile < 1 << 16, "counts of other tiles are 16 bits");
 static_assert(kMostChunks + 2 * RECD_MAX_FEATURES + 1 <= RECD_GROUP_ARRIVE, "a counter for every feature and every chunk");
 
@@ -1415,11 +1415,6 @@ bool recd_group_is_small(int F, int64_t B, int64_t M_cap, int64_t max_rows)
                                                            bits_for((uint64_t)(F > 1 ? F - 1 : 1)) <= 32;
 }
 
-bool recd_group_is_short(int F, int64_t B, int64_t M_cap)
-{
-    return (int64_t)F * B <= kSmallTilesMost && M_cap <= kSmallTilesMost;
-}
-
 const uint32_t *recd_group_rows(const RecdGroupWs &w, int F, int64_t B, int64_t U_cap, int64_t M_cap, int64_t max_rows)
 {
     int passes, dbits;
@@ -1469,8 +1464,8 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     side(g.a, w.a, slot_bits(a.B, a.U_cap), g.n_lists, ctx->group_arrive);
     side(g.b, w.b, bits_for((uint64_t)(a.max_rows > 1 ? a.max_rows - 1 : 1)), a.M_cap, ctx->group_arrive + RECD_GROUP_ARRIVE);
     g.tpf = (int)((a.B + kTile - 1) / kTile);
-    g.small_a = g.n_lists <= kSmallTilesMost && a.B <= kSmallTilesPer * kSmallTile;
-    g.small_b = a.M_cap <= kSmallTilesMost;
+    g.small_b = recd_grouping_is_short(g.n_lists, a.M_cap);
+    g.small_a = g.small_b && a.B <= kSmallTilesPer * kSmallTile;
     const int64_t chunk_a = g.small_a ? kSmallTile : g.a.chunk, chunk_b = g.small_b ? kSmallTile : g.b.chunk;
     g.cpf = (int)((a.B + chunk_a - 1) / chunk_a);
     g.pb = w.pb;

@@ -269,10 +269,6 @@ struct RecdGroupArgs {
 enum { RECD_GROUP_RUNS = 1, RECD_GROUP_LISTS = 2 };
 RecdGroupWs recd_group_carve(WsCarver &c, int F, int64_t B, int64_t M_cap);
 recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, const RecdGroupArgs &a);
-// Whether a plan is so short that it goes in line: the events that take it to the side stream and back cost the host some
-// 45 us and the device what the forward calls would hide of it (step of 65 K lists and 0.19 M ids: 150 us either way,
-// of which the host waits 42 us with the plan beside, 95 in line).
-bool recd_group_is_short(int F, int64_t B, int64_t M_cap);
 // Whether both sides are grouped by one launch.
 bool recd_group_is_small(int F, int64_t B, int64_t M_cap, int64_t max_rows);
 // The payload buffers that hold the result for these sizes.

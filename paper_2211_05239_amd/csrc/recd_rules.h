@@ -114,6 +114,15 @@ RECD_RULE int recd_jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vec
 // might return.
 RECD_RULE bool recd_looks_back(int64_t rows, bool shared_scratch) { return !shared_scratch && rows <= 256 * 1024; }
 
+// Whether the grouping of a backward pass is short: its sides go by small tiles, and a plan goes in line, since the events
+// that take it to the side stream and back cost more than the forward calls would hide of it.  480 K entries of both sides
+// are fewer than two small tiles a CU; beyond that the chip is full either way and what the small tiles count again is
+// lost.  Training step, us, F*B / M_cap in K, elements a row: beside by tiles of 4096 / in line by small tiles: 65 / 160,
+// 128: 147 / 125; 180 / 180, 32: 150 / 138; 299 / 150, 64: 201 / 195; 376 / 84, 128: 241 / 239; 175 / 325, 128: 195 / 206;
+// 325 / 175, 128: 241 / 249; 400 / 100, 64: 251 / 258; 494 / 248, 64: 218 / 240.  (Small tiles beside: 65 / 160, 128: 133;
+// 256 / 256, 128: 216, in line 220, of 4096 beside 213.)
+RECD_RULE bool recd_grouping_is_short(int64_t rows, int64_t M_cap) { return rows + M_cap <= 480 * 1024; }
+
 // Whether a build records the event that a plan beside the forward calls starts at.  The record costs the kernel behind it
 // 3 to 6 us, a plan without one up to some 90 us that the forward calls would hide: as many unused events as make up for one
 // such plan are recorded before a context stops, until a plan asks for one again.  So plans that come after one build or

@@ -67,8 +67,10 @@ CASES = [
     ([32768, 1, 1024, 0, 3073], 32768, 2000, (1 << 20) + 1, True),
     ([32769, 2000], 32769, 2000, 1 << 20, True),
     ([30000, 0, 900], 1024, 300, 200, True),
-    ([20164] * 26, 700, 650, 3000, True),    # just below the most ids that a side in small tiles may have
-    ([20165] * 26, 700, 650, 3000, True),    # and just beyond
+    ([20164] * 26, 700, 650, 3000, True),    # ids alone beyond what both sides in small tiles may have
+    ([20165] * 26, 700, 650, 3000, True),
+    ([18204] * 26, 700, 650, 3000, True),    # just below it with the rows (480 K, and M_cap is three more than the ids)
+    ([18205] * 26, 700, 650, 3000, True),    # and just beyond
 ]
 
 

@@ -12,6 +12,7 @@ HARNESS = r"""
 #include "recd_rules.h"
 extern "C" {
 int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vecs) { return recd_jagged_lists(N, U_cap, M_cap, vecs, 256); }
+bool short_grouping(int64_t rows, int64_t M_cap) { return recd_grouping_is_short(rows, M_cap); }
 bool looks_back(int64_t rows, bool shared) { return recd_looks_back(rows, shared); }
 
 // a build per character of `steps`: p: a plan follows it, -: none, s: a short one; says of each p whether it had an event
@@ -105,6 +106,15 @@ def test_room_for_every_unique_list(rules):
     assert rules.lists_held(5, 600, 3000, 10 ** 9) == 3000
     assert rules.lists_held(5, 600, 7, 40) == 45           # no fewer than a plain IKJT of M_cap ids can have
     assert rules.lists_held(5, 600, 10 ** 9, 40) == 3000
+
+
+def test_short_groupings_fit_the_chip(rules):
+    """Small tiles and plans in line up to fewer than two tiles of 1024 entries a CU, of both sides together."""
+    rules.short_grouping.restype = C.c_bool
+    rules.short_grouping.argtypes = [C.c_int64, C.c_int64]
+    assert rules.short_grouping(65536, 425984) and not rules.short_grouping(65536, 425985)
+    assert rules.short_grouping(425984, 65536) and not rules.short_grouping(1 << 19, 0)
+    assert not rules.short_grouping(1 << 18, 1 << 18) and not rules.short_grouping(1 << 19, 1 << 19)
 
 
 @pytest.mark.parametrize("steps", ["p" * 9, "-p" * 9, "p-" * 9, "--p" * 9, "s-p" * 9, "p" + "-" * 15 + "p" + "-" * 15 + "p",
