@@ -119,6 +119,21 @@ def test_grouped_singletons_equal_ungrouped(ctx):
     assert torch.equal(ik.feat_uoff, ref.feat_uoff) and torch.equal(ik.group_uoff, ref.feat_uoff)
 
 
+@pytest.mark.parametrize("F,B", [(7, 11000), (8, 32768), (8, 32769), (32, 8193)])
+def test_build_of_many_blocks(ctx, F, B):
+    """Lists in more blocks of 1024 than a wave looks back over at a time, up to the most lists that are numbered by
+    look-back and just beyond: the grouped and the plain builder against the oracle, and sizes in turn on one context."""
+    w = synth.scaled(synth.WORKLOADS["cfg1"], F=F, B=B, rows=700)
+    batch = synth.make_batch(w, 0)
+    print(f"{F} x {B} lists, {batch.N} ids", flush=True)
+    groups = [0, 1, 4, F]
+    _, _, ik = gpu_build_grouped(ctx, batch, groups)
+    _check_grouped(ik, batch, groups)
+    _, _, plain = gu.gpu_build(ctx, batch)
+    for got, want in zip(plain.numpy(), orc.build_ikjt(F, B, batch.values, batch.offsets)):
+        assert np.array_equal(got, want)
+
+
 def test_grouped_empty_sizes_and_errors(ctx, recd):
     kjt = synth.batch_from_lists([[], []])  # F = 2, B = 0
     _, _, ik = gpu_build_grouped(ctx, kjt, [0, 2])
