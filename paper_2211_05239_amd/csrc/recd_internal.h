@@ -101,7 +101,7 @@ struct recd_ctx {
     KernelTimer timers[RECD_T_COUNT];
     int validate = 0;
     int weak_hash = 0;
-    int tune_lb = 0, tune_gens = 0, tune_flat = 0;  // launch-shape overrides of the gather-sum kernel (0 = automatic)
+    int tune_lb = 0, tune_gens = 0, tune_flat = 0, tune_no_runs = 0;  // launch-shape overrides of the gather-sum kernel (0 = automatic)
     int num_cu = 256;
     // feature groups of the last grouped call, kept on the device: [0, G] boundaries, then the
     // group of every feature from RECD_MAX_FEATURES + 1 on
@@ -113,7 +113,7 @@ struct recd_ctx {
 // Not part of the public interface: launch-shape override of the gather-sum kernel, used by the
 // tuning runs and by the test that shows results do not depend on the launch shape.
 //   value = lists per block (1, 2, 4, 8 or 16) + 10000 * block generations per CU (< 100)
-//           + 1000000 * (1 = no XCD-aware block mapping); 0 = automatic
+//           + 1000000 * (1 = no XCD-aware block mapping, 2 = the KJT lookup sums every list by itself); 0 = automatic
 #define RECD_OPT_INTERNAL_TUNE_SEGSUM 1003
 // value != 0: bracket the kernels named by RECD_T_* with HIP events (see recd_internal_kernel_ms)
 #define RECD_OPT_INTERNAL_TIMING 1004

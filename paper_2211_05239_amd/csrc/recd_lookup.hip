@@ -1060,7 +1060,7 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     // Plain / 4 / 8 lists a wave, us, rows of 512 bytes, sessions of 8 and none: 32 K lists of 5 ids 17 / 15 / 14 and
     // 21 / 22 / 21, of 24 27 / 22 / 25 and 68 / 70 / 73; 64 K of 5 30 / 22 / 19 and 38 / 35 / 35, of 24 47 / 35 / 36 and
     // 134 / 143 / 151.  16 K, sessions of 8, plain / 4: of 5 10.9 / 10.3, of 64 33 / 39.
-    const bool runs = a.site == RECD_SITE_KJT && (ctx->tune_lb == 0 ? n >= kRunsLists : ctx->tune_lb > 1);
+    const bool runs = a.site == RECD_SITE_KJT && !ctx->tune_no_runs && (ctx->tune_lb == 0 ? n >= kRunsLists : ctx->tune_lb > 1);
     if (runs && ctx->tune_lb == 0)
         p.lb = lb = n >= 2 * kRunsLists ? 8 : 4;
     p.deal_log = recd_deal_log_kjt(n, a.F, kNQ, 31 - __builtin_clz(lb));

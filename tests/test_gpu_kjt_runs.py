@@ -52,7 +52,7 @@ def test_runs_of_equal_lists(F, B, run, D, dtype):
     calls.append(lambda o: ctx.kjt_pooled_lookup_weighted(tables, B, values, weights, offsets, o))
     for call in calls:
         got = {}
-        for lists_a_block in (1, 0, 2, 4, 8, 16):
+        for lists_a_block in (1, 0, 2, 4, 8, 16, 2_000_000):   # the last: no shared sums, the blocks as they come
             ctx.set_option(recd._OPT_INTERNAL_TUNE_SEGSUM, lists_a_block)
             got[lists_a_block] = torch.full((F, B, D), float("nan"), dtype=dt, device="cuda")
             call(got[lists_a_block])
