@@ -519,14 +519,22 @@ void k_segsum(const SegSumParams p)
                 // lanes to a list, sums the first of every run of equal ones and stores its row for the whole run: the same
                 // ids in the same order give the same bits.  What bounds the lookup is the gathered rows, and those of a run
                 // are gathered once; with the ids at hand the other lists cost a wave a round trip less than one by one, which
-                // pays for the comparison where it finds nothing.  us, by the plain kernel / by this one, 262 K lists:
-                // sessions of 8, 64 ids, rows of 512 bytes 522 / 303, of 64 bytes 172 / 81; 5 ids 87 / 46, 101 / 49;
-                // no sessions, 5 ids 140 / 137, 107 / 103; 64 ids 1154 / 1190, 240 / 286 (the last is the worst: tables
-                // about as large as an L2, of which 7 K waves of 8 lists use more at a time than those of 2).
+                // pays for the comparison where it finds nothing.  us, by the plain kernel / by this one, 262 K lists, ids
+                // uniform: sessions of 8, 64 ids, rows of 512 bytes 522 / 303, of 64 bytes 172 / 81; 5 ids 87 / 46, 101 / 49;
+                // no sessions, 5 ids 140 / 137, 107 / 103; 64 ids 1451 / 1578, tables of 20 K rows 993 / 1140.
+                // On average over 64 K to 1.05 M even lists without sessions as fast as the plain kernel, but slower by up to
+                // 40 % where lists are long and tables about as large as an L2 (7 K waves of 8 lists use more tables at a time
+                // than those of 2; 64 ids of 64-byte rows, 64 K rows 177 / 250, skewed ids 165 / 162), and wherever a few
+                // features have by far the longest lists, of which 8 in one wave outlast the rest: one of 32 features with
+                // half of the ids 668 / 931, skewed ids 442 / 790, sessions of 8 516 / 443; 130 K lists of 26 features, 64-byte
+                // rows, sessions of 2 118 / 287.
                 // (Each wave's lists compared in memory, ids read again by the sums: no sessions, 64 ids of 64-byte
                 // rows 290, sessions 107.  Runs that go on into other waves' lists, with those left out there: 485 for
                 // 303.  Four waves a block: its slots are free only when the last is done; sessions of 5 ids 62 for 46.
-                // A kernel before this one to look whether the batch has sessions: 3 us of 14 to 60.)
+                // A kernel before this one that looks at 128 pairs of neighbours, and waves of 2 or 8 lists by what it found:
+                // 64 K lists of 5 ids, sessions / none 16 / 35 -> 28 / 41, 262 K 39 / 105 -> 60 / 121.  2048 blocks before these
+                // that take the lists of such features two by two: those 931 -> 809, 287 -> 141, but short lists 15.4 -> 16.5,
+                // of 64-byte rows 38 -> 43, most of it for the waves' question whether their lists are among them.)
                 const int64_t base = uniform64(s_start[0]), held = uniform64(s_end[cnt - 1]) - base;
                 const int staged = (int)(held < kStage ? held : kStage);
                 int ln = lane;
