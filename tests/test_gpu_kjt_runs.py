@@ -35,7 +35,7 @@ def _batch(seed, n_lists, rows, run):
     return np.concatenate(lists), np.concatenate(weights), offsets
 
 
-# below and above the number of lists that are sampled, odd numbers of lists a feature; long and short runs
+# below and above the number of lists from which waves share sums, odd numbers of lists a feature; long and short runs
 @pytest.mark.parametrize("F,B,run,D,dtype", [(3, 341, 6, 64, "f32"), (5, 6601, 8, 20, "f32"), (9, 11003, 8, 64, "bf16"),
                                              (5, 6601, 1, 32, "f16"), (2, 16411, 40, 512, "f32")])
 def test_runs_of_equal_lists(F, B, run, D, dtype):
@@ -143,4 +143,45 @@ def test_way_depends_on_the_sizes_alone():
         size = torch.stack([tables[f][values.view(F, B, n)[f]].double().abs().sum(1) for f in range(F)])
         assert bool(((out.double() - ref).abs() <= n * 2.0 ** -24 * size).all())   # n fp32 additions
     assert len(seen[0]) == 1 and all(x == seen[0] for x in seen), seen
+    ctx.close()
+
+
+@pytest.mark.parametrize("D,dtype", [(64, torch.float32), (16, torch.bfloat16)])
+def test_runs_of_lists_around_what_a_wave_stages(D, dtype):
+    """Lists that end before, at and behind the 1024 ids that wait in LDS, begin behind them, or are longer by themselves;
+    one in four differs from its neighbour in one id or weight, also at these ids."""
+    from paper_2211_05239_amd import recd
+    F, B, rows = 3, 167, 2000
+    rng = np.random.default_rng(D)
+    lists, weights = [], []
+    while len(lists) < F * B:
+        n = int(rng.choice([0, 1, 127, 128, 129, 511, 512, 513, 1023, 1024, 1025, 2500]))
+        ids, wts = rng.integers(0, rows, n), rng.choice([0.5, 1.0, 2.0], n).astype(np.float32)
+        for _ in range(int(rng.integers(1, 7))):
+            x, w = ids.copy(), wts.copy()
+            if n and rng.random() < 0.25:
+                at = int(rng.choice([0, n - 1, min(n - 1, 511), min(n - 1, 512), min(n - 1, 1023), min(n - 1, 1024)]))
+                if rng.random() < 0.5:
+                    x[at] = (x[at] + 1) % rows
+                else:
+                    w[at] = -w[at]
+            lists.append(x)
+            weights.append(w)
+    lists, weights = lists[:F * B], weights[:F * B]
+    off = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    values, wts = torch.from_numpy(np.concatenate(lists).astype(np.int64)).cuda(), torch.from_numpy(np.concatenate(weights)).cuda()
+    offsets = torch.from_numpy(off).cuda()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    tables = [torch.empty(rows, D, dtype=dtype, device="cuda").normal_(0.0, 0.5, generator=gen) for _ in range(F)]
+    ctx = recd.Context(0)
+    for call in (lambda o: ctx.kjt_pooled_lookup(tables, B, values, offsets, o),
+                 lambda o: ctx.kjt_pooled_lookup_weighted(tables, B, values, wts, offsets, o)):
+        got = {}
+        for lists_a_block in (1, 2, 4, 8, 16):   # one: every list by itself
+            ctx.set_option(recd._OPT_INTERNAL_TUNE_SEGSUM, lists_a_block)
+            got[lists_a_block] = torch.full((F, B, D), float("nan"), dtype=dtype, device="cuda")
+            call(got[lists_a_block])
+        for lists_a_block, out in got.items():
+            assert torch.equal(out, got[1]), lists_a_block
     ctx.close()
