@@ -3,8 +3,8 @@
 // Steps, all on the device, no host round trip:
 //   hash+insert  a group of SG lanes per list.  A list equal to its predecessor in the batch (the
 //                common case once a session's samples are adjacent, Sec. 4.1) is only marked as a
-//                follower.  Any other list is a run head: its 64-bit hash (position-salted sum of mixed
-//                ids, so lanes hash strided pairs of ids and add) is inserted by open addressing into a
+//                follower.  Any other list is a run head: its 64-bit hash (a sum over pairs of ids that depends
+//                on their positions, so lanes hash strided pairs and add) is inserted by open addressing into a
 //                per-feature table whose slots hold (hash tag, sample index).  A slot belongs to one
 //                list *content*: a newcomer whose tag matches compares its list element by element
 //                with the slot's current sample and, if equal, lowers the slot's sample index with
@@ -33,16 +33,6 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x)
     return x;
 }
 
-// One list element's share of the list hash: cheaper than mix64 (one 64-bit multiply; the
-// multiplies are most of the insert kernel's arithmetic), enough because the per-list sum of the
-// terms goes through mix64 once more and an exact comparison follows every tag match anyway.
-__device__ __forceinline__ uint64_t hash_term(uint64_t x)
-{
-    x ^= x >> 31;
-    x *= 0xbf58476d1ce4e5b9ull;
-    return x ^ (x >> 29);
-}
-
 __global__ void k_copy_i64(const int64_t *src, int64_t *dst) { *dst = *src; }
 
 __global__ void k_fill_u64(uint64_t *p, int64_t n, uint64_t v)
@@ -52,200 +42,205 @@ __global__ void k_fill_u64(uint64_t *p, int64_t n, uint64_t v)
         p[i] = v;
 }
 
-// Lists per lane group and launch: the group's lists are consecutive, and the first loads of all of
-// them are issued together so that one group keeps several memory requests in flight.
-constexpr int kLPG = 1;
-constexpr int kHU = 2;   // strides of the long-list loop whose loads are issued together
-constexpr int kFirst = 3;  // strides of a list loaded up front
-// Threads per block of the insert kernel: one wave.  Lists of 1 to 256 ids finish at different times
+// Threads per block of the insert kernels: one wave.  Lists of 1 to 256 ids finish at different times
 // and a block's wave slots are free again only when its last wave is done (0.158 -> 0.149 ms).
 constexpr int kHashBlock = 64;
-// two adjacent ids; lists start on 8-byte boundaries only (global loads need no more)
+constexpr int kFirst = 3;  // strides of a list that are in flight together with those of its predecessor
+constexpr int kHU = 2;     // strides of the loops over what lies beyond them
+// two adjacent ids, two adjacent weights; lists start on 8- and 4-byte boundaries only (global loads need no more)
 typedef long long id2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef uint32_t wt2 __attribute__((ext_vector_type(2), aligned(4)));
 
-// An id and (WT) the bit pattern of its weight as one hash input.
-template <bool WT>
-__device__ __forceinline__ uint64_t hash_item(int64_t id, uint32_t wbits)
+// An id and the bit pattern of its weight (0: there are none) as 32 bits of hash input.
+__device__ __forceinline__ uint32_t hash_word(long long id, uint32_t wbits)
 {
-    return WT ? (uint64_t)id + (uint64_t)wbits * 0xc2b2ae3d27d4eb4full : (uint64_t)id;
+    const uint32_t hi = (uint32_t)((uint64_t)id >> 32);
+    return (uint32_t)id ^ ((hi << 9) | (hi >> 23)) ^ (wbits * 0x85ebca6bu);
 }
 
-// WT: the lists carry one weight per id (wbits: their bit patterns); two lists are the same only if
-// the weights agree too, so they enter the hash and every comparison.
+__device__ __forceinline__ uint32_t hash_key(uint32_t t)
+{
+    const uint32_t k = (t + 1) * 0x9e3779b1u;
+    return k ^ (k >> 15);
+}
+
+// What two adjacent ids, at positions t and t + 1, add to their list's hash: one product of 32 by 32 bits (two of 64 by 64
+// before).  That is enough: the sum goes through mix64 once a list, and an exact comparison follows every tag match.
+__device__ __forceinline__ uint64_t hash_pair(uint32_t a, uint32_t b, uint32_t t)
+{
+    return (uint64_t)(a + hash_key(t)) * (b + hash_key(t + 1));
+}
+
+// Two adjacent ids and their weights at position t, of n >= 2 from there on; at a list's odd end the last two.
+template <bool WT> struct IdPair {
+    id2 v = {0, 0};
+    wt2 w = {0, 0};
+    template <typename T> __device__ __forceinline__ void load(const int64_t *ids, const uint32_t *wbits, T t, T n)
+    {
+        const T at = t + 1 < n ? t : n - 2;
+        v = *reinterpret_cast<const id2 *>(ids + at);
+        if (WT)
+            w = *reinterpret_cast<const wt2 *>(wbits + at);
+    }
+    __device__ __forceinline__ void load_only(const int64_t *ids, const uint32_t *wbits)
+    {
+        v.x = v.y = ids[0];
+        if (WT)
+            w.x = w.y = wbits[0];
+    }
+    __device__ __forceinline__ uint64_t differ(const IdPair &o) const
+    {
+        uint64_t d = (uint64_t)((v.x ^ o.v.x) | (v.y ^ o.v.y));
+        if (WT)
+            d |= (w.x ^ o.w.x) | (w.y ^ o.w.y);
+        return d;
+    }
+    template <typename T> __device__ __forceinline__ uint64_t hash(T t, T n) const  // of a list of n
+    {
+        const bool both = t + 1 < n;
+        const uint32_t x = hash_word(v.x, w.x), y = hash_word(v.y, w.y);
+        return hash_pair(both ? x : y, both ? y : 0u, (uint32_t)t);
+    }
+};
+
+// SG lanes to a list.  A list is compared with its predecessor first, and only one that differs (in a batch that is ordered
+// by sessions a small part) is hashed, of its first strides what the registers hold, of the rest by a second look.
+// WT: the lists carry one weight per id (wbits: their bit patterns); two lists are the same only if the weights agree too,
+// so they enter the hash and every comparison.
+// Hashing every list by two 64-bit products a pair and dividing row numbers in 64 bits took 288 vector instructions a wave of
+// 8 lists, 79 % of the issue slots; now 176, 53 % (35 M ids in 1.05 M lists 91 -> 80 us, 1.8 M in 130 K 12.8 -> 10.5).  What is
+// left is two round trips a list, a third and fourth for longer lists and run heads.  A stream of the same bytes takes 46 us.
+// Tried, no faster: predecessors out of the neighbouring lanes, two to eight lists a group, 4 lanes to a list, 32 to 96 ids
+// in flight, the offsets of later blocks fetched ahead into L2.
 template <int SG, bool WT>
 __global__ __launch_bounds__(kHashBlock) void k_hash_insert(const int64_t *__restrict__ values,
                                                      const uint32_t *__restrict__ wbits,
-                                                     const int64_t *__restrict__ offsets, int64_t B,
-                                                     int64_t n_lists, uint64_t *table,
+                                                     const int64_t *__restrict__ offsets, RecdDiv rows,
+                                                     uint32_t n_lists, uint64_t *table,
                                                      uint32_t cap_mask, int32_t *__restrict__ slot_of,
                                                      int weak_hash)
 {
-    const int s = threadIdx.x % SG;
+    constexpr int kStride = 2 * SG, kHead = kFirst * kStride;
+    const int lane = threadIdx.x, s = lane % SG;
     // Blocks go to the eight XCDs in turn; every XCD takes a contiguous eighth of the lists, so that
     // the predecessor of a block's first list, and the cache lines that neighbouring lists share,
     // were fetched by the block before it through the same L2 (with neighbouring blocks on different
-    // XCDs the kernel fetched 1.3 times the ids from memory).
-    const int64_t per_xcd = ((int64_t)gridDim.x + 7) / 8;
-    const int64_t blk = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    const int64_t l0 = (blk * (kHashBlock / SG) + threadIdx.x / SG) * kLPG;
-    if (blk >= (int64_t)gridDim.x || l0 >= n_lists)
+    // XCDs the kernel fetched 1.3 times the ids from memory).  The grid is a multiple of 8 blocks.
+    const uint32_t blk = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const uint32_t l = blk * (kHashBlock / SG) + lane / SG;
+    if (l >= n_lists)
         return;  // whole lane group leaves together
+    const uint32_t f = rows.of(l), b = l - f * rows.by;
+    const id2 ends = *reinterpret_cast<const id2 *>(offsets + l);
+    const int64_t before = offsets[b != 0 ? l - 1 : l];
+    const int64_t len = ends.y - ends.x;
+    // the previous row of the same feature ends where this one starts
+    const bool alike = b != 0 && ends.x - before == len && len < INT32_MAX;  // a longer one goes by the table
+    const int64_t *ids = values + ends.x, *pids = values + before;
+    const uint32_t *wts = WT ? wbits + ends.x : nullptr, *pwts = WT ? wbits + before : nullptr;
+    const int n = len < kHead ? (len > 0 ? (int)len : 0) : kHead;
 
-    // offsets of rows l0-1 .. l0+kLPG (clamped to the array)
-    int64_t off[kLPG + 2];
+    // A lane takes two adjacent ids (and weights) per stride, one 16-byte load.  The first kFirst strides of the list and of
+    // its predecessor are in flight together.
+    IdPair<WT> own[kFirst], prev[kFirst];
 #pragma unroll
-    for (int k = 0; k < kLPG + 2; k++) {
-        int64_t i = l0 - 1 + k;
-        i = i < 0 ? 0 : (i > n_lists ? n_lists : i);
-        off[k] = offsets[i];
+    for (int u = 0; u < kFirst; u++) {
+        const int t = 2 * s + u * kStride;
+        if (t < n && n > 1) {
+            own[u].load(ids, wts, t, n);
+            if (alike)
+                prev[u].load(pids, pwts, t, n);
+        }
     }
-    int64_t start[kLPG], len[kLPG], pstart[kLPG];
-    int follows[kLPG];
-    bool live[kLPG];
-    uint64_t h[kLPG];
-#pragma unroll
-    for (int k = 0; k < kLPG; k++) {
-        const int64_t l = l0 + k;
-        live[k] = l < n_lists;
-        start[k] = off[k + 1];
-        len[k] = live[k] ? off[k + 2] - off[k + 1] : 0;
-        pstart[k] = off[k];
-        // the previous row of the same feature ends where this one starts
-        follows[k] = live[k] && (l % B) != 0 && (start[k] - pstart[k]) == len[k];
-        h[k] = 0;
+    if (n == 1 && s == 0) {
+        own[0].load_only(ids, wts);
+        if (alike)
+            prev[0].load_only(pids, pwts);
     }
-    // A lane takes two adjacent ids (and weights) per stride, one 16-byte load; a stride of the
-    // group covers 2 * SG ids.  The hash is a position-salted sum, so which lane adds which id does
-    // not matter.  The first kFirst strides of every list and of its predecessor are loaded up
-    // front, all in flight together; longer lists continue kHU strides per trip.
-    auto load2 = [&](const int64_t *base, int64_t t, int64_t n, bool on, int64_t &a, int64_t &b) {
-        a = 0;
-        b = 0;
-        if (on && t + 1 < n) {
-            const id2 p = *reinterpret_cast<const id2 *>(base + t);
-            a = p.x;
-            b = p.y;
-        } else if (on && t < n) {
-            a = base[t];
-        }
-    };
-    auto loadw2 = [&](const uint32_t *base, int64_t t, int64_t n, bool on, uint32_t &a, uint32_t &b) {
-        a = 0;
-        b = 0;
-        if (WT && on && t < n)
-            a = base[t];
-        if (WT && on && t + 1 < n)
-            b = base[t + 1];
-    };
-    auto fold2 = [&](int k, int64_t t, int64_t a, int64_t b, int64_t pa, int64_t pb, uint32_t wa, uint32_t wb,
-                     uint32_t pwa, uint32_t pwb) {
-        // position salt (t + 1) * phi from the low 32 bits of the position (one 32 x 64-bit product;
-        // it only has to be the same for equal lists)
-        const uint64_t salt = (uint64_t)(uint32_t)(t + 1) * 0x9e3779b97f4a7c15ull;
-        if (t < len[k]) {
-            follows[k] &= pa == a && pwa == wa;
-            h[k] += hash_term(hash_item<WT>(a, wa) + salt);
-        }
-        if (t + 1 < len[k]) {
-            follows[k] &= pb == b && pwb == wb;
-            h[k] += hash_term(hash_item<WT>(b, wb) + salt + 0x9e3779b97f4a7c15ull);
-        }
-    };
-    int64_t va[kLPG][kFirst], vb[kLPG][kFirst], pa[kLPG][kFirst], pb[kLPG][kFirst];
-    uint32_t wa[kLPG][kFirst], wb[kLPG][kFirst], pwa[kLPG][kFirst], pwb[kLPG][kFirst];
+    uint64_t differ = alike ? 0 : 1;
 #pragma unroll
-    for (int k = 0; k < kLPG; k++)
-#pragma unroll
-        for (int u = 0; u < kFirst; u++) {
-            const int64_t t = 2 * s + u * 2 * SG;
-            load2(values + start[k], t, len[k], true, va[k][u], vb[k][u]);
-            load2(values + pstart[k], t, len[k], follows[k], pa[k][u], pb[k][u]);
-            loadw2(wbits + start[k], t, len[k], true, wa[k][u], wb[k][u]);
-            loadw2(wbits + pstart[k], t, len[k], follows[k], pwa[k][u], pwb[k][u]);
-        }
-#pragma unroll
-    for (int k = 0; k < kLPG; k++) {
-#pragma unroll
-        for (int u = 0; u < kFirst; u++)
-            fold2(k, 2 * s + u * 2 * SG, va[k][u], vb[k][u], pa[k][u], pb[k][u], wa[k][u], wb[k][u], pwa[k][u],
-                  pwb[k][u]);
-        for (int64_t t0 = 2 * s + kFirst * 2 * SG; t0 < len[k]; t0 += kHU * 2 * SG) {
-            int64_t xa[kHU], xb[kHU], qa[kHU], qb[kHU];
-            uint32_t ya[kHU], yb[kHU], za[kHU], zb[kHU];
-#pragma unroll
-            for (int u = 0; u < kHU; u++) {
-                const int64_t t = t0 + u * 2 * SG;
-                load2(values + start[k], t, len[k], true, xa[u], xb[u]);
-                load2(values + pstart[k], t, len[k], follows[k], qa[u], qb[u]);
-                loadw2(wbits + start[k], t, len[k], true, ya[u], yb[u]);
-                loadw2(wbits + pstart[k], t, len[k], follows[k], za[u], zb[u]);
-            }
+    for (int u = 0; u < kFirst; u++)
+        differ |= own[u].differ(prev[u]);
+    if (alike)
+        for (uint32_t t0 = 2 * s + kHead, end = (uint32_t)len; t0 < end && differ == 0; t0 += kHU * kStride) {
+            IdPair<WT> x[kHU], y[kHU];
 #pragma unroll
             for (int u = 0; u < kHU; u++)
-                fold2(k, t0 + u * 2 * SG, xa[u], xb[u], qa[u], qb[u], ya[u], yb[u], za[u], zb[u]);
+                if (t0 + u * kStride < end) {
+                    x[u].load(ids, wts, t0 + u * kStride, end);
+                    y[u].load(pids, pwts, t0 + u * kStride, end);
+                }
+#pragma unroll
+            for (int u = 0; u < kHU; u++)
+                differ |= x[u].differ(y[u]);
         }
+    constexpr uint64_t group = SG == 64 ? ~0ull : (1ull << SG) - 1;
+    if (((__ballot(differ != 0) >> (lane - s)) & group) == 0) {  // same list as the previous row: no table traffic at all
+        if (s == 0)
+            slot_of[l] = -1;
+        return;
+    }
+
+    uint64_t h = 0;
+#pragma unroll
+    for (int u = 0; u < kFirst; u++) {
+        const int t = 2 * s + u * kStride;
+        if (t < n)
+            h += own[u].hash(t, n);
+    }
+    for (int64_t t0 = 2 * s + kHead; t0 < len; t0 += kHU * kStride) {
+        IdPair<WT> x[kHU];
+#pragma unroll
+        for (int u = 0; u < kHU; u++)
+            if (t0 + u * kStride < len)
+                x[u].load(ids, wts, t0 + u * kStride, len);
+#pragma unroll
+        for (int u = 0; u < kHU; u++)
+            if (t0 + u * kStride < len)
+                h += x[u].hash(t0 + u * kStride, len);
     }
 #pragma unroll
     for (int m = SG / 2; m > 0; m >>= 1)
-#pragma unroll
-        for (int k = 0; k < kLPG; k++) {
-            h[k] += __shfl_xor((unsigned long long)h[k], m, SG);
-            follows[k] &= __shfl_xor(follows[k], m, SG);
-        }
-
-#pragma unroll
-    for (int k = 0; k < kLPG; k++) {
-        if (!live[k])
-            continue;
-        const int64_t l = l0 + k;
-        if (follows[k]) {  // same list as the previous row: no table traffic at all
-            if (s == 0)
-                slot_of[l] = -1;
-            continue;
-        }
-        const int64_t f = l / B;
-        const int64_t b = l - f * B;
-        uint64_t hh = mix64(h[k] ^ ((uint64_t)len[k] * 0xd6e8feb86659fd93ull + 1ull));
-        if (weak_hash)
-            hh = (uint64_t)len[k];  // test hook: only the exact comparison separates lists
-        const uint64_t tag = hh >> 32;
-        const uint64_t mine = (tag << 32) | (uint64_t)b;
-        uint64_t *tab = table + (uint64_t)f * ((uint64_t)cap_mask + 1);
-        uint32_t slot = (uint32_t)hh & cap_mask;
-        // The table has at least 2*B slots per feature, so an empty slot or the list's own class
-        // is met.
-        for (;;) {
-            unsigned long long old = 0;
-            if (s == 0)
-                old = atomicCAS(reinterpret_cast<unsigned long long *>(&tab[slot]), kEmpty, mine);
-            old = __shfl(old, 0, SG);
-            if (old == kEmpty)
-                break;
-            if ((old >> 32) == tag) {
-                const int64_t ol = f * B + (int64_t)(old & 0xffffffffull);
-                const int64_t ostart = offsets[ol];
-                int eq = (offsets[ol + 1] - ostart) == len[k];
-                if (eq)
-                    for (int64_t t = s; t < len[k]; t += SG)
-                        if (values[start[k] + t] != values[ostart + t] ||
-                            (WT && wbits[start[k] + t] != wbits[ostart + t])) {
-                            eq = 0;
-                            break;
-                        }
-#pragma unroll
-                for (int m = SG / 2; m > 0; m >>= 1)
-                    eq &= __shfl_xor(eq, m, SG);
-                if (eq) {
-                    if (s == 0)
-                        atomicMin(reinterpret_cast<unsigned long long *>(&tab[slot]), mine);
-                    break;
-                }
-            }
-            slot = (slot + 1) & cap_mask;
-        }
+        h += __shfl_xor((unsigned long long)h, m, SG);
+    uint64_t hh = mix64(h ^ ((uint64_t)len * 0xd6e8feb86659fd93ull + 1ull));
+    if (weak_hash)
+        hh = (uint64_t)len;  // test hook: only the exact comparison separates lists
+    const uint32_t tag = (uint32_t)(hh >> 32);
+    const uint64_t mine = ((uint64_t)tag << 32) | b;
+    uint64_t *tab = table + (uint64_t)f * ((uint64_t)cap_mask + 1);
+    uint32_t slot = (uint32_t)hh & cap_mask;
+    // The table has at least 2*B slots per feature, so an empty slot or the list's own class
+    // is met.
+    for (;;) {
+        unsigned long long old = 0;
         if (s == 0)
-            slot_of[l] = (int32_t)slot;
+            old = atomicCAS(reinterpret_cast<unsigned long long *>(&tab[slot]), kEmpty, mine);
+        old = __shfl(old, 0, SG);
+        if (old == kEmpty)
+            break;
+        if ((uint32_t)(old >> 32) == tag) {
+            const int64_t ol = (int64_t)(l - b) + (int64_t)(old & 0xffffffffull);
+            const int64_t ostart = offsets[ol];
+            int eq = (offsets[ol + 1] - ostart) == len;
+            if (eq)
+                for (int64_t t = s; t < len; t += SG)
+                    if (ids[t] != values[ostart + t] || (WT && wts[t] != wbits[ostart + t])) {
+                        eq = 0;
+                        break;
+                    }
+#pragma unroll
+            for (int m = SG / 2; m > 0; m >>= 1)
+                eq &= __shfl_xor(eq, m, SG);
+            if (eq) {
+                if (s == 0)
+                    atomicMin(reinterpret_cast<unsigned long long *>(&tab[slot]), mine);
+                break;
+            }
+        }
+        slot = (slot + 1) & cap_mask;
     }
+    if (s == 0)
+        slot_of[l] = (int32_t)slot;
 }
 
 // Block-wide scan of (a, b, c): exclusive sums of a and b, and for c the maximum over the threads
@@ -1551,15 +1546,16 @@ void insert_lists(recd_ctx *ctx, hipStream_t st, const SlotWs &w, int F, int64_t
     const int64_t n_lists = (int64_t)F * B;
     if (!table_is_empty)
         clear_table(st, w, F, B);
-    int64_t hblocks = (n_lists + (kHashBlock / SG) * kLPG - 1) / ((kHashBlock / SG) * kLPG);
+    int64_t hblocks = (n_lists + kHashBlock / SG - 1) / (kHashBlock / SG);
     hblocks = (hblocks + 7) / 8 * 8;  // the kernel deals its blocks to 8 XCDs
+    const RecdDiv rows = recd_divide_by((uint32_t)B);
     recd_time_begin(ctx, RECD_T_HASH, st);
     if (wbits)
         hipLaunchKernelGGL((k_hash_insert<SG, true>), dim3((unsigned)hblocks), dim3(kHashBlock), 0, st, values, wbits,
-                           offsets, B, n_lists, w.table, (uint32_t)(w.cap - 1), w.slot_of, ctx->weak_hash);
+                           offsets, rows, (uint32_t)n_lists, w.table, (uint32_t)(w.cap - 1), w.slot_of, ctx->weak_hash);
     else
         hipLaunchKernelGGL((k_hash_insert<SG, false>), dim3((unsigned)hblocks), dim3(kHashBlock), 0, st, values, wbits,
-                           offsets, B, n_lists, w.table, (uint32_t)(w.cap - 1), w.slot_of, ctx->weak_hash);
+                           offsets, rows, (uint32_t)n_lists, w.table, (uint32_t)(w.cap - 1), w.slot_of, ctx->weak_hash);
     recd_time_end(ctx, RECD_T_HASH, st);
 }
 

@@ -10,6 +10,21 @@
 #define RECD_RULE inline
 #endif
 
+// Division of a row number, below 2^31, by a number known to the host: a high product, an addition and a shift where the
+// compiler's 64-bit division takes some hundred vector instructions (Granlund and Montgomery's method for 32-bit words; the
+// sum stays below 2^32 as n does below 2^31).
+struct RecdDiv {
+    uint32_t by, mul, shift;
+    RECD_RULE uint32_t of(uint32_t n) const { return (uint32_t)((((uint64_t)n * mul) >> 32) + n) >> shift; }
+};
+inline RecdDiv recd_divide_by(uint32_t by)  // 1 to 2^31
+{
+    uint32_t shift = 0;
+    while (((uint64_t)1 << shift) < by)
+        shift++;
+    return RecdDiv{by, (uint32_t)((((((uint64_t)1 << shift) - by) << 32) / by) + 1), shift};
+}
+
 // Unique lists that the backward's workspace has room for (rows of g_u).  U_cap bounds their number; a
 // plain IKJT has at most one empty list per feature and so at most M + F, but a grouped one stores an empty
 // list for every slot of the group, so U_cap cannot be replaced by M_cap + F.

@@ -13,6 +13,7 @@ HARNESS = r"""
 extern "C" {
 int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vecs) { return recd_jagged_lists(N, U_cap, M_cap, vecs, 256); }
 bool short_grouping(int64_t rows, int64_t M_cap) { return recd_grouping_is_short(rows, M_cap); }
+uint32_t divide(uint32_t by, uint32_t n) { return recd_divide_by(by).of(n); }
 bool looks_back(int64_t rows, bool shared) { return recd_looks_back(rows, shared); }
 
 // a build per character of `steps`: p: a plan follows it, -: none, s: a short one; says of each p whether it had an event
@@ -106,6 +107,20 @@ def test_room_for_every_unique_list(rules):
     assert rules.lists_held(5, 600, 3000, 10 ** 9) == 3000
     assert rules.lists_held(5, 600, 7, 40) == 45           # no fewer than a plain IKJT of M_cap ids can have
     assert rules.lists_held(5, 600, 10 ** 9, 40) == 3000
+
+
+def test_division_by_a_number_of_rows(rules):
+    """Quotients at and around multiples of the divisor, up to the largest row number."""
+    rules.divide.restype = C.c_uint32
+    rules.divide.argtypes = [C.c_uint32, C.c_uint32]
+    rng = np.random.default_rng(5)
+    most = (1 << 31) - 1
+    for by in [1, 2, 3, 5, 7, 37, 255, 256, 257, 2500, 5003, 16384, 65537, (1 << 30) - 1, 1 << 30, most] + \
+            [int(x) for x in 2 ** (rng.random(200) * 31)]:
+        k = rng.integers(0, most // by + 1, 50)
+        for n in {0, by - 1, by, most, most // by * by, *(k * by).tolist(), *(k * by + by - 1).tolist()}:
+            if n <= most:
+                assert rules.divide(by, n) == n // by, (by, n)
 
 
 def test_short_groupings_fit_the_chip(rules):
