@@ -10,12 +10,11 @@
 //     (id k goes to group k mod G), each group adds its rows in order, and a fixed butterfly folds
 //     the groups.  Every load instruction of a wave thus fetches G whole rows as contiguous 16-byte
 //     pieces, and UNR loads are issued before the first add so that many rows are in flight.
-//   * a block of W waves owns LB consecutive lists (W = 1 for the two lookups, 4 for the backward's
-//     sums).  Lists of at most 64 ids are summed by one wave each.  A longer list is summed by the
-//     whole block: its 64-id chunks go to the waves round-robin, the W wave partials are added in
-//     wave order.  Which path a list takes and the order of every addition depend on the list's
-//     length and content only, never on where the list sits in a batch: the deduplicated and the
-//     non-deduplicated lookup (same W) agree bit for bit.
+//   * in the lookups a wave sums a list by itself.  A block of the backward's sums has four waves and owns LB
+//     consecutive lists: those of at most 64 ids are summed by one wave each, the 64-id chunks of a longer one
+//     go to the waves round-robin, and the wave partials are added in wave order.  Which path a list takes and
+//     the order of every addition depend on the list's length and content only, never on where the list sits
+//     in a batch: the deduplicated and the non-deduplicated lookup agree bit for bit.
 //   * blocks are dealt to lists statically (no atomics; the hardware's block dispatch balances the
 //     load).  The lookups' mapping is XCD-aware: consecutive blocks go to consecutive XCDs, and block b
 //     serves every eighth stretch of neighbouring lists from the (b mod 8)-th on, so that lists that share
@@ -30,14 +29,12 @@ namespace {
 
 constexpr int kNQ = 8;         // XCDs
 constexpr int kBlock = 256;
-// Threads per block of the gather-sum kernel.  The forward lookups run one wave per block: the
-// waves of a block finish their lists at different times, and a block's registers are only free
-// again when its last wave is done, so with lists of 1 to 256 ids a four-wave block keeps idle
-// waves resident (unique lookup 0.124 ms against 0.133, KJT lookup 0.99 against 1.16).  The
-// backward's sum keeps four waves: its long segments want the whole block.
-template <int SITE> struct SegBlock {
-    static constexpr int threads = (SITE == 0 || SITE == 1 || SITE == 2 || SITE == 4) ? 64 : 256;
-};
+// Most threads per block of the gather-sum kernel.  The waves of a block finish their lists at different times, and a block's
+// registers are only free again when its last wave is done, so with lists of 1 to 256 ids a four-wave block keeps idle
+// waves resident (unique lookup 0.124 ms against 0.133, KJT lookup 0.99 against 1.16): the forward lookups' waves are on
+// their own, one to a block, or two where the grid is sized by a large bound (see recd_launch_segsum).  The backward's sum
+// keeps four waves: its long segments want the whole block.
+constexpr int seg_threads(int site) { return site == 0 || site == 4 ? 128 : (site == 1 || site == 2 ? 64 : 256); }
 constexpr int kMaxLB = 16;     // lists per block item (upper bound)
 constexpr int64_t kRunsLists = 32768;  // KJT lists from which on a wave takes several and shares equal neighbours' sums
 constexpr int kStage = 1024;   // ids of such a wave's lists that wait in LDS
@@ -50,6 +47,12 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
     uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)v);
     uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// A word that no kernel writes while this one runs, at an address that is the same in every lane, by a scalar load.
+__device__ __forceinline__ int64_t scalar_word(const int64_t *p)
+{
+    return *(const __attribute__((address_space(4))) int64_t *)(uintptr_t)p;
 }
 
 template <int TT> struct Elem;
@@ -289,12 +292,12 @@ static_assert(segsum_most_waves<64, 2, RECD_F32, RECD_F32, SITE_KJT, POOL_SUM>()
 static_assert(segsum_most_waves<8, 1, RECD_F32, RECD_F32, SITE_KJT, POOL_WSUM>() == 8, "short rows, weights: no limit");
 
 template <int LPR, int VPL, int TT, int OT, typename IdxT, int SITE, int MODE = POOL_SUM>
-__global__ __launch_bounds__(SegBlock<SITE>::threads)
+__global__ __launch_bounds__(seg_threads(SITE))
 __attribute__((amdgpu_waves_per_eu(segsum_waves<LPR, VPL, TT, OT, SITE, MODE>(),
                                    segsum_most_waves<LPR, VPL, TT, OT, SITE, MODE>())))
 void k_segsum(const SegSumParams p)
 {
-    constexpr int kSegBlock = SegBlock<SITE>::threads;
+    constexpr int kSegBlock = seg_threads(SITE);
     constexpr int kWaves = kSegBlock / 64;
     constexpr bool NT = is_kjt(SITE);  // streaming output
     constexpr int EPV = Elem<TT>::per_vec;
@@ -309,15 +312,15 @@ void k_segsum(const SegSumParams p)
     __shared__ uint32_t s_ids[kStage];                    // SITE_KJT_RUNS
     __shared__ float s_part[LL][kWaves][ROWF];
     constexpr bool EXPAND = SITE == SITE_UNIQUE_EXPAND;
-    static_assert(!EXPAND || kWaves == 1, "a finished row is in the registers of one wave");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
     const int nq = p.nq;
     const int q = nq == 1 ? 0 : (int)(blockIdx.x % kNQ);
-    const int64_t item0 = nq == 1 ? blockIdx.x : blockIdx.x / kNQ;
-    const int64_t item_stride = nq == 1 ? gridDim.x : gridDim.x / kNQ;
+    const int each = seg_threads(SITE) == 128 ? (int)(blockDim.x >> 6) : 1;  // waves of a block that take items of their own
+    const int64_t item0 = (int64_t)(nq == 1 ? blockIdx.x : blockIdx.x / kNQ) * each + (seg_threads(SITE) == 128 ? wv : 0);
+    const int64_t item_stride = (int64_t)(nq == 1 ? gridDim.x : gridDim.x / kNQ) * each;
 
     const int g = lane / LPR;   // lane group = which of the G rows of a load
     const int r = lane % LPR;   // 16-byte piece of the row
@@ -389,10 +392,6 @@ void k_segsum(const SegSumParams p)
             cur = nxt;
         }
     };
-    auto walk_long_list = [&](float (*acc)[NACC], const char *table, int64_t start, int64_t end, uint32_t cur) {
-        walk_list(acc, table, start, end, kChunk, cur);
-    };
-
     if constexpr (EXPAND) {
         // Work item = a run of the batch: adjacent rows of a feature that name the same unique list
         // (the samples of a session).  The wave of a list's first run sums the list, stores the row
@@ -409,8 +408,7 @@ void k_segsum(const SegSumParams p)
         const int64_t n_runs = ri[0] < p.run_cap ? ri[0] : p.run_cap;
         const int64_t per = (n_runs + kNQ - 1) / kNQ;
         const int64_t first_item = (int64_t)(blockIdx.x % kNQ) * per;
-        const int64_t stride = gridDim.x / kNQ;
-        for (int64_t item = blockIdx.x / kNQ; item < per; item += stride) {
+        for (int64_t item = item0; item < per; item += item_stride) {
             const int64_t rr = first_item + item;
             if (rr >= n_runs)
                 break;
@@ -441,7 +439,7 @@ void k_segsum(const SegSumParams p)
             for (int i = 0; i < NACC; i++)
                 acc[0][i] = pool_identity<MODE>();
             if (len_ids > kChunk) {
-                walk_long_list(acc, table, start, start + len_ids, (uint32_t)values[start + lane]);
+                walk_list(acc, table, start, start + len_ids, kChunk, (uint32_t)values[start + lane]);
             } else {
                 const int n = (int)len_ids;
                 add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes, lane,
@@ -467,28 +465,105 @@ void k_segsum(const SegSumParams p)
         return;
     }
 
-    if constexpr (kWaves == 1) {
-        // One wave: a lane looks at the first lists of two features, the feature of a list is a count of
-        // ballots, and one load brings the bounds of the block's lists; they wait in 320 bytes of LDS
-        // while rows are gathered (in registers they cost the seventh wave).  (Prefix sums over the
-        // features and 4.6 KB of LDS a wave before; 28 waves of that on a CU also kept blocks of other
-        // streams out.)  Queue q = blockIdx mod 8 (one XCD) takes every eighth stretch of neighbouring lists
+    if constexpr (SITE != SITE_GRAD_STREAM) {
+        // A wave on its own: a lane looks at the first lists of two features, the feature of a list is a count of
+        // ballots.  (Prefix sums over the features and 4.6 KB of LDS a wave before; 28 waves of that on a CU also kept
+        // blocks of other streams out.)  Queue q = blockIdx mod 8 (one XCD) takes every eighth stretch of neighbouring lists
         // (recd_deal_log): balanced whatever the features' mean lengths.  (A contiguous eighth each, as few XCDs for a
         // feature as there can be, is up to a tenth faster and up to 2.6 times slower: fp32 rows of 512 bytes, unique /
         // KJT lookup, us, contiguous -> dealt: 32 even features 67 / 307 -> 69 / 305, 5 even ones 22 / 53 -> 24 / 51,
         // 64 of skewed ids 122 / 987 -> 124 / 995; four of 32 of mean 64 and the rest of 2: 114 / 792 -> 53 / 250;
         // the first of 6 of mean 100, the rest of 2: 71 / 190 -> 30 / 72; one of 65 of mean 150, the rest of 4:
         // 131 / 414 -> 91 / 242.)
-        const int64_t first = p.list_off ? uniform64(p.list_off[0]) : p.list_base;
-        const int64_t end_all = p.list_off ? uniform64(p.list_off[p.F]) : p.list_base + p.F * p.lists_per_feature;
+        const int64_t first = p.list_off ? scalar_word(p.list_off) : p.list_base;
+        const int64_t end_all = p.list_off ? scalar_word(p.list_off + p.F) : p.list_base + p.F * p.lists_per_feature;
         const int64_t all = end_all - first;
-        // lists per block: as many as keep the number of blocks in bounds (measured at 61 K unique lists
-        // and at 1.05 M KJT lists: 1 and 4), by the true number of lists
+        // neighbouring lists per turn of a wave (measured at 61 K unique lists and at 1.05 M KJT lists: 1 and 4), by the
+        // true number of lists
         const int most = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
         const int deal_log = is_kjt(SITE) ? p.deal_log : recd_deal_log(all, kNQ, 31 - __builtin_clz(most));
+        if constexpr (SITE != SITE_KJT_RUNS) {
+            // A wave's lists follow each other without a wait of their own: while the rows of one are gathered, the ids of the
+            // next one's first chunk and the bounds of the one after that are on their way.
+            auto list_of = [&](int64_t item) {
+                return first + (nq == 1 ? item * most : recd_dealt(item * most, q, kNQ, deal_log));
+            };
+            int64_t item = item0;
+            auto after = [&](int64_t l, int &j) {  // the wave's list after l, the j-th of its item
+                if (++j < most && l + 1 < end_all)
+                    return l + 1;
+                j = 0;
+                item += item_stride;
+                return list_of(item);
+            };
+            // where list l starts and ends, in lanes 0 and 1
+            auto load_bounds = [&](int64_t l) {
+                int64_t x = 0;
+                if (lane < 2 && l < end_all)
+                    x = lane == 1 && p.lens ? p.lens[l] : p.offsets[l + lane];
+                return x;
+            };
+            auto lane64 = [](int64_t x, int k) {
+                return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)x >> 32), k) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane((int)(uint64_t)x, k));
+            };
+            auto end_of = [&](int64_t start, int64_t x) { return p.lens ? start + lane64(x, 1) : lane64(x, 1); };
+            auto chunk_of = [&](int64_t at, int64_t end) { return (int)(end - at < kChunk ? end - at : kChunk); };
+            int j = 0, nj = 0;
+            int64_t l = list_of(item);
+            if (l >= end_all)
+                return;
+            int64_t x = load_bounds(l);
+            nj = j;
+            int64_t nl = after(l, nj), nx = load_bounds(nl);
+            int64_t start = lane64(x, 0), end = end_of(start, x);
+            uint32_t cur = lane < chunk_of(start, end) ? (uint32_t)values[start + lane] : 0u;
+            for (;;) {
+                int f;
+                {
+                    int ln = lane;
+                    asm volatile("" : "+v"(ln));  // its addresses are made here, not kept over the gathers
+                    int64_t fo0 = INT64_MAX, fo1 = INT64_MAX;
+                    if (ln < p.F)
+                        fo0 = p.list_off ? p.list_off[ln] : p.list_base + ln * p.lists_per_feature;
+                    if (64 + ln < p.F)
+                        fo1 = p.list_off ? p.list_off[64 + ln] : p.list_base + (64 + ln) * p.lists_per_feature;
+                    f = (int)(__popcll(__ballot(fo0 <= l)) + __popcll(__ballot(fo1 <= l))) - 1;
+                }
+                const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
+                const int64_t nstart = lane64(nx, 0), nend = end_of(nstart, nx);
+                const int64_t nnl = nl < end_all ? after(nl, nj) : nl;
+                nx = load_bounds(nnl);
+                float acc[1][NACC];
+#pragma unroll
+                for (int k = 0; k < NACC; k++)
+                    acc[0][k] = pool_identity<MODE>();
+                int64_t at = start;
+                for (bool more = true; more;) {
+                    const int n = chunk_of(at, end);
+                    const int64_t base = at;
+                    at += kChunk;
+                    more = at < end;
+                    const int64_t to = more ? at : nstart;
+                    const uint32_t nxt = lane < chunk_of(to, more ? end : nend) ? (uint32_t)values[to + lane] : 0u;
+                    add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &base, &n, row_bytes, lane, g,
+                                                                        p.weights, &cur);
+                    cur = nxt;
+                }
+                fold_groups(acc[0]);
+                finish_row(l, end - start, acc[0]);
+                if (nl >= end_all)
+                    break;
+                l = nl;
+                nl = nnl;
+                start = nstart;
+                end = nend;
+            }
+            return;
+        }
         for (int64_t i = item0;; i += item_stride) {
-            const int lpb = SITE == SITE_KJT_RUNS ? recd_item_lists(i, p.whole, most) : most;
-            const int64_t t = SITE == SITE_KJT_RUNS ? recd_item_start(i, p.whole, most) : i * most;
+            const int lpb = recd_item_lists(i, p.whole, most);
+            const int64_t t = recd_item_start(i, p.whole, most);
             const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ, deal_log));
             if (l0 >= end_all)
                 break;  // so are all later items of this block
@@ -513,109 +588,86 @@ void k_segsum(const SegSumParams p)
                 }
                 __syncthreads();  // a block of one wave: orders the LDS accesses, nobody waits
             }
-            if constexpr (SITE == SITE_KJT_RUNS) {
-                // Neighbouring lists of a session-ordered batch are mostly the same list.  The wave brings the ids of all of
-                // its lists, which lie one behind the other, into LDS, compares each list with the one before it, 64 / lpb
-                // lanes to a list, sums the first of every run of equal ones and stores its row for the whole run: the same
-                // ids in the same order give the same bits.  What bounds the lookup is the gathered rows, and those of a run
-                // are gathered once; with the ids at hand the other lists cost a wave a round trip less than one by one, which
-                // pays for the comparison where it finds nothing.  us, by the plain kernel / by this one, 262 K lists, ids
-                // uniform: sessions of 8, 64 ids, rows of 512 bytes 522 / 303, of 64 bytes 172 / 81; 5 ids 87 / 46, 101 / 49;
-                // no sessions, 5 ids 140 / 137, 107 / 103; 64 ids 1451 / 1578, tables of 20 K rows 993 / 1140.
-                // On average over 64 K to 1.05 M even lists without sessions as fast as the plain kernel, but slower by up to
-                // 40 % where lists are long and tables about as large as an L2 (7 K waves of 8 lists use more tables at a time
-                // than those of 2; 64 ids of 64-byte rows, 64 K rows 177 / 250, skewed ids 165 / 162), and wherever a few
-                // features have by far the longest lists, of which 8 in one wave outlast the rest: one of 32 features with
-                // half of the ids 668 / 931, skewed ids 442 / 790, sessions of 8 516 / 443; 130 K lists of 26 features, 64-byte
-                // rows, sessions of 2 118 / 287.
-                // (Each wave's lists compared in memory, ids read again by the sums: no sessions, 64 ids of 64-byte
-                // rows 290, sessions 107.  Runs that go on into other waves' lists, with those left out there: 485 for
-                // 303.  Four waves a block: its slots are free only when the last is done; sessions of 5 ids 62 for 46.
-                // A kernel before this one that looks at 128 pairs of neighbours, and waves of 2 or 8 lists by what it found:
-                // 64 K lists of 5 ids, sessions / none 16 / 35 -> 28 / 41, 262 K 39 / 105 -> 60 / 121.  2048 blocks before these
-                // that take the lists of such features two by two: those 931 -> 809, 287 -> 141, but short lists 15.4 -> 16.5,
-                // of 64-byte rows 38 -> 43, most of it for the waves' question whether their lists are among them.)
-                const int64_t base = uniform64(s_start[0]), held = uniform64(s_end[cnt - 1]) - base;
-                const int staged = (int)(held < kStage ? held : kStage);
-                int ln = lane;
-                asm volatile("" : "+v"(ln));  // as above: nothing of this is kept over the gathers
-                for (int u0 = 0; u0 < staged; u0 += kStageLoads * 64) {
-                    uint32_t id[kStageLoads];
+            // Neighbouring lists of a session-ordered batch are mostly the same list.  The wave brings the ids of all of
+            // its lists, which lie one behind the other, into LDS, compares each list with the one before it, 64 / lpb
+            // lanes to a list, sums the first of every run of equal ones and stores its row for the whole run: the same
+            // ids in the same order give the same bits.  What bounds the lookup is the gathered rows, and those of a run
+            // are gathered once; with the ids at hand the other lists cost a wave a round trip less than one by one, which
+            // pays for the comparison where it finds nothing.  us, by the plain kernel / by this one, 262 K lists, ids
+            // uniform: sessions of 8, 64 ids, rows of 512 bytes 522 / 303, of 64 bytes 172 / 81; 5 ids 87 / 46, 101 / 49;
+            // no sessions, 5 ids 140 / 137, 107 / 103; 64 ids 1451 / 1578, tables of 20 K rows 993 / 1140.
+            // On average over 64 K to 1.05 M even lists without sessions as fast as the plain kernel, but slower by up to
+            // 40 % where lists are long and tables about as large as an L2 (7 K waves of 8 lists use more tables at a time
+            // than those of 2; 64 ids of 64-byte rows, 64 K rows 177 / 250, skewed ids 165 / 162), and wherever a few
+            // features have by far the longest lists, of which 8 in one wave outlast the rest: one of 32 features with
+            // half of the ids 668 / 931, skewed ids 442 / 790, sessions of 8 516 / 443; 130 K lists of 26 features, 64-byte
+            // rows, sessions of 2 118 / 287.
+            // (Each wave's lists compared in memory, ids read again by the sums: no sessions, 64 ids of 64-byte
+            // rows 290, sessions 107.  Runs that go on into other waves' lists, with those left out there: 485 for
+            // 303.  Four waves a block: its slots are free only when the last is done; sessions of 5 ids 62 for 46.
+            // A kernel before this one that looks at 128 pairs of neighbours, and waves of 2 or 8 lists by what it found:
+            // 64 K lists of 5 ids, sessions / none 16 / 35 -> 28 / 41, 262 K 39 / 105 -> 60 / 121.  2048 blocks before these
+            // that take the lists of such features two by two: those 931 -> 809, 287 -> 141, but short lists 15.4 -> 16.5,
+            // of 64-byte rows 38 -> 43, most of it for the waves' question whether their lists are among them.)
+            const int64_t base = uniform64(s_start[0]), held = uniform64(s_end[cnt - 1]) - base;
+            const int staged = (int)(held < kStage ? held : kStage);
+            int ln = lane;
+            asm volatile("" : "+v"(ln));  // as above: nothing of this is kept over the gathers
+            for (int u0 = 0; u0 < staged; u0 += kStageLoads * 64) {
+                uint32_t id[kStageLoads];
 #pragma unroll
-                    for (int u = 0; u < kStageLoads; u++)
-                        id[u] = u0 + u * 64 + ln < staged ? (uint32_t)values[base + u0 + u * 64 + ln] : 0u;
+                for (int u = 0; u < kStageLoads; u++)
+                    id[u] = u0 + u * 64 + ln < staged ? (uint32_t)values[base + u0 + u * 64 + ln] : 0u;
 #pragma unroll
-                    for (int u = 0; u < kStageLoads; u++)
-                        s_ids[u0 + u * 64 + ln] = id[u];
+                for (int u = 0; u < kStageLoads; u++)
+                    s_ids[u0 + u * 64 + ln] = id[u];
+            }
+            __syncthreads();
+            const int per = 6 - (31 - __builtin_clz(lpb)), at = ln & ((1 << per) - 1), mine = ln >> per;
+            bool same = false;
+            if (mine > 0 && mine < cnt && s_feat[mine] == s_feat[mine - 1]) {
+                const int64_t start = s_start[mine], len = s_end[mine] - start, back = start - s_start[mine - 1];
+                same = back == len;
+                const int64_t rel = start - base;
+                if (rel - back >= 0 && rel + len <= staged) {
+                    for (int t = at; same && t < (int)len; t += 1 << per)
+                        same = s_ids[(int)rel + t] == s_ids[(int)(rel - back) + t];
+                } else {
+                    for (int64_t t = at; same && t < len; t += 1 << per)
+                        same = (uint32_t)values[start + t] == (uint32_t)values[start + t - back];
                 }
-                __syncthreads();
-                const int per = 6 - (31 - __builtin_clz(lpb)), at = ln & ((1 << per) - 1), mine = ln >> per;
-                bool same = false;
-                if (mine > 0 && mine < cnt && s_feat[mine] == s_feat[mine - 1]) {
-                    const int64_t start = s_start[mine], len = s_end[mine] - start, back = start - s_start[mine - 1];
-                    same = back == len;
-                    const int64_t rel = start - base;
-                    if (rel - back >= 0 && rel + len <= staged) {
-                        for (int t = at; same && t < (int)len; t += 1 << per)
-                            same = s_ids[(int)rel + t] == s_ids[(int)(rel - back) + t];
-                    } else {
-                        for (int64_t t = at; same && t < len; t += 1 << per)
-                            same = (uint32_t)values[start + t] == (uint32_t)values[start + t - back];
-                    }
-                    if (MODE == POOL_WSUM)  // bit patterns: the sum depends on no more
-                        for (int64_t t = at; same && t < len; t += 1 << per)
-                            same = __float_as_uint(p.weights[start + t]) == __float_as_uint(p.weights[start + t - back]);
+                if (MODE == POOL_WSUM)  // bit patterns: the sum depends on no more
+                    for (int64_t t = at; same && t < len; t += 1 << per)
+                        same = __float_as_uint(p.weights[start + t]) == __float_as_uint(p.weights[start + t - back]);
+            }
+            const uint64_t differ = __ballot(!same), group = per == 6 ? ~0ull : (1ull << (1 << per)) - 1;
+            for (int j = 0, end; j < cnt; j = end) {
+                for (end = j + 1; end < cnt && ((differ >> (end << per)) & group) == 0; end++) {
                 }
-                const uint64_t differ = __ballot(!same), group = per == 6 ? ~0ull : (1ull << (1 << per)) - 1;
-                for (int j = 0, end; j < cnt; j = end) {
-                    for (end = j + 1; end < cnt && ((differ >> (end << per)) & group) == 0; end++) {
-                    }
-                    const int64_t start = uniform64(s_start[j]);
-                    const int64_t len = uniform64(s_end[j]) - start;
-                    const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
-                    const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
-                    const int n = (int)(len < kChunk ? len : kChunk);
-                    const int64_t rel = start - base;
-                    uint32_t cur = 0;
-                    if (rel >= 0 && rel + n <= staged) {
-                        if (lane < n)
-                            cur = s_ids[(int)rel + lane];
-                    } else if (lane < n) {
-                        cur = (uint32_t)values[start + lane];
-                    }
-                    float acc[1][NACC];
+                const int64_t start = uniform64(s_start[j]);
+                const int64_t len = uniform64(s_end[j]) - start;
+                const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
+                const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
+                const int n = (int)(len < kChunk ? len : kChunk);
+                const int64_t rel = start - base;
+                uint32_t cur = 0;
+                if (rel >= 0 && rel + n <= staged) {
+                    if (lane < n)
+                        cur = s_ids[(int)rel + lane];
+                } else if (lane < n) {
+                    cur = (uint32_t)values[start + lane];
+                }
+                float acc[1][NACC];
 #pragma unroll
-                    for (int i = 0; i < NACC; i++)
-                        acc[0][i] = pool_identity<MODE>();
-                    walk_list(acc, table, start, start + len, n, cur);
-                    fold_groups(acc[0]);  // the butterfly leaves the row in every lane group
-                    scale_row(l0 + j, len, acc[0]);
-                    int gg = g;
-                    asm volatile("" : "+v"(gg));  // its offset is not kept over the gathers either
-                    for (int k = gg; k < end - j; k += 64 / LPR)
-                        store_row(l0 + j, acc[0], (uint32_t)k * (uint32_t)out_row_bytes);
-                }
-            } else {
-                for (int j = 0; j < cnt; j++) {
-                    const int64_t l = l0 + j;
-                    const int64_t start = uniform64(s_start[j]);
-                    const int64_t len = uniform64(s_end[j]) - start;
-                    const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
-                    const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
-                    float acc[1][NACC];
-#pragma unroll
-                    for (int i = 0; i < NACC; i++)
-                        acc[0][i] = pool_identity<MODE>();
-                    if (len > kChunk) {
-                        walk_long_list(acc, table, start, start + len, (uint32_t)values[start + lane]);
-                    } else {
-                        const int n = (int)len;
-                        add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes,
-                                                                            lane, g, p.weights);
-                    }
-                    fold_groups(acc[0]);
-                    finish_row(l, len, acc[0]);
-                }
+                for (int i = 0; i < NACC; i++)
+                    acc[0][i] = pool_identity<MODE>();
+                walk_list(acc, table, start, start + len, n, cur);
+                fold_groups(acc[0]);  // the butterfly leaves the row in every lane group
+                scale_row(l0 + j, len, acc[0]);
+                int gg = g;
+                asm volatile("" : "+v"(gg));  // its offset is not kept over the gathers either
+                for (int k = gg; k < end - j; k += 64 / LPR)
+                    store_row(l0 + j, acc[0], (uint32_t)k * (uint32_t)out_row_bytes);
             }
             __syncthreads();
         }
@@ -704,9 +756,9 @@ void k_segsum(const SegSumParams p)
 }
 
 template <int TT, int OT, typename IdxT, int SITE, int MODE = POOL_SUM>
-bool launch_shape(hipStream_t st, int blocks, int vecs, const SegSumParams &p)
+bool launch_shape(hipStream_t st, int blocks, int threads, int vecs, const SegSumParams &p)
 {
-    const dim3 grid(blocks), block(SegBlock<SITE>::threads);
+    const dim3 grid(blocks), block(threads);
     if (vecs <= 8) hipLaunchKernelGGL((k_segsum<8, 1, TT, OT, IdxT, SITE, MODE>), grid, block, 0, st, p);
     else if (vecs <= 16) hipLaunchKernelGGL((k_segsum<16, 1, TT, OT, IdxT, SITE, MODE>), grid, block, 0, st, p);
     else if (vecs <= 32) hipLaunchKernelGGL((k_segsum<32, 1, TT, OT, IdxT, SITE, MODE>), grid, block, 0, st, p);
@@ -718,18 +770,18 @@ bool launch_shape(hipStream_t st, int blocks, int vecs, const SegSumParams &p)
 }
 
 template <int SITE, int MODE = POOL_SUM>
-bool launch_forward(hipStream_t st, int blocks, int v, const SegSumArgs &a, const SegSumParams &p)
+bool launch_forward(hipStream_t st, int blocks, int threads, int v, const SegSumArgs &a, const SegSumParams &p)
 {
     if (a.table_dt == RECD_F32 && a.out_dt == RECD_F32)
-        return launch_shape<RECD_F32, RECD_F32, int64_t, SITE, MODE>(st, blocks, v, p);
+        return launch_shape<RECD_F32, RECD_F32, int64_t, SITE, MODE>(st, blocks, threads, v, p);
     if (a.table_dt == RECD_F16 && a.out_dt == RECD_F16)
-        return launch_shape<RECD_F16, RECD_F16, int64_t, SITE, MODE>(st, blocks, v, p);
+        return launch_shape<RECD_F16, RECD_F16, int64_t, SITE, MODE>(st, blocks, threads, v, p);
     if (a.table_dt == RECD_F16 && a.out_dt == RECD_F32)
-        return launch_shape<RECD_F16, RECD_F32, int64_t, SITE, MODE>(st, blocks, v, p);
+        return launch_shape<RECD_F16, RECD_F32, int64_t, SITE, MODE>(st, blocks, threads, v, p);
     if (a.table_dt == RECD_BF16 && a.out_dt == RECD_BF16)
-        return launch_shape<RECD_BF16, RECD_BF16, int64_t, SITE, MODE>(st, blocks, v, p);
+        return launch_shape<RECD_BF16, RECD_BF16, int64_t, SITE, MODE>(st, blocks, threads, v, p);
     if (a.table_dt == RECD_BF16 && a.out_dt == RECD_F32)
-        return launch_shape<RECD_BF16, RECD_F32, int64_t, SITE, MODE>(st, blocks, v, p);
+        return launch_shape<RECD_BF16, RECD_F32, int64_t, SITE, MODE>(st, blocks, threads, v, p);
     return false;
 }
 
@@ -1056,8 +1108,8 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     const int64_t n = a.lists_bound > 0 ? a.lists_bound : 1;
     const bool one_wave = a.site == RECD_SITE_UNIQUE || a.site == RECD_SITE_KJT || a.site == RECD_SITE_UNIQUE_EXPAND;
     p.nq = one_wave && !a.flat && !ctx->tune_flat ? kNQ : 1;
-    // lists per block: four-wave blocks (backward) take 4 to 16, single-wave blocks (forward) 1 to 4, by
-    // the number of lists that the kernel finds (0); the grid is sized as if it were the host's bound
+    // lists per item: four-wave blocks (backward) take 4 to 16, the forward's waves 1 to 4, by the number of lists that the
+    // kernel finds (0); the grid is sized as if it were the host's bound
     int lb = one_wave ? (n >= (512 << 10) ? 4 : (n >= (128 << 10) ? 2 : 1))
                       : (n >= (512 << 10) ? 16 : (n >= (128 << 10) ? 8 : 4));
     p.lb = one_wave ? 0 : lb;
@@ -1080,16 +1132,27 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
         p.whole = recd_whole_items(most, p.nq, lb);
         nblk = (int64_t)p.nq * recd_items(most, p.whole, lb);
     }
-    const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : 64);
-    if (nblk > cap)
-        nblk = cap / kNQ * kNQ;
+    // The lookup of unique lists, and of fewer than half a million runs, has at most 64 K waves, from 32 K on two to a block.
+    // Waves without a list are not free: handing one out takes 0.16 ns, in blocks of two half of that, and a bound is often
+    // several times the lists (F*B for want of a better one).  us, one wave a block and 128 K waves at most / 32 K / 64 K /
+    // two waves a block and 64 K: 22 K lists under a bound of 130 K 38.4 / 21.2 / 25.1 / 21.8, 33 K under 1.05 M 39.5 / 21.6 /
+    // 26.2 / 23.3; a bound that is the number of lists, 61 K lists of up to 256 ids 127 / 133 / 127 / 127, 131 K 174 / 191 /
+    // 176 / 176.  Runs, 16-bit rows, the first and the last of these: 33 K of 262 K at most 44.6 / 30.6, 131 K 80.5 / 79.2,
+    // 262 K 134.4 / 136.1; of 1.05 M at most 64 K 108.0 / 107.3, but 131 K of fp32 rows 180 / 188 and all of them 498 / 511.
+    const bool bounded = a.site == RECD_SITE_UNIQUE || (a.site == RECD_SITE_UNIQUE_EXPAND && n < (512 << 10));
     if (a.site == RECD_SITE_UNIQUE_EXPAND) {
-        // one run per block and turn; the kernel deals the runs to eight queues by their true number
+        // one run per wave and turn; the kernel deals the runs to eight queues by their true number
         p.lb = 1;
         p.nq = kNQ;
         nblk = kNQ * ((n + kNQ - 1) / kNQ);
-        if (nblk > cap)
-            nblk = cap / kNQ * kNQ;
+    }
+    const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : (bounded ? 32 : 64));
+    if (nblk > cap)
+        nblk = cap / kNQ * kNQ;
+    int threads = a.site == RECD_SITE_GRAD_STREAM ? 256 : 64;
+    if (bounded && nblk > (int64_t)ctx->num_cu * 128) {
+        threads = 128;
+        nblk = p.nq == 1 ? (nblk + 1) / 2 : kNQ * ((nblk / kNQ + 1) / 2);
     }
     const int blocks = (int)nblk;
     bool ok = false;
@@ -1104,30 +1167,30 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     if (slot >= 0)
         recd_time_begin(ctx, slot, st);
     if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_SUM)
-        ok = launch_forward<SITE_UNIQUE>(st, blocks, v, a, p);
+        ok = launch_forward<SITE_UNIQUE>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_SUM)
-        ok = runs ? launch_forward<SITE_KJT_RUNS>(st, blocks, v, a, p)
-                  : launch_forward<SITE_KJT>(st, blocks, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS>(st, blocks, threads, v, a, p)
+                  : launch_forward<SITE_KJT>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE_EXPAND && fwd && a.mode == POOL_SUM && a.run_index)
-        ok = launch_forward<SITE_UNIQUE_EXPAND>(st, blocks, v, a, p);
+        ok = launch_forward<SITE_UNIQUE_EXPAND>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_MEAN)
-        ok = launch_forward<SITE_UNIQUE, POOL_MEAN>(st, blocks, v, a, p);
+        ok = launch_forward<SITE_UNIQUE, POOL_MEAN>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_MEAN)
-        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MEAN>(st, blocks, v, a, p)
-                  : launch_forward<SITE_KJT, POOL_MEAN>(st, blocks, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MEAN>(st, blocks, threads, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_MEAN>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_MAX)
-        ok = launch_forward<SITE_UNIQUE, POOL_MAX>(st, blocks, v, a, p);
+        ok = launch_forward<SITE_UNIQUE, POOL_MAX>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_MAX)
-        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MAX>(st, blocks, v, a, p)
-                  : launch_forward<SITE_KJT, POOL_MAX>(st, blocks, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MAX>(st, blocks, threads, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_MAX>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_WSUM && a.weights)
-        ok = launch_forward<SITE_UNIQUE, POOL_WSUM>(st, blocks, v, a, p);
+        ok = launch_forward<SITE_UNIQUE, POOL_WSUM>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_WSUM && a.weights)
-        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_WSUM>(st, blocks, v, a, p)
-                  : launch_forward<SITE_KJT, POOL_WSUM>(st, blocks, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_WSUM>(st, blocks, threads, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_WSUM>(st, blocks, threads, v, a, p);
     else if (a.site == RECD_SITE_GRAD_STREAM && a.values_are_i32 && a.table_dt == RECD_F32 &&
              a.out_dt == RECD_F32 && a.mode == POOL_SUM)
-        ok = launch_shape<RECD_F32, RECD_F32, int32_t, SITE_GRAD_STREAM>(st, blocks, v, p);
+        ok = launch_shape<RECD_F32, RECD_F32, int32_t, SITE_GRAD_STREAM>(st, blocks, threads, v, p);
     if (slot >= 0)
         recd_time_end(ctx, slot, st);
     if (!ok)

@@ -56,3 +56,33 @@ def test_lists_that_differ_in_one_place(ctx, n, weighted):
         build_weighted(ctx, batch, np.concatenate([x for k in range(8) for x in weights[k:] + weights[:k]]).astype(np.float32))
     else:
         _check(gu.gpu_build(ctx, batch)[2], batch)
+
+
+@pytest.mark.parametrize("F,B,S", [(1, 32, 4), (9, 3640, 4), (9, 3641, 4), (33, 993, 1), (17, 3856, 40), (31, 17000, 64)])
+@pytest.mark.parametrize("slack", [0, 1, 20])
+def test_lookups_under_tight_and_loose_bounds(ctx, F, B, S, slack):
+    """One and two waves a block, lists and runs fewer and more than waves: every bound gives what each list by itself does,
+    and writes no row beyond the lists."""
+    D = 8
+    w = synth.scaled(synth.WORKLOADS["cfg2"], F=F, B=B, rows=500, D=D, S=S, len_max=9)
+    batch = synth.make_batch(w, slack)
+    tabs = gu.tables_to_dev(synth.make_tables(w), w.table_dtype)
+    values, offsets = gu.to_dev(batch.values), gu.to_dev(batch.offsets)
+    ik = gu.DeviceIKJT(F, B, batch.N)
+    runs = torch.zeros(3 * (F * B + 2), dtype=torch.int64, device="cuda")
+    ik.U, ik.M = ctx.build_ikjt_runs(F, B, values, offsets, ik.u_values, ik.u_offsets, ik.inverse, ik.feat_uoff, runs,
+                                     want_counts=True)
+    n_runs = int(runs[0])
+    dt = gu.TORCH_DT[w.table_dtype]
+    kjt = torch.empty(F, B, D, dtype=dt, device="cuda")
+    ctx.kjt_pooled_lookup(tabs, B, values, offsets, kjt)
+    bound = {0: ik.U, 1: min(F * B, 2 * ik.U), 20: F * B}[slack]
+    pooled = torch.full((F * B, D), 7.0, dtype=dt, device="cuda")
+    out = torch.empty(F, B, D, dtype=dt, device="cuda")
+    ctx.pooled_lookup_unique(tabs, ik.u_values, ik.u_offsets, ik.feat_uoff, bound, pooled)
+    ctx.expand_inverse(F, B, pooled, ik.feat_uoff, ik.inverse, out)
+    assert torch.equal(out, kjt) and bool((pooled[ik.U:] == 7.0).all())
+    both = torch.full((F * B, D), 7.0, dtype=dt, device="cuda")
+    again = torch.full((F, B, D), float("nan"), dtype=dt, device="cuda")
+    ctx.pooled_lookup_expand(tabs, B, ik.u_values, runs, min(F * B, n_runs if slack == 0 else bound), both, again)
+    assert torch.equal(again, kjt) and torch.equal(both, pooled)
