@@ -10,13 +10,15 @@
 //                with the slot's current sample and, if equal, lowers the slot's sample index with
 //                an atomic min; if not, it probes on.  Hash collisions therefore never merge lists.
 //   number       a run head is a first occurrence iff its slot's final sample index is its own.
-//                Exclusive scan (look-back between blocks; of many rows by sums that a kernel before it leaves) of
+//                Exclusive scan (look-back between blocks; on shared scratch by sums that a kernel before it leaves) of
 //                (first, first*len) over all F*B lists in (f,b) order: the unique-list number and the position of
 //                its ids in u_values, both in first-occurrence order, and for followers the run head they copy
 //                (rep[f,b] = rep of the head = smallest b' with the same list).
 //   emit         inverse[f,b] = number[rep] - number[f,0]; first occurrences copy their ids.
 // The atomic min makes the result independent of insertion order: integer outputs are canonical.
 #include "recd_internal.h"
+
+#include <type_traits>
 
 namespace {
 
@@ -286,68 +288,192 @@ __device__ __forceinline__ void block_scan3(int64_t a, int64_t b, int64_t c, int
     eb = ob + ib - b;
 }
 
-// The scan of the numbering kernels, made of ballots: per thread two flags (first occurrence, run
-// head), the length of a first occurrence and the row of a run head.  Exclusive counts of the flags
-// and the nearest head at or before the thread come from wave ballots (no data moves between lanes);
-// only the lengths take a shuffle scan.  Totals of the block are returned to every thread.
-struct ListScan {
-    int64_t firsts_before, heads_before, len_before;  // exclusive, inside the block
-    int64_t head_row;                                  // nearest run head at or before the thread, -1: none yet
-    int64_t firsts, heads, len, last_head;             // block totals
-};
-
-template <bool TOTALS_ONLY>
-__device__ __forceinline__ ListScan block_scan_lists(bool first, bool head, int64_t flen, int64_t row)
+// Inclusive sums over the wave's lanes: shifts inside the rows of 16 lanes (data-parallel primitives,
+// no LDS traffic), then the totals of the rows before the lane's own.
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t x, int lane)
 {
-    __shared__ uint32_t s_first[kScanBlock / 64], s_heads[kScanBlock / 64];
-    __shared__ int64_t s_len[kScanBlock / 64], s_last[kScanBlock / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t mf = __ballot(first), mh = __ballot(head);
-    const uint64_t le = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1), lt = le >> 1;
-    ListScan r;
-    int64_t il = flen;  // inclusive sum of the lengths in the wave
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int64_t x = TOTALS_ONLY ? __shfl_xor(il, d) : __shfl_up(il, d);
-        if (TOTALS_ONLY || lane >= d)
-            il += x;
-    }
-    // row of the wave's lane k = row - lane + k
-    const uint64_t hb = mh & le;
-    r.head_row = hb ? row - lane + (63 - __builtin_clzll(hb)) : -1;
-    __syncthreads();  // the shared arrays are free again
-    if (lane == 63) {
-        s_first[w] = (uint32_t)__popcll(mf);
-        s_heads[w] = (uint32_t)__popcll(mh);
-        s_len[w] = il;  // lane 63 holds the wave's sum in either mode
-        s_last[w] = mh ? row - 63 + (63 - __builtin_clzll(mh)) : -1;
-    }
-    __syncthreads();
-    r.firsts_before = __popcll(mf & lt);
-    r.heads_before = __popcll(mh & lt);
-    r.len_before = il - flen;
-    r.firsts = r.heads = r.len = 0;
-    r.last_head = -1;
-    int64_t prev_last = -1;  // last head of the waves before this one (rows grow with the wave)
-    for (int i = 0; i < (int)(blockDim.x >> 6); i++) {
-        if (i < w) {
-            r.firsts_before += s_first[i];
-            r.heads_before += s_heads[i];
-            r.len_before += s_len[i];
-            prev_last = s_last[i] > prev_last ? s_last[i] : prev_last;
-        }
-        r.firsts += s_first[i];
-        r.heads += s_heads[i];
-        r.len += s_len[i];
-        r.last_head = s_last[i] > r.last_head ? s_last[i] : r.last_head;
-    }
-    if (r.head_row < 0)
-        r.head_row = prev_last;
-    return r;
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+    const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 15), t1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 31),
+                   t2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 47);
+    const int row = lane >> 4;
+    return x + (row >= 1 ? t0 : 0u) + (row >= 2 ? t1 : 0u) + (row >= 3 ? t2 : 0u);
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_flags(const int64_t *__restrict__ offsets, int64_t B,
-                                                      int64_t n_lists,
+// The same inside one row of 16 lanes only (lanes 0..15 of a wave hold the 16 values).
+__device__ __forceinline__ uint32_t row_scan_add(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    return x;
+}
+__device__ __forceinline__ int row_scan_max(int x)
+{
+    int y = __builtin_amdgcn_update_dpp(-1, x, 0x111, 0xf, 0xf, false);
+    x = y > x ? y : x;
+    y = __builtin_amdgcn_update_dpp(-1, x, 0x112, 0xf, 0xf, false);
+    x = y > x ? y : x;
+    y = __builtin_amdgcn_update_dpp(-1, x, 0x114, 0xf, 0xf, false);
+    x = y > x ? y : x;
+    y = __builtin_amdgcn_update_dpp(-1, x, 0x118, 0xf, 0xf, false);
+    return y > x ? y : x;
+}
+
+// The same of 64-bit numbers.
+__device__ __forceinline__ uint64_t row_scan_add64(uint64_t x)
+{
+    auto step = [&](auto shift) {
+        constexpr int kShift = decltype(shift)::value;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, kShift, 0xf, 0xf, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), kShift, 0xf, 0xf, false);
+        x += ((uint64_t)hi << 32) | lo;
+    };
+    step(std::integral_constant<int, 0x111>());
+    step(std::integral_constant<int, 0x112>());
+    step(std::integral_constant<int, 0x114>());
+    step(std::integral_constant<int, 0x118>());
+    return x;
+}
+
+// The scan of the numbering kernels, made of ballots.  A wave owns 64 R consecutive rows, its lane k the rows k, 64 + k, ...
+// of them, with two flags (first occurrence, run head; a first occurrence is a head), a run head's representative and the
+// length of a first occurrence.  What lies before a row in the block, exclusively, and the nearest head at or before it:
+// (row in the block + 1) << 32 | its representative, 0 for none.  Totals of the block are the same in every thread.
+template <int R> struct RowScan {
+    uint32_t firsts_before[R], heads_before[R];
+    uint64_t len_before[R], head[R];
+    uint32_t firsts, heads;
+    uint64_t len, last_head;
+};
+
+template <int R>
+__device__ __forceinline__ RowScan<R> block_scan_rows(const bool *first, const bool *head, const uint32_t *rep, const uint64_t *flen)
+{
+    constexpr int kWaves = kScanBlock / 64;
+    static_assert(kWaves == 16, "a row of 16 lanes scans the waves' totals");
+    __shared__ uint32_t s_cnt[kWaves], s_rep[kScanBlock * R];
+    __shared__ int s_last[kWaves];
+    __shared__ uint64_t s_len[kWaves];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t le = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1), lt = le >> 1;
+    RowScan<R> s;
+    int near[R], last = -1;  // nearest head at or before the row in the wave, by its place in the block
+    uint32_t nf = 0, nh = 0;
+    uint64_t ids = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int place = w * (64 * R) + r * 64;
+        const uint64_t mf = __ballot(first[r]), mh = __ballot(head[r]), hb = mh & le;
+        s.firsts_before[r] = nf + (uint32_t)__popcll(mf & lt);
+        s.heads_before[r] = nh + (uint32_t)__popcll(mh & lt);
+        nf += (uint32_t)__popcll(mf);
+        nh += (uint32_t)__popcll(mh);
+        near[r] = hb ? place + (63 - __builtin_clzll(hb)) : last;
+        last = mh ? place + (63 - __builtin_clzll(mh)) : last;
+        if (head[r])
+            s_rep[place + lane] = rep[r];
+        if (__ballot((flen[r] >> 25) != 0) == 0) {  // the wave's sum fits 32 bits
+            const uint32_t inc = wave_scan_add((uint32_t)flen[r], lane);
+            s.len_before[r] = ids + inc - flen[r];
+            ids += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        } else {
+            uint64_t inc = flen[r];
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint64_t x = __shfl_up(inc, d);
+                inc += lane >= d ? x : 0;
+            }
+            s.len_before[r] = ids + inc - flen[r];
+            ids += __shfl(inc, 63);
+        }
+    }
+    if (lane == 0) {
+        s_cnt[w] = nf | (nh << 16);  // a wave has at most 64 R of either
+        s_len[w] = ids;
+        s_last[w] = last;
+    }
+    __syncthreads();
+    // every wave scans the totals itself, in each of its rows of 16 lanes
+    const uint32_t c = s_cnt[lane & 15];
+    const uint32_t f_i = row_scan_add(c & 0xffff), h_i = row_scan_add(c >> 16);
+    const uint64_t l_i = row_scan_add64(s_len[lane & 15]);
+    const int last_i = row_scan_max(s_last[lane & 15]);
+    auto lane64 = [](uint64_t x, int k) {
+        return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), k) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, k);
+    };
+    s.firsts = (uint32_t)__builtin_amdgcn_readlane((int)f_i, 15);
+    s.heads = (uint32_t)__builtin_amdgcn_readlane((int)h_i, 15);
+    s.len = lane64(l_i, 15);
+    uint32_t pre_f = 0, pre_h = 0;
+    uint64_t pre_l = 0;
+    int pre_last = -1;
+    if (w > 0) {
+        pre_f = (uint32_t)__builtin_amdgcn_readlane((int)f_i, w - 1);
+        pre_h = (uint32_t)__builtin_amdgcn_readlane((int)h_i, w - 1);
+        pre_l = lane64(l_i, w - 1);
+        pre_last = __builtin_amdgcn_readlane(last_i, w - 1);
+    }
+    auto packed = [&](int at) { return at < 0 ? 0ull : ((uint64_t)(uint32_t)(at + 1) << 32) | s_rep[at]; };
+    s.last_head = packed(__builtin_amdgcn_readlane(last_i, 15));
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        s.firsts_before[r] += pre_f;
+        s.heads_before[r] += pre_h;
+        s.len_before[r] += pre_l;
+        s.head[r] = packed(near[r] < 0 ? pre_last : near[r]);
+    }
+    return s;
+}
+
+// What a numbering kernel finds out about its R rows: a run head's representative is its slot's final row, and a head is a
+// first occurrence iff that is its own.  offsets: null where the rows have no ids.
+template <int R> struct NumberRows {
+    uint32_t row[R], f[R], b[R], rep[R];
+    bool live[R], first[R], head[R];
+    uint64_t flen[R];
+    __device__ __forceinline__ void load(uint32_t blk, const int64_t *offsets, RecdDiv rows, uint32_t n_rows, const uint64_t *table,
+                                         uint32_t cap_mask, const int32_t *slot_of)
+    {
+        const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        int32_t slot[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            row[r] = blk * (kScanBlock * R) + w * (64 * R) + r * 64 + lane;
+            live[r] = row[r] < n_rows;
+            slot[r] = live[r] ? slot_of[row[r]] : -1;
+        }
+        uint64_t e[R];
+        int64_t len[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            f[r] = rows.of(row[r]);
+            b[r] = row[r] - f[r] * rows.by;
+            head[r] = slot[r] >= 0;
+            e[r] = 0;
+            len[r] = 0;
+            if (head[r]) {  // the lengths of all heads, though only first occurrences count: one round trip for both
+                e[r] = table[(uint64_t)f[r] * ((uint64_t)cap_mask + 1) + (uint32_t)slot[r]];
+                if (offsets)
+                    len[r] = offsets[row[r] + 1] - offsets[row[r]];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            rep[r] = (uint32_t)e[r];
+            first[r] = head[r] && rep[r] == b[r];
+            flen[r] = first[r] ? (uint64_t)len[r] : 0;
+        }
+    }
+};
+
+// The sums of every block for k_number<false>: first occurrences | run heads << 32, ids, and the last run head
+// ((row + 1) << 32 | representative, 0: none).
+__global__ __launch_bounds__(kScanBlock) void k_flags(const int64_t *__restrict__ offsets, RecdDiv rows, uint32_t n_rows,
                                                       const uint64_t *__restrict__ table,
                                                       uint32_t cap_mask,
                                                       const int32_t *__restrict__ slot_of,
@@ -355,27 +481,13 @@ __global__ __launch_bounds__(kScanBlock) void k_flags(const int64_t *__restrict_
                                                       int64_t *__restrict__ bs_len,
                                                       int64_t *__restrict__ bs_head)
 {
-    const int64_t l = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-    int64_t first = 0, flen = 0, head = -1;
-    if (l < n_lists) {
-        const int32_t slot = slot_of[l];
-        if (slot >= 0) {
-            head = l;
-            const int64_t f = l / B, b = l - f * B;
-            const uint64_t e = table[(uint64_t)f * ((uint64_t)cap_mask + 1) + (uint32_t)slot];
-            if ((int64_t)(e & 0xffffffffull) == b) {
-                first = 1;
-                flen = offsets ? offsets[l + 1] - offsets[l] : 0;
-            }
-        }
-    }
-    // two counts ride in one sum: first occurrences in the low half, run heads in the high half
-    // (both stay below 2^31)
-    const ListScan sc = block_scan_lists<true>(first != 0, head >= 0, flen, l);
+    NumberRows<1> x;
+    x.load(blockIdx.x, offsets, rows, n_rows, table, cap_mask, slot_of);
+    const RowScan<1> sc = block_scan_rows<1>(x.first, x.head, x.rep, x.flen);
     if (threadIdx.x == 0) {
-        bs_cnt[blockIdx.x] = sc.firsts + (sc.heads << 32);
-        bs_len[blockIdx.x] = sc.len;
-        bs_head[blockIdx.x] = sc.last_head;
+        bs_cnt[blockIdx.x] = (int64_t)(sc.firsts | ((uint64_t)sc.heads << 32));
+        bs_len[blockIdx.x] = (int64_t)sc.len;
+        bs_head[blockIdx.x] = sc.last_head ? (int64_t)(sc.last_head + ((uint64_t)(blockIdx.x * kScanBlock) << 32)) : 0;
     }
 }
 
@@ -411,7 +523,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_blocks(int64_t *a, int64_t 
 
 // Look-back between the blocks of a numbering kernel, which take their 1024 rows by tickets: a block waits only for blocks
 // that started before it, and says what it holds itself before it waits.  look: words that are kEmpty before the launch:
-// the ticket counter, and from kLookWords on, a block's own two sums and maximum + 1 and, four words on, those of it and
+// the ticket counter, and from kLookWords on, a block's own two sums and maximum and, four words on, those of it and
 // all before it.
 constexpr int kLookWords = 8;
 constexpr size_t look_words(int64_t rows) { return (size_t)kLookWords * (1 + (rows + kScanBlock - 1) / kScanBlock); }
@@ -425,15 +537,15 @@ __device__ __forceinline__ int64_t take_block(uint64_t *look)
     return s_block;
 }
 
-// a, b: the block's sums, c: its maximum (-1: none), the same in every thread; carry: those of all blocks before it.
+// a, b: the block's sums, c: its maximum (0: none), the same in every thread; carry: those of all blocks before it.
 // The block's first wave does it, 64 blocks at a time, the nearest first, up to one that knows all before it.
-__device__ __forceinline__ void look_back(uint64_t *look, int64_t blk, int64_t a, int64_t b, int64_t c, int64_t *carry)
+__device__ __forceinline__ void look_back(uint64_t *look, int64_t blk, uint64_t a, uint64_t b, uint64_t c, uint64_t *carry)
 {
     if (threadIdx.x >= 64)
         return;
     const int lane = threadIdx.x;
     uint64_t *const own = look + kLookWords * (1 + blk);
-    const uint64_t mine[3] = {(uint64_t)a, (uint64_t)b, (uint64_t)(c + 1)};
+    const uint64_t mine[3] = {a, b, c};
     if (lane < 3)
         __hip_atomic_store(own + lane, lane == 0 ? mine[0] : (lane == 1 ? mine[1] : mine[2]), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
@@ -475,15 +587,19 @@ __device__ __forceinline__ void look_back(uint64_t *look, int64_t blk, int64_t a
     if (lane < 3) {
         __hip_atomic_store(own + 4 + lane, lane == 0 ? upto[0] : (lane == 1 ? upto[1] : upto[2]), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-        carry[lane] = (int64_t)(lane == 0 ? sum[0] : (lane == 1 ? sum[1] : sum[2])) - (lane == 2 ? 1 : 0);
+        carry[lane] = lane == 0 ? sum[0] : (lane == 1 ? sum[1] : sum[2]);
     }
 }
 
-// A run head is a first occurrence iff its slot's final row is its own.  LOOK: the blocks learn what those before them hold
-// by look-back, else from sums that k_flags leaves (recd_looks_back).  offsets: null where the rows have no ids.
-template <bool LOOK>
-__global__ __launch_bounds__(kScanBlock) void k_number(const int64_t *__restrict__ offsets, int64_t B,
-                                                       int64_t n_lists, int F,
+// R rows a thread: one, or four of more rows than 256 blocks of 1024 hold.  LOOK: the blocks learn what those before them
+// hold by look-back, else (R = 1) from sums that k_flags leaves; that is for scratch that calls of other streams share.
+// us, k_flags and k_number / look-back with R = 2 / 4: 0.3 M rows 10.8 / 9.8 / 10.3, 0.5 M 13.0 / 12.6 / 12.2, 1.05 M 21.5 /
+// 20.8 / 16.8 (28.9 with 64-bit divisions, lengths read behind the table's words and heads' representatives read again),
+// 3.1 M 67 / 50 / 40.  65 K rows, R = 1: 8.9 -> 6.7.  offsets: null where the rows have no ids.
+constexpr int kManyRows = 4;
+template <bool LOOK, int R>
+__global__ __launch_bounds__(kScanBlock) void k_number(const int64_t *__restrict__ offsets, RecdDiv rows,
+                                                       uint32_t n_rows, int F,
                                                        const uint64_t *__restrict__ table,
                                                        uint32_t cap_mask,
                                                        const int32_t *__restrict__ slot_of,
@@ -501,40 +617,27 @@ __global__ __launch_bounds__(kScanBlock) void k_number(const int64_t *__restrict
                                                        int32_t *__restrict__ hrank = nullptr,
                                                        int64_t *__restrict__ run_index = nullptr)
 {
-    __shared__ int64_t s_carry[3];
-    const int64_t blk = LOOK ? take_block(look) : (int64_t)blockIdx.x;
-    const int64_t l = blk * kScanBlock + threadIdx.x;
-    int64_t first = 0, flen = 0, head = -1, b = -1, f = 0, my_rep = -1;
-    if (l < n_lists) {
-        f = l / B;
-        b = l - f * B;
-        const int32_t slot = slot_of[l];
-        if (slot >= 0) {
-            head = l;
-            const uint64_t e = table[(uint64_t)f * ((uint64_t)cap_mask + 1) + (uint32_t)slot];
-            my_rep = (int64_t)(e & 0xffffffffull);
-            if (my_rep == b) {
-                first = 1;
-                flen = offsets ? offsets[l + 1] - offsets[l] : 0;
-            }
-        }
-    }
-    const ListScan sc = block_scan_lists<false>(first != 0, head >= 0, flen, l);
+    __shared__ uint64_t s_carry[3];
+    const uint32_t blk = LOOK ? (uint32_t)take_block(look) : blockIdx.x;
+    NumberRows<R> x;
+    x.load(blk, offsets, rows, n_rows, table, cap_mask, slot_of);
+    const RowScan<R> sc = block_scan_rows<R>(x.first, x.head, x.rep, x.flen);
     if constexpr (LOOK) {
-        look_back(look, blk, sc.firsts + (sc.heads << 32), sc.len, sc.last_head, s_carry);
+        look_back(look, blk, sc.firsts | ((uint64_t)sc.heads << 32), sc.len,
+                  sc.last_head ? sc.last_head + ((uint64_t)(blk * (kScanBlock * R)) << 32) : 0, s_carry);
     } else if (threadIdx.x < 64) {  // the block's first wave adds up what k_flags left
-        int64_t pa = 0, pb = 0, pc = -1;
-        for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += 64) {
-            pa += bs_cnt[i];
-            pb += bs_len[i];
-            pc = bs_head[i] > pc ? bs_head[i] : pc;
+        uint64_t pa = 0, pb = 0, pc = 0;
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 64) {
+            pa += (uint64_t)bs_cnt[i];
+            pb += (uint64_t)bs_len[i];
+            pc = (uint64_t)bs_head[i] > pc ? (uint64_t)bs_head[i] : pc;
         }
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             pa += __shfl_xor(pa, d);
             pb += __shfl_xor(pb, d);
-            const int64_t x = __shfl_xor(pc, d);
-            pc = x > pc ? x : pc;
+            const uint64_t y = __shfl_xor(pc, d);
+            pc = y > pc ? y : pc;
         }
         if (threadIdx.x == 0) {
             s_carry[0] = pa;
@@ -543,34 +646,32 @@ __global__ __launch_bounds__(kScanBlock) void k_number(const int64_t *__restrict
         }
     }
     __syncthreads();
-    const int64_t carry_cnt = s_carry[0], carry_len = s_carry[1], carry_head = s_carry[2];
-    const int64_t ea = sc.firsts_before + (sc.heads_before << 32), eb = sc.len_before, ic = sc.head_row;
-    if (l < n_lists) {
-        const int64_t packed = carry_cnt + ea;   // first occurrences | run heads before l
+    const uint32_t carry_firsts = (uint32_t)s_carry[0], carry_heads = (uint32_t)(s_carry[0] >> 32);
+    const uint64_t carry_len = s_carry[1], carry_head = s_carry[2];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        if (!x.live[r])
+            continue;
+        const uint32_t l = x.row[r], heads = carry_heads + sc.heads_before[r];
         if (hrank)
-            hrank[l] = head >= 0 ? (int32_t)(packed >> 32) : -1;
-        if (head < 0) {
-            // follower: copy the representative of the run head (the nearest head at or before l;
-            // row 0 of a feature is always a head, so the run never leaves the feature)
-            const int64_t hl = ic > carry_head ? ic : carry_head;
-            const uint64_t e = table[(uint64_t)f * ((uint64_t)cap_mask + 1) + (uint32_t)slot_of[hl]];
-            my_rep = (int64_t)(e & 0xffffffffull);
-        }
-        rep[l] = (int32_t)my_rep;
-        const int64_t num = packed & 0xffffffffll;  // unique lists before (f,b), all features
-        const int64_t pos = carry_len + eb;  // their ids
+            hrank[l] = x.head[r] ? (int32_t)heads : -1;
+        // a follower has the representative of its run head, the nearest head before it (row 0 of a feature is always a
+        // head, so the run never leaves the feature)
+        rep[l] = (int32_t)(uint32_t)(x.head[r] ? x.rep[r] : (sc.head[r] ? sc.head[r] : carry_head));
+        const uint32_t num = carry_firsts + sc.firsts_before[r];  // unique lists before (f,b), all features
+        const int64_t pos = (int64_t)(carry_len + sc.len_before[r]);  // their ids
         number[l] = (int32_t)num;
-        if (first) {
+        if (x.first[r]) {
             u_offsets[num] = pos;
             src_of[num] = (int32_t)l;
         }
-        if (b == 0)
-            feat_uoff[f] = num;
-        if (l == n_lists - 1) {
-            const int64_t U = num + first, M = pos + flen;
+        if (x.b[r] == 0)
+            feat_uoff[x.f[r]] = num;
+        if (l == n_rows - 1) {
+            const int64_t U = (int64_t)num + x.first[r], M = pos + (int64_t)x.flen[r];
             u_offsets[U] = M;
             feat_uoff[F] = U;
-            const int64_t n_runs = (packed >> 32) + (head >= 0);  // runs of adjacent rows with one list
+            const int64_t n_runs = (int64_t)heads + x.head[r];  // runs of adjacent rows with one list
             counts[0] = U;
             counts[1] = M;
             counts[2] = n_runs;
@@ -579,7 +680,7 @@ __global__ __launch_bounds__(kScanBlock) void k_number(const int64_t *__restrict
                 run_index[0] = n_runs;
                 run_index[1] = U;
                 run_index[2] = M;
-                run_index[3 * (1 + n_runs)] = n_lists;
+                run_index[3 * (1 + n_runs)] = n_rows;
                 run_index[3 * (1 + n_runs) + 1] = M;
                 run_index[3 * (1 + n_runs) + 2] = 0;
             }
@@ -598,44 +699,49 @@ __global__ __launch_bounds__(kScanBlock) void k_number(const int64_t *__restrict
     }
 }
 
-// Last builder kernel, two kinds of blocks in one launch:
-//   blocks [0, inv_blocks): one thread per row, inverse[f,b] = number[rep] - number[f,0];
-//   the others: one group of SG lanes per *unique* list (source row recorded by k_number), striding
-//   until the device-side count U is reached, copy the list's ids into u_values.
+// Last builder kernel, three kinds of blocks in one launch:
+//   the first inv_blocks: one thread per row, inverse[f,b] = number[rep] - number[f,0];
+//   then copy_blocks: one group of SG lanes per *unique* list (source row recorded by k_number), striding
+//   until the device-side count U is reached, copy the list's ids into u_values, two ids a lane and kCopyFly strides in
+//   flight (one id a lane and one stride were 16 round trips for a list of 256 ids: 61 K lists of 2.2 M ids and 1.05 M rows
+//   26.9 -> 19.3 us, 14 K lists and 65 K rows 5.2 -> 4.4; 65 K lists of 10 ids and 0.5 M rows 9.4 / 9.8.  8 lanes a list, four
+//   strides, four rows a thread: no faster);
+//   the others leave the hash tables, which are no longer needed, empty for the next build.
+constexpr int kCopyFly = 2;
+
 template <int SG>
 __global__ __launch_bounds__(256) void k_emit(const int64_t *__restrict__ values,
-                                              const int64_t *__restrict__ offsets, int64_t B,
-                                              int64_t n_lists, const int32_t *__restrict__ rep,
+                                              const int64_t *__restrict__ offsets, RecdDiv rows,
+                                              uint32_t n_lists, const int32_t *__restrict__ rep,
                                               const int32_t *__restrict__ number,
                                               const int32_t *__restrict__ src_of,
                                               const int64_t *__restrict__ u_offsets,
                                               const int64_t *__restrict__ counts,
                                               int64_t *__restrict__ u_values,
-                                              int32_t *__restrict__ inverse, unsigned inv_blocks,
+                                              int32_t *__restrict__ inverse, unsigned inv_blocks, unsigned copy_blocks,
                                               const uint32_t *__restrict__ wbits = nullptr,
                                               uint32_t *__restrict__ u_wbits = nullptr,
-                                              unsigned fill_blocks = 0, uint64_t *fill = nullptr,
+                                              uint64_t *fill = nullptr,
                                               int64_t fill_n = 0, const int32_t *__restrict__ hrank = nullptr,
                                               int64_t *__restrict__ run_index = nullptr)
 {
-    if (blockIdx.x < fill_blocks) {
-        // the hash tables are no longer needed: leave them empty for the next build
-        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < fill_n; i += (int64_t)fill_blocks * 256)
+    if (blockIdx.x >= inv_blocks + copy_blocks) {
+        const int64_t at = blockIdx.x - inv_blocks - copy_blocks, blocks = gridDim.x - inv_blocks - copy_blocks;
+        for (int64_t i = at * 256 + threadIdx.x; i < fill_n; i += blocks * 256)
             fill[i] = kEmpty;
         return;
     }
-    const unsigned bid = blockIdx.x - fill_blocks;
-    if (bid < inv_blocks) {
-        const int64_t l = (int64_t)bid * 256 + threadIdx.x;
+    if (blockIdx.x < inv_blocks) {
+        const uint32_t l = blockIdx.x * 256 + threadIdx.x;
         if (l < n_lists) {
-            const int64_t f = l / B;
-            const int32_t u = number[f * B + rep[l]];
-            inverse[l] = u - number[f * B];
+            const uint32_t row0 = rows.of(l) * rows.by;
+            const int32_t u = number[row0 + (uint32_t)rep[l]];
+            inverse[l] = u - number[row0];
             if (run_index && hrank[l] >= 0) {
                 // run entry: {row | (unique list, first-occurrence flag) << 32, ids at, ids}
                 int64_t *e = run_index + 3 * (1 + (int64_t)hrank[l]);
-                const uint32_t uf = (uint32_t)u | (rep[l] == (int32_t)(l - f * B) ? 0x80000000u : 0u);
-                e[0] = (int64_t)(((uint64_t)uf << 32) | (uint32_t)l);
+                const uint32_t uf = (uint32_t)u | ((uint32_t)rep[l] == l - row0 ? 0x80000000u : 0u);
+                e[0] = (int64_t)(((uint64_t)uf << 32) | l);
                 e[1] = u_offsets[u];
                 e[2] = offsets[l + 1] - offsets[l];
             }
@@ -644,17 +750,38 @@ __global__ __launch_bounds__(256) void k_emit(const int64_t *__restrict__ values
     }
     const int s = threadIdx.x % SG;
     const int64_t U = counts[0];
-    const int64_t stride = (int64_t)(gridDim.x - fill_blocks - inv_blocks) * (256 / SG);
-    for (int64_t u = (int64_t)(bid - inv_blocks) * (256 / SG) + threadIdx.x / SG; u < U;
-         u += stride) {
+    const int64_t stride = (int64_t)copy_blocks * (256 / SG);
+    for (int64_t u = (int64_t)(blockIdx.x - inv_blocks) * (256 / SG) + threadIdx.x / SG; u < U; u += stride) {
         const int64_t l = src_of[u];
         const int64_t start = offsets[l], len = offsets[l + 1] - start;
         const int64_t dst = u_offsets[u];
-        for (int64_t t = s; t < len; t += SG)
-            u_values[dst + t] = values[start + t];
-        if (wbits)  // the weights of a weighted KJT travel with the ids
-            for (int64_t t = s; t < len; t += SG)
-                u_wbits[dst + t] = wbits[start + t];
+        if (len == 1 && s == 0) {
+            u_values[dst] = values[start];
+            if (wbits)  // the weights of a weighted KJT travel with the ids
+                u_wbits[dst] = wbits[start];
+        }
+        for (int64_t t0 = 2 * s; t0 < len && len > 1; t0 += 2 * SG * kCopyFly) {
+            id2 x[kCopyFly];
+            wt2 y[kCopyFly];
+            int64_t at[kCopyFly];  // at an odd end the last two once more
+#pragma unroll
+            for (int k = 0; k < kCopyFly; k++) {
+                const int64_t t = t0 + 2 * SG * k;
+                at[k] = t + 1 < len ? t : len - 2;
+                if (t < len) {
+                    x[k] = *reinterpret_cast<const id2 *>(values + start + at[k]);
+                    if (wbits)
+                        y[k] = *reinterpret_cast<const wt2 *>(wbits + start + at[k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kCopyFly; k++)
+                if (t0 + 2 * SG * k < len) {
+                    *reinterpret_cast<id2 *>(u_values + dst + at[k]) = x[k];
+                    if (wbits)
+                        *reinterpret_cast<wt2 *>(u_wbits + dst + at[k]) = y[k];
+                }
+        }
     }
 }
 
@@ -708,41 +835,6 @@ __device__ __forceinline__ bool small_gather(const uint64_t *agg, int n, int lan
         ok &= __shfl_xor(ok, d);
     }
     return ok != 0;
-}
-
-// Inclusive sums over the wave's lanes: shifts inside the rows of 16 lanes (data-parallel primitives,
-// no LDS traffic), then the totals of the rows before the lane's own.
-__device__ __forceinline__ uint32_t wave_scan_add(uint32_t x, int lane)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
-    const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 15), t1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 31),
-                   t2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 47);
-    const int row = lane >> 4;
-    return x + (row >= 1 ? t0 : 0u) + (row >= 2 ? t1 : 0u) + (row >= 3 ? t2 : 0u);
-}
-
-// The same inside one row of 16 lanes only (lanes 0..15 of a wave hold the 16 values).
-__device__ __forceinline__ uint32_t row_scan_add(uint32_t x)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
-    return x;
-}
-__device__ __forceinline__ int row_scan_max(int x)
-{
-    int y = __builtin_amdgcn_update_dpp(-1, x, 0x111, 0xf, 0xf, false);
-    x = y > x ? y : x;
-    y = __builtin_amdgcn_update_dpp(-1, x, 0x112, 0xf, 0xf, false);
-    x = y > x ? y : x;
-    y = __builtin_amdgcn_update_dpp(-1, x, 0x114, 0xf, 0xf, false);
-    x = y > x ? y : x;
-    y = __builtin_amdgcn_update_dpp(-1, x, 0x118, 0xf, 0xf, false);
-    return y > x ? y : x;
 }
 
 // agg: 2 words per feature, then the arrival counter and the failure mark; all zero between launches.
@@ -1169,7 +1261,7 @@ __global__ __launch_bounds__(256) void k_group_hash_insert(const int64_t *__rest
 enum { COMPACT_SUMS = 0, COMPACT_NUMBER = 1, COMPACT_LOOK = 2 };
 template <int STEP>
 __global__ __launch_bounds__(kScanBlock) void k_group_compact(const int64_t *__restrict__ offsets,
-                                                              int64_t B, int64_t n_lists, int F,
+                                                              RecdDiv rows, uint32_t n_lists, int F,
                                                               const int32_t *__restrict__ feat_group,
                                                               const int32_t *__restrict__ rep_g,
                                                               const int32_t *__restrict__ number_g,
@@ -1183,37 +1275,34 @@ __global__ __launch_bounds__(kScanBlock) void k_group_compact(const int64_t *__r
                                                               int32_t *__restrict__ inverse_f,
                                                               int64_t *__restrict__ counts)
 {
-    __shared__ int64_t s_carry[3];
-    const int64_t blk = STEP == COMPACT_LOOK ? take_block(look) : (int64_t)blockIdx.x;
-    const int64_t l = blk * kScanBlock + threadIdx.x;
-    int64_t first = 0, flen = 0, f = 0, b = -1, row0 = 0, rep = 0;
+    __shared__ uint64_t s_carry[3];
+    const uint32_t blk = STEP == COMPACT_LOOK ? (uint32_t)take_block(look) : blockIdx.x;
+    const uint32_t l = blk * kScanBlock + threadIdx.x, f = rows.of(l), b = l - f * rows.by;
+    uint32_t row0 = 0, rep = ~0u;
+    uint64_t flen = 0;
     if (l < n_lists) {
-        f = l / B;
-        b = l - f * B;
-        row0 = (int64_t)feat_group[f] * B;
-        rep = rep_g[row0 + b];
-        if (rep == b) {
-            first = 1;
-            flen = offsets[l + 1] - offsets[l];
-        }
+        const int64_t len = offsets[l + 1] - offsets[l];
+        row0 = (uint32_t)feat_group[f] * rows.by;
+        rep = (uint32_t)rep_g[row0 + b];
+        flen = rep == b ? (uint64_t)len : 0;
     }
-    int64_t ea, eb, ic, ta, tb, tc;
-    block_scan3(first, flen, -1, ea, eb, ic, ta, tb, tc);
+    const bool first = rep == b, none = false;
+    const RowScan<1> sc = block_scan_rows<1>(&first, &none, &rep, &flen);
     if (STEP == COMPACT_SUMS) {
         if (threadIdx.x == 0) {
-            bs_cnt[blockIdx.x] = ta;
-            bs_len[blockIdx.x] = tb;
+            bs_cnt[blockIdx.x] = sc.firsts;
+            bs_len[blockIdx.x] = (int64_t)sc.len;
             bs_head[blockIdx.x] = -1;
         }
         return;
     }
     if (STEP == COMPACT_LOOK) {
-        look_back(look, blk, ta, tb, -1, s_carry);
+        look_back(look, blk, sc.firsts, sc.len, 0, s_carry);
         __syncthreads();
     }
     if (l < n_lists) {
-        const int64_t num = (STEP == COMPACT_LOOK ? s_carry[0] : bs_cnt[blockIdx.x]) + ea;
-        const int64_t pos = (STEP == COMPACT_LOOK ? s_carry[1] : bs_len[blockIdx.x]) + eb;
+        const int64_t num = (int64_t)((STEP == COMPACT_LOOK ? s_carry[0] : (uint64_t)bs_cnt[blockIdx.x]) + sc.firsts_before[0]);
+        const int64_t pos = (int64_t)((STEP == COMPACT_LOOK ? s_carry[1] : (uint64_t)bs_len[blockIdx.x]) + sc.len_before[0]);
         if (first) {
             u_offsets[num] = pos;
             src_of[num] = (int32_t)l;
@@ -1223,7 +1312,7 @@ __global__ __launch_bounds__(kScanBlock) void k_group_compact(const int64_t *__r
         if (inverse_f)
             inverse_f[l] = number_g[row0 + rep] - number_g[row0];
         if (l == n_lists - 1) {
-            const int64_t U = num + first, M = pos + flen;
+            const int64_t U = num + first, M = pos + (int64_t)flen;
             u_offsets[U] = M;
             feat_uoff[F] = U;
             counts[0] = U;
@@ -1566,20 +1655,22 @@ void number_slots(hipStream_t st, const SlotWs &w, int tables, int64_t B, const 
                   int64_t *u_off, int64_t *uoff, int64_t *mailbox = nullptr, int64_t seq = 0,
                   int64_t *run_index = nullptr)
 {
-    const int64_t n = (int64_t)tables * B;
-    const unsigned nblk = (unsigned)((n + kScanBlock - 1) / kScanBlock);
-    const uint32_t mask = (uint32_t)(w.cap - 1);
+    const uint32_t n = (uint32_t)(tables * B), mask = (uint32_t)(w.cap - 1);
+    const RecdDiv rows = recd_divide_by((uint32_t)B);
+    auto number = [&](auto kernel, uint32_t rows_per_block) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(((int64_t)n + rows_per_block - 1) / rows_per_block)), dim3(kScanBlock), 0, st,
+                           offsets, rows, n, tables, w.table, mask, w.slot_of, w.look, w.bs_cnt, w.bs_len, w.bs_head, w.rep,
+                           w.number, w.src_of, u_off, uoff, w.counts, mailbox, seq, run_index ? w.hrank : nullptr, run_index);
+    };
     if (recd_looks_back(n, !w.look)) {
-        hipLaunchKernelGGL(k_number<true>, dim3(nblk), dim3(kScanBlock), 0, st, offsets, B, n, tables, w.table, mask,
-                           w.slot_of, w.look, nullptr, nullptr, nullptr, w.rep, w.number, w.src_of, u_off, uoff,
-                           w.counts, mailbox, seq, run_index ? w.hrank : nullptr, run_index);
-        return;
+        number(k_number<true, 1>, kScanBlock);
+    } else if (w.look) {
+        number(k_number<true, kManyRows>, kScanBlock * kManyRows);
+    } else {  // scratch that calls of other streams share
+        hipLaunchKernelGGL(k_flags, dim3((unsigned)(((int64_t)n + kScanBlock - 1) / kScanBlock)), dim3(kScanBlock), 0, st, offsets,
+                           rows, n, w.table, mask, w.slot_of, w.bs_cnt, w.bs_len, w.bs_head);
+        number(k_number<false, 1>, kScanBlock);
     }
-    hipLaunchKernelGGL(k_flags, dim3(nblk), dim3(kScanBlock), 0, st, offsets, B, n, w.table, mask, w.slot_of,
-                       w.bs_cnt, w.bs_len, w.bs_head);
-    hipLaunchKernelGGL(k_number<false>, dim3(nblk), dim3(kScanBlock), 0, st, offsets, B, n, tables, w.table, mask,
-                       w.slot_of, nullptr, w.bs_cnt, w.bs_len, w.bs_head, w.rep, w.number, w.src_of, u_off, uoff,
-                       w.counts, mailbox, seq, run_index ? w.hrank : nullptr, run_index);
 }
 
 unsigned copy_blocks_for(const recd_ctx *ctx, int64_t n_lists)
@@ -1588,6 +1679,20 @@ unsigned copy_blocks_for(const recd_ctx *ctx, int64_t n_lists)
     if (b > (int64_t)ctx->num_cu * 8)
         b = (int64_t)ctx->num_cu * 8;
     return (unsigned)b;
+}
+
+// The inverse of `rows` rows and, of at most `lists` stored ones, the ids; clears the n words at `fill`.
+void emit_lists(const recd_ctx *ctx, hipStream_t st, int64_t B, uint32_t rows, int64_t lists, const int64_t *values,
+                const int64_t *offsets, const SlotWs &w, const int32_t *src_of, const int64_t *u_offsets, const int64_t *counts,
+                int64_t *u_values, int32_t *inverse, const uint32_t *weights = nullptr, uint32_t *u_weights = nullptr,
+                uint64_t *fill = nullptr, int64_t n = 0, int64_t *run_index = nullptr)
+{
+    const unsigned copy = lists > 0 ? copy_blocks_for(ctx, lists) : 0;
+    const int64_t fill_blocks = (n + 4095) / 4096 < 2048 ? (n + 4095) / 4096 : 2048;
+    const unsigned inv = (unsigned)(((uint64_t)rows + 255) / 256);
+    hipLaunchKernelGGL((k_emit<16>), dim3(inv + copy + (unsigned)fill_blocks), dim3(256), 0, st, values, offsets,
+                       recd_divide_by((uint32_t)B), rows, w.rep, w.number, src_of, u_offsets, counts, u_values, inverse, inv, copy,
+                       weights, u_weights, fill, n, w.hrank, run_index);
 }
 
 } // namespace
@@ -1711,13 +1816,9 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
             published = true;
         }
         number_slots(st, w, F, B, offsets, u_offsets, feat_uoff, mailbox, seq, run_index);
-        const unsigned inv_blocks = (unsigned)((n_lists + 255) / 256);
-        const unsigned fill_blocks = (unsigned)((slots + 4095) / 4096 < 2048 ? (slots + 4095) / 4096 : 2048);
         recd_time_begin(ctx, RECD_T_EMIT, st);
-        hipLaunchKernelGGL((k_emit<16>), dim3(fill_blocks + inv_blocks + copy_blocks_for(ctx, n_lists)), dim3(256), 0,
-                           st, values, offsets, B, n_lists, w.rep, w.number, w.src_of, u_offsets, counts,
-                           u_values, inverse, inv_blocks, weights, u_weights, fill_blocks, ctx->build_table,
-                           (int64_t)slots, w.hrank, run_index);
+        emit_lists(ctx, st, B, (uint32_t)n_lists, n_lists, values, offsets, w, w.src_of, u_offsets, counts, u_values, inverse, weights,
+                   u_weights, ctx->build_table, (int64_t)slots, run_index);
         recd_time_end(ctx, RECD_T_EMIT, st);
         RECD_HIP(ctx, hipGetLastError());
         ctx->table_clean = true;
@@ -1811,10 +1912,7 @@ extern "C" recd_status recd_build_ikjt_noalloc(recd_ctx *ctx, int F, int64_t B, 
         // before it is read
         insert_lists(ctx, st, w, F, B, values, offsets, nullptr, false);
         number_slots(st, w, F, B, offsets, u_offsets, feat_uoff);
-        const unsigned inv_blocks = (unsigned)((n_lists + 255) / 256);
-        hipLaunchKernelGGL((k_emit<16>), dim3(inv_blocks + copy_blocks_for(ctx, n_lists)), dim3(256), 0, st, values,
-                           offsets, B, n_lists, w.rep, w.number, w.src_of, u_offsets, w.counts, u_values, inverse,
-                           inv_blocks);
+        emit_lists(ctx, st, B, (uint32_t)n_lists, n_lists, values, offsets, w, w.src_of, u_offsets, w.counts, u_values, inverse);
     }
     RECD_HIP(ctx, hipGetLastError());
     return RECD_OK;
@@ -1943,8 +2041,8 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
         // per feature: which lists are stored, where
         const int64_t nblk = (n_lists + kScanBlock - 1) / kScanBlock;
         auto compact = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(kScanBlock), 0, st, offsets, B, n_lists, F,
-                               dev_feat_group, w.rep, w.number, w.look_lists, w.bs_cnt, w.bs_len, w.bs_head, src_of,
+            hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(kScanBlock), 0, st, offsets,
+                               recd_divide_by((uint32_t)B), (uint32_t)n_lists, F, dev_feat_group, w.rep, w.number, w.look_lists, w.bs_cnt, w.bs_len, w.bs_head, src_of,
                                u_offsets, feat_uoff, inverse_per_feature, counts);
         };
         if (recd_looks_back(n_lists, false)) {
@@ -1955,10 +2053,7 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
             compact(k_group_compact<COMPACT_NUMBER>);
         }
         // the groups' inverse from their rows' numbers, and the stored lists' ids
-        const unsigned inv_blocks = (unsigned)((n_items + 255) / 256);
-        hipLaunchKernelGGL((k_emit<16>), dim3(inv_blocks + copy_blocks_for(ctx, n_lists)), dim3(256), 0, st, values,
-                           offsets, B, n_items, w.rep, w.number, src_of, u_offsets, counts, u_values, inverse_g,
-                           inv_blocks);
+        emit_lists(ctx, st, B, (uint32_t)n_items, n_lists, values, offsets, w, src_of, u_offsets, counts, u_values, inverse_g);
     }
     RECD_HIP(ctx, hipGetLastError());
     if (host_counts) {
@@ -2009,8 +2104,7 @@ extern "C" recd_status recd_build_partial_ikjt(recd_ctx *ctx, int F, int64_t B, 
         insert_lists(ctx, st, w, F, B, values, offsets);
         number_slots(st, w, F, B, offsets, u_off, feat_uoff);
         const unsigned inv_blocks = (unsigned)((n_lists + 255) / 256);
-        hipLaunchKernelGGL((k_emit<16>), dim3(inv_blocks), dim3(256), 0, st, values, offsets, B, n_lists,
-                           w.rep, w.number, src_of, u_off, counts, p_values, inverse, inv_blocks);
+        emit_lists(ctx, st, B, (uint32_t)n_lists, 0, values, offsets, w, src_of, u_off, counts, p_values, inverse);
         int64_t ov_blocks = (n_lists + 3) / 4;
         if (ov_blocks > (int64_t)ctx->num_cu * 16)
             ov_blocks = (int64_t)ctx->num_cu * 16;

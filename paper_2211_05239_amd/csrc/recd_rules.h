@@ -122,13 +122,11 @@ RECD_RULE int recd_jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vec
     return lists;
 }
 
-// Whether the builders number their rows in one launch whose blocks wait for what those before them hold (look-back): up to
-// 256 blocks of 1024 rows, beyond that a launch for the blocks' sums and one for the numbers.  Build of sessions of 8 in
-// two launches / by look-back, us: 20 K lists 19.3 / 16.6, 65 K 22.4 / 19.4, 131 K 25.4 / 23.5, 262 K 33.0 / 33.2, 400 K
-// 43.0 / 45.6, 1.05 M 87.9 / 93.4; in groups of four features, whose lists are then numbered too (in three launches else):
-// 65 K 38.9 / 27.4, 262 K 44.7 / 36.8, 524 K 55.9 / 53.6.  Never on scratch that calls of other streams share: one that
-// overlaps may give wrong numbers there, but as it clears the words that the blocks of the other wait for, neither might
-// return.
+// Whether the builders number their rows one a thread in one launch whose blocks wait for what those before them hold
+// (look-back): up to 256 blocks of 1024 rows.  Of more rows a thread takes four (k_number).  The stored lists of groups of
+// features are then numbered too, of more in three launches: in groups of four build 65 K 38.9 / 27.4 us in three launches /
+// by look-back, 262 K 44.7 / 36.8, 524 K 55.9 / 53.6.  Never on scratch that calls of other streams share: one that overlaps
+// may give wrong numbers there, but as it clears the words that the blocks of the other wait for, neither might return.
 RECD_RULE bool recd_looks_back(int64_t rows, bool shared_scratch) { return !shared_scratch && rows <= 256 * 1024; }
 
 // Whether the grouping of a backward pass is short: its sides go by small tiles, and a plan goes in line, since the events

@@ -86,3 +86,24 @@ def test_lookups_under_tight_and_loose_bounds(ctx, F, B, S, slack):
     again = torch.full((F, B, D), float("nan"), dtype=dt, device="cuda")
     ctx.pooled_lookup_expand(tabs, B, ik.u_values, runs, min(F * B, n_runs if slack == 0 else bound), both, again)
     assert torch.equal(again, kjt) and torch.equal(both, pooled)
+
+
+@pytest.mark.parametrize("F,B", [(1, 1025), (3, 4096), (5, 52429), (6, 43691), (8, 65537), (2, 262144 + 4096 * 3 + 1)])
+def test_numbering_across_waves_and_blocks(ctx, F, B):
+    """One row and four rows a thread; runs that begin a feature, a wave and a block or go on across several of them, lists
+    that come back blocks later, and lists of 0, 1, 32, 33 and 70 ids to be copied."""
+    rng = np.random.default_rng(F * B)
+    base = [rng.integers(0, 1000, n) for n in (0, 1, 2, 32, 33, 70, 5, 4)]
+    cuts = np.unique(np.concatenate([[0], rng.integers(0, B, 40), np.arange(0, B, 4096), np.arange(64, B, 9 * 1024) - 1]))
+    cuts = cuts[(cuts < B) & ~((cuts > 20000) & (cuts < 33000))]
+    lists = []
+    for f in range(F):
+        which = rng.integers(0, len(base), len(cuts))
+        lists.append(np.repeat(which, np.diff(np.append(cuts, B))))
+    which = np.concatenate(lists)
+    lens = np.array([len(x) for x in base])[which]
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    flat, start = np.concatenate(base), np.concatenate([[0], np.cumsum([len(x) for x in base])])[:-1]
+    values = flat[np.repeat(start[which] - offsets[:-1], lens) + np.arange(offsets[-1])].astype(np.int64)
+    batch = synth.Batch(F, B, values, offsets, np.zeros(B, np.int32), 1.0)
+    _check(gu.gpu_build(ctx, batch)[2], batch)
