@@ -183,24 +183,50 @@ __device__ __forceinline__ void fetch_row(const OptAdagrad &opt, int D, int f, i
 // elements of the row that the entry's position won.
 enum { ROWS_PLAIN = 0, ROWS_WEIGHTED = 1, ROWS_MAX = 2 };
 
-// Piece w * LPR + r of an entry's source row; won: the entry's word r (max pooling).
-template <int LPR, int MODE>
-__device__ __forceinline__ float4 entry_piece(const RowSumParams &p, uint32_t id, int w, int r, uint32_t won)
+// Piece w * LPR + r of an entry's source row.
+template <int LPR>
+__device__ __forceinline__ float4 entry_piece(const RowSumParams &p, uint32_t id, int w, int r)
 {
-    float4 v = reinterpret_cast<const float4 *>(p.table)[(int64_t)id * p.pieces + w * LPR + r];
-    if constexpr (MODE == ROWS_MAX) {
-        won >>= 8 * w;
-        v.x = won & 1u ? v.x : 0.f;
-        v.y = won & 2u ? v.y : 0.f;
-        v.z = won & 4u ? v.z : 0.f;
-        v.w = won & 8u ? v.w : 0.f;
-    }
-    return v;
+    return reinterpret_cast<const float4 *>(p.table)[(int64_t)id * p.pieces + w * LPR + r];
 }
 
-template <int LPR, int MODE> __device__ __forceinline__ uint32_t entry_won(const RowSumParams &p, uint32_t x, int r)
+// acc + what of v the four low bits of `won` leave.
+__device__ __forceinline__ void add_masked(float4 &acc, const float4 &v, uint32_t won)
 {
-    return MODE == ROWS_MAX ? p.won[(int64_t)x * LPR + r] : 0u;
+    auto left = [&](float x, int bit) { return __uint_as_float(__float_as_uint(x) & (uint32_t)((int)(won << (31 - bit)) >> 31)); };
+    acc.x += left(v.x, 0);
+    acc.y += left(v.y, 1);
+    acc.z += left(v.z, 2);
+    acc.w += left(v.w, 3);
+}
+
+// Max pooling: adds to acc what a lane group's segment's next one or two entries won (n of them count).  Lane lane0 + i holds
+// the i-th one's source row (pre) and position (prex).  An entry of a list of 25 ids won one element in 25, so six lanes in
+// seven have nothing to read of its row: those that have read both entries' pieces side by side.  (Every lane the whole row of
+// one entry after the other, 0.3 M positions of 512 bytes: 76 us, now 52; each lane its own next of eight entries 67; what
+// is left is the update's 120 MB of scattered table rows and the 32 bytes of every position's words.)
+template <int LPR>
+__device__ __forceinline__ void add_won(const RowSumParams &p, float4 *acc, uint32_t pre, uint32_t prex, int lane0, int n, int r)
+{
+    constexpr int VPL = 4;
+    const uint32_t x0 = __shfl(prex, lane0), x1 = __shfl(prex, lane0 + (n > 1 ? 1 : 0));
+    const uint32_t id0 = __shfl(pre, lane0), id1 = __shfl(pre, lane0 + (n > 1 ? 1 : 0));
+    const uint32_t won0 = p.won[(int64_t)x0 * LPR + r], won1 = n > 1 ? p.won[(int64_t)x1 * LPR + r] : 0u;
+    float4 v0[VPL], v1[VPL];
+#pragma unroll
+    for (int w = 0; w < VPL; w++) {
+        if ((won0 >> (8 * w)) & 15u)
+            v0[w] = entry_piece<LPR>(p, id0, w, r);
+        if ((won1 >> (8 * w)) & 15u)
+            v1[w] = entry_piece<LPR>(p, id1, w, r);
+    }
+#pragma unroll
+    for (int w = 0; w < VPL; w++) {
+        if ((won0 >> (8 * w)) & 15u)
+            add_masked(acc[w], v0[w], won0 >> (8 * w));
+        if ((won1 >> (8 * w)) & 15u)
+            add_masked(acc[w], v1[w], won1 >> (8 * w));
+    }
 }
 
 template <int MODE> __device__ __forceinline__ uint32_t entry_extra(const RowSumParams &p, int64_t i)
@@ -238,34 +264,31 @@ __device__ __forceinline__ void sum_chunk(const RowSumParams &p, const OptAdagra
         const uint32_t idx = base + r * (W * G);
         const uint32_t pre = idx < c.end ? p.pay[idx] : 0u, prex = idx < c.end ? entry_extra<MODE>(p, idx) : 0u;
         const int left = (int)((c.end - base + W * G - 1) / (W * G)), cnt = left < LPR ? left : LPR;
-        for (int i0 = 0; i0 < cnt; i0 += 4) {
-            uint32_t won[4];
+        if constexpr (MODE == ROWS_MAX) {
+#pragma unroll 1
+            for (int i0 = 0; i0 < cnt; i0 += 2)
+                add_won<LPR>(p, acc, pre, prex, gbase + i0, cnt - i0, r);
+            continue;
+        }
+        for (int i0 = 0; i0 < cnt; i0 += 2) {
+            const bool two = i0 + 1 < cnt;
+            const int k1 = i0 + (two ? 1 : 0);
+            const uint32_t id0 = __shfl(pre, gbase + i0), id1 = __shfl(pre, gbase + k1);
+            const uint32_t x0 = __shfl(prex, gbase + i0), x1 = __shfl(prex, gbase + k1);
+            float4 v0[VPL], v1[VPL];
 #pragma unroll
-            for (int i = 0; i < 4; i++)
-                won[i] = entry_won<LPR, MODE>(p, __shfl(prex, gbase + (i0 + i < cnt ? i0 + i : cnt - 1)), r);
+            for (int w = 0; w < VPL; w++)
+                if (piece[w]) {
+                    v0[w] = entry_piece<LPR>(p, id0, w, r);
+                    v1[w] = entry_piece<LPR>(p, id1, w, r);
+                }
 #pragma unroll
-            for (int i = 0; i < 4; i += 2) {
-                const bool one = i0 + i < cnt, two = i0 + i + 1 < cnt;
-                if (!one)
-                    break;
-                const int k1 = i0 + i + (two ? 1 : 0);
-                const uint32_t id0 = __shfl(pre, gbase + i0 + i), id1 = __shfl(pre, gbase + k1);
-                const uint32_t x0 = __shfl(prex, gbase + i0 + i), x1 = __shfl(prex, gbase + k1);
-                float4 v0[VPL], v1[VPL];
-#pragma unroll
-                for (int w = 0; w < VPL; w++)
-                    if (piece[w]) {
-                        v0[w] = entry_piece<LPR, MODE>(p, id0, w, r, won[i]);
-                        v1[w] = entry_piece<LPR, MODE>(p, id1, w, r, won[i + 1]);
-                    }
-#pragma unroll
-                for (int w = 0; w < VPL; w++)
-                    if (piece[w]) {
-                        add4<MODE>(acc[w], v0[w], x0);
-                        if (two)
-                            add4<MODE>(acc[w], v1[w], x1);
-                    }
-            }
+            for (int w = 0; w < VPL; w++)
+                if (piece[w]) {
+                    add4<MODE>(acc[w], v0[w], x0);
+                    if (two)
+                        add4<MODE>(acc[w], v1[w], x1);
+                }
         }
     }
 #pragma unroll
@@ -393,7 +416,7 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
         const bool update = mine && opt.n_feat > 0;
         // second round trip: the segment's entries (the first kPre * LPR of them, one load per lane
         // and LPR entries) together with the destination row and its accumulator
-        constexpr int kPre = 4;
+        constexpr int kPre = MODE == ROWS_MAX ? 1 : 4;
         uint32_t pre[kPre], prex[kPre];
 #pragma unroll
         for (int u = 0; u < kPre; u++) {
@@ -410,46 +433,46 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
 #pragma unroll
         for (int w = 0; w < VPL; w++)
             acc[w] = make_float4(0.f, 0.f, 0.f, 0.f);
-        auto add_entry = [&](uint32_t id, uint32_t x, uint32_t won) {
+        auto add_entry = [&](uint32_t id, uint32_t x) {
             float4 v[VPL];
 #pragma unroll
             for (int w = 0; w < VPL; w++)
                 if (piece[w])
-                    v[w] = entry_piece<LPR, MODE>(p, id, w, r, won);
+                    v[w] = entry_piece<LPR>(p, id, w, r);
 #pragma unroll
             for (int w = 0; w < VPL; w++)
                 if (piece[w])
                     add4<MODE>(acc[w], v[w], x);
         };
         // entries in ascending order: the fetched ones come out of the lane group's registers, any
-        // further ones (cuts above kPre * LPR entries) are read one by one
+        // further ones (cuts above kPre * LPR entries) are read one by one, or again by all lanes
         const int gbase = lane - r;
-#pragma unroll
-        for (int u = 0; u < kPre; u++) {
-            const int cnt = n - u * LPR < LPR ? n - u * LPR : LPR;
-            if constexpr (MODE == ROWS_MAX) {
-                // the words come from memory (another XCD wrote them) while the rows of g_u are in L2: those of
-                // eight entries are fetched ahead of the walk
-                for (int i0 = 0; i0 < cnt; i0 += 8) {
-                    uint32_t won[8];
-#pragma unroll
-                    for (int i = 0; i < 8; i++)
-                        won[i] = entry_won<LPR, MODE>(p, __shfl(prex[u], gbase + (i0 + i < cnt ? i0 + i : cnt - 1)), r);
-#pragma unroll
-                    for (int i = 0; i < 8; i++)
-                        if (i0 + i < cnt)
-                            add_entry(__shfl(pre[u], gbase + i0 + i), 0u, won[i]);
+        if constexpr (MODE == ROWS_MAX) {
+            uint32_t id = pre[0], x = prex[0];
+#pragma unroll 1
+            for (int i1 = 0; i1 < n; i1 += LPR) {
+                if (i1 > 0) {
+                    id = i1 + r < n ? p.pay[start + i1 + r] : 0u;
+                    x = i1 + r < n ? p.pay_pos[start + i1 + r] : 0u;
                 }
-            } else {
+                const int cnt = n - i1 < LPR ? n - i1 : LPR;
+#pragma unroll 1
+                for (int i0 = 0; i0 < cnt; i0 += 2)
+                    add_won<LPR>(p, acc, id, x, gbase + i0, cnt - i0, r);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kPre; u++) {
+                const int cnt = n - u * LPR < LPR ? n - u * LPR : LPR;
                 for (int ii = 0; ii < cnt; ii++) {
                     const uint32_t id = __shfl(pre[u], gbase + ii);
-                    add_entry(id, MODE != ROWS_PLAIN ? __shfl(prex[u], gbase + ii) : 0u, 0u);
+                    add_entry(id, MODE != ROWS_PLAIN ? __shfl(prex[u], gbase + ii) : 0u);
                 }
             }
-        }
-        for (int i = kPre * LPR; i < n; i++) {
-            const uint32_t x = entry_extra<MODE>(p, start + i);
-            add_entry(p.pay[start + i], x, entry_won<LPR, MODE>(p, x, r));
+            for (int i = kPre * LPR; i < n; i++) {
+                const uint32_t x = entry_extra<MODE>(p, start + i);
+                add_entry(p.pay[start + i], x);
+            }
         }
         if (mine)
             finish_segment<LPR>(p, opt, k, acc, wreg, mreg, wrow, mp, piece, r, update);
@@ -458,93 +481,116 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
 
 // ---------------------------------------------------------------- max pooling: who won
 // Backward of the max-pooled lookup: element d of g_u[u] belongs to the position of list u that holds
-// the largest table element d (the first such position).  A group of LPR lanes owns a unique list
-// (lane r: pieces r, r + LPR, ... of the row, 16 bytes each; one piece per lane up to 1 KiB rows), walks
-// its table rows, eight loads in flight per lane, and writes for every position and piece which elements
-// it won: one byte.  The row-gradient sum then takes of g_u[u] what the entry's position won; the rows
-// of g_u stay in L2.  (One masked row per position went to memory and back before: 300 K positions of
-// 512 bytes took 55 us here and 58 + 20 in the sums; now 44 and 72, the latter bound by reading and
-// writing 118 K scattered table rows.)
+// the largest table element d (the first such position).  A wave owns a unique list: the lane groups of LPR lanes
+// (lane r: pieces r, r + LPR, ... of the row, 16 bytes each; one piece per lane up to 1 KiB rows) take a part of every 64
+// positions each, eight rows in flight per lane, and agree at the end (of equal elements the smaller position).  For every
+// position and piece the kernel writes which elements it won, four bits in a byte: a few of the bytes are not zero, so they
+// are put together in LDS and leave as whole words.  The row-gradient sum then takes of g_u[u] what the entry's position won;
+// the rows of g_u stay in L2.  (One masked row per position went to memory and back once; then a lane group walked a list
+// alone, the ids of eight rows fetched by every lane before them, and stored a byte a lane and position: 0.3 M positions of
+// 512 bytes in 12 K lists 43.4 us, now 19.4; a lookup of the same lists takes 21.)
 struct MaxTables {
     const float *w[RECD_F_PER_LAUNCH];
 };
+constexpr int kWonWords = 512;  // of a window of a list's positions in LDS
 
 template <int LPR, int VPL>
-__global__ __launch_bounds__(256) void k_max_winner(const int64_t *__restrict__ u_values,
+__global__ __launch_bounds__(64) void k_max_winner(const int64_t *__restrict__ u_values,
                                                    const int64_t *__restrict__ u_offsets,
                                                    const int64_t *__restrict__ feat_uoff, int f0, int nf,
-                                                   MaxTables tabs, uint8_t *__restrict__ won, int won_lpr, int pieces,
+                                                   MaxTables tabs, uint32_t *__restrict__ won, int won_lpr, int pieces,
                                                    int64_t lists_cap, int64_t m_cap)
 {
-    constexpr int G = 64 / LPR, US = 8 / VPL;  // US positions of a list in flight per lane
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int g = lane / LPR, r = lane % LPR;
-    const int per_block = (256 / 64) * G;
+    constexpr int G = 64 / LPR, US = 8 / VPL;  // US positions in flight per lane
+    __shared__ uint4 s_won[kWonWords / 4];
+    uint32_t *const words = reinterpret_cast<uint32_t *>(s_won);
+    const int lane = threadIdx.x, g = lane / LPR, r = lane % LPR;
     const int64_t u_lo = feat_uoff[f0];
     int64_t u_hi = feat_uoff[f0 + nf];
     u_hi = u_hi < lists_cap ? u_hi : lists_cap;
-    bool piece[VPL];
-    int place[VPL];  // byte of a piece among a position's words: word = piece mod won_lpr, byte = piece / won_lpr
+    const int64_t fo0 = lane < nf ? feat_uoff[f0 + lane] : INT64_MAX, fo1 = 64 + lane < nf ? feat_uoff[f0 + 64 + lane] : INT64_MAX;
+    const int win = kWonWords / won_lpr;  // positions of a window
+    for (int64_t u = u_lo + blockIdx.x; u < u_hi; u += gridDim.x) {
+        const int f = (int)(__popcll(__ballot(fo0 <= u)) + __popcll(__ballot(fo1 <= u))) - 1;
+        const float4 *table = reinterpret_cast<const float4 *>(tabs.w[f]);
+        const int64_t j0 = u_offsets[u], j1 = u_offsets[u + 1];
+        const int len = (int)((j1 < m_cap ? j1 : m_cap) - j0);  // m_cap is below 2^31
+        float best[VPL][4];
+        int arg[VPL][4];
 #pragma unroll
-    for (int w = 0; w < VPL; w++) {
-        piece[w] = w * LPR + r < pieces;
-        place[w] = (w * LPR + r) % won_lpr * 4 + (w * LPR + r) / won_lpr;
-    }
-    for (int64_t u = u_lo + (int64_t)blockIdx.x * per_block + wv * G + g; u < u_hi;
-         u += (int64_t)gridDim.x * per_block) {
-        int lo = 0, hi = nf;  // feature of u inside [f0, f0 + nf)
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (feat_uoff[f0 + mid] <= u)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        const float4 *table = reinterpret_cast<const float4 *>(tabs.w[lo]);
-        const int64_t j0 = u_offsets[u];
-        int64_t j1 = u_offsets[u + 1];
-        j1 = j1 < m_cap ? j1 : m_cap;
-        float4 best[VPL];
-        int4 arg[VPL];
+        for (int w = 0; w < VPL; w++)
 #pragma unroll
-        for (int w = 0; w < VPL; w++) {
-            best[w] = make_float4(0.f, 0.f, 0.f, 0.f);
-            arg[w] = make_int4(0, 0, 0, 0);
-        }
-        // positions in ascending order, US rows in flight
-        for (int64_t jb = j0; jb < j1; jb += US) {
-            float4 v[US][VPL];
-#pragma unroll
-            for (int k = 0; k < US; k++) {
-                const int64_t j = jb + k < j1 ? jb + k : j1 - 1;
-                const int64_t id = u_values[j];
-#pragma unroll
-                for (int w = 0; w < VPL; w++)
-                    if (piece[w])
-                        v[k][w] = table[id * pieces + w * LPR + r];
+            for (int e = 0; e < 4; e++) {
+                best[w][e] = -INFINITY;
+                arg[w][e] = INT32_MAX;
             }
+        for (int c0 = 0; c0 < len; c0 += 64) {
+            const int nc = len - c0 < 64 ? len - c0 : 64, per = (nc + G - 1) / G;
+            const uint32_t id = lane < nc ? (uint32_t)u_values[j0 + c0 + lane] : 0u;
+            for (int k0 = 0; k0 < per; k0 += US) {
+                float4 v[US][VPL];
 #pragma unroll
-            for (int k = 0; k < US; k++)
-                if (jb + k < j1) {
-                    const int t = (int)(jb + k - j0);
+                for (int k = 0; k < US; k++) {
+                    const int t = g * per + k0 + k;
+                    const uint32_t row = __shfl(id, t & 63);
+                    if (k0 + k < per && t < nc)
 #pragma unroll
-                    for (int w = 0; w < VPL; w++)
-                        if (piece[w]) {
-                            const float4 x = v[k][w];
-                            if (t == 0 || x.x > best[w].x) { best[w].x = x.x; arg[w].x = t; }
-                            if (t == 0 || x.y > best[w].y) { best[w].y = x.y; arg[w].y = t; }
-                            if (t == 0 || x.z > best[w].z) { best[w].z = x.z; arg[w].z = t; }
-                            if (t == 0 || x.w > best[w].w) { best[w].w = x.w; arg[w].w = t; }
+                        for (int w = 0; w < VPL; w++)
+                            if (w * LPR + r < pieces)
+                                v[k][w] = table[(int64_t)row * pieces + w * LPR + r];
+                }
+#pragma unroll
+                for (int k = 0; k < US; k++) {
+                    const int t = g * per + k0 + k, pos = c0 + t;
+                    if (k0 + k < per && t < nc)
+#pragma unroll
+                        for (int w = 0; w < VPL; w++) {
+                            const float x[4] = {v[k][w].x, v[k][w].y, v[k][w].z, v[k][w].w};
+#pragma unroll
+                            for (int e = 0; e < 4; e++)
+                                if (pos == 0 || x[e] > best[w][e]) {  // a NaN wins at the first position only, and stays
+                                    best[w][e] = x[e];
+                                    arg[w][e] = pos;
+                                }
                         }
                 }
+            }
         }
-        for (int64_t j = j0; j < j1; j++) {
-            const int t = (int)(j - j0);
+#pragma unroll
+        for (int s = LPR; s < 64; s <<= 1)
 #pragma unroll
             for (int w = 0; w < VPL; w++)
-                if (piece[w])
-                    won[j * 4 * won_lpr + place[w]] = (uint8_t)((arg[w].x == t ? 1 : 0) | (arg[w].y == t ? 2 : 0) |
-                                                              (arg[w].z == t ? 4 : 0) | (arg[w].w == t ? 8 : 0));
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const float y = __shfl_xor(best[w][e], s);
+                    const int a = __shfl_xor(arg[w][e], s);
+                    const bool low = (lane & s) == 0;  // only a lower group's can be NaN
+                    const float lx = low ? best[w][e] : y, hx = low ? y : best[w][e];
+                    const int la = low ? arg[w][e] : a, ha = low ? a : arg[w][e];
+                    const bool high = hx > lx || (hx == lx && ha < la);
+                    best[w][e] = high ? hx : lx;
+                    arg[w][e] = high ? ha : la;
+                }
+        for (int w0 = 0; w0 < len; w0 += win) {
+            const int n = len - w0 < win ? len - w0 : win, vecs = n * won_lpr / 4;
+            for (int i = lane; i < vecs; i += 64)
+                s_won[i] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < VPL; w++) {
+                const int piece = w * LPR + r;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const int at = arg[w][e] - w0;
+                    if (e % G == g && piece < pieces && at >= 0 && at < n)
+                        atomicOr(&words[at * won_lpr + piece % won_lpr], 1u << (8 * (piece / won_lpr) + e));
+                }
+            }
+            __syncthreads();
+            uint4 *dst = reinterpret_cast<uint4 *>(won + (j0 + w0) * won_lpr);
+            for (int i = lane; i < vecs; i += 64)
+                dst[i] = s_won[i];
+            __syncthreads();
         }
     }
 }
@@ -1037,20 +1083,16 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
         const int P = D / 4;  // 16-byte pieces of a row: up to 64 one per lane, else 128 or 256
         const int lpr = P <= 4 ? 4 : (P <= 8 ? 8 : (P <= 16 ? 16 : (P <= 32 ? 32 : 64)));
         const int vpl = P <= 64 ? 1 : (P == 128 ? 2 : 4);
-        const int per_block = 4 * (64 / lpr);
         for (int f0 = 0; f0 < F; f0 += RECD_F_PER_LAUNCH) {
             MaxTables mt;
             const int nf = F - f0 < RECD_F_PER_LAUNCH ? F - f0 : RECD_F_PER_LAUNCH;
             for (int f = 0; f < nf; f++)
                 mt.w[f] = static_cast<const float *>(max_tables[f0 + f]);
-            int64_t nblk = (U_cap + per_block - 1) / per_block;
-            if (nblk > (int64_t)ctx->num_cu * 64)
-                nblk = (int64_t)ctx->num_cu * 64;
-            const dim3 grid((unsigned)(nblk < 1 ? 1 : nblk)), block(256);
+            const int64_t nblk = U_cap < (int64_t)ctx->num_cu * 256 ? U_cap : (int64_t)ctx->num_cu * 256;
+            const dim3 grid((unsigned)(nblk < 1 ? 1 : nblk)), block(64);
 #define RECD_MR(L, V)                                                                                    \
     hipLaunchKernelGGL((k_max_winner<L, V>), grid, block, 0, st, u_values, u_offsets, feat_uoff, f0, nf, mt,  \
-                       reinterpret_cast<uint8_t *>(w.won), row_lanes(D), P, U_cap,                            \
-                       M_cap)
+                       w.won, row_lanes(D), P, U_cap, M_cap)
             if (vpl == 4) RECD_MR(64, 4);
             else if (vpl == 2) RECD_MR(64, 2);
             else if (lpr == 4) RECD_MR(4, 1);
