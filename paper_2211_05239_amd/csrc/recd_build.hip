@@ -97,11 +97,11 @@ template <bool WT> struct IdPair {
             d |= (w.x ^ o.w.x) | (w.y ^ o.w.y);
         return d;
     }
-    template <typename T> __device__ __forceinline__ uint64_t hash(T t, T n) const  // of a list of n
+    template <typename T> __device__ __forceinline__ uint64_t hash(T t, T n, uint32_t salt = 0) const  // of a list of n
     {
         const bool both = t + 1 < n;
         const uint32_t x = hash_word(v.x, w.x), y = hash_word(v.y, w.y);
-        return hash_pair(both ? x : y, both ? y : 0u, (uint32_t)t);
+        return hash_pair(both ? x : y, both ? y : 0u, (uint32_t)t + salt);
     }
 };
 
@@ -1167,49 +1167,127 @@ __global__ void k_empty_ikjt(int F, int64_t *u_offsets, int64_t *feat_uoff, int6
 // of the list: a row equal to its predecessor in every feature is a follower; run heads are hashed
 // over all their lists (feature-salted) and meet in a per-group table; a tag match is followed by
 // an exact comparison of the whole tuple.
+// As in k_hash_insert a tuple is compared first and hashed only if it differs; the lists of kTogether features are in flight
+// together, kGroupFly strides of each.  us, every tuple hashed feature by feature / this: 65 K rows of groups of four
+// features, sessions of 8 23.3 / 20.5, 131 K of two 23.4 / 19.5, 131 K of eight, lists of up to 256 ids, 164 / 107; sessions
+// of 4, groups of five 17.0 / 17.8.  (Four features together 24.5, 30.9 and 112; 16 lanes a tuple 22.1, 23.3 and 98.)
+constexpr int kTogether = 2, kGroupFly = 2;
+
 template <int SG>
-__global__ __launch_bounds__(256) void k_group_hash_insert(const int64_t *__restrict__ values,
+__global__ __launch_bounds__(kHashBlock) void k_group_hash_insert(const int64_t *__restrict__ values,
                                                            const int64_t *__restrict__ offsets,
-                                                           int64_t B, int64_t n_items,
+                                                           RecdDiv rows, uint32_t n_items,
                                                            const int32_t *__restrict__ group_off,
                                                            uint64_t *table, uint32_t cap_mask,
                                                            int32_t *__restrict__ slot_of, int weak_hash)
 {
-    const int s = threadIdx.x % SG;
-    const int64_t item = (int64_t)blockIdx.x * (256 / SG) + threadIdx.x / SG;
+    constexpr int kStride = 2 * SG;
+    const int lane = threadIdx.x, s = lane % SG;
+    // an XCD takes a contiguous eighth of the items (see k_hash_insert); the grid is a multiple of 8 blocks
+    const uint32_t blk = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const uint32_t item = blk * (kHashBlock / SG) + lane / SG;
     if (item >= n_items)
         return;  // whole lane group leaves together
-    const int64_t g = item / B, b = item - g * B;
+    const uint32_t g = rows.of(item), b = item - g * rows.by, B = rows.by;
     const int f0 = group_off[g], f1 = group_off[g + 1];
-    int follows = b != 0;
-    uint64_t h = 0;
-    int64_t total_len = 0;
-    for (int f = f0; f < f1; f++) {
-        const int64_t l = (int64_t)f * B + b;
-        const int64_t o1 = offsets[l], len = offsets[l + 1] - o1;
-        const int64_t o0 = b != 0 ? offsets[l - 1] : o1;
-        follows &= (o1 - o0) == len;  // same for all lanes
-        const uint64_t salt = (uint64_t)(f - f0 + 1) * 0xc2b2ae3d27d4eb4full;
-        for (int64_t t = s; t < len; t += SG) {
-            const int64_t x = values[o1 + t];
-            if (follows)
-                follows &= values[o0 + t] == x;
-            h += mix64((uint64_t)x + (uint64_t)(t + 1) * 0x9e3779b97f4a7c15ull + salt);
-        }
-        if (s == 0)
-            h += mix64((uint64_t)len * 0xd6e8feb86659fd93ull + salt + 1ull);
-        total_len += len;
-    }
+    // the lists of features c, c + 1, ...: where they start, their lengths, and whether their predecessors are as long
+    int64_t start[kTogether], len[kTogether];
+    auto bounds = [&](int c, bool &alike) {
+        id2 ends[kTogether];
+        int64_t before[kTogether];
 #pragma unroll
-    for (int m = SG / 2; m > 0; m >>= 1) {
-        h += __shfl_xor((unsigned long long)h, m, SG);
-        follows &= __shfl_xor(follows, m, SG);
+        for (int k = 0; k < kTogether; k++) {
+            const int64_t l = (int64_t)(c + k < f1 ? c + k : f1 - 1) * B + b;
+            ends[k] = *reinterpret_cast<const id2 *>(offsets + l);
+            before[k] = offsets[b != 0 ? l - 1 : l];
+        }
+#pragma unroll
+        for (int k = 0; k < kTogether; k++) {
+            start[k] = ends[k].x;
+            len[k] = ends[k].y - ends[k].x;
+            alike &= ends[k].x - before[k] == len[k] && len[k] < INT32_MAX;
+            len[k] = c + k < f1 && len[k] > 0 ? len[k] : 0;
+        }
+    };
+    uint32_t differ = b != 0 ? 0 : 1;
+    for (int c = f0; c < f1 && differ == 0; c += kTogether) {
+        bool alike = true;
+        bounds(c, alike);
+        if (!alike) {  // the same in all lanes
+            differ = 1;
+            break;
+        }
+        uint32_t most = 0;
+#pragma unroll
+        for (int k = 0; k < kTogether; k++)
+            most = (uint32_t)len[k] > most ? (uint32_t)len[k] : most;
+        for (uint32_t t0 = 2 * s; t0 < most && differ == 0; t0 += kGroupFly * kStride) {
+            IdPair<false> x[kTogether][kGroupFly], y[kTogether][kGroupFly];
+#pragma unroll
+            for (int k = 0; k < kTogether; k++)
+#pragma unroll
+                for (int u = 0; u < kGroupFly; u++) {
+                    const uint32_t t = t0 + u * kStride, n = (uint32_t)len[k];
+                    const int64_t *ids = values + start[k];
+                    if (t < n && n > 1) {
+                        x[k][u].load(ids, nullptr, t, n);
+                        y[k][u].load(ids - n, nullptr, t, n);
+                    } else if (u == 0 && t < n) {
+                        x[k][u].load_only(ids, nullptr);
+                        y[k][u].load_only(ids - 1, nullptr);
+                    }
+                }
+#pragma unroll
+            for (int k = 0; k < kTogether; k++)
+#pragma unroll
+                for (int u = 0; u < kGroupFly; u++)
+                    differ |= x[k][u].differ(y[k][u]) != 0;
+        }
     }
-    if (follows) {
+    constexpr uint64_t group = SG == 64 ? ~0ull : (1ull << SG) - 1;
+    if (((__ballot(differ != 0) >> (lane - s)) & group) == 0) {
         if (s == 0)
             slot_of[item] = -1;
         return;
     }
+    uint64_t h = 0;
+    int64_t total_len = 0;
+    for (int c = f0; c < f1; c += kTogether) {
+        bool any = true;
+        bounds(c, any);
+        int64_t most = 0;
+#pragma unroll
+        for (int k = 0; k < kTogether; k++) {
+            most = len[k] > most ? len[k] : most;
+            total_len += len[k];
+            if (s == k && c + k < f1)
+                h += mix64((uint64_t)len[k] * 0xd6e8feb86659fd93ull + (uint64_t)(c + k - f0 + 1) * 0xc2b2ae3d27d4eb4full);
+        }
+        for (int64_t t0 = 2 * s; t0 < most; t0 += kGroupFly * kStride) {
+            IdPair<false> x[kTogether][kGroupFly];
+#pragma unroll
+            for (int k = 0; k < kTogether; k++)
+#pragma unroll
+                for (int u = 0; u < kGroupFly; u++) {
+                    const int64_t t = t0 + u * kStride;
+                    if (t < len[k] && len[k] > 1)
+                        x[k][u].load(values + start[k], nullptr, t, len[k]);
+                    else if (u == 0 && t < len[k])
+                        x[k][u].load_only(values + start[k], nullptr);
+                }
+#pragma unroll
+            for (int k = 0; k < kTogether; k++)
+#pragma unroll
+                for (int u = 0; u < kGroupFly; u++) {
+                    const int64_t t = t0 + u * kStride;
+                    if (t < len[k])
+                        h += x[k][u].hash(t, len[k], (uint32_t)(c + k - f0) << 20);
+                }
+        }
+    }
+#pragma unroll
+    for (int m = SG / 2; m > 0; m >>= 1)
+        h += __shfl_xor((unsigned long long)h, m, SG);
     uint64_t hh = mix64(h);
     if (weak_hash)
         hh = (uint64_t)total_len;  // test hook: only the exact comparison separates tuples
@@ -1230,10 +1308,10 @@ __global__ __launch_bounds__(256) void k_group_hash_insert(const int64_t *__rest
             int eq = 1;
             for (int f = f0; f < f1 && eq; f++) {  // eq is the same in all lanes at the loop test
                 const int64_t l = (int64_t)f * B + b, ol = (int64_t)f * B + ob;
-                const int64_t o1 = offsets[l], len = offsets[l + 1] - o1, oo = offsets[ol];
-                eq = (offsets[ol + 1] - oo) == len;
+                const int64_t o1 = offsets[l], n = offsets[l + 1] - o1, oo = offsets[ol];
+                eq = (offsets[ol + 1] - oo) == n;
                 if (eq)
-                    for (int64_t t = s; t < len; t += SG)
+                    for (int64_t t = s; t < n; t += SG)
                         if (values[o1 + t] != values[oo + t]) {
                             eq = 0;
                             break;
@@ -1698,6 +1776,35 @@ void emit_lists(const recd_ctx *ctx, hipStream_t st, int64_t B, uint32_t rows, i
 } // namespace
 
 
+// The context's own tables, which are empty between builds, in the place of the workspace's: of w.cap slots each, and behind
+// them the look-back words of `rows` rows and `more` words.  slots: all of these, for the build's last kernel to clear.
+static recd_status own_tables(recd_ctx *ctx, hipStream_t st, int tables, int64_t rows, SlotWs &w, size_t &slots, size_t more = 0)
+{
+    slots = (size_t)tables * w.cap + look_words(rows) + more;
+    if (slots > ctx->build_table_slots) {
+        RECD_HIP(ctx, hipStreamSynchronize(st));
+        if (ctx->build_table)
+            RECD_HIP(ctx, hipFree(ctx->build_table));
+        ctx->build_table = nullptr;
+        ctx->build_table_slots = 0;
+        const size_t want = slots + slots / 4;
+        void *tp = nullptr;
+        if (hipMalloc(&tp, want * sizeof(uint64_t)) != hipSuccess) {
+            (void)hipGetLastError();
+            return recd_fail(ctx, RECD_ENOMEM, "hash tables of %zu bytes: allocation failed", want * sizeof(uint64_t));
+        }
+        ctx->build_table = static_cast<uint64_t *>(tp);
+        ctx->build_table_slots = want;
+        ctx->table_clean = false;
+    }
+    if (!ctx->table_clean)
+        hipLaunchKernelGGL(k_fill_u64, dim3(4096), dim3(256), 0, st, ctx->build_table, (int64_t)ctx->build_table_slots, kEmpty);
+    w.table = ctx->build_table;
+    w.look = w.table + (size_t)tables * w.cap;
+    w.look_lists = w.look + look_words(rows);
+    return RECD_OK;
+}
+
 // weights / u_weights: null for a plain KJT
 static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const int64_t *values,
                                const uint32_t *weights, const int64_t *offsets, int64_t *u_values,
@@ -1780,30 +1887,8 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
             hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, st, reinterpret_cast<uint64_t *>(run_index),
                                (int64_t)6, 0ull);
     } else {
-        // the context's own tables (kept empty between builds) instead of the workspace's
-        const size_t slots = (size_t)F * w.cap + look_words(n_lists);
-        if (slots > ctx->build_table_slots) {
-            RECD_HIP(ctx, hipStreamSynchronize(st));
-            if (ctx->build_table)
-                RECD_HIP(ctx, hipFree(ctx->build_table));
-            ctx->build_table = nullptr;
-            ctx->build_table_slots = 0;
-            const size_t want = slots + slots / 4;
-            void *tp = nullptr;
-            if (hipMalloc(&tp, want * sizeof(uint64_t)) != hipSuccess) {
-                (void)hipGetLastError();
-                return recd_fail(ctx, RECD_ENOMEM, "hash tables of %zu bytes: allocation failed", want * sizeof(uint64_t));
-            }
-            ctx->build_table = static_cast<uint64_t *>(tp);
-            ctx->build_table_slots = want;
-            ctx->table_clean = false;
-        }
-        if (!ctx->table_clean) {
-            const int64_t all = (int64_t)ctx->build_table_slots;
-            hipLaunchKernelGGL(k_fill_u64, dim3(4096), dim3(256), 0, st, ctx->build_table, all, kEmpty);
-        }
-        w.table = ctx->build_table;
-        w.look = w.table + (size_t)F * w.cap;
+        size_t slots = 0;
+        RECD_TRY(own_tables(ctx, st, F, n_lists, w, slots));
         ctx->table_clean = false;  // until this build's last kernel is enqueued
         insert_lists(ctx, st, w, F, B, values, offsets, weights, true);
         // without a host destination the counts go to the mailbox from the kernel that computes
@@ -2018,7 +2103,7 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
     ctx->plan.valid = false;  // this call reuses the workspace a backward plan would live in
     RECD_TRY(recd_reserve(ctx, recd_build_workspace(F, B)));
     WsCarver c(ctx->ws);
-    const SlotWs w = carve_slots(c, G, B, n_items, n_lists);  // slots of the group rows
+    SlotWs w = carve_slots(c, G, B, n_items, n_lists);         // slots of the group rows
     int64_t *counts = c.take<int64_t>(4);                      // stored lists, stored ids
     int32_t *src_of = c.take<int32_t>(n_lists);
     int64_t *u_tmp = c.take<int64_t>(n_items + 1);
@@ -2030,11 +2115,21 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
         const int32_t *dev_group_off = nullptr, *dev_feat_group = nullptr;
         RECD_TRY(recd_group_map(ctx, F, G, group_off, &dev_group_off, &dev_feat_group));
         constexpr int SG = 8;
-        clear_table(st, w, G, B, look_words(n_lists));
-        const int64_t hblocks = (n_items + (256 / SG) - 1) / (256 / SG);
-        hipLaunchKernelGGL((k_group_hash_insert<SG>), dim3((unsigned)hblocks), dim3(256), 0, st, values,
-                           offsets, B, n_items, dev_group_off, w.table, (uint32_t)(w.cap - 1), w.slot_of,
-                           ctx->weak_hash);
+        size_t slots = (size_t)G * w.cap + look_words(n_items) + look_words(n_lists);
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (slots > ctx->build_table_slots)
+            RECD_HIP(ctx, hipStreamIsCapturing(st, &capture));
+        const bool own = capture == hipStreamCaptureStatusNone;  // a capture cannot wait for the context's tables to grow
+        if (own) {
+            RECD_TRY(own_tables(ctx, st, G, n_items, w, slots, look_words(n_lists)));
+            ctx->table_clean = false;  // until this build's last kernel is enqueued
+        } else {
+            clear_table(st, w, G, B, look_words(n_lists));
+        }
+        const int64_t hblocks = (n_items + kHashBlock / SG - 1) / (kHashBlock / SG);
+        hipLaunchKernelGGL((k_group_hash_insert<SG>), dim3((unsigned)((hblocks + 7) / 8 * 8)), dim3(kHashBlock), 0, st, values,
+                           offsets, recd_divide_by((uint32_t)B), (uint32_t)n_items, dev_group_off, w.table,
+                           (uint32_t)(w.cap - 1), w.slot_of, ctx->weak_hash);
         // numbering of the slots per group: the list-level kernels with the groups in the role of
         // features and rows without ids
         number_slots(st, w, G, B, nullptr, u_tmp, group_uoff);
@@ -2053,7 +2148,11 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
             compact(k_group_compact<COMPACT_NUMBER>);
         }
         // the groups' inverse from their rows' numbers, and the stored lists' ids
-        emit_lists(ctx, st, B, (uint32_t)n_items, n_lists, values, offsets, w, src_of, u_offsets, counts, u_values, inverse_g);
+        emit_lists(ctx, st, B, (uint32_t)n_items, n_lists, values, offsets, w, src_of, u_offsets, counts, u_values, inverse_g, nullptr,
+                   nullptr, own ? ctx->build_table : nullptr, own ? (int64_t)slots : 0);
+        RECD_HIP(ctx, hipGetLastError());
+        if (own)
+            ctx->table_clean = true;
     }
     RECD_HIP(ctx, hipGetLastError());
     if (host_counts) {

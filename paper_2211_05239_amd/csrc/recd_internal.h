@@ -62,7 +62,7 @@ struct recd_ctx {
         int64_t *touched_rows = nullptr, *feat_roff = nullptr;
         const char *ws = nullptr;   // the workspace the plan lives in must still be the context's
     } plan;
-    // Hash tables of the plain / weighted builder: memory of their own that is all "empty" whenever
+    // Hash tables of the plain, weighted and grouped builders: memory of their own that is all "empty" whenever
     // no build is running on the stream, because the builder's last kernel clears what the build
     // used (so no clearing kernel stands at the head of the next build).  table_clean is false
     // while that cannot be relied on (first use, or a build that failed half way).

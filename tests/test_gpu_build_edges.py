@@ -107,3 +107,58 @@ def test_numbering_across_waves_and_blocks(ctx, F, B):
     values = flat[np.repeat(start[which] - offsets[:-1], lens) + np.arange(offsets[-1])].astype(np.int64)
     batch = synth.Batch(F, B, values, offsets, np.zeros(B, np.int32), 1.0)
     _check(gu.gpu_build(ctx, batch)[2], batch)
+
+
+@pytest.mark.parametrize("seed", range(3))
+def test_grouped_tuples_that_differ_in_one_place(recd, seed):
+    """Groups of one to five features; neighbouring tuples that agree, differ in one id of one feature, or in one length; a
+    plain build between the grouped ones, which use the same tables."""
+    rng = np.random.default_rng(seed)
+    lengths = [0, 1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 64, 65, 97]
+    sizes = [1, 2, 3, 4, 5, 4]
+    F, B, G = sum(sizes), 601, len(sizes)
+    group_off = np.concatenate([[0], np.cumsum(sizes)]).tolist()
+    rows = []
+    for b in range(B):
+        if b and rng.random() < 0.7:
+            row = [list(x) for x in (rows[-1] if rng.random() < 0.8 else rows[rng.integers(b)])]
+            if rng.random() < 0.4:
+                x = row[rng.integers(F)]
+                if rng.random() < 0.3:
+                    x.append(1)
+                elif x:
+                    x[rng.choice([0, len(x) - 1, rng.integers(len(x))])] += 1
+        else:
+            row = [rng.integers(0, 50, rng.choice(lengths)).tolist() for _ in range(F)]
+        rows.append(row)
+    batch = synth.batch_from_lists([[rows[b][f] for b in range(B)] for f in range(F)])
+    c = recd.Context(0)
+    try:
+        for _ in range(2):
+            values, offsets = gu.to_dev(batch.values), gu.to_dev(batch.offsets)
+            ik = gu.DeviceIKJT(F, B, batch.N)
+            inverse_g = torch.full((G * B,), -7, dtype=torch.int32, device="cuda")
+            group_uoff = torch.full((G + 1,), -7, dtype=torch.int64, device="cuda")
+            c.build_ikjt_grouped(F, B, group_off, values, offsets, ik.u_values, ik.u_offsets, inverse_g, group_uoff, ik.feat_uoff)
+            at = 0
+            for g in range(G):
+                seen, first = {}, []
+                inv = []
+                for b in range(B):
+                    key = tuple(tuple(rows[b][f]) for f in range(group_off[g], group_off[g + 1]))
+                    if key not in seen:
+                        seen[key] = len(first)
+                        first.append(b)
+                    inv.append(seen[key])
+                assert inverse_g[g * B:(g + 1) * B].tolist() == inv
+                assert group_uoff[g:g + 2].tolist() == [at, at + len(first)]
+                at += len(first)
+                for f in range(group_off[g], group_off[g + 1]):
+                    u0, u1 = ik.feat_uoff[f:f + 2].tolist()
+                    o = ik.u_offsets[u0:u1 + 1].tolist()
+                    ids = ik.u_values[o[0]:o[-1]].tolist()
+                    assert [ids[x - o[0]:y - o[0]] for x, y in zip(o, o[1:])] == [rows[b][f] for b in first]
+            c.set_option(recd._OPT_INTERNAL_SMALL_PATH, 0)
+            _check(gu.gpu_build(c, batch)[2], batch)
+    finally:
+        c.close()
