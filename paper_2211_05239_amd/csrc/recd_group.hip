@@ -24,6 +24,7 @@
 // tickets in that order (eight queues, feature f in queue f mod 8, which the blocks of one XCD serve
 // first), so whoever is waited for has started and itself waits only further back: every wait ends.
 #include "recd_internal.h"
+#include "recd_scan.h"
 
 namespace {
 
@@ -56,36 +57,32 @@ __device__ __forceinline__ void st_agent(uint64_t *p, uint64_t v) { __hip_atomic
 // Waits until the memory system has acknowledged this wave's stores.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Inclusive sums over a wave.
-template <typename T> __device__ __forceinline__ T wave_incl(T v, int lane)
+// Inclusive sums over a wave; of 64 bits those of the halves, whose totals fit them.
+__device__ __forceinline__ uint32_t wave_incl(uint32_t v, int lane) { return wave_scan_add(v, lane); }
+__device__ __forceinline__ uint64_t wave_incl(uint64_t v, int lane)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const T x = __shfl_up(v, d);
-        if (lane >= d)
-            v += x;
-    }
-    return v;
+    return ((uint64_t)wave_scan_add((uint32_t)(v >> 32), lane) << 32) | wave_scan_add((uint32_t)v, lane);
 }
+__device__ __forceinline__ uint32_t row_incl(uint32_t v) { return row_scan_add(v); }
+__device__ __forceinline__ uint64_t row_incl(uint64_t v) { return ((uint64_t)row_scan_add((uint32_t)(v >> 32)) << 32) | row_scan_add((uint32_t)v); }
+__device__ __forceinline__ uint32_t of_lane(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ __forceinline__ uint64_t of_lane(uint64_t v, int lane) { return ((uint64_t)of_lane((uint32_t)(v >> 32), lane) << 32) | of_lane((uint32_t)v, lane); }
 
-// Exclusive sum over the block's NW waves; every thread gets the total.
+// Exclusive sum over the block's NW waves; every thread gets the total.  Every wave scans the waves' sums itself, in a row of
+// 16 lanes.  (Shuffles through LDS and a loop over the waves before: blocks of 16 waves on one CU are bound by what they issue.)
 template <typename T, int NW> __device__ __forceinline__ T block_excl(T v, T &total)
 {
+    static_assert(NW <= 16, "the waves' sums fit a row of lanes");
     __shared__ T s_w[NW];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const T inc = wave_incl(v, lane);
     __syncthreads();
     if (lane == 63)
         s_w[w] = inc;
     __syncthreads();
-    T off = 0, all = 0;
-#pragma unroll
-    for (int i = 0; i < NW; i++) {
-        off += i < w ? s_w[i] : 0;
-        all += s_w[i];
-    }
-    total = all;
-    return off + inc - v;
+    const T sums = row_incl((lane & 15) < NW ? s_w[lane & 15] : (T)0);
+    total = of_lane(sums, NW - 1);
+    return (w > 0 ? of_lane(sums, w - 1) : (T)0) + inc - v;
 }
 
 struct SideParams {
@@ -1059,57 +1056,95 @@ __global__ __launch_bounds__(kTileThreads) void k_group_segments(const GroupPara
 }
 
 // ---- small batches: both sides in one launch -------------------------------------------------------
-// Up to 8192 ids and 8192 rows per feature: block 0 groups all of side B (key = feature and row), block
-// 1 + f the rows of feature f, each by a radix sort in LDS, and writes the segments straight from there.
-// No block looks at another.  The four launches above cost such a batch their launches and a chain
-// of dependent round trips each (2048 rows, 5 K ids: 38 us of kernels); here it is one chain.
+// Up to 8192 ids and 8192 rows per feature: the first blocks group `per` neighbouring features' ids each (key = feature and
+// row), the others the rows of one feature, each by a radix sort in LDS, and write the segments straight from there.
+// The blocks of the ids take their features by tickets and meet once, when they learn how many rows and chunks the features
+// before theirs hold: a block waits for blocks that started before it only.  The last that has read the others' words
+// clears them for the next launch.
+// The four launches above cost such a batch their launches and a chain of dependent round trips each (2048 rows, 5 K ids:
+// 38 us of kernels); here it is one chain.  (One block for all ids, and scans through
+// LDS, 24 us; a block for each of the four features 16.0, with scans by lane shifts 13.9; one feature of 2.6 K ids 13.5 and 12.1.
+// Blocks of 16 waves on a CU of their own are bound by what they issue.)
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kSmallRounds = 8;
 constexpr int kSmallCap = kSmallThreads * kSmallRounds;
+static_assert(RECD_MAX_FEATURES + 2 <= RECD_GROUP_ARRIVE, "a word a block, the ticket and the count of readers");
 
-__global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams g, int row_bits, int passes_b, int dbits_b)
+__global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams g, int b_blocks, int per, int row_bits,
+                                                               int passes_b, int dbits_b)
 {
     __shared__ uint32_t s_key[kSmallCap], s_pay[kSmallCap];
     __shared__ uint16_t s_run[kSmallWaves][kMaxRadix];
     __shared__ uint16_t s_loc[kMaxRadix];
     __shared__ uint64_t s_wave[kSmallWaves];
-    __shared__ uint32_t s_fu[RECD_MAX_FEATURES + 1], s_chunks;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const bool side_a = blockIdx.x > 0;
-    const uint32_t f_a = blockIdx.x - 1;
-    const uint32_t row_mask = (1u << row_bits) - 1;  // with the feature's bits, at least one, it fits 32
-    uint32_t n;
+    __shared__ uint32_t s_fu[RECD_MAX_FEATURES + 1], s_chunks, s_blk, s_before[2];
+    static_assert(kSmallWaves == 16, "a row of lanes scans the waves' sums");
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool side_a = (int)blockIdx.x >= b_blocks;
+    const uint32_t f_a = blockIdx.x - b_blocks;
+    const uint32_t row_mask = (uint32_t)((1ull << row_bits) - 1);  // with the features' bits it fits 32
+    uint32_t *const words = g.b.arrive, *const ticket = words + RECD_MAX_FEATURES, *const readers = ticket + 1;
+    uint32_t n, blk = 0, p0 = 0;  // p0: the first position
+    uint32_t key[kSmallRounds], pay[kSmallRounds], rank[kSmallRounds];
+    int f0 = 0, f1 = 0;           // the block's features
     if (side_a) {
         n = (uint32_t)g.B;
     } else {
-        for (int i = tid; i <= g.F; i += kSmallThreads)
-            s_fu[i] = (uint32_t)g.feat_uoff[i];
-        const int64_t M = g.u_offsets[g.feat_uoff[g.F]];
-        n = (uint32_t)(M < g.M_cap ? M : g.M_cap);
-        if (tid == 0) {
-            g.too_small_b[0] = M > g.M_cap ? 1 : 0;
+        if (tid == 0)
             s_chunks = 0;
+        if (b_blocks > 1) {
+            if (tid == 0)
+                s_blk = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            blk = s_blk;
         }
-        __syncthreads();
+        f0 = (int)blk * per;
+        f1 = f0 + per < g.F ? f0 + per : g.F;
+        const uint32_t u0 = (uint32_t)g.feat_uoff[f0], u1 = (uint32_t)g.feat_uoff[f1];
+        if (per > 1) {
+            for (int i = tid; i <= f1 - f0; i += kSmallThreads)
+                s_fu[i] = (uint32_t)g.feat_uoff[f0 + i];
+            __syncthreads();
+        }
+        // one round trip: the block's positions and its first lists'
+        int64_t a = 0, e = 0;
+        if (u0 + tid < u1) {
+            a = g.u_offsets[u0 + tid];
+            e = g.u_offsets[u0 + tid + 1];
+        }
+        const int64_t P = g.u_offsets[u0], M = g.u_offsets[u1];
+        p0 = (uint32_t)(P < g.M_cap ? P : g.M_cap);
+        n = (uint32_t)(M < g.M_cap ? M : g.M_cap) - p0;
+        if (f1 == g.F && tid == 0)
+            g.too_small_b[0] = M > g.M_cap ? 1 : 0;
+        // the ids are on their way meanwhile
+        const uint32_t rounds = (n + kSmallThreads - 1) / kSmallThreads, i0 = w * (rounds * 64) + lane;
+#pragma unroll
+        for (int u = 0; u < kSmallRounds; u++) {
+            if (u >= (int)rounds)  // the same in every thread, here and below
+                break;
+            key[u] = i0 + u * 64 < n ? (uint32_t)g.u_values[p0 + i0 + u * 64] : 0u;
+        }
         // every list fills in its number and its feature at its positions (an empty list has none): a lane up to
         // 64 of them, the whole wave what lies beyond, list by list (a list of 7000 ids by one lane: backward 230 us,
         // now 44; with 16 instead of 64 the lists of 20 ids in a batch of 5 K took 1 us more)
-        const uint32_t U = s_fu[g.F];
-        for (uint32_t u0 = 0; u0 < U; u0 += kSmallThreads) {
-            const uint32_t u = u0 + tid;
+        for (uint32_t v0 = u0; v0 < u1; v0 += kSmallThreads) {
+            const uint32_t u = v0 + tid;
             uint32_t at = 0, end = 0, name = 0, fkey = 0;
-            if (u < U) {
-                const int64_t a = g.u_offsets[u], e = g.u_offsets[u + 1];
+            if (u < u1) {
+                if (v0 > u0) {
+                    a = g.u_offsets[u];
+                    e = g.u_offsets[u + 1];
+                }
                 int f = 0;  // the last feature with s_fu[f] <= u
-#pragma unroll
-                for (int st = RECD_MAX_FEATURES / 2; st >= 1; st >>= 1)
-                    if (f + st < g.F && s_fu[f + st] <= u)
+                for (int st = RECD_MAX_FEATURES / 2; per > 1 && st >= 1; st >>= 1)
+                    if (f + st < f1 - f0 && s_fu[f + st] <= u)
                         f += st;
-                at = a < (int64_t)n ? (uint32_t)a : n;
-                end = e < (int64_t)n ? (uint32_t)e : n;
+                at = a - p0 < (int64_t)n ? (uint32_t)(a - p0) : n;
+                end = e - p0 < (int64_t)n ? (uint32_t)(e - p0) : n;
                 name = (int64_t)u < g.lists_cap ? u : (uint32_t)(g.lists_cap - 1);
-                fkey = (uint32_t)f << row_bits;
+                fkey = per > 1 ? (uint32_t)f << row_bits : 0;
             }
             const uint32_t own = end > at + 64 ? at + 64 : end;
             for (uint32_t j = at; j < own; j++) {
@@ -1130,21 +1165,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
     // a wave owns `rounds` * 64 consecutive entries
     const int rounds = (int)((n + kSmallThreads - 1) / kSmallThreads);
     const uint32_t wbase = w * (rounds * 64) + lane;
-    uint32_t key[kSmallRounds], pay[kSmallRounds], rank[kSmallRounds];
 #pragma unroll
     for (int u = 0; u < kSmallRounds; u++) {
+        if (u >= rounds)
+            break;
         const uint32_t i = wbase + u * 64;
-        key[u] = pay[u] = 0;
-        if (u < rounds && i < n) {
-            if (side_a) {
-                key[u] = (uint32_t)g.inverse[f_a * g.B + i];
-                pay[u] = (uint32_t)(f_a * g.B + i);
-            } else {
-                key[u] = s_key[i] | ((uint32_t)g.u_values[i] & row_mask);  // an id beyond the tables stays in its feature
-                pay[u] = g.pay_positions ? i : s_pay[i];
-                if (g.u_weights || g.pay_pos)
-                    g.pos_list[i] = s_pay[i];
-            }
+        pay[u] = 0;
+        if (i >= n) {
+            key[u] = 0;
+        } else if (side_a) {
+            key[u] = (uint32_t)g.inverse[f_a * g.B + i];
+            pay[u] = (uint32_t)(f_a * g.B + i);
+        } else {
+            key[u] = s_key[i] | (key[u] & row_mask);  // an id beyond the tables stays in its feature
+            pay[u] = g.pay_positions ? p0 + i : s_pay[i];
+            if (g.u_weights || g.pay_pos)
+                g.pos_list[p0 + i] = s_pay[i];
         }
     }
     const int passes = side_a ? g.a.passes : passes_b, dbits = side_a ? g.a.dbits : dbits_b;
@@ -1158,7 +1194,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kSmallRounds; u++) {
-            if (u >= rounds)  // the same in every thread
+            if (u >= rounds || wbase - lane + u * 64 >= n)  // the same in every thread of the wave
                 break;
             const bool valid = wbase + u * 64 < n;
             const uint32_t d = (key[u] >> shift) & mask;
@@ -1196,21 +1232,27 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
             s_loc[tid] = (uint16_t)at;
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kSmallRounds; u++)
-            if (u < rounds && wbase + u * 64 < n) {
+        for (int u = 0; u < kSmallRounds; u++) {
+            if (u >= rounds)
+                break;
+            if (wbase + u * 64 < n) {
                 const uint32_t d = (key[u] >> shift) & mask;
                 const uint32_t to = (uint32_t)s_loc[d] + s_run[w][d] + rank[u];
                 s_key[to] = key[u];
                 s_pay[to] = pay[u];
             }
+        }
         __syncthreads();
         if (p + 1 < passes) {
 #pragma unroll
-            for (int u = 0; u < kSmallRounds; u++)
-                if (u < rounds && wbase + u * 64 < n) {
+            for (int u = 0; u < kSmallRounds; u++) {
+                if (u >= rounds)
+                    break;
+                if (wbase + u * 64 < n) {
                     key[u] = s_key[wbase + u * 64];
                     pay[u] = s_pay[wbase + u * 64];
                 }
+            }
         }
     }
     // ---- out, in the same order of threads ---------------------------------------------------------------
@@ -1230,22 +1272,16 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
         }
         return;
     }
-    if (n == 0) {  // no id anywhere
-        for (int f = tid; f <= g.F; f += kSmallThreads)
-            g.feat_roff[f] = 0;
-        if (tid == 0)
-            g.seg_start_b[0] = g.list_off_b[0] = g.list_off_b[1] = g.chunk_count[0] = 0;
-        return;
-    }
     const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    uint32_t heads = 0, last = 0;  // of the wave so far; last: position of its last head + 1
-    uint32_t num[kSmallRounds], open[kSmallRounds];
+    uint32_t heads = 0, last = 0;  // of the wave so far; last: place of its last head + 1
+    uint32_t num[kSmallRounds], open[kSmallRounds], chunk[kSmallRounds];  // chunk: the first of the segment closed here
     uint64_t hm[kSmallRounds];
 #pragma unroll
     for (int u = 0; u < kSmallRounds; u++) {
+        if (u >= rounds)
+            break;
         const uint32_t i = wbase + u * 64;
-        const bool in = u < rounds && i < n;
-        hm[u] = __ballot(in && (i == 0 || s_key[i] != s_key[i - 1]));
+        hm[u] = __ballot(i < n && (i == 0 || s_key[i] != s_key[i - 1]));
         const uint64_t below = hm[u] & lt_mask;
         const uint32_t at0 = i - lane;
         num[u] = heads + (uint32_t)__popcll(below);
@@ -1257,68 +1293,136 @@ __global__ __launch_bounds__(kSmallThreads) void k_group_small(const GroupParams
     if (lane == 0)
         s_wave[w] = ((uint64_t)heads << 32) | last;
     __syncthreads();
-    uint32_t wh = 0, wl = 0, R = 0, end_open = 0;
-#pragma unroll
-    for (int i = 0; i < kSmallWaves; i++) {
-        const uint32_t h = (uint32_t)(s_wave[i] >> 32), l = (uint32_t)s_wave[i];
-        if (i < w) {
-            wh += h;
-            wl = l > wl ? l : wl;
-        }
-        R += h;
-        end_open = l > end_open ? l : end_open;
-    }
-    auto list_chunks = [&](uint32_t seg, uint32_t start, uint32_t end) {
-        const uint32_t len = end - start;
-        if (len <= (uint32_t)g.long_seg)
-            return;
-        const uint32_t ch = len > 64 * 256 ? (len + 63) / 64 : 256u, nch = (len + ch - 1) / ch;
-        const uint32_t first = atomicAdd(&s_chunks, nch);
-        g.chunk_arrive[first] = 0;
-        for (uint32_t c = 0; c < nch; c++)
-            g.chunks[first + c] = RecdChunk{start + c * ch, c + 1 < nch ? start + (c + 1) * ch : end, seg, first, nch};
-    };
+    const uint64_t of_wave = s_wave[lane & 15];  // every wave scans the sixteen itself
+    const uint32_t heads_to = row_scan_add((uint32_t)(of_wave >> 32));
+    const int last_to = row_scan_max((int)(uint32_t)of_wave);
+    const uint32_t R = of_lane(heads_to, 15), end_open = of_lane((uint32_t)last_to, 15);
+    const uint32_t wh = w > 0 ? of_lane(heads_to, w - 1) : 0, wl = w > 0 ? of_lane((uint32_t)last_to, w - 1) : 0;
+    // chunks of a segment that is cut
+    static_assert(kSmallCap <= 64 * 256, "chunks of 256 entries, at most 64 of a segment");
+    auto chunks_of = [&](uint32_t len) { return len > (uint32_t)g.long_seg ? (len + 255) / 256 : 0u; };
+    uint32_t tail_chunk = 0;
 #pragma unroll
     for (int u = 0; u < kSmallRounds; u++) {
+        if (u >= rounds)
+            break;
         const uint32_t i = wbase + u * 64;
-        if (u >= rounds || i >= n)
+        chunk[u] = 0;
+        if (i >= n)
             continue;
-        const uint32_t pp = s_pay[i];
-        if (g.u_weights || g.pay_pos) {  // the entry's source row and its weight or position, both in sorted order
-            g.b.pay[0][i] = g.pos_list[pp];
-            if (g.u_weights)
-                g.pay_w[i] = g.u_weights[pp];
-            else
-                g.pay_pos[i] = pp;
-        } else {
-            g.b.pay[0][i] = pp;
-        }
-        const uint32_t seg = wh + num[u];
         if ((hm[u] >> lane) & 1) {
-            const uint32_t kk = s_key[i], f = kk >> row_bits;
-            const int fprev = i == 0 ? -1 : (int)(s_key[i - 1] >> row_bits);
             if (open[u] == 0)
                 open[u] = wl;
-            g.seg_start_b[seg] = i;
-            g.touched_rows[seg] = kk & row_mask;
-            g.seg_feat[seg] = (int32_t)f;
-            for (int ff = fprev + 1; ff <= (int)f; ff++)
-                g.feat_roff[ff] = seg;
-            if (i > 0)
-                list_chunks(seg - 1, open[u] - 1, i);
+            const uint32_t many = i > 0 ? chunks_of(i + 1 - open[u]) : 0;
+            if (many)
+                chunk[u] = atomicAdd(&s_chunks, many);
         }
         if (i == n - 1) {
-            list_chunks(R - 1, end_open - 1, n);
-            g.seg_start_b[R] = n;
-            g.list_off_b[0] = 0;
-            g.list_off_b[1] = R;
-            for (int ff = (int)(s_key[i] >> row_bits) + 1; ff <= g.F; ff++)
-                g.feat_roff[ff] = R;
+            const uint32_t many = chunks_of(n + 1 - end_open);
+            if (many)
+                tail_chunk = atomicAdd(&s_chunks, many);
         }
     }
     __syncthreads();
-    if (tid == 0)
-        g.chunk_count[0] = s_chunks;
+    // rows and chunks of the blocks before this one: what needs neither goes out while the words travel
+    if (tid == 0 && b_blocks > 1)
+        st_agent(words + blk, (R + 1) | (s_chunks << 16));  // 8192 and 8192 / 17 at most
+#pragma unroll
+    for (int u = 0; u < kSmallRounds; u++) {
+        if (u >= rounds)
+            break;
+        const uint32_t i = wbase + u * 64;
+        if (i >= n)
+            continue;
+        const uint32_t pp = s_pay[i];
+        if (g.u_weights || g.pay_pos) {  // the entry's source row and its weight or position, both in sorted order
+            g.b.pay[0][p0 + i] = g.pos_list[pp];
+            if (g.u_weights)
+                g.pay_w[p0 + i] = g.u_weights[pp];
+            else
+                g.pay_pos[p0 + i] = pp;
+        } else {
+            g.b.pay[0][p0 + i] = pp;
+        }
+    }
+    if (w == 0 && b_blocks > 1) {
+        uint32_t r = 0, c = 0;
+        for (uint32_t j = lane; j < blk; j += 64) {
+            uint32_t x;
+            while ((x = ld_agent(words + j)) == 0)
+                __builtin_amdgcn_s_sleep(1);
+            r += (x & 0xffff) - 1;
+            c += x >> 16;
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            r += __shfl_xor(r, d);
+            c += __shfl_xor(c, d);
+        }
+        if (lane == 0) {
+            s_before[0] = r;
+            s_before[1] = c;
+        }
+    }
+    uint32_t seg0 = 0, chunk0 = 0;
+    if (b_blocks > 1) {
+        __syncthreads();
+        seg0 = s_before[0];
+        chunk0 = s_before[1];
+    }
+    auto list_chunks = [&](uint32_t seg, uint32_t start, uint32_t end, uint32_t first) {
+        const uint32_t nch = chunks_of(end - start);
+        if (nch == 0)
+            return;
+        g.chunk_arrive[first] = 0;
+        for (uint32_t c = 0; c < nch; c++)
+            g.chunks[first + c] = RecdChunk{p0 + start + c * 256, p0 + (c + 1 < nch ? start + (c + 1) * 256 : end), seg, first, nch};
+    };
+#pragma unroll
+    for (int u = 0; u < kSmallRounds; u++) {
+        if (u >= rounds)
+            break;
+        const uint32_t i = wbase + u * 64;
+        if (i >= n)
+            continue;
+        const uint32_t seg = seg0 + wh + num[u];
+        if ((hm[u] >> lane) & 1) {
+            const uint32_t kk = s_key[i], f = per > 1 ? kk >> row_bits : 0;
+            const int fprev = i == 0 ? -1 : (per > 1 ? (int)(s_key[i - 1] >> row_bits) : 0);
+            g.seg_start_b[seg] = p0 + i;
+            g.touched_rows[seg] = kk & row_mask;
+            g.seg_feat[seg] = f0 + (int32_t)f;
+            for (int ff = fprev + 1; ff <= (int)f; ff++)
+                g.feat_roff[f0 + ff] = seg;
+            if (i > 0)
+                list_chunks(seg - 1, open[u] - 1, i, chunk0 + chunk[u]);
+        }
+        if (i == n - 1)
+            list_chunks(seg0 + R - 1, end_open - 1, n, chunk0 + tail_chunk);
+    }
+    if (tid == 0) {
+        const int held = n == 0 ? -1 : (per > 1 ? (int)(s_key[n - 1] >> row_bits) : 0);
+        for (int ff = held + 1; ff < f1 - f0; ff++)  // the block's features without ids behind the last that has some
+            g.feat_roff[f0 + ff] = seg0 + R;
+        if (f1 == g.F) {
+            g.feat_roff[g.F] = seg0 + R;
+            g.seg_start_b[seg0 + R] = p0 + n;
+            g.list_off_b[0] = 0;
+            g.list_off_b[1] = seg0 + R;
+            g.chunk_count[0] = chunk0 + s_chunks;
+        }
+    }
+    if (w == 0 && b_blocks > 1) {
+        uint32_t before = 0;
+        if (lane == 0)
+            before = __hip_atomic_fetch_add(readers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) == (uint32_t)(b_blocks - 1)) {  // every block has read the words
+            for (int i = lane; i < b_blocks; i += 64)
+                st_agent(words + i, 0u);
+            if (lane < 2)
+                st_agent(ticket + lane, 0u);
+        }
+    }
 }
 
 int bits_for(uint64_t max_value)
@@ -1498,9 +1602,12 @@ recd_status recd_group(recd_ctx *ctx, hipStream_t st, const RecdGroupWs &w, cons
     g.lists_cap = a.lists_cap;
     if (recd_group_is_small(a.F, a.B, a.M_cap, a.max_rows)) {
         const int row_bits = bits_for((uint64_t)(a.max_rows > 1 ? a.max_rows - 1 : 1));
+        // a block's ids and rows take most of a CU's LDS: no more blocks than CUs as far as the features' rows allow it
+        const int most = ctx->num_cu / 2 > 0 ? ctx->num_cu / 2 : 1, per = (a.F + most - 1) / most;
+        const int b_blocks = (a.F + per - 1) / per;
         int passes, dbits;
-        digits_for(row_bits + (a.F > 1 ? bits_for((uint64_t)(a.F - 1)) : 0), &passes, &dbits);
-        hipLaunchKernelGGL(k_group_small, dim3(1 + a.F), dim3(kSmallThreads), 0, st, g, row_bits, passes, dbits);
+        digits_for(row_bits + (per > 1 ? bits_for((uint64_t)(per - 1)) : 0), &passes, &dbits);
+        hipLaunchKernelGGL(k_group_small, dim3(b_blocks + a.F), dim3(kSmallThreads), 0, st, g, b_blocks, per, row_bits, passes, dbits);
         RECD_HIP(ctx, hipGetLastError());
         return RECD_OK;
     }
