@@ -806,13 +806,15 @@ __device__ __forceinline__ bool small_gather(const uint64_t *agg, int n, int lan
 // agg: 2 words per feature, then the arrival counter and the failure mark; all zero between launches.
 // A feature's ids are one contiguous stretch of `values`: up to kSmallStage of them are brought into
 // LDS with one round of coalesced loads, and hashing, comparing and copying read them there (longer
-// stretches are read from memory each time).  Small kernels run at low clocks, so the instruction
-// count matters here: 32-bit hashing (the exact comparison decides anyway), ballots and lane shifts
-// for the scans, one barrier per phase.
+// stretches are read from memory each time).  A block has its CU for itself and is bound by its round trips and by what its
+// waves issue: 32-bit hashing by one product a pair of ids (the exact comparison decides anyway), ballots and lane shifts
+// for the scans, one barrier per phase, and NT = 256 or 512 threads where a feature's rows and ids need no more (7 features
+// of 37 rows 8.4 us, with 512 threads 7.9; 26 of 16 rows 9.0, with 256 8.3; the arrival counted before the lists are
+// written, without a release, 0.5 us of these and of 4 features of 512 rows 10.5 -> 9.9).
 constexpr int kSmallStage = 16384;
 
-template <int SG>
-__global__ __launch_bounds__(kSmallThreads) void k_build_small(const int64_t *__restrict__ values,
+template <int SG, int NT>
+__global__ __launch_bounds__(NT) void k_build_small(const int64_t *__restrict__ values,
                                                                const int64_t *__restrict__ offsets, int B, int F,
                                                                uint32_t cap_mask, int weak_hash, int spin_limit,
                                                                uint64_t *agg, int64_t *__restrict__ u_values,
@@ -827,8 +829,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const int64_t *__
     __shared__ uint32_t s_off[kSmallB + 1], s_pos[kSmallB];  // a row's ids start at s_off, relative to the feature
     __shared__ int16_t s_slot[kSmallB];
     __shared__ uint16_t s_num[kSmallB], s_src[kSmallB];
-    __shared__ uint32_t s_wcnt[kSmallThreads / 64], s_wlen[kSmallThreads / 64];
-    __shared__ int s_wlast[kSmallThreads / 64];
+    __shared__ uint32_t s_wcnt[16], s_wlen[16];  // of waves that there are not: nothing
+    __shared__ int s_wlast[16];
     __shared__ int64_t s_base[4];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -838,25 +840,29 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const int64_t *__
 
     // offsets of the feature's rows (one load per thread), the empty table
     const int64_t fstart = offsets[l0];
-    for (int i = tid; i <= B; i += kSmallThreads)
+    for (int i = tid; i <= B; i += NT)
         s_off[i] = (uint32_t)(offsets[l0 + i] - fstart);
-    for (int i = tid; i <= (int)cap_mask; i += kSmallThreads)
+    for (int i = tid; i <= (int)cap_mask; i += NT)
         s_tab[i] = kSmallEmpty;
+    if (tid >= NT / 64 && tid < 16) {
+        s_wcnt[tid] = s_wlen[tid] = 0;
+        s_wlast[tid] = -1;
+    }
     __syncthreads();
     const int n_ids = (int)s_off[B];
     const bool staged = n_ids <= kSmallStage;
     const int64_t *gids = values + fstart;
     if (staged) {
-        for (int i0 = tid; i0 < n_ids; i0 += 8 * kSmallThreads) {
+        for (int i0 = tid; i0 < n_ids; i0 += 8 * NT) {
             int64_t v[8];
 #pragma unroll
             for (int k = 0; k < 8; k++) {
-                const int i = i0 + k * kSmallThreads;
+                const int i = i0 + k * NT;
                 v[k] = i < n_ids ? gids[i] : 0;
             }
 #pragma unroll
             for (int k = 0; k < 8; k++) {
-                const int i = i0 + k * kSmallThreads;
+                const int i = i0 + k * NT;
                 if (i < n_ids)
                     s_ids[i] = v[k];
             }
@@ -875,24 +881,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const int64_t *__
         const int pstart = b > 0 ? (int)s_off[b - 1] : start;
         int follows = b > 0 && (start - pstart) == len;
         uint32_t h = 0;
-        for (int t0 = s; t0 < len; t0 += 4 * SG) {
+        for (int t0 = 2 * s; t0 < len; t0 += 4 * SG) {  // two pairs of ids a lane
             int64_t v[4], q[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) {
-                const int t = t0 + k * SG;
+                const int t = t0 + (k & 1) + (k >> 1) * 2 * SG;
                 v[k] = t < len ? id(start + t) : 0;
                 q[k] = (follows && t < len) ? id(pstart + t) : v[k];
             }
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
+            for (int k = 0; k < 4; k += 2) {
                 const int t = t0 + k * SG;
-                if (t < len) {
-                    follows &= q[k] == v[k];
-                    // position-salted sum of mixed ids: which lane adds which id does not matter
-                    uint32_t x = (uint32_t)v[k] ^ ((uint32_t)((uint64_t)v[k] >> 32) * 0x9e3779b1u);
-                    x = (x + (uint32_t)(t + 1) * 0x7feb352du) * 0x85ebca6bu;
-                    h += x ^ (x >> 15);
-                }
+                follows &= q[k] == v[k] && q[k + 1] == v[k + 1];
+                // a sum that depends on the pairs' positions: which lane adds which pair does not matter
+                const uint64_t x = hash_pair(hash_word(v[k], 0), hash_word(v[k + 1], 0), (uint32_t)t);
+                if (t < len)
+                    h += (uint32_t)x ^ (uint32_t)(x >> 32);
             }
         }
 #pragma unroll
@@ -1022,6 +1026,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const int64_t *__
 
     // ---- the features before this one ----------------------------------------------------------------
     bool ok = true;
+    unsigned long long before = 0;  // blocks that had read the others' words
     if (wv == 0) {
         int64_t bu, br, bm;
         ok = small_gather(agg, f, lane, spin_limit, bu, br, bm);
@@ -1031,6 +1036,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const int64_t *__
             s_base[0] = bu;
             s_base[1] = br;
             s_base[2] = bm;
+            if (!ok)
+                __hip_atomic_store(agg + 2 * (size_t)F + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // This block's words and mark have reached memory and the others' are read: the arrival is counted, and its
+            // answer travels while the lists are written.  (No release: it would write back the XCD's L2 behind all the
+            // block's stores, which nobody waits for before the kernel ends.)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            before = __hip_atomic_fetch_add(agg + 2 * (size_t)F, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();
@@ -1052,7 +1064,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const int64_t *__
     }
     auto copy_lists = [&](auto id) {
         constexpr int CG = 8;  // lanes per copied list
-        for (int k = tid / CG; k < (int)n_first; k += kSmallThreads / CG) {
+        for (int k = tid / CG; k < (int)n_first; k += NT / CG) {
             const int sb = s_src[k];
             const int start = (int)s_off[sb], len = (int)s_off[sb + 1] - start;
             const int64_t dst = base_m + s_pos[sb];
@@ -1067,14 +1079,6 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const int64_t *__
 
     // ---- arrival: the last block adds up the batch and leaves the words clear -----------------------------
     if (wv == 0) {
-        uint64_t *arrived = agg + 2 * (size_t)F;
-        unsigned long long before = 0;
-        if (lane == 0) {
-            if (!ok)
-                __hip_atomic_store(agg + 2 * (size_t)F + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            // my words and my reads of the others' lie before the arrival
-            before = __hip_atomic_fetch_add(arrived, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        }
         before = __shfl(before, 0);
         if (before == (unsigned long long)(F - 1)) {
             int64_t U, R, M;
@@ -1806,18 +1810,22 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
             cap <<= 1;
         const int spin = ctx->small_path == 2 ? -1 : kSmallSpinLimit;
         const int sg = B * 8 <= kSmallThreads ? 8 : (B * 4 <= kSmallThreads ? 4 : (B * 2 <= kSmallThreads ? 2 : 1));
-#define RECD_SMALL(SG)                                                                                              \
-    hipLaunchKernelGGL((k_build_small<SG>), dim3((unsigned)F), dim3(kSmallThreads), 0, st, values, offsets, (int)B, F, \
+#define RECD_SMALL(SG, NT)                                                                                              \
+    hipLaunchKernelGGL((k_build_small<SG, NT>), dim3((unsigned)F), dim3(NT), 0, st, values, offsets, (int)B, F, \
                        cap - 1, ctx->weak_hash, spin, ctx->small_agg, u_values, u_offsets, inverse, feat_uoff,      \
                        ctx->build_counts_dev, mailbox, seq, run_index)
-        if (sg == 8)
-            RECD_SMALL(8);
+        if (B <= 32 && N <= (int64_t)F * 2048)
+            RECD_SMALL(8, 256);
+        else if (B <= 64 && N <= (int64_t)F * 4096)
+            RECD_SMALL(8, 512);
+        else if (sg == 8)
+            RECD_SMALL(8, 1024);
         else if (sg == 4)
-            RECD_SMALL(4);
+            RECD_SMALL(4, 1024);
         else if (sg == 2)
-            RECD_SMALL(2);
+            RECD_SMALL(2, 1024);
         else
-            RECD_SMALL(1);
+            RECD_SMALL(1, 1024);
 #undef RECD_SMALL
         RECD_HIP(ctx, hipGetLastError());
         ctx->ws_used_since_build = false;
