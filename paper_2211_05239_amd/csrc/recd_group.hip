@@ -29,7 +29,6 @@
 namespace {
 
 constexpr int kCountThreads = 256;
-constexpr int kFPT = RECD_MAX_FEATURES / kCountThreads;  // features per thread of k_group_count
 constexpr int kTileThreads = 512;
 constexpr int kItems = 8;
 constexpr int kTile = kTileThreads * kItems;  // entries of a tile
@@ -44,6 +43,8 @@ constexpr int kSumChunks = 16;
 // kSmallTilesPer tiles each.
 constexpr int kSmallItems = 2;
 constexpr int kSmallTile = kTileThreads * kSmallItems;
+constexpr int kSmallTileLog = 10;
+static_assert(kSmallTile == 1 << kSmallTileLog, "chunks are powers of two");
 constexpr int kSmallTilesPer = 32;
 constexpr int64_t kSmallTilesMost = 480 << 10;  // entries of a side
 static_assert(kTile % kSmallTile == 0 && kSmallTilesPer * kSmallTile < 1 << 16, "counts of other tiles are 16 bits");
@@ -181,8 +182,9 @@ __device__ __forceinline__ void write_bases(const SideParams &s, int f, const ui
 // last of every sixteen adds up these first).  The block also
 // clears the look-back flags of its tiles; further blocks write the list of every position.  Of a side that goes by
 // small tiles a block counts the first digit of one small tile, and the sweep adds up.  What is
-// read is small (8 bytes an entry): the kernel is a few dependent round trips and the LDS atomics of a
-// chunk.
+// read is small (8 bytes an entry): the kernel is a few dependent round trips, the LDS atomics of a
+// chunk, and what its waves issue: divisions by the chunk's size, four features and places of the queue order a thread,
+// sixteen key slots where a small tile fills four were half of it (0.19 M ids 11.0 us, now 5.9).
 __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams g)
 {
     extern __shared__ uint32_t s_dyn[];          // the counts [passes * radix], side B also pb [F+1]: as little
@@ -234,68 +236,64 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         if (tid == 0)
             s_pick[0] = ~0u;
         __syncthreads();
-        // a thread stands for kFPT neighbouring features, and for kFPT neighbouring places of the queue
-        // order (features 0, 8, 16, ..., then 1, 9, ...)
-        const int per_q = g.F / kQueues, more = g.F % kQueues;
-        const int wide = more * (per_q + 1);  // places in the queues that hold one feature more
         if (small) {
             bool beyond = false;
             for (int x = tid; x < g.F; x += kCountThreads)
                 beyond |= s_pb[x + 1] - s_pb[x] > (uint32_t)(kSmallTilesPer * kSmallTile);
             small = !__syncthreads_or(beyond);
         }
-        const int64_t chunk = small ? kSmallTile : s.chunk;
+        const int chunk_log = small ? kSmallTileLog : 31 - __builtin_clz((uint32_t)s.chunk);  // a power of two
+        const uint32_t chunk = 1u << chunk_log;
         auto tiles_of = [&](int x) { return (s_pb[x + 1] - s_pb[x] + kTile - 1) / kTile; };
-        auto chunks_of = [&](int x) { return (uint32_t)((s_pb[x + 1] - s_pb[x] + chunk - 1) / chunk); };
-        auto queue_of = [&](int i) { return i < wide ? i / (per_q + 1) : more + (i - wide) / per_q; };
-        auto in_queue = [&](int i) { return i < wide ? i % (per_q + 1) : (i - wide) % per_q; };
-        uint64_t sum = 0, all;
-        uint32_t sum_q = 0, all_q;
-#pragma unroll
-        for (int i = 0; i < kFPT; i++) {
-            const int x = tid * kFPT + i;
-            if (x < g.F) {
-                sum += ((uint64_t)tiles_of(x) << 32) | chunks_of(x);
-                sum_q += tiles_of(in_queue(x) * kQueues + queue_of(x));
+        auto chunks_of = [&](int x) { return (s_pb[x + 1] - s_pb[x] + chunk - 1) >> chunk_log; };
+        // the block's feature and chunk; a thread stands for one feature (of more than the block has threads, for one after
+        // the other)
+        uint64_t so_far = 0;  // tiles (high half) and chunks of the features before
+        for (int x0 = 0; x0 < g.F; x0 += kCountThreads) {
+            const int x = x0 + tid;
+            uint64_t mine = 0, all;
+            if (x < g.F)
+                mine = ((uint64_t)tiles_of(x) << 32) | chunks_of(x);
+            const uint64_t ex = so_far + block_excl<uint64_t, kCountThreads / 64>(mine, all);
+            if (blk - (uint32_t)ex < (uint32_t)mine) {
+                s_pick[0] = x;
+                s_pick[1] = blk - (uint32_t)ex;
+                s_pick[2] = (uint32_t)mine;
+                s_pick[3] = (uint32_t)(ex >> 32);
             }
+            so_far += all;
         }
-        uint64_t ex = block_excl<uint64_t, kCountThreads / 64>(sum, all);
-        uint32_t t_q = block_excl<uint32_t, kCountThreads / 64>(sum_q, all_q);
-#pragma unroll
-        for (int i = 0; i < kFPT; i++) {
-            const int x = tid * kFPT + i;
-            if (x < g.F) {
-                const uint32_t c_f = chunks_of(x), c0 = (uint32_t)ex;
-                if (blk >= c0 && blk < c0 + c_f) {
-                    s_pick[0] = x;
-                    s_pick[1] = blk - c0;
-                    s_pick[2] = c_f;
-                    s_pick[3] = (uint32_t)(ex >> 32);
+        const uint32_t tiles = (uint32_t)(so_far >> 32);
+        if (!small) {  // tiles go by queues: features 0, 8, 16, ..., then 1, 9, ...
+            const int per_q = g.F / kQueues, more = g.F % kQueues;
+            const int wide = more * (per_q + 1);  // places in the queues that hold one feature more
+            uint32_t before = 0;
+            __syncthreads();
+            for (int x0 = 0; x0 < g.F; x0 += kCountThreads) {
+                const int i = x0 + tid;  // place in the queue order
+                uint32_t mine = 0, all;
+                int q = 0, at = 0;
+                if (i < g.F) {
+                    q = i < wide ? i / (per_q + 1) : more + (i - wide) / per_q;
+                    at = i < wide ? i % (per_q + 1) : (i - wide) % per_q;
+                    mine = tiles_of(at * kQueues + q);
                 }
-                ex += ((uint64_t)tiles_of(x) << 32) | c_f;
+                const uint32_t ex = before + block_excl<uint32_t, kCountThreads / 64>(mine, all);
+                if (i < g.F && (uint32_t)(at * kQueues + q) == s_pick[0])
+                    s_pick[4] = ex;
+                if (i < g.F && blk == 0 && at == 0)
+                    g.queue_start[q] = ex;
+                before += all;
             }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kFPT; i++) {
-            const int x = tid * kFPT + i;
-            if (x < g.F) {
-                const int fq = in_queue(x) * kQueues + queue_of(x);
-                if ((uint32_t)fq == s_pick[0])
-                    s_pick[4] = t_q;
-                if (blk == 0 && in_queue(x) == 0)
-                    g.queue_start[queue_of(x)] = t_q;
-                t_q += tiles_of(fq);
-            }
+            if (blk == 0 && tid >= (g.F < kQueues ? g.F : kQueues) && tid <= kQueues)
+                g.queue_start[tid] = tiles;  // queues without a feature, and the end
         }
         if (blk == 0) {
             for (int i = tid; i <= g.F; i += kCountThreads)
                 g.pb[i] = s_pb[i];
-            if (tid >= (g.F < kQueues ? g.F : kQueues) && tid <= kQueues)
-                g.queue_start[tid] = all_q;  // queues without a feature, and the end
             if (tid == 0) {
-                g.tile_total[0] = all_q;
-                g.tile_total[1] = small ? (uint32_t)all : 0;
+                g.tile_total[0] = tiles;
+                g.tile_total[1] = small ? (uint32_t)so_far : 0;
                 const int64_t M = g.u_offsets[g.feat_uoff[g.F]];
                 g.too_small_b[0] = M > g.M_cap ? 1 : 0;
                 g.chunk_count[0] = 0;
@@ -307,17 +305,18 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         f = (int)s_pick[0];
         c = (int)s_pick[1];
         n_chunks = (int)s_pick[2];
-        begin = s_pb[f] + (uint32_t)(c * chunk);
-        end = (uint32_t)((int64_t)begin + chunk < (int64_t)s_pb[f + 1] ? begin + chunk : s_pb[f + 1]);
-        const uint32_t k0 = (uint32_t)(c * chunk / kTile);
-        first_tile = s_pick[4] + k0;
+        begin = s_pb[f] + ((uint32_t)c << chunk_log);
+        end = s_pb[f + 1] - begin > chunk ? begin + chunk : s_pb[f + 1];
+        const uint32_t k0 = ((uint32_t)c << chunk_log) / kTile;
+        first_tile = (small ? 0 : s_pick[4]) + k0;
         chunk_row = blk;
         // tiles that start in the chunk
-        const uint32_t my_tiles = small ? (c * chunk % kTile == 0 ? 1 : 0) : (end - begin + kTile - 1) / kTile;
+        const uint32_t my_tiles = small ? (((uint32_t)c << chunk_log) % kTile == 0 ? 1 : 0) : (end - begin + kTile - 1) / kTile;
         if (small && tid == 0)
             g.desc_small[blk] = make_uint4(f, c, s_pb[f], s_pb[f + 1] - s_pb[f]);
         for (uint32_t k = tid; k < my_tiles; k += kCountThreads) {
-            g.desc_queue[first_tile + k] = make_uint2(f, k0 + k);
+            if (!small)
+                g.desc_queue[first_tile + k] = make_uint2(f, k0 + k);
             g.desc_feat[s_pick[3] + k0 + k] = make_uint4(f, k0 + k, s_pb[f], s_pb[f + 1] - s_pb[f]);
             g.seg_status[s_pick[3] + k0 + k] = 0;
         }
@@ -333,11 +332,15 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
         uint32_t key[16];
 #pragma unroll
         for (int u = 0; u < 16; u++) {
+            if (i0 - tid + u * kCountThreads >= n)  // the same in every thread
+                break;
             const uint32_t i = i0 + u * kCountThreads;
             key[u] = i < n ? (side_a ? (uint32_t)g.inverse[begin + i] : (uint32_t)g.u_values[begin + i]) : 0u;
         }
 #pragma unroll
         for (int u = 0; u < 16; u++) {
+            if (i0 - tid + u * kCountThreads >= n)
+                break;
             // Side A comes in runs of one slot (the samples of a session): the first lane of a run counts for
             // all of it, where every lane's own atomic would queue at one address.
             const bool on = i0 + u * kCountThreads < n;
