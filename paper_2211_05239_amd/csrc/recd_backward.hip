@@ -614,7 +614,16 @@ __global__ void k_no_rows(int F, int64_t *feat_roff, int64_t *list_off)
 // the inner loop is row loads only, eight in flight per thread (a thread = one 16-byte piece of
 // one position); lists with more rows take further rounds that continue from the stored partial
 // sum - the same additions in the same order.
-template <int LISTS>
+//
+// Eight loads in flight are worth what the list has rows for: with one or two rows a list, six or
+// seven of the eight load the last row again and a thread waits a whole trip for each position.  Where
+// no list of the block has more than two (four) rows, FEW takes four (two) positions side by side
+// instead, two (four) rows of each: the same eight loads, all of them wanted.  Of 2 rows a list
+// 339 -> 231 us (rows of 1 KB, 1.2 GB in all), of 3 68 -> 65, of 1 211 -> 151.  Its loads are unconditional, of a row
+// of the list again where there is none: loads under a condition took 109 registers, and the 72 us of a batch of
+// 8 rows a list became 134.  Batches with more rows a list run the kernel without it (8 rows 72.5 us either way,
+// 32 rows 162 against 170).
+template <int LISTS, bool FEW>
 __global__ __launch_bounds__(256) void k_jagged_reduce(const float4 *__restrict__ grad_out,
                                                        const int64_t *__restrict__ offsets,
                                                        const uint32_t *__restrict__ ps,
@@ -682,6 +691,66 @@ __global__ __launch_bounds__(256) void k_jagged_reduce(const float4 *__restrict_
             __syncthreads();
             if (sub >= rows_per_sweep)
                 continue;
+            // Lists of few rows: AT positions of a thread side by side, ROWS rows of each
+            auto add_few = [&](auto rows_, auto at_) {
+                constexpr int ROWS = decltype(rows_)::value, AT = decltype(at_)::value;
+                for (uint32_t r0 = sub; r0 < total; r0 += rows_per_sweep * AT) {
+                    uint32_t j[AT], n[AT];
+                    bool in[AT];
+                    uint32_t src[AT][ROWS];  // below 2^31, as all rows
+#pragma unroll
+                    for (int x = 0; x < AT; x++) {
+                        const uint32_t r = r0 + x * rows_per_sweep, rc = r < total ? r : total - 1;
+                        uint32_t a = 0;  // the last list with rel_s[a] <= rc
+#pragma unroll
+                        for (uint32_t s = LISTS / 2; s >= 1; s >>= 1)
+                            if (a + s < nl && rel_s[a + s] <= rc)
+                                a += s;
+                        const uint32_t t = rc - rel_s[a], c = cnt_s[a];
+                        const int64_t at = pos_s[a] + t;
+                        j[x] = (uint32_t)at;
+                        n[x] = c;
+                        in[x] = r < total && at < m_cap;
+#pragma unroll
+                        for (int k = 0; k < ROWS; k++) {
+                            const int64_t from = c > 0 ? off_s[a][k < (int)c ? k : c - 1] + t : 0;
+                            src[x][k] = (uint32_t)(from < n_rows ? from : n_rows - 1);  // only a malformed IKJT gets here
+                        }
+                    }
+                    float4 v[AT][ROWS];
+#pragma unroll
+                    for (int x = 0; x < AT; x++)
+#pragma unroll
+                        for (int k = 0; k < ROWS; k++) {
+                            typedef float f32x4g __attribute__((ext_vector_type(4)));
+                            const f32x4g t4 = __builtin_nontemporal_load(reinterpret_cast<const f32x4g *>(grad_out) +
+                                                                         (int64_t)src[x][k] * vecs + piece);
+                            v[x][k] = make_float4(t4.x, t4.y, t4.z, t4.w);
+                        }
+#pragma unroll
+                    for (int x = 0; x < AT; x++) {
+                        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                        for (int k = 0; k < ROWS; k++)
+                            if (k < (int)n[x]) {
+                                acc.x += v[x][k].x;
+                                acc.y += v[x][k].y;
+                                acc.z += v[x][k].z;
+                                acc.w += v[x][k].w;
+                            }
+                        if (in[x])
+                            g_emb[(int64_t)j[x] * vecs + piece] = acc;
+                    }
+                }
+            };
+            if (FEW && cmax <= 2) {
+                add_few(std::integral_constant<int, 2>(), std::integral_constant<int, 4>());
+                continue;
+            }
+            if (FEW && cmax <= 4) {
+                add_few(std::integral_constant<int, 4>(), std::integral_constant<int, 2>());
+                continue;
+            }
             for (uint32_t r = sub; r < total; r += rows_per_sweep) {
                 uint32_t a = 0;  // the last list with rel_s[a] <= r; r < rel_s[nl], so it is not empty
 #pragma unroll
@@ -1062,10 +1131,15 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
                 blocks = (int64_t)ctx->num_cu * 64;
             if (blocks < 1)
                 blocks = 1;
-#define RECD_JR(L)                                                                                    \
-    hipLaunchKernelGGL((k_jagged_reduce<L>), dim3((unsigned)blocks), dim3(256), 0, st,                 \
-                       reinterpret_cast<const float4 *>(grad_out), kjt_offsets, ps_a, w.seg_start,     \
+            // At most four rows a list, on average over its positions: blocks without a longer list are
+            // likely.  Beyond, few are, and the plain kernel is the quicker one (figures at the kernel).
+            // A loose M_cap only makes the average smaller than it is.
+            const bool few = N <= 4 * M_cap;
+#define RECD_JR_(L, FEW)                                                                              \
+    hipLaunchKernelGGL((k_jagged_reduce<L, FEW>), dim3((unsigned)blocks), dim3(256), 0, st,           \
+                       reinterpret_cast<const float4 *>(grad_out), kjt_offsets, ps_a, w.seg_start,    \
                        w.list_off + 1, u_offsets, reinterpret_cast<float4 *>(grad_emb), D / 4, N, M_cap)
+#define RECD_JR(L) if (few) RECD_JR_(L, true); else RECD_JR_(L, false)
             switch (lists) {
             case 1: RECD_JR(1); break;
             case 2: RECD_JR(2); break;
@@ -1076,6 +1150,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
             default: RECD_JR(64); break;
             }
 #undef RECD_JR
+#undef RECD_JR_
             RECD_HIP(ctx, hipGetLastError());
         }
     }
