@@ -1746,30 +1746,29 @@ void emit_lists(const recd_ctx *ctx, hipStream_t st, int64_t B, uint32_t rows, i
 } // namespace
 
 
-// The context's own tables, which are empty between builds, in the place of the workspace's: of w.cap slots each, and behind
+// Tables t of the context's own, which are empty between builds, in the place of the workspace's: of w.cap slots each, and behind
 // them the look-back words of `rows` rows and `more` words.  slots: all of these, for the build's last kernel to clear.
-static recd_status own_tables(recd_ctx *ctx, hipStream_t st, int tables, int64_t rows, SlotWs &w, size_t &slots, size_t more = 0)
+static recd_status own_tables(recd_ctx *ctx, hipStream_t st, RecdTables &t, int tables, int64_t rows, SlotWs &w, size_t &slots,
+                              size_t more = 0)
 {
     slots = (size_t)tables * w.cap + look_words(rows) + more;
-    if (slots > ctx->build_table_slots) {
+    if (slots > t.slots) {
         RECD_HIP(ctx, hipStreamSynchronize(st));
-        if (ctx->build_table)
-            RECD_HIP(ctx, hipFree(ctx->build_table));
-        ctx->build_table = nullptr;
-        ctx->build_table_slots = 0;
+        if (t.words)
+            RECD_HIP(ctx, hipFree(t.words));
+        t = RecdTables();
         const size_t want = slots + slots / 4;
         void *tp = nullptr;
         if (hipMalloc(&tp, want * sizeof(uint64_t)) != hipSuccess) {
             (void)hipGetLastError();
             return recd_fail(ctx, RECD_ENOMEM, "hash tables of %zu bytes: allocation failed", want * sizeof(uint64_t));
         }
-        ctx->build_table = static_cast<uint64_t *>(tp);
-        ctx->build_table_slots = want;
-        ctx->table_clean = false;
+        t.words = static_cast<uint64_t *>(tp);
+        t.slots = want;
     }
-    if (!ctx->table_clean)
-        hipLaunchKernelGGL(k_fill_u64, dim3(4096), dim3(256), 0, st, ctx->build_table, (int64_t)ctx->build_table_slots, kEmpty);
-    w.table = ctx->build_table;
+    if (!t.clean)
+        hipLaunchKernelGGL(k_fill_u64, dim3(4096), dim3(256), 0, st, t.words, (int64_t)t.slots, kEmpty);
+    w.table = t.words;
     w.look = w.table + (size_t)tables * w.cap;
     w.look_lists = w.look + look_words(rows);
     return RECD_OK;
@@ -1862,8 +1861,8 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
                                (int64_t)6, 0ull);
     } else {
         size_t slots = 0;
-        RECD_TRY(own_tables(ctx, st, F, n_lists, w, slots));
-        ctx->table_clean = false;  // until this build's last kernel is enqueued
+        RECD_TRY(own_tables(ctx, st, ctx->build_table, F, n_lists, w, slots));
+        ctx->build_table.clean = false;  // until this build's last kernel is enqueued
         insert_lists(ctx, st, w, F, B, values, offsets, weights, true);
         // without a host destination the counts go to the mailbox from the kernel that computes
         // them (no kernel of its own between the build and what the caller enqueues next)
@@ -1877,10 +1876,10 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
         number_slots(st, w, F, B, offsets, u_offsets, feat_uoff, mailbox, seq, run_index);
         recd_time_begin(ctx, RECD_T_EMIT, st);
         emit_lists(ctx, st, B, (uint32_t)n_lists, n_lists, values, offsets, w, w.src_of, u_offsets, counts, u_values, inverse, weights,
-                   u_weights, ctx->build_table, (int64_t)slots, run_index);
+                   u_weights, ctx->build_table.words, (int64_t)slots, run_index);
         recd_time_end(ctx, RECD_T_EMIT, st);
         RECD_HIP(ctx, hipGetLastError());
-        ctx->table_clean = true;
+        ctx->build_table.clean = true;
     }
     RECD_HIP(ctx, hipGetLastError());
     ctx->build_valid = true;
@@ -2089,14 +2088,15 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
         const int32_t *dev_group_off = nullptr, *dev_feat_group = nullptr;
         RECD_TRY(recd_group_map(ctx, F, G, group_off, &dev_group_off, &dev_feat_group));
         constexpr int SG = 8;
-        size_t slots = (size_t)G * w.cap + look_words(n_items) + look_words(n_lists);
+        size_t slots = 0;
+        // A captured build has the workspace's tables, which it clears itself: those of the context may grow, and so move,
+        // with any later build.
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (slots > ctx->build_table_slots)
-            RECD_HIP(ctx, hipStreamIsCapturing(st, &capture));
-        const bool own = capture == hipStreamCaptureStatusNone;  // a capture cannot wait for the context's tables to grow
+        RECD_HIP(ctx, hipStreamIsCapturing(st, &capture));
+        const bool own = capture == hipStreamCaptureStatusNone;
         if (own) {
-            RECD_TRY(own_tables(ctx, st, G, n_items, w, slots, look_words(n_lists)));
-            ctx->table_clean = false;  // until this build's last kernel is enqueued
+            RECD_TRY(own_tables(ctx, st, ctx->group_table, G, n_items, w, slots, look_words(n_lists)));
+            ctx->group_table.clean = false;  // until this build's last kernel is enqueued
         } else {
             clear_table(st, w, G, B, look_words(n_lists));
         }
@@ -2123,10 +2123,10 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
         }
         // the groups' inverse from their rows' numbers, and the stored lists' ids
         emit_lists(ctx, st, B, (uint32_t)n_items, n_lists, values, offsets, w, src_of, u_offsets, counts, u_values, inverse_g, nullptr,
-                   nullptr, own ? ctx->build_table : nullptr, own ? (int64_t)slots : 0);
+                   nullptr, own ? ctx->group_table.words : nullptr, own ? (int64_t)slots : 0);
         RECD_HIP(ctx, hipGetLastError());
         if (own)
-            ctx->table_clean = true;
+            ctx->group_table.clean = true;
     }
     RECD_HIP(ctx, hipGetLastError());
     if (host_counts) {

@@ -339,8 +339,10 @@ recd_status recd_destroy(recd_ctx *ctx)
         (void)hipFree(ctx->small_agg);
     if (ctx->group_arrive)
         (void)hipFree(ctx->group_arrive);
-    if (ctx->build_table)
-        (void)hipFree(ctx->build_table);
+    if (ctx->build_table.words)
+        (void)hipFree(ctx->build_table.words);
+    if (ctx->group_table.words)
+        (void)hipFree(ctx->group_table.words);
     if (ctx->host_pinned)
         (void)hipHostFree(ctx->host_pinned);
     if (ctx->mailbox)

@@ -32,6 +32,13 @@ struct KernelTimer {
 
 constexpr int RECD_GROUP_ARRIVE = 4096;  // counters of a side of the grouping
 
+// Hash tables that are empty between builds.
+struct RecdTables {
+    uint64_t *words = nullptr;
+    size_t slots = 0;
+    bool clean = false;
+};
+
 struct recd_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -62,13 +69,13 @@ struct recd_ctx {
         int64_t *touched_rows = nullptr, *feat_roff = nullptr;
         const char *ws = nullptr;   // the workspace the plan lives in must still be the context's
     } plan;
-    // Hash tables of the plain, weighted and grouped builders: memory of their own that is all "empty" whenever
+    // Hash tables of the plain and weighted builders: memory of their own that is all "empty" whenever
     // no build is running on the stream, because the builder's last kernel clears what the build
-    // used (so no clearing kernel stands at the head of the next build).  table_clean is false
+    // used (so no clearing kernel stands at the head of the next build).  `clean` is false
     // while that cannot be relied on (first use, or a build that failed half way).
-    uint64_t *build_table = nullptr;
-    size_t build_table_slots = 0;
-    bool table_clean = false;
+    RecdTables build_table;
+    // those of the grouped builder: a captured plain build keeps its tables whatever grouped builds follow it
+    RecdTables group_table;
     char *ws = nullptr;          // device workspace
     size_t ws_bytes = 0;
     int64_t *host_pinned = nullptr;  // 8 x int64 pinned staging for scalar results

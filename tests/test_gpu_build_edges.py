@@ -162,3 +162,52 @@ def test_grouped_tuples_that_differ_in_one_place(recd, seed):
             _check(gu.gpu_build(c, batch)[2], batch)
     finally:
         c.close()
+
+
+def test_captured_grouped_build_outlives_larger_ones(recd):
+    """A captured grouped build, replayed after eager builds, grouped and plain, whose tables are larger than its own."""
+    def lists(F, B, seed):
+        rng = np.random.default_rng(seed)
+        pool = [rng.integers(0, 90, n).tolist() for n in (0, 1, 3, 16, 17, 40)]
+        rows = [[pool[rng.integers(6)] for _ in range(B)] for _ in range(F)]
+        for f in range(F):
+            rows[f][0] = pool[5]
+        return synth.batch_from_lists(rows)
+    F, B, group_off, many = 5, 300, [0, 2, 5], 40 * 5 * 300
+    stream = torch.cuda.Stream()
+    z = lambda n, dt=torch.int64: torch.zeros(n, dtype=dt, device="cuda")
+    with torch.cuda.stream(stream):
+        c = recd.Context(0, workspace_hint_bytes=recd.workspace_bytes(F, 4096, many, 4))
+        values, offsets = z(many), z(F * B + 1)
+        out = [z(many), z(F * B + 1), z(2 * B, torch.int32), z(3), z(F + 1)]
+    def build(values, offsets, B, out):
+        c.build_ikjt_grouped(F, B, group_off, values, offsets, *out)
+    def load(batch):
+        values[:batch.N].copy_(torch.from_numpy(batch.values))
+        offsets.copy_(torch.from_numpy(batch.offsets))
+    try:
+        with torch.cuda.stream(stream):
+            load(lists(F, B, 0))
+            build(values, offsets, B, out)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                build(values, offsets, B, out)
+            for seed in range(1, 4):
+                big = lists(F, 1000 * seed, seed)
+                bv, bo = gu.to_dev(big.values), gu.to_dev(big.offsets)
+                build(bv, bo, big.B, [z(big.N), z(F * big.B + 1), z(2 * big.B, torch.int32), z(3), z(F + 1)])
+                c.set_option(recd._OPT_INTERNAL_SMALL_PATH, 0)
+                _check(gu.gpu_build(c, big)[2], big)
+                load(lists(F, B, 10 + seed))
+                for x in out:
+                    x.zero_()
+                build(values, offsets, B, out)
+                want = [x.clone() for x in out]
+                for x in out:
+                    x.zero_()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert all(torch.equal(x, y) for x, y in zip(out, want))
+    finally:
+        c.close()
