@@ -108,26 +108,45 @@ struct RowSumParams {
 // Tail of a row-gradient segment held by a lane group: acc = the segment's sum (piece w of lane r).
 // Applies row-wise Adagrad to the destination row (operands fetched earlier into wreg/mreg) and/or
 // stores the gradient row.
-template <int LPR>
+template <int LPR, int VPL = 4>
 __device__ __forceinline__ void finish_segment(const RowSumParams &p, const OptAdagrad &opt, int64_t t,
                                                const float4 *acc, const float4 *wreg, float mreg,
                                                float *wrow, float *mp, const bool *piece, int r,
                                                bool update)
 {
-    constexpr int VPL = 4;
     if (update) {
         float ss = 0.f;
-#pragma unroll
-        for (int w = 0; w < VPL; w++)
+        auto add_squares = [&](int w) {  // products and additions as written, not as the compiler would pair them
             if (piece[w]) {
-                ss += acc[w].x * acc[w].x;
-                ss += acc[w].y * acc[w].y;
-                ss += acc[w].z * acc[w].z;
-                ss += acc[w].w * acc[w].w;
+                ss = __fmaf_rn(acc[w].x, acc[w].x, ss);
+                ss = __fmaf_rn(acc[w].y, acc[w].y, ss);
+                ss = __fmaf_rn(acc[w].z, acc[w].z, ss);
+                ss = __fmaf_rn(acc[w].w, acc[w].w, ss);
+            }
+        };
+        if constexpr (VPL == 4) {
+#pragma unroll
+            for (int w = 0; w < VPL; w++)
+                add_squares(w);
+#pragma unroll
+            for (int s = 1; s < LPR; s <<= 1)
+                ss += __shfl_xor(ss, s);
+        } else {
+            // the additions of half as many lanes with four pieces each: lane r's pieces take turns with lane r + LPR / 2's
+            constexpr int H = LPR / 2;
+            const bool upper = r >= H;
+#pragma unroll
+            for (int w = 0; w < 2 * VPL; w++) {
+                if (upper == (w % 2 == 1))
+                    add_squares(w / 2);
+                const float other = __shfl_xor(ss, H);
+                if (upper == (w % 2 == 0))
+                    ss = other;
             }
 #pragma unroll
-        for (int s = 1; s < LPR; s <<= 1)
-            ss += __shfl_xor(ss, s);
+            for (int s = 1; s < H; s <<= 1)
+                ss += __shfl_xor(ss, s);
+        }
         const float mnew = mreg + ss / (float)p.D;
         const float scale = opt.lr / (sqrtf(mnew) + opt.eps);
 #pragma unroll
@@ -163,7 +182,7 @@ __device__ __forceinline__ void finish_segment(const RowSumParams &p, const OptA
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Destination row of a segment for the update: pointers, and its operands fetched ahead of the sums.
-template <int LPR>
+template <int LPR, int VPL = 4>
 __device__ __forceinline__ void fetch_row(const OptAdagrad &opt, int D, int f, int64_t row, const bool *piece, int r,
                                           float4 *wreg, float &mreg, float *&wrow, float *&mp)
 {
@@ -172,7 +191,7 @@ __device__ __forceinline__ void fetch_row(const OptAdagrad &opt, int D, int f, i
     wrow = opt.w[f] + row * D;
     mreg = *mp;
 #pragma unroll
-    for (int w = 0; w < 4; w++)
+    for (int w = 0; w < VPL; w++)
         if (piece[w]) {
             const f32x4l t = __builtin_nontemporal_load(reinterpret_cast<const f32x4l *>(wrow) + w * LPR + r);
             wreg[w] = make_float4(t.x, t.y, t.z, t.w);
@@ -245,10 +264,10 @@ template <int MODE> __device__ __forceinline__ void add4(float4 &acc, const floa
 }
 
 // One chunk of a cut segment, summed by the block.
-template <int LPR, int MODE>
+template <int LPR_, int MODE, bool WIDE>
 __device__ __forceinline__ void sum_chunk(const RowSumParams &p, const OptAdagrad &opt, int64_t item, const bool *piece)
 {
-    constexpr int G = 64 / LPR, VPL = 4, W = 256 / 64;
+    constexpr int LPR = WIDE ? 2 * LPR_ : LPR_, VPL = WIDE ? 2 : 4, W = 256 / 64, G = 64 / LPR_;
     __shared__ float4 s_part[W][VPL][LPR];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = lane / LPR, r = lane % LPR;
@@ -260,35 +279,72 @@ __device__ __forceinline__ void sum_chunk(const RowSumParams &p, const OptAdagra
     // A group takes the entries wv * G + g, + W * G, ...: LPR of them (256 of the block) are fetched by one
     // load, one per lane, and handed round by shuffles; two source rows in flight.
     const int gbase = lane - r;
-    for (uint32_t base = c.start + wv * G + g; base < c.end; base += W * G * LPR) {
-        const uint32_t idx = base + r * (W * G);
-        const uint32_t pre = idx < c.end ? p.pay[idx] : 0u, prex = idx < c.end ? entry_extra<MODE>(p, idx) : 0u;
-        const int left = (int)((c.end - base + W * G - 1) / (W * G)), cnt = left < LPR ? left : LPR;
-        if constexpr (MODE == ROWS_MAX) {
-#pragma unroll 1
-            for (int i0 = 0; i0 < cnt; i0 += 2)
-                add_won<LPR>(p, acc, pre, prex, gbase + i0, cnt - i0, r);
-            continue;
+    if constexpr (WIDE) {
+        // the entries of two groups, 2g and 2g + 1, one of each in flight; each has its own sum, as it would alone
+        float4 acc1[VPL];
+#pragma unroll
+        for (int w = 0; w < VPL; w++)
+            acc1[w] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (uint32_t base = c.start + wv * G + 2 * g; base < c.end; base += W * G * LPR) {
+            const uint32_t idx = base + r * (W * G);
+            const uint32_t pre0 = idx < c.end ? p.pay[idx] : 0u, prex0 = idx < c.end ? entry_extra<MODE>(p, idx) : 0u;
+            const uint32_t pre1 = idx + 1 < c.end ? p.pay[idx + 1] : 0u;
+            const uint32_t prex1 = idx + 1 < c.end ? entry_extra<MODE>(p, idx + 1) : 0u;
+            const int left0 = (int)((c.end - base + W * G - 1) / (W * G)), cnt0 = left0 < LPR ? left0 : LPR;
+            const int left1 = (int)((c.end - base + W * G - 2) / (W * G)), cnt1 = left1 < LPR ? left1 : LPR;
+            for (int i = 0; i < cnt0; i++) {
+                const uint32_t id0 = __shfl(pre0, gbase + i), id1 = __shfl(pre1, gbase + i);
+                const uint32_t x0 = __shfl(prex0, gbase + i), x1 = __shfl(prex1, gbase + i);
+                float4 v0[VPL], v1[VPL];
+#pragma unroll
+                for (int w = 0; w < VPL; w++)
+                    if (piece[w]) {
+                        v0[w] = entry_piece<LPR>(p, id0, w, r);
+                        v1[w] = entry_piece<LPR>(p, i < cnt1 ? id1 : id0, w, r);
+                    }
+#pragma unroll
+                for (int w = 0; w < VPL; w++)
+                    if (piece[w]) {
+                        add4<MODE>(acc[w], v0[w], x0);
+                        if (i < cnt1)
+                            add4<MODE>(acc1[w], v1[w], x1);
+                    }
+            }
         }
-        for (int i0 = 0; i0 < cnt; i0 += 2) {
-            const bool two = i0 + 1 < cnt;
-            const int k1 = i0 + (two ? 1 : 0);
-            const uint32_t id0 = __shfl(pre, gbase + i0), id1 = __shfl(pre, gbase + k1);
-            const uint32_t x0 = __shfl(prex, gbase + i0), x1 = __shfl(prex, gbase + k1);
-            float4 v0[VPL], v1[VPL];
 #pragma unroll
-            for (int w = 0; w < VPL; w++)
-                if (piece[w]) {
-                    v0[w] = entry_piece<LPR>(p, id0, w, r);
-                    v1[w] = entry_piece<LPR>(p, id1, w, r);
-                }
+        for (int w = 0; w < VPL; w++)
+            add4<ROWS_PLAIN>(acc[w], acc1[w], 0);
+    } else {
+        for (uint32_t base = c.start + wv * G + g; base < c.end; base += W * G * LPR) {
+            const uint32_t idx = base + r * (W * G);
+            const uint32_t pre = idx < c.end ? p.pay[idx] : 0u, prex = idx < c.end ? entry_extra<MODE>(p, idx) : 0u;
+            const int left = (int)((c.end - base + W * G - 1) / (W * G)), cnt = left < LPR ? left : LPR;
+            if constexpr (MODE == ROWS_MAX) {
+#pragma unroll 1
+                for (int i0 = 0; i0 < cnt; i0 += 2)
+                    add_won<LPR>(p, acc, pre, prex, gbase + i0, cnt - i0, r);
+                continue;
+            }
+            for (int i0 = 0; i0 < cnt; i0 += 2) {
+                const bool two = i0 + 1 < cnt;
+                const int k1 = i0 + (two ? 1 : 0);
+                const uint32_t id0 = __shfl(pre, gbase + i0), id1 = __shfl(pre, gbase + k1);
+                const uint32_t x0 = __shfl(prex, gbase + i0), x1 = __shfl(prex, gbase + k1);
+                float4 v0[VPL], v1[VPL];
 #pragma unroll
-            for (int w = 0; w < VPL; w++)
-                if (piece[w]) {
-                    add4<MODE>(acc[w], v0[w], x0);
-                    if (two)
-                        add4<MODE>(acc[w], v1[w], x1);
-                }
+                for (int w = 0; w < VPL; w++)
+                    if (piece[w]) {
+                        v0[w] = entry_piece<LPR>(p, id0, w, r);
+                        v1[w] = entry_piece<LPR>(p, id1, w, r);
+                    }
+#pragma unroll
+                for (int w = 0; w < VPL; w++)
+                    if (piece[w]) {
+                        add4<MODE>(acc[w], v0[w], x0);
+                        if (two)
+                            add4<MODE>(acc[w], v1[w], x1);
+                    }
+            }
         }
     }
 #pragma unroll
@@ -363,14 +419,20 @@ __device__ __forceinline__ void sum_chunk(const RowSumParams &p, const OptAdagra
     if (g != 0)
         return;
     if (update)
-        fetch_row<LPR>(opt, p.D, opt.seg_feat[c.seg], opt.touched_rows[c.seg], piece, r, wreg, mreg, wrow, mp);
-    finish_segment<LPR>(p, opt, c.seg, acc, wreg, mreg, wrow, mp, piece, r, update);
+        fetch_row<LPR, VPL>(opt, p.D, opt.seg_feat[c.seg], opt.touched_rows[c.seg], piece, r, wreg, mreg, wrow, mp);
+    finish_segment<LPR, VPL>(p, opt, c.seg, acc, wreg, mreg, wrow, mp, piece, r, update);
 }
 
-template <int LPR, int MODE>
+// WIDE: twice the lanes a segment, two pieces each.  What bounds a batch of some hundred thousand entries is the longest
+// segment of a wave, whose entries follow each other at a round trip each, and the few waves there are: with half the
+// segments a wave and 64 registers for 86 two entries are in flight, eight waves a SIMD.  us, four pieces a lane / WIDE: 0.19 M
+// entries of skewed ids, rows of 512 bytes 33.2 / 25.3, weighted 24.6 / 19.5; 256 bytes 29.9 / 23.8, 1 KB 42.2 / 32.9.  (Two
+// entries of four pieces a lane: 29.6, but uniform ids 66 -> 70; two pieces a lane in 85 registers 28.3, and uniform ids 66 -> 80.)
+// The additions and their order are those of four pieces a lane, in the chunks and the update too: the same bits.
+template <int LPR_, int MODE, bool WIDE>
 __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const OptAdagrad opt)
 {
-    constexpr int G = 64 / LPR, VPL = 4;
+    constexpr int LPR = WIDE ? 2 * LPR_ : LPR_, VPL = WIDE ? 2 : 4, G = 64 / LPR;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int g = lane / LPR, r = lane % LPR;
     bool piece[VPL];
@@ -380,7 +442,7 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
     if (blockIdx.x < p.chunk_blocks) {
         const int64_t n = *p.chunk_count;
         for (int64_t item = blockIdx.x; item < n; item += p.chunk_blocks)
-            sum_chunk<LPR, MODE>(p, opt, item, piece);
+            sum_chunk<LPR_, MODE, WIDE>(p, opt, item, piece);
         return;
     }
     const int64_t R = *p.n_seg;
@@ -416,7 +478,7 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
         const bool update = mine && opt.n_feat > 0;
         // second round trip: the segment's entries (the first kPre * LPR of them, one load per lane
         // and LPR entries) together with the destination row and its accumulator
-        constexpr int kPre = MODE == ROWS_MAX ? 1 : 4;
+        constexpr int kPre = MODE == ROWS_MAX ? 1 : VPL;
         uint32_t pre[kPre], prex[kPre];
 #pragma unroll
         for (int u = 0; u < kPre; u++) {
@@ -428,7 +490,7 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
         float mreg = 0.f;
         float *wrow = nullptr, *mp = nullptr;
         if (update)
-            fetch_row<LPR>(opt, p.D, f_seg, row_seg, piece, r, wreg, mreg, wrow, mp);
+            fetch_row<LPR, VPL>(opt, p.D, f_seg, row_seg, piece, r, wreg, mreg, wrow, mp);
         float4 acc[VPL];
 #pragma unroll
         for (int w = 0; w < VPL; w++)
@@ -464,9 +526,35 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
 #pragma unroll
             for (int u = 0; u < kPre; u++) {
                 const int cnt = n - u * LPR < LPR ? n - u * LPR : LPR;
-                for (int ii = 0; ii < cnt; ii++) {
-                    const uint32_t id = __shfl(pre[u], gbase + ii);
-                    add_entry(id, MODE != ROWS_PLAIN ? __shfl(prex[u], gbase + ii) : 0u);
+                if constexpr (WIDE) {
+                    constexpr int FLY = 2;
+                    for (int i0 = 0; i0 < cnt; i0 += FLY) {
+                        float4 v[FLY][VPL];
+                        uint32_t x[FLY];
+#pragma unroll
+                        for (int k = 0; k < FLY; k++) {
+                            const int from = gbase + (i0 + k < LPR ? i0 + k : LPR - 1);
+                            const uint32_t id = __shfl(pre[u], from);
+                            x[k] = MODE != ROWS_PLAIN ? __shfl(prex[u], from) : 0u;
+                            if (k == 0 || i0 + k < cnt)
+#pragma unroll
+                                for (int w = 0; w < VPL; w++)
+                                    if (piece[w])
+                                        v[k][w] = entry_piece<LPR>(p, id, w, r);
+                        }
+#pragma unroll
+                        for (int k = 0; k < FLY; k++)
+                            if (k == 0 || i0 + k < cnt)
+#pragma unroll
+                                for (int w = 0; w < VPL; w++)
+                                    if (piece[w])
+                                        add4<MODE>(acc[w], v[k][w], x[k]);
+                    }
+                } else {
+                    for (int ii = 0; ii < cnt; ii++) {
+                        const uint32_t id = __shfl(pre[u], gbase + ii);
+                        add_entry(id, MODE != ROWS_PLAIN ? __shfl(prex[u], gbase + ii) : 0u);
+                    }
                 }
             }
             for (int i = kPre * LPR; i < n; i++) {
@@ -475,7 +563,7 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
             }
         }
         if (mine)
-            finish_segment<LPR>(p, opt, k, acc, wreg, mreg, wrow, mp, piece, r, update);
+            finish_segment<LPR, VPL>(p, opt, k, acc, wreg, mreg, wrow, mp, piece, r, update);
     }
 }
 
@@ -928,6 +1016,8 @@ RecdGroupArgs group_args(const BwdWs &w, int F, int64_t B, int64_t U_cap, int64_
     return a;
 }
 
+constexpr int64_t kWideRows = 512 * 1024;  // entries up to which k_segsum_rows has two pieces a lane
+
 // Step B after the grouping: all segments in one launch, optimizer fused.
 recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t M_cap, const void *table,
                      int D, void *out, int64_t *touched_rows, const OptAdagrad *opt, const float *pay_w,
@@ -945,7 +1035,11 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
     o.touched_rows = touched_rows;
     o.seg_feat = w.seg_feat;
     const int lpr = row_lanes(D);
-    const int per_block = 4 * (64 / lpr);
+    // Rows of 9 to 128 pieces, and not so many entries that what counts is the memory's rate: us, four pieces a lane / two,
+    // rows of 512 bytes, 0.34 M entries of uniform ids 32.2 / 30.2, 0.69 M 66.1 / 72.1 (of skewed ids 87.8 / 82.7), 2.2 M of
+    // skewed ids 214.9 / 212.9.
+    const bool wide = !won && D > 32 && D <= 512 && M_cap <= kWideRows;
+    const int per_block = 4 * (64 / lpr) / (wide ? 2 : 1);
     int64_t nblk = (M_cap + per_block - 1) / per_block;
     const int64_t cap = (int64_t)ctx->num_cu * 64;
     if (nblk > cap)
@@ -961,16 +1055,28 @@ recd_status sum_rows(recd_ctx *ctx, const BwdWs &w, const uint32_t *ps, int64_t 
     rp.chunk_blocks = (unsigned)((cblk + 7) / 8 * 8);
     const dim3 grid((unsigned)(nblk + rp.chunk_blocks)), block(256);
     recd_time_begin(ctx, RECD_T_GRAD_ROWS, st);
+#define RECD_ROWS(L, WIDE) hipLaunchKernelGGL((k_segsum_rows<L, MODE, WIDE>), grid, block, 0, st, rp, o)
     auto launch = [&](auto mode) {
         constexpr int MODE = decltype(mode)::value;
+        if constexpr (MODE != ROWS_MAX)
+            if (wide) {
+                switch (lpr) {
+                case 4: RECD_ROWS(4, true); break;
+                case 8: RECD_ROWS(8, true); break;
+                case 16: RECD_ROWS(16, true); break;
+                default: RECD_ROWS(32, true); break;
+                }
+                return;
+            }
         switch (lpr) {
-        case 4: hipLaunchKernelGGL((k_segsum_rows<4, MODE>), grid, block, 0, st, rp, o); break;
-        case 8: hipLaunchKernelGGL((k_segsum_rows<8, MODE>), grid, block, 0, st, rp, o); break;
-        case 16: hipLaunchKernelGGL((k_segsum_rows<16, MODE>), grid, block, 0, st, rp, o); break;
-        case 32: hipLaunchKernelGGL((k_segsum_rows<32, MODE>), grid, block, 0, st, rp, o); break;
-        default: hipLaunchKernelGGL((k_segsum_rows<64, MODE>), grid, block, 0, st, rp, o); break;
+        case 4: RECD_ROWS(4, false); break;
+        case 8: RECD_ROWS(8, false); break;
+        case 16: RECD_ROWS(16, false); break;
+        case 32: RECD_ROWS(32, false); break;
+        default: RECD_ROWS(64, false); break;
         }
     };
+#undef RECD_ROWS
     if (won)
         launch(std::integral_constant<int, ROWS_MAX>());
     else if (pay_w)
