@@ -264,7 +264,9 @@ __global__ __launch_bounds__(kCountThreads) void k_group_count(const GroupParams
             so_far += all;
         }
         const uint32_t tiles = (uint32_t)(so_far >> 32);
-        if (!small) {  // tiles go by queues: features 0, 8, 16, ..., then 1, 9, ...
+        // Tiles go by queues: features 0, 8, 16, ..., then 1, 9, ...  The sweep looks for tiles there too where there is no id
+        // at all, and so no small tile.
+        if (!small || tiles == 0) {
             const int per_q = g.F / kQueues, more = g.F % kQueues;
             const int wide = more * (per_q + 1);  // places in the queues that hold one feature more
             uint32_t before = 0;
