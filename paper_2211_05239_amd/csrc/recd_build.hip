@@ -701,7 +701,7 @@ __global__ __launch_bounds__(256) void k_emit(const int64_t *__restrict__ values
         const uint32_t l = blockIdx.x * 256 + threadIdx.x;
         if (l < n_lists) {
             const uint32_t row0 = rows.of(l) * rows.by;
-            const int32_t u = number[row0 + (uint32_t)rep[l]];
+            const int32_t u = number[row0 + recd_row_named((uint32_t)rep[l], rows.by)];
             inverse[l] = u - number[row0];
             if (run_index && hrank[l] >= 0) {
                 // run entry: {row | (unique list, first-occurrence flag) << 32, ids at, ids}

@@ -10,6 +10,10 @@
 #define RECD_RULE inline
 #endif
 
+// A row of the feature that the builder's tables name, whatever they hold: on scratch that calls of other streams share, an
+// overlapping call may have cleared them, or filled in rows of a batch with more.
+RECD_RULE uint32_t recd_row_named(uint32_t row, uint32_t rows) { return row < rows ? row : 0; }
+
 // Division of a row number, below 2^31, by a number known to the host: a high product, an addition and a shift where the
 // compiler's 64-bit division takes some hundred vector instructions (Granlund and Montgomery's method for 32-bit words; the
 // sum stays below 2^32 as n does below 2^31).

@@ -15,6 +15,7 @@ int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vecs) { return rec
 bool short_grouping(int64_t rows, int64_t M_cap) { return recd_grouping_is_short(rows, M_cap); }
 uint32_t divide(uint32_t by, uint32_t n) { return recd_divide_by(by).of(n); }
 bool looks_back(int64_t rows, bool shared) { return recd_looks_back(rows, shared); }
+uint32_t row_named(uint32_t row, uint32_t rows) { return recd_row_named(row, rows); }
 
 // a build per character of `steps`: p: a plan follows it, -: none, s: a short one; says of each p whether it had an event
 // (counted) and of every build whether it recorded one
@@ -155,6 +156,20 @@ def test_no_wait_between_blocks_on_shared_scratch(rules):
     source = open(os.path.join(CSRC, "recd_build.hip")).read()
     call = source[source.index("recd_status recd_build_ikjt_noalloc("):]
     assert "carve_slots(c, F, B, n_lists, n_lists, true)" in call[:call.index("\n}\n")]
+
+
+def test_rows_that_tables_name_stay_inside_the_feature(rules):
+    """Overlapping recd_build_ikjt_noalloc calls may clear or fill each other's tables: what the last kernel reads there it
+    uses as a row only inside its feature."""
+    rules.row_named.restype = C.c_uint32
+    rules.row_named.argtypes = [C.c_uint32, C.c_uint32]
+    for rows in (1, 2, 37, 1024, 65536, 1 << 30):
+        for row in {0, rows - 1, rows, rows + 1, 65535, 1 << 31, 0xfffffffe, 0xffffffff}:
+            assert rules.row_named(row, rows) == (row if row < rows else 0)
+    source = open(os.path.join(CSRC, "recd_build.hip")).read()
+    emit = source[source.index("void k_emit("):]
+    emit = emit[:emit.index("\n}\n")]
+    assert "number[row0 + recd_row_named((uint32_t)rep[l], rows.by)]" in emit and emit.count("number[") == 2
 
 
 @pytest.mark.parametrize("seed", range(6))
