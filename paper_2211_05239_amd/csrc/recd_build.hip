@@ -1746,6 +1746,16 @@ void emit_lists(const recd_ctx *ctx, hipStream_t st, int64_t B, uint32_t rows, i
 } // namespace
 
 
+// Whether the stream is being captured.  The null stream never is, and to ask it is an error while another stream is.
+static recd_status capturing(recd_ctx *ctx, hipStream_t st, bool &yes)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (st != nullptr && st != hipStreamLegacy)
+        RECD_HIP(ctx, hipStreamIsCapturing(st, &status));
+    yes = status != hipStreamCaptureStatusNone;
+    return RECD_OK;
+}
+
 // Tables t of the context's own, which are empty between builds, in the place of the workspace's: of w.cap slots each, and behind
 // them the look-back words of `rows` rows and `more` words.  slots: all of these, for the build's last kernel to clear.
 static recd_status own_tables(recd_ctx *ctx, hipStream_t st, RecdTables &t, int tables, int64_t rows, SlotWs &w, size_t &slots,
@@ -2091,9 +2101,9 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
         size_t slots = 0;
         // A captured build has the workspace's tables, which it clears itself: those of the context may grow, and so move,
         // with any later build.
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        RECD_HIP(ctx, hipStreamIsCapturing(st, &capture));
-        const bool own = capture == hipStreamCaptureStatusNone;
+        bool captured = false;
+        RECD_TRY(capturing(ctx, st, captured));
+        const bool own = !captured;
         if (own) {
             RECD_TRY(own_tables(ctx, st, ctx->group_table, G, n_items, w, slots, look_words(n_lists)));
             ctx->group_table.clean = false;  // until this build's last kernel is enqueued
