@@ -1756,29 +1756,49 @@ static recd_status capturing(recd_ctx *ctx, hipStream_t st, bool &yes)
     return RECD_OK;
 }
 
-// Tables t of the context's own, which are empty between builds, in the place of the workspace's: of w.cap slots each, and behind
-// them the look-back words of `rows` rows and `more` words.  slots: all of these, for the build's last kernel to clear.
-static recd_status own_tables(recd_ctx *ctx, hipStream_t st, RecdTables &t, int tables, int64_t rows, SlotWs &w, size_t &slots,
-                              size_t more = 0)
+// Tables for a build of `tables` features or groups of B rows each: those of the context (t), of w.cap slots each, behind which lie the
+// look-back words of their rows and `more` words, all empty between builds; `slots` of them from `fill` on are for the build's last
+// kernel to clear.  A captured build has them too, if they are large enough; its graph goes on using them, so that they are kept when
+// a larger build takes others.  Where none can be had, without room for them or in a capture, the build has those that carve_slots
+// puts into the workspace, and empties them at its head.
+static recd_status build_tables(recd_ctx *ctx, hipStream_t st, RecdTables &t, int tables, int64_t B, SlotWs &w, uint64_t *&fill,
+                                size_t &slots, size_t more = 0)
 {
+    const int64_t rows = (int64_t)tables * B;
+    bool captured = false;
+    RECD_TRY(capturing(ctx, st, captured));
     slots = (size_t)tables * w.cap + look_words(rows) + more;
-    if (slots > t.slots) {
-        RECD_HIP(ctx, hipStreamSynchronize(st));
-        if (t.words)
-            RECD_HIP(ctx, hipFree(t.words));
-        t = RecdTables();
+    if (slots > t.slots && !captured) {
         const size_t want = slots + slots / 4;
         void *tp = nullptr;
-        if (hipMalloc(&tp, want * sizeof(uint64_t)) != hipSuccess) {
-            (void)hipGetLastError();
-            return recd_fail(ctx, RECD_ENOMEM, "hash tables of %zu bytes: allocation failed", want * sizeof(uint64_t));
+        RECD_HIP(ctx, hipStreamSynchronize(st));
+        if (t.captured) {
+            RecdKept *k = new (std::nothrow) RecdKept{t.words, ctx->kept_tables};
+            if (!k)
+                return recd_fail(ctx, RECD_ENOMEM, "out of host memory");
+            ctx->kept_tables = k;
+        } else if (t.words) {
+            RECD_HIP(ctx, hipFree(t.words));
         }
-        t.words = static_cast<uint64_t *>(tp);
-        t.slots = want;
+        t = RecdTables();
+        if (hipMalloc(&tp, want * sizeof(uint64_t)) == hipSuccess) {
+            t.words = static_cast<uint64_t *>(tp);
+            t.slots = want;
+        } else {
+            (void)hipGetLastError();
+        }
+    }
+    if (slots > t.slots || (captured && !t.clean)) {
+        clear_table(st, w, tables, B, more);
+        fill = nullptr;
+        slots = 0;
+        return RECD_OK;
     }
     if (!t.clean)
         hipLaunchKernelGGL(k_fill_u64, dim3(4096), dim3(256), 0, st, t.words, (int64_t)t.slots, kEmpty);
-    w.table = t.words;
+    t.clean = false;  // until the build's last kernel is enqueued
+    t.captured = t.captured || captured;
+    w.table = fill = t.words;
     w.look = w.table + (size_t)tables * w.cap;
     w.look_lists = w.look + look_words(rows);
     return RECD_OK;
@@ -1871,8 +1891,8 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
                                (int64_t)6, 0ull);
     } else {
         size_t slots = 0;
-        RECD_TRY(own_tables(ctx, st, ctx->build_table, F, n_lists, w, slots));
-        ctx->build_table.clean = false;  // until this build's last kernel is enqueued
+        uint64_t *fill = nullptr;
+        RECD_TRY(build_tables(ctx, st, ctx->build_table, F, B, w, fill, slots));
         insert_lists(ctx, st, w, F, B, values, offsets, weights, true);
         // without a host destination the counts go to the mailbox from the kernel that computes
         // them (no kernel of its own between the build and what the caller enqueues next)
@@ -1886,10 +1906,11 @@ static recd_status build_plain(recd_ctx *ctx, int F, int64_t B, int64_t N, const
         number_slots(st, w, F, B, offsets, u_offsets, feat_uoff, mailbox, seq, run_index);
         recd_time_begin(ctx, RECD_T_EMIT, st);
         emit_lists(ctx, st, B, (uint32_t)n_lists, n_lists, values, offsets, w, w.src_of, u_offsets, counts, u_values, inverse, weights,
-                   u_weights, ctx->build_table.words, (int64_t)slots, run_index);
+                   u_weights, fill, (int64_t)slots, run_index);
         recd_time_end(ctx, RECD_T_EMIT, st);
         RECD_HIP(ctx, hipGetLastError());
-        ctx->build_table.clean = true;
+        if (fill)
+            ctx->build_table.clean = true;
     }
     RECD_HIP(ctx, hipGetLastError());
     ctx->build_valid = true;
@@ -2099,17 +2120,8 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
         RECD_TRY(recd_group_map(ctx, F, G, group_off, &dev_group_off, &dev_feat_group));
         constexpr int SG = 8;
         size_t slots = 0;
-        // A captured build has the workspace's tables, which it clears itself: those of the context may grow, and so move,
-        // with any later build.
-        bool captured = false;
-        RECD_TRY(capturing(ctx, st, captured));
-        const bool own = !captured;
-        if (own) {
-            RECD_TRY(own_tables(ctx, st, ctx->group_table, G, n_items, w, slots, look_words(n_lists)));
-            ctx->group_table.clean = false;  // until this build's last kernel is enqueued
-        } else {
-            clear_table(st, w, G, B, look_words(n_lists));
-        }
+        uint64_t *fill = nullptr;
+        RECD_TRY(build_tables(ctx, st, ctx->group_table, G, B, w, fill, slots, look_words(n_lists)));
         const int64_t hblocks = (n_items + kHashBlock / SG - 1) / (kHashBlock / SG);
         hipLaunchKernelGGL((k_group_hash_insert<SG>), dim3((unsigned)((hblocks + 7) / 8 * 8)), dim3(kHashBlock), 0, st, values,
                            offsets, recd_divide_by((uint32_t)B), (uint32_t)n_items, dev_group_off, w.table,
@@ -2133,9 +2145,9 @@ extern "C" recd_status recd_build_ikjt_grouped(recd_ctx *ctx, int F, int64_t B, 
         }
         // the groups' inverse from their rows' numbers, and the stored lists' ids
         emit_lists(ctx, st, B, (uint32_t)n_items, n_lists, values, offsets, w, src_of, u_offsets, counts, u_values, inverse_g, nullptr,
-                   nullptr, own ? ctx->group_table.words : nullptr, own ? (int64_t)slots : 0);
+                   nullptr, fill, (int64_t)slots);
         RECD_HIP(ctx, hipGetLastError());
-        if (own)
+        if (fill)
             ctx->group_table.clean = true;
     }
     RECD_HIP(ctx, hipGetLastError());

@@ -343,6 +343,11 @@ recd_status recd_destroy(recd_ctx *ctx)
         (void)hipFree(ctx->build_table.words);
     if (ctx->group_table.words)
         (void)hipFree(ctx->group_table.words);
+    while (RecdKept *k = ctx->kept_tables) {
+        ctx->kept_tables = k->next;
+        (void)hipFree(k->words);
+        delete k;
+    }
     if (ctx->host_pinned)
         (void)hipHostFree(ctx->host_pinned);
     if (ctx->mailbox)

@@ -37,6 +37,11 @@ struct RecdTables {
     uint64_t *words = nullptr;
     size_t slots = 0;
     bool clean = false;
+    bool captured = false;       // a graph may hold them: they are kept when larger ones take their place
+};
+struct RecdKept {
+    uint64_t *words;
+    RecdKept *next;
 };
 
 struct recd_ctx {
@@ -74,8 +79,8 @@ struct recd_ctx {
     // used (so no clearing kernel stands at the head of the next build).  `clean` is false
     // while that cannot be relied on (first use, or a build that failed half way).
     RecdTables build_table;
-    // those of the grouped builder: a captured plain build keeps its tables whatever grouped builds follow it
-    RecdTables group_table;
+    RecdTables group_table;           // those of the grouped builder
+    RecdKept *kept_tables = nullptr;  // earlier ones of both that graphs may hold, until the context is destroyed
     char *ws = nullptr;          // device workspace
     size_t ws_bytes = 0;
     int64_t *host_pinned = nullptr;  // 8 x int64 pinned staging for scalar results
