@@ -54,26 +54,6 @@ constexpr int kHU = 2;     // strides of the loops over what lies beyond them
 typedef long long id2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef uint32_t wt2 __attribute__((ext_vector_type(2), aligned(4)));
 
-// An id and the bit pattern of its weight (0: there are none) as 32 bits of hash input.
-__device__ __forceinline__ uint32_t hash_word(long long id, uint32_t wbits)
-{
-    const uint32_t hi = (uint32_t)((uint64_t)id >> 32);
-    return (uint32_t)id ^ ((hi << 9) | (hi >> 23)) ^ (wbits * 0x85ebca6bu);
-}
-
-__device__ __forceinline__ uint32_t hash_key(uint32_t t)
-{
-    const uint32_t k = (t + 1) * 0x9e3779b1u;
-    return k ^ (k >> 15);
-}
-
-// What two adjacent ids, at positions t and t + 1, add to their list's hash: one product of 32 by 32 bits (two of 64 by 64
-// before).  That is enough: the sum goes through mix64 once a list, and an exact comparison follows every tag match.
-__device__ __forceinline__ uint64_t hash_pair(uint32_t a, uint32_t b, uint32_t t)
-{
-    return (uint64_t)(a + hash_key(t)) * (b + hash_key(t + 1));
-}
-
 // Two adjacent ids and their weights at position t, of n >= 2 from there on; at a list's odd end the last two.
 template <bool WT> struct IdPair {
     id2 v = {0, 0};
@@ -101,8 +81,8 @@ template <bool WT> struct IdPair {
     template <typename T> __device__ __forceinline__ uint64_t hash(T t, T n, uint32_t salt = 0) const  // of a list of n
     {
         const bool both = t + 1 < n;
-        const uint32_t x = hash_word(v.x, w.x), y = hash_word(v.y, w.y);
-        return hash_pair(both ? x : y, both ? y : 0u, (uint32_t)t + salt);
+        const uint32_t x = recd_hash_word(v.x, w.x), y = recd_hash_word(v.y, w.y);
+        return recd_hash_pair(both ? x : y, both ? y : 0u, (uint32_t)t + salt);
     }
 };
 
@@ -894,9 +874,9 @@ __global__ __launch_bounds__(NT) void k_build_small(const int64_t *__restrict__ 
                 const int t = t0 + k * SG;
                 follows &= q[k] == v[k] && q[k + 1] == v[k + 1];
                 // a sum that depends on the pairs' positions: which lane adds which pair does not matter
-                const uint64_t x = hash_pair(hash_word(v[k], 0), hash_word(v[k + 1], 0), (uint32_t)t);
+                const uint32_t x = recd_hash_pair32(recd_hash_word(v[k], 0), recd_hash_word(v[k + 1], 0), (uint32_t)t);
                 if (t < len)
-                    h += (uint32_t)x ^ (uint32_t)(x >> 32);
+                    h += x;
             }
         }
 #pragma unroll

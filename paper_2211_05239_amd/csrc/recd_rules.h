@@ -10,6 +10,35 @@
 #define RECD_RULE inline
 #endif
 
+// An id and the bit pattern of its weight (0: there are none) as 32 bits of hash input.
+RECD_RULE uint32_t recd_hash_word(int64_t id, uint32_t wbits)
+{
+    const uint32_t hi = (uint32_t)((uint64_t)id >> 32);
+    return (uint32_t)id ^ ((hi << 9) | (hi >> 23)) ^ (wbits * 0x85ebca6bu);
+}
+
+RECD_RULE uint32_t recd_hash_key(uint32_t t)
+{
+    const uint32_t k = (t + 1) * 0x9e3779b1u;
+    return k ^ (k >> 15);
+}
+
+// What two adjacent ids, at positions t and t + 1, add to their list's hash: one product of 32 by 32 bits (two of 64 by 64
+// before), and the keyed words beside each other, without which the id whose keyed word is zero would make lists that differ in
+// its neighbour alike: x * y + x + y * 2^32 tells apart all y of an x and all x of a y.  That is enough: the sum goes through a
+// mixer once a list, and an exact comparison follows every tag match.
+RECD_RULE uint64_t recd_hash_pair(uint32_t a, uint32_t b, uint32_t t)
+{
+    const uint32_t x = a + recd_hash_key(t), y = b + recd_hash_key(t + 1);
+    return (uint64_t)x * y + (((uint64_t)y << 32) | x);
+}
+// The same in 32 bits.  (The halves' exclusive or would be the same for every neighbour of the id whose keyed word is 2^32 - 1.)
+RECD_RULE uint32_t recd_hash_pair32(uint32_t a, uint32_t b, uint32_t t)
+{
+    const uint64_t h = recd_hash_pair(a, b, t);
+    return (uint32_t)h + (uint32_t)(h >> 32) * 0xc2b2ae35u;
+}
+
 // A row of the feature that the builder's tables name, whatever they hold: on scratch that calls of other streams share, an
 // overlapping call may have cleared them, or filled in rows of a batch with more.
 RECD_RULE uint32_t recd_row_named(uint32_t row, uint32_t rows) { return row < rows ? row : 0; }

@@ -15,6 +15,14 @@ int jagged_lists(int64_t N, int64_t U_cap, int64_t M_cap, int vecs) { return rec
 bool short_grouping(int64_t rows, int64_t M_cap) { return recd_grouping_is_short(rows, M_cap); }
 uint32_t divide(uint32_t by, uint32_t n) { return recd_divide_by(by).of(n); }
 bool looks_back(int64_t rows, bool shared) { return recd_looks_back(rows, shared); }
+void hash_pairs(const int64_t *a, const int64_t *b, int64_t n, uint32_t t, uint64_t *out, uint32_t *out32)
+{
+    for (int64_t i = 0; i < n; i++) {
+        out[i] = recd_hash_pair(recd_hash_word(a[i], 0), recd_hash_word(b[i], 0), t);
+        out32[i] = recd_hash_pair32(recd_hash_word(a[i], 0), recd_hash_word(b[i], 0), t);
+    }
+}
+uint32_t hash_key(uint32_t t) { return recd_hash_key(t); }
 uint32_t row_named(uint32_t row, uint32_t rows) { return recd_row_named(row, rows); }
 
 // a build per character of `steps`: p: a plan follows it, -: none, s: a short one; says of each p whether it had an event
@@ -156,6 +164,35 @@ def test_no_wait_between_blocks_on_shared_scratch(rules):
     source = open(os.path.join(CSRC, "recd_build.hip")).read()
     call = source[source.index("recd_status recd_build_ikjt_noalloc("):]
     assert "carve_slots(c, F, B, n_lists, n_lists, true)" in call[:call.index("\n}\n")]
+
+
+@pytest.mark.parametrize("t", [0, 2, 4, 46, 254, 3 << 20])
+def test_no_id_hides_its_neighbour_from_the_hash(rules, t):
+    """Lists that differ in one id, whatever its neighbour: among the neighbours the id that cancels its position's key, and
+    those around it.  In 64 bits all differ, in 32 as good as all.  And pairs of any ids."""
+    rules.hash_key.restype = C.c_uint32
+    rules.hash_key.argtypes = [C.c_uint32]
+    rules.hash_pairs.restype = None
+    rules.hash_pairs.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_uint32, C.c_void_p, C.c_void_p]
+
+    def distinct(a, b):
+        a, b = np.ascontiguousarray(a), np.ascontiguousarray(b)
+        out, out32 = np.zeros(len(a), dtype=np.uint64), np.zeros(len(a), dtype=np.uint32)
+        rules.hash_pairs(_ptr(a), _ptr(b), len(a), t, _ptr(out), _ptr(out32))
+        return len(np.unique(out)), len(np.unique(out32))
+    rng = np.random.default_rng(t)
+    n = 20000
+    others = rng.permutation(np.unique(np.concatenate([np.arange(n), rng.integers(0, 1 << 31, n)])))[:n].astype(np.int64)
+    for at, swap in ((t, False), (t + 1, True)):
+        zero = -rules.hash_key(at) % (1 << 32)
+        for fixed in (zero, zero - 1, zero + 1, 0, 1, 12345, (1 << 31) - 1):
+            pair = [np.full(n, fixed, dtype=np.int64), others]
+            whole, folded = distinct(*(pair[::-1] if swap else pair))
+            # the few alike cost the insertion a comparison each; half a percent of the lists would cost it half a percent
+            assert whole == n and folded >= n - n // 200, (at, fixed)
+    pairs = np.unique(rng.integers(0, 1 << 31, (n, 2)) % rng.choice([50, 10 ** 6, 1 << 31], (n, 1)), axis=0).astype(np.int64)
+    whole, folded = distinct(pairs[:, 0], pairs[:, 1])
+    assert whole == len(pairs) and folded >= len(pairs) - n // 200
 
 
 def test_rows_that_tables_name_stay_inside_the_feature(rules):
