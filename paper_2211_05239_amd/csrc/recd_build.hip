@@ -215,7 +215,10 @@ __global__ __launch_bounds__(kHashBlock) void k_hash_insert(const int64_t *__res
             for (int m = SG / 2; m > 0; m >>= 1)
                 eq &= __shfl_xor(eq, m, SG);
             if (eq) {
-                if (s == 0)
+                // rows only get smaller there: with an earlier one in it the slot needs no second atomic, and those of a list that
+                // many rows hold queue at its one address (262 K rows of 931 lists a feature, not in sessions:
+                // 207 -> 121 us)
+                if (s == 0 && mine < old)
                     atomicMin(reinterpret_cast<unsigned long long *>(&tab[slot]), mine);
                 break;
             }
@@ -1271,7 +1274,7 @@ __global__ __launch_bounds__(kHashBlock) void k_group_hash_insert(const int64_t 
                     eq &= __shfl_xor(eq, m, SG);
             }
             if (eq) {
-                if (s == 0)
+                if (s == 0 && mine < old)
                     atomicMin(reinterpret_cast<unsigned long long *>(&tab[slot]), mine);
                 break;
             }
