@@ -577,32 +577,51 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
 // the rows of g_u stay in L2.  (One masked row per position went to memory and back once; then a lane group walked a list
 // alone, the ids of eight rows fetched by every lane before them, and stored a byte a lane and position: 0.3 M positions of
 // 512 bytes in 12 K lists 43.4 us, now 19.4; a lookup of the same lists takes 21.)
+// Of short lists a wave owns NL, a lane group or more each: a wave for every list left most groups idle (whole backward, us, a
+// lane group a list as it was / a wave / NL = 64 / LPR: 108 K lists of one id, rows of 64 bytes 163 / 221 / 153, 206 K of 2.5 ids
+// 208 / 317 / 196, of 256 bytes 294 / 323 / 259; 57 K of 10 ids, 64 bytes 140 / 159 / 129; 24 K of 25, 512 bytes 256 / 191 / 194).
 struct MaxTables {
     const float *w[RECD_F_PER_LAUNCH];
 };
 constexpr int kWonWords = 512;  // of a window of a list's positions in LDS
 
-template <int LPR, int VPL>
+template <int LPR, int VPL, int NL>
 __global__ __launch_bounds__(64) void k_max_winner(const int64_t *__restrict__ u_values,
                                                    const int64_t *__restrict__ u_offsets,
                                                    const int64_t *__restrict__ feat_uoff, int f0, int nf,
                                                    MaxTables tabs, uint32_t *__restrict__ won, int won_lpr, int pieces,
                                                    int64_t lists_cap, int64_t m_cap)
 {
-    constexpr int G = 64 / LPR, US = 8 / VPL;  // US positions in flight per lane
+    constexpr int W = 64 / NL, G = W / LPR, US = 8 / VPL;  // lanes and lane groups of a list; positions in flight per lane
     __shared__ uint4 s_won[kWonWords / 4];
-    uint32_t *const words = reinterpret_cast<uint32_t *>(s_won);
-    const int lane = threadIdx.x, g = lane / LPR, r = lane % LPR;
+    const int lane = threadIdx.x, n_own = lane / W, in = lane % W, g = in / LPR, r = lane % LPR;
+    uint4 *const own = s_won + n_own * (kWonWords / 4 / NL);
+    uint32_t *const words = reinterpret_cast<uint32_t *>(own);
     const int64_t u_lo = feat_uoff[f0];
     int64_t u_hi = feat_uoff[f0 + nf];
     u_hi = u_hi < lists_cap ? u_hi : lists_cap;
     const int64_t fo0 = lane < nf ? feat_uoff[f0 + lane] : INT64_MAX, fo1 = 64 + lane < nf ? feat_uoff[f0 + 64 + lane] : INT64_MAX;
-    const int win = kWonWords / won_lpr;  // positions of a window
-    for (int64_t u = u_lo + blockIdx.x; u < u_hi; u += gridDim.x) {
-        const int f = (int)(__popcll(__ballot(fo0 <= u)) + __popcll(__ballot(fo1 <= u))) - 1;
+    const int win = kWonWords / NL / won_lpr;  // positions of a window
+    for (int64_t u0 = u_lo + (int64_t)blockIdx.x * NL; u0 < u_hi; u0 += (int64_t)gridDim.x * NL) {
+        int f = (int)(__popcll(__ballot(fo0 <= u0)) + __popcll(__ballot(fo1 <= u0))) - 1;
+        const int64_t u = u0 + n_own;
+        int64_t j0 = 0;
+        int len = 0;
+        if (NL == 1 || u < u_hi) {
+            while (NL > 1 && f + 1 < nf && feat_uoff[f0 + f + 1] <= u)
+                f++;
+            j0 = u_offsets[u];
+            const int64_t j1 = u_offsets[u + 1], end = j1 < m_cap ? j1 : m_cap;
+            len = j0 < end ? (int)(end - j0) : 0;  // m_cap is below 2^31
+        }
         const float4 *table = reinterpret_cast<const float4 *>(tabs.w[f]);
-        const int64_t j0 = u_offsets[u], j1 = u_offsets[u + 1];
-        const int len = (int)((j1 < m_cap ? j1 : m_cap) - j0);  // m_cap is below 2^31
+        int most = len;  // of the wave's lists
+#pragma unroll
+        for (int s = W; s < 64; s <<= 1) {
+            const int y = __shfl_xor(most, s);
+            most = y > most ? y : most;
+        }
+        most = __builtin_amdgcn_readfirstlane(most);
         float best[VPL][4];
         int arg[VPL][4];
 #pragma unroll
@@ -612,15 +631,16 @@ __global__ __launch_bounds__(64) void k_max_winner(const int64_t *__restrict__ u
                 best[w][e] = -INFINITY;
                 arg[w][e] = INT32_MAX;
             }
-        for (int c0 = 0; c0 < len; c0 += 64) {
-            const int nc = len - c0 < 64 ? len - c0 : 64, per = (nc + G - 1) / G;
-            const uint32_t id = lane < nc ? (uint32_t)u_values[j0 + c0 + lane] : 0u;
-            for (int k0 = 0; k0 < per; k0 += US) {
+        for (int c0 = 0; c0 < most; c0 += W) {
+            const int nc = len - c0 < W ? len - c0 : W, per = (nc + G - 1) / G;  // of the list; the longest's:
+            const int per_most = (most - c0 < W ? most - c0 + G - 1 : W) / G;
+            const uint32_t id = in < nc ? (uint32_t)u_values[j0 + c0 + in] : 0u;
+            for (int k0 = 0; k0 < per_most; k0 += US) {
                 float4 v[US][VPL];
 #pragma unroll
                 for (int k = 0; k < US; k++) {
                     const int t = g * per + k0 + k;
-                    const uint32_t row = __shfl(id, t & 63);
+                    const uint32_t row = __shfl(id, n_own * W + (t & (W - 1)));
                     if (k0 + k < per && t < nc)
 #pragma unroll
                         for (int w = 0; w < VPL; w++)
@@ -645,7 +665,7 @@ __global__ __launch_bounds__(64) void k_max_winner(const int64_t *__restrict__ u
             }
         }
 #pragma unroll
-        for (int s = LPR; s < 64; s <<= 1)
+        for (int s = LPR; s < W; s <<= 1)
 #pragma unroll
             for (int w = 0; w < VPL; w++)
 #pragma unroll
@@ -659,10 +679,10 @@ __global__ __launch_bounds__(64) void k_max_winner(const int64_t *__restrict__ u
                     best[w][e] = high ? hx : lx;
                     arg[w][e] = high ? ha : la;
                 }
-        for (int w0 = 0; w0 < len; w0 += win) {
-            const int n = len - w0 < win ? len - w0 : win, vecs = n * won_lpr / 4;
-            for (int i = lane; i < vecs; i += 64)
-                s_won[i] = make_uint4(0, 0, 0, 0);
+        for (int w0 = 0; w0 < most; w0 += win) {
+            const int left = len - w0 < win ? len - w0 : win, n = left > 0 ? left : 0, vecs = n * won_lpr / 4;
+            for (int i = in; i < vecs; i += W)
+                own[i] = make_uint4(0, 0, 0, 0);
             __syncthreads();
 #pragma unroll
             for (int w = 0; w < VPL; w++) {
@@ -676,8 +696,8 @@ __global__ __launch_bounds__(64) void k_max_winner(const int64_t *__restrict__ u
             }
             __syncthreads();
             uint4 *dst = reinterpret_cast<uint4 *>(won + (j0 + w0) * won_lpr);
-            for (int i = lane; i < vecs; i += 64)
-                dst[i] = s_won[i];
+            for (int i = in; i < vecs; i += W)
+                dst[i] = own[i];
             __syncthreads();
         }
     }
@@ -1016,6 +1036,11 @@ RecdGroupArgs group_args(const BwdWs &w, int F, int64_t B, int64_t U_cap, int64_
     return a;
 }
 
+// Ids a list on average, by the caller's bounds, below which the lists of a max-pooled backward share waves (k_max_winner).  Whole
+// backward, us, a wave a list / shared, rows of 64 and 256 bytes: uniform lengths, 10 ids 159 / 129, 180 / 167; 25 ids 119 / 119,
+// 146 / 145; 40 ids 110 / 121, 139 / 153; Zipf's, 7 of at most 30 152 / 126, 165 / 155; 15 of at most 256 185 / 221, 219 / 264.
+constexpr int64_t kSharedMean = 12;
+
 constexpr int64_t kWideRows = 512 * 1024;  // entries up to which k_segsum_rows has two pieces a lane
 
 // Step B after the grouping: all segments in one launch, optimizer fused.
@@ -1269,18 +1294,23 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
             const int nf = F - f0 < RECD_F_PER_LAUNCH ? F - f0 : RECD_F_PER_LAUNCH;
             for (int f = 0; f < nf; f++)
                 mt.w[f] = static_cast<const float *>(max_tables[f0 + f]);
-            const int64_t nblk = U_cap < (int64_t)ctx->num_cu * 256 ? U_cap : (int64_t)ctx->num_cu * 256;
+            const int nl = M_cap < kSharedMean * U_cap ? 64 / lpr : 1;
+            const int64_t waves = (U_cap + nl - 1) / nl, nblk = waves < (int64_t)ctx->num_cu * 256 ? waves : (int64_t)ctx->num_cu * 256;
             const dim3 grid((unsigned)(nblk < 1 ? 1 : nblk)), block(64);
-#define RECD_MR(L, V)                                                                                    \
-    hipLaunchKernelGGL((k_max_winner<L, V>), grid, block, 0, st, u_values, u_offsets, feat_uoff, f0, nf, mt,  \
+#define RECD_MR(L, V, N)                                                                                    \
+    hipLaunchKernelGGL((k_max_winner<L, V, N>), grid, block, 0, st, u_values, u_offsets, feat_uoff, f0, nf, mt,  \
                        w.won, row_lanes(D), P, U_cap, M_cap)
-            if (vpl == 4) RECD_MR(64, 4);
-            else if (vpl == 2) RECD_MR(64, 2);
-            else if (lpr == 4) RECD_MR(4, 1);
-            else if (lpr == 8) RECD_MR(8, 1);
-            else if (lpr == 16) RECD_MR(16, 1);
-            else if (lpr == 32) RECD_MR(32, 1);
-            else RECD_MR(64, 1);
+#define RECD_MR_(L) if (nl > 1) RECD_MR(L, 1, 64 / L); else RECD_MR(L, 1, 1)
+            switch (vpl > 1 ? P : lpr) {
+            case 256: RECD_MR(64, 4, 1); break;
+            case 128: RECD_MR(64, 2, 1); break;
+            case 4: RECD_MR_(4); break;
+            case 8: RECD_MR_(8); break;
+            case 16: RECD_MR_(16); break;
+            case 32: RECD_MR_(32); break;
+            default: RECD_MR(64, 1, 1); break;
+            }
+#undef RECD_MR_
 #undef RECD_MR
         }
         RECD_HIP(ctx, hipGetLastError());
