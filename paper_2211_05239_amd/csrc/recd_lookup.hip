@@ -29,12 +29,11 @@ namespace {
 
 constexpr int kNQ = 8;         // XCDs
 constexpr int kBlock = 256;
-// Most threads per block of the gather-sum kernel.  The waves of a block finish their lists at different times, and a block's
+// Threads per block of the gather-sum kernel.  The waves of a block finish their lists at different times, and a block's
 // registers are only free again when its last wave is done, so with lists of 1 to 256 ids a four-wave block keeps idle
 // waves resident (unique lookup 0.124 ms against 0.133, KJT lookup 0.99 against 1.16): the forward lookups' waves are on
-// their own, one to a block, or two where the grid is sized by a large bound (see recd_launch_segsum).  The backward's sum
-// keeps four waves: its long segments want the whole block.
-constexpr int seg_threads(int site) { return site == 0 || site == 4 ? 128 : (site == 1 || site == 2 ? 64 : 256); }
+// their own, one to a block.  The backward's sum keeps four waves: its long segments want the whole block.
+constexpr int seg_threads(int site) { return site == 0 || site == 1 || site == 2 || site == 4 ? 64 : 256; }
 constexpr int kMaxLB = 16;     // lists per block item (upper bound)
 constexpr int64_t kRunsLists = 32768;  // KJT lists from which on a wave takes several and shares equal neighbours' sums
 constexpr int kStage = 1024;   // ids of such a wave's lists that wait in LDS
@@ -47,12 +46,6 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
     uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)v);
     uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// A word that no kernel writes while this one runs, at an address that is the same in every lane, by a scalar load.
-__device__ __forceinline__ int64_t scalar_word(const int64_t *p)
-{
-    return *(const __attribute__((address_space(4))) int64_t *)(uintptr_t)p;
 }
 
 template <int TT> struct Elem;
@@ -168,6 +161,7 @@ struct SegSumParams {
     int D;
     int vecs_per_row;  // D / elements per 16-byte vector
     int nq;            // 8: XCD-aware queues (forward sites only); 1: one flat queue
+    int64_t stride;    // blocks of a queue
     int lb;            // lists per block item, <= kMaxLB; 0 (forward sites): chosen by the number of lists
     int64_t whole;     // SITE_KJT_RUNS: a queue's items of lb lists, the later ones have fewer (recd_item_start)
     int deal_log;      // the KJT lookup: how many lists are dealt to a queue at a time (recd_deal_log_kjt)
@@ -318,9 +312,8 @@ void k_segsum(const SegSumParams p)
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
     const int nq = p.nq;
     const int q = nq == 1 ? 0 : (int)(blockIdx.x % kNQ);
-    const int each = seg_threads(SITE) == 128 ? (int)(blockDim.x >> 6) : 1;  // waves of a block that take items of their own
-    const int64_t item0 = (int64_t)(nq == 1 ? blockIdx.x : blockIdx.x / kNQ) * each + (seg_threads(SITE) == 128 ? wv : 0);
-    const int64_t item_stride = (int64_t)(nq == 1 ? gridDim.x : gridDim.x / kNQ) * each;
+    const int64_t item0 = nq == 1 ? blockIdx.x : blockIdx.x / kNQ;
+    const int64_t item_stride = p.stride;
 
     const int g = lane / LPR;   // lane group = which of the G rows of a load
     const int r = lane % LPR;   // 16-byte piece of the row
@@ -408,7 +401,17 @@ void k_segsum(const SegSumParams p)
         const int64_t n_runs = ri[0] < p.run_cap ? ri[0] : p.run_cap;
         const int64_t per = (n_runs + kNQ - 1) / kNQ;
         const int64_t first_item = (int64_t)(blockIdx.x % kNQ) * per;
-        for (int64_t item = item0; item < per; item += item_stride) {
+        // Of more runs than waves the first waves have several neighbours: the runs in flight stay neighbours (at a stride they
+        // are of as many features as there are turns: 131 K runs of 30 ids, 512-byte rows, 162 us, now 158, 262 K 208 and 203).
+        int64_t item = item0, item_end = item0 + 1;
+        if (__builtin_expect(per > item_stride, 0)) {
+            const RecdShare share = recd_share((uint32_t)item0, (uint32_t)item_stride, (uint32_t)per);
+            item = share.first;
+            item_end = item + share.count;
+        }
+        if (item >= per)
+            return;
+        for (; item < item_end; item++) {
             const int64_t rr = first_item + item;
             if (rr >= n_runs)
                 break;
@@ -475,95 +478,17 @@ void k_segsum(const SegSumParams p)
         // 64 of skewed ids 122 / 987 -> 124 / 995; four of 32 of mean 64 and the rest of 2: 114 / 792 -> 53 / 250;
         // the first of 6 of mean 100, the rest of 2: 71 / 190 -> 30 / 72; one of 65 of mean 150, the rest of 4:
         // 131 / 414 -> 91 / 242.)
-        const int64_t first = p.list_off ? scalar_word(p.list_off) : p.list_base;
-        const int64_t end_all = p.list_off ? scalar_word(p.list_off + p.F) : p.list_base + p.F * p.lists_per_feature;
+        const int64_t first = p.list_off ? uniform64(p.list_off[0]) : p.list_base;
+        const int64_t end_all = p.list_off ? uniform64(p.list_off[p.F]) : p.list_base + p.F * p.lists_per_feature;
         const int64_t all = end_all - first;
         // neighbouring lists per turn of a wave (measured at 61 K unique lists and at 1.05 M KJT lists: 1 and 4), by the
         // true number of lists
         const int most = lb > 0 ? lb : (all >= (512 << 10) ? 4 : (all >= (128 << 10) ? 2 : 1));
         const int deal_log = is_kjt(SITE) ? p.deal_log : recd_deal_log(all, kNQ, 31 - __builtin_clz(most));
-        if constexpr (SITE != SITE_KJT_RUNS) {
-            // A wave's lists follow each other without a wait of their own: while the rows of one are gathered, the ids of the
-            // next one's first chunk and the bounds of the one after that are on their way.
-            auto list_of = [&](int64_t item) {
-                return first + (nq == 1 ? item * most : recd_dealt(item * most, q, kNQ, deal_log));
-            };
-            int64_t item = item0;
-            auto after = [&](int64_t l, int &j) {  // the wave's list after l, the j-th of its item
-                if (++j < most && l + 1 < end_all)
-                    return l + 1;
-                j = 0;
-                item += item_stride;
-                return list_of(item);
-            };
-            // where list l starts and ends, in lanes 0 and 1
-            auto load_bounds = [&](int64_t l) {
-                int64_t x = 0;
-                if (lane < 2 && l < end_all)
-                    x = lane == 1 && p.lens ? p.lens[l] : p.offsets[l + lane];
-                return x;
-            };
-            auto lane64 = [](int64_t x, int k) {
-                return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)x >> 32), k) << 32) |
-                                 (uint32_t)__builtin_amdgcn_readlane((int)(uint64_t)x, k));
-            };
-            auto end_of = [&](int64_t start, int64_t x) { return p.lens ? start + lane64(x, 1) : lane64(x, 1); };
-            auto chunk_of = [&](int64_t at, int64_t end) { return (int)(end - at < kChunk ? end - at : kChunk); };
-            int j = 0, nj = 0;
-            int64_t l = list_of(item);
-            if (l >= end_all)
-                return;
-            int64_t x = load_bounds(l);
-            nj = j;
-            int64_t nl = after(l, nj), nx = load_bounds(nl);
-            int64_t start = lane64(x, 0), end = end_of(start, x);
-            uint32_t cur = lane < chunk_of(start, end) ? (uint32_t)values[start + lane] : 0u;
-            for (;;) {
-                int f;
-                {
-                    int ln = lane;
-                    asm volatile("" : "+v"(ln));  // its addresses are made here, not kept over the gathers
-                    int64_t fo0 = INT64_MAX, fo1 = INT64_MAX;
-                    if (ln < p.F)
-                        fo0 = p.list_off ? p.list_off[ln] : p.list_base + ln * p.lists_per_feature;
-                    if (64 + ln < p.F)
-                        fo1 = p.list_off ? p.list_off[64 + ln] : p.list_base + (64 + ln) * p.lists_per_feature;
-                    f = (int)(__popcll(__ballot(fo0 <= l)) + __popcll(__ballot(fo1 <= l))) - 1;
-                }
-                const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
-                const int64_t nstart = lane64(nx, 0), nend = end_of(nstart, nx);
-                const int64_t nnl = nl < end_all ? after(nl, nj) : nl;
-                nx = load_bounds(nnl);
-                float acc[1][NACC];
-#pragma unroll
-                for (int k = 0; k < NACC; k++)
-                    acc[0][k] = pool_identity<MODE>();
-                int64_t at = start;
-                for (bool more = true; more;) {
-                    const int n = chunk_of(at, end);
-                    const int64_t base = at;
-                    at += kChunk;
-                    more = at < end;
-                    const int64_t to = more ? at : nstart;
-                    const uint32_t nxt = lane < chunk_of(to, more ? end : nend) ? (uint32_t)values[to + lane] : 0u;
-                    add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &base, &n, row_bytes, lane, g,
-                                                                        p.weights, &cur);
-                    cur = nxt;
-                }
-                fold_groups(acc[0]);
-                finish_row(l, end - start, acc[0]);
-                if (nl >= end_all)
-                    break;
-                l = nl;
-                nl = nnl;
-                start = nstart;
-                end = nend;
-            }
-            return;
-        }
-        for (int64_t i = item0;; i += item_stride) {
-            const int lpb = recd_item_lists(i, p.whole, most);
-            const int64_t t = recd_item_start(i, p.whole, most);
+        // (the number of unique lists the host knows a bound of only: recd_next_item)
+        for (int64_t i = item0; i >= 0; i = SITE == SITE_UNIQUE ? recd_next_item(i, item_stride) : i + item_stride) {
+            const int lpb = SITE == SITE_KJT_RUNS ? recd_item_lists(i, p.whole, most) : most;
+            const int64_t t = SITE == SITE_KJT_RUNS ? recd_item_start(i, p.whole, most) : i * most;
             const int64_t l0 = first + (nq == 1 ? t : recd_dealt(t, q, kNQ, deal_log));
             if (l0 >= end_all)
                 break;  // so are all later items of this block
@@ -576,10 +501,14 @@ void k_segsum(const SegSumParams p)
                     fo0 = p.list_off ? p.list_off[ln] : p.list_base + ln * p.lists_per_feature;
                 if (64 + ln < p.F)
                     fo1 = p.list_off ? p.list_off[64 + ln] : p.list_base + (64 + ln) * p.lists_per_feature;
-                if (ln < cnt) {
-                    const int64_t start = p.offsets[l0 + ln];
+                if (SITE == SITE_UNIQUE && ln < cnt) {
+                    const int64_t *ends = p.lens ? p.lens + l0 : p.offsets + l0 + 1;  // no branch: both loads are on their way
+                    const int64_t start = p.offsets[l0 + ln], end = ends[ln];
                     s_start[ln] = start;
-                    s_end[ln] = p.lens ? start + p.lens[l0 + ln] : p.offsets[l0 + ln + 1];
+                    s_end[ln] = p.lens ? start + end : end;
+                } else if (ln < cnt) {
+                    s_start[ln] = p.offsets[l0 + ln];
+                    s_end[ln] = p.offsets[l0 + ln + 1];
                 }
                 for (int j = 0; j < cnt; j++) {
                     const int f = (int)(__popcll(__ballot(fo0 <= l0 + j)) + __popcll(__ballot(fo1 <= l0 + j))) - 1;
@@ -587,6 +516,29 @@ void k_segsum(const SegSumParams p)
                         s_feat[j] = f;
                 }
                 __syncthreads();  // a block of one wave: orders the LDS accesses, nobody waits
+            }
+            if constexpr (SITE != SITE_KJT_RUNS) {
+                for (int j = 0; j < cnt; j++) {
+                    const int64_t start = uniform64(s_start[j]);
+                    const int64_t len = uniform64(s_end[j]) - start;
+                    const int f = __builtin_amdgcn_readfirstlane(s_feat[j]);
+                    const char *table = static_cast<const char *>(p.tables.p[f]) + lane_off;
+                    float acc[1][NACC];
+#pragma unroll
+                    for (int k = 0; k < NACC; k++)
+                        acc[0][k] = pool_identity<MODE>();
+                    if (len > kChunk) {
+                        walk_list(acc, table, start, start + len, kChunk, (uint32_t)values[start + lane]);
+                    } else {
+                        const int n = (int)len;
+                        add_chunks<LPR, VPL, TT, IdxT, 1, UNR, MODE, false>(acc, &table, values, &start, &n, row_bytes, lane, g,
+                                                                            p.weights);
+                    }
+                    fold_groups(acc[0]);
+                    finish_row(l0 + j, len, acc[0]);
+                }
+                __syncthreads();
+                continue;
             }
             // Neighbouring lists of a session-ordered batch are mostly the same list.  The wave brings the ids of all of
             // its lists, which lie one behind the other, into LDS, compares each list with the one before it, 64 / lpb
@@ -756,9 +708,9 @@ void k_segsum(const SegSumParams p)
 }
 
 template <int TT, int OT, typename IdxT, int SITE, int MODE = POOL_SUM>
-bool launch_shape(hipStream_t st, int blocks, int threads, int vecs, const SegSumParams &p)
+bool launch_shape(hipStream_t st, int blocks, int vecs, const SegSumParams &p)
 {
-    const dim3 grid(blocks), block(threads);
+    const dim3 grid(blocks), block(seg_threads(SITE));
     if (vecs <= 8) hipLaunchKernelGGL((k_segsum<8, 1, TT, OT, IdxT, SITE, MODE>), grid, block, 0, st, p);
     else if (vecs <= 16) hipLaunchKernelGGL((k_segsum<16, 1, TT, OT, IdxT, SITE, MODE>), grid, block, 0, st, p);
     else if (vecs <= 32) hipLaunchKernelGGL((k_segsum<32, 1, TT, OT, IdxT, SITE, MODE>), grid, block, 0, st, p);
@@ -770,18 +722,18 @@ bool launch_shape(hipStream_t st, int blocks, int threads, int vecs, const SegSu
 }
 
 template <int SITE, int MODE = POOL_SUM>
-bool launch_forward(hipStream_t st, int blocks, int threads, int v, const SegSumArgs &a, const SegSumParams &p)
+bool launch_forward(hipStream_t st, int blocks, int v, const SegSumArgs &a, const SegSumParams &p)
 {
     if (a.table_dt == RECD_F32 && a.out_dt == RECD_F32)
-        return launch_shape<RECD_F32, RECD_F32, int64_t, SITE, MODE>(st, blocks, threads, v, p);
+        return launch_shape<RECD_F32, RECD_F32, int64_t, SITE, MODE>(st, blocks, v, p);
     if (a.table_dt == RECD_F16 && a.out_dt == RECD_F16)
-        return launch_shape<RECD_F16, RECD_F16, int64_t, SITE, MODE>(st, blocks, threads, v, p);
+        return launch_shape<RECD_F16, RECD_F16, int64_t, SITE, MODE>(st, blocks, v, p);
     if (a.table_dt == RECD_F16 && a.out_dt == RECD_F32)
-        return launch_shape<RECD_F16, RECD_F32, int64_t, SITE, MODE>(st, blocks, threads, v, p);
+        return launch_shape<RECD_F16, RECD_F32, int64_t, SITE, MODE>(st, blocks, v, p);
     if (a.table_dt == RECD_BF16 && a.out_dt == RECD_BF16)
-        return launch_shape<RECD_BF16, RECD_BF16, int64_t, SITE, MODE>(st, blocks, threads, v, p);
+        return launch_shape<RECD_BF16, RECD_BF16, int64_t, SITE, MODE>(st, blocks, v, p);
     if (a.table_dt == RECD_BF16 && a.out_dt == RECD_F32)
-        return launch_shape<RECD_BF16, RECD_F32, int64_t, SITE, MODE>(st, blocks, threads, v, p);
+        return launch_shape<RECD_BF16, RECD_F32, int64_t, SITE, MODE>(st, blocks, v, p);
     return false;
 }
 
@@ -1132,29 +1084,33 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
         p.whole = recd_whole_items(most, p.nq, lb);
         nblk = (int64_t)p.nq * recd_items(most, p.whole, lb);
     }
-    // The lookup of unique lists, and of fewer than half a million runs, has at most 64 K waves, from 32 K on two to a block.
-    // Waves without a list are not free: handing one out takes 0.16 ns, in blocks of two half of that, and a bound is often
-    // several times the lists (F*B for want of a better one).  us, one wave a block and 128 K waves at most / 32 K / 64 K /
-    // two waves a block and 64 K: 22 K lists under a bound of 130 K 38.4 / 21.2 / 25.1 / 21.8, 33 K under 1.05 M 39.5 / 21.6 /
-    // 26.2 / 23.3; a bound that is the number of lists, 61 K lists of up to 256 ids 127 / 133 / 127 / 127, 131 K 174 / 191 /
-    // 176 / 176.  Runs, 16-bit rows, the first and the last of these: 33 K of 262 K at most 44.6 / 30.6, 131 K 80.5 / 79.2,
-    // 262 K 134.4 / 136.1; of 1.05 M at most 64 K 108.0 / 107.3, but 131 K of fp32 rows 180 / 188 and all of them 498 / 511.
+    // The lookup of unique lists, and of fewer than half a million runs, has half as many waves as the bound allows lists, but 32 K
+    // if there are as many and 48 K at most: waves without a list are not free (handing one out takes 0.16 ns), and a bound is often
+    // several times the lists (F*B for want of a better one).  Of more lists the first waves have several, so that the last ones
+    // are short.  An estimate of the runs below F*B is taken for good: 64 K.  us, 128 K waves and a stride / 64 K, two to a
+    // block, and a stride / now: unique lists under a bound, 256-byte rows, 30 K under 262 K 37.5 / 22.3 / 20.5, 12 K under 98 K
+    // 27.5 / 14.3 / 14.7, 8 K of 512 bytes under 65 K 21.4 / 14.8 / 12.9; runs, 32 K under 262 K 41.1 / 24.7 / 24.5, 12 K under 98 K
+    // 27.6 / 16.2 / 18.0.  A bound that is the number of lists: 61 K of 10 ids, 256 bytes, 32.4 / 35.0 / 29.8, 104 K of 3, 16-bit,
+    // 128 bytes, 67.9 / 58.0 / 55.0, 208 K of 3, 64 bytes, 88.5 / 92.3 / 83.1, 1.3 M of 4, 128 bytes, 421 / 463 / 409; 512 bytes, 64 K of
+    // 30 57.5 / 57.5 / 57.8, 128 K of 30 148 / 149 / 151, 251 K of 15 179 / 178 / 178; runs, 131 K of 30 156 / 162 / 158, 262 K of 15
+    // 202 / 210 / 203, 128 K of 3, 16-bit, 128 bytes, 64.8 / 60.6 / 62.3.  (32 K waves throughout: 18.8 under 262 K, but 157 and 164 of
+    // 128 K lists of 30.  Waves whose next list's ids are on their way with the rows of one: a feature search a list, 4 to 8
+    // registers more and a wave a SIMD less; those 421 us 463.)
     const bool bounded = a.site == RECD_SITE_UNIQUE || (a.site == RECD_SITE_UNIQUE_EXPAND && n < (512 << 10));
+    const bool good = a.site == RECD_SITE_UNIQUE_EXPAND && n < (int64_t)a.F_all * a.B;
     if (a.site == RECD_SITE_UNIQUE_EXPAND) {
         // one run per wave and turn; the kernel deals the runs to eight queues by their true number
         p.lb = 1;
         p.nq = kNQ;
         nblk = kNQ * ((n + kNQ - 1) / kNQ);
     }
-    const int64_t cap = (int64_t)ctx->num_cu * 8 * (ctx->tune_gens > 0 ? ctx->tune_gens : (bounded ? 32 : 64));
+    const int64_t gen = (int64_t)ctx->num_cu * 8, half = n / 2;
+    const int64_t fewer = half < gen * 16 ? gen * 16 : (half < gen * 24 ? half : gen * 24);
+    const int64_t cap = ctx->tune_gens > 0 ? gen * ctx->tune_gens : (!bounded ? gen * 64 : (good ? gen * 32 : fewer));
     if (nblk > cap)
         nblk = cap / kNQ * kNQ;
-    int threads = a.site == RECD_SITE_GRAD_STREAM ? 256 : 64;
-    if (bounded && nblk > (int64_t)ctx->num_cu * 128) {
-        threads = 128;
-        nblk = p.nq == 1 ? (nblk + 1) / 2 : kNQ * ((nblk / kNQ + 1) / 2);
-    }
     const int blocks = (int)nblk;
+    p.stride = p.nq == 1 ? nblk : nblk / kNQ;
     bool ok = false;
     hipStream_t st = a.stream ? a.stream : ctx->stream;
     const int v = p.vecs_per_row;
@@ -1167,30 +1123,30 @@ recd_status recd_launch_segsum(recd_ctx *ctx, const SegSumArgs &a)
     if (slot >= 0)
         recd_time_begin(ctx, slot, st);
     if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_SUM)
-        ok = launch_forward<SITE_UNIQUE>(st, blocks, threads, v, a, p);
+        ok = launch_forward<SITE_UNIQUE>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_SUM)
-        ok = runs ? launch_forward<SITE_KJT_RUNS>(st, blocks, threads, v, a, p)
-                  : launch_forward<SITE_KJT>(st, blocks, threads, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS>(st, blocks, v, a, p)
+                  : launch_forward<SITE_KJT>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE_EXPAND && fwd && a.mode == POOL_SUM && a.run_index)
-        ok = launch_forward<SITE_UNIQUE_EXPAND>(st, blocks, threads, v, a, p);
+        ok = launch_forward<SITE_UNIQUE_EXPAND>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_MEAN)
-        ok = launch_forward<SITE_UNIQUE, POOL_MEAN>(st, blocks, threads, v, a, p);
+        ok = launch_forward<SITE_UNIQUE, POOL_MEAN>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_MEAN)
-        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MEAN>(st, blocks, threads, v, a, p)
-                  : launch_forward<SITE_KJT, POOL_MEAN>(st, blocks, threads, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MEAN>(st, blocks, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_MEAN>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_MAX)
-        ok = launch_forward<SITE_UNIQUE, POOL_MAX>(st, blocks, threads, v, a, p);
+        ok = launch_forward<SITE_UNIQUE, POOL_MAX>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_MAX)
-        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MAX>(st, blocks, threads, v, a, p)
-                  : launch_forward<SITE_KJT, POOL_MAX>(st, blocks, threads, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_MAX>(st, blocks, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_MAX>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_UNIQUE && fwd && a.mode == POOL_WSUM && a.weights)
-        ok = launch_forward<SITE_UNIQUE, POOL_WSUM>(st, blocks, threads, v, a, p);
+        ok = launch_forward<SITE_UNIQUE, POOL_WSUM>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_KJT && fwd && a.mode == POOL_WSUM && a.weights)
-        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_WSUM>(st, blocks, threads, v, a, p)
-                  : launch_forward<SITE_KJT, POOL_WSUM>(st, blocks, threads, v, a, p);
+        ok = runs ? launch_forward<SITE_KJT_RUNS, POOL_WSUM>(st, blocks, v, a, p)
+                  : launch_forward<SITE_KJT, POOL_WSUM>(st, blocks, v, a, p);
     else if (a.site == RECD_SITE_GRAD_STREAM && a.values_are_i32 && a.table_dt == RECD_F32 &&
              a.out_dt == RECD_F32 && a.mode == POOL_SUM)
-        ok = launch_shape<RECD_F32, RECD_F32, int32_t, SITE_GRAD_STREAM>(st, blocks, threads, v, p);
+        ok = launch_shape<RECD_F32, RECD_F32, int32_t, SITE_GRAD_STREAM>(st, blocks, v, p);
     if (slot >= 0)
         recd_time_end(ctx, slot, st);
     if (!ok)

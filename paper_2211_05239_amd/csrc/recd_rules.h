@@ -108,6 +108,32 @@ RECD_RULE int recd_deal_log_kjt(int64_t n, int F, int queues, int lb_log)
     return log > lb_log ? log : lb_log;
 }
 
+// The items of wave w among `waves` that share n neighbouring items, which the waves find by themselves: of no more items than waves
+// one each, of more the first waves have several neighbours, no more waves than half of them, and the others one each, so that
+// the chip's last waves are short ones.  In the order of the waves, and so of time, the items follow each other.
+struct RecdShare {
+    uint32_t first, count;
+};
+RECD_RULE RecdShare recd_share(uint32_t w, uint32_t waves, uint32_t n)
+{
+    uint32_t first = w, several = 1;
+    if (n > waves) {
+        const uint32_t half = waves > 1 ? waves / 2 : 1, more = n - waves, extra = (more + half - 1) / half;
+        const uint32_t whole = (more + extra - 1) / extra;  // waves of 1 + extra items
+        several = w < whole ? 1 + extra : 1;
+        first = w < whole ? w * (1 + extra) : whole * (1 + extra) + (w - whole);
+    }
+    return RecdShare{first, first >= n ? 0 : (n - first < several ? n - first : several)};
+}
+
+// The item that a wave takes after item i, of as many as it finds, on `waves` waves whose first items are their numbers; below 0:
+// none.  The first half of the waves shares those beyond one each, for the same reason.
+RECD_RULE int64_t recd_next_item(int64_t i, int64_t waves)
+{
+    const int64_t half = waves > 1 ? waves / 2 : 1;
+    return i >= waves ? i + half : (i < half ? i + waves : -1);
+}
+
 // The t-th list of queue q.
 RECD_RULE int64_t recd_dealt(int64_t t, int q, int queues, int deal_log)
 {

@@ -58,10 +58,11 @@ def test_lists_that_differ_in_one_place(ctx, n, weighted):
         _check(gu.gpu_build(ctx, batch)[2], batch)
 
 
-@pytest.mark.parametrize("F,B,S", [(1, 32, 4), (9, 3640, 4), (9, 3641, 4), (33, 993, 1), (17, 3856, 40), (31, 17000, 64)])
+@pytest.mark.parametrize("F,B,S", [(1, 32, 4), (9, 3640, 4), (9, 3641, 4), (33, 993, 1), (17, 3856, 40), (31, 17000, 64),
+                                   (11, 9973, 1), (7, 9973, 1)])
 @pytest.mark.parametrize("slack", [0, 1, 20])
 def test_lookups_under_tight_and_loose_bounds(ctx, F, B, S, slack):
-    """One and two waves a block, lists and runs fewer and more than waves: every bound gives what each list by itself does,
+    """Lists and runs fewer than waves, more, and more than twice as many: every bound gives what each list by itself does,
     and writes no row beyond the lists."""
     D = 8
     w = synth.scaled(synth.WORKLOADS["cfg2"], F=F, B=B, rows=500, D=D, S=S, len_max=9)
@@ -112,7 +113,7 @@ def test_numbering_across_waves_and_blocks(ctx, F, B):
 @pytest.mark.parametrize("seed", range(3))
 def test_grouped_tuples_that_differ_in_one_place(recd, seed):
     """Groups of one to five features; neighbouring tuples that agree, differ in one id of one feature, or in one length; a
-    plain build between the grouped ones, which use the same tables."""
+    plain build between the grouped ones, whose tables are others."""
     rng = np.random.default_rng(seed)
     lengths = [0, 1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 64, 65, 97]
     sizes = [1, 2, 3, 4, 5, 4]

@@ -22,6 +22,24 @@ void hash_pairs(const int64_t *a, const int64_t *b, int64_t n, uint32_t t, uint6
         out32[i] = recd_hash_pair32(recd_hash_word(a[i], 0), recd_hash_word(b[i], 0), t);
     }
 }
+void share(uint32_t waves, uint32_t n, int32_t *taken, uint32_t *most)
+{
+    for (uint32_t w = 0; w < waves; w++) {
+        const RecdShare s = recd_share(w, waves, n);
+        for (uint32_t i = s.first; i < s.first + s.count; i++)
+            taken[i]++;
+        most[w >= waves / 2] = most[w >= waves / 2] < s.count ? s.count : most[w >= waves / 2];
+    }
+}
+void next_items(int64_t waves, int64_t n, int32_t *taken, uint32_t *most)
+{
+    for (int64_t w = 0; w < waves; w++) {
+        uint32_t count = 0;
+        for (int64_t i = w; i >= 0 && i < n; i = recd_next_item(i, waves), count++)
+            taken[i]++;
+        most[w >= waves / 2] = most[w >= waves / 2] < count ? count : most[w >= waves / 2];
+    }
+}
 uint32_t hash_key(uint32_t t) { return recd_hash_key(t); }
 uint32_t row_named(uint32_t row, uint32_t rows) { return recd_row_named(row, rows); }
 
@@ -284,6 +302,21 @@ def test_items_of_several_and_of_two_lists_cover_every_list_once(rules, n, F, lp
         rules.deal_items(n, F, queues, lpb, items, _ptr(lens), _ptr(work), _ptr(taken))
         assert (taken == 1).all() and items * 2 >= n // queues // lpb
         assert items <= n // queues // lpb + 8192 // min(queues, 8) + 1024 // lpb + 2
+
+
+@pytest.mark.parametrize("waves", [1, 2, 3, 7, 8, 1000, 6144])
+@pytest.mark.parametrize("n", [0, 1, 2, 3, 5, 6, 7, 8, 9, 12, 999, 1000, 1001, 1500, 1501, 2500, 6145, 9215, 9216, 9217, 40000])
+def test_waves_share_all_items(rules, waves, n):
+    """Every item goes to one wave, and of more items than waves the second half of the waves has one each at most."""
+    for share in (rules.share, rules.next_items):
+        share.restype = None
+        share.argtypes = [C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p] if share is rules.share else \
+            [C.c_int64, C.c_int64, C.c_void_p, C.c_void_p]
+        taken, most = np.zeros(n + 1, dtype=np.int32), np.zeros(2, dtype=np.uint32)
+        share(waves, n, _ptr(taken), _ptr(most))
+        assert (taken[:n] == 1).all() and taken[n] == 0
+        assert waves == 1 or most[1] <= 1
+        assert most[0] <= 2 + max(n - waves, 0) // max(waves // 2, 1)
 
 
 @pytest.mark.parametrize("n", [8, 50, 100, 300, 530, 1000, 4000, 8191, 8192, 20000, 1 << 19, (1 << 20) + 5])
