@@ -12,12 +12,12 @@ SMALL = [k for k, c in enumerate(grouping.CASES) if sum(c[0]) <= 8189 and c[1] <
 
 
 @pytest.mark.parametrize("extra", [[], [[0] * 127 + [7]], [[5] + [0] * 128, [0] * 128 + [6], [0, 3] * 150], [[2, 0, 0, 40] * 64]])
-def test_small_groupings_after_each_other(recd, extra):  # noqa: F811
-    cases = list(grouping.CASES)
-    grouping.CASES += [(ids, 9, 8, 60, True) for ids in extra]
+def test_small_groupings_after_each_other(recd, extra, monkeypatch):  # noqa: F811
+    cases = grouping.CASES + [(ids, 9, 8, 60, True) for ids in extra]
+    monkeypatch.setattr(grouping, "CASES", cases)
     ctx = recd.Context(0)
     try:
-        order = SMALL + list(range(len(cases), len(grouping.CASES)))
+        order = SMALL + list(range(len(cases) - len(extra), len(cases)))
         for k in order + order[::-1]:
             c = grouping.Batch(k)
             g = c.integers(c.F * c.B, c.D)
@@ -26,5 +26,4 @@ def test_small_groupings_after_each_other(recd, extra):  # noqa: F811
             gu, most = c.list_sums(g)
             c.check(R, gu[c.list_of], most[c.list_of])
     finally:
-        grouping.CASES[:] = cases
         ctx.close()

@@ -1,5 +1,5 @@
-"""The row sums with two pieces a lane and with four: the same bits, at rows that end within a lane's pieces and segments
-around one entry, the cut and the chunks."""
+"""The row sums with two pieces a lane and with four, plain and weighted: the same bits, at rows that end within a lane's pieces
+and segments around one entry, the cut and the chunks."""
 import numpy as np
 import pytest
 import torch
@@ -25,7 +25,8 @@ def ctx(recd):
 
 @pytest.mark.parametrize("D", [32, 36, 60, 64, 68, 100, 128, 132, 200, 256, 512, 1024])
 @pytest.mark.parametrize("cut", [16, 32, 128])
-def test_both_ways_give_the_same_bits(ctx, recd, D, cut):
+@pytest.mark.parametrize("weighted", [False, True])
+def test_both_ways_give_the_same_bits(ctx, recd, D, cut, weighted):
     """Entries a row: 1 to 130 and some thousands; the bound on the positions is the number of them, and beyond that up to
     which the rows have two pieces a lane."""
     rng = np.random.default_rng(D + cut)
@@ -43,15 +44,19 @@ def test_both_ways_give_the_same_bits(ctx, recd, D, cut):
     ctx.set_option(recd.RECD_OPT_LONG_SEGMENT_CUT, cut)
     try:
         values, offsets, ik = gu.gpu_build(ctx, batch)
+        weights = gu.to_dev(rng.standard_normal(ik.M).astype(np.float32))
         got = []
         for M_cap in (ik.M, 512 * 1024, 512 * 1024 + 1):
             tables = gu.tables_to_dev(tabs, "f32")
             state = [torch.ones(rows, device="cuda") for _ in range(F)]
             touched = torch.zeros(M_cap, dtype=torch.int64, device="cuda")
             feat_roff = torch.zeros(F + 1, dtype=torch.int64, device="cuda")
-            R = ctx.backward_dedup(F, B, gout, ik.inverse, ik.feat_uoff, ik.u_values, ik.u_offsets, [rows] * F, ik.U, M_cap,
-                                   touched, feat_roff, None, tables=tables, adagrad_state=state, lr=0.1, eps=1e-8,
-                                   want_count=True)
+            rest = ik.u_offsets, [rows] * F, ik.U, M_cap, touched, feat_roff, None
+            update = dict(tables=tables, adagrad_state=state, lr=0.1, eps=1e-8, want_count=True)
+            if weighted:
+                R = ctx.backward_dedup_weighted(F, B, gout, ik.inverse, ik.feat_uoff, ik.u_values, weights, *rest, **update)
+            else:
+                R = ctx.backward_dedup(F, B, gout, ik.inverse, ik.feat_uoff, ik.u_values, *rest, **update)
             torch.cuda.synchronize()
             got.append([touched[:R], feat_roff, *tables, *state])
     finally:
