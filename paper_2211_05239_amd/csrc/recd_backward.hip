@@ -578,8 +578,9 @@ __global__ __launch_bounds__(256) void k_segsum_rows(const RowSumParams p, const
 // alone, the ids of eight rows fetched by every lane before them, and stored a byte a lane and position: 0.3 M positions of
 // 512 bytes in 12 K lists 43.4 us, now 19.4; a lookup of the same lists takes 21.)
 // Of short lists a wave owns NL, a lane group or more each: a wave for every list left most groups idle (whole backward, us, a
-// lane group a list as it was / a wave / NL = 64 / LPR: 108 K lists of one id, rows of 64 bytes 163 / 221 / 153, 206 K of 2.5 ids
-// 208 / 317 / 196, of 256 bytes 294 / 323 / 259; 57 K of 10 ids, 64 bytes 140 / 159 / 129; 24 K of 25, 512 bytes 256 / 191 / 194).
+// lane group a list as it was / a wave / NL = 64 / LPR: 108 K lists of one id, rows of 64 bytes 164 / 221 / 153, 198 K of 3 ids
+// 204 / 308 / 194, of 256 bytes 286 / 313 / 255; 57 K of 10 ids, 64 bytes 140 / 157 / 128; 24 K of 25, 512 bytes 256 / 179 / 194).
+// With NL = 1 the list's number must not hang on the lane, or its offsets and loops leave the scalar unit (12 K lists 25 for 19).
 struct MaxTables {
     const float *w[RECD_F_PER_LAUNCH];
 };
@@ -594,7 +595,7 @@ __global__ __launch_bounds__(64) void k_max_winner(const int64_t *__restrict__ u
 {
     constexpr int W = 64 / NL, G = W / LPR, US = 8 / VPL;  // lanes and lane groups of a list; positions in flight per lane
     __shared__ uint4 s_won[kWonWords / 4];
-    const int lane = threadIdx.x, n_own = lane / W, in = lane % W, g = in / LPR, r = lane % LPR;
+    const int lane = threadIdx.x, n_own = NL > 1 ? lane / W : 0, in = NL > 1 ? lane % W : lane, g = in / LPR, r = lane % LPR;
     uint4 *const own = s_won + n_own * (kWonWords / 4 / NL);
     uint32_t *const words = reinterpret_cast<uint32_t *>(own);
     const int64_t u_lo = feat_uoff[f0];
@@ -1036,10 +1037,12 @@ RecdGroupArgs group_args(const BwdWs &w, int F, int64_t B, int64_t U_cap, int64_
     return a;
 }
 
-// Ids a list on average, by the caller's bounds, below which the lists of a max-pooled backward share waves (k_max_winner).  Whole
-// backward, us, a wave a list / shared, rows of 64 and 256 bytes: uniform lengths, 10 ids 159 / 129, 180 / 167; 25 ids 119 / 119,
-// 146 / 145; 40 ids 110 / 121, 139 / 153; Zipf's, 7 of at most 30 152 / 126, 165 / 155; 15 of at most 256 185 / 221, 219 / 264.
-constexpr int64_t kSharedMean = 12;
+// Ids a list on average, by the caller's bounds, below which the lists of a max-pooled backward share waves (k_max_winner): of
+// rows of up to 256 bytes, four lists a wave or more, and of 512 bytes, two.  Whole backward, us, a wave a list / shared: rows of
+// 64 and 256 bytes, uniform lengths, 8 ids 173 / 135, 186 / 173; 14 ids 138 / 122, 155 / 157; 25 ids 117 / 118, 137 / 145; Zipf's,
+// 7 of at most 30 152 / 126, 161 / 155, 15 of at most 256 180 / 221, 203 / 265.  Rows of 512 bytes, 1.5 ids 366 / 344, 4 ids
+// 288 / 284, 6 ids 239 / 246, 14 ids 191 / 206.
+constexpr int64_t kSharedMean = 12, kSharedMeanWide = 4;
 
 constexpr int64_t kWideRows = 512 * 1024;  // entries up to which k_segsum_rows has two pieces a lane
 
@@ -1296,7 +1299,7 @@ static recd_status backward_common(recd_ctx *ctx, bool seq, bool mean, int F, in
             const int nf = F - f0 < RECD_F_PER_LAUNCH ? F - f0 : RECD_F_PER_LAUNCH;
             for (int f = 0; f < nf; f++)
                 mt.w[f] = static_cast<const float *>(max_tables[f0 + f]);
-            const int nl = M_cap < kSharedMean * U_cap ? 64 / lpr : 1;
+            const int nl = M_cap < (lpr < 32 ? kSharedMean : kSharedMeanWide) * U_cap ? 64 / lpr : 1;
             const int64_t waves = (U_cap + nl - 1) / nl, nblk = waves < (int64_t)ctx->num_cu * 256 ? waves : (int64_t)ctx->num_cu * 256;
             const dim3 grid((unsigned)(nblk < 1 ? 1 : nblk)), block(64);
 #define RECD_MR(L, V, N)                                                                                    \

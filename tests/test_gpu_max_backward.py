@@ -96,6 +96,12 @@ def _winners(ctx, recd, batch, tabs, tight):
         at += len(rows_f)
     assert R == at and np.array_equal(grad_rows[:R].double().cpu().numpy(), np.concatenate(want))
     assert bool((grad_rows[R:] == 99.0).all())
+    return ik.M / max(ik.U, 1)
+
+
+def _shared_mean(D):
+    """The mean length below which a wave owns several lists."""
+    return 12 if D <= 64 else 4
 
 
 SHORT = [0, 1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 33, 65]
@@ -111,14 +117,15 @@ def test_short_lists_share_waves(ctx, recd, D, shared):
     feats = []
     for f in range(F):
         n_pool = (1, 2, 5, B)[f % 4]
-        lens = rng.choice(SHORT[:9], B) if shared else rng.choice(SHORT[9:], B)
+        lens = rng.choice(SHORT[:9 if D <= 64 else 5], B) if shared else rng.choice(SHORT[9:], B)
         lens[rng.integers(0, B, 3)] = rng.choice(SHORT, 3)
         pool = [rng.integers(0, rows, n).tolist() for n in lens[:n_pool]]
         feats.append([pool[b] if b < n_pool else pool[rng.integers(n_pool)] for b in range(B)])
     batch = synth.batch_from_lists(feats)
     tabs = [rng.integers(-2, 3, size=(rows, D)).astype(np.float32) for _ in range(F)]
     for tight in (True, False):
-        _winners(ctx, recd, batch, tabs, tight)
+        mean = _winners(ctx, recd, batch, tabs, tight)
+        assert (mean < _shared_mean(D)) == shared
 
 
 @pytest.mark.parametrize("D", [4, 16, 32, 64, 128, 256, 512, 1024])
@@ -145,6 +152,8 @@ def test_nan_wins_at_the_first_position_only(ctx, recd, D, short):
         lists += [[30] * n, [36] * (n - 1) + [31], [31] + [5] * (n - 1), rng.choice([30, 32, 33, 36], n).tolist()]
     if not short:   # a mean length beyond which a wave owns one list
         lists += [rng.integers(0, rows, 40).tolist() for _ in range(40)]
+    elif D > 64:
+        lists += [rng.integers(0, rows, 2).tolist() for _ in range(400)]
     batch = synth.batch_from_lists([lists, lists[::-1]])
-    assert (batch.N < 12 * batch.F * batch.B) == short
-    _winners(ctx, recd, batch, [tab, tab[::-1].copy()], True)
+    mean = _winners(ctx, recd, batch, [tab, tab[::-1].copy()], True)
+    assert (mean < _shared_mean(D)) == short
