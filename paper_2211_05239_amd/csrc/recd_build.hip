@@ -91,8 +91,9 @@ template <bool WT> struct IdPair {
 // WT: the lists carry one weight per id (wbits: their bit patterns); two lists are the same only if the weights agree too,
 // so they enter the hash and every comparison.
 // Hashing every list by two 64-bit products a pair and dividing row numbers in 64 bits took 288 vector instructions a wave of
-// 8 lists, 79 % of the issue slots; now 176, 53 % (35 M ids in 1.05 M lists 91 -> 80 us, 1.8 M in 130 K 12.8 -> 10.5).  What is
-// left is two round trips a list, a third and fourth for longer lists and run heads.  A stream of the same bytes takes 46 us.
+// 8 lists, 79 % of the issue slots; then 176, 53 %, and 178 since both words of a pair count beside their product (35 M ids in
+// 1.05 M lists 91 -> 80 us, 1.8 M in 130 K 12.8 -> 10.5).  What is left is two round trips a list, a third and fourth for longer
+// lists and run heads.  A stream of the same bytes takes 46 us.
 // Tried, no faster: predecessors out of the neighbouring lanes, two to eight lists a group, 4 lanes to a list, 32 to 96 ids
 // in flight, the offsets of later blocks fetched ahead into L2.
 template <int SG, bool WT>

@@ -19,8 +19,8 @@
 //     load).  The lookups' mapping is XCD-aware: consecutive blocks go to consecutive XCDs, and block b
 //     serves every eighth stretch of neighbouring lists from the (b mod 8)-th on, so that lists that share
 //     rows meet in one XCD's L2 and features of unequal mean length load the XCDs alike.  The number of lists may live on the device only (unique lists): the grid is
-//     sized from a host-side bound and every block strides until its queue is exhausted, so any grid
-//     size is correct.
+//     sized from a host-side bound, and blocks that are fewer than the lists take the others too, so any
+//     grid size is correct.
 #include "recd_internal.h"
 
 #include <hip/hip_fp16.h>
